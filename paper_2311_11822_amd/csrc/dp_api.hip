@@ -148,13 +148,27 @@ dp_status norms_impl(const dp_layer* layers, int L, dp_dtype dt, int B, float* s
                                 : (__int128)ly.T * ly.d_in * ly.d_out;
       if (work > kF32MaxWork) return DP_ERR_UNSUPPORTED;
     }
-    for (int l = 0; l < L; ++l) {
-      const dp_layer& ly = layers[l];
-      const float* a = static_cast<const float*>(ly.a);
-      const float* g = static_cast<const float*>(ly.g);
-      float* out = sqnorm_out + (size_t)(row_of ? row_of[l] : l) * B;
-      dp_status st = ly.path == DP_PATH_GHOST ? launch_ghost_f32(a, g, B, ly.T, ly.d_in, ly.d_out, out, s)
-                                              : launch_perex_f32(a, g, B, ly.T, ly.d_in, ly.d_out, out, s);
+    const int per_launch = std::max(1, std::min(kMaxGroup, INT32_MAX / 2 / B));
+    for (int l0 = 0; l0 < L; l0 += per_launch) {
+      GroupArgs ga;
+      ga.B = B;
+      ga.accumulate = 0;
+      ga.f16 = 0;
+      ga.n_layers = std::min(per_launch, L - l0);
+      for (int j = 0; j < ga.n_layers; ++j) {
+        const dp_layer& ly = layers[l0 + j];
+        GroupLayer& gl = ga.layer[j];
+        gl = {};
+        gl.a = ly.a;
+        gl.g = ly.g;
+        gl.T = ly.T;
+        gl.d_in = ly.d_in;
+        gl.d_out = ly.d_out;
+        gl.path = ly.path;
+        gl.sq_index = row_of ? row_of[l0 + j] : l0 + j;
+      }
+      ga.total_blocks = ga.n_layers * B;
+      dp_status st = launch_norms_f32_group(ga, sqnorm_out, s);
       if (st != DP_OK) return st;
     }
     return DP_OK;
@@ -275,6 +289,16 @@ struct NoiseSpec {
   uint64_t seed, step;
 };
 
+// Everything of a kernel's noise arguments but the layers' offsets.
+void set_noise(NoiseArgs& na, const NoiseSpec& noise) {
+  na.stddev = noise.stddev;
+  na.step_lo = (uint32_t)noise.step;
+  na.step_hi = (uint32_t)(noise.step >> 32);
+  na.lo = noise.lo;
+  na.hi = noise.hi;
+  na.rk = make_round_keys(noise.seed);
+}
+
 // Separate noise pass on the part of layer l's gradient that lies inside the range.
 dp_status noise_after(const NoiseSpec* noise, int l, const dp_layer& ly, float* grad, hipStream_t s) {
   if (!noise) return DP_OK;
@@ -310,13 +334,37 @@ dp_status clipped_grad_impl(const dp_layer* layers, int L, dp_dtype dt, int B, c
     }
   }
   if (dt == DP_F32) {
-    for (int l = 0; l < L; ++l) {
-      dp_status st = launch_clipped_grad_f32(static_cast<const float*>(layers[l].a),
-                                             static_cast<const float*>(layers[l].g), B, layers[l].T,
-                                             layers[l].d_in, layers[l].d_out, C + (c_off ? c_off[l] : 0),
-                                             grads[l], accumulate, s);
-      if (st != DP_OK) return st;
-      st = noise_after(noise, l, layers[l], grads[l], s);
+    NoiseArgs na = {};
+    if (noise) set_noise(na, *noise);
+    int l = 0;
+    while (l < L) {
+      GroupArgs ga;
+      ga.B = B;
+      ga.accumulate = accumulate;
+      ga.f16 = 0;
+      ga.n_layers = 0;
+      int64_t blocks = 0;
+      for (; l < L && ga.n_layers < kMaxGroup; ++l) {
+        const int64_t tiles = clipped_grad_f32_tiles(layers[l].d_in, layers[l].d_out);
+        if (blocks + tiles > INT32_MAX / 2) {
+          if (ga.n_layers == 0) return DP_ERR_INVALID_ARG;          // one layer beyond the grid's range
+          break;
+        }
+        if (noise) na.layer_off[ga.n_layers] = noise->grad_offset[l];
+        GroupLayer& gl = ga.layer[ga.n_layers++];
+        gl = {};
+        gl.a = layers[l].a;
+        gl.g = layers[l].g;
+        gl.out = grads[l];
+        gl.T = layers[l].T;
+        gl.d_in = layers[l].d_in;
+        gl.d_out = layers[l].d_out;
+        gl.tile_begin = (int)blocks;
+        gl.c_off = c_off ? c_off[l] : 0;
+        blocks += tiles;
+      }
+      ga.total_blocks = (int)blocks;
+      dp_status st = launch_clipped_grad_f32_group(ga, C, na, s);
       if (st != DP_OK) return st;
     }
     return DP_OK;
@@ -372,14 +420,7 @@ dp_status clipped_grad_impl(const dp_layer* layers, int L, dp_dtype dt, int B, c
           fused = fused && (na.layer_off[j] & 3) == 0;
         }
       }
-      if (fused) {
-        na.stddev = noise->stddev;
-        na.step_lo = (uint32_t)noise->step;
-        na.step_hi = (uint32_t)(noise->step >> 32);
-        na.lo = noise->lo;
-        na.hi = noise->hi;
-        na.rk = make_round_keys(noise->seed);
-      }
+      if (fused) set_noise(na, *noise);
       dp_status st = pass == 0 ? launch_clipped_grad_big_group(ga, C, fused ? &na : nullptr, s, out16)
                                : launch_clipped_grad_group(ga, C, s);
       if (st != DP_OK) return st;
@@ -404,14 +445,7 @@ dp_status kept_sum_impl(const dp_layer* layers, int L, int B, const float* C, co
                         hipStream_t s) {
   const bool noisy = noise != nullptr && noise->stddev > 0.f;
   NoiseArgs na = {};
-  if (noisy) {
-    na.stddev = noise->stddev;
-    na.step_lo = (uint32_t)noise->step;
-    na.step_hi = (uint32_t)(noise->step >> 32);
-    na.lo = noise->lo;
-    na.hi = noise->hi;
-    na.rk = make_round_keys(noise->seed);
-  }
+  if (noisy) set_noise(na, *noise);
   int l = 0;
   while (l < L) {
     GroupArgs ga;

@@ -82,9 +82,9 @@ __device__ __forceinline__ int layer_of(const GroupArgs& ga, int id) {
   return lo;
 }
 
-// The fp32 norm kernels run one workgroup per sample on the vector ALUs; layers whose norm needs
-// more multiply-adds per sample than this are refused (DP_ERR_UNSUPPORTED) instead of running
-// for seconds.  2^28 multiply-adds take a few tens of milliseconds.
+// The fp32 norm kernel runs one workgroup per (layer, sample); layers whose norm needs more
+// multiply-adds per sample than this are refused (DP_ERR_UNSUPPORTED) instead of holding one
+// compute unit for long.
 constexpr int64_t kF32MaxWork = (int64_t)1 << 28;
 
 inline dp_status hip_status(hipError_t e) { return e == hipSuccess ? DP_OK : DP_ERR_HIP; }
@@ -121,12 +121,12 @@ dp_status launch_bias_norm(const void* g, dp_dtype dt, int B, int T, int p, floa
 dp_status launch_clipped_bias_grad(const float* colsum, int B, int p, const float* C, float* grad_b,
                                    int accumulate, hipStream_t s);
 
-dp_status launch_ghost_f32(const float* a, const float* g, int B, int T, int d, int p, float* out,
-                           hipStream_t s);
-dp_status launch_perex_f32(const float* a, const float* g, int B, int T, int d, int p, float* out,
-                           hipStream_t s);
-dp_status launch_clipped_grad_f32(const float* a, const float* g, int B, int T, int d, int p,
-                                  const float* C, float* grad, int accumulate, hipStream_t s);
+// fp32 kernels (fp32_kernels.hip), grouped over layers.  Norms: ga.layer[j].path selects the form, one
+// workgroup per (layer, sample).  Gradients: tile_begin = first workgroup (clipped_grad_f32_tiles per layer),
+// c_off; na.stddev == 0: no noise.
+int64_t clipped_grad_f32_tiles(int d, int p);
+dp_status launch_norms_f32_group(const GroupArgs& ga, float* sqnorm, hipStream_t s);
+dp_status launch_clipped_grad_f32_group(const GroupArgs& ga, const float* C, const NoiseArgs& na, hipStream_t s);
 
 // bf16 MFMA kernels, grouped over layers.
 int ghost_tiles_per_sample(int T);

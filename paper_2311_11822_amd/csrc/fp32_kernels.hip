@@ -1,108 +1,299 @@
-// fp32-input forms of the three contractions, for small layers (the tiny all-fp32
-// configuration).  Plain vector-ALU code: these shapes are launch-latency bound, so there
-// is nothing for the matrix cores to win.  Reductions run in a fixed order (no atomics).
-// The norm kernels run one workgroup per sample, so they are meant for layers of a few
-// thousand elements; the host side refuses fp32 layers beyond kF32MaxWork multiply-adds per
-// sample (DP_ERR_UNSUPPORTED) rather than run for seconds.
+// fp32-input forms of the three contractions, grouped over layers: one launch for the norms of a
+// stack and one for its gradients (+ noise).  fp32 layers are small (a few thousand weights), so
+// what bounds them is latency: launches, and the serial chain of a workgroup.  Products run on the
+// fp32 matrix cores (v_mfma_f32_32x32x2_f32: fp32 operands and sums, 64 clocks for 32 x 32 x 2), whose
+// operands come straight from global memory: one register per lane holds 32 consecutive columns
+// of two token rows (TN products), or a quarter of a float4 of 32 token rows (NT products), so no LDS
+// staging and no barrier sits in the loops.  The eight waves of a workgroup split the contraction (or
+// the tiles) and meet once, in LDS, in a fixed order: no atomics, the same bits every time.
+// Measured on eight layers of width 64..256 (B = 16, T = 48): one thread per output and one launch per
+// layer took 2904 us a step (182 us per gradient, 174 us per norm); this form 31 us: three launches.
+#include <algorithm>
+
 #include "dp_internal.h"
 
 namespace dpbk {
 
 namespace {
 
-constexpr int kThreads = 256;
+typedef __attribute__((ext_vector_type(4))) float f32x4v;
+constexpr int kWaves = 8, kThreads = 64 * kWaves;
+constexpr int kTile = 32;                        // output tile edge = MFMA edge
+constexpr int kChunk = 16;                       // token rows per work item: 8 MFMAs
 
-// Sum over the workgroup in a fixed order; result valid in thread 0.
-__device__ float block_sum(float v) {
-  __shared__ float red[kThreads];
-  red[threadIdx.x] = v;
+__device__ __forceinline__ f32x16 mfma32(float a, float b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x16 zero16() {
+  f32x16 z;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) z[r] = 0.f;
+  return z;
+}
+
+// Sum over the workgroup in a fixed order; every thread calls it, the result is valid in thread 0.
+__device__ __forceinline__ float block_sum(float v, float* red) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  __syncthreads();                               // earlier readers of `red` are done
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int w = kThreads / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  return red[0];
+  float s = 0.f;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) s += red[w];
+  return s;
 }
 
-// Ghost norm (appendix A.1): sum over token pairs of (a_t . a_t')(g_t . g_t'); one workgroup per sample.
-__global__ void __launch_bounds__(kThreads)
-ghost_f32_kernel(const float* __restrict__ a, const float* __restrict__ g, int T, int d, int p,
-                 float* __restrict__ out) {
-  const int i = blockIdx.x;
-  const float* ai = a + (size_t)i * T * d;
-  const float* gi = g + (size_t)i * T * p;
-  float acc = 0.f;
-  const long pairs = (long)T * T;
-  for (long q = threadIdx.x; q < pairs; q += kThreads) {
-    const int t = (int)(q / T), u = (int)(q % T);
-    if (u < t) continue;                       // Gram matrices are symmetric
-    float da = 0.f, dg = 0.f;
-    for (int k = 0; k < d; ++k) da = fmaf(ai[(size_t)t * d + k], ai[(size_t)u * d + k], da);
-    for (int k = 0; k < p; ++k) dg = fmaf(gi[(size_t)t * p + k], gi[(size_t)u * p + k], dg);
-    acc += (u == t ? 1.f : 2.f) * da * dg;
+// Four consecutive elements k .. k + 3 of a row of `width`, zeros past its end.  VEC: width is a
+// multiple of 4 (rows are then 16-byte aligned).
+template <bool VEC>
+__device__ __forceinline__ f32x4v load4(const float* row, int k, int width) {
+  f32x4v v = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (VEC) {
+    if (k < width) v = *reinterpret_cast<const f32x4v*>(row + k);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (k + e < width) v[e] = row[k + e];
   }
-  const float total = block_sum(acc);
-  if (threadIdx.x == 0) out[i] = total;
+  return v;
 }
 
-// Instantiated norm (appendix A.1): || a_i^T g_i ||_F^2; one workgroup per sample.
+// This wave's part of the 32 x 32 tile (t0, u0) of x x^T: the k's of every kWaves-th group of 8.
+// The order of the k's inside an MFMA is free as long as both operands share it.
+template <bool VEC>
+__device__ __forceinline__ f32x16 gram_part(const float* x, int T, int width, int t0, int u0, int wave, int lane) {
+  f32x16 acc = zero16();
+  const bool same = t0 == u0;
+  const int t = t0 + (lane & 31), u = u0 + (lane & 31);
+  const float* rt = x + (size_t)min(t, T - 1) * width;
+  const float* ru = x + (size_t)min(u, T - 1) * width;
+  const int wt = t < T ? width : 0, wu = u < T ? width : 0;          // rows past the sample: zeros
+  for (int k0 = wave * 8; k0 < width; k0 += 4 * kWaves * 8) {
+    f32x4v a[4], b[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = k0 + q * kWaves * 8 + 4 * (lane >> 5);
+      a[q] = load4<VEC>(rt, k, wt);
+      b[q] = same ? a[q] : load4<VEC>(ru, k, wu);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = mfma32(a[q][e], b[q][e], acc);
+  }
+  return acc;
+}
+
+__device__ __forceinline__ f32x16 gram_part(const float* x, int T, int width, int t0, int u0, int wave, int lane) {
+  return (width & 3) ? gram_part<false>(x, T, width, t0, u0, wave, lane)
+                     : gram_part<true>(x, T, width, t0, u0, wave, lane);
+}
+
+// Operands of one work item of a TN product: rows [t0, t0 + kChunk) of a and g (already offset to
+// the sample), columns j of a and k of g per lane; two rows per register, zeros outside.
+struct TnItem {
+  float a[kChunk / 2], g[kChunk / 2];
+};
+__device__ __forceinline__ void load_item(TnItem& it, const float* a, const float* g, int t0, int T, int d, int p,
+                                          int j, int k, int lane) {
+#pragma unroll
+  for (int q = 0; q < kChunk / 2; ++q) {
+    const int t = t0 + 2 * q + (lane >> 5);
+    it.a[q] = t < T && j < d ? a[(size_t)t * d + j] : 0.f;
+    it.g[q] = t < T && k < p ? g[(size_t)t * p + k] : 0.f;
+  }
+}
+// The g operand first: lane l then holds row l & 31 of the tile and runs of four consecutive
+// columns, 8 q + 4 (l >> 5) + e in register 4 q + e.
+__device__ __forceinline__ f32x16 mul_item(const TnItem& it, f32x16 acc) {
+#pragma unroll
+  for (int q = 0; q < kChunk / 2; ++q) acc = mfma32(it.g[q], it.a[q], acc);
+  return acc;
+}
+
+// Squared per-sample norms, one workgroup per (layer, sample), by the layer's path (appendix A.1):
+// ghost: sum over token pairs of (a_t . a_u)(g_t . g_u), tile pairs on and above the diagonal;
+// instantiated: || a_i^T g_i ||_F^2.
 __global__ void __launch_bounds__(kThreads)
-perex_f32_kernel(const float* __restrict__ a, const float* __restrict__ g, int T, int d, int p,
-                 float* __restrict__ out) {
-  const int i = blockIdx.x;
-  const float* ai = a + (size_t)i * T * d;
-  const float* gi = g + (size_t)i * T * p;
-  float acc = 0.f;
-  const long cells = (long)d * p;
-  for (long q = threadIdx.x; q < cells; q += kThreads) {
-    const int j = (int)(q / p), k = (int)(q % p);
+norms_f32_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
+  __shared__ float part_a[kWaves][16][64], part_g[kWaves][16][64];   // 64 KiB
+  const int l = blockIdx.x / ga.B, i = blockIdx.x - l * ga.B;
+  const GroupLayer& ly = ga.layer[l];
+  const int T = ly.T, d = ly.d_in, p = ly.d_out;
+  const float* a = static_cast<const float*>(ly.a) + (size_t)i * T * d;
+  const float* g = static_cast<const float*>(ly.g) + (size_t)i * T * p;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  float sum = 0.f;
+  auto put = [&](float (*part)[16][64], const f32x16& acc) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part[wave][r][lane] = acc[r];
+  };
+  auto total = [&](float (*part)[16][64], int e) {      // element e of the tile over the waves
     float s = 0.f;
-    for (int t = 0; t < T; ++t) s = fmaf(ai[(size_t)t * d + j], gi[(size_t)t * p + k], s);
-    acc = fmaf(s, s, acc);
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) s += part[w][e >> 6][e & 63];
+    return s;
+  };
+
+  if (ly.path == DP_PATH_GHOST) {
+    for (int t0 = 0; t0 < T; t0 += kTile)
+      for (int u0 = t0; u0 < T; u0 += kTile) {
+        const f32x16 xa = gram_part(a, T, d, t0, u0, wave, lane);
+        const f32x16 xg = gram_part(g, T, p, t0, u0, wave, lane);
+        put(part_a, xa);
+        put(part_g, xg);
+        __syncthreads();
+        float s = 0.f;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) s = fmaf(total(part_a, tid + h * kThreads), total(part_g, tid + h * kThreads), s);
+        sum += t0 == u0 ? s : 2.f * s;
+        __syncthreads();
+      }
+  } else {
+    const int tn = (p + kTile - 1) / kTile, tiles = ((d + kTile - 1) / kTile) * tn;
+    const int items = (T + kChunk - 1) / kChunk;
+    const bool split = tiles < kWaves;                   // few tiles: the waves share each one's tokens
+    for (int tile = split ? 0 : wave; tile < tiles; tile += split ? 1 : kWaves) {
+      const int j = (tile / tn) * kTile + (lane & 31), k = (tile % tn) * kTile + (lane & 31);
+      f32x16 acc = zero16();
+      for (int c = split ? wave : 0; c < items; c += split ? kWaves : 1) {
+        TnItem it;
+        load_item(it, a, g, c * kChunk, T, d, p, j, k, lane);
+        acc = mul_item(it, acc);
+      }
+      if (split) {
+        put(part_a, acc);
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const float v = total(part_a, tid + h * kThreads);
+          sum = fmaf(v, v, sum);
+        }
+        __syncthreads();
+      } else {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum = fmaf(acc[r], acc[r], sum);
+      }
+    }
   }
-  const float total = block_sum(acc);
-  if (threadIdx.x == 0) out[i] = total;
+  const float s = block_sum(sum, &part_g[0][0][0]);
+  if (tid == 0) sqnorm[(size_t)ly.sq_index * ga.B + i] = s;
 }
 
-// Clip-weighted gradient (section 3): grad[j,k] = sum_i C_i sum_t a[i,t,j] g[i,t,k].
+// Clip-weighted gradient (section 3): grad[j,k] = sum_i C_i sum_t a[i,t,j] g[i,t,k] (+ noise, eq. (1)).
+// One workgroup per 32 x 32 tile; its waves take contiguous runs of the (sample, 16 tokens) items.
+// An item's product is formed unweighted and folded in as total += C_i * item; a sample with
+// C_i == 0 is not read, as in the 16-bit kernels.
 __global__ void __launch_bounds__(kThreads)
-clipped_grad_f32_kernel(const float* __restrict__ a, const float* __restrict__ g, int B, int T,
-                        int d, int p, const float* __restrict__ C, float* __restrict__ grad,
-                        int accumulate) {
-  const long q = (long)blockIdx.x * kThreads + threadIdx.x;
-  if (q >= (long)d * p) return;
-  const int j = (int)(q / p), k = (int)(q % p);
-  float total = 0.f;
-  for (int i = 0; i < B; ++i) {
-    if (C[i] == 0.f) continue;                 // a masked sample is not read, as in the 16-bit kernels
-    const float* ai = a + (size_t)i * T * d;
-    const float* gi = g + (size_t)i * T * p;
-    float s = 0.f;
-    for (int t = 0; t < T; ++t) s = fmaf(ai[(size_t)t * d + j], gi[(size_t)t * p + k], s);
-    total = fmaf(C[i], s, total);
+clipped_grad_f32_kernel(const GroupArgs ga, const float* __restrict__ C_all, const NoiseArgs na) {
+  __shared__ float part[kWaves][16][64];                 // 32 KiB
+  const int l = layer_of(ga, blockIdx.x);
+  const GroupLayer& ly = ga.layer[l];
+  const int T = ly.T, d = ly.d_in, p = ly.d_out;
+  const int tile = blockIdx.x - ly.tile_begin, tn = (p + kTile - 1) / kTile;
+  const int m0 = (tile / tn) * kTile, n0 = (tile % tn) * kTile;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float* a = static_cast<const float*>(ly.a);
+  const float* g = static_cast<const float*>(ly.g);
+  const float* __restrict__ C = C_all + ly.c_off;
+  const int j = m0 + (lane & 31), k = n0 + (lane & 31);
+
+  const int per_sample = (T + kChunk - 1) / kChunk;
+  const int64_t items = (int64_t)ga.B * per_sample;
+  const int64_t begin = items * wave / kWaves, end = items * (wave + 1) / kWaves;
+  int i = (int)(begin / per_sample), c = (int)(begin - (int64_t)i * per_sample);
+  f32x16 sum = zero16();
+  TnItem cur, next;
+  float wc = 0.f, wn = 0.f;
+  auto fetch = [&](TnItem& it, float& w) {               // item (i, c), then step to the next one
+    w = C[i];
+    if (w != 0.f)
+      load_item(it, a + (size_t)i * T * d, g + (size_t)i * T * p, c * kChunk, T, d, p, j, k, lane);
+    if (++c == per_sample) {
+      c = 0;
+      ++i;
+    }
+  };
+  if (begin < end) fetch(cur, wc);
+  for (int64_t n = begin; n < end; ++n) {
+    if (n + 1 < end) fetch(next, wn);
+    if (wc != 0.f) {
+      const f32x16 acc = mul_item(cur, zero16());
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sum[r] = fmaf(wc, acc[r], sum[r]);
+    }
+    cur = next;
+    wc = wn;
   }
-  grad[q] = accumulate ? grad[q] + total : total;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) part[wave][r][lane] = sum[r];
+  __syncthreads();
+  if (tid >= 256) return;
+  // thread: one run of four consecutive columns (register group q of lane `lane`)
+  const int q = tid >> 6;
+  const int row = m0 + (lane & 31), col = n0 + 8 * q + 4 * (lane >> 5);
+  if (row >= d || col >= p) return;
+  const int n = min(4, p - col);
+  float v[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    v[e] = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) v[e] += part[w][4 * q + e][lane];
+  }
+  float* out = ly.out + (size_t)row * p + col;
+  if (ga.accumulate) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < n) v[e] = out[e] + v[e];
+  }
+  if (na.stddev != 0.f) {
+    const uint64_t idx = na.layer_off[l] + (uint64_t)row * p + col;
+    if (idx + n > na.lo && idx < na.hi) {
+      if ((idx & 3) == 0) {
+        float z[4];
+        normal_block(idx >> 2, na.step_lo, na.step_hi, na.rk, z);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (idx + e >= na.lo && idx + e < na.hi) v[e] = fmaf(na.stddev, z[e], v[e]);
+      } else {                                           // the run straddles generator blocks
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (idx + e >= na.lo && idx + e < na.hi) {
+            float z[4];
+            normal_block((idx + e) >> 2, na.step_lo, na.step_hi, na.rk, z);
+            const int s = (int)((idx + e) & 3);
+            v[e] = fmaf(na.stddev, s == 0 ? z[0] : s == 1 ? z[1] : s == 2 ? z[2] : z[3], v[e]);
+          }
+      }
+    }
+  }
+  if ((p & 3) == 0) {
+    *reinterpret_cast<f32x4v*>(out) = f32x4v{v[0], v[1], v[2], v[3]};
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < n) out[e] = v[e];
+  }
 }
 
 }  // namespace
 
-dp_status launch_ghost_f32(const float* a, const float* g, int B, int T, int d, int p, float* out,
-                           hipStream_t s) {
-  hipLaunchKernelGGL(ghost_f32_kernel, dim3(B), dim3(kThreads), 0, s, a, g, T, d, p, out);
+int64_t clipped_grad_f32_tiles(int d, int p) {
+  return (((int64_t)d + kTile - 1) / kTile) * (((int64_t)p + kTile - 1) / kTile);
+}
+
+dp_status launch_norms_f32_group(const GroupArgs& ga, float* sqnorm, hipStream_t s) {
+  hipLaunchKernelGGL(norms_f32_kernel, dim3((unsigned)ga.n_layers * ga.B), dim3(kThreads), 0, s, ga, sqnorm);
   return hip_status(hipGetLastError());
 }
 
-dp_status launch_perex_f32(const float* a, const float* g, int B, int T, int d, int p, float* out,
-                           hipStream_t s) {
-  hipLaunchKernelGGL(perex_f32_kernel, dim3(B), dim3(kThreads), 0, s, a, g, T, d, p, out);
-  return hip_status(hipGetLastError());
-}
-
-dp_status launch_clipped_grad_f32(const float* a, const float* g, int B, int T, int d, int p,
-                                  const float* C, float* grad, int accumulate, hipStream_t s) {
-  const long cells = (long)d * p;
-  hipLaunchKernelGGL(clipped_grad_f32_kernel, dim3((unsigned)((cells + kThreads - 1) / kThreads)),
-                     dim3(kThreads), 0, s, a, g, B, T, d, p, C, grad, accumulate);
+dp_status launch_clipped_grad_f32_group(const GroupArgs& ga, const float* C, const NoiseArgs& na, hipStream_t s) {
+  hipLaunchKernelGGL(clipped_grad_f32_kernel, dim3(ga.total_blocks), dim3(kThreads), 0, s, ga, C, na);
   return hip_status(hipGetLastError());
 }
 
