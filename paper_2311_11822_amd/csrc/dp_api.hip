@@ -308,6 +308,24 @@ dp_status noise_after(const NoiseSpec* noise, int l, const dp_layer& ly, float* 
   return launch_noise(grad + (lo - begin), lo, hi - lo, noise->stddev, noise->seed, noise->step, s);
 }
 
+// Which gradient kernel a 16-bit layer takes.
+//  kGradPacked: layers narrower than half a large tile (its 256 x 256 would be mostly padding), and samples
+//    of less than kPackedTokens: the large-tile kernel spends ~1400 clocks per 32 tokens and ~4400 per
+//    sample boundary, the packed one three (fp16: six) times the matrix instructions and nothing
+//    per sample.
+//  kGradBig: whole 32-token k-blocks and slabs its 32-bit addressing reaches.
+//  kGradEdge: the rest.
+enum GradKernel { kGradBig = 0, kGradPacked = 1, kGradEdge = 2 };
+constexpr int kGradKernels = 3;
+constexpr int kPackedTokens = 48, kPackedTokensF16 = 12;
+
+GradKernel grad_kernel_of(const dp_layer& ly, dp_dtype dt, int B) {
+  const bool narrow = ly.d_in < 128 || ly.d_out < 128;
+  const bool brief = ly.T < (dt == DP_F16 ? kPackedTokensF16 : kPackedTokens);
+  if ((narrow || brief) && grad_packed_supports(B, ly.T, ly.d_in, ly.d_out)) return kGradPacked;
+  return !narrow && clipped_grad_big_supports(ly.T, ly.d_in, ly.d_out) ? kGradBig : kGradEdge;
+}
+
 // out16: grads[l] address 16-bit arrays of the operands' storage type; only the large-tile kernels
 // write those, with the noise in their epilogue, so every layer must qualify for them.
 dp_status clipped_grad_impl(const dp_layer* layers, int L, dp_dtype dt, int B, const float* C,
@@ -369,16 +387,10 @@ dp_status clipped_grad_impl(const dp_layer* layers, int L, dp_dtype dt, int B, c
     }
     return DP_OK;
   }
-  // Layers wide enough to fill 256x256 tiles take the large-tile kernel; the rest (and slabs
-  // beyond its 32-bit addressing) take the 8-wave kernel with per-element edge handling.
-  std::vector<int> big, small;
-  for (int l = 0; l < L; ++l) {
-    const dp_layer& ly = layers[l];
-    const bool use_big = ly.d_in >= 128 && ly.d_out >= 128 && clipped_grad_big_supports(ly.T, ly.d_in, ly.d_out);
-    (use_big ? big : small).push_back(l);
-  }
-  for (int pass = 0; pass < 2; ++pass) {
-    const std::vector<int>& which = pass == 0 ? big : small;
+  std::vector<int> of_kernel[kGradKernels];
+  for (int l = 0; l < L; ++l) of_kernel[grad_kernel_of(layers[l], dt, B)].push_back(l);
+  for (int kernel = 0; kernel < kGradKernels; ++kernel) {
+    const std::vector<int>& which = of_kernel[kernel];
     size_t pos = 0;
     while (pos < which.size()) {
       GroupArgs ga;
@@ -389,17 +401,19 @@ dp_status clipped_grad_impl(const dp_layer* layers, int L, dp_dtype dt, int B, c
       int64_t blocks = 0;
       while (pos < which.size() && ga.n_layers < kMaxGroup) {
         const int l = which[pos];
-        const int64_t tiles = pass == 0 ? clipped_grad_big_tiles(layers[l].d_in, layers[l].d_out)
-                                        : clipped_grad_tiles(layers[l].d_in, layers[l].d_out);
+        const int d = layers[l].d_in, p = layers[l].d_out;
+        const int64_t tiles = kernel == kGradBig      ? clipped_grad_big_tiles(d, p)
+                              : kernel == kGradPacked ? grad_packed_tiles(d, p)
+                                                      : clipped_grad_tiles(d, p);
         if (ga.n_layers > 0 && blocks + tiles > INT32_MAX / 2) break;
         GroupLayer& gl = ga.layer[ga.n_layers++];
         gl.a = layers[l].a;
         gl.g = layers[l].g;
         gl.out = grads[l];
         gl.T = layers[l].T;
-        gl.d_in = layers[l].d_in;
-        gl.d_out = layers[l].d_out;
-        gl.path = 0;
+        gl.d_in = d;
+        gl.d_out = p;
+        gl.path = kernel == kGradPacked ? grad_packed_shape(d, p) : 0;
         gl.tile_begin = (int)blocks;
         gl.sq_index = l;
         gl.part_begin = 0;
@@ -409,10 +423,10 @@ dp_status clipped_grad_impl(const dp_layer* layers, int L, dp_dtype dt, int B, c
         ++pos;
       }
       ga.total_blocks = (int)blocks;
-      // The large-tile kernels add the noise in their epilogue when every layer of the launch
-      // starts on a generator block (offset a multiple of 4); otherwise, and for the small-layer
-      // kernel, the noise pass runs on the layer's slice afterwards.
-      bool fused = noise && pass == 0;
+      // The kernels add the noise in their epilogue when every layer of the launch starts on a
+      // generator block (offset a multiple of 4); otherwise, and for the 64-bit fallback, the noise
+      // pass runs on the layer's slice afterwards.
+      bool fused = noise && kernel != kGradEdge;
       NoiseArgs na;
       if (fused) {
         for (int j = 0; j < ga.n_layers; ++j) {
@@ -421,8 +435,10 @@ dp_status clipped_grad_impl(const dp_layer* layers, int L, dp_dtype dt, int B, c
         }
       }
       if (fused) set_noise(na, *noise);
-      dp_status st = pass == 0 ? launch_clipped_grad_big_group(ga, C, fused ? &na : nullptr, s, out16)
-                               : launch_clipped_grad_group(ga, C, s);
+      const NoiseArgs* in_kernel = fused ? &na : nullptr;
+      dp_status st = kernel == kGradBig      ? launch_clipped_grad_big_group(ga, C, in_kernel, s, out16)
+                     : kernel == kGradPacked ? launch_grad_packed_group(ga, C, in_kernel, s, out16)
+                                             : launch_clipped_grad_group(ga, C, s);
       if (st != DP_OK) return st;
       if (noise && !fused) {
         for (int j = 0; j < ga.n_layers; ++j) {

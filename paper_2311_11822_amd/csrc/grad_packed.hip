@@ -1,0 +1,406 @@
+// Clip-weighted gradient over packed token rows (section 3 of the paper, "DP gradient"), for short
+// samples and for narrow layers:   grad[j,k] = sum_r C_{r / T} a[r,j] g[r,k],   r = 0 .. B T - 1.
+//
+// The kernels that keep the weights out of the operands (grad_gemm.hip, tn_tile.h) re-express
+// their accumulator at every sample boundary and pad every sample to whole 32-row k-blocks: about four
+// k-blocks' time per sample plus the padding, which at T = 1 is all they do.  Here the rows of all
+// samples form one contraction of B T rows and the weight is multiplied into the a operand in fp32;
+// that product is then cut into three bfloat16 parts, whose sum is within 2^-25 of the product, so each
+// 16-row step takes three matrix instructions and less is lost than by rounding C a to fp32.  fp16
+// operands: g (11 bits) is cut into two bfloat16 parts exactly, six instructions.  Gradients measured
+// against 64 bits: 1.7e-7 (T = 1, B = 512), 2.1e-7 (T = 31) here, 6.0e-7 and 3.9e-7 in the large-tile kernel.
+//   Measured, eight layers of 1024 x 1024 .. 4096 outputs, bf16: B = 512, T = 1: 1384 us before, 86 us here;
+// 4096 rows: 560 us here whatever T is (what bounds it: the matrix cores at the clock they hold under
+// load, then the cutting), the large-tile kernel 789 us at T = 16, 651 at 32, 412 at 64; fp16 here
+// 1100 us.  grad_kernel_of (dp_api.hip) draws its line there.
+//
+// Tiles (four waves, 32 gradient rows each where the layer is wide): 128 x 128, or 128 x 32 / 32 x 128 for layers
+// narrower than a tile, where the stream over the wide operand is the bound and padding the
+// narrow one to 128 would multiply its LDS traffic.  Operand rows go global -> LDS without passing
+// through registers, four stages of 32 rows, three blocks in flight; the 32 rows' weights travel
+// with them (a 4-byte gather of C by row / T).  Two workgroups share a compute unit: one's splitting
+// runs beside the other's matrix instructions.
+//
+// Rows of a sample with C == 0 do not enter (whatever they hold): a wave that meets a zero weight clears
+// those rows in both operands.  An infinity in an operand would meet the zero low parts of the other (inf x 0):
+// a wave that finds a NaN among its sums forms its tile again, sample by sample in fp32, without the split.
+#include "dp_internal.h"
+#include "grad_epilogue.h"
+#include "lds_dma.h"
+#include "tile_order.h"
+
+namespace dpbk {
+
+namespace {
+
+constexpr int BK = 32, NSTAGE = 4, NT = 256;
+
+// WM x WN waves over a BM x BN tile; each holds 32 rows x (BN / WN) columns.
+template <int BM_, int BN_, int WM_, int WN_>
+struct Shape {
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
+  static constexpr int TN = BN / WN / 32;
+  static constexpr int A_BYTES = BK * BM * 2, B_BYTES = BK * BN * 2;
+  static constexpr int W_BYTES = 256;                          // weights of the 32 rows (twice)
+  static constexpr int STAGE_BYTES = A_BYTES + B_BYTES + W_BYTES;
+  static constexpr int LOADS = (BM == 128 ? 2 : 1) + (BN == 128 ? 2 : 1) + 1;     // per wave per k-block
+  static_assert(BM / WM == 32 && WM * WN == 4 && (BM == 128 || BM == 32) && (BN == 128 || BN == 32), "shape");
+};
+using Wide = Shape<128, 128, 4, 1>;
+using Tall = Shape<128, 32, 4, 1>;
+using Flat = Shape<32, 128, 1, 4>;
+constexpr int LDS_BYTES = NSTAGE * Wide::STAGE_BYTES;          // 65 KiB: two workgroups per compute unit
+
+// One operand (W = 128 or 32 columns of a row-major [rows, width] matrix) on its way to LDS.
+// W = 128: load j of a wave covers rows 16 j + 4 wave + (lane >> 4), 16 chunks of 16 bytes each; the
+// lane's chunk c holds logical chunk c ^ ((row & 3) << 2), which spreads the four consecutive rows
+// of a transposing read over the banks.  W = 32: one load of half the lanes covers rows
+// 8 wave + (lane >> 2); rows are 64 bytes, so four of them span the banks as they lie.
+template <int W>
+struct Operand {
+  i32x4 rsrc;
+  unsigned v, step;                // byte offset of this lane's chunk; bytes per 16 rows
+  unsigned lds;                    // first LDS byte of this wave's loads inside a stage
+  __device__ __forceinline__ void init(const void* base, int64_t rows, int width, int col0, unsigned lds_base, int wave,
+                                       int lane) {
+    rsrc = make_rsrc(base, (unsigned)(rows * width * 2));
+    const int row = W == 128 ? wave * 4 + (lane >> 4) : wave * 8 + ((lane >> 2) & 7);
+    const int chunk = W == 128 ? (lane & 15) ^ ((row & 3) << 2) : lane & 3;
+    v = col0 + chunk * 8 < width ? (unsigned)(row * width + col0 + chunk * 8) * 2u : OOB;
+    step = 32u * width;
+    lds = lds_base + (W == 128 ? wave * 1024 : wave * 512);
+  }
+  __device__ __forceinline__ void issue(unsigned stage_off, int lane) {
+    if (W == 128) {
+      load_to_lds(rsrc, v, 0, lds + stage_off);
+      load_to_lds(rsrc, v + step, 0, lds + stage_off + 4096);
+    } else if (lane < 32) {
+      load_to_lds(rsrc, v, 0, lds + stage_off);
+    }
+    v += 2 * step;                 // rows past the last one lie past the descriptor's size: zeros
+  }
+};
+
+// LDS byte of a lane's first transposing read of the 32-column tile at col0 (see tn_tile.h): k row
+// 8 (b >> 1) + (s >> 2), columns 16 (b & 1) + 4 (s & 3) with b = lane >> 4, s = lane & 15.
+template <int W>
+__device__ __forceinline__ unsigned frag_base(int col0, int lane) {
+  const int b = lane >> 4, s = lane & 15;
+  const int row = 8 * (b >> 1) + (s >> 2), col = col0 + 16 * (b & 1) + 4 * (s & 3);
+  const int chunk = W == 128 ? (col >> 3) ^ ((row & 3) << 2) : col >> 3;
+  return row * (W * 2) + (chunk << 4) + (s & 1) * 8;
+}
+template <int W>
+__device__ __forceinline__ bf16x8 read_frag(unsigned addr) {
+  Frag f;
+  f.h[0] = lds_read_tr(addr);
+  f.h[1] = lds_read_tr(addr + 4 * W * 2);
+  return f.v;
+}
+
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
+template <bool F16>
+__device__ __forceinline__ float widen_lo(uint32_t u) {
+  return F16 ? (float)__builtin_bit_cast(_Float16, (uint16_t)(u & 0xFFFFu)) : __uint_as_float(u << 16);
+}
+template <bool F16>
+__device__ __forceinline__ float widen_hi(uint32_t u) {
+  return F16 ? (float)__builtin_bit_cast(_Float16, (uint16_t)(u >> 16)) : __uint_as_float(u & 0xFFFF0000u);
+}
+// The upper halves of two fp32 values as one pair of bfloat16 (truncation).
+__device__ __forceinline__ uint32_t pack_hi(float x0, float x1) {
+  return __builtin_amdgcn_perm(__float_as_uint(x1), __float_as_uint(x0), 0x07060302u);
+}
+__device__ __forceinline__ float top8(float x) { return __uint_as_float(__float_as_uint(x) & 0xFFFF0000u); }
+
+// The products w x of a pair -> three pairs of bfloat16 parts, the highest first.  The remainder behind the
+// first part is formed from the exact product and fits 24 bits; the last part is rounded to nearest.
+__device__ __forceinline__ void cut_product(float w0, float x0, float w1, float x1, uint32_t (&part)[3]) {
+  typedef __attribute__((ext_vector_type(2))) float f2;
+  typedef __attribute__((ext_vector_type(2))) __bf16 b2;
+  const float y0 = w0 * x0, y1 = w1 * x1;
+  const float r0 = fmaf(w0, x0, -top8(y0)), r1 = fmaf(w1, x1, -top8(y1));
+  const f2 last = {r0 - top8(r0), r1 - top8(r1)};
+  part[0] = pack_hi(y0, y1);
+  part[1] = pack_hi(r0, r1);
+  part[2] = __builtin_bit_cast(uint32_t, __builtin_convertvector(last, b2));
+}
+// A pair of fp16 values (11 bits) -> two pairs of bfloat16 parts, exactly.
+__device__ __forceinline__ void cut_f16(uint32_t u, uint32_t (&part)[2]) {
+  const float x0 = widen_lo<true>(u), x1 = widen_hi<true>(u);
+  part[0] = pack_hi(x0, x1);
+  part[1] = pack_hi(x0 - top8(x0), x1 - top8(x1));
+}
+
+// A 32 x 32 piece of the gradient again, sample by sample with unweighted fp32 products (sums that held a NaN).
+template <bool F16>
+__device__ __forceinline__ f32x16 retry_piece(const uint16_t* a, const uint16_t* g, int B, int T, int d, int p,
+                                              const float* C, int row0, int col0, int lane) {
+  const int j = row0 + (lane & 31), k = col0 + (lane & 31);
+  f32x16 total, zero;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) total[r] = zero[r] = 0.f;
+#pragma unroll 1
+  for (int i = 0; i < B; ++i) {
+    const float c = C[i];
+    if (c == 0.f) continue;
+    f32x16 s = zero;
+#pragma unroll 1
+    for (int t0 = 0; t0 < T; t0 += 2) {
+      const int t = t0 + (lane >> 5);
+      const size_t row = (size_t)i * T + t;
+      const float x = t < T && j < d ? widen_lo<F16>(a[row * d + j]) : 0.f;
+      const float z = t < T && k < p ? widen_lo<F16>(g[row * p + k]) : 0.f;
+      s = __builtin_amdgcn_mfma_f32_32x32x2f32(z, x, s, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) total[r] = fmaf(c, s[r], total[r]);
+  }
+  return total;
+}
+
+template <class S, bool F16, bool NOISE, bool OUT16>
+__device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int tile, int B, bool accumulate,
+                                            const float* C, const NoiseArgs& na, unsigned lds0) {
+  const int T = ly.T, d = ly.d_in, p = ly.d_out;
+  const int tiles_n = (p + S::BN - 1) / S::BN;
+  const int m0 = (tile / tiles_n) * S::BM, n0 = (tile % tiles_n) * S::BN;
+  const int rows = B * T, nkb = (rows + BK - 1) / BK;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = (wave / S::WN) * 32, wn = (wave % S::WN) * (S::BN / S::WN);
+
+  Operand<S::BM> oa;
+  Operand<S::BN> ob;
+  oa.init(ly.a, rows, d, m0, lds0, wave, lane);
+  ob.init(ly.g, rows, p, n0, lds0 + S::A_BYTES, wave, lane);
+  // weights: lane -> row (lane & 31) of the k-block, sample w_i and token w_t of that row
+  const i32x4 rw = make_rsrc(C, (unsigned)B * 4u);
+  int w_i = (lane & 31) / T, w_t = (lane & 31) % T;
+  const int w_di = BK / T, w_dt = BK % T;
+  int p_stage = 0;
+  auto issue = [&]() {
+    const unsigned so = p_stage * S::STAGE_BYTES;
+    oa.issue(so, lane);
+    ob.issue(so, lane);
+    load_dword_to_lds(rw, (unsigned)w_i * 4u, lds0 + so + S::A_BYTES + S::B_BYTES);    // rows past the end: 0
+    w_i += w_di;
+    w_t += w_dt;
+    if (w_t >= T) {
+      w_t -= T;
+      ++w_i;
+    }
+    p_stage = p_stage + 1 == NSTAGE ? 0 : p_stage + 1;
+  };
+
+  const unsigned a_rd = lds0 + frag_base<S::BM>(wm, lane);
+  unsigned b_rd[S::TN];
+#pragma unroll
+  for (int y = 0; y < S::TN; ++y) b_rd[y] = lds0 + S::A_BYTES + frag_base<S::BN>(wn + 32 * y, lane);
+  const unsigned w_rd = lds0 + S::A_BYTES + S::B_BYTES + 32u * (lane >> 5);
+
+  typedef __attribute__((ext_vector_type(4))) float f4;
+  typedef __attribute__((address_space(3))) f4 lds_f4;
+  constexpr int G_PARTS = F16 ? 2 : 1;
+  // The products of the low parts go to sums of their own, whose roundings are 2^-8 of the others': the
+  // result is rounded as often as one matrix instruction per step would.
+  f32x16 acc[S::TN], low[S::TN];
+#pragma unroll
+  for (int y = 0; y < S::TN; ++y)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[y][r] = low[y][r] = 0.f;
+
+  for (int q = 0; q < NSTAGE - 1; ++q) issue();
+  int stage = 0;
+  for (int kb = 0; kb < nkb; ++kb) {
+    // own loads of block kb landed, own LDS reads of block kb - 1 done; then everyone's
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NSTAGE - 2) * S::LOADS) : "memory");
+    issue();
+    const unsigned so = stage * S::STAGE_BYTES;
+    f4 w[2][2];                                          // weights of this lane's 8 rows, per 16-row step
+    u32x4 fa[2], fb[2][S::TN];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const lds_f4* wp = (const lds_f4*)(uintptr_t)(w_rd + so + ks * 64);
+      w[ks][0] = wp[0];
+      w[ks][1] = wp[1];
+      fa[ks] = __builtin_bit_cast(u32x4, read_frag<S::BM>(a_rd + so + ks * 16 * S::BM * 2));
+#pragma unroll
+      for (int y = 0; y < S::TN; ++y)
+        fb[ks][y] = __builtin_bit_cast(u32x4, read_frag<S::BN>(b_rd[y] + so + ks * 16 * S::BN * 2));
+    }
+    DP_PIN();
+    float least = fabsf(w[0][0][0]);
+#pragma unroll
+    for (int e = 1; e < 16; ++e) least = fminf(least, fabsf(w[e >> 3][(e >> 2) & 1][e & 3]));
+    if (__any(least == 0.f)) {                           // rows that do not count (or lie past the end)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int ks = q >> 2, e = 2 * q & 3;
+        const f4 ww = w[ks][(q >> 1) & 1];
+        const uint32_t m = (ww[e] == 0.f ? 0u : 0xFFFFu) | (ww[e + 1] == 0.f ? 0u : 0xFFFF0000u);
+        fa[ks][q & 3] &= m;
+#pragma unroll
+        for (int y = 0; y < S::TN; ++y) fb[ks][y][q & 3] &= m;
+      }
+    }
+    // The second step's cutting fills the gaps between the first step's matrix instructions.
+    u32x4 xa[2][3], xb[2][S::TN][G_PARTS];
+    auto cut = [&](int ks) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f4 ww = w[ks][q >> 1];
+        const int e = 2 * q & 3;
+        uint32_t part[3];
+        cut_product(ww[e], widen_lo<F16>(fa[ks][q]), ww[e + 1], widen_hi<F16>(fa[ks][q]), part);
+#pragma unroll
+        for (int n = 0; n < 3; ++n) xa[ks][n][q] = part[n];
+#pragma unroll
+        for (int y = 0; y < S::TN; ++y) {
+          if constexpr (F16) {
+            uint32_t gp[2];
+            cut_f16(fb[ks][y][q], gp);
+#pragma unroll
+            for (int m = 0; m < G_PARTS; ++m) xb[ks][y][m][q] = gp[m];
+          } else {
+            xb[ks][y][0][q] = fb[ks][y][q];
+          }
+        }
+      }
+    };
+    auto multiply = [&](int ks) {
+#pragma unroll
+      for (int n = 2; n >= 0; --n)
+#pragma unroll
+        for (int m = G_PARTS - 1; m >= 0; --m)
+#pragma unroll
+          for (int y = 0; y < S::TN; ++y) {
+            f32x16& sum = n + m ? low[y] : acc[y];
+            sum = mfma16<false>(__builtin_bit_cast(bf16x8, xb[ks][y][m]), __builtin_bit_cast(bf16x8, xa[ks][n]), sum);
+          }
+    };
+    cut(0);
+    DP_PIN();
+    multiply(0);
+    cut(1);
+#pragma unroll
+    for (int n = 0; n < 3 * G_PARTS * S::TN; ++n) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                       // one MFMA
+      __builtin_amdgcn_sched_group_barrier(0x002, F16 ? 8 : 6, 0);             // some vector-ALU instructions
+    }
+    DP_PIN();
+    multiply(1);
+    stage = stage + 1 == NSTAGE ? 0 : stage + 1;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // zero-fill loads past the end
+
+  bool nan = false;
+#pragma unroll
+  for (int y = 0; y < S::TN; ++y)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      acc[y][r] += low[y][r];
+      nan |= acc[y][r] != acc[y][r];
+    }
+  if (__any(nan)) {
+#pragma unroll
+    for (int y = 0; y < S::TN; ++y)
+      acc[y] = retry_piece<F16>(static_cast<const uint16_t*>(ly.a), static_cast<const uint16_t*>(ly.g), B, T, d, p, C,
+                                m0 + wm, n0 + wn + 32 * y, lane);
+  }
+
+  // epilogue in the transposed layout described at tile_noise
+  TileNoise tn = {};
+  if (NOISE) tn = load_tile_noise(na, layer);
+  float* out = ly.out;
+  const int row = m0 + wm + (lane & 31);
+#pragma unroll
+  for (int y = 0; y < S::TN; ++y) {
+    const int col0 = n0 + wn + 32 * y + 4 * (lane >> 5);
+    const size_t base = (size_t)row * p + col0;
+    float v[16];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float old[4] = {0.f, 0.f, 0.f, 0.f};
+      if (accumulate && row < d && col0 + 8 * q < p) load_old4<F16, OUT16, true>(out, base + 8 * q, old);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[4 * q + k] = accumulate ? old[k] + acc[y][4 * q + k] : acc[y][4 * q + k];
+    }
+    if (NOISE) tile_noise(v, tn, m0 + wm, n0 + wn + 32 * y, d, p, lane);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (row < d && col0 + 8 * q < p) store4<F16, OUT16>(out, base + 8 * q, v + 4 * q);
+  }
+}
+
+// GroupLayer::path holds the layer's tile shape (packed_shape).
+template <bool F16, bool NOISE, bool OUT16>
+__global__ void __launch_bounds__(NT, 2)
+grad_packed_kernel(const GroupArgs ga, const float* __restrict__ C_all, const NoiseArgs na) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
+  const unsigned lds0 = (unsigned)(uintptr_t)lds_raw;
+  // tiles of one row share a panel of a: consecutive numbers meet in one XCD's L2
+  const int item = contiguous_eighth(blockIdx.x, ga.total_blocks);
+  const int l = layer_of(ga, item);
+  const GroupLayer& ly = ga.layer[l];
+  const float* C = C_all + ly.c_off;
+  const int tile = item - ly.tile_begin;
+  if (ly.path == 0)
+    packed_tile<Wide, F16, NOISE, OUT16>(ly, l, tile, ga.B, ga.accumulate, C, na, lds0);
+  else if (ly.path == 1)
+    packed_tile<Tall, F16, NOISE, OUT16>(ly, l, tile, ga.B, ga.accumulate, C, na, lds0);
+  else
+    packed_tile<Flat, F16, NOISE, OUT16>(ly, l, tile, ga.B, ga.accumulate, C, na, lds0);
+}
+
+template <bool F16, bool NOISE, bool OUT16>
+dp_status launch_t(const GroupArgs& ga, const float* C, const NoiseArgs& na, hipStream_t s) {
+  auto kernel = grad_packed_kernel<F16, NOISE, OUT16>;
+  static ReadyTable ready;
+  dp_status st = allow_big_lds(kernel, LDS_BYTES, ready);
+  if (st != DP_OK) return st;
+  hipLaunchKernelGGL(kernel, dim3(ga.total_blocks), dim3(NT), LDS_BYTES, s, ga, C, na);
+  return hip_status(hipGetLastError());
+}
+
+int tiles_of(int d, int p, int bm, int bn) { return ((d + bm - 1) / bm) * ((p + bn - 1) / bn); }
+
+}  // namespace
+
+// A layer of up to 64 columns (rows) takes 32-wide tiles along that side: at most two of them, so
+// the other operand is read at most twice.
+int grad_packed_shape(int d, int p) { return p <= 64 ? 1 : d <= 64 ? 2 : 0; }
+
+int grad_packed_tiles(int d, int p) {
+  switch (grad_packed_shape(d, p)) {
+    case 1: return tiles_of(d, p, Tall::BM, Tall::BN);
+    case 2: return tiles_of(d, p, Flat::BM, Flat::BN);
+    default: return tiles_of(d, p, Wide::BM, Wide::BN);
+  }
+}
+
+// All rows of an operand through one descriptor with 32-bit byte offsets; the prefetch runs up to
+// NSTAGE blocks past the last row without wrapping.
+bool grad_packed_supports(int B, int T, int d, int p) {
+  const int64_t rows = (int64_t)B * T + (NSTAGE + 1) * BK;
+  return rows * d * 2 < (int64_t)1 << 31 && rows * p * 2 < (int64_t)1 << 31;
+}
+
+dp_status launch_grad_packed_group(const GroupArgs& ga, const float* C, const NoiseArgs* noise, hipStream_t s,
+                                   bool out16) {
+  static const NoiseArgs none = {};
+  const NoiseArgs& na = noise ? *noise : none;
+  switch ((ga.f16 ? 4 : 0) + (noise ? 2 : 0) + (out16 ? 1 : 0)) {
+    case 0: return launch_t<false, false, false>(ga, C, na, s);
+    case 1: return launch_t<false, false, true>(ga, C, na, s);
+    case 2: return launch_t<false, true, false>(ga, C, na, s);
+    case 3: return launch_t<false, true, true>(ga, C, na, s);
+    case 4: return launch_t<true, false, false>(ga, C, na, s);
+    case 5: return launch_t<true, false, true>(ga, C, na, s);
+    case 6: return launch_t<true, true, false>(ga, C, na, s);
+    default: return launch_t<true, true, true>(ga, C, na, s);
+  }
+}
+
+}  // namespace dpbk

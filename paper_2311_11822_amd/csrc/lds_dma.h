@@ -2,8 +2,7 @@
 // by the kernels that stage their operand tiles this way.
 #pragma once
 
-#include <hip/hip_runtime.h>
-#include <stdint.h>
+#include "dp_internal.h"
 
 namespace dpbk {
 
@@ -35,6 +34,30 @@ __device__ __forceinline__ void load_to_lds(i32x4 rsrc, unsigned voff, unsigned 
       : "s"(lds_base), "v"(voff), "s"(rsrc), "s"(soff)
       : "memory", "m0");
 }
+
+// 4 bytes per lane, to LDS at lds_base + 4 * lane; range check and wave-uniform base as above.
+__device__ __forceinline__ void load_dword_to_lds(i32x4 rsrc, unsigned voff, unsigned lds_base) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "buffer_load_dword %1, %2, 0 offen lds"
+      :
+      : "s"(lds_base), "v"(voff), "s"(rsrc)
+      : "memory", "m0");
+}
+
+// Transposing 64-bit LDS read and the MFMA operand that two of them (k rows 0..3 and 4..7) make.
+__device__ __forceinline__ s16x4 lds_read_tr(unsigned addr) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (__attribute__((address_space(3))) s16x4*)(uintptr_t)addr);
+}
+
+struct Frag {
+  union {
+    s16x4 h[2];
+    bf16x8 v;
+  };
+};
 
 // Nothing moves across this point in the compiler's instruction scheduling.
 #define DP_PIN() __builtin_amdgcn_sched_barrier(0)

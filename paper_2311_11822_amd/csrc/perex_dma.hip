@@ -42,18 +42,6 @@ constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES;        // 80 KiB: two workgroups
 constexpr int LOADS = 2;                               // per operand per thread per k-block
 constexpr int LOADS_ALL = 2 * LOADS;
 
-__device__ __forceinline__ s16x4 lds_read_tr(unsigned addr) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (__attribute__((address_space(3))) s16x4*)(uintptr_t)addr);
-}
-
-struct Frag {
-  union {
-    s16x4 h[2];
-    bf16x8 v;
-  };
-};
-
 template <bool F16>
 __global__ void __launch_bounds__(NT)
 perex_dma_kernel(const GroupArgs ga, float* __restrict__ partials) {

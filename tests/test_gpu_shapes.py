@@ -91,3 +91,67 @@ def test_fp32_stack(B, T, dims):
 def test_fp32_more_layers_than_one_launch():
     check_step(si.F32, 2, 5, [(4 * (1 + l % 5), 3 + l % 7) if l % 2 else (8, 4) for l in range(50)],
                paths=[l % 2 for l in range(50)])
+
+
+HALF = [si.BF16, si.F16]
+
+
+# Packed-row gradient (short samples, narrow layers): one token, tokens that divide no 32-row block, a
+# total below and off a multiple of 32, tile edges and the three tile shapes, masked samples
+# that hold NaN (first, inside, last).
+@pytest.mark.parametrize("dtype", HALF)
+@pytest.mark.parametrize("B,T,dims", [
+    (1, 1, [(8, 8)]), (70, 1, [(136, 264), (128, 128)]), (9, 7, [(200, 328), (24, 304), (304, 24)]),
+    (5, 31, [(72, 72), (64, 200), (200, 64)]), (2, 33, [(256, 8), (8, 256)]), (3, 70, [(16, 1104), (1104, 40)]),
+])
+def test_packed_rows(dtype, B, T, dims):
+    check_step(dtype, B, T, dims, paths=[0] * len(dims))
+    check_step(dtype, B, T, dims, mode=o.CLIP_AUTOMATIC, mask=sorted({0, B // 2, B - 1}) if B > 2 else ())
+
+
+@pytest.mark.parametrize("dtype", HALF)
+@pytest.mark.parametrize("where", ["a", "g", "both"])
+def test_packed_rows_with_infinities(dtype, where):
+    """An infinity stays where it belongs: same infinities and NaNs as sample-by-sample sums, the rest untouched."""
+    from paper_2311_11822_amd import binding as dp
+    B, T, d, p = 6, 5, 136, 152
+    w = si.small_workload("inf", dtype, B, T, [(d, p)], g_std=1e-2)
+    a, g = si.gen_layer(w, 0)
+    one, inf = (0x3F80, 0x7F80) if dtype == si.BF16 else (1.0, np.inf)
+    a[:, :, 3] = one                                     # exact in one part: the others are zero
+    if where in ("a", "both"):
+        a[2, 4, 5] = inf
+    if where in ("g", "both"):
+        g[1, 0, 140] = inf
+        g[4, 2, 0] = inf
+    C = np.array([1.0, 0.5, 0.25, 0.0, 2.0, 0.7], dtype=np.float32)
+    with np.errstate(invalid="ignore"):
+        want = o.clipped_grad(si.to_f64(a), si.to_f64(g), C.astype(np.float64))
+    grad = torch.zeros((d, p), device="cuda")
+    dt = dp.DP_BF16 if dtype == si.BF16 else dp.DP_F16
+    dp.dp_clipped_grad(dev(a), dev(g), dt, B, T, d, p, dev(C), grad, 0)
+    got = host(grad)
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(want))
+    np.testing.assert_array_equal(np.isposinf(got), np.isposinf(want))
+    np.testing.assert_array_equal(np.isneginf(got), np.isneginf(want))
+    ok = np.isfinite(want)
+    assert ok.sum() > 0.9 * ok.size and frob(got[ok], want[ok]) <= TOL
+
+
+@pytest.mark.parametrize("dtype,T", [(si.BF16, 32), (si.F16, 32), (si.BF16, 64)])
+def test_half_gradient_of_short_samples(dtype, T):
+    """The 16-bit gradient is the fp32 one rounded once, whichever kernel the token count selects."""
+    from paper_2311_11822_amd import binding as dp
+    B, dims = 5, [(136, 264), (128, 128)]
+    w = si.small_workload("h16", dtype, B, T, dims)
+    keep = [tuple(dev(x) for x in si.gen_layer(w, l)) for l in range(2)]
+    dt, tdt = (dp.DP_BF16, torch.bfloat16) if dtype == si.BF16 else (dp.DP_F16, torch.float16)
+    desc = dp.layer_array([(a, g, T, d, p, 0) for (a, g), (d, p) in zip(keep, dims)])
+    C = dev(np.array([0.7, 0.0, 0.05, 1.0, 0.3], dtype=np.float32))
+    offs, n = [0, dims[0][0] * dims[0][1]], sum(d * p for d, p in dims)
+    old = [(torch.randn(d, p, device="cuda") * 0.05).to(tdt) for d, p in dims]
+    got, ref = [x.clone() for x in old], [x.float() for x in old]
+    dp.dp_clipped_grad_noise_multi_h16(desc, dt, B, C, got, offs, 1, 6, n - 9, 0.01, 2.0, 5, 9)
+    dp.dp_clipped_grad_noise_multi(desc, dt, B, C, ref, offs, 1, 6, n - 9, 0.01, 2.0, 5, 9)
+    for x, y in zip(got, ref):
+        assert torch.equal(x.view(torch.int16), y.to(tdt).view(torch.int16))
