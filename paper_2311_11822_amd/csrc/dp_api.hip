@@ -50,8 +50,8 @@ int tiles_per_sample(int path, const dp_layer& ly) {
 
 // Launches the norm kernels of one path for the listed layers, in chunks of kMaxGroup.
 // part_begin[l] is the layer's first slot in the partial-sum workspace.
-enum NormKernel { kGhostBig = 0, kGhostSmall = 1, kPerex = 2, kGhostSample = 3 };
-constexpr int kNormKernels = 4;
+enum NormKernel { kGhostBig = 0, kGhostSmall = 1, kPerex = 2, kGhostSample = 3, kGhostBrief = 4 };
+constexpr int kNormKernels = 5;
 
 dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, int n_which,
                         const int64_t* part_begin, dp_dtype dt, int B, float* partials,
@@ -92,9 +92,14 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
       gl.part_begin = (int)part_begin[l];
       gl.tiles_per_sample = tiles_per_sample(gl.path, layers[l]);
       gl.c_off = 0;
-      blocks += (int64_t)gl.tiles_per_sample * B;
+      blocks += kernel == kGhostBrief ? ghost_brief_blocks(B, gl.T) : (int64_t)gl.tiles_per_sample * B;
     }
     ga.total_blocks = (int)blocks;
+    if (kernel == kGhostBrief) {                     // writes final norms: nothing to add up
+      dp_status st = launch_ghost_brief_group(ga, sqnorm_out, s);
+      if (st != DP_OK) return st;
+      continue;
+    }
     // instantiated norm: the kernel with the deep load pipeline unless a slab is beyond its
     // 32-bit addressing (both use the same tiles and partial-sum slots)
     bool dma = DP_PEREX_DMA;
@@ -175,10 +180,12 @@ dp_status norms_impl(const dp_layer* layers, int L, dp_dtype dt, int B, float* s
   }
   if (!ws || ws_bytes < (size_t)slots * sizeof(float)) return DP_ERR_WORKSPACE;
   if (!aligned16(ws)) return DP_ERR_INVALID_ARG;
-  int* list[kNormKernels] = {idx, idx + L, idx + 2 * L, idx + 3 * L};
-  int count[kNormKernels] = {0, 0, 0, 0};
+  int* list[kNormKernels];
+  for (int k = 0; k < kNormKernels; ++k) list[k] = idx + (size_t)k * L;
+  int count[kNormKernels] = {};
   for (int l = 0; l < L; ++l) {
     const int k = layers[l].path == DP_PATH_PEREX ? kPerex
+                  : ghost_brief_supports(layers[l].T) ? kGhostBrief
                   : ghost_uses_sample(layers[l])  ? kGhostSample
                   : ghost_uses_big(layers[l])     ? kGhostBig
                                                   : kGhostSmall;

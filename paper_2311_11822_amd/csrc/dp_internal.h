@@ -148,6 +148,11 @@ dp_status launch_ghost_big_group(const GroupArgs& ga, float* partials, hipStream
 // partial sum per sample.
 bool ghost_sample_supports(int T, int d, int p);
 dp_status launch_ghost_sample_group(const GroupArgs& ga, float* partials, hipStream_t s);
+// Samples of up to 32 tokens, several to a workgroup, final squared norms (ghost_brief.hip):
+// ga.layer[j].tile_begin = first workgroup (ghost_brief_blocks per layer).
+bool ghost_brief_supports(int T);
+int ghost_brief_blocks(int B, int T);
+dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, hipStream_t s);
 // 256x256-tile kernel with direct global->LDS loads (grad_gemm.hip).
 int clipped_grad_big_tiles(int d, int p);
 // Of a launch of n large tiles, how many (the last ones) go to the sub-tile kernel.

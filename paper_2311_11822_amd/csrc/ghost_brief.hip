@@ -1,0 +1,117 @@
+// Ghost norm of short samples (appendix A.1 of the paper, right side of eq. "mixed ghost norm"), up to
+// 32 tokens:   sqnorm[i] = sum_{t,t'} (a_t . a_t') (g_t . g_t').
+//
+// A sample of T tokens fills T of the 32 rows of a matrix instruction, and the kernels that give a
+// sample a workgroup and a 128- or 256-row tile spend their time on LDS traffic for rows that are
+// not there (measured at T = 1, d = 1024: 437 us for 512 samples x 8 layers whose a and g take 7 us to read).
+// Here one workgroup takes the 32 / T consecutive samples that fit 32 rows, which are consecutive rows
+// in memory too: one 32 x 32 Gram matrix per operand, of which the T x T blocks on the diagonal count. Both
+// operands of a x x^T product are the same registers, loaded straight from global memory (a lane's
+// 16 bytes are eight consecutive columns of one row), so nothing is staged; the eight waves take every eighth
+// 16-column step and add their parts in LDS in a fixed order.  What bounds it is the read of a and g.
+// The squared norms are final: no per-tile partial sums, no launch that adds them.
+#include "dp_internal.h"
+
+namespace dpbk {
+
+namespace {
+
+constexpr int kWaves = 8, kThreads = 64 * kWaves, kRows = 32;
+constexpr int kDepth = 8;                        // 16-byte loads in flight per lane
+
+// This wave's part of the Gram matrix of the 32 rows at x (those with `valid` lanes; the others count as zeros).
+template <bool F16>
+__device__ __forceinline__ f32x16 gram_part(const uint16_t* x, int width, bool valid, int wave, int lane) {
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  const uint16_t* row = x + (size_t)(lane & 31) * width;
+  for (int k0 = wave * 16; k0 < width; k0 += kDepth * kWaves * 16) {
+    bf16x8 f[kDepth];
+#pragma unroll
+    for (int q = 0; q < kDepth; ++q) {
+      const int k = k0 + q * kWaves * 16 + 8 * (lane >> 5);
+      uint4 w = make_uint4(0, 0, 0, 0);
+      if (valid && k < width) w = *reinterpret_cast<const uint4*>(row + k);
+      f[q] = __builtin_bit_cast(bf16x8, w);
+    }
+#pragma unroll
+    for (int q = 0; q < kDepth; ++q) acc = mfma16<F16>(f[q], f[q], acc);
+  }
+  return acc;
+}
+
+template <bool F16>
+__global__ void __launch_bounds__(kThreads)
+ghost_brief_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
+  __shared__ float part_a[kWaves][16][64], part_g[kWaves][16][64];       // 64 KiB: two workgroups per compute unit
+  const int l = layer_of(ga, blockIdx.x);
+  const GroupLayer& ly = ga.layer[l];
+  const int T = ly.T, per = kRows / T;
+  const int i0 = (blockIdx.x - ly.tile_begin) * per, n = min(per, ga.B - i0);     // samples [i0, i0 + n)
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool valid = (lane & 31) < n * T;
+  const size_t row0 = (size_t)i0 * T;
+  const f32x16 xa = gram_part<F16>(static_cast<const uint16_t*>(ly.a) + row0 * ly.d_in, ly.d_in, valid, wave, lane);
+  const f32x16 xg = gram_part<F16>(static_cast<const uint16_t*>(ly.g) + row0 * ly.d_out, ly.d_out, valid, wave, lane);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    part_a[wave][r][lane] = xa[r];
+    part_g[wave][r][lane] = xg[r];
+  }
+  __syncthreads();
+  // Register r of lane x holds row 8 (r >> 2) + 4 (x >> 5) + (r & 3), column x & 31; this thread: registers
+  // wave and wave + 8.  Row sums inside the row's own sample, then the T rows of each sample.
+  float row_sum[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int r = wave + 8 * h;
+    float sa = 0.f, sg = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      sa += part_a[w][r][lane];
+      sg += part_g[w][r][lane];
+    }
+    const int row = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    float v = (lane & 31) / T == row / T ? sa * sg : 0.f;
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    row_sum[h] = v;
+  }
+  __syncthreads();
+  float* rows = &part_a[0][0][0];
+  if ((lane & 31) == 0) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int r = wave + 8 * h;
+      rows[8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)] = row_sum[h];
+    }
+  }
+  __syncthreads();
+  if (tid < n) {
+    float s = 0.f;
+    for (int t = 0; t < T; ++t) s += rows[tid * T + t];
+    sqnorm[(size_t)ly.sq_index * ga.B + i0 + tid] = s;
+  }
+}
+
+}  // namespace
+
+bool ghost_brief_supports(int T) { return T <= kRows; }
+
+// Workgroups of a layer.
+int ghost_brief_blocks(int B, int T) {
+  const int per = kRows / T;
+  return (B + per - 1) / per;
+}
+
+dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, hipStream_t s) {
+  if (ga.f16)
+    hipLaunchKernelGGL(ghost_brief_kernel<true>, dim3(ga.total_blocks), dim3(kThreads), 0, s, ga, sqnorm);
+  else
+    hipLaunchKernelGGL(ghost_brief_kernel<false>, dim3(ga.total_blocks), dim3(kThreads), 0, s, ga, sqnorm);
+  return hip_status(hipGetLastError());
+}
+
+}  // namespace dpbk

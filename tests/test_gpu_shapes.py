@@ -155,3 +155,24 @@ def test_half_gradient_of_short_samples(dtype, T):
     dp.dp_clipped_grad_noise_multi(desc, dt, B, C, ref, offs, 1, 6, n - 9, 0.01, 2.0, 5, 9)
     for x, y in zip(got, ref):
         assert torch.equal(x.view(torch.int16), y.to(tdt).view(torch.int16))
+
+
+# Ghost norm of short samples: several samples to a workgroup (the last one not full), one sample of 17 .. 32
+# rows, widths that end inside a 16-column step, more columns than the waves take in one go.
+@pytest.mark.parametrize("dtype", HALF)
+@pytest.mark.parametrize("B,T,d,p", [
+    (1, 1, 8, 8), (33, 1, 24, 1032), (67, 2, 136, 40), (31, 3, 2056, 64), (7, 16, 72, 200), (3, 17, 264, 88),
+    (2, 32, 1160, 8), (5, 31, 16, 4104),
+])
+def test_ghost_norm_of_short_samples(dtype, B, T, d, p):
+    from paper_2311_11822_amd import binding as dp
+    w = si.small_workload("brief", dtype, B, T, [(d, p)], g_std=1e-2)
+    a, g = si.gen_layer(w, 0)
+    dt = dp.DP_BF16 if dtype == si.BF16 else dp.DP_F16
+    out = torch.full((B + 1,), -1.0, device="cuda")
+    ws = torch.empty(max(16, dp.dp_norm_workspace_bytes(0, dt, B, T, d, p)), dtype=torch.uint8, device="cuda")
+    dp.dp_ghost_norm(dev(a), dev(g), dt, B, T, d, p, out, ws)
+    want = o.ghost_sqnorm(si.to_f64(a), si.to_f64(g))
+    # sums of d + p exact products: relative to the sum of their magnitudes, which the diagonal bounds
+    np.testing.assert_allclose(host(out)[:B], want, rtol=TOL)
+    assert host(out)[B] == -1.0
