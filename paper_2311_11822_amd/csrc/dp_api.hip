@@ -317,14 +317,15 @@ dp_status noise_after(const NoiseSpec* noise, int l, const dp_layer& ly, float* 
 
 // Which gradient kernel a 16-bit layer takes.
 //  kGradPacked: layers narrower than half a large tile (its 256 x 256 would be mostly padding), and samples
-//    of less than kPackedTokens: the large-tile kernel spends ~1400 clocks per 32 tokens and ~4400 per
-//    sample boundary, the packed one three (fp16: six) times the matrix instructions and nothing
-//    per sample.
-//  kGradBig: whole 32-token k-blocks and slabs its 32-bit addressing reaches.
+//    of less than kPackedTokens: the large-tile kernel takes as long for a sample of up to 32 tokens
+//    (2.7 us on eight 1024-wide layers: ~1400 clocks a k-block, ~900 a sample boundary) as the packed one
+//    for 20 rows (fp16: 10), whose matrix instructions are three (six) times as many.  4096 rows:
+//    T = 16 684 us against 595, T = 32 352 against 555.
+//  kGradBig: slabs its 32-bit addressing reaches.
 //  kGradEdge: the rest.
 enum GradKernel { kGradBig = 0, kGradPacked = 1, kGradEdge = 2 };
 constexpr int kGradKernels = 3;
-constexpr int kPackedTokens = 48, kPackedTokensF16 = 12;
+constexpr int kPackedTokens = 20, kPackedTokensF16 = 10;
 
 GradKernel grad_kernel_of(const dp_layer& ly, dp_dtype dt, int B) {
   const bool narrow = ly.d_in < 128 || ly.d_out < 128;
@@ -353,7 +354,7 @@ dp_status clipped_grad_impl(const dp_layer* layers, int L, dp_dtype dt, int B, c
     if (dt == DP_F32) return DP_ERR_UNSUPPORTED;
     for (int l = 0; l < L; ++l) {
       const dp_layer& ly = layers[l];
-      if (!(ly.d_in >= 128 && ly.d_out >= 128 && clipped_grad_big_supports(ly.T, ly.d_in, ly.d_out)))
+      if (!(ly.T % 32 == 0 && ly.d_in >= 128 && ly.d_out >= 128 && clipped_grad_big_supports(ly.T, ly.d_in, ly.d_out)))
         return DP_ERR_UNSUPPORTED;
       if (noise && (noise->grad_offset[l] & 3)) return DP_ERR_UNSUPPORTED;
     }
@@ -444,7 +445,7 @@ dp_status clipped_grad_impl(const dp_layer* layers, int L, dp_dtype dt, int B, c
       if (fused) set_noise(na, *noise);
       const NoiseArgs* in_kernel = fused ? &na : nullptr;
       dp_status st = kernel == kGradBig      ? launch_clipped_grad_big_group(ga, C, in_kernel, s, out16)
-                     : kernel == kGradPacked ? launch_grad_packed_group(ga, C, in_kernel, s, out16)
+                     : kernel == kGradPacked ? launch_grad_packed_group(ga, C, in_kernel, s)
                                              : launch_clipped_grad_group(ga, C, s);
       if (st != DP_OK) return st;
       if (noise && !fused) {

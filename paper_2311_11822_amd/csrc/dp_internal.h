@@ -168,8 +168,7 @@ dp_status launch_clipped_grad_big_group(const GroupArgs& ga, const float* C, con
 int grad_packed_shape(int d, int p);
 int grad_packed_tiles(int d, int p);
 bool grad_packed_supports(int B, int T, int d, int p);
-dp_status launch_grad_packed_group(const GroupArgs& ga, const float* C, const NoiseArgs* noise, hipStream_t s,
-                                   bool out16);
+dp_status launch_grad_packed_group(const GroupArgs& ga, const float* C, const NoiseArgs* noise, hipStream_t s);
 
 // Clip-weighted sum of kept per-sample gradients (kept.hip).  ga.layer[j]: a = kept [B, d * p] fp32,
 // out = grad, tile_begin = first workgroup (kept_blocks(d, p) per layer), c_off; noise as NoiseArgs,

@@ -3,26 +3,31 @@
 //
 // Design for gfx950 (measured on the device: dense bf16 MFMA sustains 2.2 PFLOP/s; the
 // transposing 64-bit LDS read sustains ~130-150 B/clk/CU, half the rate of 128-bit reads):
-//  * 256x256 output tile per workgroup, 4 waves of 128x128: LDS read traffic per MFMA is the
-//    lowest the register file allows (256 accumulator registers per lane), so the transposing
-//    reads use about half of their bandwidth.
+//  * 256x256 output tile per workgroup, 8 waves of 128x64 (two per SIMD).  A wave holds 128 accumulators in
+//    ordinary registers next to its fragments.  Four waves of 128x128, measured before, read a third
+//    less LDS per MFMA, but their 256 accumulators sit in accumulator registers, which the vector ALU reaches
+//    only through copies: re-expressing them at a sample boundary (below) cost ~4400 clocks against
+//    ~1400 per 32 tokens, here ~900.  Eight 1024-wide layers (gradient stage): 64 x 64 tokens 410 -> 268
+//    us, 32 x 128 316 -> 240; 12 GPT blocks of width 768, 16 x 256 tokens 780 -> 704, of 1280, 8 x 512
+//    1863 -> 1787; at 2048 tokens and more equal within 1 %.
 //  * global -> LDS without passing through registers (buffer_load ... lds, 16 B per lane).
 //    A wave's load lands as 1 KiB of consecutive LDS = two 512-byte k rows, so rows cannot be
 //    padded; instead the 16-byte chunks of row k are XOR-swizzled by (k & 3) << 2, which
 //    spreads four consecutive k rows over the four 64-byte bank groups the transposing read
-//    touches at once.  Out-of-range chunks (tile edge, ragged T, past the last k-block) are
-//    fetched with an offset past the buffer descriptor's size and arrive as zeros.
+//    touches at once.  Out-of-range chunks (tile edge, rows past the end of a sample whose T is no multiple
+//    of the k-block, past the last k-block) are fetched with an offset past the buffer descriptor's size
+//    and arrive as zeros: the lane's offset holds the whole row, since the range check sees it alone.
 //  * five LDS stages of 32 k rows (all 160 KiB of the CU).  In iteration i a wave waits for its
 //    own loads of k-block i+1, meets the others at one barrier (which certifies block i+1 in
 //    LDS and block i-1 no longer read), issues the loads of block i+4 into the stage block i-1
 //    used, and computes block i.  A load has three iterations (about 3000 clocks) to land.
 //    Operand fragments of the next k-step are fetched from LDS during the MFMAs of the current
-//    one, across the barrier too, so the matrix pipe never waits for LDS latency.
+//    one, across the barrier and across samples too, so the matrix pipe never waits for LDS latency.
 //    The loads are issued from inline assembly because the compiler otherwise waits for every
-//    outstanding LDS-DMA load before any LDS read; MFMAs, LDS reads and loads are interleaved
-//    by hand (one wave per SIMD: there is no second wave to hide issue gaps).
-//  * per-sample weights: see tn_gemm.hip (single accumulator set, re-expressed at sample
-//    boundaries).
+//    outstanding LDS-DMA load before any LDS read; MFMAs, LDS reads and loads are interleaved by hand.
+//  * per-sample weights: single accumulator set, re-expressed at sample boundaries (tn_tile.h).  Folding the
+//    multiplies into the boundary block's MFMA stream needs a second copy of the block, between which the
+//    compiler moves the accumulators through scratch memory (126 registers spilled).
 #include <type_traits>
 
 #include "dp_internal.h"
@@ -39,12 +44,12 @@ namespace {
 #define DP_GRAD_NSTAGE 5
 #endif
 constexpr int BM = 256, BN = 256, BK = 32, NSTAGE = DP_GRAD_NSTAGE;
-constexpr int NT = 256;
+constexpr int NT = 512;
 constexpr int ROW_BYTES = 512;                         // 256 bf16
 constexpr int TILE_BYTES = BK * ROW_BYTES;             // one operand, one stage (16 KiB)
 constexpr int STAGE_BYTES = 2 * TILE_BYTES;            // 32 KiB
 constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES;        // 160 KiB with 5 stages: all of the CU's LDS
-constexpr int LOADS = BK / 8;                          // per operand per thread per k-block
+constexpr int LOADS = BK / 16;                         // per operand per thread per k-block
 
 // Tile t of the launch -> layer and tile origin (order inside a layer: tile_order.h).
 __device__ __forceinline__ void locate_tile(const GroupArgs& ga, int t, int& layer, int& m0, int& n0) {
@@ -80,49 +85,42 @@ clipped_grad_big_kernel(const GroupArgs ga, const float* __restrict__ C_global, 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // wave-uniform: keeps LDS bases scalar
 
-  // ---- global -> LDS addressing -------------------------------------------------------
-  // Load j of a wave covers rows j*8 + wave*2 + (lane >> 5) of the 32-row k-block; the lane's
-  // LDS chunk (lane & 31) holds logical chunk (lane & 31) ^ ((row & 3) << 2).
+  // ---- global -> LDS addressing: load j of a wave covers rows 16 j + 2 wave + (lane >> 5) of the
+  // 32-row k-block; the lane's LDS chunk (lane & 31) holds logical chunk (lane & 31) ^ ((row & 3) << 2).
   const int lrow = wave * 2 + (lane >> 5);
   const int chunk = (lane & 31) ^ ((lrow & 3) << 2);
-  const bool a_in = m0 + chunk * 8 < d, b_in = n0 + chunk * 8 < p;
-  const unsigned a_off0 = (unsigned)(lrow * d + m0 + chunk * 8) * 2u;
-  const unsigned b_off0 = (unsigned)(lrow * p + n0 + chunk * 8) * 2u;
-  const unsigned a_step = 8u * d * 2u, b_step = 8u * p * 2u;          // bytes per 8 rows
+  const unsigned a_org = m0 + chunk * 8 < d ? (unsigned)(lrow * d + m0 + chunk * 8) * 2u : OOB;
+  const unsigned b_org = n0 + chunk * 8 < p ? (unsigned)(lrow * p + n0 + chunk * 8) * 2u : OOB;
+  const unsigned a_half = 16u * d * 2u, b_half = 16u * p * 2u;       // bytes per 16 rows
   const unsigned a_slab = (unsigned)T * d * 2u, b_slab = (unsigned)T * p * 2u;
   const unsigned char* a_base = static_cast<const unsigned char*>(ly.a);
   const unsigned char* b_base = static_cast<const unsigned char*>(ly.g);
   const unsigned lds_ld = lds0 + wave * 2 * ROW_BYTES;
-
   // Prefetch stream: (p_i, p_kb) is the next k-block to fetch.  Once p_i >= B ("past the
   // end") every lane fetches zeros, so each iteration issues the same number of loads.
-  // T is a multiple of BK here (checked on the host), so rows never run past a sample.
   int p_i = 0, p_kb = 0, p_stage = 0;
   while (p_i < B && C[p_i] == 0.f) ++p_i;
   i32x4 ra, rb;
-  unsigned va, vb;                 // per-lane byte offset inside the sample's slab, or OOB
-  unsigned sa = 0, sb = 0;         // scalar byte offset of the k-block inside the slab
+  unsigned va, vb;                 // per-lane byte offset of the k-block's row inside the slab, or past OOB
   auto prefetch_sample = [&]() {
     const bool valid = p_i < B;
     const int smp = valid ? p_i : 0;
     ra = make_rsrc(a_base + (size_t)smp * a_slab, a_slab);
     rb = make_rsrc(b_base + (size_t)smp * b_slab, b_slab);
-    va = (valid && a_in) ? a_off0 : OOB;
-    vb = (valid && b_in) ? b_off0 : OOB;
-    sa = 0;
-    sb = 0;
+    va = valid ? a_org : OOB;
+    vb = valid ? b_org : OOB;
   };
   prefetch_sample();
-  // One of the LOADS load pairs of the current prefetch block.
-  auto prefetch_issue_a = [&](int j) {
-    load_to_lds(ra, va, sa + j * a_step, lds_ld + p_stage * STAGE_BYTES + j * 8 * ROW_BYTES);
-  };
-  auto prefetch_issue_b = [&](int j) {
-    load_to_lds(rb, vb, sb + j * b_step, lds_ld + p_stage * STAGE_BYTES + j * 8 * ROW_BYTES + TILE_BYTES);
+  auto prefetch_issue = [&](int x) {                   // x = 0, 1: a; 2, 3: g
+    const unsigned dst = lds_ld + p_stage * STAGE_BYTES + (x & 1) * 16 * ROW_BYTES;
+    if (x < 2)
+      load_to_lds(ra, va + (x & 1) * a_half, 0, dst);
+    else
+      load_to_lds(rb, vb + (x & 1) * b_half, 0, dst + TILE_BYTES);
   };
   auto prefetch_advance = [&]() {
-    sa += BK * d * 2u;
-    sb += BK * p * 2u;
+    va += 2 * a_half;
+    vb += 2 * b_half;
     if (p_i < B && ++p_kb == nkb) {
       p_kb = 0;
       ++p_i;
@@ -137,43 +135,41 @@ clipped_grad_big_kernel(const GroupArgs ga, const float* __restrict__ C_global, 
   // half), element column = 16*(b&1) + 4*(s&3) inside a 32-wide MFMA tile.
   const int blk = lane >> 4, s = lane & 15;
   const int rrow = 8 * (blk >> 1) + (s >> 2);
-  const int wm = (wave >> 1) * 128, wn = (wave & 1) * 128;
-  unsigned a_rd[4], b_rd[4];
+  const int sw = (rrow & 3) << 2;
+  const int wm = (wave >> 2) * 128, wn = (wave & 3) * 64;
+  unsigned a_rd[4], b_rd[2];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int ca = (wm + i * 32 + 16 * (blk & 1) + 4 * (s & 3)) >> 3;
-    const int cb = (wn + i * 32 + 16 * (blk & 1) + 4 * (s & 3)) >> 3;
-    const int sw = (rrow & 3) << 2;
     a_rd[i] = lds0 + rrow * ROW_BYTES + ((ca ^ sw) << 4) + (s & 1) * 8;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int cb = (wn + i * 32 + 16 * (blk & 1) + 4 * (s & 3)) >> 3;
     b_rd[i] = lds0 + TILE_BYTES + rrow * ROW_BYTES + ((cb ^ sw) << 4) + (s & 1) * 8;
   }
-
-  f32x16 acc[4][4];
+  f32x16 acc[4][2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int x = 0; x < 4; ++x)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int y = 0; y < 2; ++y)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  Frag fa[2][4], fb[2][4];
-  // Fragment reads of k-step `ks` of the block in `stage`: item q in 0..7 reads fb[q] (q < 4)
-  // or fa[q - 4].  The first MFMA row of the next k-step needs every fb but only fa[0], so the
-  // B fragments go first and the last-issued read (fa[3]) is needed last.
+      for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
+  Frag fa[2][4], fb[2][2];
+  // Items 0 .. 5 of a k-step's fragments in the order its matrix instructions need them.
   auto read_frag = [&](int buf, int q, int stage, int ks) {
     const unsigned o = stage * STAGE_BYTES + ks * 16 * ROW_BYTES;
-    if (q < 4) {
-      fb[buf][q].h[0] = lds_read_tr(b_rd[q] + o);
-      fb[buf][q].h[1] = lds_read_tr(b_rd[q] + o + 4 * ROW_BYTES);
+    if (q == 0 || q == 2) {
+      fb[buf][q >> 1].h[0] = lds_read_tr(b_rd[q >> 1] + o);
+      fb[buf][q >> 1].h[1] = lds_read_tr(b_rd[q >> 1] + o + 4 * ROW_BYTES);
     } else {
-      fa[buf][q - 4].h[0] = lds_read_tr(a_rd[q - 4] + o);
-      fa[buf][q - 4].h[1] = lds_read_tr(a_rd[q - 4] + o + 4 * ROW_BYTES);
+      const int i = q == 1 ? 0 : q - 2;
+      fa[buf][i].h[0] = lds_read_tr(a_rd[i] + o);
+      fa[buf][i].h[1] = lds_read_tr(a_rd[i] + o + 4 * ROW_BYTES);
     }
   };
 
-  // Compute stream: outer loop over samples with a non-zero weight, inner loop over the
-  // sample's k-blocks.  The global->LDS prefetch runs ahead across sample boundaries; the
-  // fragment pipeline restarts at each sample (one exposed LDS latency per sample).
+  // Compute stream over the samples with a non-zero weight.
   int c_i = p_i;
   float held = 0.f;
   if (c_i < B) {
@@ -181,98 +177,56 @@ clipped_grad_big_kernel(const GroupArgs ga, const float* __restrict__ C_global, 
     // prologue: blocks 0 .. NSTAGE-2 in flight; block 0 complete in LDS
     for (int q = 0; q < NSTAGE - 1; ++q) {
 #pragma unroll
-      for (int j = 0; j < LOADS; ++j) {
-        prefetch_issue_a(j);
-        prefetch_issue_b(j);
-      }
+      for (int x = 0; x < 2 * LOADS; ++x) prefetch_issue(x);
       prefetch_advance();
     }
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NSTAGE - 2) * 2 * LOADS) : "memory");
     __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 6; ++q) read_frag(0, q, 0, 0);
 
     int c_stage = 0;
-    // One k-block: wait for block +1, barrier, issue block +(NSTAGE-1), 32 MFMAs.  `last` = last block
-    // of the sample: the fragments of the following block are not fetched here.
-    auto block = [&](auto last_tag) {
-      constexpr bool last = decltype(last_tag)::value;
+    // One k-block: wait for block +1, barrier, 16 MFMAs with the reads of the next fragments and the
+    // loads of block +(NSTAGE-1) between them.
+    auto block = [&]() {
       asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NSTAGE - 3) * 2 * LOADS) : "memory");
       __builtin_amdgcn_s_barrier();
       const int n_stage = c_stage + 1 == NSTAGE ? 0 : c_stage + 1;
       DP_PIN();
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
-        const int cb = ks, nb = ks ^ 1;
-        const bool fetch = ks == 0 || !last;
         const int r_stage = ks == 0 ? c_stage : n_stage, r_ks = ks == 0 ? 1 : 0;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          acc[g][0] = mfma16<F16>(fb[cb][0].v, fa[cb][g].v, acc[g][0]);
-          DP_PIN();
-          if (fetch) read_frag(nb, 2 * g, r_stage, r_ks);
-          DP_PIN();
-          acc[g][1] = mfma16<F16>(fb[cb][1].v, fa[cb][g].v, acc[g][1]);
-          DP_PIN();
-          if (fetch) read_frag(nb, 2 * g + 1, r_stage, r_ks);
-          DP_PIN();
-          acc[g][2] = mfma16<F16>(fb[cb][2].v, fa[cb][g].v, acc[g][2]);
-          DP_PIN();
-          if (g & 1)
-            prefetch_issue_b(ks * 2 + (g >> 1));
-          else
-            prefetch_issue_a(ks * 2 + (g >> 1));
-          DP_PIN();
-          acc[g][3] = mfma16<F16>(fb[cb][3].v, fa[cb][g].v, acc[g][3]);
-          DP_PIN();
-        }
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+          for (int y = 0; y < 2; ++y) {
+            acc[g][y] = mfma16<F16>(fb[ks][y].v, fa[ks][g].v, acc[g][y]);
+            DP_PIN();
+            const int slot = 2 * g + y;
+            if (slot < 6)
+              read_frag(ks ^ 1, slot, r_stage, r_ks);
+            else
+              prefetch_issue(2 * (slot - 6) + ks);
+            DP_PIN();
+          }
       }
       prefetch_advance();
       c_stage = n_stage;
     };
-
     bool first = true;
     while (c_i < B) {
       const float c = C[c_i];
-      if (!first) {
-        // re-express the accumulator in this sample's weight
-        // In place on the accumulator registers, four at a time, from assembly: left to the
-        // compiler this block wants every accumulator in a VGPR at once and spills the loop's
-        // operands.  The s_nop pairs cover the MFMA-result -> VALU-read and the
-        // accumulator-write -> MFMA-read wait states, which the compiler does not track
-        // through inline assembly.
-        const float f = held / c;
-        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-        if (f != 1.f)                       // equal weights (e.g. nothing clipped): nothing to do
+      const float f = first ? 1.f : held / c;            // re-express the accumulator in this sample's weight
+      first = false;
+      held = c;
+      if (f != 1.f)
 #pragma unroll
         for (int x = 0; x < 4; ++x)
 #pragma unroll
-          for (int y = 0; y < 4; ++y)
+          for (int y = 0; y < 2; ++y)
 #pragma unroll
-            for (int h = 0; h < 4; ++h) {
-              float e0 = acc[x][y][4 * h], e1 = acc[x][y][4 * h + 1], e2 = acc[x][y][4 * h + 2],
-                    e3 = acc[x][y][4 * h + 3];
-              float t0, t1, t2, t3;
-              asm volatile(
-                  "v_accvgpr_read_b32 %4, %0\n\tv_accvgpr_read_b32 %5, %1\n\t"
-                  "v_accvgpr_read_b32 %6, %2\n\tv_accvgpr_read_b32 %7, %3\n\t"
-                  "v_mul_f32 %4, %8, %4\n\tv_mul_f32 %5, %8, %5\n\t"
-                  "v_mul_f32 %6, %8, %6\n\tv_mul_f32 %7, %8, %7\n\t"
-                  "v_accvgpr_write_b32 %0, %4\n\tv_accvgpr_write_b32 %1, %5\n\t"
-                  "v_accvgpr_write_b32 %2, %6\n\tv_accvgpr_write_b32 %3, %7"
-                  : "+a"(e0), "+a"(e1), "+a"(e2), "+a"(e3), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3)
-                  : "v"(f));
-              acc[x][y][4 * h] = e0;
-              acc[x][y][4 * h + 1] = e1;
-              acc[x][y][4 * h + 2] = e2;
-              acc[x][y][4 * h + 3] = e3;
-            }
-        asm volatile("s_nop 7" ::: "memory");
-      }
-      first = false;
-      held = c;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) read_frag(0, q, c_stage, 0);
-      for (int kb = 0; kb + 1 < nkb; ++kb) block(std::false_type{});
-      block(std::true_type{});
+            for (int r = 0; r < 16; ++r) acc[x][y][r] *= f;
+      for (int kb = 0; kb < nkb; ++kb) block();
       ++c_i;
       while (c_i < B && C[c_i] == 0.f) ++c_i;
     }
@@ -289,10 +243,10 @@ clipped_grad_big_kernel(const GroupArgs ga, const float* __restrict__ C_global, 
 #pragma unroll
     for (int x = 0; x < 4; ++x)
 #pragma unroll
-      for (int y = 0; y < 4; ++y) {
+      for (int y = 0; y < 2; ++y) {
         const int row = m0 + wm + x * 32 + (lane & 31);
         const int col0 = n0 + wn + y * 32 + 4 * (lane >> 5);
-        const size_t base = (size_t)row * p + col0;                  // + 8 q: columns col0 + 8 q ..
+        const size_t base = (size_t)row * p + col0;
         float v[16];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -520,11 +474,11 @@ clipped_grad_tail_kernel(const GroupArgs ga, const float* __restrict__ C_all, in
 
 int clipped_grad_big_tiles(int d, int p) { return ((d + BM - 1) / BM) * ((p + BN - 1) / BN); }
 
-// The kernel addresses each sample's slab of a layer with 32-bit byte offsets and uses
-// bit 31 as the "fetch zeros" marker, so a slab must be smaller than 2 GiB; k-blocks must
-// not straddle samples, so T must be a multiple of the k-block.
+// The kernel addresses each sample's slab of a layer with 32-bit byte offsets and uses bit 31 as
+// the "fetch zeros" marker; offsets run up to the end of the last, perhaps partial, k-block.
 bool clipped_grad_big_supports(int T, int d, int p) {
-  return T % BK == 0 && (int64_t)T * d * 2 < (int64_t)1 << 31 && (int64_t)T * p * 2 < (int64_t)1 << 31;
+  const int64_t rows = ((int64_t)T + BK - 1) / BK * BK;
+  return rows * d * 2 < (int64_t)1 << 31 && rows * p * 2 < (int64_t)1 << 31;
 }
 
 // Tiles left for the tail kernel: the last n mod 256 tiles of the launch when they are few.

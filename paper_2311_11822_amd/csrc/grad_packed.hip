@@ -2,8 +2,8 @@
 // samples and for narrow layers:   grad[j,k] = sum_r C_{r / T} a[r,j] g[r,k],   r = 0 .. B T - 1.
 //
 // The kernels that keep the weights out of the operands (grad_gemm.hip, tn_tile.h) re-express
-// their accumulator at every sample boundary and pad every sample to whole 32-row k-blocks: about four
-// k-blocks' time per sample plus the padding, which at T = 1 is all they do.  Here the rows of all
+// their accumulator at every sample boundary and pad every sample to whole 32-row k-blocks: at T = 1
+// that is all they do.  Here the rows of all
 // samples form one contraction of B T rows and the weight is multiplied into the a operand in fp32;
 // that product is then cut into three bfloat16 parts, whose sum is within 2^-25 of the product, so each
 // 16-row step takes three matrix instructions and less is lost than by rounding C a to fp32.  fp16
@@ -11,8 +11,7 @@
 // against 64 bits: 1.7e-7 (T = 1, B = 512), 2.1e-7 (T = 31) here, 6.0e-7 and 3.9e-7 in the large-tile kernel.
 //   Measured, eight layers of 1024 x 1024 .. 4096 outputs, bf16: B = 512, T = 1: 1384 us before, 86 us here;
 // 4096 rows: 560 us here whatever T is (what bounds it: the matrix cores at the clock they hold under
-// load, then the cutting), the large-tile kernel 789 us at T = 16, 651 at 32, 412 at 64; fp16 here
-// 1100 us.  grad_kernel_of (dp_api.hip) draws its line there.
+// load, then the cutting), fp16 1080 us; the large-tile kernel 684 us at T = 16, 352 at 32.  grad_kernel_of (dp_api.hip) draws its line there.
 //
 // Tiles (four waves, 32 gradient rows each where the layer is wide): 128 x 128, or 128 x 32 / 32 x 128 for layers
 // narrower than a tile, where the stream over the wide operand is the bound and padding the
@@ -160,7 +159,7 @@ __device__ __forceinline__ f32x16 retry_piece(const uint16_t* a, const uint16_t*
   return total;
 }
 
-template <class S, bool F16, bool NOISE, bool OUT16>
+template <class S, bool F16, bool NOISE>
 __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int tile, int B, bool accumulate,
                                             const float* C, const NoiseArgs& na, unsigned lds0) {
   const int T = ly.T, d = ly.d_in, p = ly.d_out;
@@ -323,40 +322,42 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       float old[4] = {0.f, 0.f, 0.f, 0.f};
-      if (accumulate && row < d && col0 + 8 * q < p) load_old4<F16, OUT16, true>(out, base + 8 * q, old);
+      if (accumulate && row < d && col0 + 8 * q < p) load_old4<F16, false, true>(out, base + 8 * q, old);
 #pragma unroll
       for (int k = 0; k < 4; ++k) v[4 * q + k] = accumulate ? old[k] + acc[y][4 * q + k] : acc[y][4 * q + k];
     }
     if (NOISE) tile_noise(v, tn, m0 + wm, n0 + wn + 32 * y, d, p, lane);
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      if (row < d && col0 + 8 * q < p) store4<F16, OUT16>(out, base + 8 * q, v + 4 * q);
+      if (row < d && col0 + 8 * q < p) store4<F16, false>(out, base + 8 * q, v + 4 * q);
   }
 }
 
 // GroupLayer::path holds the layer's tile shape (packed_shape).
-template <bool F16, bool NOISE, bool OUT16>
+template <bool F16, bool NOISE>
 __global__ void __launch_bounds__(NT, 2)
 grad_packed_kernel(const GroupArgs ga, const float* __restrict__ C_all, const NoiseArgs na) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
   const unsigned lds0 = (unsigned)(uintptr_t)lds_raw;
-  // tiles of one row share a panel of a: consecutive numbers meet in one XCD's L2
-  const int item = contiguous_eighth(blockIdx.x, ga.total_blocks);
+  // Tiles of one row share a panel of a: runs of 32 consecutive numbers meet in one XCD's L2.  (Not
+  // an eighth of the launch each: a shard's noise lies in consecutive tiles and would land on few XCDs;
+  // noise on an eighth of 12.6 M elements, eight layers, B = 512: DPN us against DPO us.)
+  const int item = grad_logical_tile(blockIdx.x, ga.total_blocks);
   const int l = layer_of(ga, item);
   const GroupLayer& ly = ga.layer[l];
   const float* C = C_all + ly.c_off;
   const int tile = item - ly.tile_begin;
   if (ly.path == 0)
-    packed_tile<Wide, F16, NOISE, OUT16>(ly, l, tile, ga.B, ga.accumulate, C, na, lds0);
+    packed_tile<Wide, F16, NOISE>(ly, l, tile, ga.B, ga.accumulate, C, na, lds0);
   else if (ly.path == 1)
-    packed_tile<Tall, F16, NOISE, OUT16>(ly, l, tile, ga.B, ga.accumulate, C, na, lds0);
+    packed_tile<Tall, F16, NOISE>(ly, l, tile, ga.B, ga.accumulate, C, na, lds0);
   else
-    packed_tile<Flat, F16, NOISE, OUT16>(ly, l, tile, ga.B, ga.accumulate, C, na, lds0);
+    packed_tile<Flat, F16, NOISE>(ly, l, tile, ga.B, ga.accumulate, C, na, lds0);
 }
 
-template <bool F16, bool NOISE, bool OUT16>
+template <bool F16, bool NOISE>
 dp_status launch_t(const GroupArgs& ga, const float* C, const NoiseArgs& na, hipStream_t s) {
-  auto kernel = grad_packed_kernel<F16, NOISE, OUT16>;
+  auto kernel = grad_packed_kernel<F16, NOISE>;
   static ReadyTable ready;
   dp_status st = allow_big_lds(kernel, LDS_BYTES, ready);
   if (st != DP_OK) return st;
@@ -387,19 +388,14 @@ bool grad_packed_supports(int B, int T, int d, int p) {
   return rows * d * 2 < (int64_t)1 << 31 && rows * p * 2 < (int64_t)1 << 31;
 }
 
-dp_status launch_grad_packed_group(const GroupArgs& ga, const float* C, const NoiseArgs* noise, hipStream_t s,
-                                   bool out16) {
+dp_status launch_grad_packed_group(const GroupArgs& ga, const float* C, const NoiseArgs* noise, hipStream_t s) {
   static const NoiseArgs none = {};
   const NoiseArgs& na = noise ? *noise : none;
-  switch ((ga.f16 ? 4 : 0) + (noise ? 2 : 0) + (out16 ? 1 : 0)) {
-    case 0: return launch_t<false, false, false>(ga, C, na, s);
-    case 1: return launch_t<false, false, true>(ga, C, na, s);
-    case 2: return launch_t<false, true, false>(ga, C, na, s);
-    case 3: return launch_t<false, true, true>(ga, C, na, s);
-    case 4: return launch_t<true, false, false>(ga, C, na, s);
-    case 5: return launch_t<true, false, true>(ga, C, na, s);
-    case 6: return launch_t<true, true, false>(ga, C, na, s);
-    default: return launch_t<true, true, true>(ga, C, na, s);
+  switch ((ga.f16 ? 2 : 0) + (noise ? 1 : 0)) {
+    case 0: return launch_t<false, false>(ga, C, na, s);
+    case 1: return launch_t<false, true>(ga, C, na, s);
+    case 2: return launch_t<true, false>(ga, C, na, s);
+    default: return launch_t<true, true>(ga, C, na, s);
   }
 }
 

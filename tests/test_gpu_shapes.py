@@ -176,3 +176,15 @@ def test_ghost_norm_of_short_samples(dtype, B, T, d, p):
     # sums of d + p exact products: relative to the sum of their magnitudes, which the diagonal bounds
     np.testing.assert_allclose(host(out)[:B], want, rtol=TOL)
     assert host(out)[B] == -1.0
+
+
+# Token counts that end inside a 32-token k-block: last block of 1, 16, 17 and 31 rows, one block only,
+# on large tiles (56 of 256 x 256) and on the sub-tiles that small launches take.
+@pytest.mark.parametrize("dtype", HALF)
+@pytest.mark.parametrize("B,T,dims", [
+    (3, 49, [(1800, 1544)]), (2, 65, [(1800, 1544), (136, 520)]), (3, 100, [(264, 136), (128, 2048)]),
+    (2, 127, [(1800, 1544)]), (1, 80, [(1800, 1544)]),
+])
+def test_ragged_tokens(dtype, B, T, dims):
+    check_step(dtype, B, T, dims, paths=[0] * len(dims))
+    check_step(dtype, B, T, dims, mode=o.CLIP_AUTOMATIC, mask=[1] if B > 1 else ())
