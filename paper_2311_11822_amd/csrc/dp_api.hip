@@ -13,10 +13,6 @@ namespace {
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-#ifndef DP_PEREX_DMA
-#define DP_PEREX_DMA true
-#endif
-
 bool dtype_ok(dp_dtype dt) { return dt == DP_F32 || dt == DP_BF16 || dt == DP_F16; }
 
 bool dims_ok(dp_dtype dt, int B, int T, int d, int p) {
@@ -46,6 +42,11 @@ int tiles_per_sample(int path, const dp_layer& ly) {
   if (path == DP_PATH_PEREX) return perex_tiles_per_sample(ly.d_in, ly.d_out);
   if (ghost_uses_sample(ly)) return 1;
   return ghost_uses_big(ly) ? ghost_big_tiles_per_sample(ly.T) : ghost_tiles_per_sample(ly.T);
+}
+
+// Instantiated norm on n_big tiles of 256 x 256 or n_mid of 128 x 128?
+bool perex_on_big_tiles(int64_t n_big, int64_t n_mid) {
+  return kBigRoundCost * ((n_big + kBigRound - 1) / kBigRound) < kMidRoundCost * ((n_mid + kMidRound - 1) / kMidRound);
 }
 
 // Launches the norm kernels of one path for the listed layers, in chunks of kMaxGroup.
@@ -101,14 +102,29 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
       continue;
     }
     // instantiated norm: the kernel with the deep load pipeline unless a slab is beyond its
-    // 32-bit addressing (both use the same tiles and partial-sum slots)
-    bool dma = DP_PEREX_DMA;
+    // 32-bit addressing, on large tiles (fewer partial sums in the same slots) where they pay
+    bool dma = kernel == kPerex, big = false;
     for (int j = 0; j < ga.n_layers; ++j)
       dma = dma && perex_dma_supports(ga.layer[j].T, ga.layer[j].d_in, ga.layer[j].d_out);
+    if (dma) {
+      int64_t n = 0;
+      for (int j = 0; j < ga.n_layers; ++j) n += (int64_t)clipped_grad_big_tiles(ga.layer[j].d_in, ga.layer[j].d_out) * B;
+      big = perex_on_big_tiles(n, blocks);
+      if (big) {
+        blocks = 0;
+        for (int j = 0; j < ga.n_layers; ++j) {
+          GroupLayer& gl = ga.layer[j];
+          gl.tile_begin = (int)blocks;
+          gl.tiles_per_sample = clipped_grad_big_tiles(gl.d_in, gl.d_out);
+          blocks += (int64_t)gl.tiles_per_sample * B;
+        }
+        ga.total_blocks = (int)blocks;
+      }
+    }
     dp_status st = kernel == kGhostBig      ? launch_ghost_big_group(ga, partials, s)
                    : kernel == kGhostSmall  ? launch_ghost_group(ga, partials, s)
                    : kernel == kGhostSample ? launch_ghost_sample_group(ga, partials, s)
-                   : dma                    ? launch_perex_dma_group(ga, partials, s)
+                   : dma                    ? launch_perex_dma_group(ga, partials, big, s)
                                             : launch_perex_group(ga, partials, s);
     if (st != DP_OK) return st;
     st = launch_norm_reduce_group(ga, partials, sqnorm_out, s);

@@ -128,15 +128,23 @@ int64_t clipped_grad_f32_tiles(int d, int p);
 dp_status launch_norms_f32_group(const GroupArgs& ga, float* sqnorm, hipStream_t s);
 dp_status launch_clipped_grad_f32_group(const GroupArgs& ga, const float* C, const NoiseArgs& na, hipStream_t s);
 
+// Tiles of tn_pipeline.h.  A launch runs in rounds of the tiles that are resident at a time: 256 large ones
+// (one per compute unit) or 512 of 128 x 128 (two), and a round of the latter, half the work, takes three
+// fifths of the time (measured on 1024-wide layers, 2048 tokens: 57 us and 34 us).  So large tiles
+// where they come in whole rounds, small ones where few tiles or padding would leave large ones idle.
+constexpr int kBigRound = 256, kMidRound = 512;
+constexpr int kBigRoundCost = 5, kMidRoundCost = 3;
+
 // bf16 MFMA kernels, grouped over layers.
 int ghost_tiles_per_sample(int T);
 int perex_tiles_per_sample(int d, int p);
 int clipped_grad_tiles(int d, int p);
 dp_status launch_ghost_group(const GroupArgs& ga, float* partials, hipStream_t s);
 dp_status launch_perex_group(const GroupArgs& ga, float* partials, hipStream_t s);
-// Same tiles and partial-sum slots with direct global->LDS loads, three k-blocks ahead (perex_dma.hip).
+// With direct global->LDS loads, three k-blocks ahead (perex_dma.hip); tiles of 128 x 128 as above or, `big`,
+// of 256 x 256 (ga laid out for clipped_grad_big_tiles tiles per sample).
 bool perex_dma_supports(int T, int d, int p);
-dp_status launch_perex_dma_group(const GroupArgs& ga, float* partials, hipStream_t s);
+dp_status launch_perex_dma_group(const GroupArgs& ga, float* partials, bool big, hipStream_t s);
 dp_status launch_norm_reduce_group(const GroupArgs& ga, const float* partials, float* sqnorm_out,
                                    hipStream_t s);
 dp_status launch_clipped_grad_group(const GroupArgs& ga, const float* C, hipStream_t s);

@@ -179,12 +179,22 @@ def test_ghost_norm_of_short_samples(dtype, B, T, d, p):
 
 
 # Token counts that end inside a 32-token k-block: last block of 1, 16, 17 and 31 rows, one block only,
-# on large tiles (56 of 256 x 256) and on the sub-tiles that small launches take.
+# on large tiles (168 of 256 x 256) and on the sub-tiles that smaller launches take (56 and a few tiles, and
+# 160 tiles whose padding makes sub-tiles the better choice).
 @pytest.mark.parametrize("dtype", HALF)
 @pytest.mark.parametrize("B,T,dims", [
     (3, 49, [(1800, 1544)]), (2, 65, [(1800, 1544), (136, 520)]), (3, 100, [(264, 136), (128, 2048)]),
     (2, 127, [(1800, 1544)]), (1, 80, [(1800, 1544)]),
+    (2, 49, [(2824, 3336)]), (2, 21, [(264, 264)] * 40),
 ])
 def test_ragged_tokens(dtype, B, T, dims):
     check_step(dtype, B, T, dims, paths=[0] * len(dims))
     check_step(dtype, B, T, dims, mode=o.CLIP_AUTOMATIC, mask=[1] if B > 1 else ())
+
+
+# Instantiated norms and kept gradients on 256 x 256 tiles (168 of them, 572 of 128 x 128) and on 128 x 128 ones, odd
+# and even numbers of k-blocks, a last block that is not full.
+@pytest.mark.parametrize("dtype", HALF)
+@pytest.mark.parametrize("B,T,dims", [(4, 40, [(1544, 1288)]), (3, 97, [(392, 136)]), (2, 64, [(128, 264)])])
+def test_instantiated_norm_tiles(dtype, B, T, dims):
+    check_step(dtype, B, T, dims, paths=[1] * len(dims))
