@@ -51,8 +51,8 @@ bool perex_on_big_tiles(int64_t n_big, int64_t n_mid) {
 
 // Launches the norm kernels of one path for the listed layers, in chunks of kMaxGroup.
 // part_begin[l] is the layer's first slot in the partial-sum workspace.
-enum NormKernel { kGhostBig = 0, kGhostSmall = 1, kPerex = 2, kGhostSample = 3, kGhostBrief = 4 };
-constexpr int kNormKernels = 5;
+enum NormKernel { kGhostBig = 0, kGhostSmall = 1, kPerex = 2, kGhostSample = 3, kGhostBrief = 4, kPerexNarrow = 5 };
+constexpr int kNormKernels = 6;
 
 dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, int n_which,
                         const int64_t* part_begin, dp_dtype dt, int B, float* partials,
@@ -63,7 +63,7 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
   // the order inside a launch is free.  (Stable insertion sort in place: this path must not
   // touch the heap, see dp_norms_multi_static.)
   auto length = [&](int l) {
-    return kernel == kPerex ? (int64_t)layers[l].T : (int64_t)layers[l].d_in + layers[l].d_out;
+    return kernel == kPerex || kernel == kPerexNarrow ? (int64_t)layers[l].T : (int64_t)layers[l].d_in + layers[l].d_out;
   };
   for (int i = 1; i < n_which; ++i) {
     const int x = which[i];
@@ -83,11 +83,11 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
       GroupLayer& gl = ga.layer[j];
       gl.a = layers[l].a;
       gl.g = layers[l].g;
-      gl.out = kernel == kPerex && kept ? kept[l] : nullptr;
+      gl.out = (kernel == kPerex || kernel == kPerexNarrow) && kept ? kept[l] : nullptr;
       gl.T = layers[l].T;
       gl.d_in = layers[l].d_in;
       gl.d_out = layers[l].d_out;
-      gl.path = kernel == kPerex ? DP_PATH_PEREX : DP_PATH_GHOST;
+      gl.path = layers[l].path;
       gl.tile_begin = (int)blocks;
       gl.sq_index = row_of ? row_of[l] : l;
       gl.part_begin = (int)part_begin[l];
@@ -124,6 +124,7 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
     dp_status st = kernel == kGhostBig      ? launch_ghost_big_group(ga, partials, s)
                    : kernel == kGhostSmall  ? launch_ghost_group(ga, partials, s)
                    : kernel == kGhostSample ? launch_ghost_sample_group(ga, partials, s)
+                   : kernel == kPerexNarrow ? launch_perex_narrow_group(ga, partials, s)
                    : dma                    ? launch_perex_dma_group(ga, partials, big, s)
                                             : launch_perex_group(ga, partials, s);
     if (st != DP_OK) return st;
@@ -200,7 +201,8 @@ dp_status norms_impl(const dp_layer* layers, int L, dp_dtype dt, int B, float* s
   for (int k = 0; k < kNormKernels; ++k) list[k] = idx + (size_t)k * L;
   int count[kNormKernels] = {};
   for (int l = 0; l < L; ++l) {
-    const int k = layers[l].path == DP_PATH_PEREX ? kPerex
+    const bool narrow = perex_narrow_supports(layers[l].T, layers[l].d_in, layers[l].d_out);
+    const int k = layers[l].path == DP_PATH_PEREX ? (narrow ? kPerexNarrow : kPerex)
                   : ghost_brief_supports(layers[l].T) ? kGhostBrief
                   : ghost_uses_sample(layers[l])  ? kGhostSample
                   : ghost_uses_big(layers[l])     ? kGhostBig

@@ -145,6 +145,9 @@ dp_status launch_perex_group(const GroupArgs& ga, float* partials, hipStream_t s
 // of 256 x 256 (ga laid out for clipped_grad_big_tiles tiles per sample).
 bool perex_dma_supports(int T, int d, int p);
 dp_status launch_perex_dma_group(const GroupArgs& ga, float* partials, bool big, hipStream_t s);
+// Narrow layers on tiles of the 128 x 128 ones' numbering (perex_narrow.hip).
+bool perex_narrow_supports(int T, int d, int p);
+dp_status launch_perex_narrow_group(const GroupArgs& ga, float* partials, hipStream_t s);
 dp_status launch_norm_reduce_group(const GroupArgs& ga, const float* partials, float* sqnorm_out,
                                    hipStream_t s);
 dp_status launch_clipped_grad_group(const GroupArgs& ga, const float* C, hipStream_t s);

@@ -13,7 +13,7 @@
 // 4096 rows: 560 us here whatever T is (what bounds it: the matrix cores at the clock they hold under
 // load, then the cutting), fp16 1080 us; the large-tile kernel 684 us at T = 16, 352 at 32.  grad_kernel_of (dp_api.hip) draws its line there.
 //
-// Tiles (four waves, 32 gradient rows each where the layer is wide): 128 x 128, or 128 x 32 / 32 x 128 for layers
+// Tiles (four waves, 32 gradient rows each where the layer is wide): 128 x 128, or 128 x 32, 128 x 64 and their transposes for layers
 // narrower than a tile, where the stream over the wide operand is the bound and padding the
 // narrow one to 128 would multiply its LDS traffic.  Operand rows go global -> LDS without passing
 // through registers, four stages of 32 rows, three blocks in flight; the 32 rows' weights travel
@@ -25,7 +25,7 @@
 // a wave that finds a NaN among its sums forms its tile again, sample by sample in fp32, without the split.
 #include "dp_internal.h"
 #include "grad_epilogue.h"
-#include "lds_dma.h"
+#include "row_tile.h"
 #include "tile_order.h"
 
 namespace dpbk {
@@ -42,60 +42,15 @@ struct Shape {
   static constexpr int A_BYTES = BK * BM * 2, B_BYTES = BK * BN * 2;
   static constexpr int W_BYTES = 256;                          // weights of the 32 rows (twice)
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES + W_BYTES;
-  static constexpr int LOADS = (BM == 128 ? 2 : 1) + (BN == 128 ? 2 : 1) + 1;     // per wave per k-block
-  static_assert(BM / WM == 32 && WM * WN == 4 && (BM == 128 || BM == 32) && (BN == 128 || BN == 32), "shape");
+  static constexpr int LOADS = kRowLoads<BM> + kRowLoads<BN> + 1;                 // per wave per k-block
+  static_assert(BM / WM == 32 && WM * WN == 4, "shape");
 };
 using Wide = Shape<128, 128, 4, 1>;
 using Tall = Shape<128, 32, 4, 1>;
+using Tall2 = Shape<128, 64, 4, 1>;
 using Flat = Shape<32, 128, 1, 4>;
+using Flat2 = Shape<64, 128, 2, 2>;
 constexpr int LDS_BYTES = NSTAGE * Wide::STAGE_BYTES;          // 65 KiB: two workgroups per compute unit
-
-// One operand (W = 128 or 32 columns of a row-major [rows, width] matrix) on its way to LDS.
-// W = 128: load j of a wave covers rows 16 j + 4 wave + (lane >> 4), 16 chunks of 16 bytes each; the
-// lane's chunk c holds logical chunk c ^ ((row & 3) << 2), which spreads the four consecutive rows
-// of a transposing read over the banks.  W = 32: one load of half the lanes covers rows
-// 8 wave + (lane >> 2); rows are 64 bytes, so four of them span the banks as they lie.
-template <int W>
-struct Operand {
-  i32x4 rsrc;
-  unsigned v, step;                // byte offset of this lane's chunk; bytes per 16 rows
-  unsigned lds;                    // first LDS byte of this wave's loads inside a stage
-  __device__ __forceinline__ void init(const void* base, int64_t rows, int width, int col0, unsigned lds_base, int wave,
-                                       int lane) {
-    rsrc = make_rsrc(base, (unsigned)(rows * width * 2));
-    const int row = W == 128 ? wave * 4 + (lane >> 4) : wave * 8 + ((lane >> 2) & 7);
-    const int chunk = W == 128 ? (lane & 15) ^ ((row & 3) << 2) : lane & 3;
-    v = col0 + chunk * 8 < width ? (unsigned)(row * width + col0 + chunk * 8) * 2u : OOB;
-    step = 32u * width;
-    lds = lds_base + (W == 128 ? wave * 1024 : wave * 512);
-  }
-  __device__ __forceinline__ void issue(unsigned stage_off, int lane) {
-    if (W == 128) {
-      load_to_lds(rsrc, v, 0, lds + stage_off);
-      load_to_lds(rsrc, v + step, 0, lds + stage_off + 4096);
-    } else if (lane < 32) {
-      load_to_lds(rsrc, v, 0, lds + stage_off);
-    }
-    v += 2 * step;                 // rows past the last one lie past the descriptor's size: zeros
-  }
-};
-
-// LDS byte of a lane's first transposing read of the 32-column tile at col0 (see tn_tile.h): k row
-// 8 (b >> 1) + (s >> 2), columns 16 (b & 1) + 4 (s & 3) with b = lane >> 4, s = lane & 15.
-template <int W>
-__device__ __forceinline__ unsigned frag_base(int col0, int lane) {
-  const int b = lane >> 4, s = lane & 15;
-  const int row = 8 * (b >> 1) + (s >> 2), col = col0 + 16 * (b & 1) + 4 * (s & 3);
-  const int chunk = W == 128 ? (col >> 3) ^ ((row & 3) << 2) : col >> 3;
-  return row * (W * 2) + (chunk << 4) + (s & 1) * 8;
-}
-template <int W>
-__device__ __forceinline__ bf16x8 read_frag(unsigned addr) {
-  Frag f;
-  f.h[0] = lds_read_tr(addr);
-  f.h[1] = lds_read_tr(addr + 4 * W * 2);
-  return f.v;
-}
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
@@ -170,8 +125,8 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave / S::WN) * 32, wn = (wave % S::WN) * (S::BN / S::WN);
 
-  Operand<S::BM> oa;
-  Operand<S::BN> ob;
+  RowOperand<S::BM> oa;
+  RowOperand<S::BN> ob;
   oa.init(ly.a, rows, d, m0, lds0, wave, lane);
   ob.init(ly.g, rows, p, n0, lds0 + S::A_BYTES, wave, lane);
   // weights: lane -> row (lane & 31) of the k-block, sample w_i and token w_t of that row
@@ -193,10 +148,10 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
     p_stage = p_stage + 1 == NSTAGE ? 0 : p_stage + 1;
   };
 
-  const unsigned a_rd = lds0 + frag_base<S::BM>(wm, lane);
+  const unsigned a_rd = lds0 + row_frag_base<S::BM>(wm, lane);
   unsigned b_rd[S::TN];
 #pragma unroll
-  for (int y = 0; y < S::TN; ++y) b_rd[y] = lds0 + S::A_BYTES + frag_base<S::BN>(wn + 32 * y, lane);
+  for (int y = 0; y < S::TN; ++y) b_rd[y] = lds0 + S::A_BYTES + row_frag_base<S::BN>(wn + 32 * y, lane);
   const unsigned w_rd = lds0 + S::A_BYTES + S::B_BYTES + 32u * (lane >> 5);
 
   typedef __attribute__((ext_vector_type(4))) float f4;
@@ -224,10 +179,10 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
       const lds_f4* wp = (const lds_f4*)(uintptr_t)(w_rd + so + ks * 64);
       w[ks][0] = wp[0];
       w[ks][1] = wp[1];
-      fa[ks] = __builtin_bit_cast(u32x4, read_frag<S::BM>(a_rd + so + ks * 16 * S::BM * 2));
+      fa[ks] = __builtin_bit_cast(u32x4, read_row_frag<S::BM>(a_rd + so + ks * 16 * S::BM * 2));
 #pragma unroll
       for (int y = 0; y < S::TN; ++y)
-        fb[ks][y] = __builtin_bit_cast(u32x4, read_frag<S::BN>(b_rd[y] + so + ks * 16 * S::BN * 2));
+        fb[ks][y] = __builtin_bit_cast(u32x4, read_row_frag<S::BN>(b_rd[y] + so + ks * 16 * S::BN * 2));
     }
     DP_PIN();
     float least = fabsf(w[0][0][0]);
@@ -347,12 +302,16 @@ grad_packed_kernel(const GroupArgs ga, const float* __restrict__ C_all, const No
   const GroupLayer& ly = ga.layer[l];
   const float* C = C_all + ly.c_off;
   const int tile = item - ly.tile_begin;
-  if (ly.path == 0)
-    packed_tile<Wide, F16, NOISE>(ly, l, tile, ga.B, ga.accumulate, C, na, lds0);
-  else if (ly.path == 1)
-    packed_tile<Tall, F16, NOISE>(ly, l, tile, ga.B, ga.accumulate, C, na, lds0);
-  else
-    packed_tile<Flat, F16, NOISE>(ly, l, tile, ga.B, ga.accumulate, C, na, lds0);
+  auto run = [&](auto shape) {
+    packed_tile<decltype(shape), F16, NOISE>(ly, l, tile, ga.B, ga.accumulate, C, na, lds0);
+  };
+  switch (ly.path) {
+    case 0: run(Wide{}); break;
+    case 1: run(Tall{}); break;
+    case 2: run(Flat{}); break;
+    case 3: run(Tall2{}); break;
+    default: run(Flat2{});
+  }
 }
 
 template <bool F16, bool NOISE>
@@ -369,14 +328,15 @@ int tiles_of(int d, int p, int bm, int bn) { return ((d + bm - 1) / bm) * ((p + 
 
 }  // namespace
 
-// A layer of up to 64 columns (rows) takes 32-wide tiles along that side: at most two of them, so
-// the other operand is read at most twice.
-int grad_packed_shape(int d, int p) { return p <= 64 ? 1 : d <= 64 ? 2 : 0; }
+// A layer of up to 64 columns (rows) takes a tile that covers that side, so the other operand is read once.
+int grad_packed_shape(int d, int p) { return p <= 32 ? 1 : d <= 32 ? 2 : p <= 64 ? 3 : d <= 64 ? 4 : 0; }
 
 int grad_packed_tiles(int d, int p) {
   switch (grad_packed_shape(d, p)) {
     case 1: return tiles_of(d, p, Tall::BM, Tall::BN);
     case 2: return tiles_of(d, p, Flat::BM, Flat::BN);
+    case 3: return tiles_of(d, p, Tall2::BM, Tall2::BN);
+    case 4: return tiles_of(d, p, Flat2::BM, Flat2::BN);
     default: return tiles_of(d, p, Wide::BM, Wide::BN);
   }
 }

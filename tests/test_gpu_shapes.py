@@ -198,3 +198,14 @@ def test_ragged_tokens(dtype, B, T, dims):
 @pytest.mark.parametrize("B,T,dims", [(4, 40, [(1544, 1288)]), (3, 97, [(392, 136)]), (2, 64, [(128, 264)])])
 def test_instantiated_norm_tiles(dtype, B, T, dims):
     check_step(dtype, B, T, dims, paths=[1] * len(dims))
+
+
+# Narrow layers on the instantiated path: sides of up to 32 and up to 64, wide sides off the 128-column tiles, fewer
+# tokens than the stages hold, a last k-block of one row.
+@pytest.mark.parametrize("dtype", HALF)
+@pytest.mark.parametrize("B,T,dims", [
+    (3, 97, [(264, 16), (16, 264), (392, 64), (64, 392)]), (2, 40, [(40, 40), (8, 8), (24, 48), (136, 40)]),
+    (5, 256, [(768, 16), (16, 768)]), (1, 33, [(48, 1032), (1032, 32)]),
+])
+def test_narrow_instantiated(dtype, B, T, dims):
+    check_step(dtype, B, T, dims, paths=[1] * len(dims))
