@@ -763,6 +763,9 @@ namespace {
 // 2.3 ms, 8 layers 1.39 ms, 16 layers 1.38 ms, all norms then all gradients 1.31 ms).
 constexpr int64_t kPassBytes = (int64_t)128 << 20;
 constexpr int64_t kPassTiles = 1024;
+// For the same reason a pass takes the rest of the stack when that would not fill two rounds (24 layers
+// of width 1024, 10 x 100 fp16 tokens: a second pass of the last two layers took 83 of 347 us).
+constexpr int64_t kLastPassTiles = 512;
 
 // Which layers the one-pass kernel takes, and its sample chunks.
 struct FusedPlan {
@@ -869,7 +872,11 @@ dp_status dp_layerwise_clipped_grad(const dp_layer* layers, int L, dp_dtype dt, 
   na.hi = shard_offset + shard_count;
   na.rk = make_round_keys(seed);
 
-  int64_t fused_off = 0;
+  auto pass_tiles = [&](int l) {
+    return fp.shape[l] >= 0 ? (int64_t)0 : (int64_t)clipped_grad_big_tiles(layers[l].d_in, layers[l].d_out);
+  };
+  int64_t fused_off = 0, tiles_left = 0;                 // tiles of the layers from l1 on
+  for (int l = 0; l < L; ++l) tiles_left += pass_tiles(l);
   for (int l0 = 0; l0 < L;) {
     // one pass: consecutive layers whose a and g stay in the memory-side cache between the norm
     // kernels and the gradient kernels (or layers_per_pass of them when the caller says so)
@@ -880,9 +887,11 @@ dp_status dp_layerwise_clipped_grad(const dp_layer* layers, int L, dp_dtype dt, 
       const bool small = fp.shape[l1] >= 0;
       const int64_t lb = small ? 0 : (int64_t)B * layers[l1].T * ((int64_t)layers[l1].d_in + layers[l1].d_out) * esize;
       if (l1 > l0 && (layers_per_pass > 0 ? l1 - l0 >= layers_per_pass
-                                          : bytes + lb > kPassBytes && tiles >= kPassTiles)) break;
+                                          : bytes + lb > kPassBytes && tiles >= kPassTiles &&
+                                                tiles_left >= kLastPassTiles)) break;
       bytes += lb;
-      tiles += small ? 0 : clipped_grad_big_tiles(layers[l1].d_in, layers[l1].d_out);
+      tiles += pass_tiles(l1);
+      tiles_left -= pass_tiles(l1);
       ++l1;
     }
     // (1) layers that fit one workgroup tile: norm, clip factor and weighted sum in one kernel
