@@ -87,6 +87,10 @@ def _stream(stream) -> Optional[int]:
     if stream is not None:
         return stream if isinstance(stream, int) else stream.cuda_stream
     import torch
+    if torch.cuda.is_initialized():
+        # the handle behind current_stream().cuda_stream without building a Stream object (2.9 -> 0.6 us; a step
+        # of one small layer makes three calls in 30 us)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return torch.cuda.current_stream().cuda_stream
 
 
