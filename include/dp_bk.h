@@ -229,9 +229,9 @@ dp_status dp_norms_multi_static(const dp_layer* layers, int L, dp_dtype dt, int 
  *   grad_offset  HOST array of L global element offsets (the layers' places in the flattened
  *                model; they need not be contiguous or ordered, but must not overlap)
  *   sigma, R     as dp_add_noise (sigma >= 0, finite; R > 0; sigma == 0 adds nothing)
- * Layers that the large-tile kernels compute and whose grad_offset is a multiple of 4 get the
- * noise in the kernel's epilogue; for all others the noise pass runs on the layer's slice
- * after its gradient.  Errors as dp_clipped_grad_multi and dp_add_noise.
+ * Layers whose grad_offset is a multiple of 4 (fp32: all) get the noise in the gradient kernel's
+ * epilogue; for the others, and for 16-bit sample slabs of 2 GiB and more, the noise pass runs on the
+ * layer's slice after its gradient.  Errors as dp_clipped_grad_multi and dp_add_noise.
  */
 dp_status dp_clipped_grad_noise_multi(const dp_layer* layers, int L, dp_dtype dt, int B, const float* C,
                                       float* const* grads, const uint64_t* grad_offset, int accumulate,
@@ -326,7 +326,8 @@ dp_status dp_clipped_grad_kept_multi(const dp_layer* layers, int L, dp_dtype dt,
  *                sigma == 0 or shard_count == 0)
  *   sqnorm_out, C_out   device, [L, B] fp32, overwritten
  *   ws           device scratch >= dp_layerwise_workspace_bytes(...), 16-byte aligned
- *   layers_per_pass   0: a pass ends once it holds 128 MiB of a and g and 1024 gradient tiles;
+ *   layers_per_pass   0: a pass ends once it holds 128 MiB of a and g and 1024 gradient tiles,
+ *                     unless fewer than 512 tiles are left;
  *                     > 0: that many layers per pass
  */
 size_t dp_layerwise_workspace_bytes(const dp_layer* layers, int L, dp_dtype dt, int B);

@@ -29,8 +29,8 @@ dp_status check_layer_ptrs(const void* a, const void* g) {
   return DP_OK;
 }
 
-// Ghost layers with whole 64-wide k-blocks and more than a handful of tokens take the
-// large-tile kernel; the rest take the 128x128-tile kernel with per-chunk edge handling.
+// Ghost layers of more than a handful of tokens take the large-tile kernel; the rest take the
+// 128x128-tile kernel with per-chunk edge handling.
 bool ghost_uses_big(const dp_layer& ly) {
   return ly.T >= 96 && ghost_big_supports(ly.T, ly.d_in, ly.d_out);
 }

@@ -58,7 +58,9 @@ constexpr int load_slot(int mi, int per_ks, int x) {
   return x == 0 ? 3 : 6;                                       // 8 MFMAs, two loads
 }
 
-template <bool COMPACT, bool F16>
+// RAGGED: some width is no multiple of the k-block.  (Kept apart: the test for an operand's last block costs
+// whole-block layers of 2048 tokens 2.7 %.)
+template <bool COMPACT, bool F16, bool RAGGED>
 __global__ void __launch_bounds__(NT)
 ghost_big_kernel(const GroupArgs ga, float* __restrict__ partials) {
   constexpr int STAGE_BYTES = Plan<COMPACT>::STAGE_BYTES, NSTAGE = Plan<COMPACT>::NSTAGE;
@@ -91,7 +93,7 @@ ghost_big_kernel(const GroupArgs ga, float* __restrict__ partials) {
   // Wave-load j of the row block covers rows (wave*8 + j)*8 + (lane >> 3); the lane's LDS chunk
   // (lane & 7) holds logical chunk (lane & 7) ^ ((row >> 1) & 7).  Same for the column block
   // with wave*4 + j.
-  const int nka = ly.d_in / BK, nkg = ly.d_out / BK, nblocks = nka + nkg;
+  const int nka = (ly.d_in + BK - 1) / BK, nkg = (ly.d_out + BK - 1) / BK, nblocks = nka + nkg;
   unsigned vi[LOADS_I], vj[LOADS_J];
   i32x4 rs;
   auto set_operand = [&](const void* base, int width) {
@@ -110,11 +112,29 @@ ghost_big_kernel(const GroupArgs ga, float* __restrict__ partials) {
       vj[j] = (unsigned)(c0 + row) * width * 2u + chunk * 16u;
     }
   };
+  // A width that is no multiple of the k-block: in its last block the lanes whose chunk lies past the
+  // row's end fetch zeros.
+  int columns;                                    // of the operand, from the next block's first one on
+  auto cut_columns = [&]() {
+    if (!RAGGED || columns >= BK) return;
+#pragma unroll
+    for (int j = 0; j < LOADS_I; ++j) {
+      const int row = (wave * li + j) * 8 + (lane >> 3);
+      if ((((lane & 7) ^ ((row >> 1) & 7)) * 8) >= columns) vi[j] = OOB;
+    }
+#pragma unroll
+    for (int j = 0; j < LOADS_J; ++j) {
+      const int row = (wave * LOADS_J + j) * 8 + (lane >> 3);
+      if ((((lane & 7) ^ ((row >> 1) & 7)) * 8) >= columns) vj[j] = OOB;
+    }
+  };
   int p_blk = 0, p_stage = 0;
   unsigned p_soff = 0;
   // this wave's first LDS destination inside a stage, row block and column block
   const unsigned ld_i = lds0 + wave * li * 1024, ld_j = lds0 + I_BYTES + wave * LOADS_J * 1024;
   set_operand(ly.a, ly.d_in);
+  columns = ly.d_in;
+  cut_columns();
   // item in 0 .. LOADS_I + LOADS_J - 1: one wave-load of the row block or of the column block
   auto issue = [&](int item, bool with_j) {
     if (item < LOADS_I)
@@ -125,9 +145,11 @@ ghost_big_kernel(const GroupArgs ga, float* __restrict__ partials) {
   auto advance = [&]() {
     ++p_blk;
     p_soff += BK * 2;
+    columns -= BK;
     p_stage = p_stage + 1 == NSTAGE ? 0 : p_stage + 1;
     if (p_blk == nka) {
       set_operand(ly.g, ly.d_out);
+      columns = ly.d_out;
       p_soff = 0;
     } else if (p_blk == nblocks) {
       // past the end of the stream: keep issuing (the waits count loads) but fetch nothing
@@ -136,7 +158,9 @@ ghost_big_kernel(const GroupArgs ga, float* __restrict__ partials) {
 #pragma unroll
       for (int j = 0; j < LOADS_J; ++j) vj[j] = 0x80000000u;
       p_soff = 0;
+      columns = INT32_MAX;
     }
+    cut_columns();
   };
 
   // ---- LDS -> MFMA operand addressing ---------------------------------------------------
@@ -350,27 +374,34 @@ int ghost_big_tiles_per_sample(int T) {
   return n;
 }
 
-// Needs whole 64-wide k-blocks and 32-bit byte offsets inside a sample's slab.
+// Needs 32-bit byte offsets inside a sample's slab.
 bool ghost_big_supports(int T, int d, int p) {
-  return d % BK == 0 && p % BK == 0 && (int64_t)(T + TI) * d * 2 < (int64_t)1 << 31 &&
+  return (int64_t)(T + TI) * d * 2 < (int64_t)1 << 31 &&
          (int64_t)(T + TI) * p * 2 < (int64_t)1 << 31;
 }
 
-template <bool COMPACT, bool F16>
+template <bool COMPACT, bool F16, bool RAGGED>
 dp_status launch_plan(const GroupArgs& ga, float* partials, hipStream_t s) {
   static ReadyTable ready;
-  auto kernel = ghost_big_kernel<COMPACT, F16>;
+  auto kernel = ghost_big_kernel<COMPACT, F16, RAGGED>;
   dp_status st = allow_big_lds(kernel, Plan<COMPACT>::LDS_BYTES, ready);
   if (st != DP_OK) return st;
   hipLaunchKernelGGL(kernel, dim3(ga.total_blocks), dim3(NT), Plan<COMPACT>::LDS_BYTES, s, ga, partials);
   return hip_status(hipGetLastError());
 }
 
+template <bool COMPACT, bool F16>
+dp_status launch_widths(const GroupArgs& ga, float* partials, hipStream_t s) {
+  bool ragged = false;
+  for (int l = 0; l < ga.n_layers; ++l) ragged = ragged || ga.layer[l].d_in % BK || ga.layer[l].d_out % BK;
+  return ragged ? launch_plan<COMPACT, F16, true>(ga, partials, s) : launch_plan<COMPACT, F16, false>(ga, partials, s);
+}
+
 dp_status launch_ghost_big_group(const GroupArgs& ga, float* partials, hipStream_t s) {
   bool compact = true;
   for (int l = 0; l < ga.n_layers; ++l) compact = compact && ga.layer[l].T <= TI;
-  if (ga.f16) return compact ? launch_plan<true, true>(ga, partials, s) : launch_plan<false, true>(ga, partials, s);
-  return compact ? launch_plan<true, false>(ga, partials, s) : launch_plan<false, false>(ga, partials, s);
+  if (ga.f16) return compact ? launch_widths<true, true>(ga, partials, s) : launch_widths<false, true>(ga, partials, s);
+  return compact ? launch_widths<true, false>(ga, partials, s) : launch_widths<false, false>(ga, partials, s);
 }
 
 }  // namespace dpbk

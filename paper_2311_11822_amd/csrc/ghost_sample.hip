@@ -63,7 +63,7 @@ ghost_sample_kernel(const GroupArgs ga, float* __restrict__ partials) {
   // ---- prefetch stream ---------------------------------------------------------------
   // Wave-load j of a wave covers rows (wave * LOADS + j) * 8 + (lane >> 3); the lane's LDS chunk
   // (lane & 7) holds logical chunk (lane & 7) ^ ((row >> 1) & 7).
-  const int nka = ly.d_in / BK, nkg = ly.d_out / BK, nblocks = nka + nkg;
+  const int nka = (ly.d_in + BK - 1) / BK, nkg = (ly.d_out + BK - 1) / BK, nblocks = nka + nkg;
   unsigned vi[LOADS];
   i32x4 rs;
   auto set_operand = [&](const void* base, int width) {
@@ -76,24 +76,41 @@ ghost_sample_kernel(const GroupArgs ga, float* __restrict__ partials) {
       vi[j] = (unsigned)row * width * 2u + chunk * 16u;             // rows >= T: past the slab -> zeros
     }
   };
+  // A width that is no multiple of the k-block: in its last block the lanes whose chunk lies past the
+  // row's end fetch zeros.
+  int columns;                                        // of the operand, from the next block's first one on
+  auto cut_columns = [&]() {
+    if (columns >= BK) return;
+#pragma unroll
+    for (int j = 0; j < LOADS; ++j) {
+      const int row = (wave * LOADS + j) * 8 + (lane >> 3);
+      if ((((lane & 7) ^ ((row >> 1) & 7)) * 8) >= columns) vi[j] = OOB;
+    }
+  };
   int p_blk = 0, p_stage = 0;
   unsigned p_soff = 0;
   const unsigned ld_base = lds0 + wave * LOADS * 1024;
   set_operand(ly.a, ly.d_in);
+  columns = ly.d_in;
+  cut_columns();
   auto issue = [&](int j) { load_to_lds(rs, vi[j], p_soff, ld_base + p_stage * STAGE_BYTES + j * 1024); };
   auto advance = [&]() {
     ++p_blk;
     p_soff += BK * 2;
+    columns -= BK;
     p_stage = p_stage + 1 == NSTAGE ? 0 : p_stage + 1;
     if (p_blk == nka) {
       set_operand(ly.g, ly.d_out);
+      columns = ly.d_out;
       p_soff = 0;
     } else if (p_blk == nblocks) {
       // past the end of the stream: keep issuing (the waits count loads) but fetch nothing
 #pragma unroll
       for (int j = 0; j < LOADS; ++j) vi[j] = 0x80000000u;
       p_soff = 0;
+      columns = INT32_MAX;
     }
+    cut_columns();
   };
 
   // ---- LDS -> MFMA operand addressing ---------------------------------------------------
@@ -231,9 +248,9 @@ dp_status launch_t(const GroupArgs& ga, float* partials, hipStream_t s) {
 
 }  // namespace
 
-// Whole 64-wide k-blocks, 129 .. 256 tokens, 32-bit byte offsets inside a sample's slab.
+// 129 .. 256 tokens, 32-bit byte offsets inside a sample's slab.
 bool ghost_sample_supports(int T, int d, int p) {
-  return T > 128 && T <= ROWS && d % BK == 0 && p % BK == 0 && (int64_t)(T + ROWS) * d * 2 < (int64_t)1 << 31 &&
+  return T > 128 && T <= ROWS && (int64_t)(T + ROWS) * d * 2 < (int64_t)1 << 31 &&
          (int64_t)(T + ROWS) * p * 2 < (int64_t)1 << 31;
 }
 

@@ -209,3 +209,19 @@ def test_instantiated_norm_tiles(dtype, B, T, dims):
 ])
 def test_narrow_instantiated(dtype, B, T, dims):
     check_step(dtype, B, T, dims, paths=[1] * len(dims))
+
+
+# Ghost norms of widths that end inside a 64-column k-block (8, 16, 56 columns of the last one; narrower than a
+# block), in each of the kernels of more than 95 tokens: compact, whole-sample and large tiles.
+@pytest.mark.parametrize("dtype", HALF)
+@pytest.mark.parametrize("T", [97, 128, 130, 256, 257, 400])
+def test_ghost_norm_ragged_widths(dtype, T):
+    from paper_2311_11822_amd import binding as dp
+    B, dt = 3, dp.DP_BF16 if dtype == si.BF16 else dp.DP_F16
+    for d, p in [(72, 264), (136, 56), (24, 120), (64, 8)]:
+        w = si.small_workload("widths", dtype, B, T, [(d, p)], g_std=1e-2)
+        a, g = si.gen_layer(w, 0)
+        out = torch.zeros(B, device="cuda")
+        ws = torch.empty(max(16, dp.dp_norm_workspace_bytes(0, dt, B, T, d, p)), dtype=torch.uint8, device="cuda")
+        dp.dp_ghost_norm(dev(a), dev(g), dt, B, T, d, p, out, ws)
+        np.testing.assert_allclose(host(out), o.ghost_sqnorm(si.to_f64(a), si.to_f64(g)), rtol=TOL)
