@@ -96,8 +96,9 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
       blocks += kernel == kGhostBrief ? ghost_brief_blocks(B, gl.T) : (int64_t)gl.tiles_per_sample * B;
     }
     ga.total_blocks = (int)blocks;
-    if (kernel == kGhostBrief) {                     // writes final norms: nothing to add up
-      dp_status st = launch_ghost_brief_group(ga, sqnorm_out, s);
+    if (kernel == kGhostBrief || kernel == kGhostSample) {       // final norms: nothing to add up
+      dp_status st = kernel == kGhostBrief ? launch_ghost_brief_group(ga, sqnorm_out, s)
+                                           : launch_ghost_sample_group(ga, sqnorm_out, s);
       if (st != DP_OK) return st;
       continue;
     }
@@ -123,7 +124,6 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
     }
     dp_status st = kernel == kGhostBig      ? launch_ghost_big_group(ga, partials, s)
                    : kernel == kGhostSmall  ? launch_ghost_group(ga, partials, s)
-                   : kernel == kGhostSample ? launch_ghost_sample_group(ga, partials, s)
                    : kernel == kPerexNarrow ? launch_perex_narrow_group(ga, partials, s)
                    : dma                    ? launch_perex_dma_group(ga, partials, big, s)
                                             : launch_perex_group(ga, partials, s);

@@ -155,10 +155,10 @@ dp_status launch_clipped_grad_group(const GroupArgs& ga, const float* C, hipStre
 int ghost_big_tiles_per_sample(int T);
 bool ghost_big_supports(int T, int d, int p);
 dp_status launch_ghost_big_group(const GroupArgs& ga, float* partials, hipStream_t s);
-// Whole-sample ghost-norm kernel for 129 .. 256 tokens (ghost_sample.hip): one workgroup and one
-// partial sum per sample.
+// Whole-sample ghost-norm kernel for 129 .. 256 tokens (ghost_sample.hip): one workgroup per sample, final
+// squared norms.
 bool ghost_sample_supports(int T, int d, int p);
-dp_status launch_ghost_sample_group(const GroupArgs& ga, float* partials, hipStream_t s);
+dp_status launch_ghost_sample_group(const GroupArgs& ga, float* sqnorm, hipStream_t s);
 // Samples of up to 32 tokens, several to a workgroup, final squared norms (ghost_brief.hip):
 // ga.layer[j].tile_begin = first workgroup (ghost_brief_blocks per layer).
 bool ghost_brief_supports(int T);

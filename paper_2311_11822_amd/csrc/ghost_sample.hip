@@ -36,9 +36,10 @@ __device__ __forceinline__ bf16x8 lds_read16(unsigned addr) {
   return *(__attribute__((address_space(3))) bf16x8*)(uintptr_t)addr;
 }
 
-template <bool F16>
+// Writes the squared norms themselves: a sample is one workgroup's.  RAGGED: some width is no multiple of the k-block.
+template <bool F16, bool RAGGED>
 __global__ void __launch_bounds__(NT)
-ghost_sample_kernel(const GroupArgs ga, float* __restrict__ partials) {
+ghost_sample_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
   const unsigned lds0 = (unsigned)(uintptr_t)lds_raw;
   const int l = layer_of(ga, blockIdx.x);
@@ -80,7 +81,7 @@ ghost_sample_kernel(const GroupArgs ga, float* __restrict__ partials) {
   // row's end fetch zeros.
   int columns;                                        // of the operand, from the next block's first one on
   auto cut_columns = [&]() {
-    if (columns >= BK) return;
+    if (!RAGGED || columns >= BK) return;
 #pragma unroll
     for (int j = 0; j < LOADS; ++j) {
       const int row = (wave * LOADS + j) * 8 + (lane >> 3);
@@ -233,16 +234,16 @@ ghost_sample_kernel(const GroupArgs ga, float* __restrict__ partials) {
   if (lane == 0) red[wave] = s;
   __syncthreads();
   if (tid == 0)
-    partials[ly.part_begin + sample] = ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7]));
+    sqnorm[(size_t)ly.sq_index * ga.B + sample] = ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7]));
 }
 
-template <bool F16>
-dp_status launch_t(const GroupArgs& ga, float* partials, hipStream_t s) {
+template <bool F16, bool RAGGED>
+dp_status launch_t(const GroupArgs& ga, float* sqnorm, hipStream_t s) {
   static ReadyTable ready;
-  auto kernel = ghost_sample_kernel<F16>;
+  auto kernel = ghost_sample_kernel<F16, RAGGED>;
   dp_status st = allow_big_lds(kernel, LDS_BYTES, ready);
   if (st != DP_OK) return st;
-  hipLaunchKernelGGL(kernel, dim3(ga.total_blocks), dim3(NT), LDS_BYTES, s, ga, partials);
+  hipLaunchKernelGGL(kernel, dim3(ga.total_blocks), dim3(NT), LDS_BYTES, s, ga, sqnorm);
   return hip_status(hipGetLastError());
 }
 
@@ -254,9 +255,12 @@ bool ghost_sample_supports(int T, int d, int p) {
          (int64_t)(T + ROWS) * p * 2 < (int64_t)1 << 31;
 }
 
-// ga.layer[j]: tile_begin = first workgroup, tiles_per_sample = 1, part_begin = first partial-sum slot.
-dp_status launch_ghost_sample_group(const GroupArgs& ga, float* partials, hipStream_t s) {
-  return ga.f16 ? launch_t<true>(ga, partials, s) : launch_t<false>(ga, partials, s);
+// ga.layer[j]: tile_begin = first workgroup, tiles_per_sample = 1.
+dp_status launch_ghost_sample_group(const GroupArgs& ga, float* sqnorm, hipStream_t s) {
+  bool ragged = false;
+  for (int l = 0; l < ga.n_layers; ++l) ragged = ragged || ga.layer[l].d_in % BK || ga.layer[l].d_out % BK;
+  if (ga.f16) return ragged ? launch_t<true, true>(ga, sqnorm, s) : launch_t<true, false>(ga, sqnorm, s);
+  return ragged ? launch_t<false, true>(ga, sqnorm, s) : launch_t<false, false>(ga, sqnorm, s);
 }
 
 }  // namespace dpbk
