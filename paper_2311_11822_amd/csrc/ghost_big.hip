@@ -93,7 +93,8 @@ ghost_big_kernel(const GroupArgs ga, float* __restrict__ partials) {
   // Wave-load j of the row block covers rows (wave*8 + j)*8 + (lane >> 3); the lane's LDS chunk
   // (lane & 7) holds logical chunk (lane & 7) ^ ((row >> 1) & 7).  Same for the column block
   // with wave*4 + j.
-  const int nka = (ly.d_in + BK - 1) / BK, nkg = (ly.d_out + BK - 1) / BK, nblocks = nka + nkg;
+  constexpr int PART = RAGGED ? BK - 1 : 0;            // a last block that is not full
+  const int nka = (ly.d_in + PART) / BK, nkg = (ly.d_out + PART) / BK, nblocks = nka + nkg;
   unsigned vi[LOADS_I], vj[LOADS_J];
   i32x4 rs;
   auto set_operand = [&](const void* base, int width) {
@@ -116,7 +117,7 @@ ghost_big_kernel(const GroupArgs ga, float* __restrict__ partials) {
   // row's end fetch zeros.
   int columns;                                    // of the operand, from the next block's first one on
   auto cut_columns = [&]() {
-    if (!RAGGED || columns >= BK) return;
+    if (columns >= BK) return;
 #pragma unroll
     for (int j = 0; j < LOADS_I; ++j) {
       const int row = (wave * li + j) * 8 + (lane >> 3);
@@ -133,8 +134,10 @@ ghost_big_kernel(const GroupArgs ga, float* __restrict__ partials) {
   // this wave's first LDS destination inside a stage, row block and column block
   const unsigned ld_i = lds0 + wave * li * 1024, ld_j = lds0 + I_BYTES + wave * LOADS_J * 1024;
   set_operand(ly.a, ly.d_in);
-  columns = ly.d_in;
-  cut_columns();
+  if constexpr (RAGGED) {
+    columns = ly.d_in;
+    cut_columns();
+  }
   // item in 0 .. LOADS_I + LOADS_J - 1: one wave-load of the row block or of the column block
   auto issue = [&](int item, bool with_j) {
     if (item < LOADS_I)
@@ -145,11 +148,11 @@ ghost_big_kernel(const GroupArgs ga, float* __restrict__ partials) {
   auto advance = [&]() {
     ++p_blk;
     p_soff += BK * 2;
-    columns -= BK;
+    if constexpr (RAGGED) columns -= BK;
     p_stage = p_stage + 1 == NSTAGE ? 0 : p_stage + 1;
     if (p_blk == nka) {
       set_operand(ly.g, ly.d_out);
-      columns = ly.d_out;
+      if constexpr (RAGGED) columns = ly.d_out;
       p_soff = 0;
     } else if (p_blk == nblocks) {
       // past the end of the stream: keep issuing (the waits count loads) but fetch nothing
@@ -158,9 +161,9 @@ ghost_big_kernel(const GroupArgs ga, float* __restrict__ partials) {
 #pragma unroll
       for (int j = 0; j < LOADS_J; ++j) vj[j] = 0x80000000u;
       p_soff = 0;
-      columns = INT32_MAX;
+      if constexpr (RAGGED) columns = INT32_MAX;
     }
-    cut_columns();
+    if constexpr (RAGGED) cut_columns();
   };
 
   // ---- LDS -> MFMA operand addressing ---------------------------------------------------

@@ -64,7 +64,8 @@ ghost_sample_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
   // ---- prefetch stream ---------------------------------------------------------------
   // Wave-load j of a wave covers rows (wave * LOADS + j) * 8 + (lane >> 3); the lane's LDS chunk
   // (lane & 7) holds logical chunk (lane & 7) ^ ((row >> 1) & 7).
-  const int nka = (ly.d_in + BK - 1) / BK, nkg = (ly.d_out + BK - 1) / BK, nblocks = nka + nkg;
+  constexpr int PART = RAGGED ? BK - 1 : 0;            // a last block that is not full
+  const int nka = (ly.d_in + PART) / BK, nkg = (ly.d_out + PART) / BK, nblocks = nka + nkg;
   unsigned vi[LOADS];
   i32x4 rs;
   auto set_operand = [&](const void* base, int width) {
@@ -81,7 +82,7 @@ ghost_sample_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
   // row's end fetch zeros.
   int columns;                                        // of the operand, from the next block's first one on
   auto cut_columns = [&]() {
-    if (!RAGGED || columns >= BK) return;
+    if (columns >= BK) return;
 #pragma unroll
     for (int j = 0; j < LOADS; ++j) {
       const int row = (wave * LOADS + j) * 8 + (lane >> 3);
@@ -92,26 +93,28 @@ ghost_sample_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
   unsigned p_soff = 0;
   const unsigned ld_base = lds0 + wave * LOADS * 1024;
   set_operand(ly.a, ly.d_in);
-  columns = ly.d_in;
-  cut_columns();
+  if constexpr (RAGGED) {
+    columns = ly.d_in;
+    cut_columns();
+  }
   auto issue = [&](int j) { load_to_lds(rs, vi[j], p_soff, ld_base + p_stage * STAGE_BYTES + j * 1024); };
   auto advance = [&]() {
     ++p_blk;
     p_soff += BK * 2;
-    columns -= BK;
+    if constexpr (RAGGED) columns -= BK;
     p_stage = p_stage + 1 == NSTAGE ? 0 : p_stage + 1;
     if (p_blk == nka) {
       set_operand(ly.g, ly.d_out);
-      columns = ly.d_out;
+      if constexpr (RAGGED) columns = ly.d_out;
       p_soff = 0;
     } else if (p_blk == nblocks) {
       // past the end of the stream: keep issuing (the waits count loads) but fetch nothing
 #pragma unroll
       for (int j = 0; j < LOADS; ++j) vi[j] = 0x80000000u;
       p_soff = 0;
-      columns = INT32_MAX;
+      if constexpr (RAGGED) columns = INT32_MAX;
     }
-    cut_columns();
+    if constexpr (RAGGED) cut_columns();
   };
 
   // ---- LDS -> MFMA operand addressing ---------------------------------------------------
