@@ -1,8 +1,8 @@
 // Clip-weighted gradient on the matrix cores (section 3 of the paper,
 // "DP gradient"):   grad[j,k] = sum_i C_i sum_t a[i,t,j] g[i,t,k].
 //
-// 256 x 256 output tiles, one workgroup per compute unit (contraction: tn_pipeline.h), and 128 x 128 or 64 x 64 ones
-// for the end of a launch and for launches that would leave compute units idle.
+// 256 x 256 output tiles, one workgroup per compute unit (contraction: tn_pipeline.h), and 128 x 128
+// or 64 x 64 ones for the end of a launch and for launches that would leave compute units idle.
 #include <type_traits>
 
 #include "dp_internal.h"

@@ -3,15 +3,16 @@
 //
 // The kernels that keep the weights out of the operands (grad_gemm.hip, tn_tile.h) re-express
 // their accumulator at every sample boundary and pad every sample to whole 32-row k-blocks: at T = 1
-// that is all they do.  Here the rows of all
-// samples form one contraction of B T rows and the weight is multiplied into the a operand in fp32;
-// that product is then cut into three bfloat16 parts, whose sum is within 2^-25 of the product, so each
-// 16-row step takes three matrix instructions and less is lost than by rounding C a to fp32.  fp16
-// operands: g (11 bits) is cut into two bfloat16 parts exactly, six instructions.  Gradients measured
-// against 64 bits: 1.7e-7 (T = 1, B = 512), 2.1e-7 (T = 31) here, 6.0e-7 and 3.9e-7 in the large-tile kernel.
-//   Measured, eight layers of 1024 x 1024 .. 4096 outputs, bf16: B = 512, T = 1: 1384 us before, 86 us here;
-// 4096 rows: 560 us here whatever T is (what bounds it: the matrix cores at the clock they hold under
-// load, then the cutting), fp16 1080 us; the large-tile kernel 684 us at T = 16, 352 at 32.  grad_kernel_of (dp_api.hip) draws its line there.
+// that is all they do.  Here the rows of all samples form one contraction of B T rows and the weight
+// is multiplied into the a operand in fp32; that product is then cut into three bfloat16 parts, whose
+// sum is within 2^-25 of it, so each 16-row step takes three matrix instructions and less is lost than
+// by rounding C a to fp32.  fp16 operands: g (11 bits) is cut into two bfloat16 parts exactly, six
+// instructions.  Gradients measured against 64 bits: 1.4e-7 (T = 1, B = 512) and 2.1e-7 (T = 31) here,
+// 6.0e-7 and 3.9e-7 in the large-tile kernel.
+//   Measured, eight layers of 1024 x 1024 .. 4096 outputs, bf16: B = 512, T = 1: 1384 us before, 89 us
+// here; 4096 rows: 560 us here whatever T is (what bounds it: the matrix cores at the clock they hold
+// under load, then the cutting), fp16 1080 us; the large-tile kernel 684 us at T = 16, 352 at 32.
+// grad_kernel_of (dp_api.hip) draws its line there.
 //
 // Tiles (four waves, 32 gradient rows each where the layer is wide): 128 x 128, or 128 x 32, 128 x 64 and their transposes for layers
 // narrower than a tile, where the stream over the wide operand is the bound and padding the
