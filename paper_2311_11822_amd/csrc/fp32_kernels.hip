@@ -116,6 +116,8 @@ __device__ __forceinline__ f32x16 mul_item(const TnItem& it, f32x16 acc) {
 // Squared per-sample norms, one workgroup per (layer, sample), by the layer's path (appendix A.1):
 // ghost: sum over token pairs of (a_t . a_u)(g_t . g_u), tile pairs on and above the diagonal;
 // instantiated: || a_i^T g_i ||_F^2.
+// A tile's entries outside the layer (past d, p or T) are selected out before they are added: their
+// zero operands meet the other side's values, and an infinity there would make them NaN.
 __global__ void __launch_bounds__(kThreads)
 norms_f32_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
   __shared__ float part_a[kWaves][16][64], part_g[kWaves][16][64];   // 64 KiB
@@ -138,6 +140,9 @@ norms_f32_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
     return s;
   };
 
+  // Register r of a lane: place run(r) along the tile's Gram rows (gradient columns), lane & 31 along the other side.
+  auto run = [&](int r) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); };
+
   if (ly.path == DP_PATH_GHOST) {
     for (int t0 = 0; t0 < T; t0 += kTile)
       for (int u0 = t0; u0 < T; u0 += kTile) {
@@ -148,7 +153,10 @@ norms_f32_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
         __syncthreads();
         float s = 0.f;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) s = fmaf(total(part_a, tid + h * kThreads), total(part_g, tid + h * kThreads), s);
+        for (int h = 0; h < 2; ++h) {
+          const float va = total(part_a, tid + h * kThreads), vg = total(part_g, tid + h * kThreads);
+          if (t0 + run(wave + h * kWaves) < T && u0 + (lane & 31) < T) s = fmaf(va, vg, s);
+        }
         sum += t0 == u0 ? s : 2.f * s;
         __syncthreads();
       }
@@ -157,7 +165,8 @@ norms_f32_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
     const int items = (T + kChunk - 1) / kChunk;
     const bool split = tiles < kWaves;                   // few tiles: the waves share each one's tokens
     for (int tile = split ? 0 : wave; tile < tiles; tile += split ? 1 : kWaves) {
-      const int j = (tile / tn) * kTile + (lane & 31), k = (tile % tn) * kTile + (lane & 31);
+      const int n0 = (tile % tn) * kTile;
+      const int j = (tile / tn) * kTile + (lane & 31), k = n0 + (lane & 31);
       f32x16 acc = zero16();
       for (int c = split ? wave : 0; c < items; c += split ? kWaves : 1) {
         TnItem it;
@@ -170,12 +179,13 @@ norms_f32_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const float v = total(part_a, tid + h * kThreads);
-          sum = fmaf(v, v, sum);
+          if (j < d && n0 + run(wave + h * kWaves) < p) sum = fmaf(v, v, sum);
         }
         __syncthreads();
       } else {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sum = fmaf(acc[r], acc[r], sum);
+        for (int r = 0; r < 16; ++r)
+          if (j < d && n0 + run(r) < p) sum = fmaf(acc[r], acc[r], sum);
       }
     }
   }
