@@ -60,7 +60,19 @@ perex_dma_kernel(const GroupArgs ga, float* __restrict__ partials) {
       }
   }
 
-  // Rows/columns past the layer's edge were loaded as zeros, so they add nothing.
+  // Rows and columns past the layer's edge were loaded as zeros, but an infinity of the other operand
+  // makes NaN of them: they stay out of the sum (d_out is a multiple of 8, so runs of four are in or out).
+  if (m0 + S::BM > d || n0 + S::BN > p) {
+#pragma unroll
+    for (int x = 0; x < S::TM; ++x)
+#pragma unroll
+      for (int y = 0; y < S::TN; ++y)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const bool in = m0 + wm + x * 32 + (lane & 31) < d && n0 + wn + y * 32 + 8 * (r >> 2) + 4 * (lane >> 5) < p;
+          acc[x][y][r] = in ? acc[x][y][r] : 0.f;
+        }
+  }
   float sum = 0.f;
 #pragma unroll
   for (int x = 0; x < S::TM; ++x)

@@ -98,11 +98,15 @@ __device__ __forceinline__ void narrow_tile(const GroupLayer& ly, int sample, in
         }
     }
   }
-  float sum = 0.f;
+  float sum = 0.f;                                       // without the padding: an infinity beside it makes it NaN
+  const bool in_rows = m0 + wm + (lane & 31) < d;
 #pragma unroll
   for (int y = 0; y < S::TN; ++y)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sum = fmaf(acc[y][r], acc[y][r], sum);
+    for (int r = 0; r < 16; ++r) {
+      const float v = in_rows && n0 + wn + 32 * y + 8 * (r >> 2) + 4 * (lane >> 5) < p ? acc[y][r] : 0.f;
+      sum = fmaf(v, v, sum);
+    }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
   if (lane == 0) red[wave] = sum;

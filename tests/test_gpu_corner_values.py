@@ -75,3 +75,13 @@ def check_infinite_norms(dp, dtype, path, B, T, d, p, where, positive=False):
 ])
 def test_infinite_norms_fp32(dp, path, B, T, d, p, where):
     check_infinite_norms(dp, si.F32, path, B, T, d, p, where, positive=path == 0)
+
+
+# 16-bit instantiated norms: 256 x 256 tiles whose edge lies inside a 128 x 128 one (256 of them, 576 of 128 x 128),
+# 128 x 128 tiles with and without padding, the narrow tiles.
+@pytest.mark.parametrize("dtype", HALF)
+@pytest.mark.parametrize("where", ["a", "g"])
+@pytest.mark.parametrize("B,T,d,p", [(64, 40, 384, 384), (3, 33, 384, 128), (3, 70, 200, 136), (3, 40, 768, 16),
+                                     (3, 40, 24, 200), (3, 40, 104, 56), (3, 40, 40, 136)])
+def test_infinite_instantiated_norms(dp, dtype, where, B, T, d, p):
+    check_infinite_norms(dp, dtype, 1, B, T, d, p, where)
