@@ -87,6 +87,17 @@ __device__ __forceinline__ int layer_of(const GroupArgs& ga, int id) {
 // compute unit for long.
 constexpr int64_t kF32MaxWork = (int64_t)1 << 28;
 
+// A launch takes less than 2^32 work items in a dimension (beyond it workgroups go missing without an error).
+// Kernels whose workgroups of 512 threads can come in larger numbers (2^23: one per sample of a stack, or per
+// tile of a layer of 1 x 2^28) are launched on block_grid(n) and number their workgroups with
+// block_number(); numbers from n on have nothing to do.
+constexpr int kGridRowBits = 22;
+inline dim3 block_grid(int64_t blocks) {
+  constexpr int64_t row = (int64_t)1 << kGridRowBits;
+  return blocks <= row ? dim3((unsigned)blocks) : dim3((unsigned)row, (unsigned)((blocks + row - 1) / row));
+}
+__device__ __forceinline__ int block_number() { return (int)((blockIdx.y << kGridRowBits) + blockIdx.x); }
+
 inline dp_status hip_status(hipError_t e) { return e == hipSuccess ? DP_OK : DP_ERR_HIP; }
 
 // Kernels that need more than 64 KiB of LDS must be told so once per device; `done` is the

@@ -121,7 +121,9 @@ __device__ __forceinline__ f32x16 mul_item(const TnItem& it, f32x16 acc) {
 __global__ void __launch_bounds__(kThreads)
 norms_f32_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
   __shared__ float part_a[kWaves][16][64], part_g[kWaves][16][64];   // 64 KiB
-  const int l = blockIdx.x / ga.B, i = blockIdx.x - l * ga.B;
+  const int block = block_number();
+  if (block >= ga.total_blocks) return;
+  const int l = block / ga.B, i = block - l * ga.B;
   const GroupLayer& ly = ga.layer[l];
   const int T = ly.T, d = ly.d_in, p = ly.d_out;
   const float* a = static_cast<const float*>(ly.a) + (size_t)i * T * d;
@@ -200,10 +202,12 @@ norms_f32_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
 __global__ void __launch_bounds__(kThreads)
 clipped_grad_f32_kernel(const GroupArgs ga, const float* __restrict__ C_all, const NoiseArgs na) {
   __shared__ float part[kWaves][16][64];                 // 32 KiB
-  const int l = layer_of(ga, blockIdx.x);
+  const int block = block_number();
+  if (block >= ga.total_blocks) return;
+  const int l = layer_of(ga, block);
   const GroupLayer& ly = ga.layer[l];
   const int T = ly.T, d = ly.d_in, p = ly.d_out;
-  const int tile = blockIdx.x - ly.tile_begin, tn = (p + kTile - 1) / kTile;
+  const int tile = block - ly.tile_begin, tn = (p + kTile - 1) / kTile;
   const int m0 = (tile / tn) * kTile, n0 = (tile % tn) * kTile;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -298,12 +302,12 @@ int64_t clipped_grad_f32_tiles(int d, int p) {
 }
 
 dp_status launch_norms_f32_group(const GroupArgs& ga, float* sqnorm, hipStream_t s) {
-  hipLaunchKernelGGL(norms_f32_kernel, dim3((unsigned)ga.n_layers * ga.B), dim3(kThreads), 0, s, ga, sqnorm);
+  hipLaunchKernelGGL(norms_f32_kernel, block_grid(ga.total_blocks), dim3(kThreads), 0, s, ga, sqnorm);
   return hip_status(hipGetLastError());
 }
 
 dp_status launch_clipped_grad_f32_group(const GroupArgs& ga, const float* C, const NoiseArgs& na, hipStream_t s) {
-  hipLaunchKernelGGL(clipped_grad_f32_kernel, dim3(ga.total_blocks), dim3(kThreads), 0, s, ga, C, na);
+  hipLaunchKernelGGL(clipped_grad_f32_kernel, block_grid(ga.total_blocks), dim3(kThreads), 0, s, ga, C, na);
   return hip_status(hipGetLastError());
 }
 

@@ -45,10 +45,12 @@ template <bool F16>
 __global__ void __launch_bounds__(kThreads)
 ghost_brief_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
   __shared__ float part_a[kWaves][16][64], part_g[kWaves][16][64];       // 64 KiB: two workgroups per compute unit
-  const int l = layer_of(ga, blockIdx.x);
+  const int block = block_number();
+  if (block >= ga.total_blocks) return;
+  const int l = layer_of(ga, block);
   const GroupLayer& ly = ga.layer[l];
   const int T = ly.T, per = kRows / T;
-  const int i0 = (blockIdx.x - ly.tile_begin) * per, n = min(per, ga.B - i0);     // samples [i0, i0 + n)
+  const int i0 = (block - ly.tile_begin) * per, n = min(per, ga.B - i0);     // samples [i0, i0 + n)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool valid = (lane & 31) < n * T;
@@ -108,9 +110,9 @@ int ghost_brief_blocks(int B, int T) {
 
 dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, hipStream_t s) {
   if (ga.f16)
-    hipLaunchKernelGGL(ghost_brief_kernel<true>, dim3(ga.total_blocks), dim3(kThreads), 0, s, ga, sqnorm);
+    hipLaunchKernelGGL(ghost_brief_kernel<true>, block_grid(ga.total_blocks), dim3(kThreads), 0, s, ga, sqnorm);
   else
-    hipLaunchKernelGGL(ghost_brief_kernel<false>, dim3(ga.total_blocks), dim3(kThreads), 0, s, ga, sqnorm);
+    hipLaunchKernelGGL(ghost_brief_kernel<false>, block_grid(ga.total_blocks), dim3(kThreads), 0, s, ga, sqnorm);
   return hip_status(hipGetLastError());
 }
 

@@ -85,3 +85,45 @@ def test_infinite_norms_fp32(dp, path, B, T, d, p, where):
                                      (3, 40, 24, 200), (3, 40, 104, 56), (3, 40, 40, 136)])
 def test_infinite_instantiated_norms(dp, dtype, where, B, T, d, p):
     check_infinite_norms(dp, dtype, 1, B, T, d, p, where)
+
+
+def norms_of_copies(dp, dtype, path, L, B, T, d, p):
+    """Squared norms of a stack of L layers that all hold the same a and g, and these on the device."""
+    tdt = {si.F32: torch.float32, si.BF16: torch.bfloat16, si.F16: torch.float16}[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(B + T)
+    a = torch.randn(B, T, d, device="cuda", generator=gen).to(tdt)
+    g = torch.randn(B, T, p, device="cuda", generator=gen).to(tdt)
+    desc = dp.layer_array([(a, g, T, d, p, path)] * L)
+    dt = dtype_code(dp, dtype)
+    ws = torch.empty(dp.dp_norms_multi_workspace_bytes(desc, dt, B), dtype=torch.uint8, device="cuda")
+    out = torch.full((L, B), -1.0, device="cuda")
+    dp.dp_norms_multi(desc, dt, B, out, ws)
+    return out, a, g
+
+
+# More workgroups of 512 threads than one grid dimension holds (2^23): a stack of 48 layers whose samples have one
+# each, and a single layer.
+@pytest.mark.parametrize("path", [0, 1])
+@pytest.mark.parametrize("L,B", [(48, 180000), (1, 2 ** 23 + 5)])
+def test_fp32_norms_of_very_many_samples(dp, path, L, B):
+    out, a, g = norms_of_copies(dp, si.F32, path, L, B, 1, 4, 3)
+    want = a.double().square().sum((1, 2)) * g.double().square().sum((1, 2))          # one token: ||a||^2 ||g||^2
+    assert torch.all((out.double() - want).abs() <= TOL * want)
+
+
+@pytest.mark.parametrize("dtype,T", [(si.BF16, 17), (si.F16, 32)])
+def test_ghost_norms_of_very_many_short_samples(dp, dtype, T):
+    L, B = 48, 180000
+    out, a, g = norms_of_copies(dp, dtype, 0, L, B, T, 8, 8)
+    assert torch.all(out == out[:1])                                                   # every layer, every sample
+    pick = [0, 1, B // 3, B - 2, B - 1]
+    np.testing.assert_allclose(host(out[0, pick]), o.ghost_sqnorm(host(a[pick].float()), host(g[pick].float())), rtol=TOL)
+
+
+def test_fp32_gradient_of_very_many_tiles(dp):
+    p = 2 ** 28 + 64                                                                   # 2^23 + 2 tiles of 32 columns
+    a, C = torch.full((1, 1, 1), 3.0, device="cuda"), torch.full((1,), 0.5, device="cuda")
+    g = torch.arange(p, device="cuda", dtype=torch.int32).remainder_(1009).float()
+    grad = torch.full((p,), -1.0, device="cuda")
+    dp.dp_clipped_grad(a, g, dp.DP_F32, 1, 1, 1, p, C, grad, 0)
+    assert torch.equal(grad, g.mul_(1.5))                                              # exact products
