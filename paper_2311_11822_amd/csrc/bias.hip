@@ -82,12 +82,13 @@ bias_sqnorm_kernel(const float* __restrict__ colsum, int p, float* __restrict__ 
   __shared__ float red[kSqThreads / 64];
   const float* row = colsum + (size_t)blockIdx.x * p;
   float s = 0.f;
-  for (int k0 = threadIdx.x; k0 < p; k0 += kSqBatch * kSqThreads) {
+  // unsigned: the last round's columns may lie past INT32_MAX
+  for (unsigned k0 = threadIdx.x; k0 < (unsigned)p; k0 += kSqBatch * kSqThreads) {
     float v[kSqBatch];
 #pragma unroll
     for (int q = 0; q < kSqBatch; ++q) {
-      const int k = k0 + q * kSqThreads;
-      v[q] = k < p ? row[k] : 0.f;
+      const unsigned k = k0 + q * kSqThreads;
+      v[q] = k < (unsigned)p ? row[k] : 0.f;
     }
 #pragma unroll
     for (int q = 0; q < kSqBatch; ++q) s = fmaf(v[q], v[q], s);
@@ -113,17 +114,17 @@ clipped_bias_kernel(const float* __restrict__ colsum, int B, int p, const float*
   if (k >= p) return;
   const float old = accumulate ? grad_b[k] : 0.f;
   float s = 0.f;
-  for (int i0 = 0; i0 < B; i0 += kSumBatch) {
+  for (unsigned i0 = 0; i0 < (unsigned)B; i0 += kSumBatch) {
     float c[kSumBatch], v[kSumBatch];
 #pragma unroll
     for (int q = 0; q < kSumBatch; ++q) {
-      const int i = min(i0 + q, B - 1);
+      const unsigned i = min(i0 + q, (unsigned)B - 1);
       c[q] = C[i];
       v[q] = colsum[(size_t)i * p + k];
     }
 #pragma unroll
     for (int q = 0; q < kSumBatch; ++q)
-      if (i0 + q < B) s = fmaf(c[q], v[q], s);
+      if (i0 + q < (unsigned)B) s = fmaf(c[q], v[q], s);
   }
   grad_b[k] = accumulate ? old + s : s;
 }

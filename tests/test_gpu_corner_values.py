@@ -127,3 +127,16 @@ def test_fp32_gradient_of_very_many_tiles(dp):
     grad = torch.full((p,), -1.0, device="cuda")
     dp.dp_clipped_grad(a, g, dp.DP_F32, 1, 1, 1, p, C, grad, 0)
     assert torch.equal(grad, g.mul_(1.5))                                              # exact products
+
+
+def test_bias_of_nearly_2_31_columns(dp):
+    p = 2 ** 31 - 512                                    # inside the last 4096: the indices of the last round pass 2^31
+    g = torch.ones((1, 1, p), dtype=torch.bfloat16, device="cuda")
+    colsum = torch.empty((1, p), device="cuda")
+    sq = torch.zeros(1, device="cuda")
+    dp.dp_bias_norm(g, dp.DP_BF16, 1, 1, p, colsum, sq)
+    assert abs(sq.item() - p) <= 1e-6 * p
+    del g
+    grad = torch.full((p,), -1.0, device="cuda")
+    dp.dp_clipped_bias_grad(colsum, 1, p, torch.full((1,), 0.5, device="cuda"), grad, 0)
+    assert grad.min().item() == 0.5 and grad.max().item() == 0.5
