@@ -119,10 +119,9 @@ __device__ __forceinline__ f32x16 mul_item(const TnItem& it, f32x16 acc) {
 // A tile's entries outside the layer (past d, p or T) are selected out before they are added: their
 // zero operands meet the other side's values, and an infinity there would make them NaN.
 __global__ void __launch_bounds__(kThreads)
-norms_f32_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
+norms_f32_kernel(const GroupArgs ga, float* __restrict__ sqnorm, int first) {
   __shared__ float part_a[kWaves][16][64], part_g[kWaves][16][64];   // 64 KiB
-  const int block = block_number();
-  if (block >= ga.total_blocks) return;
+  const unsigned block = first + blockIdx.x;
   const int l = block / ga.B, i = block - l * ga.B;
   const GroupLayer& ly = ga.layer[l];
   const int T = ly.T, d = ly.d_in, p = ly.d_out;
@@ -200,10 +199,9 @@ norms_f32_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
 // An item's product is formed unweighted and folded in as total += C_i * item; a sample with
 // C_i == 0 is not read, as in the 16-bit kernels.
 __global__ void __launch_bounds__(kThreads)
-clipped_grad_f32_kernel(const GroupArgs ga, const float* __restrict__ C_all, const NoiseArgs na) {
+clipped_grad_f32_kernel(const GroupArgs ga, const float* __restrict__ C_all, const NoiseArgs na, int first) {
   __shared__ float part[kWaves][16][64];                 // 32 KiB
-  const int block = block_number();
-  if (block >= ga.total_blocks) return;
+  const int block = first + blockIdx.x;
   const int l = layer_of(ga, block);
   const GroupLayer& ly = ga.layer[l];
   const int T = ly.T, d = ly.d_in, p = ly.d_out;
@@ -302,13 +300,15 @@ int64_t clipped_grad_f32_tiles(int d, int p) {
 }
 
 dp_status launch_norms_f32_group(const GroupArgs& ga, float* sqnorm, hipStream_t s) {
-  hipLaunchKernelGGL(norms_f32_kernel, block_grid(ga.total_blocks), dim3(kThreads), 0, s, ga, sqnorm);
-  return hip_status(hipGetLastError());
+  return launch_in_runs(ga.total_blocks, [&](dim3 grid, int first) {
+    hipLaunchKernelGGL(norms_f32_kernel, grid, dim3(kThreads), 0, s, ga, sqnorm, first);
+  });
 }
 
 dp_status launch_clipped_grad_f32_group(const GroupArgs& ga, const float* C, const NoiseArgs& na, hipStream_t s) {
-  hipLaunchKernelGGL(clipped_grad_f32_kernel, block_grid(ga.total_blocks), dim3(kThreads), 0, s, ga, C, na);
-  return hip_status(hipGetLastError());
+  return launch_in_runs(ga.total_blocks, [&](dim3 grid, int first) {
+    hipLaunchKernelGGL(clipped_grad_f32_kernel, grid, dim3(kThreads), 0, s, ga, C, na, first);
+  });
 }
 
 }  // namespace dpbk

@@ -43,10 +43,9 @@ __device__ __forceinline__ f32x16 gram_part(const uint16_t* x, int width, bool v
 
 template <bool F16>
 __global__ void __launch_bounds__(kThreads)
-ghost_brief_kernel(const GroupArgs ga, float* __restrict__ sqnorm) {
+ghost_brief_kernel(const GroupArgs ga, float* __restrict__ sqnorm, int first) {
   __shared__ float part_a[kWaves][16][64], part_g[kWaves][16][64];       // 64 KiB: two workgroups per compute unit
-  const int block = block_number();
-  if (block >= ga.total_blocks) return;
+  const int block = first + blockIdx.x;
   const int l = layer_of(ga, block);
   const GroupLayer& ly = ga.layer[l];
   const int T = ly.T, per = kRows / T;
@@ -109,11 +108,12 @@ int ghost_brief_blocks(int B, int T) {
 }
 
 dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, hipStream_t s) {
-  if (ga.f16)
-    hipLaunchKernelGGL(ghost_brief_kernel<true>, block_grid(ga.total_blocks), dim3(kThreads), 0, s, ga, sqnorm);
-  else
-    hipLaunchKernelGGL(ghost_brief_kernel<false>, block_grid(ga.total_blocks), dim3(kThreads), 0, s, ga, sqnorm);
-  return hip_status(hipGetLastError());
+  return launch_in_runs(ga.total_blocks, [&](dim3 grid, int first) {
+    if (ga.f16)
+      hipLaunchKernelGGL(ghost_brief_kernel<true>, grid, dim3(kThreads), 0, s, ga, sqnorm, first);
+    else
+      hipLaunchKernelGGL(ghost_brief_kernel<false>, grid, dim3(kThreads), 0, s, ga, sqnorm, first);
+  });
 }
 
 }  // namespace dpbk
