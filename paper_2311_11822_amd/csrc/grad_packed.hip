@@ -22,8 +22,11 @@
 // runs beside the other's matrix instructions.
 //
 // Rows of a sample with C == 0 do not enter (whatever they hold): a wave that meets a zero weight clears
-// those rows in both operands.  An infinity in an operand would meet the zero low parts of the other (inf x 0):
-// a wave that finds a NaN among its sums forms its tile again, sample by sample in fp32, without the split.
+// those rows in both operands.
+//   An infinity in an operand meets the zero low parts of the other (inf x 0): a workgroup that finds a NaN among its
+// sums forms its tile again without the cutting: the same loads, the rows of one sample at a time, unweighted,
+// folded in as total += C_i * sum.  (One wave on its own, two rows of its 32 x 32 pieces at a time straight from
+// memory, took 52.6 ms for 131072 rows of eight 768 x 16 layers; so 4.4, and 2.1 without a NaN.)
 #include "dp_internal.h"
 #include "grad_epilogue.h"
 #include "row_tile.h"
@@ -88,33 +91,6 @@ __device__ __forceinline__ void cut_f16(uint32_t u, uint32_t (&part)[2]) {
   part[1] = pack_hi(x0 - top8(x0), x1 - top8(x1));
 }
 
-// A 32 x 32 piece of the gradient again, sample by sample with unweighted fp32 products (sums that held a NaN).
-template <bool F16>
-__device__ __forceinline__ f32x16 retry_piece(const uint16_t* a, const uint16_t* g, int B, int T, int d, int p,
-                                              const float* C, int row0, int col0, int lane) {
-  const int j = row0 + (lane & 31), k = col0 + (lane & 31);
-  f32x16 total, zero;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) total[r] = zero[r] = 0.f;
-#pragma unroll 1
-  for (int i = 0; i < B; ++i) {
-    const float c = C[i];
-    if (c == 0.f) continue;
-    f32x16 s = zero;
-#pragma unroll 1
-    for (int t0 = 0; t0 < T; t0 += 2) {
-      const int t = t0 + (lane >> 5);
-      const size_t row = (size_t)i * T + t;
-      const float x = t < T && j < d ? widen_lo<F16>(a[row * d + j]) : 0.f;
-      const float z = t < T && k < p ? widen_lo<F16>(g[row * p + k]) : 0.f;
-      s = __builtin_amdgcn_mfma_f32_32x32x2f32(z, x, s, 0, 0, 0);
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) total[r] = fmaf(c, s[r], total[r]);
-  }
-  return total;
-}
-
 template <class S, bool F16, bool NOISE>
 __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int tile, int B, bool accumulate,
                                             const float* C, const NoiseArgs& na, unsigned lds0) {
@@ -128,13 +104,20 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
 
   RowOperand<S::BM> oa;
   RowOperand<S::BN> ob;
-  oa.init(ly.a, rows, d, m0, lds0, wave, lane);
-  ob.init(ly.g, rows, p, n0, lds0 + S::A_BYTES, wave, lane);
   // weights: lane -> row (lane & 31) of the k-block, sample w_i and token w_t of that row
   const i32x4 rw = make_rsrc(C, (unsigned)B * 4u);
-  int w_i = (lane & 31) / T, w_t = (lane & 31) % T;
+  int w_i, w_t;
   const int w_di = BK / T, w_dt = BK % T;
-  int p_stage = 0;
+  int p_stage;
+  auto rewind = [&]() {                                  // the load stream to the first k-block
+    int x = lane;
+    asm volatile("" : "+v"(x));                          // computed anew each time, not kept in registers through the loop
+    oa.init(ly.a, rows, d, m0, lds0, wave, x);
+    ob.init(ly.g, rows, p, n0, lds0 + S::A_BYTES, wave, x);
+    w_i = (x & 31) / T;
+    w_t = (x & 31) % T;
+    p_stage = 0;
+  };
   auto issue = [&]() {
     const unsigned so = p_stage * S::STAGE_BYTES;
     oa.issue(so, lane);
@@ -157,6 +140,7 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
 
   typedef __attribute__((ext_vector_type(4))) float f4;
   typedef __attribute__((address_space(3))) f4 lds_f4;
+  typedef __attribute__((address_space(3))) float lds_float;
   constexpr int G_PARTS = F16 ? 2 : 1;
   // The products of the low parts go to sums of their own, whose roundings are 2^-8 of the others': the
   // result is rounded as often as one matrix instruction per step would.
@@ -166,6 +150,7 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[y][r] = low[y][r] = 0.f;
 
+  rewind();
   for (int q = 0; q < NSTAGE - 1; ++q) issue();
   int stage = 0;
   for (int kb = 0; kb < nkb; ++kb) {
@@ -173,6 +158,7 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NSTAGE - 2) * S::LOADS) : "memory");
     issue();
     const unsigned so = stage * S::STAGE_BYTES;
+    const float own = *(const lds_float*)(uintptr_t)(lds0 + so + S::A_BYTES + S::B_BYTES + 4 * lane);  // row lane & 31
     f4 w[2][2];                                          // weights of this lane's 8 rows, per 16-row step
     u32x4 fa[2], fb[2][S::TN];
 #pragma unroll
@@ -186,10 +172,7 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
         fb[ks][y] = __builtin_bit_cast(u32x4, read_row_frag<S::BN>(b_rd[y] + so + ks * 16 * S::BN * 2));
     }
     DP_PIN();
-    float least = fabsf(w[0][0][0]);
-#pragma unroll
-    for (int e = 1; e < 16; ++e) least = fminf(least, fabsf(w[e >> 3][(e >> 2) & 1][e & 3]));
-    if (__any(least == 0.f)) {                           // rows that do not count (or lie past the end)
+    if (__any(own == 0.f)) {                             // rows that do not count (or lie past the end)
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         const int ks = q >> 2, e = 2 * q & 3;
@@ -250,19 +233,85 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // zero-fill loads past the end
 
-  bool nan = false;
+  bool off = false;
 #pragma unroll
   for (int y = 0; y < S::TN; ++y)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      acc[y][r] += low[y][r];
-      nan |= acc[y][r] != acc[y][r];
+      acc[y][r] = acc[y][r] + low[y][r];
+      off |= acc[y][r] != acc[y][r];
     }
-  if (__any(nan)) {
+  __syncthreads();                                       // LDS is reused
+  typedef __attribute__((address_space(3))) int lds_int;
+  const bool wave_off = __any(off);
+  if (lane == 0) *(lds_int*)(uintptr_t)(lds0 + 4 * wave) = wave_off;
+  __syncthreads();
+  int any_off = 0;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) any_off |= *(lds_int*)(uintptr_t)(lds0 + 4 * v);
+  if (any_off) {
+    // The tile again, unweighted, sample by sample (low: the sample's sum so far).
+    __syncthreads();                                     // the flags have been read
 #pragma unroll
     for (int y = 0; y < S::TN; ++y)
-      acc[y] = retry_piece<F16>(static_cast<const uint16_t*>(ly.a), static_cast<const uint16_t*>(ly.g), B, T, d, p, C,
-                                m0 + wm, n0 + wn + 32 * y, lane);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[y][r] = low[y][r] = 0.f;
+    rewind();
+    for (int q = 0; q < NSTAGE - 1; ++q) issue();
+    stage = 0;
+    int left = T;                                        // rows of the sample from here on
+    for (int kb = 0; kb < nkb; ++kb) {
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NSTAGE - 2) * S::LOADS) : "memory");
+      issue();
+      const unsigned so = stage * S::STAGE_BYTES;
+      u32x4 fa[2], fb[2][S::TN];
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        fa[ks] = __builtin_bit_cast(u32x4, read_row_frag<S::BM>(a_rd + so + ks * 16 * S::BM * 2));
+#pragma unroll
+        for (int y = 0; y < S::TN; ++y)
+          fb[ks][y] = __builtin_bit_cast(u32x4, read_row_frag<S::BN>(b_rd[y] + so + ks * 16 * S::BN * 2));
+      }
+      const int here = min(BK, rows - kb * BK);
+#pragma unroll 1
+      for (int begin = 0; begin < here;) {
+        const int end = min(here, begin + left);
+        const int c_bits = *(const lds_int*)(uintptr_t)(lds0 + so + S::A_BYTES + S::B_BYTES + 4 * begin);
+        const float c = __int_as_float(__builtin_amdgcn_readfirstlane(c_bits));
+        if (c != 0.f) {
+#pragma unroll
+          for (int ks = 0; ks < 2; ++ks) {
+            u32x4 keep;                                  // this lane's rows 16 ks + 8 (lane >> 5) + 0 .. 7
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const int row = 16 * ks + 8 * (lane >> 5) + 2 * q;
+              keep[q] = (row >= begin && row < end ? 0xFFFFu : 0u) |
+                        (row + 1 >= begin && row + 1 < end ? 0xFFFF0000u : 0u);
+            }
+            const bf16x8 x = __builtin_bit_cast(bf16x8, fa[ks] & keep);
+#pragma unroll
+            for (int y = 0; y < S::TN; ++y)
+              low[y] = mfma16<F16>(__builtin_bit_cast(bf16x8, fb[ks][y] & keep), x, low[y]);
+          }
+        }
+        left -= end - begin;
+        begin = end;
+        if (left == 0) {
+          left = T;
+          if (c != 0.f) {
+#pragma unroll
+            for (int y = 0; y < S::TN; ++y)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) {
+                acc[y][r] = fmaf(c, low[y][r], acc[y][r]);
+                low[y][r] = 0.f;
+              }
+          }
+        }
+      }
+      stage = stage + 1 == NSTAGE ? 0 : stage + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // zero-fill loads past the end
   }
 
   // epilogue in the transposed layout described at tile_noise

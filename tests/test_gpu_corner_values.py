@@ -140,3 +140,41 @@ def test_bias_of_nearly_2_31_columns(dp):
     grad = torch.full((p,), -1.0, device="cuda")
     dp.dp_clipped_bias_grad(colsum, 1, p, torch.full((1,), 0.5, device="cuda"), grad, 0)
     assert grad.min().item() == 0.5 and grad.max().item() == 0.5
+
+
+@pytest.mark.parametrize("dtype", HALF)
+@pytest.mark.parametrize("B,T,d,p", [(40, 1, 136, 264), (5, 40, 200, 16), (6, 7, 24, 136), (3, 100, 48, 136)])
+def test_packed_rows_with_nan_weight(dp, dtype, B, T, d, p):
+    """A NaN weight makes every entry NaN, the others' zeros included."""
+    w = si.small_workload("nanw", dtype, B, T, [(d, p)])
+    a, g = (x.copy() for x in si.gen_layer(w, 0))
+    a[:, :, 0] = 0
+    grad = torch.zeros((d, p), device="cuda")
+    C = np.full(B, 0.5, dtype=np.float32)
+    C[B // 2] = np.nan
+    dp.dp_clipped_grad(dev(a), dev(g), dtype_code(dp, dtype), B, T, d, p, dev(C), grad, 0)
+    assert np.all(np.isnan(host(grad)))
+
+
+def test_packed_rows_with_infinity_take_no_detour(dp):
+    """Forming a tile again, without the split, costs about the pass it repeats (once 25 times as long)."""
+    B, T, d, p = 16, 2048, 768, 16
+    a = torch.randn(B, T, d, device="cuda").to(torch.bfloat16)
+    g = torch.randn(B, T, p, device="cuda").to(torch.bfloat16)
+    C, grad = torch.full((B,), 0.5, device="cuda"), torch.zeros(d, p, device="cuda")
+
+    def shortest():
+        us = []
+        for _ in range(6):
+            begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            begin.record()
+            dp.dp_clipped_grad(a, g, dp.DP_BF16, B, T, d, p, C, grad, 0)
+            end.record()
+            torch.cuda.synchronize()
+            us.append(begin.elapsed_time(end) * 1e3)
+        return min(us)
+
+    clean = shortest()
+    a[:, 7, ::32] = float("inf")
+    assert shortest() <= 8 * clean
+    assert not torch.isfinite(grad[::32]).any() and torch.isfinite(grad[1::32]).all()
