@@ -23,10 +23,18 @@
 //
 // Rows of a sample with C == 0 do not enter (whatever they hold): a wave that meets a zero weight clears
 // those rows in both operands.
-//   An infinity in an operand meets the zero low parts of the other (inf x 0): a workgroup that finds a NaN among its
-// sums forms its tile again without the cutting: the same loads, the rows of one sample at a time, unweighted,
-// folded in as total += C_i * sum.  (One wave on its own, two rows of its 32 x 32 pieces at a time straight from
-// memory, took 52.6 ms for 131072 rows of eight 768 x 16 layers; so 4.4, and 2.1 without a NaN.)
+//
+// Range.  The contract is that of weights applied to a sample's exact partial product, so no part of C a may be lost
+// below the normal numbers: the weights are multiplied by 2^80 on their way in and the sums by 2^-80 at the
+// end.  C a >= 2^-178 then keeps its parts (2^-98 scaled, 2^-126 the last part's end), which every weight of 2^-45
+// and more does with every bfloat16 (2^-133 at least), and every weight with every fp16 (2^-24).  Where a smaller
+// weight came by, or a sum is not finite (an infinity in an operand meets the zero low parts of the other; C a or
+// sums beyond 2^48), the workgroup forms its tile again without the cutting: the same loads, the rows of one
+// sample at a time, unweighted, folded in as total += C_i * sum.  (One wave on its own, two rows of its 32 x 32
+// pieces at a time straight from memory, took 52.6 ms for 131072 rows of eight 768 x 16 layers; so 4.4, and 2.1
+// where all is finite.)  The scaling and the test cost 2 % of the kernel.
+#include <float.h>
+
 #include "dp_internal.h"
 #include "grad_epilogue.h"
 #include "row_tile.h"
@@ -57,6 +65,9 @@ using Flat2 = Shape<64, 128, 2, 2>;
 constexpr int LDS_BYTES = NSTAGE * Wide::STAGE_BYTES;          // 65 KiB: two workgroups per compute unit
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+constexpr float kScale = 0x1p80f;                             // of the weights: see "Range"
+template <bool F16>
+constexpr float kLeastWeight = F16 ? 0.f : 0x1p-45f;
 
 template <bool F16>
 __device__ __forceinline__ float widen_lo(uint32_t u) {
@@ -150,6 +161,8 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[y][r] = low[y][r] = 0.f;
 
+  float least_w = INFINITY;                              // smallest non-zero weight that this lane met
+
   rewind();
   for (int q = 0; q < NSTAGE - 1; ++q) issue();
   int stage = 0;
@@ -172,6 +185,9 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
         fb[ks][y] = __builtin_bit_cast(u32x4, read_row_frag<S::BN>(b_rd[y] + so + ks * 16 * S::BN * 2));
     }
     DP_PIN();
+#pragma unroll
+    for (int e = 0; e < 16; ++e) w[e >> 3][(e >> 2) & 1][e & 3] *= kScale;
+    least_w = own == 0.f ? least_w : fminf(least_w, fabsf(own));
     if (__any(own == 0.f)) {                             // rows that do not count (or lie past the end)
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
@@ -233,13 +249,13 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // zero-fill loads past the end
 
-  bool off = false;
+  bool off = least_w < kLeastWeight<F16>;
 #pragma unroll
   for (int y = 0; y < S::TN; ++y)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      acc[y][r] = acc[y][r] + low[y][r];
-      off |= acc[y][r] != acc[y][r];
+      acc[y][r] = (acc[y][r] + low[y][r]) * (1.f / kScale);
+      off |= !(fabsf(acc[y][r]) <= FLT_MAX);
     }
   __syncthreads();                                       // LDS is reused
   typedef __attribute__((address_space(3))) int lds_int;

@@ -178,3 +178,52 @@ def test_packed_rows_with_infinity_take_no_detour(dp):
     a[:, 7, ::32] = float("inf")
     assert shortest() <= 8 * clean
     assert not torch.isfinite(grad[::32]).any() and torch.isfinite(grad[1::32]).all()
+
+
+def check_weighted_gradient(dp, dtype, B, T, d, p, C, a_scale=1.0, g_scale=1.0, edit=None):
+    """Gradient under weights C against the oracle, row by row (a row of the gradient sees one column of a)."""
+    rng = np.random.default_rng([B, T, d, p])
+    tdt = torch.bfloat16 if dtype == si.BF16 else torch.float16
+    a = torch.from_numpy(rng.standard_normal((B, T, d)) * a_scale).to(tdt)
+    g = torch.from_numpy(rng.standard_normal((B, T, p)) * g_scale).to(tdt)
+    if edit is not None:
+        edit(a, g)
+    C = np.asarray(C, dtype=np.float32)
+    grad = torch.full((d, p), 3.0, device="cuda")
+    dp.dp_clipped_grad(a.cuda(), g.cuda(), dtype_code(dp, dtype), B, T, d, p, dev(C), grad, 0)
+    want = o.clipped_grad(a.double().numpy(), g.double().numpy(), C.astype(np.float64))
+    got = host(grad)
+    assert np.all(np.isfinite(got))
+    err = np.linalg.norm(got - want, axis=1) / np.linalg.norm(want, axis=1)
+    assert err.max() <= TOL, err.max()
+
+
+# Weights go onto the exact products of the packed-row kernel too, whatever their size: shapes it takes, in each
+# tile shape.
+PACKED = [(6, 1, 136, 264), (6, 7, 264, 136), (6, 70, 16, 200), (6, 70, 200, 16), (6, 40, 48, 136), (6, 33, 136, 64)]
+
+
+@pytest.mark.parametrize("dtype", HALF)
+@pytest.mark.parametrize("B,T,d,p", PACKED)
+def test_packed_rows_weight_ranges(dp, dtype, B, T, d, p):
+    for C in ([1e-8, 1e2, 1e-8, 3e-3, 1e2, 1.0], [-1.0, 1e2, 0.0, -1e-8, 1.0, 1e2], [1e-30] * 6, [3e-36] * 6,
+              [1e30, 1e28, 1e30, 2e30, 1e30, 1e30]):
+        check_weighted_gradient(dp, dtype, B, T, d, p, C)
+    # columns that only one sample reaches, whose weight is far below the others'
+    def one_sample(a, g):
+        a[:5, :, :8] = 0
+    check_weighted_gradient(dp, dtype, B, T, d, p, [1.0, 0.5, 1.0, 2.0, 1.0, 1e-33], edit=one_sample)
+
+
+@pytest.mark.parametrize("B,T,d,p", PACKED)
+def test_packed_rows_operand_ranges(dp, B, T, d, p):
+    # bf16: weight times activation below and above the fp32 range, results inside it
+    check_weighted_gradient(dp, si.BF16, B, T, d, p, [1e-30] * 6, a_scale=1e-12, g_scale=1e20)
+    check_weighted_gradient(dp, si.BF16, B, T, d, p, [2.0 ** -100] * 6, a_scale=2.0 ** -80, g_scale=2.0 ** 120)
+    check_weighted_gradient(dp, si.BF16, B, T, d, p, [1e30] * 6, a_scale=1e20, g_scale=1e-30)
+    check_weighted_gradient(dp, si.BF16, B, T, d, p, [0.5, 1e-3, 1e-5, 1.0, 0.1, 0.0], a_scale=1e-35, g_scale=1e15)
+    # one tiny activation among ordinary ones
+    def tiny(a, g):
+        a[2, 0, 3] = 2.0 ** -126
+        a[:, :, 5] = 2.0 ** -120
+    check_weighted_gradient(dp, si.BF16, B, T, d, p, [0.5, 1e-3, 1e-5, 1.0, 0.1, 0.7], edit=tiny)
