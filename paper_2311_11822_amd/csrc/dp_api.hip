@@ -334,22 +334,34 @@ dp_status noise_after(const NoiseSpec* noise, int l, const dp_layer& ly, float* 
 }
 
 // Which gradient kernel a 16-bit layer takes.
-//  kGradPacked: layers narrower than half a large tile (its 256 x 256 would be mostly padding), and samples
-//    of less than kPackedTokens: the large-tile kernel takes as long for a sample of up to 32 tokens
-//    (2.7 us on eight 1024-wide layers: ~1400 clocks a k-block, ~900 a sample boundary) as the packed one
-//    for 20 rows (fp16: 10), whose matrix instructions are three (six) times as many.  4096 rows:
-//    T = 16 684 us against 595, T = 32 352 against 555.
+//  kGradPacked: short samples.  The large-tile kernels (256 x 256, 128 x 128) pay per sample, ~900 clocks and
+//    ~1400 per begun 32 tokens; the packed one pays per row, three matrix instructions (fp16: six) where they
+//    need one, but its tiles cover a narrow side without padding.  The lines lie where the two meet:
+//      sides             bf16   fp16   gradients of 48 layers 1024 x side, 16384 rows, us: packed / 128 x 128 tiles
+//      up to 32            -     48    fp16 600 at any T / 640 at T = 48, 550 at 56, 390 at 256
+//      33 .. 64            -     28    fp16 840 / 780 at T = 28, 490 at 64, 400 at 256
+//      65 .. 127          48     18    bf16 645-690 / 690 at T = 32, 650 at 48, 420-450 at 256;
+//                                      fp16 1220-1380 / 1370 at T = 16, 1100 at 20
+//      128 and more       20     10    4096 rows of eight layers 1024 x 1024 .. 4096: 566 / 684 at T = 16, 352 at 32
+//    Without the lines (everything with a side below 128 packed) fp16 stacks of 65 .. 127 columns took 1220 us where
+//    the register-staged kernel they came from took 570 .. 600 from 256 tokens on, and bf16 ones 645.
 //  kGradBig: slabs its 32-bit addressing reaches.
 //  kGradEdge: the rest.
 enum GradKernel { kGradBig = 0, kGradPacked = 1, kGradEdge = 2 };
 constexpr int kGradKernels = 3;
-constexpr int kPackedTokens = 20, kPackedTokensF16 = 10;
+
+// Samples of fewer tokens than this take the packed kernel.
+int packed_below(int side, bool f16) {
+  if (side <= 32) return f16 ? 48 : INT32_MAX;
+  if (side <= 64) return f16 ? 28 : INT32_MAX;
+  if (side < 128) return f16 ? 18 : 48;
+  return f16 ? 10 : 20;
+}
 
 GradKernel grad_kernel_of(const dp_layer& ly, dp_dtype dt, int B) {
-  const bool narrow = ly.d_in < 128 || ly.d_out < 128;
-  const bool brief = ly.T < (dt == DP_F16 ? kPackedTokensF16 : kPackedTokens);
-  if ((narrow || brief) && grad_packed_supports(B, ly.T, ly.d_in, ly.d_out)) return kGradPacked;
-  return !narrow && clipped_grad_big_supports(ly.T, ly.d_in, ly.d_out) ? kGradBig : kGradEdge;
+  const bool packed = ly.T < packed_below(std::min(ly.d_in, ly.d_out), dt == DP_F16);
+  if (packed && grad_packed_supports(B, ly.T, ly.d_in, ly.d_out)) return kGradPacked;
+  return clipped_grad_big_supports(ly.T, ly.d_in, ly.d_out) ? kGradBig : kGradEdge;
 }
 
 // out16: grads[l] address 16-bit arrays of the operands' storage type; only the large-tile kernels

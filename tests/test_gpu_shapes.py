@@ -225,3 +225,39 @@ def test_ghost_norm_ragged_widths(dtype, T):
         ws = torch.empty(max(16, dp.dp_norm_workspace_bytes(0, dt, B, T, d, p)), dtype=torch.uint8, device="cuda")
         dp.dp_ghost_norm(dev(a), dev(g), dt, B, T, d, p, out, ws)
         np.testing.assert_allclose(host(out), o.ghost_sqnorm(si.to_f64(a), si.to_f64(g)), rtol=TOL)
+
+
+# Narrow sides on either side of the token counts at which they change from packed rows to the 128 x 128 tiles, one and
+# two sides narrow, next to a wide layer in one launch.
+@pytest.mark.parametrize("dtype,T,dims", [
+    (si.BF16, 47, [(72, 264), (264, 120), (120, 96)]), (si.BF16, 48, [(72, 264), (264, 120), (120, 96)]),
+    (si.F16, 17, [(72, 264), (264, 120), (120, 96)]), (si.F16, 18, [(72, 264), (264, 120), (120, 96)]),
+    (si.F16, 27, [(40, 264), (264, 64), (48, 120)]), (si.F16, 28, [(40, 264), (264, 64), (48, 120)]),
+    (si.F16, 47, [(16, 264), (264, 32), (8, 24)]), (si.F16, 48, [(16, 264), (264, 32), (8, 24)]),
+    (si.F16, 70, [(24, 1104), (392, 520), (1104, 88), (56, 136)]),
+])
+def test_narrow_sides_at_the_packed_lines(dtype, T, dims):
+    check_step(dtype, 3, T, dims, paths=[0] * len(dims))
+    check_step(dtype, 4, T, dims, paths=[0] * len(dims), mode=o.CLIP_AUTOMATIC, mask=[1])
+
+
+def test_fp16_narrow_layers_keep_pace_with_bf16():
+    """Long fp16 samples of narrow layers take as many matrix instructions as bf16 ones (six times as many once)."""
+    from paper_2311_11822_amd.pipeline import BkPipeline
+
+    def shortest(dt):
+        dims = [(1024, 96), (96, 1024)] * 8
+        pipe = BkPipeline([(torch.randn(64, 128, d, device="cuda").to(dt), torch.randn(64, 128, p, device="cuda").to(dt))
+                           for d, p in dims], [0] * len(dims))
+        pipe.C.fill_(0.5)
+        us = []
+        for _ in range(8):
+            begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            begin.record()
+            pipe.grad()
+            end.record()
+            torch.cuda.synchronize()
+            us.append(begin.elapsed_time(end) * 1e3)
+        return min(us)
+
+    assert shortest(torch.float16) <= 1.4 * shortest(torch.bfloat16)
