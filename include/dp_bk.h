@@ -229,9 +229,10 @@ dp_status dp_norms_multi_static(const dp_layer* layers, int L, dp_dtype dt, int 
  *   grad_offset  HOST array of L global element offsets (the layers' places in the flattened
  *                model; they need not be contiguous or ordered, but must not overlap)
  *   sigma, R     as dp_add_noise (sigma >= 0, finite; R > 0; sigma == 0 adds nothing)
- * Layers whose grad_offset is a multiple of 4 (fp32: all) get the noise in the gradient kernel's
- * epilogue; for the others, and for 16-bit sample slabs of 2 GiB and more, the noise pass runs on the
- * layer's slice after its gradient.  Errors as dp_clipped_grad_multi and dp_add_noise.
+ * fp32 layers get the noise in the gradient kernel's epilogue, 16-bit ones where every layer of their launch (up to
+ * 48 layers that take the same kernel) has a grad_offset that is a multiple of 4; for the launches with another
+ * offset, and for samples whose a or g has 2 GiB and more, the noise pass runs on the layers' slices
+ * after their gradients.  Errors as dp_clipped_grad_multi and dp_add_noise.
  */
 dp_status dp_clipped_grad_noise_multi(const dp_layer* layers, int L, dp_dtype dt, int B, const float* C,
                                       float* const* grads, const uint64_t* grad_offset, int accumulate,

@@ -227,3 +227,29 @@ def test_packed_rows_operand_ranges(dp, B, T, d, p):
         a[2, 0, 3] = 2.0 ** -126
         a[:, :, 5] = 2.0 ** -120
     check_weighted_gradient(dp, si.BF16, B, T, d, p, [0.5, 1e-3, 1e-5, 1.0, 0.1, 0.7], edit=tiny)
+
+
+# Narrow layers whose operands of the whole batch pass 2 GiB, the packed-row kernel's addressing: the 128 x 128 tiles
+# take them as long as one sample's slab fits, with the noise in the same pass.
+@pytest.mark.parametrize("B,T,d,p", [(16, 4224, 8, 16384), (33000, 1, 32768, 8)])
+def test_narrow_layers_beyond_the_packed_batch(dp, B, T, d, p):
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    a = torch.randn(B, T, d, device="cuda", generator=gen).to(torch.bfloat16)
+    g = torch.randn(B, T, p, device="cuda", generator=gen).to(torch.bfloat16)
+    assert B * T * max(d, p) * 2 > 2 ** 31
+    C = torch.rand(B, device="cuda", generator=gen)
+    C[B // 2] = 0
+    want = torch.zeros(d, p, dtype=torch.float64)
+    step = max(1, B // 16)
+    for i in range(0, B, step):
+        ca = a[i:i + step].double() * C[i:i + step].double()[:, None, None]
+        want += (ca.reshape(-1, d).t() @ g[i:i + step].double().reshape(-1, p)).cpu()
+    want = want.numpy()
+    desc = dp.layer_array([(a, g, T, d, p, 0)])
+    plain, noisy = torch.empty(d * p, device="cuda"), torch.empty(d * p, device="cuda")
+    dp.dp_clipped_grad_multi(desc, dp.DP_BF16, B, C, [plain])
+    assert frob(host(plain).reshape(d, p), want) <= TOL
+    lo, n = 6, d * p - 17
+    dp.dp_clipped_grad_noise_multi(desc, dp.DP_BF16, B, C, [noisy], [0], 0, lo, n, 0.5, 2.0, 3, 4)
+    dp.dp_add_noise(plain[lo:], lo, n, 0.5, 2.0, 3, 4)
+    assert torch.equal(noisy, plain)
