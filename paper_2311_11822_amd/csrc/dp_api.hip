@@ -1069,15 +1069,29 @@ int64_t dp_clipped_grad_tile_order(int d_in, int d_out, int32_t* tile_row0, int3
   if (d_in <= 0 || d_out <= 0 || capacity < 0) return -1;
   const int64_t n = clipped_grad_big_tiles(d_in, d_out);
   if (n > INT32_MAX / 2) return -1;
-  const int n_tail = clipped_grad_big_tail_tiles((int)n), n_main = (int)n - n_tail;
+  const GradTail cut = clipped_grad_tail((int)n, clipped_grad_mid_tiles(d_in, d_out));
+  const int n_main = (int)n - cut.tiles;
   const int tiles_m = (d_in + 255) / 256, tiles_n = (d_out + 255) / 256;
-  for (int64_t b = 0; b < n && b < capacity; ++b) {
-    // workgroups of the large-tile kernel first, then the tiles left to the sub-tile kernel
-    const int t = b < n_main ? grad_logical_tile((int)b, n_main) : (int)b;
+  auto put = [&](int64_t b, int t) {
     int tm, tn;
     grad_tile_of(tiles_m, tiles_n, t, tm, tn);
     if (tile_row0) tile_row0[b] = tm * 256;
     if (tile_col0) tile_col0[b] = tn * 256;
+  };
+  // workgroups of the large-tile kernel first, then the tiles that are cut, by the workgroup of their first sub-tile
+  for (int b = 0; b < n_main && b < capacity; ++b) put(b, grad_logical_tile(b, n_main));
+  if (capacity <= n_main) return n;
+  const int subs = cut.side * cut.side;
+  if ((int64_t)cut.tiles * subs > INT32_MAX) return -1;
+  const int total = cut.tiles * subs;
+  std::vector<uint16_t> seen(cut.tiles);
+  int64_t b = n_main;
+  for (int w = 0; w < total; ++w) {
+    const SubTile s = cut.side == kGradTailSide ? grad_sub_tile<kGradTailSide>(w, total) : grad_sub_tile<kGradMidSide>(w, total);
+    const int sub = s.row * cut.side + s.col;
+    if (s.tile < 0 || s.tile >= cut.tiles || sub >= subs || (seen[s.tile] >> sub & 1)) return -1;
+    seen[s.tile] |= 1 << sub;
+    if (sub == 0 && b < capacity) put(b++, n_main + s.tile);
   }
   return n;
 }

@@ -181,8 +181,14 @@ int ghost_brief_blocks(int B, int T);
 dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, hipStream_t s);
 // 256x256-tile kernel with direct global->LDS loads (grad_gemm.hip).
 int clipped_grad_big_tiles(int d, int p);
-// Of a launch of n large tiles, how many (the last ones) go to the sub-tile kernel.
-int clipped_grad_big_tail_tiles(int n);
+int64_t clipped_grad_mid_tiles(int d, int p);
+// Of a launch of n large tiles whose layers hold n_mid tiles of 128 x 128, how many (the last ones) are cut into
+// side x side sub-tiles.
+constexpr int kGradMidSide = 2, kGradTailSide = 4;
+struct GradTail {
+  int tiles, side;
+};
+GradTail clipped_grad_tail(int n, int64_t n_mid);
 bool clipped_grad_big_supports(int T, int d, int p);
 // noise == nullptr: gradients only.  out16: the layers' `out` pointers address 16-bit arrays of the
 // operands' storage type (bf16 or fp16) instead of fp32.

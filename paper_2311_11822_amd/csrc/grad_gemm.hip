@@ -90,22 +90,19 @@ clipped_grad_big_kernel(const GroupArgs ga, const float* __restrict__ C, const N
 
 // End of a launch.  All tiles of a launch take the same time and one workgroup fills a compute
 // unit, so n tiles run in ceil(n / 256) rounds; what the last round would hold is cut into 128 x 128
-// sub-tiles where these fill the chip better (clipped_grad_big_tail_tiles).  Workgroup b belongs to tile first_tile + b /
-// MID_SUBS of locate_tile's order.  The k-steps of an output element are added in the same order as
+// sub-tiles where these fill the chip better (clipped_grad_tail), in the order of grad_sub_tile.  The k-steps of an output element are added in the same order as
 // in the kernel above: the same bits.
-constexpr int MID_SUBS_N = BN / MidTile::BN, MID_SUBS = (BM / MidTile::BM) * MID_SUBS_N;
+constexpr int MID_SIDE = kGradMidSide, MID_SUBS = MID_SIDE * MID_SIDE;
+static_assert(MID_SIDE * MidTile::BM == BM && MID_SIDE * MidTile::BN == BN, "sub-tiles of a tile");
 
 template <bool F16, bool NOISE, bool OUT16>
 __global__ void __launch_bounds__(MidTile::NT, 2)
 clipped_grad_mid_kernel(const GroupArgs ga, const float* __restrict__ C, int first_tile, const NoiseArgs na) {
-  // Each XCD takes a contiguous run of the sub-tiles, so that those of a tile, which share its
-  // operand panels, meet in one L2.
-  const int logical = contiguous_eighth(blockIdx.x, gridDim.x);
+  const SubTile sub = grad_sub_tile<MID_SIDE>(blockIdx.x, gridDim.x);
   int l, m0, n0;
-  locate_tile(ga, first_tile + logical / MID_SUBS, l, m0, n0);
-  const int sub = logical % MID_SUBS;
-  m0 += (sub / MID_SUBS_N) * MidTile::BM;
-  n0 += (sub % MID_SUBS_N) * MidTile::BN;
+  locate_tile(ga, first_tile + sub.tile, l, m0, n0);
+  m0 += sub.row * MidTile::BM;
+  n0 += sub.col * MidTile::BN;
   if (m0 >= ga.layer[l].d_in || n0 >= ga.layer[l].d_out) return;      // past the layer's edge (whole workgroup)
   gradient_tile<MidTile, F16, NOISE, OUT16>(ga, l, m0, n0, C, na);
 }
@@ -113,7 +110,7 @@ clipped_grad_mid_kernel(const GroupArgs ga, const float* __restrict__ C, int fir
 // ---------------------------------------------------------------------------------
 // The last few tiles of a launch are cut finer still, into TAIL x TAIL sub-tiles of one small
 // workgroup each (register-staged tile code of tn_tile.h), which spreads them over the whole
-// chip.  Sub-tile b of the launch belongs to tile first_tile + b / SUBS of locate_tile's order.
+// chip.
 // ---------------------------------------------------------------------------------
 #ifndef DP_TAIL_SHAPE
 #define DP_TAIL_SHAPE 64, 64, 64, 2, 2
@@ -282,24 +279,20 @@ __device__ __forceinline__ void clipped_grad_tile_deep(const GroupLayer& ly, int
 // Sub-tiles are 64 x 64 (16 per tile), k-blocks of 64 rows, four k-blocks in flight: three
 // workgroups fit in a compute unit's LDS.
 using TailShape = TnShape<DP_TAIL_SHAPE>;
-constexpr int TAIL = 64, SUBS_N = BN / TAIL, SUBS = (BM / TAIL) * SUBS_N;
-static_assert(TailShape::BM == TAIL && TailShape::BN == TAIL, "sub-tile shape");
+constexpr int TAIL = 64, TAIL_SIDE = kGradTailSide, SUBS = TAIL_SIDE * TAIL_SIDE;
+static_assert(TailShape::BM == TAIL && TailShape::BN == TAIL && TAIL_SIDE * TAIL == BM && BM == BN, "sub-tile shape");
 
 template <bool F16, bool NOISE, bool OUT16>
 __global__ void __launch_bounds__(TailShape::NT)
 clipped_grad_tail_kernel(const GroupArgs ga, const float* __restrict__ C_all, int first_tile,
                          const NoiseArgs na) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds_tail[];
-  // Workgroup b runs on XCD b % 8: give each XCD a contiguous eighth of the sub-tiles (the grid
-  // is a multiple of 16), so that the 16 sub-tiles of a tile, which share its operand panels,
-  // meet in one L2.
-  const int logical = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const SubTile sub = grad_sub_tile<TAIL_SIDE>(blockIdx.x, gridDim.x);
   int l, m0, n0;
-  locate_tile(ga, first_tile + logical / SUBS, l, m0, n0);
+  locate_tile(ga, first_tile + sub.tile, l, m0, n0);
   const GroupLayer& ly = ga.layer[l];
-  const int sub = logical % SUBS;
-  m0 += (sub / SUBS_N) * TAIL;
-  n0 += (sub % SUBS_N) * TAIL;
+  m0 += sub.row * TAIL;
+  n0 += sub.col * TAIL;
   if (m0 >= ly.d_in || n0 >= ly.d_out) return;       // sub-tile past the layer's edge (whole workgroup)
   const __attribute__((address_space(4))) float* C =
       (const __attribute__((address_space(4))) float*)(uintptr_t)(C_all + ly.c_off);
@@ -318,18 +311,25 @@ bool clipped_grad_big_supports(int T, int d, int p) {
   return rows * d * 2 < (int64_t)1 << 31 && rows * p * 2 < (int64_t)1 << 31;
 }
 
-// Of a launch of n large tiles, how many (the last ones) go to the sub-tile kernels: those of the last round
-// where they fit one round of 128 x 128 sub-tiles.  K = 4096, alone: 64 tiles 94 us as they are, 51 as
-// sub-tiles; 128 tiles 96 and 74; 160 tiles 98 and 114.
-int clipped_grad_big_tail_tiles(int n) {
-  const int n_tail = n % kBigRound;
-  return n_tail * MID_SUBS > kMidRound ? 0 : n_tail;
+int64_t clipped_grad_mid_tiles(int d, int p) {
+  return ((int64_t)d + MidTile::BM - 1) / MidTile::BM * (((int64_t)p + MidTile::BN - 1) / MidTile::BN);
 }
 
-// Up to this many tiles are cut into 64 x 64: 16 tiles of K = 4096 take 34 us so, 44 us in 128 x 128; 32
+// The tiles of the last round go to sub-tiles where they fit one round of 128 x 128.  K = 4096, alone: 64 tiles 94 us
+// as they are, 51 as sub-tiles; 128 tiles 96 and 74; 160 tiles 98 and 114.  All tiles do where that takes fewer
+// rounds' time, because of the layers' edges (which sub-tiles leave out).
+// Up to kTailMax tiles are cut into 64 x 64: 16 tiles of K = 4096 take 34 us so, 44 us in 128 x 128; 32
 // tiles 43 and 46; 64 tiles 117 and 51 (sub-tiles fetch four times the operand bytes per flop of a
 // large tile, so their kernel runs at the rate the L2 delivers them).
-constexpr int kTailMax = 32;
+GradTail clipped_grad_tail(int n, int64_t n_mid) {
+  constexpr int kTailMax = 32;
+  int tail = n % kBigRound;
+  if (tail * MID_SUBS > kMidRound) tail = 0;
+  const int64_t mixed = (int64_t)(n / kBigRound) * kBigRoundCost +
+                        (tail ? kMidRoundCost : n % kBigRound ? kBigRoundCost : 0);
+  if (kMidRoundCost * ((n_mid + kMidRound - 1) / kMidRound) < mixed) tail = n;
+  return {tail, tail <= kTailMax ? TAIL_SIDE : MID_SIDE};
+}
 
 template <bool F16, bool NOISE, bool OUT16>
 dp_status launch_clipped_grad_big_group_t(const GroupArgs& ga, const float* C, const NoiseArgs& na,
@@ -343,16 +343,10 @@ dp_status launch_clipped_grad_big_group_t(const GroupArgs& ga, const float* C, c
   if (st == DP_OK) st = allow_big_lds(tail, (int)TailShape::LDS_BYTES, ready_tail);
   if (st != DP_OK) return st;
   const int n = ga.total_blocks;
-  int n_tail = clipped_grad_big_tail_tiles(n);
-  // All on sub-tiles where that takes fewer rounds' time, because of the layers' edges.
   int64_t n_mid = 0;
-  for (int j = 0; j < ga.n_layers; ++j) {
-    const int64_t d = ga.layer[j].d_in, p = ga.layer[j].d_out;
-    n_mid += ((d + MidTile::BM - 1) / MidTile::BM) * ((p + MidTile::BN - 1) / MidTile::BN);
-  }
-  const int64_t mixed = (int64_t)(n / kBigRound) * kBigRoundCost +
-                        (n_tail ? kMidRoundCost : n % kBigRound ? kBigRoundCost : 0);
-  if (kMidRoundCost * ((n_mid + kMidRound - 1) / kMidRound) < mixed) n_tail = n;
+  for (int j = 0; j < ga.n_layers; ++j) n_mid += clipped_grad_mid_tiles(ga.layer[j].d_in, ga.layer[j].d_out);
+  const GradTail cut = clipped_grad_tail(n, n_mid);
+  const int n_tail = cut.tiles;
   if (n > n_tail) {
     GroupArgs main_args = ga;
     main_args.total_blocks = n - n_tail;
@@ -361,7 +355,7 @@ dp_status launch_clipped_grad_big_group_t(const GroupArgs& ga, const float* C, c
     if (st != DP_OK) return st;
   }
   if (n_tail == 0) return DP_OK;
-  if (n_tail <= kTailMax)
+  if (cut.side == TAIL_SIDE)
     hipLaunchKernelGGL(tail, dim3(n_tail * SUBS), dim3(TailShape::NT), TailShape::LDS_BYTES, s, ga, C, n - n_tail, na);
   else
     hipLaunchKernelGGL(mid, dim3(n_tail * MID_SUBS), dim3(MidTile::NT), MidTile::LDS_BYTES, s, ga, C, n - n_tail, na);

@@ -51,6 +51,18 @@ __host__ __device__ __forceinline__ int grad_logical_tile(int block, int total) 
   return base + contiguous_eighth(q, imin(ROUND, total - base));
 }
 
+// Sub-tile launches (the last tiles of a launch, or all): workgroup -> tile, counted from the first one that is cut,
+// and place of the sub-tile in it.  Each XCD takes a contiguous run of the SIDE x SIDE sub-tiles, so that those of a
+// tile, which share its operand panels, meet in one L2.
+struct SubTile {
+  int tile, row, col;
+};
+template <int SIDE>
+__host__ __device__ __forceinline__ SubTile grad_sub_tile(int block, int total) {
+  const int logical = contiguous_eighth(block, total), sub = logical % (SIDE * SIDE);
+  return {logical / (SIDE * SIDE), sub / SIDE, sub % SIDE};
+}
+
 // ---------------------------------------------------------------------------------
 // Ghost norm: 256 x 128 tiles (I, J), J >= 2 I, of the T x T Gram matrices of each sample,
 // numbered sample by sample and, inside a sample, tile row by tile row (row I has nj - 2 I tiles).

@@ -156,3 +156,40 @@ def test_ghost_tile_order_is_a_bijection(dp, T, B):
     # partial-sum slots: each used once, and a sample's slots are contiguous
     assert sorted(slot.tolist()) == list(range(B * tps))
     assert np.all(slot // tps == sample)
+
+
+def sub_tile_order(n_tail, side):
+    """Tiles of a sub-tile launch by the workgroup of their first sub-tile: workgroup b runs on XCD b % 8, each XCD
+    takes a contiguous run of the side x side sub-tiles of every tile."""
+    total = n_tail * side * side
+    runs = np.array_split(np.arange(total), 8)               # the first total % 8 runs are one longer
+    order = [runs[b % 8][b // 8] for b in range(total)]
+    return [w // (side * side) for w in order if w % (side * side) == 0]
+
+
+# A launch may be cut whole into 128 x 128 (edges would leave 256 x 256 mostly empty), in its last round, or its last
+# tiles into 64 x 64.
+@pytest.mark.parametrize("d,p,n_tail,side", [
+    (264, 16640, 130, 2), (72, 120000, 469, 2), (136, 70000, 18, 4), (1032, 8200, 0, 4), (4352, 8448, 49, 2), (1800, 1544, 56, 2),
+    (256, 256, 1, 4), (8192, 2304, 32, 4), (8192, 2560, 64, 2), (12288, 12288, 0, 4)])
+def test_gradient_tile_order_of_cut_tiles(dp, d, p, n_tail, side):
+    r, c = dp.dp_clipped_grad_tile_order(d, p)
+    tiles_m, tiles_n = -(-d // 256), -(-p // 256)
+    assert len(r) == tiles_m * tiles_n and len(set(zip(r.tolist(), c.tolist()))) == len(r)
+    # the numbering behind the order: a launch of as many tiles whose first workgroups are all there is
+    number = {}
+    for q, t in enumerate(grad_tiles_in_number_order(tiles_m, tiles_n)):
+        number[t] = q
+    got = [number[(y // 256, x // 256)] for y, x in zip(r[len(r) - n_tail:].tolist(), c[len(r) - n_tail:].tolist())]
+    assert got == [len(r) - n_tail + t for t in sub_tile_order(n_tail, side)]
+
+
+def grad_tiles_in_number_order(tiles_m, tiles_n):
+    """Tile numbers of a layer: super-patches of 16 x 16 row by row, in them patches of 4 x 8, in them columns."""
+    for sr in range(0, tiles_m, 16):
+        for sc in range(0, tiles_n, 16):
+            for pr in range(sr, min(sr + 16, tiles_m), 4):
+                for pc in range(sc, min(sc + 16, tiles_n), 8):
+                    for tn in range(pc, min(pc + 8, sc + 16, tiles_n)):
+                        for tm in range(pr, min(pr + 4, sr + 16, tiles_m)):
+                            yield tm, tn
