@@ -89,8 +89,11 @@ def _stream(stream) -> Optional[int]:
     import torch
     if torch.cuda.is_initialized():
         # the handle behind current_stream().cuda_stream without building a Stream object (2.9 -> 0.6 us; a step
-        # of one small layer makes three calls in 30 us)
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        # of one small layer makes three calls in 30 us); private to torch, so not taken for granted
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            pass
     return torch.cuda.current_stream().cuda_stream
 
 

@@ -193,3 +193,17 @@ def grad_tiles_in_number_order(tiles_m, tiles_n):
                     for tn in range(pc, min(pc + 8, sc + 16, tiles_n)):
                         for tm in range(pr, min(pr + 4, sr + 16, tiles_m)):
                             yield tm, tn
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_torch_private_functions(dp, monkeypatch, missing):
+    torch = pytest.importorskip("torch")
+    from types import SimpleNamespace
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: SimpleNamespace(cuda_stream=77))
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.setattr(torch._C, name, lambda *a: 78, raising=False)
+    assert dp._stream(None) == 78
+    monkeypatch.delattr(torch._C, missing)
+    assert dp._stream(None) == 77
+    assert dp._stream(5) == 5
