@@ -62,7 +62,8 @@ using Tall = Shape<128, 32, 4, 1>;
 using Tall2 = Shape<128, 64, 4, 1>;
 using Flat = Shape<32, 128, 1, 4>;
 using Flat2 = Shape<64, 128, 2, 2>;
-constexpr int LDS_BYTES = NSTAGE * Wide::STAGE_BYTES;          // 65 KiB: two workgroups per compute unit
+constexpr int FLAGS = NSTAGE * Wide::STAGE_BYTES;              // a word per wave behind the stages
+constexpr int LDS_BYTES = FLAGS + 16;                          // 65 KiB: two workgroups per compute unit
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 constexpr float kScale = 0x1p80f;                             // of the weights: see "Range"
@@ -249,25 +250,24 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // zero-fill loads past the end
 
-  bool off = least_w < kLeastWeight<F16>;
+  float largest = 0.f;                                   // NaN if a sum is
 #pragma unroll
   for (int y = 0; y < S::TN; ++y)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       acc[y][r] = (acc[y][r] + low[y][r]) * (1.f / kScale);
-      off |= !(fabsf(acc[y][r]) <= FLT_MAX);
+      largest = __builtin_elementwise_maximum(largest, fabsf(acc[y][r]));
     }
-  __syncthreads();                                       // LDS is reused
+  const bool off = least_w < kLeastWeight<F16> || !(largest <= FLT_MAX);
   typedef __attribute__((address_space(3))) int lds_int;
   const bool wave_off = __any(off);
-  if (lane == 0) *(lds_int*)(uintptr_t)(lds0 + 4 * wave) = wave_off;
-  __syncthreads();
+  if (lane == 0) *(lds_int*)(uintptr_t)(lds0 + FLAGS + 4 * wave) = wave_off;
+  __syncthreads();                                       // nobody reads a stage any more either
   int any_off = 0;
 #pragma unroll
-  for (int v = 0; v < 4; ++v) any_off |= *(lds_int*)(uintptr_t)(lds0 + 4 * v);
-  if (any_off) {
+  for (int v = 0; v < 4; ++v) any_off |= *(lds_int*)(uintptr_t)(lds0 + FLAGS + 4 * v);
+  if (__builtin_amdgcn_readfirstlane(any_off)) {
     // The tile again, unweighted, sample by sample (low: the sample's sum so far).
-    __syncthreads();                                     // the flags have been read
 #pragma unroll
     for (int y = 0; y < S::TN; ++y)
 #pragma unroll
