@@ -103,7 +103,7 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
       continue;
     }
     // instantiated norm: the kernel with the deep load pipeline unless a slab is beyond its
-    // 32-bit addressing, on large tiles (fewer partial sums in the same slots) where they pay
+    // 32-bit addressing, on large tiles (with the same partial sums) where they pay
     bool dma = kernel == kPerex, big = false;
     for (int j = 0; j < ga.n_layers; ++j)
       dma = dma && perex_dma_supports(ga.layer[j].T, ga.layer[j].d_in, ga.layer[j].d_out);
@@ -128,6 +128,9 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
                    : dma                    ? launch_perex_dma_group(ga, partials, big, s)
                                             : launch_perex_group(ga, partials, s);
     if (st != DP_OK) return st;
+    if (big)
+      for (int j = 0; j < ga.n_layers; ++j)
+        ga.layer[j].tiles_per_sample = perex_tiles_per_sample(ga.layer[j].d_in, ga.layer[j].d_out);
     st = launch_norm_reduce_group(ga, partials, sqnorm_out, s);
     if (st != DP_OK) return st;
   }

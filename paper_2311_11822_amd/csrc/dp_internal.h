@@ -157,7 +157,7 @@ int clipped_grad_tiles(int d, int p);
 dp_status launch_ghost_group(const GroupArgs& ga, float* partials, hipStream_t s);
 dp_status launch_perex_group(const GroupArgs& ga, float* partials, hipStream_t s);
 // With direct global->LDS loads, three k-blocks ahead (perex_dma.hip); tiles of 128 x 128 as above or, `big`,
-// of 256 x 256 (ga laid out for clipped_grad_big_tiles tiles per sample).
+// of 256 x 256 (ga laid out for clipped_grad_big_tiles tiles per sample, partial sums as above: the same bits).
 bool perex_dma_supports(int T, int d, int p);
 dp_status launch_perex_dma_group(const GroupArgs& ga, float* partials, bool big, hipStream_t s);
 // Narrow layers on tiles of the 128 x 128 ones' numbering (perex_narrow.hip).

@@ -73,23 +73,33 @@ perex_dma_kernel(const GroupArgs ga, float* __restrict__ partials) {
           acc[x][y][r] = in ? acc[x][y][r] : 0.f;
         }
   }
-  float sum = 0.f;
-#pragma unroll
-  for (int x = 0; x < S::TM; ++x)
-#pragma unroll
-    for (int y = 0; y < S::TN; ++y)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sum = fmaf(acc[x][y][r], acc[x][y][r], sum);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+  // One partial sum per 128 x 128, added in the same order on either tile (four 64 x 64 pieces, two MFMA rows each):
+  // the tile is chosen by what else is in the launch, and a layer's norm must not depend on that.
+  constexpr int SIDE = S::BM / 128, SUBS = SIDE * SIDE, PIECES = S::TM / 2;
   float* red = reinterpret_cast<float*>(lds_raw);
-  if (lane == 0) red[wave] = sum;
+#pragma unroll
+  for (int h = 0; h < PIECES; ++h) {
+    float sum = 0.f;
+#pragma unroll
+    for (int x = 2 * h; x < 2 * h + 2; ++x)
+#pragma unroll
+      for (int y = 0; y < S::TN; ++y)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum = fmaf(acc[x][y][r], acc[x][y][r], sum);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+    const int row = wm + 64 * h;                        // of the piece, inside the tile
+    if (lane == 0) red[4 * (row / 128 * SIDE + wn / 128) + 2 * (row / 64 % 2) + wn / 64 % 2] = sum;
+  }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < SUBS) {
     float total = 0.f;
 #pragma unroll
-    for (int w = 0; w < S::WM * S::WN; ++w) total += red[w];
-    partials[ly.part_begin + local] = total;
+    for (int w = 0; w < 4; ++w) total += red[4 * threadIdx.x + w];
+    const int row = m0 + 128 * (threadIdx.x / SIDE), col = n0 + 128 * (threadIdx.x % SIDE);
+    const int subs_m = (d + 127) / 128, subs_n = (p + 127) / 128;
+    if (row < d && col < p)
+      partials[ly.part_begin + (sample * subs_m + row / 128) * subs_n + col / 128] = total;
   }
 }
 

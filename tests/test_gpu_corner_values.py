@@ -253,3 +253,20 @@ def test_narrow_layers_beyond_the_packed_batch(dp, B, T, d, p):
     dp.dp_clipped_grad_noise_multi(desc, dp.DP_BF16, B, C, [noisy], [0], 0, lo, n, 0.5, 2.0, 3, 4)
     dp.dp_add_noise(plain[lo:], lo, n, 0.5, 2.0, 3, 4)
     assert torch.equal(noisy, plain)
+
+
+# A layer's squared norms do not depend on the stack it stands in, though the tiles do: 256 x 256 ones where a launch
+# fills whole rounds of them.
+@pytest.mark.parametrize("dtype", HALF)
+@pytest.mark.parametrize("L,B,T,d,p", [(32, 8, 70, 256, 256), (10, 16, 40, 384, 520), (24, 16, 33, 200, 264)])
+def test_instantiated_norms_do_not_depend_on_the_stack(dp, dtype, L, B, T, d, p):
+    check_stack_independence(dp, dtype, 1, L, B, T, d, p)
+
+
+def check_stack_independence(dp, dtype, path, L, B, T, d, p):
+    stack, a, g = norms_of_copies(dp, dtype, path, L, B, T, d, p)
+    alone, a1, g1 = norms_of_copies(dp, dtype, path, 1, B, T, d, p)
+    assert torch.equal(a, a1) and torch.equal(g, g1)
+    assert torch.all(stack == alone)
+    np.testing.assert_allclose(host(alone[0]), (o.ghost_sqnorm, o.perex_sqnorm)[path](host(a.float()), host(g.float())),
+                               rtol=TOL)
