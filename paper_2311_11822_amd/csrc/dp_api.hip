@@ -35,6 +35,20 @@ bool ghost_uses_big(const dp_layer& ly) {
   return ly.T >= 96 && ghost_big_supports(ly.T, ly.d_in, ly.d_out);
 }
 
+// Up to 128 tokens a sample is one workgroup in either kernel.  The large-tile kernel keeps deeper prefetch and has a
+// compute unit to itself; of the other two share one, and a round of these 512 takes 5/3 of the time of 256 large
+// ones (112 tokens, d_in + d_out = 912: 25.1 and 15.3 us).  So the rounds decide, but narrow layers, whose samples are
+// over before a deep prefetch pays, stay on the small kernel beyond one round (d_in + d_out = 272: 12.5 and 9.7 us a
+// round), and wide ones on the large kernel (2096: 43.5 and 24.4).  512 samples 24 + 16 wide: 10.0 us here, 13.3 on the
+// large kernel, 2048 of 392 + 296: 80 and 94; 768 of 760 + 520: 49.5 and 45.9.
+// Whole 64-wide k-blocks: the large kernel, which has no edge handling there.
+bool ghost_stays_small(const dp_layer& ly, int64_t samples) {
+  if (ly.T > 128 || (ly.d_in % 64 == 0 && ly.d_out % 64 == 0)) return false;
+  const int64_t width = (int64_t)ly.d_in + ly.d_out;
+  if (samples <= 256 || width >= 1800) return false;
+  return width < 500 || 3 * ((samples + 255) / 256) >= 5 * ((samples + 511) / 512);
+}
+
 // Samples of 129 .. 256 tokens take the kernel that holds a whole sample in one workgroup.
 bool ghost_uses_sample(const dp_layer& ly) { return ghost_sample_supports(ly.T, ly.d_in, ly.d_out); }
 
@@ -203,13 +217,16 @@ dp_status norms_impl(const dp_layer* layers, int L, dp_dtype dt, int B, float* s
   int* list[kNormKernels];
   for (int k = 0; k < kNormKernels; ++k) list[k] = idx + (size_t)k * L;
   int count[kNormKernels] = {};
+  int64_t samples = 0;                                   // that either large-tile or 128 x 128 kernel may take
+  for (int l = 0; l < L; ++l)
+    if (layers[l].path == DP_PATH_GHOST && ghost_uses_big(layers[l]) && layers[l].T <= 128) samples += B;
   for (int l = 0; l < L; ++l) {
     const bool narrow = perex_narrow_supports(layers[l].T, layers[l].d_in, layers[l].d_out);
     const int k = layers[l].path == DP_PATH_PEREX ? (narrow ? kPerexNarrow : kPerex)
                   : ghost_brief_supports(layers[l].T) ? kGhostBrief
                   : ghost_uses_sample(layers[l])  ? kGhostSample
-                  : ghost_uses_big(layers[l])     ? kGhostBig
-                                                  : kGhostSmall;
+                  : ghost_uses_big(layers[l]) && !ghost_stays_small(layers[l], samples) ? kGhostBig
+                                                                                        : kGhostSmall;
     list[k][count[k]++] = l;
   }
   float* partials = static_cast<float*>(ws);

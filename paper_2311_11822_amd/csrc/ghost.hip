@@ -161,9 +161,11 @@ ghost_norm_kernel(const GroupArgs ga, float* __restrict__ partials) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (lane == 0) red[wave] = s;
   __syncthreads();
+  // Pieces, products and sums in the order of the large-tile kernel's diagonal tile: which of the two takes a
+  // sample of 96 .. 128 tokens depends on the launch, and its norm must not.
+  static_assert(S::WM == 2 && S::WN == 2, "four pieces");
   if (threadIdx.x == 0) {
-    float total = 0.f;
-    for (int w = 0; w < S::WM * S::WN; ++w) total += red[w];
+    const float total = (red[0] + red[1]) + (red[2] + red[3]);
     partials[ly.part_begin + local] = t.diag ? total : 2.f * total;
   }
 }

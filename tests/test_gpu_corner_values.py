@@ -270,3 +270,12 @@ def check_stack_independence(dp, dtype, path, L, B, T, d, p):
     assert torch.all(stack == alone)
     np.testing.assert_allclose(host(alone[0]), (o.ghost_sqnorm, o.perex_sqnorm)[path](host(a.float()), host(g.float())),
                                rtol=TOL)
+
+
+# Ghost norms of 96 .. 128 tokens and widths off the 64-column k-blocks: the number of samples of the call chooses between
+# 128 x 128 tiles and the large-tile kernel, with the same bits.
+@pytest.mark.parametrize("dtype", HALF)
+@pytest.mark.parametrize("L,B,T,d,p", [(12, 40, 112, 392, 296), (9, 30, 96, 24, 136), (20, 60, 128, 264, 1000),
+                                       (3, 90, 105, 520, 72), (12, 40, 120, 256, 64)])
+def test_ghost_norms_do_not_depend_on_the_stack(dp, dtype, L, B, T, d, p):
+    check_stack_independence(dp, dtype, 0, L, B, T, d, p)
