@@ -363,6 +363,9 @@ dp_status noise_after(const NoiseSpec* noise, int l, const dp_layer& ly, float* 
 //      65 .. 127          48     18    bf16 645-690 / 690 at T = 32, 650 at 48, 420-450 at 256;
 //                                      fp16 1220-1380 / 1370 at T = 16, 1100 at 20
 //      128 and more       20     10    4096 rows of eight layers 1024 x 1024 .. 4096: 566 / 684 at T = 16, 352 at 32
+//    A batch of one sample (fp16: two) pays the other kernels next to nothing: eight layers 4096 x 4096, one token:
+//    141 us packed, 129 on the tiles (fp16 158 and 131); one layer 72 x 3000 12.5 and 7.1; eight layers 1024 x 1024
+//    15.8 and 16.9.  (A layer's kernel depends on nothing but the layer: the same bits in any stack.)
 //    Without the lines (everything with a side below 128 packed) fp16 stacks of 65 .. 127 columns took 1220 us where
 //    the register-staged kernel they came from took 570 .. 600 from 256 tokens on, and bf16 ones 645.
 //  kGradBig: slabs its 32-bit addressing reaches.
@@ -379,7 +382,9 @@ int packed_below(int side, bool f16) {
 }
 
 GradKernel grad_kernel_of(const dp_layer& ly, dp_dtype dt, int B) {
-  const bool packed = ly.T < packed_below(std::min(ly.d_in, ly.d_out), dt == DP_F16);
+  const int side = std::min(ly.d_in, ly.d_out);
+  const bool few = side > 64 && B <= (dt == DP_F16 ? 2 : 1);
+  const bool packed = !few && ly.T < packed_below(side, dt == DP_F16);
   if (packed && grad_packed_supports(B, ly.T, ly.d_in, ly.d_out)) return kGradPacked;
   return clipped_grad_big_supports(ly.T, ly.d_in, ly.d_out) ? kGradBig : kGradEdge;
 }
