@@ -138,11 +138,26 @@ perex_narrow_kernel(const GroupArgs ga, float* __restrict__ partials) {
     run(Flat2{});
 }
 
+// Long samples of many tiles: half a compute unit's LDS each, so that two workgroups share it and not four.  An XCD's
+// 128 workgroups would stream from twice as many samples at a time, which costs 5 to 7 % once the loads set the time
+// (96 samples of 4096 tokens, 2048 x 16: 293 us, so 277; of 256 tokens four are better, 19 us against 22).
+constexpr int kLongTokens = 1024, kLongTiles = 16, kHalfLds = 79 * 1024;
+
 template <bool F16>
 dp_status launch_t(const GroupArgs& ga, float* partials, hipStream_t s) {
-  int lds = NSTAGE * Tall::STAGE_BYTES;
-  for (int j = 0; j < ga.n_layers; ++j)
-    if (ga.layer[j].d_in > 32 && ga.layer[j].d_out > 32) lds = NSTAGE * Tall2::STAGE_BYTES;
+  int lds = NSTAGE * Tall::STAGE_BYTES, tiles = 0, T = INT32_MAX;
+  for (int j = 0; j < ga.n_layers; ++j) {
+    const GroupLayer& ly = ga.layer[j];
+    if (ly.d_in > 32 && ly.d_out > 32) lds = NSTAGE * Tall2::STAGE_BYTES;
+    tiles = ly.tiles_per_sample > tiles ? ly.tiles_per_sample : tiles;
+    T = ly.T < T ? ly.T : T;
+  }
+  if (T >= kLongTokens && tiles >= kLongTiles) {
+    static ReadyTable ready;
+    lds = kHalfLds;
+    dp_status st = allow_big_lds(perex_narrow_kernel<F16>, lds, ready);
+    if (st != DP_OK) return st;
+  }
   hipLaunchKernelGGL(perex_narrow_kernel<F16>, dim3(ga.total_blocks), dim3(NT), lds, s, ga, partials);
   return hip_status(hipGetLastError());
 }
