@@ -52,14 +52,16 @@ __host__ __device__ __forceinline__ int grad_logical_tile(int block, int total) 
 }
 
 // Sub-tile launches (the last tiles of a launch, or all): workgroup -> tile, counted from the first one that is cut,
-// and place of the sub-tile in it.  Each XCD takes a contiguous run of the SIDE x SIDE sub-tiles, so that those of a
-// tile, which share its operand panels, meet in one L2.
+// and place of the sub-tile in it.  Runs of 32 sub-tiles per XCD, as above, so that those of a tile, which share its
+// operand panels, meet in one L2.  (A contiguous eighth of the launch each serves the L2 as well, but a shard's noise lies
+// in consecutive tiles and then falls to few XCDs: one sample of two layers 2904 x 1384, noise on a quarter of
+// the gradient, 21.4 us against 14.6.)
 struct SubTile {
   int tile, row, col;
 };
 template <int SIDE>
 __host__ __device__ __forceinline__ SubTile grad_sub_tile(int block, int total) {
-  const int logical = contiguous_eighth(block, total), sub = logical % (SIDE * SIDE);
+  const int logical = grad_logical_tile(block, total), sub = logical % (SIDE * SIDE);
   return {logical / (SIDE * SIDE), sub / SIDE, sub % SIDE};
 }
 

@@ -160,10 +160,13 @@ def test_ghost_tile_order_is_a_bijection(dp, T, B):
 
 def sub_tile_order(n_tail, side):
     """Tiles of a sub-tile launch by the workgroup of their first sub-tile: workgroup b runs on XCD b % 8, each XCD
-    takes a contiguous run of the side x side sub-tiles of every tile."""
+    takes a contiguous run of each 256 of the side x side sub-tiles of every tile."""
     total = n_tail * side * side
-    runs = np.array_split(np.arange(total), 8)               # the first total % 8 runs are one longer
-    order = [runs[b % 8][b // 8] for b in range(total)]
+    order = []
+    for base in range(0, total, 256):
+        part = np.arange(base, min(base + 256, total))
+        runs = np.array_split(part, 8)                       # the first len % 8 runs are one longer
+        order += [runs[b % 8][b // 8] for b in range(len(part))]
     return [w // (side * side) for w in order if w % (side * side) == 0]
 
 
