@@ -321,9 +321,14 @@ int64_t clipped_grad_mid_tiles(int d, int p) {
 // Up to kTailMax tiles are cut into 64 x 64: 16 tiles of K = 4096 take 34 us so, 44 us in 128 x 128; 32
 // tiles 43 and 46; 64 tiles 117 and 51 (sub-tiles fetch four times the operand bytes per flop of a
 // large tile, so their kernel runs at the rate the L2 delivers them).
-GradTail clipped_grad_tail(int n, int64_t n_mid) {
-  constexpr int kTailMax = 32;
+// Short contractions (rows: 32-token blocks of all samples, in tokens) are bound by the epilogue, which a large tile has
+// a compute unit to itself for: 128 x 128, two to a unit, unless large ones come in whole rounds.  One sample:
+// two layers 3744 x 2352 33.2 us mixed, 24.7 on 128 x 128 (before: 29); 17 of 33 tokens 76 and 69; 16 of 100 104 and
+// 104; four layers 4096 x 4096 (four whole rounds) 62 and 66; 24 of 768 x 3072 64 and 59, three of 40 tokens 79 and 80.
+GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows) {
+  constexpr int kTailMax = 32, kShortRows = 512;
   int tail = n % kBigRound;
+  if (n > kTailMax && tail != 0 && rows * (n < kBigRound ? 1 : n / kBigRound) <= kShortRows) return {n, MID_SIDE};
   if (tail * MID_SUBS > kMidRound) tail = 0;
   const int64_t mixed = (int64_t)(n / kBigRound) * kBigRoundCost +
                         (tail ? kMidRoundCost : n % kBigRound ? kBigRoundCost : 0);
@@ -343,9 +348,14 @@ dp_status launch_clipped_grad_big_group_t(const GroupArgs& ga, const float* C, c
   if (st == DP_OK) st = allow_big_lds(tail, (int)TailShape::LDS_BYTES, ready_tail);
   if (st != DP_OK) return st;
   const int n = ga.total_blocks;
-  int64_t n_mid = 0;
-  for (int j = 0; j < ga.n_layers; ++j) n_mid += clipped_grad_mid_tiles(ga.layer[j].d_in, ga.layer[j].d_out);
-  const GradTail cut = clipped_grad_tail(n, n_mid);
+  int64_t n_mid = 0, rows = 0;
+  for (int j = 0; j < ga.n_layers; ++j) {
+    const GroupLayer& ly = ga.layer[j];
+    n_mid += clipped_grad_mid_tiles(ly.d_in, ly.d_out);
+    const int64_t r = (int64_t)ga.B * ((ly.T + BigTile::BK - 1) / BigTile::BK) * BigTile::BK;
+    rows = r > rows ? r : rows;
+  }
+  const GradTail cut = clipped_grad_tail(n, n_mid, rows);
   const int n_tail = cut.tiles;
   if (n > n_tail) {
     GroupArgs main_args = ga;
