@@ -363,9 +363,11 @@ dp_status noise_after(const NoiseSpec* noise, int l, const dp_layer& ly, float* 
 //      65 .. 127          48     18    bf16 645-690 / 690 at T = 32, 650 at 48, 420-450 at 256;
 //                                      fp16 1220-1380 / 1370 at T = 16, 1100 at 20
 //      128 and more       20     10    4096 rows of eight layers 1024 x 1024 .. 4096: 566 / 684 at T = 16, 352 at 32
-//    A batch of one sample (fp16: two) pays the other kernels next to nothing: eight layers 4096 x 4096, one token:
-//    141 us packed, 129 on the tiles (fp16 158 and 131); one layer 72 x 3000 12.5 and 7.1; eight layers 1024 x 1024
-//    15.8 and 16.9.  (A layer's kernel depends on nothing but the layer: the same bits in any stack.)
+//    A batch of one or two samples pays the other kernels next to nothing: eight layers 4096 x 4096, one token: 141 us
+//    packed, 129 on the tiles (fp16 158 and 131), one layer 72 x 3000 12.5 and 7.1, 24 layers 768 x 3072 64 and 60.
+//    In fp16, sides up to 64 stay packed below 1024 rows of the batch, where the tiles' padding of the side is not paid
+//    for yet: seven layers 6016 x 64, 40 rows 11 us and 20, 918 rows 49 and 70, 1024 rows 53 and 49.
+//    (A layer's kernel depends on nothing but the layer: the same bits in any stack.)
 //    Without the lines (everything with a side below 128 packed) fp16 stacks of 65 .. 127 columns took 1220 us where
 //    the register-staged kernel they came from took 570 .. 600 from 256 tokens on, and bf16 ones 645.
 //  kGradBig: slabs its 32-bit addressing reaches.
@@ -374,17 +376,18 @@ enum GradKernel { kGradBig = 0, kGradPacked = 1, kGradEdge = 2 };
 constexpr int kGradKernels = 3;
 
 // Samples of fewer tokens than this take the packed kernel.
-int packed_below(int side, bool f16) {
-  if (side <= 32) return f16 ? 48 : INT32_MAX;
-  if (side <= 64) return f16 ? 28 : INT32_MAX;
+int packed_below(int side, bool f16, int64_t rows) {
+  if (side <= 64 && (!f16 || rows < 1024)) return INT32_MAX;
+  if (side <= 32) return 48;
+  if (side <= 64) return 28;
   if (side < 128) return f16 ? 18 : 48;
   return f16 ? 10 : 20;
 }
 
 GradKernel grad_kernel_of(const dp_layer& ly, dp_dtype dt, int B) {
   const int side = std::min(ly.d_in, ly.d_out);
-  const bool few = side > 64 && B <= (dt == DP_F16 ? 2 : 1);
-  const bool packed = !few && ly.T < packed_below(side, dt == DP_F16);
+  const bool few = side > 64 && B <= 2;
+  const bool packed = !few && ly.T < packed_below(side, dt == DP_F16, (int64_t)B * ly.T);
   if (packed && grad_packed_supports(B, ly.T, ly.d_in, ly.d_out)) return kGradPacked;
   return clipped_grad_big_supports(ly.T, ly.d_in, ly.d_out) ? kGradBig : kGradEdge;
 }

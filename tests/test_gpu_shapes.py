@@ -234,11 +234,21 @@ def test_ghost_norm_ragged_widths(dtype, T):
     (si.F16, 17, [(72, 264), (264, 120), (120, 96)]), (si.F16, 18, [(72, 264), (264, 120), (120, 96)]),
     (si.F16, 27, [(40, 264), (264, 64), (48, 120)]), (si.F16, 28, [(40, 264), (264, 64), (48, 120)]),
     (si.F16, 47, [(16, 264), (264, 32), (8, 24)]), (si.F16, 48, [(16, 264), (264, 32), (8, 24)]),
-    (si.F16, 70, [(24, 1104), (392, 520), (1104, 88), (56, 136)]),
+    (si.F16, 70, [(24, 1104), (392, 520), (1104, 88), (56, 136)]), (si.BF16, 9, [(128, 520), (72, 264), (264, 264)]),
 ])
-def test_narrow_sides_at_the_packed_lines(dtype, T, dims):
-    check_step(dtype, 3, T, dims, paths=[0] * len(dims))
-    check_step(dtype, 4, T, dims, paths=[0] * len(dims), mode=o.CLIP_AUTOMATIC, mask=[1])
+@pytest.mark.parametrize("B", [2, 4, 40])                       # 40 samples: more rows than the line of narrow fp16 sides
+def test_narrow_sides_at_the_packed_lines(dtype, T, dims, B):
+    check_step(dtype, B, T, dims, paths=[0] * len(dims))
+    check_step(dtype, B, T, dims, paths=[0] * len(dims), mode=o.CLIP_AUTOMATIC, mask=[1])
+
+
+# Short contractions, whose tiles are cut into 128 x 128 throughout (60 and 280 large tiles), just below and above the
+# line.
+@pytest.mark.parametrize("dtype", HALF)
+@pytest.mark.parametrize("B,T,dims", [(1, 70, [(1800, 1928)]), (15, 31, [(1800, 1928)]), (17, 31, [(1800, 1928)]),
+                                      (2, 33, [(1800, 1928), (1544, 1288), (2824, 3336)])])
+def test_short_contractions(dtype, B, T, dims):
+    check_step(dtype, B, T, dims, paths=[0] * len(dims))
 
 
 def test_fp16_narrow_layers_keep_pace_with_bf16():
