@@ -60,36 +60,44 @@ perex_dma_kernel(const GroupArgs ga, float* __restrict__ partials) {
       }
   }
 
-  // Rows and columns past the layer's edge were loaded as zeros, but an infinity of the other operand
-  // makes NaN of them: they stay out of the sum (d_out is a multiple of 8, so runs of four are in or out).
-  if (m0 + S::BM > d || n0 + S::BN > p) {
-#pragma unroll
-    for (int x = 0; x < S::TM; ++x)
-#pragma unroll
-      for (int y = 0; y < S::TN; ++y)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const bool in = m0 + wm + x * 32 + (lane & 31) < d && n0 + wn + y * 32 + 8 * (r >> 2) + 4 * (lane >> 5) < p;
-          acc[x][y][r] = in ? acc[x][y][r] : 0.f;
-        }
-  }
   // One partial sum per 128 x 128, added in the same order on either tile (four 64 x 64 pieces, two MFMA rows each):
   // the tile is chosen by what else is in the launch, and a layer's norm must not depend on that.
   constexpr int SIDE = S::BM / 128, SUBS = SIDE * SIDE, PIECES = S::TM / 2;
   float* red = reinterpret_cast<float*>(lds_raw);
+  float sum[PIECES];
 #pragma unroll
-  for (int h = 0; h < PIECES; ++h) {
-    float sum = 0.f;
+  for (int h = 0; h < PIECES; ++h) sum[h] = 0.f;
+  if (m0 + wm + S::WTM <= d && n0 + wn + S::WTN <= p) {
 #pragma unroll
-    for (int x = 2 * h; x < 2 * h + 2; ++x)
+    for (int x = 0; x < 2; ++x)
 #pragma unroll
       for (int y = 0; y < S::TN; ++y)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) sum = fmaf(acc[x][y][r], acc[x][y][r], sum);
+        for (int r = 0; r < 16; ++r)
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+          for (int h = 0; h < PIECES; ++h) sum[h] = fmaf(acc[2 * h + x][y][r], acc[2 * h + x][y][r], sum[h]);
+  } else {
+    // Rows and columns past the layer's edge were loaded as zeros, but an infinity of the other operand
+    // makes NaN of them: they stay out.  d_out is a multiple of 8: eight columns, four to a half wave, are in or out.
+#pragma unroll
+    for (int x = 0; x < S::TM; ++x)
+      if (m0 + wm + x * 32 + (lane & 31) < d)
+#pragma unroll
+        for (int y = 0; y < S::TN; ++y)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (n0 + wn + y * 32 + 8 * q < p)
+#pragma unroll
+              for (int r = 4 * q; r < 4 * q + 4; ++r) sum[x / 2] = fmaf(acc[x][y][r], acc[x][y][r], sum[x / 2]);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+    for (int h = 0; h < PIECES; ++h) sum[h] += __shfl_xor(sum[h], off);
+#pragma unroll
+  for (int h = 0; h < PIECES; ++h) {
     const int row = wm + 64 * h;                        // of the piece, inside the tile
-    if (lane == 0) red[4 * (row / 128 * SIDE + wn / 128) + 2 * (row / 64 % 2) + wn / 64 % 2] = sum;
+    if (lane == 0) red[4 * (row / 128 * SIDE + wn / 128) + 2 * (row / 64 % 2) + wn / 64 % 2] = sum[h];
   }
   __syncthreads();
   if (threadIdx.x < SUBS) {

@@ -125,9 +125,17 @@ norm_reduce_kernel(const GroupArgs ga, const float* __restrict__ partials, float
   const int l = blockIdx.x / ga.B, i = blockIdx.x % ga.B;
   const GroupLayer& ly = ga.layer[l];
   const float* src = partials + ly.part_begin + (size_t)i * ly.tiles_per_sample;
-  // 64 lanes each add a strided subset in order, then a fixed butterfly: deterministic.
+  // 64 lanes each add a strided subset in order, then a fixed butterfly: deterministic.  Four loads at a time: one
+  // after the other, 1012 sums took 1.7 us longer.
   float s = 0.f;
-  for (int q = threadIdx.x; q < ly.tiles_per_sample; q += 64) s += src[q];
+  const int n = ly.tiles_per_sample;
+  for (int q0 = threadIdx.x; q0 < n; q0 += 256) {
+    float v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = q0 + 64 * j < n ? src[q0 + 64 * j] : 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s += v[j];
+  }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
   if (threadIdx.x == 0) sqnorm[(size_t)ly.sq_index * ga.B + i] = s;
