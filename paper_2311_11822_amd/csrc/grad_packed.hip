@@ -32,7 +32,7 @@
 // sums beyond 2^48), the workgroup forms its tile again without the cutting: the same loads, the rows of one
 // sample at a time, unweighted, folded in as total += C_i * sum.  (One wave on its own, two rows of its 32 x 32
 // pieces at a time straight from memory, took 52.6 ms for 131072 rows of eight 768 x 16 layers; so 4.4, and 2.1
-// where all is finite.)  The scaling and the test cost 2 % of the kernel.
+// where all is finite.)  The scaling, where each weight is used, and the test cost nothing measurable (4 % of a launch of a few workgroups).
 #include <float.h>
 
 #include "dp_internal.h"
@@ -186,8 +186,6 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
         fb[ks][y] = __builtin_bit_cast(u32x4, read_row_frag<S::BN>(b_rd[y] + so + ks * 16 * S::BN * 2));
     }
     DP_PIN();
-#pragma unroll
-    for (int e = 0; e < 16; ++e) w[e >> 3][(e >> 2) & 1][e & 3] *= kScale;
     least_w = own == 0.f ? least_w : fminf(least_w, fabsf(own));
     if (__any(own == 0.f)) {                             // rows that do not count (or lie past the end)
 #pragma unroll
@@ -208,7 +206,7 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
         const f4 ww = w[ks][q >> 1];
         const int e = 2 * q & 3;
         uint32_t part[3];
-        cut_product(ww[e], widen_lo<F16>(fa[ks][q]), ww[e + 1], widen_hi<F16>(fa[ks][q]), part);
+        cut_product(ww[e] * kScale, widen_lo<F16>(fa[ks][q]), ww[e + 1] * kScale, widen_hi<F16>(fa[ks][q]), part);
 #pragma unroll
         for (int n = 0; n < 3; ++n) xa[ks][n][q] = part[n];
 #pragma unroll

@@ -129,10 +129,10 @@ norm_reduce_kernel(const GroupArgs ga, const float* __restrict__ partials, float
   // after the other, 1012 sums took 1.7 us longer.
   float s = 0.f;
   const int n = ly.tiles_per_sample;
-  for (int q0 = threadIdx.x; q0 < n; q0 += 256) {
+  for (unsigned q0 = threadIdx.x; q0 < (unsigned)n; q0 += 256) {
     float v[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = q0 + 64 * j < n ? src[q0 + 64 * j] : 0.f;
+    for (int j = 0; j < 4; ++j) v[j] = q0 + 64 * j < (unsigned)n ? src[q0 + 64 * j] : 0.f;
 #pragma unroll
     for (int j = 0; j < 4; ++j) s += v[j];
   }
