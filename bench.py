@@ -328,7 +328,8 @@ def main():
         with open(os.path.join(ROOT, "profiles", "l2_miss_traffic.json")) as f:
             per = json.load(f)["per_launch"][w.name]
         traffic = sum(per[k]["fetch_bytes"] + per[k]["write_bytes"]
-                      for k in ("clipped_grad_big_kernel", "clipped_grad_tail_kernel") if k in per)
+                      for k in ("clipped_grad_big_kernel", "clipped_grad_mid_kernel", "clipped_grad_tail_kernel")
+                      if k in per)
     except (OSError, KeyError, ValueError):
         pass
     props = torch.cuda.get_device_properties(0)
