@@ -32,8 +32,9 @@
  *    DP_ERR_UNSUPPORTED, DP_ERR_WORKSPACE) means nothing has been enqueued.  A
  *    launch the runtime refuses gives DP_ERR_HIP; the multi-layer calls consist of
  *    several launches, so earlier ones may already be queued then.
- *  - DP_F32 layers run on the vector ALUs, one workgroup per sample in the norm
- *    kernels: they are meant for layers of a few thousand elements.  A norm that
+ *  - DP_F32 layers run on the fp32 matrix instructions (fp32 operands and sums),
+ *    one workgroup per layer and sample in the norm kernel: they are meant for
+ *    layers of a few thousand elements.  A norm that
  *    needs more than 2^28 multiply-adds per sample (T^2 (d_in + d_out) / 2 for the
  *    ghost norm, T d_in d_out for the instantiated one) is refused with
  *    DP_ERR_UNSUPPORTED; store such layers in a 16-bit type.
@@ -140,8 +141,9 @@ dp_status dp_clip_factors(const float* sqnorm, int L, int B, dp_clip_mode mode, 
 /*
  * Clip-weighted gradient (section 3, "DP gradient" without the noise term):
  *   grad[j, k] (+)= sum_i C[i] * sum_t a[i,t,j] * g[i,t,k],   j < d_in, k < d_out.
- * C[i] is applied in fp32 to sample i's exact partial product, never to the bf16 inputs.
- * Samples with C[i] == 0 are not read.  The 16-bit kernels keep one accumulator, expressed in
+ * C[i] is applied in fp32 to exact products, never to the 16-bit inputs: nothing of it is rounded
+ * to 16 bits.  Samples with C[i] == 0 are not counted, whatever they hold.  Short samples and narrow
+ * layers take any finite weights.  The other 16-bit kernels keep one accumulator, expressed in
  * units of the current sample's weight, and multiply it by C[i] / C[i+1] between samples: any
  * finite weights work whose ratios C[i] / C[j] (j the next sample with a non-zero weight) times
  * the largest partial sum stay inside fp32 range -- in particular every set of clip factors of

@@ -148,8 +148,8 @@ dp_status launch_bias_norm(const void* g, dp_dtype dt, int B, int T, int p, floa
 
 dp_status launch_clipped_bias_grad(const float* colsum, int B, int p, const float* C, float* grad_b,
                                    int accumulate, hipStream_t s) {
-  hipLaunchKernelGGL(clipped_bias_kernel, dim3((p + kSumThreads - 1) / kSumThreads), dim3(kSumThreads), 0, s, colsum, B, p, C, grad_b,
-                     accumulate);
+  hipLaunchKernelGGL(clipped_bias_kernel, dim3((p + kSumThreads - 1) / kSumThreads), dim3(kSumThreads), 0, s, colsum,
+                     B, p, C, grad_b, accumulate);
   return hip_status(hipGetLastError());
 }
 

@@ -9,14 +9,14 @@
 // by rounding C a to fp32.  fp16 operands: g (11 bits) is cut into two bfloat16 parts exactly, six
 // instructions.  Gradients measured against 64 bits: 1.4e-7 (T = 1, B = 512) and 2.1e-7 (T = 31) here,
 // 6.0e-7 and 3.9e-7 in the large-tile kernel.
-//   Measured, eight layers of 1024 x 1024 .. 4096 outputs, bf16: B = 512, T = 1: 1384 us before, 89 us
-// here; 4096 rows: 560 us here whatever T is (what bounds it: the matrix cores at the clock they hold
+//   Measured, eight layers of 1024 x 1024 .. 4096 outputs, bf16: B = 512, T = 1: 1384 us before, 87 us here; 4096
+// rows: 570 us here for T = 16, 620 for T = 1 (what bounds it: the matrix cores at the clock they hold
 // under load, then the cutting), fp16 1080 us; the large-tile kernel 684 us at T = 16, 352 at 32.
-// grad_kernel_of (dp_api.hip) draws its line there.
+// packed_below (dp_api.hip) draws its lines there.
 //
-// Tiles (four waves, 32 gradient rows each where the layer is wide): 128 x 128, or 128 x 32, 128 x 64 and their transposes for layers
-// narrower than a tile, where the stream over the wide operand is the bound and padding the
-// narrow one to 128 would multiply its LDS traffic.  Operand rows go global -> LDS without passing
+// Tiles (four waves, 32 gradient rows each where the layer is wide): 128 x 128, or 128 x 32, 128 x 64 and
+// their transposes for layers narrower than a tile, where the stream over the wide operand is the bound and padding
+// the narrow one to 128 would multiply its LDS traffic.  Operand rows go global -> LDS without passing
 // through registers, four stages of 32 rows, three blocks in flight; the 32 rows' weights travel
 // with them (a 4-byte gather of C by row / T).  Two workgroups share a compute unit: one's splitting
 // runs beside the other's matrix instructions.
@@ -32,7 +32,8 @@
 // sums beyond 2^48), the workgroup forms its tile again without the cutting: the same loads, the rows of one
 // sample at a time, unweighted, folded in as total += C_i * sum.  (One wave on its own, two rows of its 32 x 32
 // pieces at a time straight from memory, took 52.6 ms for 131072 rows of eight 768 x 16 layers; so 4.4, and 2.1
-// where all is finite.)  The scaling, where each weight is used, and the test cost nothing measurable (4 % of a launch of a few workgroups).
+// where all is finite.)  The scaling, where each weight is used, and the test cost nothing measurable (4 % of a launch
+// of a few workgroups).
 #include <float.h>
 
 #include "dp_internal.h"

@@ -97,7 +97,7 @@ HALF = [si.BF16, si.F16]
 
 
 # Packed-row gradient (short samples, narrow layers): one token, tokens that divide no 32-row block, a
-# total below and off a multiple of 32, tile edges and the three tile shapes, masked samples
+# total below and off a multiple of 32, tile edges and the five tile shapes, masked samples
 # that hold NaN (first, inside, last).
 @pytest.mark.parametrize("dtype", HALF)
 @pytest.mark.parametrize("B,T,dims", [
