@@ -271,3 +271,33 @@ def test_fp16_narrow_layers_keep_pace_with_bf16():
         return min(us)
 
     assert shortest(torch.float16) <= 1.4 * shortest(torch.bfloat16)
+
+
+# The weighted contraction's stream on 256 x 256 tiles (a whole round of them) and on 128 x 128: samples that end inside
+# a 32-row block (odd numbers of 16-row steps), samples of one block with and without gaps, fewer and more samples
+# than the 64 whose weights a wave holds, windows without a sample that counts, and equal weights.
+@pytest.mark.parametrize("side,n", [(2048, 4), (1536, 1)])
+@pytest.mark.parametrize("B,T,zero", [
+    (3, 21, ()), (64, 32, ()), (65, 32, (0, 63, 64)), (67, 20, ()), (131, 24, tuple(range(64, 128))), (66, 33, (1, 2, 65)),
+    (5, 48, (4,)), (7, 40, (0, 1, 3)), (3, 49, ()), (2, 112, ()), (4, 33, (0, 1, 2, 3)),
+])
+def test_weighted_stream(side, n, B, T, zero):
+    from paper_2311_11822_amd import binding as dp
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(B * 1000 + T)
+    layers = [tuple(torch.randn((B, T, side), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+              for _ in range(n)]
+    desc = dp.layer_array([(a, g, T, side, side, dp.DP_PATH_GHOST) for a, g in layers])
+    C = torch.rand(B, generator=gen, device="cuda") + 0.1
+    C[B // 2:B // 2 + 2] = 0.75                           # two equal weights in a row: no multiply between them
+    for i in zero:
+        C[i] = 0.0
+        for a, _ in layers:
+            a[i] = float("nan")
+    grads = [torch.full((side, side), float("nan"), device="cuda") for _ in layers]
+    dp.dp_clipped_grad_multi(desc, dp.DP_BF16, B, C, grads)
+    keep = C != 0
+    for (a, g), got in zip(layers, grads):
+        weighted = (a[keep].double() * C[keep].double()[:, None, None]).reshape(-1, side)
+        want = weighted.t().contiguous() @ g[keep].double().reshape(-1, side)
+        assert torch.linalg.norm(got.double() - want) <= TOL * torch.linalg.norm(want)
