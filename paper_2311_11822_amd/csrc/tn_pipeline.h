@@ -200,9 +200,9 @@ __device__ __forceinline__ float tn_contract(const void* a, const void* g, int T
   auto read_frag = [&](int buf, int q, int stage, int ks) {
     const bool is_b = q == 0 || q == 2;
     const int i = is_b ? q >> 1 : q == 1 ? 0 : q - 2;
-    unsigned addr = (is_b ? b_rd[i] : a_rd[i]) + stage * STAGE_BYTES;
-    asm("" : "+v"(addr));                                // one address, the rest in the instructions' offsets
-    addr += ks * KSTEP * ROW_BYTES;
+    unsigned base = stage * STAGE_BYTES;
+    asm("" : "+s"(base));                                // one address, the rest in the instructions' offsets
+    const unsigned addr = (is_b ? b_rd[i] : a_rd[i]) + base + ks * KSTEP * ROW_BYTES;
     Frag& f = is_b ? fb[buf][i] : fa[buf][i];
     f.h[0] = lds_read_tr(addr);
     f.h[1] = lds_read_tr(addr + 4 * ROW_BYTES);
