@@ -2,7 +2,7 @@
 // 1^T dL/ds_i, the sum of sample i's T output-gradient rows; its norm is taken by
 // instantiation.  The B x d_out matrix of these sums is tiny, so it is kept (book-keeping): the
 // clipped bias gradient sum_i C_i 1^T g_i is then formed from it without reading g again.
-// Both kernels are streams over memory (HBM-bound); sums run in a fixed order.
+// The kernels are streams over memory (HBM-bound) or, for small samples, latency-bound; sums run in a fixed order.
 #include "dp_internal.h"
 
 namespace dpbk {
@@ -71,6 +71,78 @@ bias_colsum_kernel(const void* __restrict__ g_all, int T, int p, float* __restri
   }
 }
 
+// Column sums and their norm in one launch, one workgroup to a sample, where that is no slower than two: a launch costs
+// the host 2.4 us, and one compute unit reads 90 GB/s.  Thread (rg, ct) adds rows rg, rg + groups, ... of its 8 columns,
+// eight rows in flight and added in pairs; the row groups are added through LDS.  Times on the GPU, us, here and in two
+// launches (8 samples): 32 tokens of 768 columns 3.2 and 4.6, 128 x 256 3.4 and 4.3, 8 x 8192 5.2 and 5.1,
+// 128 x 768 5.0 and 5.0, 32 x 3072 5.1 and 5.1, 128 x 1536 7.2 and 5.1.  Up to 256 columns the two-launch form has one workgroup to a sample
+// too, of a quarter of the loads in flight: 2048 x 64 5.9 and 11.3, 2048 x 256 13 and 17.
+constexpr int kOneThreads = 1024, kOneRows = 8;
+template <int DT>
+__global__ void __launch_bounds__(kOneThreads)
+bias_norm_kernel(const uint16_t* __restrict__ g_all, int T, int p, float* __restrict__ colsum, float* __restrict__ sqnorm) {
+  __shared__ float red[kOneThreads * 8];
+  __shared__ float wave_sum[kOneThreads / 64];
+  const int tid = threadIdx.x, i = blockIdx.x;
+  const int chunks = p / 8;                              // at most kOneThreads
+  const int groups = min(kOneThreads / chunks, (T + kOneRows - 1) / kOneRows);
+  const int rg = tid / chunks, ct = tid - rg * chunks;
+  if (rg < groups) {
+    const uint16_t* g = g_all + (size_t)i * T * p + 8 * ct;
+    float acc[8] = {};
+    for (unsigned t0 = rg; t0 < (unsigned)T; t0 += kOneRows * groups) {
+      uint4 w[kOneRows];
+#pragma unroll
+      for (int u = 0; u < kOneRows; ++u) {
+        const unsigned t = min(t0 + u * groups, (unsigned)T - 1);
+        w[u] = *reinterpret_cast<const uint4*>(g + (size_t)t * p);
+      }
+#pragma unroll
+      for (int u = 0; u < kOneRows; ++u)
+        if (t0 + u * groups >= (unsigned)T) w[u] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        float v[kOneRows];
+#pragma unroll
+        for (int u = 0; u < kOneRows; ++u) {
+          const uint32_t x[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
+          const uint32_t pair = x[k / 2];
+          if (DT == DP_BF16)
+            v[u] = __uint_as_float(k & 1 ? pair & 0xFFFF0000u : pair << 16);      // bf16 -> fp32 is a shift
+          else
+            v[u] = (float)__builtin_bit_cast(_Float16, (uint16_t)(k & 1 ? pair >> 16 : pair & 0xFFFFu));
+        }
+        acc[k] += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) red[rg * p + 8 * ct + k] = acc[k];
+  }
+  __syncthreads();
+  float s = 0.f;
+  for (int c = tid; c < p; c += kOneThreads) {
+    float part[4] = {};
+    int r = 0;
+    for (; r + 4 <= groups; r += 4)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) part[q] += red[(r + q) * p + c];
+    for (; r < groups; ++r) part[r & 3] += red[r * p + c];
+    const float v = (part[0] + part[1]) + (part[2] + part[3]);
+    colsum[(size_t)i * p + c] = v;
+    s = fmaf(v, v, s);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+  if ((tid & 63) == 0) wave_sum[tid >> 6] = s;
+  __syncthreads();
+  if (tid == 0) {
+    float total = 0.f;
+#pragma unroll
+    for (int w = 0; w < kOneThreads / 64; ++w) total += wave_sum[w];
+    sqnorm[i] = total;
+  }
+}
+
 // These two kernels move a few hundred KiB at most: what bounds them is the chain of memory latencies of a
 // thread, so every thread asks for all it needs at once.  (One load after the other, the square
 // sum took 4.1 us and the weighted sum 4.8 us for 8 x 768 .. 3072 values; so 2.7 and 3.3.)
@@ -129,10 +201,20 @@ clipped_bias_kernel(const float* __restrict__ colsum, int B, int p, const float*
   grad_b[k] = accumulate ? old + s : s;
 }
 
+constexpr int kOneColumns = 256, kOneValues = 160 * 512;
+
 }  // namespace
 
 dp_status launch_bias_norm(const void* g, dp_dtype dt, int B, int T, int p, float* colsum,
                            float* sqnorm_out, hipStream_t s) {
+  if (dt != DP_F32 && p <= 8 * kOneThreads && (p <= kOneColumns || (int64_t)T * p <= kOneValues)) {
+    const uint16_t* g16 = static_cast<const uint16_t*>(g);
+    if (dt == DP_BF16)
+      hipLaunchKernelGGL(bias_norm_kernel<DP_BF16>, dim3(B), dim3(kOneThreads), 0, s, g16, T, p, colsum, sqnorm_out);
+    else
+      hipLaunchKernelGGL(bias_norm_kernel<DP_F16>, dim3(B), dim3(kOneThreads), 0, s, g16, T, p, colsum, sqnorm_out);
+    return hip_status(hipGetLastError());
+  }
   const int cols_per_block = kColThreads * (dt == DP_F32 ? 1 : 8);
   const dim3 grid((p + cols_per_block - 1) / cols_per_block, B), block(kRowGroups * kColThreads);
   if (dt == DP_BF16)

@@ -301,3 +301,23 @@ def test_weighted_stream(side, n, B, T, zero):
         weighted = (a[keep].double() * C[keep].double()[:, None, None]).reshape(-1, side)
         want = weighted.t().contiguous() @ g[keep].double().reshape(-1, side)
         assert torch.linalg.norm(got.double() - want) <= TOL * torch.linalg.norm(want)
+
+
+# Column sums and their norm in one launch and in two: fewer and more rows than a thread takes at once, row groups that
+# do not come out even, the widest row of the one-launch form and one beyond, both sides of its line.
+@pytest.mark.parametrize("dtype", HALF)
+@pytest.mark.parametrize("B,T,p", [
+    (1, 1, 8), (3, 7, 8), (2, 9, 24), (5, 70, 264), (2, 8, 8192), (2, 7, 8200), (3, 160, 512), (3, 161, 512), (2, 700, 256),
+    (2, 700, 264), (1, 4097, 16),
+])
+def test_bias_norm_forms(dtype, B, T, p):
+    from paper_2311_11822_amd import binding as dp
+    dt = {si.BF16: dp.DP_BF16, si.F16: dp.DP_F16}[dtype]
+    w = si.small_workload("bias", dtype, B, T, [(8, p)], g_std=1.0)
+    g = si.gen_layer(w, 0)[1]
+    colsum = torch.full((B, p), float("nan"), device="cuda")
+    sq = torch.full((B,), float("nan"), device="cuda")
+    dp.dp_bias_norm(dev(g), dt, B, T, p, colsum, sq)
+    g64 = si.to_f64(g)
+    assert frob(host(colsum), o.bias_per_sample_grad(g64)) <= TOL
+    np.testing.assert_allclose(host(sq), o.bias_sqnorm(g64), rtol=TOL)
