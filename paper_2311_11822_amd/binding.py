@@ -57,6 +57,8 @@ _PROTOS = {
     "dp_norms_multi_keep": (_i, [C.POINTER(dp_layer), _i, _i, _i, _vp, C.POINTER(_vp), _vp, _sz, _vp]),
     "dp_clipped_grad_kept_multi": (_i, [C.POINTER(dp_layer), _i, _i, _i, _vp, C.POINTER(_vp), C.POINTER(_vp),
                                        C.POINTER(_u64), _i, _u64, _u64, _f, _f, _u64, _u64, _vp]),
+    "dp_private_step_multi": (_i, [C.POINTER(dp_layer), _i, _i, _i, _i, _f, _f, C.POINTER(_vp), C.POINTER(_vp),
+                                  C.POINTER(_u64), _i, _u64, _u64, _f, _u64, _u64, _vp, _vp, _vp, _vp, _sz, _vp]),
     "dp_layerwise_workspace_bytes": (_sz, [C.POINTER(dp_layer), _i, _i, _i]),
     "dp_layerwise_clipped_grad": (_i, [C.POINTER(dp_layer), _i, _i, _i, C.POINTER(_f), _i, _f, C.POINTER(_vp),
                                       C.POINTER(_u64), _i, _u64, _u64, _f, _u64, _u64, _vp, _vp, _vp, _sz, _i, _vp]),
@@ -261,6 +263,18 @@ def dp_clipped_grad_kept_multi(layers, dt, B, Cf, kept, grads, grad_offset, accu
     _check(lib.dp_clipped_grad_kept_multi(arr, len(arr), dt, B, _ptr(Cf), _ptr_array(kept) if kept is not None else None,
                                           _ptr_array(grads), offs, accumulate, shard_offset, shard_count, sigma, R,
                                           seed, step, _stream(stream)), "dp_clipped_grad_kept_multi")
+
+
+def dp_private_step_multi(layers, dt, B, mode, R, stability, kept, grads, grad_offset, accumulate, shard_offset,
+                          shard_count, sigma, seed, step, sqnorm_out, C_out, norm_out, ws, stream=None) -> None:
+    arr = layers if isinstance(layers, C.Array) else layer_array(layers)
+    offs = None
+    if grad_offset is not None:
+        offs = grad_offset if isinstance(grad_offset, C.Array) else (C.c_uint64 * len(grad_offset))(*grad_offset)
+    _check(lib.dp_private_step_multi(arr, len(arr), dt, B, mode, R, stability,
+                                     _ptr_array(kept) if kept is not None else None, _ptr_array(grads), offs, accumulate,
+                                     shard_offset, shard_count, sigma, seed, step, _ptr(sqnorm_out), _ptr(C_out),
+                                     _ptr(norm_out), _ptr(ws), _nbytes(ws), _stream(stream)), "dp_private_step_multi")
 
 
 def dp_layerwise_workspace_bytes(layers, dt, B) -> int:

@@ -63,6 +63,32 @@ bool perex_on_big_tiles(int64_t n_big, int64_t n_mid) {
   return kBigRoundCost * ((n_big + kBigRound - 1) / kBigRound) < kMidRoundCost * ((n_mid + kMidRound - 1) / kMidRound);
 }
 
+// Clip factors that the norm launches form on the way.
+struct ClipSpec {
+  int mode;
+  float stability;
+  float* C_out;
+  const float* layer_R;          // layer-wise: thresholds by layer of the call; nullptr: all layers in one group
+  float R;                       // one group
+  float* norm_out;
+};
+
+// One group: the last launch of partial sums, not added up yet.
+struct PendingReduce {
+  GroupArgs ga;
+  bool any = false;
+};
+
+// For the kernels' arguments, R still to be filled in.
+LayerClip layer_clip(const ClipSpec* clip) {
+  LayerClip lc;
+  const bool layer_wise = clip && clip->layer_R;
+  lc.C_out = layer_wise ? clip->C_out : nullptr;
+  lc.mode = layer_wise ? clip->mode : 0;
+  lc.stability = layer_wise ? clip->stability : 0.f;
+  return lc;
+}
+
 // Launches the norm kernels of one path for the listed layers, in chunks of kMaxGroup.
 // part_begin[l] is the layer's first slot in the partial-sum workspace.
 enum NormKernel { kGhostBig = 0, kGhostSmall = 1, kPerex = 2, kGhostSample = 3, kGhostBrief = 4, kPerexNarrow = 5 };
@@ -70,7 +96,8 @@ constexpr int kNormKernels = 6;
 
 dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, int n_which,
                         const int64_t* part_begin, dp_dtype dt, int B, float* partials,
-                        float* sqnorm_out, hipStream_t s, const int* row_of, float* const* kept) {
+                        float* sqnorm_out, hipStream_t s, const int* row_of, float* const* kept,
+                        const ClipSpec* clip, PendingReduce* pending) {
   // A tile's length is the contraction it runs over (d_in + d_out for the ghost norm, T for the
   // instantiated one).  Longest first: workgroups are handed out in order, so the short tiles
   // fill the end of the launch.  Each layer writes its own workspace slots and sqnorm row, so
@@ -87,6 +114,7 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
   }
   for (int begin = 0; begin < n_which; begin += kMaxGroup) {
     GroupArgs ga;
+    LayerClip lc = layer_clip(clip);
     ga.B = B;
     ga.accumulate = 0;
     ga.f16 = dt == DP_F16;
@@ -95,6 +123,7 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
     for (int j = 0; j < ga.n_layers; ++j) {
       const int l = which[begin + j];
       GroupLayer& gl = ga.layer[j];
+      if (lc.C_out) lc.R[j] = clip->layer_R[l];
       gl.a = layers[l].a;
       gl.g = layers[l].g;
       gl.out = (kernel == kPerex || kernel == kPerexNarrow) && kept ? kept[l] : nullptr;
@@ -111,8 +140,8 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
     }
     ga.total_blocks = (int)blocks;
     if (kernel == kGhostBrief || kernel == kGhostSample) {       // final norms: nothing to add up
-      dp_status st = kernel == kGhostBrief ? launch_ghost_brief_group(ga, sqnorm_out, s)
-                                           : launch_ghost_sample_group(ga, sqnorm_out, s);
+      dp_status st = kernel == kGhostBrief ? launch_ghost_brief_group(ga, sqnorm_out, lc, s)
+                                           : launch_ghost_sample_group(ga, sqnorm_out, lc, s);
       if (st != DP_OK) return st;
       continue;
     }
@@ -145,8 +174,10 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
     if (big)
       for (int j = 0; j < ga.n_layers; ++j)
         ga.layer[j].tiles_per_sample = perex_tiles_per_sample(ga.layer[j].d_in, ga.layer[j].d_out);
-    st = launch_norm_reduce_group(ga, partials, sqnorm_out, s);
+    if (pending) std::swap(pending->ga, ga);             // the launch before it, if any, is added up now
+    if (!pending || pending->any) st = launch_norm_reduce_group(ga, partials, sqnorm_out, lc, s);
     if (st != DP_OK) return st;
+    if (pending) pending->any = true;
   }
   return DP_OK;
 }
@@ -165,12 +196,24 @@ int64_t norm_slots(const dp_layer* layers, int L, dp_dtype dt, int B, int64_t* b
   return total;
 }
 
+// The factors of one group over all layers, together with the partial sums that wait, if there are any.
+constexpr int kNormClipSamples = 1 << 20;                // workgroups of 1024 threads: one grid dimension
+dp_status group_clip(const ClipSpec* clip, const PendingReduce* pending, float* sqnorm, const float* partials, int L, int B,
+                     hipStream_t s) {
+  if (!clip || clip->layer_R) return DP_OK;
+  if (pending && pending->any)
+    return launch_norm_clip(pending->ga, partials, sqnorm, L, clip->mode, clip->R, clip->stability, clip->C_out,
+                            clip->norm_out, s);
+  return launch_clip_factors(sqnorm, L, B, clip->mode, clip->R, clip->stability, clip->C_out, clip->norm_out, s);
+}
+
 // begin: room for L values; idx: room for kNormKernels * L values (the layers of each kernel).  The caller
 // provides both so that this function never touches the heap.  row_of (or nullptr): layer l's
-// squared norms go to row row_of[l] of sqnorm_out instead of row l.
+// squared norms go to row row_of[l] of sqnorm_out instead of row l.  clip (or nullptr): clip factors too, of each layer,
+// or (row_of is nullptr then) of all together.
 dp_status norms_impl(const dp_layer* layers, int L, dp_dtype dt, int B, float* sqnorm_out, void* ws,
                      size_t ws_bytes, hipStream_t s, int64_t* begin, int* idx, const int* row_of = nullptr,
-                     float* const* kept = nullptr) {
+                     float* const* kept = nullptr, const ClipSpec* clip = nullptr) {
   if (!dtype_ok(dt)) return DP_ERR_INVALID_ARG;
   if (!sqnorm_out) return DP_ERR_INVALID_ARG;
   const int64_t slots = norm_slots(layers, L, dt, B, begin);
@@ -190,6 +233,7 @@ dp_status norms_impl(const dp_layer* layers, int L, dp_dtype dt, int B, float* s
     const int per_launch = std::max(1, std::min(kMaxGroup, INT32_MAX / 2 / B));
     for (int l0 = 0; l0 < L; l0 += per_launch) {
       GroupArgs ga;
+      LayerClip lc = layer_clip(clip);
       ga.B = B;
       ga.accumulate = 0;
       ga.f16 = 0;
@@ -205,12 +249,13 @@ dp_status norms_impl(const dp_layer* layers, int L, dp_dtype dt, int B, float* s
         gl.d_out = ly.d_out;
         gl.path = ly.path;
         gl.sq_index = row_of ? row_of[l0 + j] : l0 + j;
+        if (lc.C_out) lc.R[j] = clip->layer_R[l0 + j];
       }
       ga.total_blocks = ga.n_layers * B;
-      dp_status st = launch_norms_f32_group(ga, sqnorm_out, s);
+      dp_status st = launch_norms_f32_group(ga, sqnorm_out, lc, s);
       if (st != DP_OK) return st;
     }
-    return DP_OK;
+    return group_clip(clip, nullptr, sqnorm_out, nullptr, L, B, s);
   }
   if (!ws || ws_bytes < (size_t)slots * sizeof(float)) return DP_ERR_WORKSPACE;
   if (!aligned16(ws)) return DP_ERR_INVALID_ARG;
@@ -230,20 +275,23 @@ dp_status norms_impl(const dp_layer* layers, int L, dp_dtype dt, int B, float* s
     list[k][count[k]++] = l;
   }
   float* partials = static_cast<float*>(ws);
+  PendingReduce held;
+  PendingReduce* pending = clip && !clip->layer_R && B <= kNormClipSamples && norm_clip_supports(L) ? &held : nullptr;
   for (int k = 0; k < kNormKernels; ++k) {
     dp_status st = run_norm_path((NormKernel)k, layers, list[k], count[k], begin, dt, B, partials, sqnorm_out, s,
-                                 row_of, kept);
+                                 row_of, kept, clip, pending);
     if (st != DP_OK) return st;
   }
-  return DP_OK;
+  return group_clip(clip, pending, sqnorm_out, partials, L, B, s);
 }
 
 dp_status norms_impl(const dp_layer* layers, int L, dp_dtype dt, int B, float* sqnorm_out, void* ws,
-                     size_t ws_bytes, hipStream_t s, const int* row_of = nullptr, float* const* kept = nullptr) {
+                     size_t ws_bytes, hipStream_t s, const int* row_of = nullptr, float* const* kept = nullptr,
+                     const ClipSpec* clip = nullptr) {
   if (!layers || L <= 0) return DP_ERR_INVALID_ARG;
   std::vector<int64_t> begin(L);
   std::vector<int> idx(kNormKernels * (size_t)L);
-  return norms_impl(layers, L, dt, B, sqnorm_out, ws, ws_bytes, s, begin.data(), idx.data(), row_of, kept);
+  return norms_impl(layers, L, dt, B, sqnorm_out, ws, ws_bytes, s, begin.data(), idx.data(), row_of, kept, clip);
 }
 
 dp_status single_norm(dp_path path, const void* a, const void* g, dp_dtype dt, int B, int T, int d_in,
@@ -790,6 +838,27 @@ dp_status dp_clipped_grad_kept_multi(const dp_layer* layers, int L, dp_dtype dt,
   return kept_sum_impl(layers, L, B, C, nullptr, kept, grads, noisy ? &spec : nullptr, accumulate, s);
 }
 
+dp_status dp_private_step_multi(const dp_layer* layers, int L, dp_dtype dt, int B, dp_clip_mode mode, float R,
+                                float stability, float* const* kept, float* const* grads, const uint64_t* grad_offset,
+                                int accumulate, uint64_t shard_offset, uint64_t shard_count, float sigma, uint64_t seed,
+                                uint64_t step, float* sqnorm_out, float* C_out, float* norm_out, void* ws,
+                                size_t ws_bytes, void* stream) {
+  if (!layers || L <= 0 || !C_out) return DP_ERR_INVALID_ARG;
+  if (mode != DP_CLIP_STANDARD && mode != DP_CLIP_AUTOMATIC) return DP_ERR_INVALID_ARG;
+  if (!(R > 0.f) || !(stability >= 0.f) || isinf(stability)) return DP_ERR_INVALID_ARG;
+  const dp_status kept_ok = check_kept(layers, L, dt, kept);
+  if (kept_ok != DP_OK) return kept_ok;
+  const ClipSpec clip = {(int)mode, stability, C_out, nullptr, R, norm_out};
+  const dp_status st = norms_impl(layers, L, dt, B, sqnorm_out, ws, ws_bytes, static_cast<hipStream_t>(stream), nullptr,
+                                  kept, &clip);
+  if (st != DP_OK) return st;
+  if (kept)
+    return dp_clipped_grad_kept_multi(layers, L, dt, B, C_out, kept, grads, grad_offset, accumulate, shard_offset,
+                                      shard_count, sigma, R, seed, step, stream);
+  return dp_clipped_grad_noise_multi(layers, L, dt, B, C_out, grads, grad_offset, accumulate, shard_offset, shard_count,
+                                     sigma, R, seed, step, stream);
+}
+
 }  // extern "C"
 
 // ---------------------------------------------------------------------------------
@@ -978,6 +1047,7 @@ dp_status dp_layerwise_clipped_grad(const dp_layer* layers, int L, dp_dtype dt, 
     //     (instantiated layers keep G_i in the workspace: their gradient is sum_i C_i G_i)
     std::vector<dp_layer> sub;
     std::vector<int> row, c_off;
+    std::vector<float> sub_R;
     std::vector<float*> sub_grads, sub_kept;
     std::vector<uint64_t> sub_off;
     bool any_kept = false;
@@ -985,6 +1055,7 @@ dp_status dp_layerwise_clipped_grad(const dp_layer* layers, int L, dp_dtype dt, 
       if (fp.shape[l] < 0) {
         sub.push_back(layers[l]);
         row.push_back(l);
+        sub_R.push_back(R[l]);
         c_off.push_back(l * B);
         sub_grads.push_back(grads[l]);
         sub_off.push_back(noisy ? grad_offset[l] : 0);
@@ -993,13 +1064,9 @@ dp_status dp_layerwise_clipped_grad(const dp_layer* layers, int L, dp_dtype dt, 
       }
     if (!sub.empty()) {
       const int n = (int)sub.size();
+      const ClipSpec clip = {(int)mode, stability, C_out, sub_R.data(), 0.f, nullptr};
       dp_status st = norms_impl(sub.data(), n, dt, B, sqnorm_out, ws, ws_bytes, s, row.data(),
-                                any_kept ? sub_kept.data() : nullptr);
-      if (st != DP_OK) return st;
-      std::vector<int32_t> begin(l1 - l0 + 1);
-      for (int l = l0; l <= l1; ++l) begin[l - l0] = l;
-      st = launch_clip_factors_grouped(sqnorm_out, B, begin.data(), l1 - l0, R + l0, (int)mode, stability,
-                                       C_out + (size_t)l0 * B, nullptr, s);
+                                any_kept ? sub_kept.data() : nullptr, &clip);
       if (st != DP_OK) return st;
       NoiseSpec spec;
       spec.grad_offset = sub_off.data();

@@ -69,6 +69,15 @@ struct NoiseArgs {
   uint64_t layer_off[kMaxGroup];
 };
 
+// Layer-wise clipping (one group per layer): the kernel that finishes a squared norm writes the factor too.
+// R[j] is the threshold of the launch's layer j, C_out as large as the whole stack's norms; C_out == nullptr: no factors.
+struct LayerClip {
+  float* C_out;
+  int mode;
+  float stability;
+  float R[kMaxGroup];
+};
+
 // The layer that owns workgroup (or tile) number `id`: the last one whose tile_begin is <= id.
 __device__ __forceinline__ int layer_of(const GroupArgs& ga, int id) {
   int lo = 0, hi = ga.n_layers - 1;
@@ -128,6 +137,11 @@ dp_status launch_philox_blocks(uint32_t* out, uint64_t first_block, uint64_t n_b
                                uint64_t seed, uint64_t step, hipStream_t s);
 dp_status launch_clip_factors(const float* sqnorm, int L, int B, int mode, float R, float stability,
                               float* C_out, float* norm_out, hipStream_t s);
+// norm_reduce of the launch's layers (launch_norm_reduce_group) and the clip factors of all L rows in one launch, the same
+// bits; norm_clip_supports: L is not beyond its LDS.
+bool norm_clip_supports(int L);
+dp_status launch_norm_clip(const GroupArgs& ga, const float* partials, float* sqnorm, int L, int mode, float R,
+                           float stability, float* C_out, float* norm_out, hipStream_t s);
 dp_status launch_clip_factors_grouped(const float* sqnorm, int B, const int32_t* group_begin, int M,
                                       const float* R, int mode, float stability, float* C_out,
                                       float* norm_out, hipStream_t s);
@@ -140,7 +154,7 @@ dp_status launch_clipped_bias_grad(const float* colsum, int B, int p, const floa
 // workgroup per (layer, sample).  Gradients: tile_begin = first workgroup (clipped_grad_f32_tiles per layer),
 // c_off; na.stddev == 0: no noise.
 int64_t clipped_grad_f32_tiles(int d, int p);
-dp_status launch_norms_f32_group(const GroupArgs& ga, float* sqnorm, hipStream_t s);
+dp_status launch_norms_f32_group(const GroupArgs& ga, float* sqnorm, const LayerClip& lc, hipStream_t s);
 dp_status launch_clipped_grad_f32_group(const GroupArgs& ga, const float* C, const NoiseArgs& na, hipStream_t s);
 
 // Tiles of tn_pipeline.h.  A launch runs in rounds of the tiles that are resident at a time: 256 large ones
@@ -164,7 +178,7 @@ dp_status launch_perex_dma_group(const GroupArgs& ga, float* partials, bool big,
 bool perex_narrow_supports(int T, int d, int p);
 dp_status launch_perex_narrow_group(const GroupArgs& ga, float* partials, hipStream_t s);
 dp_status launch_norm_reduce_group(const GroupArgs& ga, const float* partials, float* sqnorm_out,
-                                   hipStream_t s);
+                                   const LayerClip& lc, hipStream_t s);
 dp_status launch_clipped_grad_group(const GroupArgs& ga, const float* C, hipStream_t s);
 // 256x128-tile ghost-norm kernel with direct global->LDS loads (ghost_big.hip).
 int ghost_big_tiles_per_sample(int T);
@@ -173,12 +187,12 @@ dp_status launch_ghost_big_group(const GroupArgs& ga, float* partials, hipStream
 // Whole-sample ghost-norm kernel for 129 .. 256 tokens (ghost_sample.hip): one workgroup per sample, final
 // squared norms.
 bool ghost_sample_supports(int T, int d, int p);
-dp_status launch_ghost_sample_group(const GroupArgs& ga, float* sqnorm, hipStream_t s);
+dp_status launch_ghost_sample_group(const GroupArgs& ga, float* sqnorm, const LayerClip& lc, hipStream_t s);
 // Samples of up to 32 tokens, several to a workgroup, final squared norms (ghost_brief.hip):
 // ga.layer[j].tile_begin = first workgroup (ghost_brief_blocks per layer).
 bool ghost_brief_supports(int T);
 int ghost_brief_blocks(int B, int T);
-dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, hipStream_t s);
+dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, const LayerClip& lc, hipStream_t s);
 // 256x256-tile kernel with direct global->LDS loads (grad_gemm.hip).
 int clipped_grad_big_tiles(int d, int p);
 int64_t clipped_grad_mid_tiles(int d, int p);

@@ -10,6 +10,7 @@
 // 16 bytes are eight consecutive columns of one row), so nothing is staged; the eight waves take every eighth
 // 16-column step and add their parts in LDS in a fixed order.  What bounds it is the read of a and g.
 // The squared norms are final: no per-tile partial sums, no launch that adds them.
+#include "clip.h"
 #include "dp_internal.h"
 
 namespace dpbk {
@@ -43,7 +44,7 @@ __device__ __forceinline__ f32x16 gram_part(const uint16_t* x, int width, bool v
 
 template <bool F16>
 __global__ void __launch_bounds__(kThreads)
-ghost_brief_kernel(const GroupArgs ga, float* __restrict__ sqnorm, int first) {
+ghost_brief_kernel(const GroupArgs ga, float* __restrict__ sqnorm, const LayerClip lc, int first) {
   __shared__ float part_a[kWaves][16][64], part_g[kWaves][16][64];       // 64 KiB: two workgroups per compute unit
   const int block = first + blockIdx.x;
   const int l = layer_of(ga, block);
@@ -93,7 +94,7 @@ ghost_brief_kernel(const GroupArgs ga, float* __restrict__ sqnorm, int first) {
   if (tid < n) {
     float s = 0.f;
     for (int t = 0; t < T; ++t) s += rows[tid * T + t];
-    sqnorm[(size_t)ly.sq_index * ga.B + i0 + tid] = s;
+    store_norm(ga, lc, l, i0 + tid, s, sqnorm);
   }
 }
 
@@ -107,12 +108,12 @@ int ghost_brief_blocks(int B, int T) {
   return (B + per - 1) / per;
 }
 
-dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, hipStream_t s) {
+dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, const LayerClip& lc, hipStream_t s) {
   return launch_in_runs(ga.total_blocks, [&](dim3 grid, int first) {
     if (ga.f16)
-      hipLaunchKernelGGL(ghost_brief_kernel<true>, grid, dim3(kThreads), 0, s, ga, sqnorm, first);
+      hipLaunchKernelGGL(ghost_brief_kernel<true>, grid, dim3(kThreads), 0, s, ga, sqnorm, lc, first);
     else
-      hipLaunchKernelGGL(ghost_brief_kernel<false>, grid, dim3(kThreads), 0, s, ga, sqnorm, first);
+      hipLaunchKernelGGL(ghost_brief_kernel<false>, grid, dim3(kThreads), 0, s, ga, sqnorm, lc, first);
   });
 }
 

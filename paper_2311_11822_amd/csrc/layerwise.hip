@@ -12,20 +12,13 @@
 // accumulators to a second set.  The chunk's weighted sum goes to a workspace; a second small
 // kernel adds the chunks in order, adds the noise of eq. (1) and writes the gradient.  No
 // atomics: the result is deterministic.
+#include "clip.h"
 #include "dp_internal.h"
 #include "tn_tile.h"
 
 namespace dpbk {
 
 namespace {
-
-// As in clip.hip: NaN norm -> NaN factor; automatic clipping with norm + stability == 0 -> 0.
-__device__ __forceinline__ float clip_factor_of(float norm, int mode, float R, float stability) {
-  if (norm != norm) return norm;
-  if (mode == DP_CLIP_STANDARD) return fminf(R / norm, 1.f);
-  const float den = norm + stability;
-  return den > 0.f ? R / den : 0.f;
-}
 
 struct FusedArgs {
   int mode;
@@ -91,8 +84,7 @@ layerwise_fused_kernel(const GroupArgs ga, const FusedArgs fa, float* __restrict
 #pragma unroll
     for (int w = 0; w < NW; ++w) sq += red[w];     // same order in every thread
     __syncthreads();                               // red is overwritten by the next sample's tiles
-    const float norm = sq != sq ? sq : __builtin_sqrtf(fmaxf(sq, 0.f));
-    const float c = clip_factor_of(norm, fa.mode, fa.R[l], fa.stability);
+    const float c = clip_factor(norm_of(sq), fa.mode, fa.R[l], fa.stability);
     if (threadIdx.x == 0) {
       sqnorm[(size_t)ly.sq_index * ga.B + i] = sq;
       C_out[(size_t)ly.sq_index * ga.B + i] = c;

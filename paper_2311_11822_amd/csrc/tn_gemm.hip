@@ -13,7 +13,9 @@
 // The gradient keeps one accumulator set re-expressed at sample boundaries (tn_tile.h): the
 // register file cannot hold two at these tile sizes, and the re-expression adds only B fp32
 // roundings per output.
+#include "clip.h"
 #include "dp_internal.h"
+#include "norm_partials.h"
 #include "tile_order.h"
 #include "tn_tile.h"
 
@@ -121,24 +123,12 @@ perex_norm_kernel(const GroupArgs ga, float* __restrict__ partials) {
 
 // sqnorm[l, i] = sum of the layer's per-tile partials of sample i, in tile order.
 __global__ void __launch_bounds__(64)
-norm_reduce_kernel(const GroupArgs ga, const float* __restrict__ partials, float* __restrict__ sqnorm) {
+norm_reduce_kernel(const GroupArgs ga, const float* __restrict__ partials, float* __restrict__ sqnorm,
+                   const LayerClip lc) {
   const int l = blockIdx.x / ga.B, i = blockIdx.x % ga.B;
   const GroupLayer& ly = ga.layer[l];
-  const float* src = partials + ly.part_begin + (size_t)i * ly.tiles_per_sample;
-  // 64 lanes each add a strided subset in order, then a fixed butterfly: deterministic.  Four loads at a time: one
-  // after the other, 1012 sums took 1.7 us longer.
-  float s = 0.f;
-  const int n = ly.tiles_per_sample;
-  for (unsigned q0 = threadIdx.x; q0 < (unsigned)n; q0 += 256) {
-    float v[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = q0 + 64 * j < (unsigned)n ? src[q0 + 64 * j] : 0.f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) s += v[j];
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-  if (threadIdx.x == 0) sqnorm[(size_t)ly.sq_index * ga.B + i] = s;
+  const float sum = partial_sum(ly, i, partials, threadIdx.x, 64);
+  if (threadIdx.x == 0) store_norm(ga, lc, l, i, sum, sqnorm);
 }
 
 // Tile shapes.  Gradient: 256x256 output tile, 8 waves of 128x64, k-step 32.
@@ -190,9 +180,9 @@ dp_status launch_perex_group(const GroupArgs& ga, float* partials, hipStream_t s
 }
 
 dp_status launch_norm_reduce_group(const GroupArgs& ga, const float* partials, float* sqnorm_out,
-                                   hipStream_t s) {
+                                   const LayerClip& lc, hipStream_t s) {
   hipLaunchKernelGGL(norm_reduce_kernel, dim3(ga.n_layers * ga.B), dim3(64), 0, s, ga, partials,
-                     sqnorm_out);
+                     sqnorm_out, lc);
   return hip_status(hipGetLastError());
 }
 

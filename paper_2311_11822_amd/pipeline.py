@@ -122,10 +122,12 @@ class BkPipeline:
                                      self.sqnorm, self.C_groups, self.ws_layerwise, layers_per_pass, stream)
 
     def step(self, mode, R, sigma, stability, seed, step, offset, count, stream=None, fused=True):
+        if fused:                      # norms, clip and grad_noise in one call of the library
+            dp.dp_private_step_multi(self.desc, self.dt, self.B, mode, R, stability,
+                                     self.kept_ptrs if self.any_kept else None, self.grad_ptrs, self.grad_offsets, 0,
+                                     offset, count, sigma, seed, step, self.sqnorm, self.C, self.norm, self.ws, stream)
+            return
         self.norms(stream)
         self.clip(mode, R, stability, stream)
-        if fused:
-            self.grad_noise(sigma, R, seed, step, offset, count, 0, stream)
-        else:
-            self.grad(0, stream)
-            self.noise(sigma, R, seed, step, offset, count, stream)
+        self.grad(0, stream)
+        self.noise(sigma, R, seed, step, offset, count, stream)

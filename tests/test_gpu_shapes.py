@@ -321,3 +321,46 @@ def test_bias_norm_forms(dtype, B, T, p):
     g64 = si.to_f64(g)
     assert frob(host(colsum), o.bias_per_sample_grad(g64)) <= TOL
     np.testing.assert_allclose(host(sq), o.bias_sqnorm(g64), rtol=TOL)
+
+
+# One call for a step against its three stages, and factors written by the kernels that finish the norms against the
+# clip kernels: the same bits.  Stacks whose norms end in every kernel (partial sums of one launch, of several and of two
+# kernels, final norms alone), more layers than a launch or a wave's lanes hold, a NaN and a zero sample.
+STEP_STACKS = [
+    (si.F32, 3, 9, [(16, 24)] * 3, None),
+    (si.BF16, 5, 21, [(64, 72), (128, 136)], None),
+    (si.F16, 4, 140, [(136, 264), (264, 72)], [0, 1]),
+    (si.BF16, 3, 300, [(72, 136), (136, 200), (16, 200), (136, 136)], [0, 1, 1, 0]),
+    (si.BF16, 2, 40, [(64 + 8 * (l % 3), 72) for l in range(103)], [l % 2 for l in range(103)]),
+]
+
+
+@pytest.mark.parametrize("dtype,B,T,dims,paths", STEP_STACKS)
+@pytest.mark.parametrize("mode", [o.CLIP_STANDARD, o.CLIP_AUTOMATIC])
+def test_step_in_one_call(dtype, B, T, dims, paths, mode):
+    from paper_2311_11822_amd.pipeline import BkPipeline
+    w = si.small_workload("step", dtype, B, T, dims, g_std=1.0 if dtype == si.F32 else 1e-2)
+    layers = [si.gen_layer(w, l) for l in range(w.L)]
+    layers = [(dev(a), dev(g)) for a, g in layers]
+    for a, g in layers:
+        g[0] = 0
+    layers[0][0][B - 1, 0, 0] = float("nan") if layers[0][0].dtype != torch.int16 else 0x7FC0
+    pipe = BkPipeline(layers, paths)
+    outputs = [pipe.sqnorm, pipe.C, pipe.norm, pipe.flat]
+    pipe.norms()
+    pipe.clip(mode, 0.5, 0.01)
+    pipe.grad_noise(0.7, 0.5, 3, 1, 4, pipe.psi - 8)
+    want = [x.clone() for x in outputs]
+    for x in outputs:
+        x.fill_(123.0)
+    pipe.step(mode, 0.5, 0.7, 0.01, 3, 1, 4, pipe.psi - 8)
+    for got, x in zip(outputs, want):
+        assert torch.equal(got.view(torch.int32), x.view(torch.int32))
+    # layer-wise
+    R = [0.1 + 0.01 * l for l in range(w.L)]
+    pipe.set_groups(list(range(w.L)), R)
+    pipe.layerwise_step(mode, 0.01, 0.0, 3, 1, 0, 0)
+    C = pipe.C_groups.clone()
+    pipe.C_groups.fill_(123.0)
+    pipe.clip_grouped(mode, 0.01)
+    assert torch.equal(C.view(torch.int32), pipe.C_groups.view(torch.int32))
