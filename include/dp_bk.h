@@ -310,12 +310,14 @@ dp_status dp_clipped_grad_kept_multi(const dp_layer* layers, int L, dp_dtype dt,
  * One step of all-layer clipping with one call: dp_norms_multi_keep (kept == NULL: dp_norms_multi), dp_clip_factors and
  * dp_clipped_grad_kept_multi (kept == NULL: dp_clipped_grad_noise_multi) on the same arguments, with the same results,
  * fewer launches and one validation of each argument.  norm_out may be NULL.
+ *   counter  device, 4 bytes that are zero when the call's work begins and are left zero (one such cell may serve any
+ *            calls whose work does not overlap on the GPU, as sqnorm_out and ws may); or NULL, which costs small stacks a launch
  */
 dp_status dp_private_step_multi(const dp_layer* layers, int L, dp_dtype dt, int B, dp_clip_mode mode, float R,
                                 float stability, float* const* kept, float* const* grads, const uint64_t* grad_offset,
                                 int accumulate, uint64_t shard_offset, uint64_t shard_count, float sigma, uint64_t seed,
                                 uint64_t step, float* sqnorm_out, float* C_out, float* norm_out, void* ws,
-                                size_t ws_bytes, void* stream);
+                                size_t ws_bytes, void* counter, void* stream);
 
 /*
  * Layer-wise clipping without book-keeping (section 3.3 (II), and the per-layer formula of the

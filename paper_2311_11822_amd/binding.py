@@ -58,7 +58,7 @@ _PROTOS = {
     "dp_clipped_grad_kept_multi": (_i, [C.POINTER(dp_layer), _i, _i, _i, _vp, C.POINTER(_vp), C.POINTER(_vp),
                                        C.POINTER(_u64), _i, _u64, _u64, _f, _f, _u64, _u64, _vp]),
     "dp_private_step_multi": (_i, [C.POINTER(dp_layer), _i, _i, _i, _i, _f, _f, C.POINTER(_vp), C.POINTER(_vp),
-                                  C.POINTER(_u64), _i, _u64, _u64, _f, _u64, _u64, _vp, _vp, _vp, _vp, _sz, _vp]),
+                                  C.POINTER(_u64), _i, _u64, _u64, _f, _u64, _u64, _vp, _vp, _vp, _vp, _sz, _vp, _vp]),
     "dp_layerwise_workspace_bytes": (_sz, [C.POINTER(dp_layer), _i, _i, _i]),
     "dp_layerwise_clipped_grad": (_i, [C.POINTER(dp_layer), _i, _i, _i, C.POINTER(_f), _i, _f, C.POINTER(_vp),
                                       C.POINTER(_u64), _i, _u64, _u64, _f, _u64, _u64, _vp, _vp, _vp, _sz, _i, _vp]),
@@ -266,7 +266,8 @@ def dp_clipped_grad_kept_multi(layers, dt, B, Cf, kept, grads, grad_offset, accu
 
 
 def dp_private_step_multi(layers, dt, B, mode, R, stability, kept, grads, grad_offset, accumulate, shard_offset,
-                          shard_count, sigma, seed, step, sqnorm_out, C_out, norm_out, ws, stream=None) -> None:
+                          shard_count, sigma, seed, step, sqnorm_out, C_out, norm_out, ws, counter=None,
+                          stream=None) -> None:
     arr = layers if isinstance(layers, C.Array) else layer_array(layers)
     offs = None
     if grad_offset is not None:
@@ -274,7 +275,8 @@ def dp_private_step_multi(layers, dt, B, mode, R, stability, kept, grads, grad_o
     _check(lib.dp_private_step_multi(arr, len(arr), dt, B, mode, R, stability,
                                      _ptr_array(kept) if kept is not None else None, _ptr_array(grads), offs, accumulate,
                                      shard_offset, shard_count, sigma, seed, step, _ptr(sqnorm_out), _ptr(C_out),
-                                     _ptr(norm_out), _ptr(ws), _nbytes(ws), _stream(stream)), "dp_private_step_multi")
+                                     _ptr(norm_out), _ptr(ws), _nbytes(ws), _ptr(counter), _stream(stream)),
+           "dp_private_step_multi")
 
 
 def dp_layerwise_workspace_bytes(layers, dt, B) -> int:

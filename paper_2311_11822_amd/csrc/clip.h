@@ -22,12 +22,56 @@ __device__ __forceinline__ float clip_factor(float norm, int mode, float R, floa
   return den > 0.f ? R / den : 0.f;
 }
 
+// Sum of rows [l0, l1) of sqnorm at column i, by one wave: each lane adds a strided subset in
+// order, then a fixed butterfly, so the result is deterministic; the rows are loaded in
+// parallel (a serial loop would pay one memory latency per layer).
+__device__ __forceinline__ float column_sum(const float* sqnorm, int B, int i, int l0, int l1, int lane) {
+  float total = 0.f;
+  for (int l = l0 + lane; l < l1; l += 64) total += sqnorm[(size_t)l * B + i];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off);
+  return total;
+}
+
 // Squared norm of sample i of the launch's layer l, and with layer-wise clipping the sample's factor.
-__device__ __forceinline__ void store_norm(const GroupArgs& ga, const LayerClip& lc, int l, int i, float sq,
-                                           float* __restrict__ sqnorm) {
+__device__ __forceinline__ void store_norm(const GroupArgs& ga, const NormClip& nc, int l, int i, float sq, float* sqnorm) {
   const size_t o = (size_t)ga.layer[l].sq_index * ga.B + i;
-  sqnorm[o] = sq;
-  if (lc.C_out) lc.C_out[o] = clip_factor(norm_of(sq), lc.mode, lc.R[l], lc.stability);
+  if (nc.kind == kGroupFactors)
+    __hip_atomic_store(&sqnorm[o], sq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);      // read by another workgroup
+  else
+    sqnorm[o] = sq;
+  if (nc.kind == kLayerFactors) nc.C_out[o] = clip_factor(norm_of(sq), nc.mode, nc.R[l], nc.stability);
+}
+
+// End of every workgroup of a kernel that stores final norms, all of them from its first wave: kGroupFactors.  The norms
+// are stored past the caches that another workgroup does not share and are complete before the count, whose
+// last reader adds them up, nc.width lanes to a sample, in the order of the clip kernel: the same bits.  (With
+// fences in their place, which write back and drop the whole cache, it took 1 to 2 us longer.)  lds: a word of the
+// workgroup's LDS.
+template <int THREADS>
+__device__ __forceinline__ void finish_norms(const GroupArgs& ga, const NormClip& nc, const float* sqnorm, unsigned* lds) {
+  if (nc.kind != kGroupFactors) return;
+  __syncthreads();                                     // nobody reads that word any more
+  if (threadIdx.x < 64) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (threadIdx.x == 0)
+      *lds = __hip_atomic_fetch_add(nc.counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  if (*lds != nc.blocks - 1) return;
+  const int width = nc.width, sub = threadIdx.x & (width - 1);
+  for (int i = threadIdx.x / width; i < ga.B; i += THREADS / width) {
+    float total = 0.f;
+    for (int l = sub; l < nc.L; l += 64)
+      total += __hip_atomic_load(&sqnorm[(size_t)l * ga.B + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int off = width / 2; off > 0; off >>= 1) total += __shfl_xor(total, off);
+    const float norm = norm_of(total);
+    if (sub == 0) {
+      nc.C_out[i] = clip_factor(norm, nc.mode, nc.R[0], nc.stability);
+      if (nc.norm_out) nc.norm_out[i] = norm;
+    }
+  }
+  if (threadIdx.x == 0) *nc.counter = 0;
 }
 
 }  // namespace dpbk

@@ -7,22 +7,11 @@ namespace dpbk {
 
 namespace {
 
-// Sum of rows [l0, l1) of sqnorm at column i, by one wave: each lane adds a strided subset in
-// order, then a fixed butterfly, so the result is deterministic; the rows are loaded in
-// parallel (a serial loop would pay one memory latency per layer).
-__device__ __forceinline__ float column_sum(const float* __restrict__ sqnorm, int B, int i, int l0, int l1) {
-  float total = 0.f;
-  for (int l = l0 + (int)threadIdx.x; l < l1; l += 64) total += sqnorm[(size_t)l * B + i];
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off);
-  return total;
-}
-
 __global__ void __launch_bounds__(64)
 clip_factor_kernel(const float* __restrict__ sqnorm, int L, int B, int mode, float R,
                    float stability, float* __restrict__ C_out, float* __restrict__ norm_out) {
   const int i = blockIdx.x;                                  // one wave per sample
-  const float total = column_sum(sqnorm, B, i, 0, L);
+  const float total = column_sum(sqnorm, B, i, 0, L, threadIdx.x);
   if (threadIdx.x != 0) return;
   const float norm = norm_of(total);
   C_out[i] = clip_factor(norm, mode, R, stability);
@@ -86,7 +75,7 @@ clip_factor_grouped_kernel(const float* __restrict__ sqnorm, int B, int mode, fl
                            float* __restrict__ C_out, float* __restrict__ norm_out,
                            const GroupedClipArgs ga) {
   const int i = blockIdx.x, m = blockIdx.y;                  // one wave per (sample, group)
-  const float total = column_sum(sqnorm, B, i, ga.begin[m], ga.begin[m + 1]);
+  const float total = column_sum(sqnorm, B, i, ga.begin[m], ga.begin[m + 1], threadIdx.x);
   if (threadIdx.x != 0) return;
   const float norm = norm_of(total);
   const float c = clip_factor(norm, mode, ga.R[m], stability);

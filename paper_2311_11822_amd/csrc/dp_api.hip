@@ -71,6 +71,7 @@ struct ClipSpec {
   const float* layer_R;          // layer-wise: thresholds by layer of the call; nullptr: all layers in one group
   float R;                       // one group
   float* norm_out;
+  unsigned* counter;             // one group: device, zero between the calls; or nullptr
 };
 
 // One group: the last launch of partial sums, not added up yet.
@@ -79,25 +80,50 @@ struct PendingReduce {
   bool any = false;
 };
 
-// For the kernels' arguments, R still to be filled in.
-LayerClip layer_clip(const ClipSpec* clip) {
-  LayerClip lc;
-  const bool layer_wise = clip && clip->layer_R;
-  lc.C_out = layer_wise ? clip->C_out : nullptr;
-  lc.mode = layer_wise ? clip->mode : 0;
-  lc.stability = layer_wise ? clip->stability : 0.f;
-  return lc;
+// For the kernels' arguments, layer-wise thresholds still to be filled in.
+NormClip layer_clip(const ClipSpec* clip) {
+  NormClip nc;
+  nc.kind = clip && clip->layer_R ? kLayerFactors : kNoFactors;
+  if (!clip) return nc;
+  nc.mode = clip->mode;
+  nc.stability = clip->stability;
+  nc.C_out = clip->C_out;
+  return nc;
+}
+
+// The last launch of final norms forms the factors of the one group where that is cheaper than a launch (3 us of host
+// time, about 2 on the GPU): one round of workgroups, whose count is a round trip to memory each, and no more norms
+// than the last of them adds up in two rounds.
+int lanes_for(int L) {
+  int width = 1;
+  while (width < 64 && width < L) width *= 2;
+  return width;
+}
+
+bool last_forms_factors(const ClipSpec* clip, int64_t blocks, int L, int B) {
+  return clip && !clip->layer_R && clip->counter && blocks <= 256 && L <= 256 && (int64_t)B * lanes_for(L) <= 1024;
+}
+
+void set_group_factors(NormClip& nc, const ClipSpec& clip, int64_t blocks, int L) {
+  nc.kind = kGroupFactors;
+  nc.norm_out = clip.norm_out;
+  nc.counter = clip.counter;
+  nc.blocks = (unsigned)blocks;
+  nc.L = L;
+  nc.width = lanes_for(L);
+  nc.R[0] = clip.R;
 }
 
 // Launches the norm kernels of one path for the listed layers, in chunks of kMaxGroup.
-// part_begin[l] is the layer's first slot in the partial-sum workspace.
+// part_begin[l] is the layer's first slot in the partial-sum workspace.  last_rows: rows of the whole call if these are
+// its last norm launches (0: not); *formed: the last of them formed the factors.
 enum NormKernel { kGhostBig = 0, kGhostSmall = 1, kPerex = 2, kGhostSample = 3, kGhostBrief = 4, kPerexNarrow = 5 };
 constexpr int kNormKernels = 6;
 
 dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, int n_which,
                         const int64_t* part_begin, dp_dtype dt, int B, float* partials,
                         float* sqnorm_out, hipStream_t s, const int* row_of, float* const* kept,
-                        const ClipSpec* clip, PendingReduce* pending) {
+                        const ClipSpec* clip, PendingReduce* pending, int last_rows, bool* formed) {
   // A tile's length is the contraction it runs over (d_in + d_out for the ghost norm, T for the
   // instantiated one).  Longest first: workgroups are handed out in order, so the short tiles
   // fill the end of the launch.  Each layer writes its own workspace slots and sqnorm row, so
@@ -114,7 +140,7 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
   }
   for (int begin = 0; begin < n_which; begin += kMaxGroup) {
     GroupArgs ga;
-    LayerClip lc = layer_clip(clip);
+    NormClip nc = layer_clip(clip);
     ga.B = B;
     ga.accumulate = 0;
     ga.f16 = dt == DP_F16;
@@ -123,7 +149,7 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
     for (int j = 0; j < ga.n_layers; ++j) {
       const int l = which[begin + j];
       GroupLayer& gl = ga.layer[j];
-      if (lc.C_out) lc.R[j] = clip->layer_R[l];
+      if (nc.kind == kLayerFactors) nc.R[j] = clip->layer_R[l];
       gl.a = layers[l].a;
       gl.g = layers[l].g;
       gl.out = (kernel == kPerex || kernel == kPerexNarrow) && kept ? kept[l] : nullptr;
@@ -140,8 +166,12 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
     }
     ga.total_blocks = (int)blocks;
     if (kernel == kGhostBrief || kernel == kGhostSample) {       // final norms: nothing to add up
-      dp_status st = kernel == kGhostBrief ? launch_ghost_brief_group(ga, sqnorm_out, lc, s)
-                                           : launch_ghost_sample_group(ga, sqnorm_out, lc, s);
+      if (last_rows && begin + kMaxGroup >= n_which && last_forms_factors(clip, blocks, last_rows, B)) {
+        set_group_factors(nc, *clip, blocks, last_rows);
+        *formed = true;
+      }
+      dp_status st = kernel == kGhostBrief ? launch_ghost_brief_group(ga, sqnorm_out, nc, s)
+                                           : launch_ghost_sample_group(ga, sqnorm_out, nc, s);
       if (st != DP_OK) return st;
       continue;
     }
@@ -175,7 +205,7 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
       for (int j = 0; j < ga.n_layers; ++j)
         ga.layer[j].tiles_per_sample = perex_tiles_per_sample(ga.layer[j].d_in, ga.layer[j].d_out);
     if (pending) std::swap(pending->ga, ga);             // the launch before it, if any, is added up now
-    if (!pending || pending->any) st = launch_norm_reduce_group(ga, partials, sqnorm_out, lc, s);
+    if (!pending || pending->any) st = launch_norm_reduce_group(ga, partials, sqnorm_out, nc, s);
     if (st != DP_OK) return st;
     if (pending) pending->any = true;
   }
@@ -231,9 +261,10 @@ dp_status norms_impl(const dp_layer* layers, int L, dp_dtype dt, int B, float* s
       if (work > kF32MaxWork) return DP_ERR_UNSUPPORTED;
     }
     const int per_launch = std::max(1, std::min(kMaxGroup, INT32_MAX / 2 / B));
+    bool formed = false;
     for (int l0 = 0; l0 < L; l0 += per_launch) {
       GroupArgs ga;
-      LayerClip lc = layer_clip(clip);
+      NormClip nc = layer_clip(clip);
       ga.B = B;
       ga.accumulate = 0;
       ga.f16 = 0;
@@ -249,13 +280,17 @@ dp_status norms_impl(const dp_layer* layers, int L, dp_dtype dt, int B, float* s
         gl.d_out = ly.d_out;
         gl.path = ly.path;
         gl.sq_index = row_of ? row_of[l0 + j] : l0 + j;
-        if (lc.C_out) lc.R[j] = clip->layer_R[l0 + j];
+        if (nc.kind == kLayerFactors) nc.R[j] = clip->layer_R[l0 + j];
       }
       ga.total_blocks = ga.n_layers * B;
-      dp_status st = launch_norms_f32_group(ga, sqnorm_out, lc, s);
+      if (l0 + per_launch >= L && last_forms_factors(clip, ga.total_blocks, L, B)) {
+        set_group_factors(nc, *clip, ga.total_blocks, L);
+        formed = true;
+      }
+      dp_status st = launch_norms_f32_group(ga, sqnorm_out, nc, s);
       if (st != DP_OK) return st;
     }
-    return group_clip(clip, nullptr, sqnorm_out, nullptr, L, B, s);
+    return formed ? DP_OK : group_clip(clip, nullptr, sqnorm_out, nullptr, L, B, s);
   }
   if (!ws || ws_bytes < (size_t)slots * sizeof(float)) return DP_ERR_WORKSPACE;
   if (!aligned16(ws)) return DP_ERR_INVALID_ARG;
@@ -277,12 +312,16 @@ dp_status norms_impl(const dp_layer* layers, int L, dp_dtype dt, int B, float* s
   float* partials = static_cast<float*>(ws);
   PendingReduce held;
   PendingReduce* pending = clip && !clip->layer_R && B <= kNormClipSamples && norm_clip_supports(L) ? &held : nullptr;
-  for (int k = 0; k < kNormKernels; ++k) {
+  int last = kNormKernels - 1;
+  while (count[last] == 0) --last;
+  bool formed = false;
+  for (int k = 0; k <= last; ++k) {
+    const bool ends = k == last && !(pending && pending->any);
     dp_status st = run_norm_path((NormKernel)k, layers, list[k], count[k], begin, dt, B, partials, sqnorm_out, s,
-                                 row_of, kept, clip, pending);
+                                 row_of, kept, clip, pending, ends ? L : 0, &formed);
     if (st != DP_OK) return st;
   }
-  return group_clip(clip, pending, sqnorm_out, partials, L, B, s);
+  return formed ? DP_OK : group_clip(clip, pending, sqnorm_out, partials, L, B, s);
 }
 
 dp_status norms_impl(const dp_layer* layers, int L, dp_dtype dt, int B, float* sqnorm_out, void* ws,
@@ -842,13 +881,14 @@ dp_status dp_private_step_multi(const dp_layer* layers, int L, dp_dtype dt, int 
                                 float stability, float* const* kept, float* const* grads, const uint64_t* grad_offset,
                                 int accumulate, uint64_t shard_offset, uint64_t shard_count, float sigma, uint64_t seed,
                                 uint64_t step, float* sqnorm_out, float* C_out, float* norm_out, void* ws,
-                                size_t ws_bytes, void* stream) {
+                                size_t ws_bytes, void* counter, void* stream) {
   if (!layers || L <= 0 || !C_out) return DP_ERR_INVALID_ARG;
+  if (reinterpret_cast<uintptr_t>(counter) & 3u) return DP_ERR_INVALID_ARG;
   if (mode != DP_CLIP_STANDARD && mode != DP_CLIP_AUTOMATIC) return DP_ERR_INVALID_ARG;
   if (!(R > 0.f) || !(stability >= 0.f) || isinf(stability)) return DP_ERR_INVALID_ARG;
   const dp_status kept_ok = check_kept(layers, L, dt, kept);
   if (kept_ok != DP_OK) return kept_ok;
-  const ClipSpec clip = {(int)mode, stability, C_out, nullptr, R, norm_out};
+  const ClipSpec clip = {(int)mode, stability, C_out, nullptr, R, norm_out, static_cast<unsigned*>(counter)};
   const dp_status st = norms_impl(layers, L, dt, B, sqnorm_out, ws, ws_bytes, static_cast<hipStream_t>(stream), nullptr,
                                   kept, &clip);
   if (st != DP_OK) return st;
@@ -1064,7 +1104,7 @@ dp_status dp_layerwise_clipped_grad(const dp_layer* layers, int L, dp_dtype dt, 
       }
     if (!sub.empty()) {
       const int n = (int)sub.size();
-      const ClipSpec clip = {(int)mode, stability, C_out, sub_R.data(), 0.f, nullptr};
+      const ClipSpec clip = {(int)mode, stability, C_out, sub_R.data(), 0.f, nullptr, nullptr};
       dp_status st = norms_impl(sub.data(), n, dt, B, sqnorm_out, ws, ws_bytes, s, row.data(),
                                 any_kept ? sub_kept.data() : nullptr, &clip);
       if (st != DP_OK) return st;

@@ -69,13 +69,22 @@ struct NoiseArgs {
   uint64_t layer_off[kMaxGroup];
 };
 
-// Layer-wise clipping (one group per layer): the kernel that finishes a squared norm writes the factor too.
-// R[j] is the threshold of the launch's layer j, C_out as large as the whole stack's norms; C_out == nullptr: no factors.
-struct LayerClip {
-  float* C_out;
+// What the kernels that finish squared norms make of them.
+//  kLayerFactors: one group per layer: the factor of each norm as it is written (R[j]: threshold of the launch's layer j;
+//    C_out as large as the whole stack's norms).
+//  kGroupFactors: one group of all L rows of the call: the workgroup that ends last (of `blocks`, counted in
+//    *counter, which is zero before and after) adds the rows up and writes C_out[B] and norm_out[B] (or nullptr).
+enum ClipKind { kNoFactors = 0, kLayerFactors = 1, kGroupFactors = 2 };
+struct NormClip {
+  int kind;
   int mode;
   float stability;
-  float R[kMaxGroup];
+  float* C_out;
+  float* norm_out;
+  unsigned* counter;
+  unsigned blocks;
+  int L, width;                 // width: power of two, 64 or no less than L
+  float R[kMaxGroup];           // kGroupFactors: R[0]
 };
 
 // The layer that owns workgroup (or tile) number `id`: the last one whose tile_begin is <= id.
@@ -154,7 +163,7 @@ dp_status launch_clipped_bias_grad(const float* colsum, int B, int p, const floa
 // workgroup per (layer, sample).  Gradients: tile_begin = first workgroup (clipped_grad_f32_tiles per layer),
 // c_off; na.stddev == 0: no noise.
 int64_t clipped_grad_f32_tiles(int d, int p);
-dp_status launch_norms_f32_group(const GroupArgs& ga, float* sqnorm, const LayerClip& lc, hipStream_t s);
+dp_status launch_norms_f32_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s);
 dp_status launch_clipped_grad_f32_group(const GroupArgs& ga, const float* C, const NoiseArgs& na, hipStream_t s);
 
 // Tiles of tn_pipeline.h.  A launch runs in rounds of the tiles that are resident at a time: 256 large ones
@@ -178,7 +187,7 @@ dp_status launch_perex_dma_group(const GroupArgs& ga, float* partials, bool big,
 bool perex_narrow_supports(int T, int d, int p);
 dp_status launch_perex_narrow_group(const GroupArgs& ga, float* partials, hipStream_t s);
 dp_status launch_norm_reduce_group(const GroupArgs& ga, const float* partials, float* sqnorm_out,
-                                   const LayerClip& lc, hipStream_t s);
+                                   const NormClip& nc, hipStream_t s);
 dp_status launch_clipped_grad_group(const GroupArgs& ga, const float* C, hipStream_t s);
 // 256x128-tile ghost-norm kernel with direct global->LDS loads (ghost_big.hip).
 int ghost_big_tiles_per_sample(int T);
@@ -187,12 +196,12 @@ dp_status launch_ghost_big_group(const GroupArgs& ga, float* partials, hipStream
 // Whole-sample ghost-norm kernel for 129 .. 256 tokens (ghost_sample.hip): one workgroup per sample, final
 // squared norms.
 bool ghost_sample_supports(int T, int d, int p);
-dp_status launch_ghost_sample_group(const GroupArgs& ga, float* sqnorm, const LayerClip& lc, hipStream_t s);
+dp_status launch_ghost_sample_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s);
 // Samples of up to 32 tokens, several to a workgroup, final squared norms (ghost_brief.hip):
 // ga.layer[j].tile_begin = first workgroup (ghost_brief_blocks per layer).
 bool ghost_brief_supports(int T);
 int ghost_brief_blocks(int B, int T);
-dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, const LayerClip& lc, hipStream_t s);
+dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s);
 // 256x256-tile kernel with direct global->LDS loads (grad_gemm.hip).
 int clipped_grad_big_tiles(int d, int p);
 int64_t clipped_grad_mid_tiles(int d, int p);

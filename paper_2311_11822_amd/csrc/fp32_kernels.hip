@@ -120,7 +120,7 @@ __device__ __forceinline__ f32x16 mul_item(const TnItem& it, f32x16 acc) {
 // A tile's entries outside the layer (past d, p or T) are selected out before they are added: their
 // zero operands meet the other side's values, and an infinity there would make them NaN.
 __global__ void __launch_bounds__(kThreads)
-norms_f32_kernel(const GroupArgs ga, float* __restrict__ sqnorm, const LayerClip lc, int first) {
+norms_f32_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int first) {
   __shared__ float part_a[kWaves][16][64], part_g[kWaves][16][64];   // 64 KiB
   const unsigned block = first + blockIdx.x;
   const int l = block / ga.B, i = block - l * ga.B;
@@ -206,7 +206,8 @@ norms_f32_kernel(const GroupArgs ga, float* __restrict__ sqnorm, const LayerClip
     }
   }
   const float s = block_sum(sum, &part_g[0][0][0]);
-  if (tid == 0) store_norm(ga, lc, l, i, s, sqnorm);
+  if (tid == 0) store_norm(ga, nc, l, i, s, sqnorm);
+  finish_norms<kThreads>(ga, nc, sqnorm, reinterpret_cast<unsigned*>(&part_a[0][0][0]));
 }
 
 // Clip-weighted gradient (section 3): grad[j,k] = sum_i C_i sum_t a[i,t,j] g[i,t,k] (+ noise, eq. (1)).
@@ -314,9 +315,9 @@ int64_t clipped_grad_f32_tiles(int d, int p) {
   return (((int64_t)d + kTile - 1) / kTile) * (((int64_t)p + kTile - 1) / kTile);
 }
 
-dp_status launch_norms_f32_group(const GroupArgs& ga, float* sqnorm, const LayerClip& lc, hipStream_t s) {
+dp_status launch_norms_f32_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s) {
   return launch_in_runs(ga.total_blocks, [&](dim3 grid, int first) {
-    hipLaunchKernelGGL(norms_f32_kernel, grid, dim3(kThreads), 0, s, ga, sqnorm, lc, first);
+    hipLaunchKernelGGL(norms_f32_kernel, grid, dim3(kThreads), 0, s, ga, sqnorm, nc, first);
   });
 }
 

@@ -44,7 +44,7 @@ __device__ __forceinline__ f32x16 gram_part(const uint16_t* x, int width, bool v
 
 template <bool F16>
 __global__ void __launch_bounds__(kThreads)
-ghost_brief_kernel(const GroupArgs ga, float* __restrict__ sqnorm, const LayerClip lc, int first) {
+ghost_brief_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int first) {
   __shared__ float part_a[kWaves][16][64], part_g[kWaves][16][64];       // 64 KiB: two workgroups per compute unit
   const int block = first + blockIdx.x;
   const int l = layer_of(ga, block);
@@ -94,8 +94,9 @@ ghost_brief_kernel(const GroupArgs ga, float* __restrict__ sqnorm, const LayerCl
   if (tid < n) {
     float s = 0.f;
     for (int t = 0; t < T; ++t) s += rows[tid * T + t];
-    store_norm(ga, lc, l, i0 + tid, s, sqnorm);
+    store_norm(ga, nc, l, i0 + tid, s, sqnorm);
   }
+  finish_norms<kThreads>(ga, nc, sqnorm, reinterpret_cast<unsigned*>(rows));
 }
 
 }  // namespace
@@ -108,12 +109,12 @@ int ghost_brief_blocks(int B, int T) {
   return (B + per - 1) / per;
 }
 
-dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, const LayerClip& lc, hipStream_t s) {
+dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s) {
   return launch_in_runs(ga.total_blocks, [&](dim3 grid, int first) {
     if (ga.f16)
-      hipLaunchKernelGGL(ghost_brief_kernel<true>, grid, dim3(kThreads), 0, s, ga, sqnorm, lc, first);
+      hipLaunchKernelGGL(ghost_brief_kernel<true>, grid, dim3(kThreads), 0, s, ga, sqnorm, nc, first);
     else
-      hipLaunchKernelGGL(ghost_brief_kernel<false>, grid, dim3(kThreads), 0, s, ga, sqnorm, lc, first);
+      hipLaunchKernelGGL(ghost_brief_kernel<false>, grid, dim3(kThreads), 0, s, ga, sqnorm, nc, first);
   });
 }
 

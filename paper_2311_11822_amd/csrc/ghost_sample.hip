@@ -40,7 +40,7 @@ __device__ __forceinline__ bf16x8 lds_read16(unsigned addr) {
 // Writes the squared norms themselves: a sample is one workgroup's.  RAGGED: some width is no multiple of the k-block.
 template <bool F16, bool RAGGED>
 __global__ void __launch_bounds__(NT)
-ghost_sample_kernel(const GroupArgs ga, float* __restrict__ sqnorm, const LayerClip lc) {
+ghost_sample_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
   const unsigned lds0 = (unsigned)(uintptr_t)lds_raw;
   const int l = layer_of(ga, blockIdx.x);
@@ -238,16 +238,17 @@ ghost_sample_kernel(const GroupArgs ga, float* __restrict__ sqnorm, const LayerC
   if (lane == 0) red[wave] = s;
   __syncthreads();
   if (tid == 0)
-    store_norm(ga, lc, l, sample, ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7])), sqnorm);
+    store_norm(ga, nc, l, sample, ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7])), sqnorm);
+  finish_norms<NT>(ga, nc, sqnorm, reinterpret_cast<unsigned*>(lds_raw));
 }
 
 template <bool F16, bool RAGGED>
-dp_status launch_t(const GroupArgs& ga, float* sqnorm, const LayerClip& lc, hipStream_t s) {
+dp_status launch_t(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s) {
   static ReadyTable ready;
   auto kernel = ghost_sample_kernel<F16, RAGGED>;
   dp_status st = allow_big_lds(kernel, LDS_BYTES, ready);
   if (st != DP_OK) return st;
-  hipLaunchKernelGGL(kernel, dim3(ga.total_blocks), dim3(NT), LDS_BYTES, s, ga, sqnorm, lc);
+  hipLaunchKernelGGL(kernel, dim3(ga.total_blocks), dim3(NT), LDS_BYTES, s, ga, sqnorm, nc);
   return hip_status(hipGetLastError());
 }
 
@@ -260,11 +261,11 @@ bool ghost_sample_supports(int T, int d, int p) {
 }
 
 // ga.layer[j]: tile_begin = first workgroup, tiles_per_sample = 1.
-dp_status launch_ghost_sample_group(const GroupArgs& ga, float* sqnorm, const LayerClip& lc, hipStream_t s) {
+dp_status launch_ghost_sample_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s) {
   bool ragged = false;
   for (int l = 0; l < ga.n_layers; ++l) ragged = ragged || ga.layer[l].d_in % BK || ga.layer[l].d_out % BK;
-  if (ga.f16) return ragged ? launch_t<true, true>(ga, sqnorm, lc, s) : launch_t<true, false>(ga, sqnorm, lc, s);
-  return ragged ? launch_t<false, true>(ga, sqnorm, lc, s) : launch_t<false, false>(ga, sqnorm, lc, s);
+  if (ga.f16) return ragged ? launch_t<true, true>(ga, sqnorm, nc, s) : launch_t<true, false>(ga, sqnorm, nc, s);
+  return ragged ? launch_t<false, true>(ga, sqnorm, nc, s) : launch_t<false, false>(ga, sqnorm, nc, s);
 }
 
 }  // namespace dpbk

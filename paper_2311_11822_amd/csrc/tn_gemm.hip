@@ -124,11 +124,11 @@ perex_norm_kernel(const GroupArgs ga, float* __restrict__ partials) {
 // sqnorm[l, i] = sum of the layer's per-tile partials of sample i, in tile order.
 __global__ void __launch_bounds__(64)
 norm_reduce_kernel(const GroupArgs ga, const float* __restrict__ partials, float* __restrict__ sqnorm,
-                   const LayerClip lc) {
+                   const NormClip nc) {
   const int l = blockIdx.x / ga.B, i = blockIdx.x % ga.B;
   const GroupLayer& ly = ga.layer[l];
   const float sum = partial_sum(ly, i, partials, threadIdx.x, 64);
-  if (threadIdx.x == 0) store_norm(ga, lc, l, i, sum, sqnorm);
+  if (threadIdx.x == 0) store_norm(ga, nc, l, i, sum, sqnorm);
 }
 
 // Tile shapes.  Gradient: 256x256 output tile, 8 waves of 128x64, k-step 32.
@@ -180,9 +180,9 @@ dp_status launch_perex_group(const GroupArgs& ga, float* partials, hipStream_t s
 }
 
 dp_status launch_norm_reduce_group(const GroupArgs& ga, const float* partials, float* sqnorm_out,
-                                   const LayerClip& lc, hipStream_t s) {
+                                   const NormClip& nc, hipStream_t s) {
   hipLaunchKernelGGL(norm_reduce_kernel, dim3(ga.n_layers * ga.B), dim3(64), 0, s, ga, partials,
-                     sqnorm_out, lc);
+                     sqnorm_out, nc);
   return hip_status(hipGetLastError());
 }
 

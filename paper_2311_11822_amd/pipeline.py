@@ -47,6 +47,7 @@ class BkPipeline:
         if ws_bytes == 0:
             raise dp.DpError(dp.DP_ERR_INVALID_ARG, "dp_norms_multi_workspace_bytes")
         self.ws = torch.empty(ws_bytes, dtype=torch.uint8, device=self.device)
+        self.counter = torch.zeros(1, dtype=torch.int32, device=self.device)      # zero between steps
         # Layers on the instantiated path keep their per-sample gradients [B, d, p] between the norm
         # pass and the gradient pass (smaller than the layer's Gram matrices by the path rule).
         self.kept = [None] * L
@@ -125,7 +126,8 @@ class BkPipeline:
         if fused:                      # norms, clip and grad_noise in one call of the library
             dp.dp_private_step_multi(self.desc, self.dt, self.B, mode, R, stability,
                                      self.kept_ptrs if self.any_kept else None, self.grad_ptrs, self.grad_offsets, 0,
-                                     offset, count, sigma, seed, step, self.sqnorm, self.C, self.norm, self.ws, stream)
+                                     offset, count, sigma, seed, step, self.sqnorm, self.C, self.norm, self.ws, self.counter,
+                                     stream)
             return
         self.norms(stream)
         self.clip(mode, R, stability, stream)

@@ -351,11 +351,26 @@ def test_step_in_one_call(dtype, B, T, dims, paths, mode):
     pipe.clip(mode, 0.5, 0.01)
     pipe.grad_noise(0.7, 0.5, 3, 1, 4, pipe.psi - 8)
     want = [x.clone() for x in outputs]
+    step = lambda: pipe.step(mode, 0.5, 0.7, 0.01, 3, 1, 4, pipe.psi - 8)
+
+    def check():
+        for got, x in zip(outputs, want):
+            assert torch.equal(got.view(torch.int32), x.view(torch.int32))
+            got.fill_(123.0)
+        assert pipe.counter.item() == 0
     for x in outputs:
         x.fill_(123.0)
-    pipe.step(mode, 0.5, 0.7, 0.01, 3, 1, 4, pipe.psi - 8)
-    for got, x in zip(outputs, want):
-        assert torch.equal(got.view(torch.int32), x.view(torch.int32))
+    for _ in range(2):                                # the count of finished workgroups is back at zero
+        step()
+        check()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for _ in range(3):
+        graph.replay()
+        check()
+        step()                                        # eager work between the replays
+        check()
     # layer-wise
     R = [0.1 + 0.01 * l for l in range(w.L)]
     pipe.set_groups(list(range(w.L)), R)
