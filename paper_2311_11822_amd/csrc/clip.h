@@ -60,15 +60,32 @@ __device__ __forceinline__ void finish_norms(const GroupArgs& ga, const NormClip
   __syncthreads();
   if (*lds != nc.blocks - 1) return;
   const int width = nc.width, sub = threadIdx.x & (width - 1);
-  for (int i = threadIdx.x / width; i < ga.B; i += THREADS / width) {
-    float total = 0.f;
-    for (int l = sub; l < nc.L; l += 64)
-      total += __hip_atomic_load(&sqnorm[(size_t)l * ga.B + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (int off = width / 2; off > 0; off >>= 1) total += __shfl_xor(total, off);
-    const float norm = norm_of(total);
-    if (sub == 0) {
-      nc.C_out[i] = clip_factor(norm, nc.mode, nc.R[0], nc.stability);
-      if (nc.norm_out) nc.norm_out[i] = norm;
+  constexpr int AT_A_TIME = 8;                         // samples whose norms a lane has in flight
+  const int stride = THREADS / width;
+  for (int i0 = threadIdx.x / width; i0 < ga.B; i0 += AT_A_TIME * stride) {
+    float total[AT_A_TIME];
+#pragma unroll
+    for (int q = 0; q < AT_A_TIME; ++q) total[q] = 0.f;
+    for (int l = sub; l < nc.L; l += 64) {
+      float v[AT_A_TIME];
+#pragma unroll
+      for (int q = 0; q < AT_A_TIME; ++q) {
+        const int i = i0 + q * stride;
+        v[q] = i < ga.B ? __hip_atomic_load(&sqnorm[(size_t)l * ga.B + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
+      }
+#pragma unroll
+      for (int q = 0; q < AT_A_TIME; ++q) total[q] += v[q];
+    }
+#pragma unroll
+    for (int q = 0; q < AT_A_TIME; ++q) {
+      const int i = i0 + q * stride;
+      if (i >= ga.B) break;                            // of all the sample's lanes
+      for (int off = width / 2; off > 0; off >>= 1) total[q] += __shfl_xor(total[q], off);
+      const float norm = norm_of(total[q]);
+      if (sub == 0) {
+        nc.C_out[i] = clip_factor(norm, nc.mode, nc.R[0], nc.stability);
+        if (nc.norm_out) nc.norm_out[i] = norm;
+      }
     }
   }
   if (threadIdx.x == 0) *nc.counter = 0;

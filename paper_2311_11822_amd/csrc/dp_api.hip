@@ -93,7 +93,7 @@ NormClip layer_clip(const ClipSpec* clip) {
 
 // The last launch of final norms forms the factors of the one group where that is cheaper than a launch (3 us of host
 // time, about 2 on the GPU): one round of workgroups, whose count is a round trip to memory each, and no more norms
-// than the last of them adds up in two rounds.
+// than the last of them reads at one time.
 int lanes_for(int L) {
   int width = 1;
   while (width < 64 && width < L) width *= 2;
@@ -101,7 +101,7 @@ int lanes_for(int L) {
 }
 
 bool last_forms_factors(const ClipSpec* clip, int64_t blocks, int L, int B) {
-  return clip && !clip->layer_R && clip->counter && blocks <= 256 && L <= 256 && (int64_t)B * lanes_for(L) <= 1024;
+  return clip && !clip->layer_R && clip->counter && blocks <= 256 && L <= 256 && (int64_t)B * lanes_for(L) <= 4096;
 }
 
 void set_group_factors(NormClip& nc, const ClipSpec& clip, int64_t blocks, int L) {
@@ -112,6 +112,33 @@ void set_group_factors(NormClip& nc, const ClipSpec& clip, int64_t blocks, int L
   nc.L = L;
   nc.width = lanes_for(L);
   nc.R[0] = clip.R;
+}
+
+// Workgroups to 32 rows in the brief kernel: one, or two, four ... while all of them have a compute unit of their own.
+// (Two of a compute unit measured the same: 256 and 512 workgroups of one-token samples 107.8 and 107.6 us a step.)
+// Returns the workgroups of the launch.
+constexpr int kBriefBlocks = 256;
+int64_t share_brief_samples(GroupArgs& ga) {
+  int64_t blocks = 0;
+  for (int parts = 1;; parts *= 2) {
+    int64_t n = 0;
+    bool more = false;
+    for (int j = 0; j < ga.n_layers; ++j) {
+      const int most = ghost_brief_max_parts(ga.layer[j].T);
+      more = more || parts < most;
+      n += ghost_brief_blocks(ga.B, ga.layer[j].T, std::min(parts, most));
+    }
+    if (parts > 1 && n > kBriefBlocks) return blocks;
+    blocks = n;
+    n = 0;
+    for (int j = 0; j < ga.n_layers; ++j) {
+      GroupLayer& gl = ga.layer[j];
+      gl.tiles_per_sample = std::min(parts, ghost_brief_max_parts(gl.T));
+      gl.tile_begin = (int)n;
+      n += ghost_brief_blocks(ga.B, gl.T, gl.tiles_per_sample);
+    }
+    if (!more) return blocks;
+  }
 }
 
 // Launches the norm kernels of one path for the listed layers, in chunks of kMaxGroup.
@@ -162,8 +189,9 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
       gl.part_begin = (int)part_begin[l];
       gl.tiles_per_sample = tiles_per_sample(gl.path, layers[l]);
       gl.c_off = 0;
-      blocks += kernel == kGhostBrief ? ghost_brief_blocks(B, gl.T) : (int64_t)gl.tiles_per_sample * B;
+      blocks += (int64_t)gl.tiles_per_sample * B;
     }
+    if (kernel == kGhostBrief) blocks = share_brief_samples(ga);
     ga.total_blocks = (int)blocks;
     if (kernel == kGhostBrief || kernel == kGhostSample) {       // final norms: nothing to add up
       if (last_rows && begin + kMaxGroup >= n_which && last_forms_factors(clip, blocks, last_rows, B)) {

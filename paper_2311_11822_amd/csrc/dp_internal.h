@@ -198,9 +198,10 @@ dp_status launch_ghost_big_group(const GroupArgs& ga, float* partials, hipStream
 bool ghost_sample_supports(int T, int d, int p);
 dp_status launch_ghost_sample_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s);
 // Samples of up to 32 tokens, several to a workgroup, final squared norms (ghost_brief.hip):
-// ga.layer[j].tile_begin = first workgroup (ghost_brief_blocks per layer).
+// ga.layer[j].tiles_per_sample = workgroups to 32 rows, up to ghost_brief_max_parts, tile_begin = first workgroup.
 bool ghost_brief_supports(int T);
-int ghost_brief_blocks(int B, int T);
+int64_t ghost_brief_blocks(int B, int T, int parts);
+int ghost_brief_max_parts(int T);
 dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s);
 // 256x256-tile kernel with direct global->LDS loads (grad_gemm.hip).
 int clipped_grad_big_tiles(int d, int p);

@@ -162,7 +162,7 @@ def test_half_gradient_of_short_samples(dtype, T):
 @pytest.mark.parametrize("dtype", HALF)
 @pytest.mark.parametrize("B,T,d,p", [
     (1, 1, 8, 8), (33, 1, 24, 1032), (67, 2, 136, 40), (31, 3, 2056, 64), (7, 16, 72, 200), (3, 17, 264, 88),
-    (2, 32, 1160, 8), (5, 31, 16, 4104),
+    (2, 32, 1160, 8), (5, 31, 16, 4104), (45, 3, 40, 24), (2600, 3, 16, 8),
 ])
 def test_ghost_norm_of_short_samples(dtype, B, T, d, p):
     from paper_2311_11822_amd import binding as dp
@@ -329,6 +329,7 @@ def test_bias_norm_forms(dtype, B, T, p):
 STEP_STACKS = [
     (si.F32, 3, 9, [(16, 24)] * 3, None),
     (si.BF16, 5, 21, [(64, 72), (128, 136)], None),
+    (si.F16, 77, 5, [(40, 24)] * 9, None),            # 13 and 26 workgroups a layer: two shares, 693 norms added by the last
     (si.F16, 4, 140, [(136, 264), (264, 72)], [0, 1]),
     (si.BF16, 3, 300, [(72, 136), (136, 200), (16, 200), (136, 136)], [0, 1, 1, 0]),
     (si.BF16, 2, 40, [(64 + 8 * (l % 3), 72) for l in range(103)], [l % 2 for l in range(103)]),
