@@ -507,31 +507,65 @@ GradKernel grad_kernel_of(const dp_layer& ly, dp_dtype dt, int B) {
   return clipped_grad_big_supports(ly.T, ly.d_in, ly.d_out) ? kGradBig : kGradEdge;
 }
 
-// out16: grads[l] address 16-bit arrays of the operands' storage type; only the large-tile kernels
-// write those, with the noise in their epilogue, so every layer must qualify for them.
-dp_status clipped_grad_impl(const dp_layer* layers, int L, dp_dtype dt, int B, const float* C,
-                            const int* c_off, float* const* grads, int accumulate, void* stream,
-                            const NoiseSpec* noise = nullptr, bool out16 = false) {
+// What the gradient calls refuse of a layer whose a and g they read.
+dp_status check_grad_layer(const dp_layer& ly, dp_dtype dt, int B, const float* grad) {
+  if (!dims_ok(dt, B, ly.T, ly.d_in, ly.d_out)) return DP_ERR_INVALID_ARG;
+  const dp_status st = check_layer_ptrs(ly.a, ly.g);
+  if (st != DP_OK) return st;
+  if (!grad || !aligned16(grad)) return DP_ERR_INVALID_ARG;
+  const int64_t tiles = dt == DP_F32 ? clipped_grad_f32_tiles(ly.d_in, ly.d_out) : clipped_grad_tiles(ly.d_in, ly.d_out);
+  return tiles > INT32_MAX / 2 ? DP_ERR_INVALID_ARG : DP_OK;              // one layer beyond the grid's range
+}
+
+// Everything that launch_grads' callers refuse (but for the noise: make_noise).  out16: grads[l] address 16-bit arrays of
+// the operands' storage type; only the large-tile kernels write those, with the noise in their epilogue, so every layer
+// must qualify for them.
+dp_status check_grads(const dp_layer* layers, int L, dp_dtype dt, int B, const float* C, float* const* grads,
+                      int accumulate, const NoiseSpec* noise = nullptr, bool out16 = false) {
   if (!dtype_ok(dt)) return DP_ERR_INVALID_ARG;
   if (!layers || !grads || !C || L <= 0 || B <= 0) return DP_ERR_INVALID_ARG;
   if (accumulate != 0 && accumulate != 1) return DP_ERR_INVALID_ARG;
   for (int l = 0; l < L; ++l) {
-    if (!dims_ok(dt, B, layers[l].T, layers[l].d_in, layers[l].d_out)) return DP_ERR_INVALID_ARG;
-    dp_status st = check_layer_ptrs(layers[l].a, layers[l].g);
+    const dp_status st = check_grad_layer(layers[l], dt, B, grads[l]);
     if (st != DP_OK) return st;
-    if (!grads[l] || !aligned16(grads[l])) return DP_ERR_INVALID_ARG;
-    if ((int64_t)clipped_grad_tiles(layers[l].d_in, layers[l].d_out) > INT32_MAX / 2) return DP_ERR_INVALID_ARG;
   }
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  if (out16) {
-    if (dt == DP_F32) return DP_ERR_UNSUPPORTED;
-    for (int l = 0; l < L; ++l) {
-      const dp_layer& ly = layers[l];
-      if (!(ly.T % 32 == 0 && ly.d_in >= 128 && ly.d_out >= 128 && clipped_grad_big_supports(ly.T, ly.d_in, ly.d_out)))
-        return DP_ERR_UNSUPPORTED;
-      if (noise && (noise->grad_offset[l] & 3)) return DP_ERR_UNSUPPORTED;
-    }
+  if (!out16) return DP_OK;
+  if (dt == DP_F32) return DP_ERR_UNSUPPORTED;
+  for (int l = 0; l < L; ++l) {
+    const dp_layer& ly = layers[l];
+    if (!(ly.T % 32 == 0 && ly.d_in >= 128 && ly.d_out >= 128 && clipped_grad_big_supports(ly.T, ly.d_in, ly.d_out)))
+      return DP_ERR_UNSUPPORTED;
+    if (noise && (noise->grad_offset[l] & 3)) return DP_ERR_UNSUPPORTED;
   }
+  return DP_OK;
+}
+
+// Noise arguments as the caller gave them.  *noisy: there is some to add; *spec is filled then.
+dp_status make_noise(const dp_layer* layers, int L, const uint64_t* grad_offset, uint64_t shard_offset,
+                     uint64_t shard_count, float sigma, float R, uint64_t seed, uint64_t step, NoiseSpec* spec, bool* noisy) {
+  if (!(sigma >= 0.f) || isinf(sigma)) return DP_ERR_INVALID_ARG;
+  if (!(R > 0.f)) return DP_ERR_INVALID_ARG;
+  if (shard_offset + shard_count < shard_offset) return DP_ERR_INVALID_ARG;   // wraps 2^64
+  *noisy = sigma > 0.f && shard_count > 0;
+  if (!*noisy) return DP_OK;
+  if (isinf(R) || !grad_offset || !layers || L <= 0) return DP_ERR_INVALID_ARG;
+  for (int l = 0; l < L; ++l) {
+    const uint64_t n = (uint64_t)std::max(layers[l].d_in, 0) * (uint64_t)std::max(layers[l].d_out, 0);
+    if (grad_offset[l] + n < grad_offset[l]) return DP_ERR_INVALID_ARG;
+  }
+  spec->grad_offset = grad_offset;
+  spec->lo = shard_offset;
+  spec->hi = shard_offset + shard_count;
+  spec->stddev = sigma * R;
+  spec->seed = seed;
+  spec->step = step;
+  return DP_OK;
+}
+
+// The gradient kernels of layers that check_grads has passed.
+dp_status launch_grads(const dp_layer* layers, int L, dp_dtype dt, int B, const float* C, const int* c_off,
+                       float* const* grads, int accumulate, hipStream_t s, const NoiseSpec* noise = nullptr,
+                       bool out16 = false) {
   if (dt == DP_F32) {
     NoiseArgs na = {};
     if (noise) set_noise(na, *noise);
@@ -545,10 +579,7 @@ dp_status clipped_grad_impl(const dp_layer* layers, int L, dp_dtype dt, int B, c
       int64_t blocks = 0;
       for (; l < L && ga.n_layers < kMaxGroup; ++l) {
         const int64_t tiles = clipped_grad_f32_tiles(layers[l].d_in, layers[l].d_out);
-        if (blocks + tiles > INT32_MAX / 2) {
-          if (ga.n_layers == 0) return DP_ERR_INVALID_ARG;          // one layer beyond the grid's range
-          break;
-        }
+        if (ga.n_layers > 0 && blocks + tiles > INT32_MAX / 2) break;
         if (noise) na.layer_off[ga.n_layers] = noise->grad_offset[l];
         GroupLayer& gl = ga.layer[ga.n_layers++];
         gl = {};
@@ -633,6 +664,14 @@ dp_status clipped_grad_impl(const dp_layer* layers, int L, dp_dtype dt, int B, c
   return DP_OK;
 }
 
+dp_status clipped_grad_impl(const dp_layer* layers, int L, dp_dtype dt, int B, const float* C, const int* c_off,
+                            float* const* grads, int accumulate, void* stream, const NoiseSpec* noise = nullptr,
+                            bool out16 = false) {
+  const dp_status st = check_grads(layers, L, dt, B, C, grads, accumulate, noise, out16);
+  if (st != DP_OK) return st;
+  return launch_grads(layers, L, dt, B, C, c_off, grads, accumulate, static_cast<hipStream_t>(stream), noise, out16);
+}
+
 // Sum_i C_i G_i from kept per-sample gradients for the layers that have them (kept[l] != nullptr),
 // up to kMaxGroup layers per launch.  c_off (or nullptr): layer l's weights are C[c_off[l] + i].
 // noise (or nullptr): added by the same kernel when the layer starts on a generator block, else
@@ -701,49 +740,23 @@ dp_status dp_clipped_grad_noise_multi(const dp_layer* layers, int L, dp_dtype dt
                                       float* const* grads, const uint64_t* grad_offset, int accumulate,
                                       uint64_t shard_offset, uint64_t shard_count, float sigma, float R,
                                       uint64_t seed, uint64_t step, void* stream) {
-  if (!(sigma >= 0.f) || isinf(sigma)) return DP_ERR_INVALID_ARG;
-  if (!(R > 0.f)) return DP_ERR_INVALID_ARG;
-  if (shard_offset + shard_count < shard_offset) return DP_ERR_INVALID_ARG;   // wraps 2^64
-  if (sigma == 0.f || shard_count == 0)                                        // nothing to add
-    return clipped_grad_impl(layers, L, dt, B, C, nullptr, grads, accumulate, stream);
-  if (isinf(R) || !grad_offset || !layers || L <= 0) return DP_ERR_INVALID_ARG;
-  for (int l = 0; l < L; ++l) {
-    const uint64_t n = (uint64_t)std::max(layers[l].d_in, 0) * (uint64_t)std::max(layers[l].d_out, 0);
-    if (grad_offset[l] + n < grad_offset[l]) return DP_ERR_INVALID_ARG;
-  }
   NoiseSpec spec;
-  spec.grad_offset = grad_offset;
-  spec.lo = shard_offset;
-  spec.hi = shard_offset + shard_count;
-  spec.stddev = sigma * R;
-  spec.seed = seed;
-  spec.step = step;
-  return clipped_grad_impl(layers, L, dt, B, C, nullptr, grads, accumulate, stream, &spec);
+  bool noisy;
+  const dp_status st = make_noise(layers, L, grad_offset, shard_offset, shard_count, sigma, R, seed, step, &spec, &noisy);
+  if (st != DP_OK) return st;
+  return clipped_grad_impl(layers, L, dt, B, C, nullptr, grads, accumulate, stream, noisy ? &spec : nullptr);
 }
 
 dp_status dp_clipped_grad_noise_multi_h16(const dp_layer* layers, int L, dp_dtype dt, int B, const float* C,
                                           void* const* grads16, const uint64_t* grad_offset, int accumulate,
                                           uint64_t shard_offset, uint64_t shard_count, float sigma, float R,
                                           uint64_t seed, uint64_t step, void* stream) {
-  if (!(sigma >= 0.f) || isinf(sigma)) return DP_ERR_INVALID_ARG;
-  if (!(R > 0.f)) return DP_ERR_INVALID_ARG;
-  if (shard_offset + shard_count < shard_offset) return DP_ERR_INVALID_ARG;
-  float* const* grads = reinterpret_cast<float* const*>(grads16);      // the kernels store 16-bit values there
-  if (sigma == 0.f || shard_count == 0)
-    return clipped_grad_impl(layers, L, dt, B, C, nullptr, grads, accumulate, stream, nullptr, true);
-  if (isinf(R) || !grad_offset || !layers || L <= 0) return DP_ERR_INVALID_ARG;
-  for (int l = 0; l < L; ++l) {
-    const uint64_t n = (uint64_t)std::max(layers[l].d_in, 0) * (uint64_t)std::max(layers[l].d_out, 0);
-    if (grad_offset[l] + n < grad_offset[l]) return DP_ERR_INVALID_ARG;
-  }
   NoiseSpec spec;
-  spec.grad_offset = grad_offset;
-  spec.lo = shard_offset;
-  spec.hi = shard_offset + shard_count;
-  spec.stddev = sigma * R;
-  spec.seed = seed;
-  spec.step = step;
-  return clipped_grad_impl(layers, L, dt, B, C, nullptr, grads, accumulate, stream, &spec, true);
+  bool noisy;
+  const dp_status st = make_noise(layers, L, grad_offset, shard_offset, shard_count, sigma, R, seed, step, &spec, &noisy);
+  if (st != DP_OK) return st;
+  float* const* grads = reinterpret_cast<float* const*>(grads16);      // the kernels store 16-bit values there
+  return clipped_grad_impl(layers, L, dt, B, C, nullptr, grads, accumulate, stream, noisy ? &spec : nullptr, true);
 }
 
 dp_status dp_clipped_grad_grouped(const dp_layer* layers, int L, dp_dtype dt, int B, const float* C,
@@ -843,6 +856,45 @@ dp_status check_kept(const dp_layer* layers, int L, dp_dtype dt, float* const* k
   return DP_OK;
 }
 
+// Everything that launch_grads_kept's callers refuse, but for the noise.
+dp_status check_grads_kept(const dp_layer* layers, int L, dp_dtype dt, int B, const float* C, float* const* kept,
+                           float* const* grads, int accumulate) {
+  if (!layers || !grads || !C || L <= 0 || B <= 0 || !dtype_ok(dt)) return DP_ERR_INVALID_ARG;
+  if (accumulate != 0 && accumulate != 1) return DP_ERR_INVALID_ARG;
+  for (int l = 0; l < L; ++l) {
+    if (!dims_ok(dt, B, layers[l].T, layers[l].d_in, layers[l].d_out)) return DP_ERR_INVALID_ARG;
+    if (layers[l].path != DP_PATH_GHOST && layers[l].path != DP_PATH_PEREX) return DP_ERR_INVALID_ARG;
+    if (!grads[l] || !aligned16(grads[l])) return DP_ERR_INVALID_ARG;
+  }
+  dp_status st = check_kept(layers, L, dt, kept);
+  for (int l = 0; l < L && st == DP_OK; ++l)
+    if (!kept || !kept[l]) st = check_grad_layer(layers[l], dt, B, grads[l]);
+  return st;
+}
+
+// Layers without kept gradients: the contraction over a and g; with: weighted sums.
+dp_status launch_grads_kept(const dp_layer* layers, int L, dp_dtype dt, int B, const float* C, float* const* kept,
+                            float* const* grads, int accumulate, hipStream_t s, const NoiseSpec* noise) {
+  std::vector<dp_layer> sub;
+  std::vector<float*> sub_grads;
+  std::vector<uint64_t> sub_off;
+  for (int l = 0; l < L; ++l)
+    if (!kept || !kept[l]) {
+      sub.push_back(layers[l]);
+      sub_grads.push_back(grads[l]);
+      sub_off.push_back(noise ? noise->grad_offset[l] : 0);
+    }
+  if (!sub.empty()) {
+    NoiseSpec sub_spec;
+    if (noise) sub_spec = *noise;
+    sub_spec.grad_offset = sub_off.data();
+    const dp_status st = launch_grads(sub.data(), (int)sub.size(), dt, B, C, nullptr, sub_grads.data(), accumulate, s,
+                                      noise ? &sub_spec : nullptr);
+    if (st != DP_OK) return st;
+  }
+  return kept_sum_impl(layers, L, B, C, nullptr, kept, grads, noise, accumulate, s);
+}
+
 }  // namespace
 
 extern "C" {
@@ -861,48 +913,13 @@ dp_status dp_clipped_grad_kept_multi(const dp_layer* layers, int L, dp_dtype dt,
                                      float* const* kept, float* const* grads, const uint64_t* grad_offset,
                                      int accumulate, uint64_t shard_offset, uint64_t shard_count, float sigma,
                                      float R, uint64_t seed, uint64_t step, void* stream) {
-  if (!layers || !grads || !C || L <= 0 || B <= 0 || !dtype_ok(dt)) return DP_ERR_INVALID_ARG;
-  if (accumulate != 0 && accumulate != 1) return DP_ERR_INVALID_ARG;
-  if (!(sigma >= 0.f) || isinf(sigma) || !(R > 0.f)) return DP_ERR_INVALID_ARG;
-  if (shard_offset + shard_count < shard_offset) return DP_ERR_INVALID_ARG;
-  const bool noisy = sigma > 0.f && shard_count > 0;
-  if (noisy && (isinf(R) || !grad_offset)) return DP_ERR_INVALID_ARG;
-  for (int l = 0; l < L; ++l) {
-    if (!dims_ok(dt, B, layers[l].T, layers[l].d_in, layers[l].d_out)) return DP_ERR_INVALID_ARG;
-    if (layers[l].path != DP_PATH_GHOST && layers[l].path != DP_PATH_PEREX) return DP_ERR_INVALID_ARG;
-    if (!grads[l] || !aligned16(grads[l])) return DP_ERR_INVALID_ARG;
-    const uint64_t n = (uint64_t)layers[l].d_in * (uint64_t)layers[l].d_out;
-    if (noisy && grad_offset[l] + n < grad_offset[l]) return DP_ERR_INVALID_ARG;
-  }
-  dp_status st = check_kept(layers, L, dt, kept);
-  if (st != DP_OK) return st;
-  hipStream_t s = static_cast<hipStream_t>(stream);
   NoiseSpec spec;
-  spec.grad_offset = grad_offset;
-  spec.lo = shard_offset;
-  spec.hi = shard_offset + shard_count;
-  spec.stddev = noisy ? sigma * R : 0.f;
-  spec.seed = seed;
-  spec.step = step;
-  // (1) layers without kept gradients: the contraction over a and g
-  std::vector<dp_layer> sub;
-  std::vector<float*> sub_grads;
-  std::vector<uint64_t> sub_off;
-  for (int l = 0; l < L; ++l)
-    if (!kept || !kept[l]) {
-      sub.push_back(layers[l]);
-      sub_grads.push_back(grads[l]);
-      sub_off.push_back(noisy ? grad_offset[l] : 0);
-    }
-  if (!sub.empty()) {
-    NoiseSpec sub_spec = spec;
-    sub_spec.grad_offset = sub_off.data();
-    st = clipped_grad_impl(sub.data(), (int)sub.size(), dt, B, C, nullptr, sub_grads.data(), accumulate, stream,
-                           noisy ? &sub_spec : nullptr);
-    if (st != DP_OK) return st;
-  }
-  // (2) layers with kept gradients: weighted sums
-  return kept_sum_impl(layers, L, B, C, nullptr, kept, grads, noisy ? &spec : nullptr, accumulate, s);
+  bool noisy;
+  dp_status st = make_noise(layers, L, grad_offset, shard_offset, shard_count, sigma, R, seed, step, &spec, &noisy);
+  if (st == DP_OK) st = check_grads_kept(layers, L, dt, B, C, kept, grads, accumulate);
+  if (st != DP_OK) return st;
+  return launch_grads_kept(layers, L, dt, B, C, kept, grads, accumulate, static_cast<hipStream_t>(stream),
+                           noisy ? &spec : nullptr);
 }
 
 dp_status dp_private_step_multi(const dp_layer* layers, int L, dp_dtype dt, int B, dp_clip_mode mode, float R,
@@ -914,17 +931,21 @@ dp_status dp_private_step_multi(const dp_layer* layers, int L, dp_dtype dt, int 
   if (reinterpret_cast<uintptr_t>(counter) & 3u) return DP_ERR_INVALID_ARG;
   if (mode != DP_CLIP_STANDARD && mode != DP_CLIP_AUTOMATIC) return DP_ERR_INVALID_ARG;
   if (!(R > 0.f) || !(stability >= 0.f) || isinf(stability)) return DP_ERR_INVALID_ARG;
-  const dp_status kept_ok = check_kept(layers, L, dt, kept);
-  if (kept_ok != DP_OK) return kept_ok;
-  const ClipSpec clip = {(int)mode, stability, C_out, nullptr, R, norm_out, static_cast<unsigned*>(counter)};
-  const dp_status st = norms_impl(layers, L, dt, B, sqnorm_out, ws, ws_bytes, static_cast<hipStream_t>(stream), nullptr,
-                                  kept, &clip);
+  // All that the gradients refuse before the norms, which check the rest and launch.
+  NoiseSpec spec;
+  bool noisy;
+  dp_status st = make_noise(layers, L, grad_offset, shard_offset, shard_count, sigma, R, seed, step, &spec, &noisy);
+  if (st == DP_OK)
+    st = kept ? check_grads_kept(layers, L, dt, B, C_out, kept, grads, accumulate)
+              : check_grads(layers, L, dt, B, C_out, grads, accumulate);
   if (st != DP_OK) return st;
-  if (kept)
-    return dp_clipped_grad_kept_multi(layers, L, dt, B, C_out, kept, grads, grad_offset, accumulate, shard_offset,
-                                      shard_count, sigma, R, seed, step, stream);
-  return dp_clipped_grad_noise_multi(layers, L, dt, B, C_out, grads, grad_offset, accumulate, shard_offset, shard_count,
-                                     sigma, R, seed, step, stream);
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  const ClipSpec clip = {(int)mode, stability, C_out, nullptr, R, norm_out, static_cast<unsigned*>(counter)};
+  st = norms_impl(layers, L, dt, B, sqnorm_out, ws, ws_bytes, s, nullptr, kept, &clip);
+  if (st != DP_OK) return st;
+  const NoiseSpec* noise = noisy ? &spec : nullptr;
+  return kept ? launch_grads_kept(layers, L, dt, B, C_out, kept, grads, accumulate, s, noise)
+              : launch_grads(layers, L, dt, B, C_out, nullptr, grads, accumulate, s, noise);
 }
 
 }  // extern "C"

@@ -107,6 +107,41 @@ def test_validation_of_the_later_entry_points(dp):
     assert lib.dp_clipped_bias_grad(fake, 1, 8, fake, fake, 2, None) == INV
 
 
+# Every refusal of a whole step's gradient half comes before its norms are launched: without a GPU a launch would give
+# DP_ERR_HIP, on a GPU the norms would have been overwritten (test_refused_step_touches_nothing).
+@pytest.mark.parametrize("keeps", [False, True])
+@pytest.mark.parametrize("bad", [
+    dict(sigma=-1.0), dict(sigma=float("nan")), dict(sigma=float("inf")), dict(R=float("inf")), dict(R=0.0), dict(accumulate=2),
+    dict(shard=(2 ** 64 - 1, 2)), dict(grad=0x1004), dict(grad=None), dict(grads=None), dict(offsets=None), dict(offset=2 ** 64 - 1),
+    dict(counter=0x1002), dict(mode=2), dict(stability=-1.0), dict(C=None), dict(sqnorm=None), dict(ws=None),
+])
+def test_step_refuses_before_any_launch(dp, bad, keeps):
+    import ctypes as C
+    fake = 0x1000
+    layers = dp.layer_array([(fake, fake, 64, 8, 8, dp.DP_PATH_PEREX), (fake, fake, 64, 8, 8, dp.DP_PATH_GHOST)])
+    ok = dict(sigma=1.0, R=1.0, accumulate=0, shard=(0, 128), grad=fake, grads=(), offsets=(), offset=64, counter=fake, mode=0,
+              stability=0.01, C=fake, sqnorm=fake, ws=fake)
+    a = dict(ok, **bad)
+    kept = (C.c_void_p * 2)(fake, None) if keeps else None
+    grads = (C.c_void_p * 2)(fake, a["grad"]) if a["grads"] is not None else None
+    offsets = (C.c_uint64 * 2)(0, a["offset"]) if a["offsets"] is not None else None
+    st = dp.lib.dp_private_step_multi(layers, 2, dp.DP_BF16, 4, a["mode"], a["R"], a["stability"], kept, grads, offsets,
+                                      a["accumulate"], *a["shard"], a["sigma"], 0, 0, a["sqnorm"], a["C"], None, a["ws"],
+                                      1 << 20, a["counter"], None)
+    assert st == (dp.DP_ERR_WORKSPACE if bad == dict(ws=None) else dp.DP_ERR_INVALID_ARG)
+
+
+def test_step_refuses_what_fp32_layers_refuse(dp):
+    import ctypes as C
+    fake = 0x1000
+    grads = (C.c_void_p * 1)(fake)
+    step = lambda T, d, kept: dp.lib.dp_private_step_multi(
+        dp.layer_array([(fake, fake, T, d, d, dp.DP_PATH_PEREX)]), 1, dp.DP_F32, 1, 0, 1.0, 0.01, kept, grads, None, 0, 0, 0,
+        0.0, 0, 0, fake, fake, None, None, 0, None, None)
+    assert step(4096, 4096, None) == dp.DP_ERR_UNSUPPORTED                         # more than 2^28 multiply-adds a sample
+    assert step(8, 8, (C.c_void_p * 1)(fake)) == dp.DP_ERR_UNSUPPORTED             # kept gradients are for 16-bit layers
+
+
 # ----------------------------------------------------------------------------
 # tile orders of the large-tile kernels: every tile exactly once, for any shape
 # ----------------------------------------------------------------------------

@@ -380,3 +380,29 @@ def test_step_in_one_call(dtype, B, T, dims, paths, mode):
     pipe.C_groups.fill_(123.0)
     pipe.clip_grouped(mode, 0.01)
     assert torch.equal(C.view(torch.int32), pipe.C_groups.view(torch.int32))
+
+
+# A step that is refused has touched none of its outputs.
+@pytest.mark.parametrize("bad", [
+    dict(sigma=-1.0), dict(R=float("inf")), dict(accumulate=2), dict(offset=2 ** 64 - 1), dict(count=2 ** 64 - 1), dict(grads=4),
+    dict(ws=None), dict(counter=2),
+])
+def test_refused_step_touches_nothing(bad):
+    from paper_2311_11822_amd import binding as dp
+    from paper_2311_11822_amd.pipeline import BkPipeline
+    w = si.small_workload("refused", si.BF16, 3, 40, [(72, 136), (16, 24)], g_std=1e-2)
+    pipe = BkPipeline([tuple(dev(x) for x in si.gen_layer(w, l)) for l in range(w.L)], [dp.DP_PATH_GHOST, dp.DP_PATH_PEREX])
+    outputs = [pipe.sqnorm, pipe.C, pipe.norm, pipe.flat, pipe.kept[1]]
+    for x in outputs:
+        x.fill_(123.0)
+    a = dict(dict(sigma=0.5, R=1.0, accumulate=0, offset=8, count=16, grads=0, ws=pipe.ws, counter=0), **bad)
+    grads = [x.data_ptr() for x in pipe.grads]
+    grads[1] += a["grads"]
+    with pytest.raises(dp.DpError):
+        dp.dp_private_step_multi(pipe.desc, pipe.dt, pipe.B, dp.DP_CLIP_STANDARD, a["R"], 0.01, pipe.kept_ptrs, grads,
+                                 pipe.grad_offsets, a["accumulate"], a["offset"], a["count"], a["sigma"], 3, 0, pipe.sqnorm,
+                                 pipe.C, pipe.norm, a["ws"], pipe.counter.data_ptr() + a["counter"])
+    torch.cuda.synchronize()
+    for x in outputs:
+        assert (x == 123.0).all()
+    assert pipe.counter.item() == 0
