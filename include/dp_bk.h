@@ -310,8 +310,10 @@ dp_status dp_clipped_grad_kept_multi(const dp_layer* layers, int L, dp_dtype dt,
  * One step of all-layer clipping with one call: dp_norms_multi_keep (kept == NULL: dp_norms_multi), dp_clip_factors and
  * dp_clipped_grad_kept_multi (kept == NULL: dp_clipped_grad_noise_multi) on the same arguments, with the same results
  * and fewer launches; what any of the three would refuse is refused before anything is enqueued.  norm_out may be NULL.
- *   counter  device, 4 bytes that are zero when the call's work begins and are left zero (one such cell may serve any
- *            calls whose work does not overlap on the GPU, as sqnorm_out and ws may); or NULL, which costs small stacks a launch
+ *   counter  device, 4 bytes, 4-byte aligned, that are zero when the call's work begins and are left zero (one such cell may
+ *            serve any calls whose work does not overlap on the GPU, as sqnorm_out and ws may); or NULL, which costs small
+ *            stacks a launch.  Clear it on the stream of the calls, or before them: a call that finds another value there
+ *            may leave C_out and norm_out unwritten, and so may each one after it.
  */
 dp_status dp_private_step_multi(const dp_layer* layers, int L, dp_dtype dt, int B, dp_clip_mode mode, float R,
                                 float stability, float* const* kept, float* const* grads, const uint64_t* grad_offset,

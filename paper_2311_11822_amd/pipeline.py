@@ -47,7 +47,9 @@ class BkPipeline:
         if ws_bytes == 0:
             raise dp.DpError(dp.DP_ERR_INVALID_ARG, "dp_norms_multi_workspace_bytes")
         self.ws = torch.empty(ws_bytes, dtype=torch.uint8, device=self.device)
-        self.counter = torch.zeros(1, dtype=torch.int32, device=self.device)      # zero between steps
+        # Zero between steps; cleared on the stream that is current here, so only steps on that stream may count on it.
+        self.counter = torch.zeros(1, dtype=torch.int32, device=self.device)
+        self.counter_stream = torch.cuda.current_stream(self.device).cuda_stream if self.device.type == "cuda" else None
         # Layers on the instantiated path keep their per-sample gradients [B, d, p] between the norm
         # pass and the gradient pass (smaller than the layer's Gram matrices by the path rule).
         self.kept = [None] * L
@@ -124,10 +126,11 @@ class BkPipeline:
 
     def step(self, mode, R, sigma, stability, seed, step, offset, count, stream=None, fused=True):
         if fused:                      # norms, clip and grad_noise in one call of the library
+            stream = dp._stream(stream)
             dp.dp_private_step_multi(self.desc, self.dt, self.B, mode, R, stability,
                                      self.kept_ptrs if self.any_kept else None, self.grad_ptrs, self.grad_offsets, 0,
-                                     offset, count, sigma, seed, step, self.sqnorm, self.C, self.norm, self.ws, self.counter,
-                                     stream)
+                                     offset, count, sigma, seed, step, self.sqnorm, self.C, self.norm, self.ws,
+                                     self.counter if stream == self.counter_stream else None, stream)
             return
         self.norms(stream)
         self.clip(mode, R, stability, stream)

@@ -406,3 +406,40 @@ def test_refused_step_touches_nothing(bad):
     for x in outputs:
         assert (x == 123.0).all()
     assert pipe.counter.item() == 0
+
+
+def test_step_counts_only_where_its_counter_was_cleared(monkeypatch):
+    """The cell in which workgroups count must be zero when a step begins: a step on another stream than the one that
+    cleared it has nothing that orders the two, and forms the factors in a launch of their own."""
+    from paper_2311_11822_amd import binding as dp
+    from paper_2311_11822_amd.pipeline import BkPipeline
+    w = si.small_workload("cell", si.F32, 4, 8, [(16, 16)])
+    layers = [tuple(dev(x) for x in si.gen_layer(w, 0))]
+    torch.cuda.synchronize()
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        pipe = BkPipeline(layers)
+    given = []
+    step = lambda stream=None: pipe.step(o.CLIP_STANDARD, 0.5, 0.0, 0.01, 0, 0, 0, 0, stream)
+    with monkeypatch.context() as m:                      # which cell is passed, nothing enqueued
+        m.setattr(dp, "dp_private_step_multi", lambda *args: given.append(args[-2]))
+        step()
+        step(side)
+        step(side.cuda_stream)
+        step(other)
+        with torch.cuda.stream(other):
+            step()
+            step(side)
+    assert [x is pipe.counter for x in given] == [False, True, True, False, False, True]
+    assert all(x is None for x in given if x is not pipe.counter)
+    want = None
+    for stream in (side, other, torch.cuda.current_stream(), side):
+        for x in (pipe.C, pipe.norm, pipe.flat):
+            x.fill_(123.0)
+        torch.cuda.synchronize()
+        step(stream)
+        torch.cuda.synchronize()
+        got = [x.clone() for x in (pipe.sqnorm, pipe.C, pipe.norm, pipe.flat)]
+        want = want or got
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+        assert pipe.counter.item() == 0
