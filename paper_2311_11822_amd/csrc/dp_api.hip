@@ -91,9 +91,12 @@ NormClip layer_clip(const ClipSpec* clip) {
   return nc;
 }
 
-// The last launch of final norms forms the factors of the one group where that is cheaper than a launch (3 us of host
-// time, about 2 on the GPU): one round of workgroups, whose count is a round trip to memory each, and no more norms
-// than the last of them reads at one time.
+// The last launch of final norms forms the factors of the one group where that is cheaper than a launch: few workgroups,
+// whose counts are added one after the other, and few layers, which are as many lanes of the last sum.  Against a launch
+// of its own (fp32 and 16-bit layers 16 to 768 wide), us on the GPU and of a step that the host enqueues: one to three
+// layers, up to 64 workgroups 0.1 to 0.8 and 0.4 to 2.5 less; eight layers, 32 and 64 workgroups 0.1 and 0.7 less, 96
+// 0.2 more and 0.5 less, 128 0.6 more and the same; twelve and sixteen layers, up to 64 workgroups 0.2 more and 0.6 less.
+constexpr int kLastBlocks = 64, kLastLayers = 8;
 int lanes_for(int L) {
   int width = 1;
   while (width < 64 && width < L) width *= 2;
@@ -101,7 +104,8 @@ int lanes_for(int L) {
 }
 
 bool last_forms_factors(const ClipSpec* clip, int64_t blocks, int L, int B) {
-  return clip && !clip->layer_R && clip->counter && blocks <= 256 && L <= 256 && (int64_t)B * lanes_for(L) <= 4096;
+  return clip && !clip->layer_R && clip->counter && blocks <= kLastBlocks && L <= kLastLayers &&
+         (int64_t)B * lanes_for(L) <= kFinishLanes;
 }
 
 void set_group_factors(NormClip& nc, const ClipSpec& clip, int64_t blocks, int L) {
