@@ -17,10 +17,8 @@ namespace {
 
 constexpr int BM = BigTile::BM, BN = BigTile::BN;
 
-// Tile t of the launch -> layer and tile origin (order inside a layer: tile_order.h).
-__device__ __forceinline__ void locate_tile(const GroupArgs& ga, int t, int& layer, int& m0, int& n0) {
-  const int l = layer_of(ga, t);
-  layer = l;
+// Tile t of the launch, one of layer l's -> tile origin (order inside a layer: tile_order.h).
+__device__ __forceinline__ void locate_tile(const GroupArgs& ga, int l, int t, int& m0, int& n0) {
   const GroupLayer& ly = ga.layer[l];
   int tm, tn;
   grad_tile_of((ly.d_in + BM - 1) / BM, (ly.d_out + BN - 1) / BN, t - ly.tile_begin, tm, tn);
@@ -29,14 +27,13 @@ __device__ __forceinline__ void locate_tile(const GroupArgs& ga, int t, int& lay
 }
 
 template <class S, bool F16, bool NOISE, bool OUT16>
-__device__ __forceinline__ void gradient_tile(const GroupArgs& ga, int l, int m0, int n0, const float* C_global,
+__device__ __forceinline__ void gradient_tile(const GroupArgs& ga, int l, int m0, int n0, const float* C, float w,
                                               const NoiseArgs& na) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
   const GroupLayer& ly = ga.layer[l];
   const int d = ly.d_in, p = ly.d_out;
-  const const_floats C = (const_floats)(uintptr_t)(C_global + ly.c_off);          // the layer's clipping group
   f32x16 acc[S::TM][S::TN];
-  const float held = tn_contract<S, F16, true>(ly.a, ly.g, ly.T, d, p, 0, ga.B, C, m0, n0,
+  const float held = tn_contract<S, F16, true>(ly.a, ly.g, ly.T, d, p, 0, ga.B, C, w, m0, n0,
                                                (unsigned)(uintptr_t)lds_raw, acc);
 
   // epilogue: grad (+)= held * acc (+ noise), in the transposed layout described at tile_noise.
@@ -81,11 +78,14 @@ __device__ __forceinline__ void gradient_tile(const GroupArgs& ga, int l, int m0
 
 template <bool F16, bool NOISE, bool OUT16>
 __global__ void __launch_bounds__(BigTile::NT)
-clipped_grad_big_kernel(const GroupArgs ga, const float* __restrict__ C, const NoiseArgs na) {
+clipped_grad_big_kernel(const GroupArgs ga, const float* __restrict__ C_all, const NoiseArgs na) {
   const int logical = grad_logical_tile(blockIdx.x, ga.total_blocks);     // XCD-aware: tile_order.h
-  int l, m0, n0;
-  locate_tile(ga, logical, l, m0, n0);
-  gradient_tile<BigTile, F16, NOISE, OUT16>(ga, l, m0, n0, C, na);
+  const int l = layer_of(ga, logical);
+  const float* C = C_all + ga.layer[l].c_off;                             // the layer's clipping group
+  const float w = window_weights(C, 0, ga.B);
+  int m0, n0;
+  locate_tile(ga, l, logical, m0, n0);
+  gradient_tile<BigTile, F16, NOISE, OUT16>(ga, l, m0, n0, C, w, na);
 }
 
 // End of a launch.  All tiles of a launch take the same time and one workgroup fills a compute
@@ -97,14 +97,20 @@ static_assert(MID_SIDE * MidTile::BM == BM && MID_SIDE * MidTile::BN == BN, "sub
 
 template <bool F16, bool NOISE, bool OUT16>
 __global__ void __launch_bounds__(MidTile::NT, 2)
-clipped_grad_mid_kernel(const GroupArgs ga, const float* __restrict__ C, int first_tile, const NoiseArgs na) {
+clipped_grad_mid_kernel(const GroupArgs ga, const float* __restrict__ C_all, int first_tile, const NoiseArgs na) {
   const SubTile sub = grad_sub_tile<MID_SIDE>(blockIdx.x, gridDim.x);
-  int l, m0, n0;
-  locate_tile(ga, first_tile + sub.tile, l, m0, n0);
+  const int l = layer_of(ga, first_tile + sub.tile);
+  const float* C = C_all + ga.layer[l].c_off;
+  const float w = window_weights(C, 0, ga.B);
+  int m0, n0;
+  locate_tile(ga, l, first_tile + sub.tile, m0, n0);
   m0 += sub.row * MidTile::BM;
   n0 += sub.col * MidTile::BN;
-  if (m0 >= ga.layer[l].d_in || n0 >= ga.layer[l].d_out) return;      // past the layer's edge (whole workgroup)
-  gradient_tile<MidTile, F16, NOISE, OUT16>(ga, l, m0, n0, C, na);
+  if (m0 >= ga.layer[l].d_in || n0 >= ga.layer[l].d_out) {            // past the layer's edge (whole workgroup)
+    asm volatile("" ::"v"(w));                                        // keeps the load of w above this branch
+    return;
+  }
+  gradient_tile<MidTile, F16, NOISE, OUT16>(ga, l, m0, n0, C, w, na);
 }
 
 // ---------------------------------------------------------------------------------
@@ -288,8 +294,9 @@ clipped_grad_tail_kernel(const GroupArgs ga, const float* __restrict__ C_all, in
                          const NoiseArgs na) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds_tail[];
   const SubTile sub = grad_sub_tile<TAIL_SIDE>(blockIdx.x, gridDim.x);
-  int l, m0, n0;
-  locate_tile(ga, first_tile + sub.tile, l, m0, n0);
+  const int l = layer_of(ga, first_tile + sub.tile);
+  int m0, n0;
+  locate_tile(ga, l, first_tile + sub.tile, m0, n0);
   const GroupLayer& ly = ga.layer[l];
   m0 += sub.row * TAIL;
   n0 += sub.col * TAIL;

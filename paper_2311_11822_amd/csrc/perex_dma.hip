@@ -36,7 +36,7 @@ perex_dma_kernel(const GroupArgs ga, float* __restrict__ partials) {
   const int wm = (wave / S::WN) * S::WTM, wn = (wave % S::WN) * S::WTN;
 
   f32x16 acc[S::TM][S::TN];
-  tn_contract<S, F16, false>(ly.a, ly.g, ly.T, d, p, sample, sample + 1, nullptr, m0, n0,
+  tn_contract<S, F16, false>(ly.a, ly.g, ly.T, d, p, sample, ga.B, nullptr, 0.f, m0, n0,
                              (unsigned)(uintptr_t)lds_raw, acc);
   __syncthreads();                                      // LDS is reused below
 

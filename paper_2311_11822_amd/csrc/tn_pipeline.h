@@ -36,6 +36,12 @@
 //    (17 .. 32 tokens) next to nothing.  Gradient stage, us, before and after: 31 x 32 tokens, ten layers
 //    704 x 704 37.6, 31.2; 64 x 32, eight layers 1024 wide 196, 161; 32 x 48 141, 118; 10 x 100, 24 layers 270, 246;
 //    32 x 197, 48 layers 768 wide 1258, 1201; 4 x 2048, four layers 4096 wide 2872, 2854.
+//    Few k-blocks are bound by what comes before and after them, so that the first weights are asked for before the tile is
+//    located, the loads begin when it is known which samples count and the divisions wait until then (one sample: none),
+//    and the last sample's blocks, of whatever number of k-steps, test nothing.  Gradient stage, us, on the 32-row blocks
+//    with scalar loads, with all of it before the first load, and now: 64 tokens, eight layers 1024 wide 17.0, 17.8, 16.8;
+//    16 tokens of 4096 170.8, 176.1, 167.7; 40 tokens, 24 layers 768 x 3072 82.0, 85.1, 82.7; two layers 3744 x 2352
+//    32.6, 34.1, 32.9; 512 tokens, four layers 4096 wide 143.0, 146.2, 142.8.
 //    Measured and not kept: multiplies between the matrix instructions, a branch or 16 multiplies for each (+9 % at 2048
 //    tokens, no gain at 32); one of a SIMD's two waves multiplying after its block, the other before its
 //    (64 x 32 tokens: 95 us where both before it take 87); all of the bookkeeping without branches (spills scalars).
@@ -65,8 +71,6 @@ struct PipeShape {
 };
 using BigTile = PipeShape<256, 2, 4>;
 using MidTile = PipeShape<128, 2, 2>;
-
-typedef const __attribute__((address_space(4))) float* const_floats;
 
 // c *= f (the bits of a float) where turn is not zero.  Branch and multiplies are inside the assembly and every accumulator
 // is one operand, so that for the compiler the contraction is one piece of straight code over whole register tuples:
@@ -104,11 +108,18 @@ __device__ __forceinline__ void scale_if(unsigned turn, unsigned f, f32x16 (&c)[
 }
 #undef DP_SCALE_TUPLES
 
-// Samples [first, end) of the layer (one, unless WEIGHTED) into `acc` (zeroed here); returns the weight the sum is
-// expressed in (WEIGHTED; 0 when no sample counts), else 1.  C: weights by sample.
+// Weights of the samples window .. window + 63, one a lane; 0 from sample B on.
+__device__ __forceinline__ float window_weights(const float* C, unsigned window, int B) {
+  const auto r = __builtin_amdgcn_make_buffer_rsrc((void*)(C + window), 0, 4 * min(B - (int)window, 64), 0x00020000);
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, 4 * (threadIdx.x & 63), 0, 0));
+}
+
+// Samples [0, B) of the layer (one, `sample`, unless WEIGHTED) into `acc` (zeroed here); returns the weight the sum is
+// expressed in (WEIGHTED; 0 when no sample counts), else 1.  C: weights by sample; w: those of the first window, which the
+// caller asks for as early as it can (nothing is loaded before they are known).
 template <class S, bool F16, bool WEIGHTED>
-__device__ __forceinline__ float tn_contract(const void* a, const void* g, int T, int d, int p, int first_sample,
-                                             int end_sample, const_floats C, int m0, int n0, unsigned lds0,
+__device__ __forceinline__ float tn_contract(const void* a, const void* g, int T, int d, int p, int sample, int B,
+                                             const float* C, float w, int m0, int n0, unsigned lds0,
                                              f32x16 (&acc)[S::TM][S::TN]) {
   constexpr int NSTAGE = S::NSTAGE, STAGE_BYTES = S::STAGE_BYTES, TILE_BYTES = S::TILE_BYTES, ROW_BYTES = S::ROW_BYTES;
   constexpr int BLOCK_LOADS = 2 * S::LOADS, KSTEP = 16;
@@ -209,15 +220,16 @@ __device__ __forceinline__ float tn_contract(const void* a, const void* g, int T
   };
   constexpr int ITEMS = S::TM + S::TN, STEPS = S::TM * S::TN;
   int c_stage;
-  // The stream begins at sample smp: blocks 0 .. NSTAGE-2 in flight; block 0 complete in LDS, its first fragments
+  // The stream begins at sample smp: blocks 0 .. NSTAGE-2 in flight; then block 0 complete in LDS, its first fragments
   // requested.
-  auto open_stream = [&](int smp) {
+  auto start_stream = [&](int smp) {
     c_stage = p_stage = 0;
     p_steps = steps;
     va = a_org;
     vb = b_org;
     ra = make_rsrc(static_cast<const unsigned char*>(a) + (size_t)smp * a_slab, a_slab);
     rb = make_rsrc(static_cast<const unsigned char*>(g) + (size_t)smp * b_slab, b_slab);
+#pragma unroll 1
     for (int q = 0; q < NSTAGE - 1; ++q)
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
@@ -225,6 +237,8 @@ __device__ __forceinline__ float tn_contract(const void* a, const void* g, int T
         prefetch_b(ks);
         prefetch_advance(ks);
       }
+  };
+  auto await_stream = [&]() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NSTAGE - 2) * BLOCK_LOADS) : "memory");
     __syncthreads();
 #pragma unroll
@@ -273,30 +287,33 @@ __device__ __forceinline__ float tn_contract(const void* a, const void* g, int T
   if constexpr (WEIGHTED) {
     // Samples in windows of 64: their weights are in the lanes, which of them count in a scalar mask, so that the step
     // from one to the next is a few scalar instructions between matrix instructions.
-    for (int window = first_sample; window < end_sample; window += 64) {
-      const int i = window + lane;
-      const float w = i < end_sample ? C[i] : 0.f;
+    for (unsigned window = 0; window < (unsigned)B; window += 64) {
+      if (window > 0) w = window_weights(C, window, B);
       uint64_t mask = __ballot(w != 0.f);
       if (mask == 0) continue;
-      const uint64_t before = mask & ((1ull << lane) - 1);
-      const float prev = __shfl(w, before ? 63 - __builtin_clzll(before) : lane);
-      const float ratio = before ? prev / w : held != 0.f ? held / w : 1.f;
       if (held != 0.f) __syncthreads();                  // the last window's fragments are read
-      held = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), 63 - __builtin_clzll(mask)));
       const int first = __builtin_ctzll(mask);
       const uint64_t p_all = mask >> first;
       p_mask = p_all;
-      open_stream(window + first);
+      start_stream(window + first);                      // the ratios while its first loads are on their way
+      float ratio = 1.f;
+      if (B > 1) {                                       // one sample: nothing to go on from
+        const uint64_t before = mask & ((1ull << lane) - 1);
+        const float prev = __shfl(w, before ? 63 - __builtin_clzll(before) : lane);
+        ratio = before ? prev / w : held != 0.f ? held / w : 1.f;
+      }
+      held = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), 63 - __builtin_clzll(mask)));
+      await_stream();
       constexpr unsigned kOne = 0x3f800000u;             // bits of 1.f
       int n = __builtin_popcountll(mask) * steps;        // odd: the last k-step's rows are zeros
       // f: ratio of the sample that comes next; turn: not zero where the next k-step is its first and it is not 1
       unsigned f = __builtin_amdgcn_readlane(__float_as_uint(ratio), first), turn = f ^ kOne;
-      int left = steps;
+      int left;                                          // k-steps to the end of the sample at hand; two more for the last one
       unsigned f_next;                                   // the ratio of the sample after the one at hand
       auto to_next = [&]() {
         mask &= mask - 1;
         f_next = mask ? __builtin_amdgcn_readlane(__float_as_uint(ratio), __builtin_ctzll(mask)) : kOne;
-        left = steps;
+        left = mask ? steps : steps + 2;
       };
       to_next();
       auto count = [&](int ks) {
@@ -337,12 +354,14 @@ __device__ __forceinline__ float tn_contract(const void* a, const void* g, int T
         n = 0;
       }
       while (n > 0) {
-        if (turn == 0)
-          for (; left > 2; left -= 2, n -= 2) {          // blocks inside the sample
+        if (turn == 0) {
+          for (; left > 2; left -= 2, n -= 2) {          // blocks inside the sample, or to the end of the last one
             open_block();
             step(even, even, prefetch_advance);
             step(odd, even, prefetch_advance);
           }
+          if (n <= 0) break;
+        }
         n -= 2;
         open_block();
         scale(turn, f);
@@ -354,7 +373,8 @@ __device__ __forceinline__ float tn_contract(const void* a, const void* g, int T
     }
   } else {                                               // one sample
     held = 1.f;
-    open_stream(first_sample);
+    start_stream(sample);
+    await_stream();
     const int nkb = (T + S::BK - 1) / S::BK;
     for (int kb = 0; kb < nkb; kb += DEPTH) {
       open_block();

@@ -280,6 +280,7 @@ def test_fp16_narrow_layers_keep_pace_with_bf16():
 @pytest.mark.parametrize("B,T,zero", [
     (3, 21, ()), (64, 32, ()), (65, 32, (0, 63, 64)), (67, 20, ()), (131, 24, tuple(range(64, 128))), (66, 33, (1, 2, 65)),
     (5, 48, (4,)), (7, 40, (0, 1, 3)), (3, 49, ()), (2, 112, ()), (4, 33, (0, 1, 2, 3)),
+    (1, 40, ()), (1, 64, ()), (1, 24, (0,)), (2, 48, (0,)), (65, 48, tuple(range(64))), (66, 24, (65,)), (129, 40, ()),
 ])
 def test_weighted_stream(side, n, B, T, zero):
     from paper_2311_11822_amd import binding as dp
