@@ -94,9 +94,10 @@ NormClip layer_clip(const ClipSpec* clip) {
 // The last launch of final norms forms the factors of the one group where that is cheaper than a launch: few workgroups,
 // whose counts are added one after the other, and few layers, which are as many lanes of the last sum.  Against a launch
 // of its own (fp32 and 16-bit layers 16 to 768 wide), us on the GPU and of a step that the host enqueues: one to three
-// layers, up to 64 workgroups 0.1 to 0.8 and 0.4 to 2.5 less; eight layers, 32 and 64 workgroups 0.1 and 0.7 less, 96
-// 0.2 more and 0.5 less, 128 0.6 more and the same; twelve and sixteen layers, up to 64 workgroups 0.2 more and 0.6 less.
-constexpr int kLastBlocks = 64, kLastLayers = 8;
+// layers, up to 64 workgroups 0.1 to 0.8 and 0.4 to 2.5 less; eight to sixteen layers, up to 96 workgroups 0.2 more and
+// 0.5 less (steps of 10 us on the GPU and 13 on the host); 128 workgroups 0.6 more and the same; 32 layers of one sample
+// 0.5 more and 0.4 less, 64 0.4 and 0.3 more.
+constexpr int kLastBlocks = 96, kLastLayers = 16;
 int lanes_for(int L) {
   int width = 1;
   while (width < 64 && width < L) width *= 2;
