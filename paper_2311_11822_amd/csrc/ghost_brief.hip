@@ -54,9 +54,18 @@ ghost_brief_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int fir
   const int l = layer_of(ga, block);
   const GroupLayer& ly = ga.layer[l];
   const int T = ly.T, per = kRows / T, parts = ly.tiles_per_sample;
-  const int local = block - ly.tile_begin, i0 = local / parts * per;         // first sample of the 32 rows
-  const int share = (per + parts - 1) / parts, begin = local % parts * share;
-  const int end = min(min(begin + share, per), ga.B - i0);                   // this workgroup's: i0 + [begin, end)
+  int rows32 = block - ly.tile_begin, begin = 0, end = per;                  // which 32 rows; this workgroup's samples
+  // Launches of more than 256 workgroups have one to 32 rows.  The quotients are of numbers below 512 by up to 32 (integer
+  // divisions cost 0.1 us: two samples of 32 tokens, 24 layers 128 x 384 5.0 -> 4.8 us, 3000 of ten tokens 18.7 -> 17.9).
+  if (parts > 1) {
+    const float inv = __builtin_amdgcn_rcpf((float)parts);
+    const int share = (int)(((float)(per + parts - 1) + 0.5f) * inv), local = rows32;
+    rows32 = (int)(((float)local + 0.5f) * inv);
+    begin = (local - rows32 * parts) * share;
+    end = min(begin + share, per);
+  }
+  const int i0 = rows32 * per;                                               // first sample of the 32 rows
+  end = min(end, ga.B - i0);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool valid = (lane & 31) >= begin * T && (lane & 31) < end * T;
