@@ -3,6 +3,9 @@
 // instantiation.  The B x d_out matrix of these sums is tiny, so it is kept (book-keeping): the
 // clipped bias gradient sum_i C_i 1^T g_i is then formed from it without reading g again.
 // The kernels are streams over memory (HBM-bound) or, for small samples, latency-bound; sums run in a fixed order.
+#include <algorithm>
+#include <type_traits>
+
 #include "dp_internal.h"
 
 namespace dpbk {
@@ -72,20 +75,24 @@ bias_colsum_kernel(const void* __restrict__ g_all, int T, int p, float* __restri
 }
 
 // Column sums and their norm in one launch, one workgroup to a sample, where that is no slower than two: a launch costs
-// the host 2.4 us, and one compute unit reads 90 GB/s.  Thread (rg, ct) adds rows rg, rg + groups, ... of its 8 columns,
-// eight rows in flight and added in pairs; the row groups are added through LDS.  Times on the GPU, us, here and in two
-// launches (8 samples): 32 tokens of 768 columns 3.2 and 4.6, 128 x 256 3.4 and 4.3, 8 x 8192 5.2 and 5.1,
-// 128 x 768 5.0 and 5.0, 32 x 3072 5.1 and 5.1, 128 x 1536 7.2 and 5.1.  Up to 256 columns the two-launch form has one workgroup to a sample
-// too, of a quarter of the loads in flight: 2048 x 64 5.9 and 11.3, 2048 x 256 13 and 17.
+// the host 2.4 us, and a workgroup of 1024 threads that has eight loads of each in flight reads 90 GB/s.  Thread (rg, ct)
+// adds rows rg, rg + groups, ... of its 8 columns, eight rows in flight and added in pairs; the row groups are added
+// through LDS.  Times on the GPU, us, here and in two launches (8 samples): 16 tokens of 768 columns 3.7 and 4.9,
+// 160 x 256 4.1 and 5.2, 16 x 3072 4.9 and 5.1, 1 x 8192 5.8 and 5.6, 160 x 512 5.5 and 5.3, 128 x 1536 7.2 and 5.1.  Up to
+// 256 columns the two-launch form has one workgroup to a sample too, of a quarter of the loads in flight: 2048 x 64 6.4
+// and 11.5, 2048 x 200 10.9 and 12.0.
+// A workgroup has 64, 256 or 1024 threads, as many as have rows to load or a column to add up (the sums are the same):
+// with 1024 for any sample, many small ones wait for waves with nothing to do (65535 samples of 1 x 64: 228 us, 168 in
+// two launches, now 29; 4096 of 16 x 256 18.4, 16.1, 8.3).
 constexpr int kOneThreads = 1024, kOneRows = 8;
-template <int DT>
-__global__ void __launch_bounds__(kOneThreads)
+template <int DT, int THREADS>
+__global__ void __launch_bounds__(THREADS)
 bias_norm_kernel(const uint16_t* __restrict__ g_all, int T, int p, float* __restrict__ colsum, float* __restrict__ sqnorm) {
-  __shared__ float red[kOneThreads * 8];
-  __shared__ float wave_sum[kOneThreads / 64];
+  __shared__ float red[THREADS * 8];
+  __shared__ float wave_sum[THREADS / 64];
   const int tid = threadIdx.x, i = blockIdx.x;
-  const int chunks = p / 8;                              // at most kOneThreads
-  const int groups = min(kOneThreads / chunks, (T + kOneRows - 1) / kOneRows);
+  const int chunks = p / 8;
+  const int groups = min(kOneThreads / chunks, (T - 1) / kOneRows + 1);      // of all sizes: the same sums
   const int rg = tid / chunks, ct = tid - rg * chunks;
   if (rg < groups) {
     const uint16_t* g = g_all + (size_t)i * T * p + 8 * ct;
@@ -120,7 +127,7 @@ bias_norm_kernel(const uint16_t* __restrict__ g_all, int T, int p, float* __rest
   }
   __syncthreads();
   float s = 0.f;
-  for (int c = tid; c < p; c += kOneThreads) {
+  for (int c = tid; c < p; c += THREADS) {
     float part[4] = {};
     int r = 0;
     for (; r + 4 <= groups; r += 4)
@@ -138,7 +145,7 @@ bias_norm_kernel(const uint16_t* __restrict__ g_all, int T, int p, float* __rest
   if (tid == 0) {
     float total = 0.f;
 #pragma unroll
-    for (int w = 0; w < kOneThreads / 64; ++w) total += wave_sum[w];
+    for (int w = 0; w < THREADS / 64; ++w) total += wave_sum[w];
     sqnorm[i] = total;
   }
 }
@@ -201,18 +208,32 @@ clipped_bias_kernel(const float* __restrict__ colsum, int B, int p, const float*
   grad_b[k] = accumulate ? old + s : s;
 }
 
-constexpr int kOneColumns = 256, kOneValues = 160 * 512;
+// One launch?  Near the lines (160 x 512 values, one row of 8192) it takes 0.2 to 0.4 us more on the GPU for the host's 2.4.
+// Many samples of 129 to 256 columns that take a thread more than one trip stream better in the other form (256 x 1024
+// tokens of 256 columns: 27.7 and 22.8 us, 2048 x 1024 207 and 188; of 200 columns, 512 x 1024: the same).
+constexpr int kOneColumns = 256, kOneValues = 160 * 512, kManySamples = 256;
+bool one_launch(int B, int64_t T, int p) {
+  if (T * p <= kOneValues) return p <= 8 * kOneThreads;
+  return p <= kOneColumns && (p <= kOneColumns / 2 || B < kManySamples);
+}
 
 }  // namespace
 
 dp_status launch_bias_norm(const void* g, dp_dtype dt, int B, int T, int p, float* colsum,
                            float* sqnorm_out, hipStream_t s) {
-  if (dt != DP_F32 && p <= 8 * kOneThreads && (p <= kOneColumns || (int64_t)T * p <= kOneValues)) {
-    const uint16_t* g16 = static_cast<const uint16_t*>(g);
-    if (dt == DP_BF16)
-      hipLaunchKernelGGL(bias_norm_kernel<DP_BF16>, dim3(B), dim3(kOneThreads), 0, s, g16, T, p, colsum, sqnorm_out);
+  if (dt != DP_F32 && one_launch(B, T, p)) {
+    const int need = std::max(std::min(kOneThreads / (p / 8), (T - 1) / kOneRows + 1) * (p / 8), p);
+    auto launch = [&](auto threads_tag) {
+      constexpr int THREADS = decltype(threads_tag)::value;
+      auto kernel = dt == DP_BF16 ? bias_norm_kernel<DP_BF16, THREADS> : bias_norm_kernel<DP_F16, THREADS>;
+      hipLaunchKernelGGL(kernel, dim3(B), dim3(THREADS), 0, s, static_cast<const uint16_t*>(g), T, p, colsum, sqnorm_out);
+    };
+    if (need <= 64)
+      launch(std::integral_constant<int, 64>{});
+    else if (need <= 256)
+      launch(std::integral_constant<int, 256>{});
     else
-      hipLaunchKernelGGL(bias_norm_kernel<DP_F16>, dim3(B), dim3(kOneThreads), 0, s, g16, T, p, colsum, sqnorm_out);
+      launch(std::integral_constant<int, kOneThreads>{});
     return hip_status(hipGetLastError());
   }
   const int cols_per_block = kColThreads * (dt == DP_F32 ? 1 : 8);

@@ -309,7 +309,7 @@ def test_weighted_stream(side, n, B, T, zero):
 @pytest.mark.parametrize("dtype", HALF)
 @pytest.mark.parametrize("B,T,p", [
     (1, 1, 8), (3, 7, 8), (2, 9, 24), (5, 70, 264), (2, 8, 8192), (2, 7, 8200), (3, 160, 512), (3, 161, 512), (2, 700, 256),
-    (2, 700, 264), (1, 4097, 16),
+    (2, 700, 264), (1, 4097, 16), (300, 1, 8), (300, 9, 40), (300, 33, 128), (300, 1, 264), (255, 330, 256), (256, 330, 256),
 ])
 def test_bias_norm_forms(dtype, B, T, p):
     from paper_2311_11822_amd import binding as dp
