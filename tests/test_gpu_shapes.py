@@ -325,12 +325,23 @@ def test_bias_norm_forms(dtype, B, T, p):
 
 
 # One call for a step against its three stages, and factors written by the kernels that finish the norms against the
-# clip kernels: the same bits.  Stacks whose norms end in every kernel (partial sums of one launch, of several and of two
-# kernels, final norms alone), more layers than a launch or a wave's lanes hold, a NaN and a zero sample.
+# clip kernels: the same bits.  Stacks whose norms end in every kernel: partial sums of one launch, of several and of two
+# kernels; final norms (fp32, short samples, 129 to 256 tokens in whole and ragged widths) of few workgroups and layers,
+# which form the factors themselves, of 96 and of sixteen, the most that do, and of more; more layers than a launch or a
+# wave's lanes hold.
 STEP_STACKS = [
     (si.F32, 3, 9, [(16, 24)] * 3, None),
+    (si.F32, 6, 5, [(8, 8)] * 16, None),              # 96 workgroups
+    (si.F32, 7, 5, [(8, 8)] * 14, None),              # 98
+    (si.F32, 1, 5, [(8, 8)] * 17, None),
+    (si.F32, 2, 5, [(8, 8)] * 70, None),
+    (si.F32, 90, 3, [(8, 8)], None),
     (si.BF16, 5, 21, [(64, 72), (128, 136)], None),
-    (si.F16, 77, 5, [(40, 24)] * 9, None),            # 13 and 26 workgroups a layer: two shares, 693 norms added by the last
+    (si.BF16, 40, 7, [(16, 8)] * 2, None),            # 2 x 10 workgroups of four samples, shared by four each
+    (si.F16, 77, 5, [(40, 24)] * 9, None),            # 13 and 26 workgroups a layer
+    (si.BF16, 2, 130, [(64, 128)] * 3, [0] * 3),
+    (si.F16, 32, 256, [(72, 136), (128, 64), (8, 8)], [0] * 3),
+    (si.BF16, 33, 200, [(72, 64)] * 3, [0] * 3),      # 99
     (si.F16, 4, 140, [(136, 264), (264, 72)], [0, 1]),
     (si.BF16, 3, 300, [(72, 136), (136, 200), (16, 200), (136, 136)], [0, 1, 1, 0]),
     (si.BF16, 2, 40, [(64 + 8 * (l % 3), 72) for l in range(103)], [l % 2 for l in range(103)]),
@@ -340,47 +351,75 @@ STEP_STACKS = [
 @pytest.mark.parametrize("dtype,B,T,dims,paths", STEP_STACKS)
 @pytest.mark.parametrize("mode", [o.CLIP_STANDARD, o.CLIP_AUTOMATIC])
 def test_step_in_one_call(dtype, B, T, dims, paths, mode):
+    from paper_2311_11822_amd import binding as dp
     from paper_2311_11822_amd.pipeline import BkPipeline
     w = si.small_workload("step", dtype, B, T, dims, g_std=1.0 if dtype == si.F32 else 1e-2)
     layers = [si.gen_layer(w, l) for l in range(w.L)]
     layers = [(dev(a), dev(g)) for a, g in layers]
-    for a, g in layers:
-        g[0] = 0
-    layers[0][0][B - 1, 0, 0] = float("nan") if layers[0][0].dtype != torch.int16 else 0x7FC0
+    if B > 1:
+        for a, g in layers:
+            g[0] = 0
     pipe = BkPipeline(layers, paths)
     outputs = [pipe.sqnorm, pipe.C, pipe.norm, pipe.flat]
-    pipe.norms()
-    pipe.clip(mode, 0.5, 0.01)
-    pipe.grad_noise(0.7, 0.5, 3, 1, 4, pipe.psi - 8)
-    want = [x.clone() for x in outputs]
-    step = lambda: pipe.step(mode, 0.5, 0.7, 0.01, 3, 1, 4, pipe.psi - 8)
 
-    def check():
-        for got, x in zip(outputs, want):
+    def stages(accumulate=0):
+        pipe.norms()
+        pipe.clip(mode, 0.5, 0.01)
+        pipe.grad_noise(0.7, 0.5, 3, 1, 4, pipe.psi - 8, accumulate)
+        return [x.clone() for x in outputs]
+
+    def call(counter, accumulate=0):
+        dp.dp_private_step_multi(pipe.desc, pipe.dt, pipe.B, mode, 0.5, 0.01, pipe.kept_ptrs if pipe.any_kept else None,
+                                 pipe.grad_ptrs, pipe.grad_offsets, accumulate, 4, pipe.psi - 8, 0.7, 3, 1, pipe.sqnorm,
+                                 pipe.C, pipe.norm, pipe.ws, counter)
+
+    def check(want, which=slice(None)):
+        for got, x in list(zip(outputs, want))[which]:
             assert torch.equal(got.view(torch.int32), x.view(torch.int32))
             got.fill_(123.0)
         assert pipe.counter.item() == 0
     for x in outputs:
         x.fill_(123.0)
+    want = stages()
+    assert all(torch.isfinite(x).all() for x in want) and (want[3][4:-4] != 0).any()
+    for x in outputs:
+        x.fill_(123.0)
     for _ in range(2):                                # the count of finished workgroups is back at zero
-        step()
-        check()
+        pipe.step(mode, 0.5, 0.7, 0.01, 3, 1, 4, pipe.psi - 8)
+        check(want)
+    call(None)
+    check(want)
+    pipe.flat.fill_(0.25)
+    more = stages(accumulate=1)
+    for x in outputs:
+        x.fill_(0.25)
+    call(pipe.counter, accumulate=1)
+    check(more)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
-        step()
+        call(pipe.counter)
     for _ in range(3):
         graph.replay()
-        check()
-        step()                                        # eager work between the replays
-        check()
+        check(want)
+        pipe.step(mode, 0.5, 0.7, 0.01, 3, 1, 4, pipe.psi - 8)      # eager work between the replays
+        check(want)
     # layer-wise
     R = [0.1 + 0.01 * l for l in range(w.L)]
     pipe.set_groups(list(range(w.L)), R)
     pipe.layerwise_step(mode, 0.01, 0.0, 3, 1, 0, 0)
     C = pipe.C_groups.clone()
+    assert torch.isfinite(C).all()
     pipe.C_groups.fill_(123.0)
     pipe.clip_grouped(mode, 0.01)
     assert torch.equal(C.view(torch.int32), pipe.C_groups.view(torch.int32))
+    # a NaN in one sample is that sample's norm and factor, in both
+    layers[0][0][B - 1, 0, 0] = float("nan") if layers[0][0].dtype != torch.int16 else 0x7FC0
+    want = stages()
+    assert torch.isnan(want[1][B - 1]) and torch.isfinite(want[1][:B - 1]).all()
+    for x in outputs:
+        x.fill_(123.0)
+    call(pipe.counter)
+    check(want, slice(0, 3))
 
 
 # A step that is refused has touched none of its outputs.
