@@ -82,7 +82,7 @@ struct PendingReduce {
 
 // For the kernels' arguments, layer-wise thresholds still to be filled in.
 NormClip layer_clip(const ClipSpec* clip) {
-  NormClip nc;
+  NormClip nc = {};
   nc.kind = clip && clip->layer_R ? kLayerFactors : kNoFactors;
   if (!clip) return nc;
   nc.mode = clip->mode;
@@ -474,22 +474,24 @@ dp_status noise_after(const NoiseSpec* noise, int l, const dp_layer& ly, float* 
 }
 
 // Which gradient kernel a 16-bit layer takes.
-//  kGradPacked: short samples.  The large-tile kernels (256 x 256, 128 x 128) pay per sample, ~900 clocks and
-//    ~1400 per begun 32 tokens; the packed one pays per row, three matrix instructions (fp16: six) where they
-//    need one, but its tiles cover a narrow side without padding.  The lines lie where the two meet:
-//      sides             bf16   fp16   gradients of 48 layers 1024 x side, 16384 rows, us: packed / 128 x 128 tiles
-//      up to 32            -     48    fp16 600 at any T / 640 at T = 48, 550 at 56, 390 at 256
-//      33 .. 64            -     28    fp16 840 / 780 at T = 28, 490 at 64, 400 at 256
-//      65 .. 127          48     18    bf16 645-690 / 690 at T = 32, 650 at 48, 420-450 at 256;
-//                                      fp16 1220-1380 / 1370 at T = 16, 1100 at 20
-//      128 and more       20     10    4096 rows of eight layers 1024 x 1024 .. 4096: 566 / 684 at T = 16, 352 at 32
+//  kGradPacked: short samples.  The large-tile kernels (256 x 256, 128 x 128) pay per sample, ~600 clocks and ~700 per
+//    begun 16 tokens; the packed one pays per row, three matrix instructions (fp16: six) where they need one, but its
+//    tiles cover a narrow side without padding, and its error against 64 bits is smaller.  Gradients, us and relative
+//    error (48 layers 1024 x side, 16384 rows; 128 and more: eight layers 1024 x 1024 .. 4096, 4096 rows):
+//      sides           packed below   packed          128 x 128 or larger tiles
+//      up to 32        fp16 48        575, 8.1e-7     823 at T = 16, 529 at 28, 532 at 48; 9 to 11e-7
+//      33 .. 64        fp16 28        810, 8.1e-7     1312 at T = 10, 827 at 16, 732 at 20, 539 at 28; 10 to 13e-7
+//      65 .. 127       bf16 48        630, 8.1e-7     830 at T = 16, 730 at 20, 616 at 24, 507 at 32, 539 at 48; 9 to 11e-7
+//                      fp16 18        1214, 8.1e-7    1640 at T = 8, 1099 at 12, 833 at 16; 10 to 13e-7
+//      128 and more    bf16 20        470, 4.0e-7     645 at T = 8, 443 at 12, 339 at 16, 310 at 20; 5 to 8e-7
+//                      fp16 10        910, 4.0e-7     1261 at T = 4, 850 at 6, 645 at 8, 524 at 10; 6 to 14e-7
+//    The lines are where the times met while the tiles padded a sample to 32 rows.  With 16-row k-steps the tiles are the
+//    faster ones from fewer tokens on, but a size that has had the packed kernel's accuracy keeps it.
 //    A batch of one or two samples pays the other kernels next to nothing: eight layers 4096 x 4096, one token: 141 us
 //    packed, 129 on the tiles (fp16 158 and 131), one layer 72 x 3000 12.5 and 7.1, 24 layers 768 x 3072 64 and 60.
 //    In fp16, sides up to 64 stay packed below 1024 rows of the batch, where the tiles' padding of the side is not paid
 //    for yet: seven layers 6016 x 64, 40 rows 11 us and 20, 918 rows 49 and 70, 1024 rows 53 and 49.
-//    (A layer's kernel depends on nothing but the layer: the same bits in any stack.)
-//    Without the lines (everything with a side below 128 packed) fp16 stacks of 65 .. 127 columns took 1220 us where
-//    the register-staged kernel they came from took 570 .. 600 from 256 tokens on, and bf16 ones 645.
+//    (A layer's kernel depends on nothing but the layer and the batch: the same bits in any stack.)
 //  kGradBig: slabs its 32-bit addressing reaches.
 //  kGradEdge: the rest.
 enum GradKernel { kGradBig = 0, kGradPacked = 1, kGradEdge = 2 };

@@ -7,7 +7,7 @@
 // staging and no barrier sits in the loops.  The eight waves of a workgroup split the contraction (or
 // the tiles) and meet once, in LDS, in a fixed order: no atomics, the same bits every time.
 // Measured on eight layers of width 64..256 (B = 16, T = 48): one thread per output and one launch per
-// layer took 2904 us a step (182 us per gradient, 174 us per norm); this form 31 us: three launches.
+// layer took 2904 us a step (182 us per gradient, 174 us per norm); this form 29 us: norms, clip factors, gradients.
 #include <algorithm>
 
 #include "clip.h"

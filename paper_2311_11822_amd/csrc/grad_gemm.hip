@@ -328,10 +328,11 @@ int64_t clipped_grad_mid_tiles(int d, int p) {
 // Up to kTailMax tiles are cut into 64 x 64: 16 tiles of K = 4096 take 34 us so, 44 us in 128 x 128; 32
 // tiles 43 and 46; 64 tiles 117 and 51 (sub-tiles fetch four times the operand bytes per flop of a
 // large tile, so their kernel runs at the rate the L2 delivers them).
-// Short contractions (rows: 32-token blocks of all samples, in tokens) are bound by the epilogue, which a large tile has
-// a compute unit to itself for: 128 x 128, two to a unit, unless large ones come in whole rounds.  One sample:
-// two layers 3744 x 2352 33.2 us mixed, 24.7 on 128 x 128 (before: 29); 17 of 33 tokens 76 and 69; 16 of 100 104 and
-// 104; four layers 4096 x 4096 (four whole rounds) 62 and 66; 24 of 768 x 3072 64 and 59, three of 40 tokens 79 and 80.
+// Short contractions (rows: of all samples, each rounded up to 32, as these lines were measured) are bound by the
+// epilogue, which a large tile has a compute unit to itself for: 128 x 128, two to a unit, unless large ones come in whole
+// rounds.  One sample: two layers 3744 x 2352 33.2 us mixed, 24.7 on 128 x 128 (before: 29); 17 of 33 tokens 76 and 69;
+// 16 of 100 104 and 104; four layers 4096 x 4096 (four whole rounds) 62 and 66; 24 of 768 x 3072 64 and 59, three of 40
+// tokens 79 and 80.
 GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows) {
   constexpr int kTailMax = 32, kShortRows = 512;
   int tail = n % kBigRound;
