@@ -194,11 +194,19 @@ def measure(name, args, torch, BkPipeline, noise_pass=False):
     torch.cuda.synchronize()
     elapsed = time.perf_counter() - t0
 
-    # The same K steps once more without the per-stage event records: on the small workloads the
-    # four records per step cost more than the launches they separate.
+    # The same K steps once more as a program takes them: without the per-stage event records (on the small
+    # workloads the four records per step cost more than the launches they separate) and, with all-layer clipping, in one call.
+    def plain():
+        if passes or layerwise:
+            step()
+        else:
+            pipe.step(w.clip_mode, w.R, w.sigma, w.stability, w.noise_seed, w.noise_step, off, cnt, fused=fused)
+
+    plain()
+    torch.cuda.synchronize()
     t0 = time.perf_counter()
     for k in range(args.steps):
-        step()
+        plain()
     torch.cuda.synchronize()
     ms_plain = (time.perf_counter() - t0) * 1e3 / args.steps
 
