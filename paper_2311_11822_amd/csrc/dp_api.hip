@@ -129,7 +129,7 @@ int64_t share_brief_samples(GroupArgs& ga) {
     int64_t n = 0;
     bool more = false;
     for (int j = 0; j < ga.n_layers; ++j) {
-      const int most = ghost_brief_max_parts(ga.layer[j].T);
+      const int most = ghost_brief_max_parts(ga.B, ga.layer[j].T);
       more = more || parts < most;
       n += ghost_brief_blocks(ga.B, ga.layer[j].T, std::min(parts, most));
     }
@@ -138,7 +138,7 @@ int64_t share_brief_samples(GroupArgs& ga) {
     n = 0;
     for (int j = 0; j < ga.n_layers; ++j) {
       GroupLayer& gl = ga.layer[j];
-      gl.tiles_per_sample = std::min(parts, ghost_brief_max_parts(gl.T));
+      gl.tiles_per_sample = std::min(parts, ghost_brief_max_parts(ga.B, gl.T));
       gl.tile_begin = (int)n;
       n += ghost_brief_blocks(ga.B, gl.T, gl.tiles_per_sample);
     }

@@ -202,7 +202,7 @@ dp_status launch_ghost_sample_group(const GroupArgs& ga, float* sqnorm, const No
 // ga.layer[j].tiles_per_sample = workgroups to 32 rows, up to ghost_brief_max_parts, tile_begin = first workgroup.
 bool ghost_brief_supports(int T);
 int64_t ghost_brief_blocks(int B, int T, int parts);
-int ghost_brief_max_parts(int T);
+int ghost_brief_max_parts(int B, int T);
 dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s);
 // 256x256-tile kernel with direct global->LDS loads (grad_gemm.hip).
 int clipped_grad_big_tiles(int d, int p);

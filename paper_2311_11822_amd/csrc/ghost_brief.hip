@@ -14,6 +14,8 @@
 // they have in any case, so that the bits do not depend on it: a workgroup of this kernel, which waits for its
 // loads before it multiplies, reads no more than 24 to 30 GB/s.
 // 512 samples of one token, eight layers 1024 x 1024 .. 4096, with 128 and 256 workgroups: 14.1 -> 10.2 us.
+#include <algorithm>
+
 #include "clip.h"
 #include "dp_internal.h"
 
@@ -59,10 +61,11 @@ ghost_brief_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int fir
   // divisions cost 0.1 us: two samples of 32 tokens, 24 layers 128 x 384 5.0 -> 4.8 us, 3000 of ten tokens 18.7 -> 17.9).
   if (parts > 1) {
     const float inv = __builtin_amdgcn_rcpf((float)parts);
-    const int share = (int)(((float)(per + parts - 1) + 0.5f) * inv), local = rows32;
+    const int slots = min(per, ga.B);                                        // of 32 rows that hold a sample
+    const int share = (int)(((float)(slots + parts - 1) + 0.5f) * inv), local = rows32;
     rows32 = (int)(((float)local + 0.5f) * inv);
     begin = (local - rows32 * parts) * share;
-    end = min(begin + share, per);
+    end = min(begin + share, slots);
   }
   const int i0 = rows32 * per;                                               // first sample of the 32 rows
   end = min(end, ga.B - i0);
@@ -118,13 +121,13 @@ ghost_brief_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int fir
 
 bool ghost_brief_supports(int T) { return T <= kRows; }
 
-// Workgroups of a layer, each with one of `parts` shares of the samples that fit the rows.  (A share may be empty.)
+// Workgroups of a layer, each with one of `parts` shares of the samples that fit the rows.  (A share may be empty: of the last rows.)
 int64_t ghost_brief_blocks(int B, int T, int parts) {
   const int per = kRows / T;
   return (int64_t)((B + per - 1) / per) * parts;
 }
 
-int ghost_brief_max_parts(int T) { return kRows / T; }
+int ghost_brief_max_parts(int B, int T) { return std::min(kRows / T, B); }
 
 dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s) {
   return launch_in_runs(ga.total_blocks, [&](dim3 grid, int first) {

@@ -162,7 +162,7 @@ def test_half_gradient_of_short_samples(dtype, T):
 @pytest.mark.parametrize("dtype", HALF)
 @pytest.mark.parametrize("B,T,d,p", [
     (1, 1, 8, 8), (33, 1, 24, 1032), (67, 2, 136, 40), (31, 3, 2056, 64), (7, 16, 72, 200), (3, 17, 264, 88),
-    (2, 32, 1160, 8), (5, 31, 16, 4104), (45, 3, 40, 24), (2600, 3, 16, 8),
+    (2, 32, 1160, 8), (5, 31, 16, 4104), (45, 3, 40, 24), (2600, 3, 16, 8), (5, 1, 40, 24), (3, 2, 264, 16),
 ])
 def test_ghost_norm_of_short_samples(dtype, B, T, d, p):
     from paper_2311_11822_amd import binding as dp
