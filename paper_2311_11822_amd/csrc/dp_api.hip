@@ -92,12 +92,12 @@ NormClip layer_clip(const ClipSpec* clip) {
 }
 
 // The last launch of final norms forms the factors of the one group where that is cheaper than a launch: few workgroups,
-// whose counts are added one after the other, and few layers, which are as many lanes of the last sum.  Against a launch
-// of its own (fp32 and 16-bit layers 16 to 768 wide), us on the GPU and of a step that the host enqueues: one to three
-// layers, up to 64 workgroups 0.1 to 0.8 and 0.4 to 2.5 less; eight to sixteen layers, up to 96 workgroups 0.2 more and
-// 0.5 less (steps of 10 us on the GPU and 13 on the host); 128 workgroups 0.6 more and the same; 32 layers of one sample
-// 0.5 more and 0.4 less, 64 0.4 and 0.3 more.
-constexpr int kLastBlocks = 96, kLastLayers = 16;
+// whose counts are added one after the other, and few layers, which are lanes of the last sum.  Against a launch of its
+// own (fp32 and 16-bit layers 16 to 768 wide), us on the GPU and of a step that the host enqueues: one to eight layers, up
+// to 80 workgroups 0.8 less to 0.2 more and 0.4 to 2.5 less; 16 to 32 layers, up to 64 workgroups 0.3 more and 0.5 less
+// (steps of 11 us on the GPU and 13 on the host); 96 of 16 layers 0.4 more and 0.3 less, of 32 layers 0.7 more and 0.2 less;
+// 128 workgroups 0.6 more and the same; 64 layers of one sample 0.4 and 0.3 more.
+constexpr int kLastCost = 96, kLastLayers = 32;
 int lanes_for(int L) {
   int width = 1;
   while (width < 64 && width < L) width *= 2;
@@ -105,7 +105,7 @@ int lanes_for(int L) {
 }
 
 bool last_forms_factors(const ClipSpec* clip, int64_t blocks, int L, int B) {
-  return clip && !clip->layer_R && clip->counter && blocks <= kLastBlocks && L <= kLastLayers &&
+  return clip && !clip->layer_R && clip->counter && blocks + L <= kLastCost && L <= kLastLayers &&
          (int64_t)B * lanes_for(L) <= kFinishLanes;
 }
 

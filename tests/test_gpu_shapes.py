@@ -327,21 +327,22 @@ def test_bias_norm_forms(dtype, B, T, p):
 # One call for a step against its three stages, and factors written by the kernels that finish the norms against the
 # clip kernels: the same bits.  Stacks whose norms end in every kernel: partial sums of one launch, of several and of two
 # kernels; final norms (fp32, short samples, 129 to 256 tokens in whole and ragged widths) of few workgroups and layers,
-# which form the factors themselves, of 96 and of sixteen, the most that do, and of more; more layers than a launch or a
-# wave's lanes hold.
+# which form the factors themselves, of 96 both together and of 32 layers, the most that do, and of more; more layers than
+# a launch or a wave's lanes hold.
 STEP_STACKS = [
     (si.F32, 3, 9, [(16, 24)] * 3, None),
-    (si.F32, 6, 5, [(8, 8)] * 16, None),              # 96 workgroups
-    (si.F32, 7, 5, [(8, 8)] * 14, None),              # 98
-    (si.F32, 1, 5, [(8, 8)] * 17, None),
+    (si.F32, 5, 5, [(8, 8)] * 16, None),              # 80 workgroups, 16 layers
+    (si.F32, 6, 5, [(8, 8)] * 14, None),              # 84, 14
+    (si.F32, 2, 5, [(8, 8)] * 32, None),
+    (si.F32, 1, 5, [(8, 8)] * 33, None),
     (si.F32, 2, 5, [(8, 8)] * 70, None),
-    (si.F32, 90, 3, [(8, 8)], None),
+    (si.F32, 95, 3, [(8, 8)], None),
     (si.BF16, 5, 21, [(64, 72), (128, 136)], None),
     (si.BF16, 40, 7, [(16, 8)] * 2, None),            # 2 x 10 workgroups of four samples, shared by four each
     (si.F16, 77, 5, [(40, 24)] * 9, None),            # 13 and 26 workgroups a layer
     (si.BF16, 2, 130, [(64, 128)] * 3, [0] * 3),
-    (si.F16, 32, 256, [(72, 136), (128, 64), (8, 8)], [0] * 3),
-    (si.BF16, 33, 200, [(72, 64)] * 3, [0] * 3),      # 99
+    (si.F16, 31, 256, [(72, 136), (128, 64), (8, 8)], [0] * 3),      # 93, 3
+    (si.BF16, 32, 200, [(72, 64)] * 3, [0] * 3),
     (si.F16, 4, 140, [(136, 264), (264, 72)], [0, 1]),
     (si.BF16, 3, 300, [(72, 136), (136, 200), (16, 200), (136, 136)], [0, 1, 1, 0]),
     (si.BF16, 2, 40, [(64 + 8 * (l % 3), 72) for l in range(103)], [l % 2 for l in range(103)]),
