@@ -97,19 +97,16 @@ static_assert(MID_SIDE * MidTile::BM == BM && MID_SIDE * MidTile::BN == BN, "sub
 
 template <bool F16, bool NOISE, bool OUT16>
 __global__ void __launch_bounds__(MidTile::NT, 2)
-clipped_grad_mid_kernel(const GroupArgs ga, const float* __restrict__ C_all, int first_tile, const NoiseArgs na) {
+clipped_grad_mid_kernel(const GroupArgs ga, const float* C_all, int first_tile, const NoiseArgs na) {
   const SubTile sub = grad_sub_tile<MID_SIDE>(blockIdx.x, gridDim.x);
   const int l = layer_of(ga, first_tile + sub.tile);
   const float* C = C_all + ga.layer[l].c_off;
-  const float w = window_weights(C, 0, ga.B);
+  const float w = first_weights(C, ga.B);
   int m0, n0;
   locate_tile(ga, l, first_tile + sub.tile, m0, n0);
   m0 += sub.row * MidTile::BM;
   n0 += sub.col * MidTile::BN;
-  if (m0 >= ga.layer[l].d_in || n0 >= ga.layer[l].d_out) {            // past the layer's edge (whole workgroup)
-    asm volatile("" ::"v"(w));                                        // keeps the load of w above this branch
-    return;
-  }
+  if (m0 >= ga.layer[l].d_in || n0 >= ga.layer[l].d_out) return;      // past the layer's edge (whole workgroup)
   gradient_tile<MidTile, F16, NOISE, OUT16>(ga, l, m0, n0, C, w, na);
 }
 

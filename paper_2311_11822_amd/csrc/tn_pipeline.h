@@ -111,10 +111,17 @@ __device__ __forceinline__ void scale_if(unsigned turn, unsigned f, f32x16 (&c)[
 }
 #undef DP_SCALE_TUPLES
 
-// Weights of the samples window .. window + 63, one a lane; 0 from sample B on.
+// Weights of the samples window .. window + 63, one a lane; lanes from sample B on: not to be used.
 __device__ __forceinline__ float window_weights(const float* C, unsigned window, int B) {
   const auto r = __builtin_amdgcn_make_buffer_rsrc((void*)(C + window), 0, 4 * min(B - (int)window, 64), 0x00020000);
   return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, 4 * (threadIdx.x & 63), 0, 0));
+}
+
+// Those of the first window by a load that the compiler leaves above what follows, branches too.
+__device__ __forceinline__ float first_weights(const float* C, int B) {
+  const float w = C[min(threadIdx.x & 63, (unsigned)B - 1)];
+  asm volatile("" ::: "memory");
+  return w;
 }
 
 // Samples [0, B) of the layer (one, `sample`, unless WEIGHTED) into `acc` (zeroed here); returns the weight the sum is
@@ -292,7 +299,7 @@ __device__ __forceinline__ float tn_contract(const void* a, const void* g, int T
     // from one to the next is a few scalar instructions between matrix instructions.
     for (unsigned window = 0; window < (unsigned)B; window += 64) {
       if (window > 0) w = window_weights(C, window, B);
-      uint64_t mask = __ballot(w != 0.f);
+      uint64_t mask = __ballot(w != 0.f && window + lane < (unsigned)B);
       if (mask == 0) continue;
       if (held != 0.f) __syncthreads();                  // the last window's fragments are read
       const int first = __builtin_ctzll(mask);
