@@ -1,6 +1,8 @@
 // Clip factors (section 2.1 of the paper) as the kernels that finish a norm form them.
 #pragma once
 
+#include <type_traits>
+
 #include "dp_internal.h"
 
 namespace dpbk {
@@ -45,12 +47,12 @@ __device__ __forceinline__ void store_norm(const GroupArgs& ga, const NormClip& 
 
 // End of every workgroup of a kernel that stores final norms, all of them from its first wave: kGroupFactors.  The norms
 // are stored past the caches that another workgroup does not share and are complete before the count, whose
-// last reader adds them up, nc.width lanes to a sample (all samples at one time), in the order of the clip kernel: the
-// same bits.  (With fences in their place, which write back and drop the whole cache, it took 1 to 2 us longer.)  lds: a
+// last reader adds them up, nc.width lanes to a sample (all samples at one time, a lane up to eight of them), in the order
+// of the clip kernel: the same bits.  (With fences in their place, which write back and drop the whole cache, it took 1 to 2 us longer.)  lds: a
 // word of the workgroup's LDS.
 template <int THREADS>
 __device__ __forceinline__ void finish_norms(const GroupArgs& ga, const NormClip& nc, const float* sqnorm, unsigned* lds) {
-  static_assert(THREADS >= kFinishLanes, "all samples at one time");
+  static_assert(8 * THREADS >= kFinishLanes, "all samples at one time");
   if (nc.kind != kGroupFactors) return;
   __syncthreads();                                     // nobody reads that word any more
   if (threadIdx.x < 64) {
@@ -60,16 +62,36 @@ __device__ __forceinline__ void finish_norms(const GroupArgs& ga, const NormClip
   }
   __syncthreads();
   if (*lds != nc.blocks - 1) return;
-  const int i = threadIdx.x / nc.width, l = threadIdx.x & (nc.width - 1);
-  if (i < ga.B) {                                      // the same for all of a sample's lanes
-    float total = l < nc.L ? __hip_atomic_load(&sqnorm[(size_t)l * ga.B + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
-    for (int off = nc.width / 2; off > 0; off >>= 1) total += __shfl_xor(total, off);
-    const float norm = norm_of(total);
-    if (l == 0) {
-      nc.C_out[i] = clip_factor(norm, nc.mode, nc.R[0], nc.stability);
-      if (nc.norm_out) nc.norm_out[i] = norm;
+  const int width = nc.width, sub = threadIdx.x & (width - 1), i0 = threadIdx.x / width, stride = THREADS / width;
+  auto add_up = [&](auto n) {                          // samples i0, i0 + stride, ..., n of them in flight
+    constexpr int N = decltype(n)::value;
+    float total[N] = {};
+    for (int l = sub; l < nc.L; l += 64) {             // more than once for 64 lanes only
+      float v[N];
+#pragma unroll
+      for (int q = 0; q < N; ++q) {
+        const int i = i0 + q * stride;
+        v[q] = i < ga.B ? __hip_atomic_load(&sqnorm[(size_t)l * ga.B + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
+      }
+#pragma unroll
+      for (int q = 0; q < N; ++q) total[q] += v[q];
     }
-  }
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      const int i = i0 + q * stride;
+      if (i >= ga.B) break;                            // of all the sample's lanes
+      for (int off = width / 2; off > 0; off >>= 1) total[q] += __shfl_xor(total[q], off);
+      const float norm = norm_of(total[q]);
+      if (sub == 0) {
+        nc.C_out[i] = clip_factor(norm, nc.mode, nc.R[0], nc.stability);
+        if (nc.norm_out) nc.norm_out[i] = norm;
+      }
+    }
+  };
+  if (ga.B <= stride)
+    add_up(std::integral_constant<int, 1>{});
+  else
+    add_up(std::integral_constant<int, 8>{});
   if (threadIdx.x == 0) *nc.counter = 0;
 }
 

@@ -91,22 +91,37 @@ NormClip layer_clip(const ClipSpec* clip) {
   return nc;
 }
 
-// The last launch of final norms forms the factors of the one group where that is cheaper than a launch: few workgroups,
-// whose counts are added one after the other, and few layers, which are lanes of the last sum.  Against a launch of its
-// own (fp32 and 16-bit layers 16 to 768 wide), us on the GPU and of a step that the host enqueues: one to eight layers, up
-// to 80 workgroups 0.8 less to 0.2 more and 0.4 to 2.5 less; 16 to 32 layers, up to 64 workgroups 0.3 more and 0.5 less
-// (steps of 11 us on the GPU and 13 on the host); 96 of 16 layers 0.4 more and 0.3 less, of 32 layers 0.7 more and 0.2 less;
-// 128 workgroups 0.6 more and the same; 64 layers of one sample 0.4 and 0.3 more.
-constexpr int kLastCost = 96, kLastLayers = 32;
+// The last launch of final norms forms the factors of the one group where that is cheaper than a launch.  A launch costs the
+// host 3 us of a step; the count, workgroups after each other in one cell, costs the GPU from 0.1 us at 100 to 1.9 at 250
+// workgroups more than the launch.  So: few workgroups and layers, or a step so small that the host bounds it (it takes
+// 20 us from Python).  A step, us, factors here and in a launch.  Below the line: seven fp32 layers 16 x 16 of 14 x 39 tokens
+// 18.6 and 23.1, twelve bf16 64 x 64 of 10 x 32 20.7 and 23.6, 24 fp16 384 x 32 of 7 x 32 (5.7 MB) 20.9 and 23.7, 22 bf16
+// 64 x 32 of 8 x 24 20.2 and 23.5; at its worst eight fp32 58 x 58 of 17 x 35 31.8 and 31.5.  Above it: eleven bf16
+// 256 x 256 of 17 x 17 (6.1 MB) 27.3 and 25.9, 22 fp16 696 x 48 of 11 x 32 28.2 and 26.5, four bf16 128 x 40 of 56 x 31
+// (2.4 MB, but a chain of 1736 rows) 45.8 and 44.1, nine fp16 112 x 112 of 16 x 23 (twice the matrix instructions a row)
+// 25.2 and 24.5.  fp32 layers take longer for a byte: four 76 to 304 wide of 25 x 18 (2.5 MB) 21.9 and 23.3.
+constexpr int kLastCost = 96, kLastBlocks = 256, kLastLayers = 256;
 int lanes_for(int L) {
   int width = 1;
   while (width < 64 && width < L) width *= 2;
   return width;
 }
 
-bool last_forms_factors(const ClipSpec* clip, int64_t blocks, int L, int B) {
-  return clip && !clip->layer_R && clip->counter && blocks + L <= kLastCost && L <= kLastLayers &&
-         (int64_t)B * lanes_for(L) <= kFinishLanes;
+bool host_bounds_step(const dp_layer* layers, int L, dp_dtype dt, int B) {
+  const int64_t size = dt == DP_F32 ? 4 : 2, most_bytes = dt == DP_F32 ? 3000000 : 6000000;
+  const int64_t most_rows = dt == DP_F32 ? 1024 : dt == DP_BF16 ? 512 : 256;
+  int64_t bytes = 0;
+  for (int l = 0; l < L && bytes <= most_bytes; ++l) {
+    const int64_t rows = (int64_t)B * layers[l].T, d = layers[l].d_in, p = layers[l].d_out;
+    if (rows > most_rows || d > most_bytes || p > most_bytes) return false;      // the sums below stay far from 2^63
+    bytes += rows * (d + p) * size + 4 * d * p;
+  }
+  return bytes <= most_bytes;
+}
+
+bool last_forms_factors(const ClipSpec* clip, int64_t blocks, const dp_layer* layers, int L, dp_dtype dt, int B) {
+  return clip && !clip->layer_R && clip->counter && blocks <= kLastBlocks && L <= kLastLayers &&
+         (int64_t)B * lanes_for(L) <= kFinishLanes && (blocks + L <= kLastCost || host_bounds_step(layers, L, dt, B));
 }
 
 void set_group_factors(NormClip& nc, const ClipSpec& clip, int64_t blocks, int L) {
@@ -199,7 +214,7 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
     if (kernel == kGhostBrief) blocks = share_brief_samples(ga);
     ga.total_blocks = (int)blocks;
     if (kernel == kGhostBrief || kernel == kGhostSample) {       // final norms: nothing to add up
-      if (last_rows && begin + kMaxGroup >= n_which && last_forms_factors(clip, blocks, last_rows, B)) {
+      if (last_rows && begin + kMaxGroup >= n_which && last_forms_factors(clip, blocks, layers, last_rows, dt, B)) {
         set_group_factors(nc, *clip, blocks, last_rows);
         *formed = true;
       }
@@ -316,7 +331,7 @@ dp_status norms_impl(const dp_layer* layers, int L, dp_dtype dt, int B, float* s
         if (nc.kind == kLayerFactors) nc.R[j] = clip->layer_R[l0 + j];
       }
       ga.total_blocks = ga.n_layers * B;
-      if (l0 + per_launch >= L && last_forms_factors(clip, ga.total_blocks, L, B)) {
+      if (l0 + per_launch >= L && last_forms_factors(clip, ga.total_blocks, layers, L, dt, B)) {
         set_group_factors(nc, *clip, ga.total_blocks, L);
         formed = true;
       }

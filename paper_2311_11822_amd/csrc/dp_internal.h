@@ -74,7 +74,7 @@ struct NoiseArgs {
 //    C_out as large as the whole stack's norms).
 //  kGroupFactors: one group of all L rows of the call: the workgroup that ends last (of `blocks`, counted in
 //    *counter, which is zero before and after) adds the rows up and writes C_out[B] and norm_out[B] (or nullptr).
-constexpr int kFinishLanes = 512;      // kGroupFactors: B * width at most
+constexpr int kFinishLanes = 4096;     // kGroupFactors: B * width at most
 enum ClipKind { kNoFactors = 0, kLayerFactors = 1, kGroupFactors = 2 };
 struct NormClip {
   int kind;
@@ -84,7 +84,7 @@ struct NormClip {
   float* norm_out;
   unsigned* counter;
   unsigned blocks;
-  int L, width;                 // width: lanes to a sample, a power of two up to 64 and no less than L
+  int L, width;                 // width: lanes to a sample, a power of two, 64 or no less than L
   float R[kMaxGroup];           // kGroupFactors: R[0]
 };
 

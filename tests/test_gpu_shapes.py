@@ -326,9 +326,9 @@ def test_bias_norm_forms(dtype, B, T, p):
 
 # One call for a step against its three stages, and factors written by the kernels that finish the norms against the
 # clip kernels: the same bits.  Stacks whose norms end in every kernel: partial sums of one launch, of several and of two
-# kernels; final norms (fp32, short samples, 129 to 256 tokens in whole and ragged widths) of few workgroups and layers,
-# which form the factors themselves, of 96 both together and of 32 layers, the most that do, and of more; more layers than
-# a launch or a wave's lanes hold.
+# kernels; final norms (fp32, short samples, 129 to 256 tokens in whole and ragged widths) of few workgroups and layers, and of
+# many in small steps (up to 256 workgroups, 4096 lanes of norms, more layers than a wave's lanes), which form the factors
+# themselves, and of larger steps, which do not; more layers than a launch holds.
 STEP_STACKS = [
     (si.F32, 3, 9, [(16, 24)] * 3, None),
     (si.F32, 5, 5, [(8, 8)] * 16, None),              # 80 workgroups, 16 layers
@@ -337,6 +337,15 @@ STEP_STACKS = [
     (si.F32, 1, 5, [(8, 8)] * 33, None),
     (si.F32, 2, 5, [(8, 8)] * 70, None),
     (si.F32, 95, 3, [(8, 8)], None),
+    (si.F32, 256, 3, [(8, 8)], None),                 # 256 workgroups
+    (si.F32, 257, 3, [(8, 8)], None),
+    (si.F32, 3, 5, [(8, 8)] * 70, None),              # 210 workgroups, lanes of two layers
+    (si.F16, 60, 2, [(64, 64)] * 36, None),           # 3840 lanes of norms: eight samples a lane
+    (si.BF16, 65, 2, [(64, 64)] * 36, None),          # 4160
+    (si.BF16, 7, 8, [(256, 512)] * 9, None),          # 5.0 MB
+    (si.BF16, 7, 8, [(256, 512)] * 11, None),         # 6.1 MB
+    (si.BF16, 16, 32, [(16, 8)] * 9, None),           # 512 rows, the most that do
+    (si.BF16, 17, 32, [(16, 8)] * 9, None),
     (si.BF16, 5, 21, [(64, 72), (128, 136)], None),
     (si.BF16, 40, 7, [(16, 8)] * 2, None),            # 2 x 10 workgroups of four samples, shared by four each
     (si.F16, 77, 5, [(40, 24)] * 9, None),            # 13 and 26 workgroups a layer
