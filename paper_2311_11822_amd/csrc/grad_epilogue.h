@@ -100,18 +100,29 @@ __device__ __forceinline__ void tile_noise(float (&v)[16], const TileNoise& na, 
   const uint64_t e_last = na.layer_off + (uint64_t)(tile_row0 + rows - 1) * p + (tile_col0 + cols - 1);
   if (e_last < na.lo || e_first >= na.hi) return;               // wave-uniform: tile outside the shard
   const bool whole = e_first >= na.lo && e_last < na.hi;
-  const int row = tile_row0 + (lane & 31);
+  // The four blocks side by side, and all of them before the test of the shard's ends, into which the compiler would move
+  // the chains one by one.  (Lanes past the layer's edge draw values that are not stored.)
+  const uint64_t e = na.layer_off + (uint64_t)(tile_row0 + (lane & 31)) * p + (tile_col0 + 4 * (lane >> 5));
+  const uint64_t block[4] = {e >> 2, (e >> 2) + 2, (e >> 2) + 4, (e >> 2) + 6};
+  float z[4][4];
+  normal_blocks(block, na.step_lo, na.step_hi, na.rk, z);
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int col = tile_col0 + 8 * q + 4 * (lane >> 5);
-    if (row < d && col < p) {
-      const uint64_t e = na.layer_off + (uint64_t)row * p + col;
-      float z[4];
-      normal_block(e >> 2, na.step_lo, na.step_hi, na.rk, z);
+  for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (whole || (e + k >= na.lo && e + k < na.hi)) v[4 * q + k] = fmaf(na.stddev, z[k], v[4 * q + k]);
-    }
+    for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(z[q][k]));
+  if (whole) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[4 * q + k] = fmaf(na.stddev, z[q][k], v[4 * q + k]);
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint64_t at = e + 8 * q + k;
+        if (at >= na.lo && at < na.hi) v[4 * q + k] = fmaf(na.stddev, z[q][k], v[4 * q + k]);
+      }
   }
 }
 
