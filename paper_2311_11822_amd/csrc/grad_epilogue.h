@@ -7,6 +7,7 @@
 namespace dpbk {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4v;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4v;
 
 // 16-bit gradient output (mixed-precision training keeps gradients in the storage type of the
 // activations: section 2.3 of the paper): the fp32 value - weighted sum, old value when
@@ -29,36 +30,7 @@ __device__ __forceinline__ float from_half_bits(uint16_t h) {
     return __uint_as_float((uint32_t)h << 16);
 }
 
-// Four consecutive outputs of one row: (+)= and store, fp32 (16 bytes) or 16-bit (8 bytes).
-template <bool F16, bool OUT16, bool ACCUMULATE>
-__device__ __forceinline__ void load_old4(const float* out32, size_t index, float (&old)[4]) {
-  if constexpr (!ACCUMULATE) {
-    old[0] = old[1] = old[2] = old[3] = 0.f;
-  } else if constexpr (OUT16) {
-    const uint2 w = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(out32) + index);
-    old[0] = from_half_bits<F16>((uint16_t)(w.x & 0xFFFFu));
-    old[1] = from_half_bits<F16>((uint16_t)(w.x >> 16));
-    old[2] = from_half_bits<F16>((uint16_t)(w.y & 0xFFFFu));
-    old[3] = from_half_bits<F16>((uint16_t)(w.y >> 16));
-  } else {
-    const f32x4v w = *reinterpret_cast<const f32x4v*>(out32 + index);
-    old[0] = w[0]; old[1] = w[1]; old[2] = w[2]; old[3] = w[3];
-  }
-}
-template <bool F16, bool OUT16>
-__device__ __forceinline__ void store4(float* out32, size_t index, const float* v) {
-  if constexpr (OUT16) {
-    uint2 w;
-    w.x = (uint32_t)to_half_bits<F16>(v[0]) | ((uint32_t)to_half_bits<F16>(v[1]) << 16);
-    w.y = (uint32_t)to_half_bits<F16>(v[2]) | ((uint32_t)to_half_bits<F16>(v[3]) << 16);
-    *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out32) + index) = w;
-  } else {
-    const f32x4v w = {v[0], v[1], v[2], v[3]};
-    *reinterpret_cast<f32x4v*>(out32 + index) = w;
-  }
-}
-
-// The kernel's copy of what tile_noise needs, read once from the kernel arguments into registers.
+// The kernel's copy of what the noise needs, read once from the kernel arguments into registers.
 struct TileNoise {
   float stddev;
   uint32_t step_lo, step_hi;
@@ -82,47 +54,124 @@ __device__ __forceinline__ TileNoise load_tile_noise(const NoiseArgs& na, int la
   return t;
 }
 
-// Output layout.  The MFMAs take the g fragment as first operand and the a fragment as second,
-// so a wave holds the transposed product: lane l has row (l & 31) of a 32 x 32 output tile and
-// the columns 8 q + 4 (l >> 5) + e (q, e = 0 .. 3) in register 4 q + e: four runs of four
-// consecutive columns, which are stored as 16-byte vectors (a quarter of the store
-// instructions of the untransposed layout, whose lanes hold single columns) and each of which
-// is exactly one block of the noise generator.
+// Output of one wave: NY 32 x 32 tiles side by side, 32 rows of 32 NY columns.
 //
-// Adds the noise of eq. (1) to the lane's 16 values of the tile at (tile_row0, tile_col0): same
-// values as the separate noise pass, which indexes the generator by global element too.
-// Requires layer_off and d_out to be multiples of 4.
-__device__ __forceinline__ void tile_noise(float (&v)[16], const TileNoise& na, int tile_row0, int tile_col0,
-                                           int d, int p, int lane) {
-  const int rows = min(32, d - tile_row0), cols = min(32, p - tile_col0);
-  if (rows <= 0 || cols <= 0) return;
-  const uint64_t e_first = na.layer_off + (uint64_t)tile_row0 * p + tile_col0;
-  const uint64_t e_last = na.layer_off + (uint64_t)(tile_row0 + rows - 1) * p + (tile_col0 + cols - 1);
-  if (e_last < na.lo || e_first >= na.hi) return;               // wave-uniform: tile outside the shard
-  const bool whole = e_first >= na.lo && e_last < na.hi;
-  // The four blocks side by side, and all of them before the test of the shard's ends, into which the compiler would move
-  // the chains one by one.  (Lanes past the layer's edge draw values that are not stored.)
-  const uint64_t e = na.layer_off + (uint64_t)(tile_row0 + (lane & 31)) * p + (tile_col0 + 4 * (lane >> 5));
-  const uint64_t block[4] = {e >> 2, (e >> 2) + 2, (e >> 2) + 4, (e >> 2) + 6};
-  float z[4][4];
-  normal_blocks(block, na.step_lo, na.step_hi, na.rk, z);
+// The MFMAs take the g fragment as first operand and the a fragment as second, so a wave holds the transposed product:
+// lane l has row (l & 31) of a tile and the columns 8 q + 4 (l >> 5) + e (q, e = 0 .. 3) in register 4 q + e.  Stored from
+// there, an instruction touches 32 rows, 32 bytes of each (16-bit output: 16), and L2 takes four (eight) requests for a line:
+// that many requests, not the bytes, were the bound of short contractions (104 M elements of fp32: 13 M requests of 32
+// bytes, 3.3 M lines).  So the values go through LDS, a region of the wave's own, and every store instruction writes whole
+// rows of the wave's piece, 16 bytes a lane.  Steps, us, from the registers and through LDS: 2 x 32 tokens, 44 layers of width
+// 1344 stored in 16 bits 290, 255; 2 x 32, 44 of width 1488 in fp32 355, 312; 18 tokens of 3 samples, 48 of width 320 40, 34;
+// 4096 tokens, 144 of width 1280 7.31, 7.36 ms.  (Streaming stores of the registers' 32-byte pieces, which pass L2 by, took
+// four times as long.)
+template <int NY>
+struct WaveRows {
+  static constexpr int W = 32 * NY;
+  static constexpr int STRIDE = 4 * W + 16;            // bytes of a row: 16 of them begin in different banks
+  static constexpr int BYTES = 32 * STRIDE;
+};
+
+// acc * held (+ old value) (+ noise of eq. (1)) -> out, in fp32 or the operands' 16-bit type; lds: the wave's WaveRows::BYTES.
+// Noise: same values as the separate pass, which indexes the generator by global element too; requires layer_off and d_out
+// to be multiples of 4, as a lane's four columns are one block of the generator.
+template <int NY, bool F16, bool NOISE, bool OUT16, bool ACCUMULATE>
+__device__ __forceinline__ void store_rows(const f32x16* acc, float held, unsigned lds, float* out32, int row0, int col0,
+                                           int d, int p, const TileNoise& na, int lane) {
+  using R = WaveRows<NY>;
+  typedef __attribute__((address_space(3))) f32x4v lds_f4;
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
+  for (int y = 0; y < NY; ++y)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(z[q][k]));
-  if (whole) {
+    for (int q = 0; q < 4; ++q) {
+      const f32x4v w = {acc[y][4 * q] * held, acc[y][4 * q + 1] * held, acc[y][4 * q + 2] * held, acc[y][4 * q + 3] * held};
+      *(lds_f4*)(uintptr_t)(lds + (lane & 31) * R::STRIDE + (32 * y + 8 * q + 4 * (lane >> 5)) * 4) = w;
+    }
+  bool noisy = false, whole = false;
+  if constexpr (NOISE) {
+    const int rows = min(32, d - row0), cols = min(R::W, p - col0);
+    const uint64_t e_first = na.layer_off + (uint64_t)row0 * p + col0;
+    const uint64_t e_last = na.layer_off + (uint64_t)(row0 + rows - 1) * p + (col0 + cols - 1);
+    noisy = rows > 0 && cols > 0 && e_last >= na.lo && e_first < na.hi;              // wave-uniform
+    whole = e_first >= na.lo && e_last < na.hi;
+  }
+  constexpr int VEC = OUT16 ? 8 : 4, LANES = R::W / VEC, ROWS = 64 / LANES, N = 32 / ROWS;      // N instructions of ROWS rows
+  constexpr int BLOCKS = VEC / 4, U = 4 / BLOCKS;                                     // U at a time: four generator blocks
+  static_assert(N % U == 0, "whole groups");
+  const int row = row0 + lane / LANES, col = col0 + lane % LANES * VEC;
+  const unsigned from = lds + lane / LANES * R::STRIDE + lane % LANES * VEC * 4;
+  const size_t at = (size_t)row * p + col, step = (size_t)ROWS * p;      // the lane's first element; from one to the next
+  float v[N][VEC];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+  for (int n = 0; n < N; ++n)
 #pragma unroll
-      for (int k = 0; k < 4; ++k) v[4 * q + k] = fmaf(na.stddev, z[q][k], v[4 * q + k]);
-  } else {
+    for (int b = 0; b < BLOCKS; ++b) {
+      const f32x4v w = *(const lds_f4*)(uintptr_t)(from + n * ROWS * R::STRIDE + 16 * b);
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+      for (int k = 0; k < 4; ++k) v[n][4 * b + k] = w[k];
+    }
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const uint64_t at = e + 8 * q + k;
-        if (at >= na.lo && at < na.hi) v[4 * q + k] = fmaf(na.stddev, z[q][k], v[4 * q + k]);
+  for (int n = 0; n < N; n += U) {
+    if constexpr (ACCUMULATE) {
+#pragma unroll
+      for (int u = n; u < n + U; ++u)
+        if (row + u * ROWS < d && col < p) {
+          if constexpr (OUT16) {
+            const u32x4v w = *reinterpret_cast<const u32x4v*>(reinterpret_cast<const uint16_t*>(out32) + at + u * step);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              v[u][2 * k] = from_half_bits<F16>((uint16_t)(w[k] & 0xFFFFu)) + v[u][2 * k];
+              v[u][2 * k + 1] = from_half_bits<F16>((uint16_t)(w[k] >> 16)) + v[u][2 * k + 1];
+            }
+          } else {
+            const f32x4v w = *reinterpret_cast<const f32x4v*>(out32 + at + u * step);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[u][k] = w[k] + v[u][k];
+          }
+        }
+    }
+    if (NOISE && noisy) {
+      // The four blocks side by side, and all of them before the test of the shard's ends, into which the compiler would
+      // move the chains one by one.  (Lanes past the layer's edge draw values that are not stored.)
+      const uint64_t e = na.layer_off + at + n * step;
+      uint64_t block[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) block[q] = ((e + q / BLOCKS * step) >> 2) + q % BLOCKS;
+      float z[4][4];
+      normal_blocks(block, na.step_lo, na.step_hi, na.rk, z);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(z[q][k]));
+      if (whole) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int k = 0; k < VEC; ++k) v[n + u][k] = fmaf(na.stddev, z[u * BLOCKS + k / 4][k % 4], v[n + u][k]);
+      } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int k = 0; k < VEC; ++k)
+            if (e + u * step + k >= na.lo && e + u * step + k < na.hi)
+              v[n + u][k] = fmaf(na.stddev, z[u * BLOCKS + k / 4][k % 4], v[n + u][k]);
       }
+    }
+#pragma unroll
+    for (int u = n; u < n + U; ++u)
+      if (row + u * ROWS < d && col < p) {
+        if constexpr (OUT16) {
+          u32x4v w;
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            w[k] = (uint32_t)to_half_bits<F16>(v[u][2 * k]) | ((uint32_t)to_half_bits<F16>(v[u][2 * k + 1]) << 16);
+          *reinterpret_cast<u32x4v*>(reinterpret_cast<uint16_t*>(out32) + at + u * step) = w;
+        } else {
+          const f32x4v w = {v[u][0], v[u][1], v[u][2], v[u][3]};
+          *reinterpret_cast<f32x4v*>(out32 + at + u * step) = w;
+        }
+      }
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 

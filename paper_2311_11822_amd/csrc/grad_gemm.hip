@@ -36,39 +36,19 @@ __device__ __forceinline__ void gradient_tile(const GroupArgs& ga, int l, int m0
   const float held = tn_contract<S, F16, true>(ly.a, ly.g, ly.T, d, p, 0, ga.B, C, w, m0, n0,
                                                (unsigned)(uintptr_t)lds_raw, acc);
 
-  // epilogue: grad (+)= held * acc (+ noise), in the transposed layout described at tile_noise.
-  // With no active sample the accumulator is zero.
+  // epilogue: grad (+)= held * acc (+ noise).  With no active sample the accumulator is zero.
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int wm = (wave / S::WN) * S::WTM, wn = (wave % S::WN) * S::WTN;
-  float* out = ly.out;
+  static_assert(WaveRows<S::TN>::BYTES * S::WM * S::WN <= S::LDS_BYTES, "a region for each wave");
+  const unsigned region = (unsigned)(uintptr_t)lds_raw + wave * WaveRows<S::TN>::BYTES;
   TileNoise tn = {};
   if (NOISE) tn = load_tile_noise(na, l);
+  __syncthreads();                                     // the last fragments are read
   auto store_tile = [&](auto acc_tag) {
-    constexpr bool accumulate = decltype(acc_tag)::value;
 #pragma unroll
     for (int x = 0; x < S::TM; ++x)
-#pragma unroll
-      for (int y = 0; y < S::TN; ++y) {
-        const int row = m0 + wm + x * 32 + (lane & 31);
-        const int col0 = n0 + wn + y * 32 + 4 * (lane >> 5);
-        const size_t base = (size_t)row * p + col0;                  // + 8 q: columns col0 + 8 q ..
-        float v[16];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          float old[4] = {0.f, 0.f, 0.f, 0.f};
-          if (accumulate && row < d && col0 + 8 * q < p) load_old4<F16, OUT16, accumulate>(out, base + 8 * q, old);
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const float t = acc[x][y][4 * q + k] * held;
-            v[4 * q + k] = accumulate ? old[k] + t : t;
-          }
-        }
-        if (NOISE) tile_noise(v, tn, m0 + wm + x * 32, n0 + wn + y * 32, d, p, lane);
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (row < d && col0 + 8 * q < p) store4<F16, OUT16>(out, base + 8 * q, v + 4 * q);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      store_rows<S::TN, F16, NOISE, OUT16, decltype(acc_tag)::value>(acc[x], held, region, ly.out, m0 + wm + x * 32, n0 + wn,
+                                                                     d, p, tn, lane);
   };
   if (ga.accumulate)
     store_tile(std::true_type{});
@@ -258,25 +238,15 @@ __device__ __forceinline__ void clipped_grad_tile_deep(const GroupLayer& ly, int
     }
   }
 
-  // epilogue in the transposed layout described at tile_noise
-  float* out = ly.out;
-  const int row = m0 + wm + (lane & 31), col0 = n0 + wn + 4 * (lane >> 5);
-  const size_t base = (size_t)row * p + col0;
-  float v[16];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    float old[4] = {0.f, 0.f, 0.f, 0.f};
-    if (accumulate && row < d && col0 + 8 * q < p) load_old4<F16, OUT16, true>(out, base + 8 * q, old);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float t = acc[0][0][4 * q + k] * held;
-      v[4 * q + k] = accumulate ? old[k] + t : t;
-    }
-  }
-  if (NOISE) tile_noise(v, load_tile_noise(na, layer), m0 + wm, n0 + wn, d, p, lane);
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (row < d && col0 + 8 * q < p) store4<F16, OUT16>(out, base + 8 * q, v + 4 * q);
+  // epilogue; everyone is past the loop's last barrier
+  static_assert(WaveRows<1>::BYTES * 4 <= S::LDS_BYTES, "a region for each wave");
+  const unsigned region = (unsigned)(uintptr_t)lds + wave * WaveRows<1>::BYTES;
+  TileNoise tn = {};
+  if (NOISE) tn = load_tile_noise(na, layer);
+  if (accumulate)
+    store_rows<1, F16, NOISE, OUT16, true>(acc[0], held, region, ly.out, m0 + wm, n0 + wn, d, p, tn, lane);
+  else
+    store_rows<1, F16, NOISE, OUT16, false>(acc[0], held, region, ly.out, m0 + wm, n0 + wn, d, p, tn, lane);
 }
 
 // Sub-tiles are 64 x 64 (16 per tile), k-blocks of 64 rows, four k-blocks in flight: three

@@ -327,29 +327,21 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
       stage = stage + 1 == NSTAGE ? 0 : stage + 1;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // zero-fill loads past the end
+    __syncthreads();
   }
 
-  // epilogue in the transposed layout described at tile_noise
+  // epilogue; nobody reads a stage any more
   TileNoise tn = {};
   if (NOISE) tn = load_tile_noise(na, layer);
-  float* out = ly.out;
-  const int row = m0 + wm + (lane & 31);
+  constexpr int NY = S::TN < 2 ? 1 : 2;
+  static_assert(WaveRows<NY>::BYTES * 4 <= NSTAGE * S::STAGE_BYTES, "a region for each wave");
+  const unsigned region = lds0 + wave * WaveRows<NY>::BYTES;
 #pragma unroll
-  for (int y = 0; y < S::TN; ++y) {
-    const int col0 = n0 + wn + 32 * y + 4 * (lane >> 5);
-    const size_t base = (size_t)row * p + col0;
-    float v[16];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      float old[4] = {0.f, 0.f, 0.f, 0.f};
-      if (accumulate && row < d && col0 + 8 * q < p) load_old4<F16, false, true>(out, base + 8 * q, old);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) v[4 * q + k] = accumulate ? old[k] + acc[y][4 * q + k] : acc[y][4 * q + k];
-    }
-    if (NOISE) tile_noise(v, tn, m0 + wm, n0 + wn + 32 * y, d, p, lane);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (row < d && col0 + 8 * q < p) store4<F16, false>(out, base + 8 * q, v + 4 * q);
+  for (int y = 0; y < S::TN; y += NY) {
+    if (accumulate)
+      store_rows<NY, F16, NOISE, false, true>(acc + y, 1.f, region, ly.out, m0 + wm, n0 + wn + 32 * y, d, p, tn, lane);
+    else
+      store_rows<NY, F16, NOISE, false, false>(acc + y, 1.f, region, ly.out, m0 + wm, n0 + wn + 32 * y, d, p, tn, lane);
   }
 }
 
