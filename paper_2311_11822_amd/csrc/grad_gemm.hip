@@ -75,8 +75,8 @@ clipped_grad_big_kernel(const GroupArgs ga, const float* __restrict__ C_all, con
 constexpr int MID_SIDE = kGradMidSide, MID_SUBS = MID_SIDE * MID_SIDE;
 static_assert(MID_SIDE * MidTile::BM == BM && MID_SIDE * MidTile::BN == BN, "sub-tiles of a tile");
 
-template <bool F16, bool NOISE, bool OUT16>
-__global__ void __launch_bounds__(MidTile::NT, 2)
+template <class S, bool F16, bool NOISE, bool OUT16>
+__global__ void __launch_bounds__(S::NT, 163840 / S::LDS_BYTES)
 clipped_grad_mid_kernel(const GroupArgs ga, const float* C_all, int first_tile, const NoiseArgs na) {
   const SubTile sub = grad_sub_tile<MID_SIDE>(blockIdx.x, gridDim.x);
   const int l = layer_of(ga, first_tile + sub.tile);
@@ -87,7 +87,7 @@ clipped_grad_mid_kernel(const GroupArgs ga, const float* C_all, int first_tile, 
   m0 += sub.row * MidTile::BM;
   n0 += sub.col * MidTile::BN;
   if (m0 >= ga.layer[l].d_in || n0 >= ga.layer[l].d_out) return;      // past the layer's edge (whole workgroup)
-  gradient_tile<MidTile, F16, NOISE, OUT16>(ga, l, m0, n0, C, w, na);
+  gradient_tile<S, F16, NOISE, OUT16>(ga, l, m0, n0, C, w, na);
 }
 
 // ---------------------------------------------------------------------------------
@@ -300,22 +300,40 @@ int64_t clipped_grad_mid_tiles(int d, int p) {
 // rounds.  One sample: two layers 3744 x 2352 33.2 us mixed, 24.7 on 128 x 128 (before: 29); 17 of 33 tokens 76 and 69;
 // 16 of 100 104 and 104; four layers 4096 x 4096 (four whole rounds) 62 and 66; 24 of 768 x 3072 64 and 59, three of 40
 // tokens 79 and 80.
-GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows) {
-  constexpr int kTailMax = 32, kShortRows = 512;
+//
+// Short contractions of more 128 x 128 tiles than have a place at two to a compute unit take three to a unit, of three
+// stages each, where these are estimated to be through first: a round of 256 large tiles takes 12 us and 1 for each begun 32
+// rows, 768 small ones 8.5 and 1.15 (16-bit gradients: 8.2 and 1.05, 5.2 and 1).  What they gain is that the fixed part of
+// a tile (its lookup, first loads, noise and stores) runs beside other tiles' contraction; what they lose is operands read
+// twice as often.  Gradients, us, large and 128 x 128 of five stages, 128 x 128 of three: one sample of 32 tokens, 16 layers of
+// width 1472 100, 79, with noise 140, 107, in 16 bits 69, 53; four of 32, 24 layers of width 768 44, 40, with noise 60, 53; eight
+// 56, 51 and 73, 66; eight of 32, 16 layers of width 808 52, 46 and 66, 60; above the line 16 x 32, width 768 84, 83; eight,
+// width 1472 144, 166.
+GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows, bool out16) {
+  constexpr int kTailMax = 32, kShortRows = 512, kBriefMost = 1 << 20;         // (of these launch workgroups of 256 threads)
+  constexpr int64_t kBriefRound = 768;
   int tail = n % kBigRound;
-  if (n > kTailMax && tail != 0 && rows * (n < kBigRound ? 1 : n / kBigRound) <= kShortRows) return {n, MID_SIDE};
+  const bool crowded = n_mid > kMidRound && rows <= kShortRows && n <= kBriefMost;
+  if (n > kTailMax && tail != 0 && rows * (n < kBigRound ? 1 : n / kBigRound) <= kShortRows) return {n, MID_SIDE, crowded};
+  if (crowded) {
+    const int64_t blocks = (rows + BigTile::BK - 1) / BigTile::BK;
+    const int64_t big = out16 ? 820 + 105 * blocks : 1200 + 100 * blocks, brief = out16 ? 520 + 100 * blocks : 850 + 115 * blocks;
+    const int64_t rounds10 = n / kBigRound * 10 + (tail == 0 ? 0 : tail * MID_SUBS <= kMidRound ? 6 : 10);
+    if (brief * std::max(n_mid, kBriefRound) * 10 < big * rounds10 * kBriefRound) return {n, MID_SIDE, true};
+  }
   if (tail * MID_SUBS > kMidRound) tail = 0;
   const int64_t mixed = (int64_t)(n / kBigRound) * kBigRoundCost +
                         (tail ? kMidRoundCost : n % kBigRound ? kBigRoundCost : 0);
   if (kMidRoundCost * ((n_mid + kMidRound - 1) / kMidRound) < mixed) tail = n;
-  return {tail, tail <= kTailMax ? TAIL_SIDE : MID_SIDE};
+  return {tail, tail <= kTailMax ? TAIL_SIDE : MID_SIDE, false};
 }
 
 template <bool F16, bool NOISE, bool OUT16>
 dp_status launch_clipped_grad_big_group_t(const GroupArgs& ga, const float* C, const NoiseArgs& na,
                                           hipStream_t s) {
   auto big = clipped_grad_big_kernel<F16, NOISE, OUT16>;
-  auto mid = clipped_grad_mid_kernel<F16, NOISE, OUT16>;
+  auto mid = clipped_grad_mid_kernel<MidTile, F16, NOISE, OUT16>;
+  auto brief = clipped_grad_mid_kernel<ShortTile, F16, NOISE, OUT16>;
   auto tail = clipped_grad_tail_kernel<F16, NOISE, OUT16>;
   static ReadyTable ready_big, ready_mid, ready_tail;
   dp_status st = allow_big_lds(big, BigTile::LDS_BYTES, ready_big);
@@ -330,7 +348,7 @@ dp_status launch_clipped_grad_big_group_t(const GroupArgs& ga, const float* C, c
     const int64_t r = (int64_t)ga.B * ((ly.T + BigTile::BK - 1) / BigTile::BK) * BigTile::BK;
     rows = r > rows ? r : rows;
   }
-  const GradTail cut = clipped_grad_tail(n, n_mid, rows);
+  const GradTail cut = clipped_grad_tail(n, n_mid, rows, OUT16);
   const int n_tail = cut.tiles;
   if (n > n_tail) {
     GroupArgs main_args = ga;
@@ -342,6 +360,8 @@ dp_status launch_clipped_grad_big_group_t(const GroupArgs& ga, const float* C, c
   if (n_tail == 0) return DP_OK;
   if (cut.side == TAIL_SIDE)
     hipLaunchKernelGGL(tail, dim3(n_tail * SUBS), dim3(TailShape::NT), TailShape::LDS_BYTES, s, ga, C, n - n_tail, na);
+  else if (cut.brief)
+    hipLaunchKernelGGL(brief, dim3(n_tail * MID_SUBS), dim3(ShortTile::NT), ShortTile::LDS_BYTES, s, ga, C, n - n_tail, na);
   else
     hipLaunchKernelGGL(mid, dim3(n_tail * MID_SUBS), dim3(MidTile::NT), MidTile::LDS_BYTES, s, ga, C, n - n_tail, na);
   return hip_status(hipGetLastError());

@@ -54,9 +54,9 @@
 
 namespace dpbk {
 
-template <int BM_, int WM_, int WN_>
+template <int BM_, int WM_, int WN_, int NSTAGE_>
 struct PipeShape {
-  static constexpr int BM = BM_, BN = BM_, BK = 32, NSTAGE = 5, WM = WM_, WN = WN_;
+  static constexpr int BM = BM_, BN = BM_, BK = 32, NSTAGE = NSTAGE_, WM = WM_, WN = WN_;
   static constexpr int NT = 64 * WM * WN;
   static constexpr int WTM = BM / WM, WTN = BN / WN;             // wave tile
   static constexpr int TM = WTM / 32, TN = WTN / 32;             // 32 x 32 MFMA tiles per wave
@@ -69,8 +69,9 @@ struct PipeShape {
   static constexpr int LOADS = 2;                                // per operand, wave and k-block: 16 rows of the workgroup each
   static_assert(ROWS_PER_LOAD * WM * WN * LOADS == BK && TN == 2, "load split and fragment order");
 };
-using BigTile = PipeShape<256, 2, 4>;
-using MidTile = PipeShape<128, 2, 2>;
+using BigTile = PipeShape<256, 2, 4, 5>;
+using MidTile = PipeShape<128, 2, 2, 5>;
+using ShortTile = PipeShape<128, 2, 2, 3>;                         // 48 KiB: three workgroups per compute unit
 
 // c *= f (the bits of a float) where turn is not zero.  Branch and multiplies are inside the assembly and every accumulator
 // is one operand, so that for the compiler the contraction is one piece of straight code over whole register tuples:

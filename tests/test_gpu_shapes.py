@@ -493,3 +493,37 @@ def test_step_counts_only_where_its_counter_was_cleared(monkeypatch):
         want = want or got
         assert all(torch.equal(a, b) for a, b in zip(got, want))
         assert pipe.counter.item() == 0
+
+
+# Short contractions of many 128 x 128 tiles: three workgroups to a compute unit, three stages.  One k-block, an odd number of
+# k-steps, the longest that qualifies; ragged edges; a weight of zero.
+@pytest.mark.parametrize("dtype", [si.BF16, si.F16])
+@pytest.mark.parametrize("B,T", [(3, 20), (5, 33), (1, 512)])
+def test_short_contractions_of_many_tiles(dtype, B, T):
+    from paper_2311_11822_amd import binding as dp
+    dims = [(1160, 1032)] * 7 + [(1160, 264)]
+    dt, tdt = (dp.DP_BF16, torch.bfloat16) if dtype == si.BF16 else (dp.DP_F16, torch.float16)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    keep = [tuple((torch.randn((B, T, n), generator=gen, device="cuda") * s).to(tdt) for n, s in ((d, 1.0), (p, 0.01))) for d, p in dims]
+    C = torch.rand(B, generator=gen, device="cuda") + 0.1
+    if B > 1:
+        C[1] = 0.0
+    desc = dp.layer_array([(a, g, T, d, p, 0) for (a, g), (d, p) in zip(keep, dims)])
+    offs = [sum(d * p for d, p in dims[:l]) for l in range(len(dims))]
+    total = sum(d * p for d, p in dims)
+    got = [torch.full((d, p), 7.0, device="cuda") for d, p in dims]
+    dp.dp_clipped_grad_noise_multi(desc, dt, B, C, got, offs, 0, 1001, total - 2002, 0.5, 1.0, 3, 4)
+    for l, ((a, g), (d, p)) in enumerate(zip(keep, dims)):
+        alone, clean = torch.empty((d, p), device="cuda"), torch.empty((d, p), device="cuda")
+        one = dp.layer_array([(a, g, T, d, p, 0)])
+        dp.dp_clipped_grad_noise_multi(one, dt, B, C, [alone], [offs[l]], 0, 1001, total - 2002, 0.5, 1.0, 3, 4)
+        assert torch.equal(got[l], alone)                     # whichever tiles the launch takes
+        dp.dp_clipped_grad_multi(one, dt, B, C, [clean], 0)
+        ref = (a.double() * C.double()[:, None, None]).reshape(B * T, d).t().contiguous() @ g.double().reshape(B * T, p)
+        # exact products, sums of up to 512 terms and B re-expressions in fp32: some units of 2^-24 a step
+        assert float((clean.double() - ref).norm() / ref.norm()) < 3e-6
+    half = [torch.empty((d, p), device="cuda", dtype=tdt) for d, p in dims]
+    if T % 32 == 0:
+        dp.dp_clipped_grad_noise_multi_h16(desc, dt, B, C, half, offs, 0, 1001, total - 2002, 0.5, 1.0, 3, 4)
+        for x, y in zip(half, got):
+            assert torch.equal(x.view(torch.int16), y.to(tdt).view(torch.int16))
