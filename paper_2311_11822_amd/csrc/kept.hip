@@ -3,7 +3,7 @@
 // eq. "mixed ghost norm"):
 //     grad[e] (+)= sum_i C_i G_i[e]  (+ sigma R z_e, eq. (1)),     G_i = a_i^T g_i as kept, [B, d_in * d_out] fp32.
 // A stream over B + 1 arrays of d_in * d_out floats (HBM-bound) in place of a second contraction over
-// the T tokens of a and g.  Samples are added in index order; samples with C_i == 0 are not read.
+// the T tokens of a and g.  Samples are added in index order; samples with C_i == 0 do not enter.
 #include "dp_internal.h"
 
 namespace dpbk {
@@ -12,6 +12,7 @@ namespace {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4v;
 constexpr int kPerBlock = 1024;                 // elements per workgroup: 256 threads x one float4
+constexpr int kInFlight = 8;
 
 // GroupLayer fields as used here: a = kept gradients [B, n], out = grad [n], d_in * d_out = n (a
 // multiple of 4), tile_begin = first workgroup of the layer, c_off = the layer's row of C.
@@ -26,12 +27,22 @@ kept_weighted_sum_kernel(const GroupArgs ga, const float* __restrict__ C_all, co
   const float* __restrict__ C = C_all + ly.c_off;
   const float* src = static_cast<const float*>(ly.a) + e;
   f32x4v v = {0.f, 0.f, 0.f, 0.f};
-  for (int i = 0; i < ga.B; ++i) {
-    const float c = C[i];
-    if (c == 0.f) continue;
-    const f32x4v x = *reinterpret_cast<const f32x4v*>(src + (size_t)i * n);
+  // Eight samples in flight, added in order (their factors are the same for all lanes: scalar loads and branches).
+  for (int i0 = 0; i0 < ga.B; i0 += kInFlight) {
+    float c[kInFlight];
+    f32x4v x[kInFlight];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = fmaf(c, x[k], v[k]);
+    for (int q = 0; q < kInFlight; ++q) {
+      const int i = min(i0 + q, ga.B - 1);
+      c[q] = C[i];
+      x[q] = *reinterpret_cast<const f32x4v*>(src + (size_t)i * n);
+    }
+#pragma unroll
+    for (int q = 0; q < kInFlight; ++q)
+      if (i0 + q < ga.B && c[q] != 0.f) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = fmaf(c[q], x[q][k], v[k]);
+      }
   }
   f32x4v* dst = reinterpret_cast<f32x4v*>(ly.out + e);
   if (ga.accumulate) {
