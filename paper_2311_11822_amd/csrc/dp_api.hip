@@ -989,7 +989,7 @@ constexpr int64_t kLastPassTiles = 512;
 
 // Which layers the one-pass kernel takes, and its sample chunks.
 struct FusedPlan {
-  std::vector<int> shape;        // per layer: shape class or -1
+  std::vector<char> fused;       // per layer
   int n_fused = 0;
   int chunks = 1;                // sample chunks per fused layer
   int64_t floats = 0;            // partial sums of all fused layers
@@ -1004,15 +1004,32 @@ constexpr int64_t kKeptMaxBytes = (int64_t)2 << 30;
 
 FusedPlan plan_fused(const dp_layer* layers, int L, dp_dtype dt, int B) {
   FusedPlan fp;
-  fp.shape.assign(L, -1);
+  fp.fused.assign(L, 0);
   fp.kept_off.assign(L, -1);
   if (dt == DP_F32) return fp;
+  // The one-pass kernel saves writing and reading the per-sample gradients, but a workgroup goes through its samples one
+  // after the other with one k-block in flight, and it takes two launches.  So: short samples, and the whole stack or 64 MB
+  // of per-sample gradients each way.  Steps, us, fused and apart: eight layers 128 x 128, 8 x 256 tokens 14.0, 15.0; 64 x 512
+  // 31.8, 38.6; 256 x 128 39.9, 82.4; 8 x 512 17.0, 16.4; 8 x 1024 23.9, 18.5; 2 x 4096 60.9, 36.5; four 64 x 64 among four
+  // 64 x 192, 8 x 128 22.4, 14.0, 256 x 128 71.7, 56.5.  (Strips of up to 512 x 32, which it took too, were the slower ones for
+  // every batch and length: six adapter pairs of 192 x 32, 8 x 3600 180.6, 26.4, 256 x 128 77.6, 48.5.)
+  constexpr int kFusedTokens = 512;
+  constexpr int64_t kFusedSaves = (int64_t)64 << 20;
+  int64_t saved = 0;
+  for (int l = 0; l < L; ++l) {
+    const dp_layer& ly = layers[l];
+    fp.fused[l] = ly.path == DP_PATH_PEREX && ly.T <= kFusedTokens && layerwise_fused_fits(ly.d_in, ly.d_out);
+    fp.n_fused += fp.fused[l];
+    if (fp.fused[l]) saved += (int64_t)B * ly.d_in * ly.d_out * 4;
+  }
+  if (fp.n_fused < L && saved <= kFusedSaves) {
+    fp.fused.assign(L, 0);
+    fp.n_fused = 0;
+  }
   for (int l = 0; l < L; ++l)
-    if (layers[l].path == DP_PATH_PEREX) {
-      fp.shape[l] = layerwise_fused_shape(layers[l].d_in, layers[l].d_out);
-      fp.n_fused += fp.shape[l] >= 0;
+    if (layers[l].path == DP_PATH_PEREX && !fp.fused[l]) {
       const int64_t n = (int64_t)B * layers[l].d_in * layers[l].d_out;
-      if (fp.shape[l] < 0 && n <= INT32_MAX - 4096 && (fp.kept_floats + n) * 4 <= kKeptMaxBytes) {
+      if (n <= INT32_MAX - 4096 && (fp.kept_floats + n) * 4 <= kKeptMaxBytes) {
         fp.kept_off[l] = fp.kept_floats;
         fp.kept_floats += (n + 3) & ~(int64_t)3;                  // blocks stay 16-byte aligned
       }
@@ -1023,7 +1040,7 @@ FusedPlan plan_fused(const dp_layer* layers, int L, dp_dtype dt, int B) {
   const int per = (B + want - 1) / want;
   fp.chunks = (B + per - 1) / per;
   for (int l = 0; l < L; ++l)
-    if (fp.shape[l] >= 0) fp.floats += (int64_t)fp.chunks * layers[l].d_in * layers[l].d_out;
+    if (fp.fused[l]) fp.floats += (int64_t)fp.chunks * layers[l].d_in * layers[l].d_out;
   return fp;
 }
 
@@ -1093,7 +1110,7 @@ dp_status dp_layerwise_clipped_grad(const dp_layer* layers, int L, dp_dtype dt, 
   na.rk = make_round_keys(seed);
 
   auto pass_tiles = [&](int l) {
-    return fp.shape[l] >= 0 ? (int64_t)0 : (int64_t)clipped_grad_big_tiles(layers[l].d_in, layers[l].d_out);
+    return fp.fused[l] ? (int64_t)0 : (int64_t)clipped_grad_big_tiles(layers[l].d_in, layers[l].d_out);
   };
   int64_t fused_off = 0, tiles_left = 0;                 // tiles of the layers from l1 on
   for (int l = 0; l < L; ++l) tiles_left += pass_tiles(l);
@@ -1104,7 +1121,7 @@ dp_status dp_layerwise_clipped_grad(const dp_layer* layers, int L, dp_dtype dt, 
     int64_t bytes = 0, tiles = 0;
     const int64_t esize = dt == DP_F32 ? 4 : 2;
     while (l1 < L) {
-      const bool small = fp.shape[l1] >= 0;
+      const bool small = fp.fused[l1];
       const int64_t lb = small ? 0 : (int64_t)B * layers[l1].T * ((int64_t)layers[l1].d_in + layers[l1].d_out) * esize;
       if (l1 > l0 && (layers_per_pass > 0 ? l1 - l0 >= layers_per_pass
                                           : bytes + lb > kPassBytes && tiles >= kPassTiles &&
@@ -1115,44 +1132,41 @@ dp_status dp_layerwise_clipped_grad(const dp_layer* layers, int L, dp_dtype dt, 
       ++l1;
     }
     // (1) layers that fit one workgroup tile: norm, clip factor and weighted sum in one kernel
-    for (int shape = 0; shape < 3; ++shape) {
-      int l = l0;
-      while (l < l1) {
-        GroupArgs ga;
-        ga.B = B;
-        ga.accumulate = accumulate;
-        ga.f16 = dt == DP_F16;
-        ga.n_layers = 0;
-        float Rg[kMaxGroup];
-        int blocks = 0;
-        for (; l < l1 && ga.n_layers < kMaxGroup; ++l) {
-          if (fp.shape[l] != shape) continue;
-          GroupLayer& gl = ga.layer[ga.n_layers];
-          gl.a = layers[l].a;
-          gl.g = layers[l].g;
-          gl.out = grads[l];
-          gl.T = layers[l].T;
-          gl.d_in = layers[l].d_in;
-          gl.d_out = layers[l].d_out;
-          gl.path = DP_PATH_PEREX;
-          gl.tile_begin = blocks;
-          gl.sq_index = l;
-          gl.part_begin = (int)fused_off;
-          gl.tiles_per_sample = fp.chunks;
-          gl.c_off = 0;
-          Rg[ga.n_layers] = R[l];
-          na.layer_off[ga.n_layers] = noisy ? grad_offset[l] : 0;
-          fused_off += (int64_t)fp.chunks * gl.d_in * gl.d_out;
-          blocks += fp.chunks;
-          ++ga.n_layers;
-        }
-        if (ga.n_layers == 0) break;
-        ga.total_blocks = blocks;
-        dp_status st = launch_layerwise_fused(shape, ga, Rg, (int)mode, stability, fused_partial, sqnorm_out, C_out, s);
-        if (st != DP_OK) return st;
-        st = launch_layerwise_reduce(ga, fused_partial, na, s);
-        if (st != DP_OK) return st;
+    for (int l = l0; l < l1;) {
+      GroupArgs ga;
+      ga.B = B;
+      ga.accumulate = accumulate;
+      ga.f16 = dt == DP_F16;
+      ga.n_layers = 0;
+      float Rg[kMaxGroup];
+      int blocks = 0;
+      for (; l < l1 && ga.n_layers < kMaxGroup; ++l) {
+        if (!fp.fused[l]) continue;
+        GroupLayer& gl = ga.layer[ga.n_layers];
+        gl.a = layers[l].a;
+        gl.g = layers[l].g;
+        gl.out = grads[l];
+        gl.T = layers[l].T;
+        gl.d_in = layers[l].d_in;
+        gl.d_out = layers[l].d_out;
+        gl.path = DP_PATH_PEREX;
+        gl.tile_begin = blocks;
+        gl.sq_index = l;
+        gl.part_begin = (int)fused_off;
+        gl.tiles_per_sample = fp.chunks;
+        gl.c_off = 0;
+        Rg[ga.n_layers] = R[l];
+        na.layer_off[ga.n_layers] = noisy ? grad_offset[l] : 0;
+        fused_off += (int64_t)fp.chunks * gl.d_in * gl.d_out;
+        blocks += fp.chunks;
+        ++ga.n_layers;
       }
+      if (ga.n_layers == 0) break;
+      ga.total_blocks = blocks;
+      dp_status st = launch_layerwise_fused(ga, Rg, (int)mode, stability, fused_partial, sqnorm_out, C_out, s);
+      if (st != DP_OK) return st;
+      st = launch_layerwise_reduce(ga, fused_partial, na, s);
+      if (st != DP_OK) return st;
     }
     // (2) the other layers of the pass: norms, clip factors, weighted gradients
     //     (instantiated layers keep G_i in the workspace: their gradient is sum_i C_i G_i)
@@ -1163,7 +1177,7 @@ dp_status dp_layerwise_clipped_grad(const dp_layer* layers, int L, dp_dtype dt, 
     std::vector<uint64_t> sub_off;
     bool any_kept = false;
     for (int l = l0; l < l1; ++l)
-      if (fp.shape[l] < 0) {
+      if (!fp.fused[l]) {
         sub.push_back(layers[l]);
         row.push_back(l);
         sub_R.push_back(R[l]);

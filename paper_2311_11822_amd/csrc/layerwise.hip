@@ -125,7 +125,13 @@ layerwise_reduce_kernel(const GroupArgs ga, const float* __restrict__ partial, c
   if (e >= n) return;
   const float* src = partial + ly.part_begin + e;
   float v = 0.f;
-  for (int c = 0; c < ly.tiles_per_sample; ++c) v += src[(size_t)c * n];
+  for (int c0 = 0; c0 < ly.tiles_per_sample; c0 += 8) {          // eight chunks in flight, added in order
+    float x[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) x[q] = src[(size_t)min(c0 + q, ly.tiles_per_sample - 1) * n];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v += c0 + q < ly.tiles_per_sample ? x[q] : 0.f;
+  }
   if (ga.accumulate) v += ly.out[e];
   if (na.stddev != 0.f) {
     const uint64_t idx = na.layer_off[blockIdx.y] + (uint64_t)e;
@@ -139,11 +145,8 @@ layerwise_reduce_kernel(const GroupArgs ga, const float* __restrict__ partial, c
   ly.out[e] = v;
 }
 
-// One workgroup tile holds the whole layer: 128 x 128, or a strip 512 x 32 / 32 x 512 (the
-// shapes of low-rank adapter factors).
+// One workgroup tile holds the whole layer.
 using FusedSquare = TnShape<128, 128, 64, 2, 2>;
-using FusedTall = TnShape<512, 32, 64, 4, 1>;
-using FusedWide = TnShape<32, 512, 64, 1, 4>;
 
 template <class S, bool F16>
 dp_status launch_fused_t(const GroupArgs& ga, const FusedArgs& fa, float* partial, float* sqnorm, float* C_out,
@@ -158,29 +161,17 @@ dp_status launch_fused_t(const GroupArgs& ga, const FusedArgs& fa, float* partia
 
 }  // namespace
 
-int layerwise_fused_shape(int d, int p) {
-  if (d <= 128 && p <= 128) return 0;
-  if (d <= 512 && p <= 32) return 1;
-  if (d <= 32 && p <= 512) return 2;
-  return -1;
-}
+bool layerwise_fused_fits(int d, int p) { return d <= FusedSquare::BM && p <= FusedSquare::BN; }
 
-dp_status launch_layerwise_fused(int shape, const GroupArgs& ga, const float* R, int mode, float stability,
-                                 float* partial, float* sqnorm, float* C_out, hipStream_t s) {
+dp_status launch_layerwise_fused(const GroupArgs& ga, const float* R, int mode, float stability, float* partial,
+                                 float* sqnorm, float* C_out, hipStream_t s) {
   FusedArgs fa;
   fa.mode = mode;
   fa.stability = stability;
   for (int j = 0; j < ga.n_layers; ++j) fa.R[j] = R[j];
   for (int j = ga.n_layers; j < kMaxGroup; ++j) fa.R[j] = 1.f;
-  switch (shape * 2 + (ga.f16 ? 1 : 0)) {
-    case 0: return launch_fused_t<FusedSquare, false>(ga, fa, partial, sqnorm, C_out, s);
-    case 1: return launch_fused_t<FusedSquare, true>(ga, fa, partial, sqnorm, C_out, s);
-    case 2: return launch_fused_t<FusedTall, false>(ga, fa, partial, sqnorm, C_out, s);
-    case 3: return launch_fused_t<FusedTall, true>(ga, fa, partial, sqnorm, C_out, s);
-    case 4: return launch_fused_t<FusedWide, false>(ga, fa, partial, sqnorm, C_out, s);
-    case 5: return launch_fused_t<FusedWide, true>(ga, fa, partial, sqnorm, C_out, s);
-  }
-  return DP_ERR_INVALID_ARG;
+  return ga.f16 ? launch_fused_t<FusedSquare, true>(ga, fa, partial, sqnorm, C_out, s)
+                : launch_fused_t<FusedSquare, false>(ga, fa, partial, sqnorm, C_out, s);
 }
 
 dp_status launch_layerwise_reduce(const GroupArgs& ga, const float* partial, const NoiseArgs& na, hipStream_t s) {

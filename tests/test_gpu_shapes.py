@@ -527,3 +527,29 @@ def test_short_contractions_of_many_tiles(dtype, B, T):
         dp.dp_clipped_grad_noise_multi_h16(desc, dt, B, C, half, offs, 0, 1001, total - 2002, 0.5, 1.0, 3, 4)
         for x, y in zip(half, got):
             assert torch.equal(x.view(torch.int16), y.to(tdt).view(torch.int16))
+
+
+# Layer-wise pass on either side of the one-kernel form's lines: its longest sample, one token more, a stack that it does
+# not take whole, strips of adapters, and per-sample gradients of more than 64 MB beside another layer.
+@pytest.mark.parametrize("dtype", [si.BF16, si.F16])
+@pytest.mark.parametrize("B,T,dims", [(3, 512, [(128, 96), (64, 64)]), (3, 513, [(128, 96), (64, 64)]),
+                                      (9, 200, [(64, 192), (64, 64)]), (5, 130, [(512, 16), (16, 512), (24, 32)]),
+                                      (520, 130, [(128, 128), (128, 128), (128, 136)])])
+def test_layerwise_either_form(dtype, B, T, dims):
+    from paper_2311_11822_amd import binding as dp
+    from paper_2311_11822_amd.pipeline import BkPipeline
+    tdt = torch.bfloat16 if dtype == si.BF16 else torch.float16
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    layers = [tuple((torch.randn((B, T, n), generator=gen, device="cuda") * s).to(tdt) for n, s in ((d, 1.0), (p, 0.01)))
+              for d, p in dims]
+    pipe = BkPipeline(layers, paths=[dp.DP_PATH_PEREX] * len(dims))
+    pipe.set_groups(list(range(len(dims))), [0.5] * len(dims))
+    pipe.layerwise_step(dp.DP_CLIP_STANDARD, 0.01, 0.0, 1, 0, 0, pipe.psi)
+    for l, (a, g) in enumerate(layers):
+        each = torch.stack([a[i].double().t().contiguous() @ g[i].double() for i in range(B)])
+        sq = each.square().sum((1, 2))
+        factor = (0.5 / sq.sqrt()).clamp(max=1.0)
+        ref = (each * factor[:, None, None]).sum(0)
+        # exact products; sums of T rows and B samples in fp32
+        assert float(((pipe.sqnorm[l].double() - sq) / sq).abs().max()) < 1e-5
+        assert float((pipe.grads[l].double() - ref).norm() / ref.norm()) < 3e-6
