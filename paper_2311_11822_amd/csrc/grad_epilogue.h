@@ -2,6 +2,8 @@
 // noise -> store, in fp32 or in the operands' 16-bit storage type.
 #pragma once
 
+#include <type_traits>
+
 #include "dp_internal.h"
 
 namespace dpbk {
@@ -72,6 +74,29 @@ struct WaveRows {
   static constexpr int BYTES = 32 * STRIDE;
 };
 
+// How a wave's piece leaves: N store instructions of ROWS rows, LANES lanes to a row, VEC columns a lane.
+template <int NY, bool OUT16>
+struct RowStores {
+  static constexpr int VEC = OUT16 ? 8 : 4, LANES = WaveRows<NY>::W / VEC, ROWS = 64 / LANES, N = 32 / ROWS;
+};
+
+// The old values of a piece, asked for before its sums go through LDS.
+template <int NY, bool OUT16>
+struct OldRows {
+  u32x4v raw[RowStores<NY, OUT16>::N];
+  __device__ __forceinline__ void load(const float* out32, int row0, int col0, int d, int p, int lane) {
+    using S = RowStores<NY, OUT16>;
+    const int row = row0 + lane / S::LANES, col = col0 + lane % S::LANES * S::VEC;
+    const char* at = reinterpret_cast<const char*>(out32) + ((size_t)row * p + col) * (OUT16 ? 2 : 4);
+    const size_t step = (size_t)S::ROWS * p * (OUT16 ? 2 : 4);
+#pragma unroll
+    for (int n = 0; n < S::N; ++n) {
+      raw[n] = u32x4v{0, 0, 0, 0};
+      if (row + n * S::ROWS < d && col < p) raw[n] = *reinterpret_cast<const u32x4v*>(at + n * step);
+    }
+  }
+};
+
 // acc * held (+ old value) (+ noise of eq. (1)) -> out, in fp32 or the operands' 16-bit type; lds: the wave's WaveRows::BYTES.
 // Noise: same values as the separate pass, which indexes the generator by global element too; requires layer_off and d_out
 // to be multiples of 4, as a lane's four columns are one block of the generator.
@@ -79,6 +104,8 @@ template <int NY, bool F16, bool NOISE, bool OUT16, bool ACCUMULATE>
 __device__ __forceinline__ void store_rows(const f32x16* acc, float held, unsigned lds, float* out32, int row0, int col0,
                                            int d, int p, const TileNoise& na, int lane) {
   using R = WaveRows<NY>;
+  OldRows<NY, OUT16> old;
+  if (ACCUMULATE) old.load(out32, row0, col0, d, p, lane);
   typedef __attribute__((address_space(3))) f32x4v lds_f4;
 #pragma unroll
   for (int y = 0; y < NY; ++y)
@@ -95,7 +122,8 @@ __device__ __forceinline__ void store_rows(const f32x16* acc, float held, unsign
     noisy = rows > 0 && cols > 0 && e_last >= na.lo && e_first < na.hi;              // wave-uniform
     whole = e_first >= na.lo && e_last < na.hi;
   }
-  constexpr int VEC = OUT16 ? 8 : 4, LANES = R::W / VEC, ROWS = 64 / LANES, N = 32 / ROWS;      // N instructions of ROWS rows
+  constexpr int VEC = RowStores<NY, OUT16>::VEC, LANES = RowStores<NY, OUT16>::LANES;
+  constexpr int ROWS = RowStores<NY, OUT16>::ROWS, N = RowStores<NY, OUT16>::N;
   constexpr int BLOCKS = VEC / 4, U = 4 / BLOCKS;                                     // U at a time: four generator blocks
   static_assert(N % U == 0, "whole groups");
   const int row = row0 + lane / LANES, col = col0 + lane % LANES * VEC;
@@ -115,18 +143,13 @@ __device__ __forceinline__ void store_rows(const f32x16* acc, float held, unsign
     if constexpr (ACCUMULATE) {
 #pragma unroll
       for (int u = n; u < n + U; ++u)
-        if (row + u * ROWS < d && col < p) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
           if constexpr (OUT16) {
-            const u32x4v w = *reinterpret_cast<const u32x4v*>(reinterpret_cast<const uint16_t*>(out32) + at + u * step);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              v[u][2 * k] = from_half_bits<F16>((uint16_t)(w[k] & 0xFFFFu)) + v[u][2 * k];
-              v[u][2 * k + 1] = from_half_bits<F16>((uint16_t)(w[k] >> 16)) + v[u][2 * k + 1];
-            }
+            v[u][2 * k] = from_half_bits<F16>((uint16_t)(old.raw[u][k] & 0xFFFFu)) + v[u][2 * k];
+            v[u][2 * k + 1] = from_half_bits<F16>((uint16_t)(old.raw[u][k] >> 16)) + v[u][2 * k + 1];
           } else {
-            const f32x4v w = *reinterpret_cast<const f32x4v*>(out32 + at + u * step);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) v[u][k] = w[k] + v[u][k];
+            v[u][k] = __uint_as_float(old.raw[u][k]) + v[u][k];
           }
         }
     }
@@ -173,6 +196,27 @@ __device__ __forceinline__ void store_rows(const f32x16* acc, float held, unsign
       }
     __builtin_amdgcn_sched_barrier(0);
   }
+}
+
+// COUNT pieces of the wave.  piece(i): its tiles' sums, first row and column.
+struct WavePiece {
+  const f32x16* acc;
+  int row0, col0;
+};
+template <int COUNT, int NY, bool F16, bool NOISE, bool OUT16, class Piece>
+__device__ __forceinline__ void store_pieces(Piece piece, bool accumulate, float held, unsigned lds, float* out32, int d, int p,
+                                             const TileNoise& na, int lane) {
+  auto store_all = [&](auto acc_tag) {
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i) {
+      const WavePiece x = piece(i);
+      store_rows<NY, F16, NOISE, OUT16, decltype(acc_tag)::value>(x.acc, held, lds, out32, x.row0, x.col0, d, p, na, lane);
+    }
+  };
+  if (accumulate)
+    store_all(std::true_type{});
+  else
+    store_all(std::false_type{});
 }
 
 }  // namespace dpbk

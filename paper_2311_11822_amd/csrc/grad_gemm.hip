@@ -44,16 +44,8 @@ __device__ __forceinline__ void gradient_tile(const GroupArgs& ga, int l, int m0
   TileNoise tn = {};
   if (NOISE) tn = load_tile_noise(na, l);
   __syncthreads();                                     // the last fragments are read
-  auto store_tile = [&](auto acc_tag) {
-#pragma unroll
-    for (int x = 0; x < S::TM; ++x)
-      store_rows<S::TN, F16, NOISE, OUT16, decltype(acc_tag)::value>(acc[x], held, region, ly.out, m0 + wm + x * 32, n0 + wn,
-                                                                     d, p, tn, lane);
-  };
-  if (ga.accumulate)
-    store_tile(std::true_type{});
-  else
-    store_tile(std::false_type{});
+  store_pieces<S::TM, S::TN, F16, NOISE, OUT16>(
+      [&](int x) { return WavePiece{acc[x], m0 + wm + x * 32, n0 + wn}; }, ga.accumulate, held, region, ly.out, d, p, tn, lane);
 }
 
 template <bool F16, bool NOISE, bool OUT16>
@@ -243,10 +235,8 @@ __device__ __forceinline__ void clipped_grad_tile_deep(const GroupLayer& ly, int
   const unsigned region = (unsigned)(uintptr_t)lds + wave * WaveRows<1>::BYTES;
   TileNoise tn = {};
   if (NOISE) tn = load_tile_noise(na, layer);
-  if (accumulate)
-    store_rows<1, F16, NOISE, OUT16, true>(acc[0], held, region, ly.out, m0 + wm, n0 + wn, d, p, tn, lane);
-  else
-    store_rows<1, F16, NOISE, OUT16, false>(acc[0], held, region, ly.out, m0 + wm, n0 + wn, d, p, tn, lane);
+  store_pieces<1, 1, F16, NOISE, OUT16>([&](int) { return WavePiece{acc[0], m0 + wm, n0 + wn}; }, accumulate, held, region,
+                                        ly.out, d, p, tn, lane);
 }
 
 // Sub-tiles are 64 x 64 (16 per tile), k-blocks of 64 rows, four k-blocks in flight: three

@@ -336,13 +336,9 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
   constexpr int NY = S::TN < 2 ? 1 : 2;
   static_assert(WaveRows<NY>::BYTES * 4 <= NSTAGE * S::STAGE_BYTES, "a region for each wave");
   const unsigned region = lds0 + wave * WaveRows<NY>::BYTES;
-#pragma unroll
-  for (int y = 0; y < S::TN; y += NY) {
-    if (accumulate)
-      store_rows<NY, F16, NOISE, false, true>(acc + y, 1.f, region, ly.out, m0 + wm, n0 + wn + 32 * y, d, p, tn, lane);
-    else
-      store_rows<NY, F16, NOISE, false, false>(acc + y, 1.f, region, ly.out, m0 + wm, n0 + wn + 32 * y, d, p, tn, lane);
-  }
+  store_pieces<S::TN / NY, NY, F16, NOISE, false>(
+      [&](int y) { return WavePiece{acc + NY * y, m0 + wm, n0 + wn + 32 * NY * y}; }, accumulate, 1.f, region, ly.out, d, p, tn,
+      lane);
 }
 
 // GroupLayer::path holds the layer's tile shape (packed_shape).
