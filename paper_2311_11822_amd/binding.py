@@ -17,6 +17,10 @@ if not os.path.exists(LIB_PATH):
 
 lib = C.CDLL(LIB_PATH)
 
+from . import _pycall  # noqa: E402  (the same library's calls with native argument conversion, built with it)
+
+_pycall.set_array_type(C.Array)
+
 DP_OK, DP_ERR_INVALID_ARG, DP_ERR_UNSUPPORTED, DP_ERR_WORKSPACE, DP_ERR_HIP = range(5)
 DP_F32, DP_BF16, DP_F16 = 0, 1, 2
 DP_CLIP_STANDARD, DP_CLIP_AUTOMATIC = 0, 1
@@ -93,7 +97,9 @@ def _stream(stream) -> Optional[int]:
         # the handle behind current_stream().cuda_stream without building a Stream object (2.9 -> 0.6 us; a step
         # of one small layer makes three calls in 30 us); private to torch, so not taken for granted
         try:
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            handle = torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            _pycall.set_torch(torch._C)        # its calls look there themselves from now on
+            return handle
         except AttributeError:
             pass
     return torch.cuda.current_stream().cuda_stream
@@ -106,6 +112,17 @@ def _nbytes(ws) -> int:
 def _check(status: int, where: str) -> None:
     if status != DP_OK:
         raise DpError(status, where)
+
+
+def _call(name: str, *args) -> None:
+    """Library call `name`; pointers as tensors, addresses, None or ctypes arrays, the stream last."""
+    status = getattr(_pycall, name)(*args)
+    if status is None:                     # something that the native conversion leaves to ctypes
+        fn = getattr(lib, name)
+        status = fn(*[_ptr(x) if t is _vp and not isinstance(x, C.Array) else x for x, t in zip(args[:-1], fn.argtypes)],
+                    _stream(args[-1]))
+    if status:
+        raise DpError(status, name)
 
 
 def layer_array(layers: Sequence) -> "C.Array[dp_layer]":
@@ -129,28 +146,23 @@ def dp_norm_workspace_bytes(path, dt, B, T, d_in, d_out) -> int:
 
 
 def dp_ghost_norm(a, g, dt, B, T, d_in, d_out, sqnorm_out, ws, stream=None) -> None:
-    _check(lib.dp_ghost_norm(_ptr(a), _ptr(g), dt, B, T, d_in, d_out, _ptr(sqnorm_out), _ptr(ws),
-                             _nbytes(ws), _stream(stream)), "dp_ghost_norm")
+    _call("dp_ghost_norm", a, g, dt, B, T, d_in, d_out, sqnorm_out, ws, _nbytes(ws), stream)
 
 
 def dp_perex_norm(a, g, dt, B, T, d_in, d_out, sqnorm_out, ws, stream=None) -> None:
-    _check(lib.dp_perex_norm(_ptr(a), _ptr(g), dt, B, T, d_in, d_out, _ptr(sqnorm_out), _ptr(ws),
-                             _nbytes(ws), _stream(stream)), "dp_perex_norm")
+    _call("dp_perex_norm", a, g, dt, B, T, d_in, d_out, sqnorm_out, ws, _nbytes(ws), stream)
 
 
 def dp_clip_factors(sqnorm, L, B, mode, R, stability, C_out, norm_out=None, stream=None) -> None:
-    _check(lib.dp_clip_factors(_ptr(sqnorm), L, B, mode, R, stability, _ptr(C_out), _ptr(norm_out),
-                               _stream(stream)), "dp_clip_factors")
+    _call("dp_clip_factors", sqnorm, L, B, mode, R, stability, C_out, norm_out, stream)
 
 
 def dp_clipped_grad(a, g, dt, B, T, d_in, d_out, Cf, grad, accumulate=0, stream=None) -> None:
-    _check(lib.dp_clipped_grad(_ptr(a), _ptr(g), dt, B, T, d_in, d_out, _ptr(Cf), _ptr(grad),
-                               accumulate, _stream(stream)), "dp_clipped_grad")
+    _call("dp_clipped_grad", a, g, dt, B, T, d_in, d_out, Cf, grad, accumulate, stream)
 
 
 def dp_add_noise(grad_slice, global_offset, count, sigma, R, seed, step, stream=None) -> None:
-    _check(lib.dp_add_noise(_ptr(grad_slice), global_offset, count, sigma, R, seed, step,
-                            _stream(stream)), "dp_add_noise")
+    _call("dp_add_noise", grad_slice, global_offset, count, sigma, R, seed, step, stream)
 
 
 def dp_philox_blocks(out, first_block, n_blocks, seed, step, stream=None) -> None:
@@ -165,8 +177,7 @@ def dp_norms_multi_workspace_bytes(layers, dt, B) -> int:
 
 def dp_norms_multi(layers, dt, B, sqnorm_out, ws, stream=None) -> None:
     arr = layers if isinstance(layers, C.Array) else layer_array(layers)
-    _check(lib.dp_norms_multi(arr, len(arr), dt, B, _ptr(sqnorm_out), _ptr(ws), _nbytes(ws),
-                              _stream(stream)), "dp_norms_multi")
+    _call("dp_norms_multi", arr, len(arr), dt, B, sqnorm_out, ws, _nbytes(ws), stream)
 
 
 def dp_norms_multi_static(layers, dt, B, sqnorm_out, stream=None) -> None:
@@ -178,8 +189,7 @@ def dp_norms_multi_static(layers, dt, B, sqnorm_out, stream=None) -> None:
 def dp_clipped_grad_multi(layers, dt, B, Cf, grads, accumulate=0, stream=None) -> None:
     arr = layers if isinstance(layers, C.Array) else layer_array(layers)
     gp = grads if isinstance(grads, C.Array) else (C.c_void_p * len(grads))(*[_ptr(x) for x in grads])
-    _check(lib.dp_clipped_grad_multi(arr, len(arr), dt, B, _ptr(Cf), gp, accumulate, _stream(stream)),
-           "dp_clipped_grad_multi")
+    _call("dp_clipped_grad_multi", arr, len(arr), dt, B, Cf, gp, accumulate, stream)
 
 
 def dp_clipped_grad_noise_multi(layers, dt, B, Cf, grads, grad_offset, accumulate, shard_offset, shard_count,
@@ -187,9 +197,8 @@ def dp_clipped_grad_noise_multi(layers, dt, B, Cf, grads, grad_offset, accumulat
     arr = layers if isinstance(layers, C.Array) else layer_array(layers)
     gp = grads if isinstance(grads, C.Array) else (C.c_void_p * len(grads))(*[_ptr(x) for x in grads])
     offs = grad_offset if isinstance(grad_offset, C.Array) else (C.c_uint64 * len(grad_offset))(*grad_offset)
-    _check(lib.dp_clipped_grad_noise_multi(arr, len(arr), dt, B, _ptr(Cf), gp, offs, accumulate, shard_offset,
-                                           shard_count, sigma, R, seed, step, _stream(stream)),
-           "dp_clipped_grad_noise_multi")
+    _call("dp_clipped_grad_noise_multi", arr, len(arr), dt, B, Cf, gp, offs, accumulate, shard_offset, shard_count, sigma, R,
+          seed, step, stream)
 
 
 def dp_clipped_grad_noise_multi_h16(layers, dt, B, Cf, grads16, grad_offset, accumulate, shard_offset, shard_count,
@@ -199,9 +208,8 @@ def dp_clipped_grad_noise_multi_h16(layers, dt, B, Cf, grads16, grad_offset, acc
     offs = None
     if grad_offset is not None:
         offs = grad_offset if isinstance(grad_offset, C.Array) else (C.c_uint64 * len(grad_offset))(*grad_offset)
-    _check(lib.dp_clipped_grad_noise_multi_h16(arr, len(arr), dt, B, _ptr(Cf), gp, offs, accumulate, shard_offset,
-                                               shard_count, sigma, R, seed, step, _stream(stream)),
-           "dp_clipped_grad_noise_multi_h16")
+    _call("dp_clipped_grad_noise_multi_h16", arr, len(arr), dt, B, Cf, gp, offs, accumulate, shard_offset, shard_count,
+          sigma, R, seed, step, stream)
 
 
 def _i32(xs):
@@ -232,13 +240,11 @@ def dp_group_noise_threshold(R) -> float:
 
 
 def dp_bias_norm(g, dt, B, T, d_out, colsum, sqnorm_out, stream=None) -> None:
-    _check(lib.dp_bias_norm(_ptr(g), dt, B, T, d_out, _ptr(colsum), _ptr(sqnorm_out), _stream(stream)),
-           "dp_bias_norm")
+    _call("dp_bias_norm", g, dt, B, T, d_out, colsum, sqnorm_out, stream)
 
 
 def dp_clipped_bias_grad(colsum, B, d_out, Cf, grad_b, accumulate=0, stream=None) -> None:
-    _check(lib.dp_clipped_bias_grad(_ptr(colsum), B, d_out, _ptr(Cf), _ptr(grad_b), accumulate, _stream(stream)),
-           "dp_clipped_bias_grad")
+    _call("dp_clipped_bias_grad", colsum, B, d_out, Cf, grad_b, accumulate, stream)
 
 
 def _ptr_array(xs):
@@ -250,8 +256,8 @@ def _ptr_array(xs):
 
 def dp_norms_multi_keep(layers, dt, B, sqnorm_out, kept, ws, stream=None) -> None:
     arr = layers if isinstance(layers, C.Array) else layer_array(layers)
-    _check(lib.dp_norms_multi_keep(arr, len(arr), dt, B, _ptr(sqnorm_out), _ptr_array(kept) if kept is not None else None,
-                                   _ptr(ws), _nbytes(ws), _stream(stream)), "dp_norms_multi_keep")
+    _call("dp_norms_multi_keep", arr, len(arr), dt, B, sqnorm_out, _ptr_array(kept) if kept is not None else None, ws,
+          _nbytes(ws), stream)
 
 
 def dp_clipped_grad_kept_multi(layers, dt, B, Cf, kept, grads, grad_offset, accumulate, shard_offset, shard_count,
@@ -260,9 +266,8 @@ def dp_clipped_grad_kept_multi(layers, dt, B, Cf, kept, grads, grad_offset, accu
     offs = None
     if grad_offset is not None:
         offs = grad_offset if isinstance(grad_offset, C.Array) else (C.c_uint64 * len(grad_offset))(*grad_offset)
-    _check(lib.dp_clipped_grad_kept_multi(arr, len(arr), dt, B, _ptr(Cf), _ptr_array(kept) if kept is not None else None,
-                                          _ptr_array(grads), offs, accumulate, shard_offset, shard_count, sigma, R,
-                                          seed, step, _stream(stream)), "dp_clipped_grad_kept_multi")
+    _call("dp_clipped_grad_kept_multi", arr, len(arr), dt, B, Cf, _ptr_array(kept) if kept is not None else None,
+          _ptr_array(grads), offs, accumulate, shard_offset, shard_count, sigma, R, seed, step, stream)
 
 
 def dp_private_step_multi(layers, dt, B, mode, R, stability, kept, grads, grad_offset, accumulate, shard_offset,
@@ -272,11 +277,9 @@ def dp_private_step_multi(layers, dt, B, mode, R, stability, kept, grads, grad_o
     offs = None
     if grad_offset is not None:
         offs = grad_offset if isinstance(grad_offset, C.Array) else (C.c_uint64 * len(grad_offset))(*grad_offset)
-    _check(lib.dp_private_step_multi(arr, len(arr), dt, B, mode, R, stability,
-                                     _ptr_array(kept) if kept is not None else None, _ptr_array(grads), offs, accumulate,
-                                     shard_offset, shard_count, sigma, seed, step, _ptr(sqnorm_out), _ptr(C_out),
-                                     _ptr(norm_out), _ptr(ws), _nbytes(ws), _ptr(counter), _stream(stream)),
-           "dp_private_step_multi")
+    _call("dp_private_step_multi", arr, len(arr), dt, B, mode, R, stability, _ptr_array(kept) if kept is not None else None,
+          _ptr_array(grads), offs, accumulate, shard_offset, shard_count, sigma, seed, step, sqnorm_out, C_out, norm_out, ws,
+          _nbytes(ws), counter, stream)
 
 
 def dp_layerwise_workspace_bytes(layers, dt, B) -> int:
@@ -292,10 +295,8 @@ def dp_layerwise_clipped_grad(layers, dt, B, R, mode, stability, grads, grad_off
     offs = None
     if grad_offset is not None:
         offs = grad_offset if isinstance(grad_offset, C.Array) else (C.c_uint64 * len(grad_offset))(*grad_offset)
-    _check(lib.dp_layerwise_clipped_grad(arr, len(arr), dt, B, _f32(R), mode, stability, gp, offs, accumulate,
-                                         shard_offset, shard_count, sigma, seed, step, _ptr(sqnorm_out),
-                                         _ptr(C_out), _ptr(ws), _nbytes(ws), layers_per_pass, _stream(stream)),
-           "dp_layerwise_clipped_grad")
+    _call("dp_layerwise_clipped_grad", arr, len(arr), dt, B, _f32(R), mode, stability, gp, offs, accumulate, shard_offset,
+          shard_count, sigma, seed, step, sqnorm_out, C_out, ws, _nbytes(ws), layers_per_pass, stream)
 
 
 def dp_clipped_grad_tile_order(d_in: int, d_out: int):

@@ -4,11 +4,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdp_bk.so")
+PYCALL = os.path.join(HERE, "_pycall.so")          # the library's calls for Python
 SOURCES = ["dp_api.hip", "noise.hip", "clip.hip", "fp32_kernels.hip", "ghost.hip", "tn_gemm.hip", "grad_gemm.hip", "grad_packed.hip", "ghost_big.hip", "ghost_brief.hip", "bias.hip", "layerwise.hip", "kept.hip", "ghost_sample.hip", "perex_dma.hip", "perex_narrow.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -40,6 +42,10 @@ def build(verbose: bool = False) -> str:
         objs.append(obj)
     link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(link, check=True)
+    subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall",
+                    "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"],
+                    os.path.join(CSRC, "pycall.cpp"), "-o", PYCALL, "-L", HERE, "-l:libdp_bk.so", "-Wl,-rpath,$ORIGIN"],
+                   check=True)
     return LIB
 
 

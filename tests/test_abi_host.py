@@ -245,3 +245,20 @@ def test_current_stream_without_torch_private_functions(dp, monkeypatch, missing
     monkeypatch.delattr(torch._C, missing)
     assert dp._stream(None) == 77
     assert dp._stream(5) == 5
+
+
+def test_native_argument_conversion(dp):
+    """What the native conversion does not take reaches ctypes and is refused as it always was; statuses raise."""
+    import ctypes
+    import numpy as np
+    with pytest.raises(dp.DpError) as e:
+        dp.dp_bias_norm(None, dp.DP_BF16, 4, 8, 64, None, None, stream=0)
+    assert e.value.status == dp.DP_ERR_INVALID_ARG and "dp_bias_norm" in str(e.value)
+    with pytest.raises(dp.DpError):
+        dp.dp_clipped_grad_multi(dp.layer_array([(16, 16, 4, 8, 8, 0)]), dp.DP_BF16, 1, None, [16], stream=0)
+    with pytest.raises(ctypes.ArgumentError):
+        dp.dp_bias_norm(16, 1.5, 4, 8, 64, 16, 16, stream=0)
+    with pytest.raises(ctypes.ArgumentError):
+        dp.dp_clip_factors(16, 1, 1, dp.DP_CLIP_STANDARD, "R", 0.01, 16, None, 0)
+    with pytest.raises(AttributeError):
+        dp.dp_bias_norm(np.zeros(64, dtype=np.float32), dp.DP_F32, 1, 1, 64, 16, 16, stream=0)    # host memory, no data_ptr
