@@ -205,13 +205,13 @@ dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, const Nor
 int clipped_grad_big_tiles(int d, int p);
 int64_t clipped_grad_mid_tiles(int d, int p);
 // Of a launch of n large tiles whose layers hold n_mid tiles of 128 x 128 and contract over up to `rows` rows, how many
-// (the last ones) are cut into side x side sub-tiles; brief: on the 128 x 128 tiles of short contractions.
+// (the last ones) are cut into side x side sub-tiles (whole_lines: every row of every operand is whole 128-byte lines); brief: on the 128 x 128 tiles of short contractions.
 constexpr int kGradMidSide = 2, kGradTailSide = 4;
 struct GradTail {
   int tiles, side;
   bool brief;
 };
-GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows, bool out16);
+GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows, bool whole_lines, bool out16);
 bool clipped_grad_big_supports(int T, int d, int p);
 // noise == nullptr: gradients only.  out16: the layers' `out` pointers address 16-bit arrays of the
 // operands' storage type (bf16 or fp16) instead of fp32.

@@ -299,7 +299,7 @@ int64_t clipped_grad_mid_tiles(int d, int p) {
 // width 1472 100, 79, with noise 140, 107, in 16 bits 69, 53; four of 32, 24 layers of width 768 44, 40, with noise 60, 53; eight
 // 56, 51 and 73, 66; eight of 32, 16 layers of width 808 52, 46 and 66, 60; above the line 16 x 32, width 768 84, 83; eight,
 // width 1472 144, 166.
-GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows, bool out16) {
+GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows, bool whole_lines, bool out16) {
   constexpr int kTailMax = 32, kShortRows = 512, kBriefMost = 1 << 20;         // (of these launch workgroups of 256 threads)
   constexpr int64_t kBriefRound = 768;
   int tail = n % kBigRound;
@@ -312,9 +312,14 @@ GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows, bool out16) {
     if (brief * std::max(n_mid, kBriefRound) * 10 < big * rounds10 * kBriefRound) return {n, MID_SIDE, true};
   }
   if (tail * MID_SUBS > kMidRound) tail = 0;
-  const int64_t mixed = (int64_t)(n / kBigRound) * kBigRoundCost +
-                        (tail ? kMidRoundCost : n % kBigRound ? kBigRoundCost : 0);
-  if (kMidRoundCost * ((n_mid + kMidRound - 1) / kMidRound) < mixed) tail = n;
+  // A round of small tiles in tenths of a large round's time.  Rows that are not whole 128-byte lines of memory cost them half
+  // as many lines again (large tiles a quarter), and the longer the contraction the less of that L2 has at hand: 16 layers
+  // 1024 x 1024 0.56 at 2048 rows and 0.64 at 8192, 1016 x 1016 0.65 and 0.76; nine 784 x 2352 .. 3136 in fp16, 10638 rows, 520 us
+  // on large tiles and 767 on small ones; 16 of 520 x 1560 .. 2080, 16384 rows, 655 and 1024; eight of 1000 x 3000 .. 4000,
+  // 4096 rows, 211 and 265.
+  const int64_t mid_cost = whole_lines || rows <= 2048 ? 6 : rows <= 8192 ? 8 : 10;
+  const int64_t mixed = (int64_t)(n / kBigRound) * 10 + (tail ? mid_cost : n % kBigRound ? 10 : 0);
+  if (mid_cost * ((n_mid + kMidRound - 1) / kMidRound) < mixed) tail = n;
   return {tail, tail <= kTailMax ? TAIL_SIDE : MID_SIDE, false};
 }
 
@@ -332,13 +337,15 @@ dp_status launch_clipped_grad_big_group_t(const GroupArgs& ga, const float* C, c
   if (st != DP_OK) return st;
   const int n = ga.total_blocks;
   int64_t n_mid = 0, rows = 0;
+  bool whole_lines = true;
   for (int j = 0; j < ga.n_layers; ++j) {
     const GroupLayer& ly = ga.layer[j];
     n_mid += clipped_grad_mid_tiles(ly.d_in, ly.d_out);
+    whole_lines = whole_lines && ly.d_in % 64 == 0 && ly.d_out % 64 == 0;
     const int64_t r = (int64_t)ga.B * ((ly.T + BigTile::BK - 1) / BigTile::BK) * BigTile::BK;
     rows = r > rows ? r : rows;
   }
-  const GradTail cut = clipped_grad_tail(n, n_mid, rows, OUT16);
+  const GradTail cut = clipped_grad_tail(n, n_mid, rows, whole_lines, OUT16);
   const int n_tail = cut.tiles;
   if (n > n_tail) {
     GroupArgs main_args = ga;
