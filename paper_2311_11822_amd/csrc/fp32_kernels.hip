@@ -81,10 +81,44 @@ __device__ __forceinline__ f32x16 gram_part(const float* x, int T, int width, in
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q)
+      // past the width there are zeros only (widths of single loads: the branch costs their order more than it saves)
+      if (!VEC || k0 + q * kWaves * 8 < width) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc = mfma32(a[q][e], b[q][e], acc);
+        for (int e = 0; e < 4; ++e) acc = mfma32(a[q][e], b[q][e], acc);
+      }
   }
   return acc;
+}
+
+// The same of the tiles (0, 0), (0, 32), (32, 32) of a sample of 33 to 64 tokens: its rows read once, no load waits for
+// another tile's sums.  Widths that are multiples of 4: eight layers of width 64 .. 256, 16 x 48 tokens, 15.4 -> 10.4 us; of others,
+// with their single loads, slower (ten to 40 wide, 28 x 56: 11.0 -> 17.4).
+__device__ __forceinline__ void gram_parts3(const float* x, int T, int width, int wave, int lane, f32x16 (&acc)[3]) {
+#pragma unroll
+  for (int n = 0; n < 3; ++n) acc[n] = zero16();
+  const int t = lane & 31, u = 32 + (lane & 31);
+  const float* rt = x + (size_t)t * width;
+  const float* ru = x + (size_t)min(u, T - 1) * width;
+  const int wu = u < T ? width : 0;
+  for (int k0 = wave * 8; k0 < width; k0 += 4 * kWaves * 8) {
+    f32x4v a[4], b[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = k0 + q * kWaves * 8 + 4 * (lane >> 5);
+      a[q] = load4<true>(rt, k, width);
+      b[q] = load4<true>(ru, k, wu);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (k0 + q * kWaves * 8 < width) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc[0] = mfma32(a[q][e], a[q][e], acc[0]);
+          acc[1] = mfma32(a[q][e], b[q][e], acc[1]);
+          acc[2] = mfma32(b[q][e], b[q][e], acc[2]);
+        }
+      }
+  }
 }
 
 __device__ __forceinline__ f32x16 gram_part(const float* x, int T, int width, int t0, int u0, int wave, int lane) {
@@ -106,6 +140,18 @@ __device__ __forceinline__ void load_item(TnItem& it, const float* a, const floa
     it.g[q] = t < T && k < p ? g[(size_t)t * p + k] : 0.f;
   }
 }
+// The same through buffer descriptors over the sample's rows, whose range check makes the zeros: no masks around the loads.
+// ja, kg: byte of the lane's column in a row, or kOutside.
+constexpr unsigned kOutside = 0x80000000u;
+__device__ __forceinline__ void load_item(TnItem& it, __amdgpu_buffer_rsrc_t a, __amdgpu_buffer_rsrc_t g, int t0, int d, int p,
+                                          unsigned ja, unsigned kg, int lane) {
+#pragma unroll
+  for (int q = 0; q < kChunk / 2; ++q) {
+    const unsigned t = t0 + 2 * q + (lane >> 5);
+    it.a[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(a, t * d * 4u + ja, 0, 0));
+    it.g[q] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(g, t * p * 4u + kg, 0, 0));
+  }
+}
 // The g operand first: lane l then holds row l & 31 of the tile and runs of four consecutive
 // columns, 8 q + 4 (l >> 5) + e in register 4 q + e.
 __device__ __forceinline__ f32x16 mul_item(const TnItem& it, f32x16 acc) {
@@ -119,6 +165,10 @@ __device__ __forceinline__ f32x16 mul_item(const TnItem& it, f32x16 acc) {
 // instantiated: || a_i^T g_i ||_F^2.
 // A tile's entries outside the layer (past d, p or T) are selected out before they are added: their
 // zero operands meet the other side's values, and an infinity there would make them NaN.
+// VEC: every width of the launch is a multiple of 4.  (A kernel of its own: beside the single loads of other widths the
+// compiler orders either form's loads worse; eight layers ten to 40 wide, 28 x 56 tokens, 34.8 us a step apart, 36.6 to 45.8
+// in one.)
+template <bool VEC>
 __global__ void __launch_bounds__(kThreads)
 norms_f32_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int first) {
   __shared__ float part_a[kWaves][16][64], part_g[kWaves][16][64];   // 64 KiB
@@ -146,36 +196,54 @@ norms_f32_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int first
   auto run = [&](int r) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); };
 
   if (ly.path == DP_PATH_GHOST) {
-    for (int t0 = 0; t0 < T; t0 += kTile)
-      for (int u0 = t0; u0 < T; u0 += kTile) {
-        const f32x16 xa = gram_part(a, T, d, t0, u0, wave, lane);
-        const f32x16 xg = gram_part(g, T, p, t0, u0, wave, lane);
-        put(part_a, xa);
-        put(part_g, xg);
-        __syncthreads();
-        float s = 0.f;
+    auto add_tile = [&](int t0, int u0, const f32x16& xa, const f32x16& xg) {
+      put(part_a, xa);
+      put(part_g, xg);
+      __syncthreads();
+      float s = 0.f;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const float va = total(part_a, tid + h * kThreads), vg = total(part_g, tid + h * kThreads);
-          const bool in = t0 + run(wave + h * kWaves) < T && u0 + (lane & 31) < T;
-          s = in ? fmaf(va, vg, s) : s;
-        }
-        sum += t0 == u0 ? s : 2.f * s;
-        __syncthreads();
+      for (int h = 0; h < 2; ++h) {
+        const float va = total(part_a, tid + h * kThreads), vg = total(part_g, tid + h * kThreads);
+        const bool in = t0 + run(wave + h * kWaves) < T && u0 + (lane & 31) < T;
+        s = in ? fmaf(va, vg, s) : s;
       }
+      sum += t0 == u0 ? s : 2.f * s;
+      __syncthreads();
+    };
+    if (VEC && T > kTile && T <= 2 * kTile) {
+      f32x16 xa[3], xg[3];
+      gram_parts3(a, T, d, wave, lane, xa);
+      gram_parts3(g, T, p, wave, lane, xg);
+      add_tile(0, 0, xa[0], xg[0]);
+      add_tile(0, kTile, xa[1], xg[1]);
+      add_tile(kTile, kTile, xa[2], xg[2]);
+    } else {
+      for (int t0 = 0; t0 < T; t0 += kTile)
+        for (int u0 = t0; u0 < T; u0 += kTile)
+          if constexpr (VEC)
+            add_tile(t0, u0, gram_part<true>(a, T, d, t0, u0, wave, lane), gram_part<true>(g, T, p, t0, u0, wave, lane));
+          else
+            add_tile(t0, u0, gram_part(a, T, d, t0, u0, wave, lane), gram_part(g, T, p, t0, u0, wave, lane));
+    }
   } else {
     const int tn = (p + kTile - 1) / kTile, tiles = ((d + kTile - 1) / kTile) * tn;
     const int items = (T + kChunk - 1) / kChunk;
     // The waves share the tokens of each tile where that employs more of them than a tile to each (5 x 176, 7 tokens, 406
     // samples of 11 layers: 59 us before there were tiles, 77 shared, 29 so).
     const bool split = tiles < kWaves && items > tiles;
+    // T d p <= 2^28: 32-bit byte offsets
+    const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)a, 0, T * d * 4, 0x00020000);
+    const auto rg = __builtin_amdgcn_make_buffer_rsrc((void*)g, 0, T * p * 4, 0x00020000);
     for (int tile = split ? 0 : wave; tile < tiles; tile += split ? 1 : kWaves) {
       const int n0 = (tile % tn) * kTile;
       const int j = (tile / tn) * kTile + (lane & 31), k = n0 + (lane & 31);
       f32x16 acc = zero16();
       for (int c = split ? wave : 0; c < items; c += split ? kWaves : 1) {
         TnItem it;
-        load_item(it, a, g, c * kChunk, T, d, p, j, k, lane);
+        if constexpr (VEC)
+          load_item(it, ra, rg, c * kChunk, d, p, j < d ? 4u * j : kOutside, k < p ? 4u * k : kOutside, lane);
+        else
+          load_item(it, a, g, c * kChunk, T, d, p, j, k, lane);
         acc = mul_item(it, acc);
       }
       // Columns of a and g left in the tile, formed anew: from j < d the compiler makes a mask that it holds through the
@@ -316,8 +384,11 @@ int64_t clipped_grad_f32_tiles(int d, int p) {
 }
 
 dp_status launch_norms_f32_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s) {
+  int widths = 0;
+  for (int l = 0; l < ga.n_layers; ++l) widths |= ga.layer[l].d_in | ga.layer[l].d_out;
+  auto kernel = widths & 3 ? norms_f32_kernel<false> : norms_f32_kernel<true>;
   return launch_in_runs(ga.total_blocks, [&](dim3 grid, int first) {
-    hipLaunchKernelGGL(norms_f32_kernel, grid, dim3(kThreads), 0, s, ga, sqnorm, nc, first);
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, ga, sqnorm, nc, first);
   });
 }
 

@@ -553,3 +553,22 @@ def test_layerwise_either_form(dtype, B, T, dims):
         # exact products; sums of T rows and B samples in fp32
         assert float(((pipe.sqnorm[l].double() - sq) / sq).abs().max()) < 1e-5
         assert float((pipe.grads[l].double() - ref).norm() / ref.norm()) < 3e-6
+
+
+# fp32 norms of stacks whose widths are all multiples of four (either path) and of stacks with another width: the two halves
+# of 33 to 64 tokens, one tile, more than two.
+@pytest.mark.parametrize("T", [32, 33, 48, 64, 65])
+@pytest.mark.parametrize("dims", [[(36, 100), (300, 8), (4, 4)], [(36, 100), (300, 8), (5, 6)]])
+def test_f32_norms_by_width(T, dims):
+    from paper_2311_11822_amd import binding as dp
+    B = 3
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    keep = [tuple(torch.randn((B, T, n), generator=gen, device="cuda") for n in dim) for dim in dims]
+    want = torch.stack([torch.stack([(a[i].double().t() @ g[i].double()).square().sum() for i in range(B)]) for a, g in keep])
+    for path in (dp.DP_PATH_GHOST, dp.DP_PATH_PEREX):
+        desc = dp.layer_array([(a, g, T, d, p, path) for (a, g), (d, p) in zip(keep, dims)])
+        ws = torch.empty(dp.dp_norms_multi_workspace_bytes(desc, dp.DP_F32, B), dtype=torch.uint8, device="cuda")
+        got = torch.empty((len(dims), B), device="cuda")
+        dp.dp_norms_multi(desc, dp.DP_F32, B, got, ws)
+        # sums of up to T^2 products, each of sums of up to 300, in fp32
+        assert float(((got.double() - want) / want).abs().max()) < 1e-5
