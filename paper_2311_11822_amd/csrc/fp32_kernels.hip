@@ -282,6 +282,8 @@ norms_f32_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int first
 // One workgroup per 32 x 32 tile; its waves take contiguous runs of the (sample, 16 tokens) items.
 // An item's product is formed unweighted and folded in as total += C_i * item; a sample with
 // C_i == 0 is not read, as in the 16-bit kernels.
+// SMALL: every sample's a and g are less than 2 GiB, so that they load through buffer descriptors.
+template <bool SMALL>
 __global__ void __launch_bounds__(kThreads)
 clipped_grad_f32_kernel(const GroupArgs ga, const float* __restrict__ C_all, const NoiseArgs na, int first) {
   __shared__ float part[kWaves][16][64];                 // 32 KiB
@@ -307,8 +309,13 @@ clipped_grad_f32_kernel(const GroupArgs ga, const float* __restrict__ C_all, con
   float wc = 0.f, wn = 0.f;
   auto fetch = [&](TnItem& it, float& w) {               // item (i, c), then step to the next one
     w = C[i];
-    if (w != 0.f)
+    if constexpr (SMALL) {                               // whether it counts or not: the loads need not wait for the weight
+      const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)(a + (size_t)i * T * d), 0, T * d * 4, 0x00020000);
+      const auto rg = __builtin_amdgcn_make_buffer_rsrc((void*)(g + (size_t)i * T * p), 0, T * p * 4, 0x00020000);
+      load_item(it, ra, rg, c * kChunk, d, p, j < d ? 4u * j : kOutside, k < p ? 4u * k : kOutside, lane);
+    } else if (w != 0.f) {
       load_item(it, a + (size_t)i * T * d, g + (size_t)i * T * p, c * kChunk, T, d, p, j, k, lane);
+    }
     if (++c == per_sample) {
       c = 0;
       ++i;
@@ -393,8 +400,14 @@ dp_status launch_norms_f32_group(const GroupArgs& ga, float* sqnorm, const NormC
 }
 
 dp_status launch_clipped_grad_f32_group(const GroupArgs& ga, const float* C, const NoiseArgs& na, hipStream_t s) {
+  bool small = true;                                     // rows of the last chunk past the end included
+  for (int l = 0; l < ga.n_layers; ++l) {
+    const int64_t rows = (int64_t)ga.layer[l].T + kChunk;
+    small = small && rows * std::max(ga.layer[l].d_in, ga.layer[l].d_out) * 4 < (int64_t)1 << 31;
+  }
+  auto kernel = small ? clipped_grad_f32_kernel<true> : clipped_grad_f32_kernel<false>;
   return launch_in_runs(ga.total_blocks, [&](dim3 grid, int first) {
-    hipLaunchKernelGGL(clipped_grad_f32_kernel, grid, dim3(kThreads), 0, s, ga, C, na, first);
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, ga, C, na, first);
   });
 }
 
