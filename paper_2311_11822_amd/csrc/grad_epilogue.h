@@ -111,7 +111,7 @@ __device__ __forceinline__ void store_rows(const f32x16* acc, float held, unsign
   for (int y = 0; y < NY; ++y)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const f32x4v w = {acc[y][4 * q] * held, acc[y][4 * q + 1] * held, acc[y][4 * q + 2] * held, acc[y][4 * q + 3] * held};
+      const f32x4v w = {acc[y][4 * q], acc[y][4 * q + 1], acc[y][4 * q + 2], acc[y][4 * q + 3]};
       *(lds_f4*)(uintptr_t)(lds + (lane & 31) * R::STRIDE + (32 * y + 8 * q + 4 * (lane >> 5)) * 4) = w;
     }
   bool noisy = false, whole = false;
@@ -136,7 +136,7 @@ __device__ __forceinline__ void store_rows(const f32x16* acc, float held, unsign
     for (int b = 0; b < BLOCKS; ++b) {
       const f32x4v w = *(const lds_f4*)(uintptr_t)(from + n * ROWS * R::STRIDE + 16 * b);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) v[n][4 * b + k] = w[k];
+      for (int k = 0; k < 4; ++k) v[n][4 * b + k] = ACCUMULATE ? w[k] : w[k] * held;
     }
 #pragma unroll
   for (int n = 0; n < N; n += U) {
@@ -146,10 +146,10 @@ __device__ __forceinline__ void store_rows(const f32x16* acc, float held, unsign
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           if constexpr (OUT16) {
-            v[u][2 * k] = from_half_bits<F16>((uint16_t)(old.raw[u][k] & 0xFFFFu)) + v[u][2 * k];
-            v[u][2 * k + 1] = from_half_bits<F16>((uint16_t)(old.raw[u][k] >> 16)) + v[u][2 * k + 1];
+            v[u][2 * k] = fmaf(v[u][2 * k], held, from_half_bits<F16>((uint16_t)(old.raw[u][k] & 0xFFFFu)));
+            v[u][2 * k + 1] = fmaf(v[u][2 * k + 1], held, from_half_bits<F16>((uint16_t)(old.raw[u][k] >> 16)));
           } else {
-            v[u][k] = __uint_as_float(old.raw[u][k]) + v[u][k];
+            v[u][k] = fmaf(v[u][k], held, __uint_as_float(old.raw[u][k]));       // one rounding
           }
         }
     }

@@ -572,3 +572,20 @@ def test_f32_norms_by_width(T, dims):
         dp.dp_norms_multi(desc, dp.DP_F32, B, got, ws)
         # sums of up to T^2 products, each of sums of up to 300, in fp32
         assert float(((got.double() - want) / want).abs().max()) < 1e-5
+
+
+# Accumulating: the weight, the old value and their sum are one rounding, in every tile size.
+@pytest.mark.parametrize("dims,T", [([(136, 72)], 200), ([(1024, 1024)] * 2, 300), ([(4096, 4096)], 600), ([(1160, 1032)] * 8, 40)])
+def test_accumulate_rounds_once(dims, T):
+    from paper_2311_11822_amd import binding as dp
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    keep = [tuple((torch.randn((1, T, n), generator=gen, device="cuda")).to(torch.bfloat16) for n in dim) for dim in dims]
+    desc = dp.layer_array([(a, g, T, d, p, 0) for (a, g), (d, p) in zip(keep, dims)])
+    plain = [torch.empty(dim, device="cuda") for dim in dims]
+    old = [torch.randn(dim, generator=gen, device="cuda") for dim in dims]
+    got = [x.clone() for x in old]
+    c = torch.tensor([0.3], device="cuda")
+    dp.dp_clipped_grad_multi(desc, dp.DP_BF16, 1, torch.ones(1, device="cuda"), plain, 0)
+    dp.dp_clipped_grad_multi(desc, dp.DP_BF16, 1, c, got, 1)
+    for x, y, z in zip(got, plain, old):
+        assert torch.equal(x, (y.double() * c.double() + z.double()).float())
