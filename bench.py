@@ -34,7 +34,7 @@ import synth_inputs as si  # noqa: E402
 
 PEAK_BF16_FLOPS = 2.5e15       # MI355X dense bf16 MFMA
 PEAK_HBM_BYTES = 8.0e12
-NOISE_ALU_PEAK_BLOCKS = 256 * 4 * 64 * 2.4e9 / 690      # Philox4x32-10 + Box-Muller blocks/s the vector ALUs can issue
+NOISE_ALU_PEAK_BLOCKS = 487e9   # Philox4x32-10 + Box-Muller blocks/s of the bare generator, two waves per SIMD, measured
 HEADLINE = "cfg4"
 
 

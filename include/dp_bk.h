@@ -296,7 +296,7 @@ float dp_group_noise_threshold(const float* R, int M);
  *          DP_ERR_INVALID_ARG / DP_ERR_UNSUPPORTED).
  * dp_clipped_grad_kept_multi: dp_clipped_grad_noise_multi, with the layers that have kept[l] != NULL
  *   computed from kept[l] (a and g of those layers are not read; their descriptors still give
- *   the shapes).  Samples are added in index order in fp32; samples with C[i] == 0 are not read.
+ *   the shapes).  Samples are added in index order in fp32; samples with C[i] == 0 do not enter.
  *   grad_offset may be NULL when sigma == 0 or shard_count == 0.
  */
 dp_status dp_norms_multi_keep(const dp_layer* layers, int L, dp_dtype dt, int B, float* sqnorm_out,
@@ -329,9 +329,10 @@ dp_status dp_private_step_multi(const dp_layer* layers, int L, dp_dtype dt, int 
  * gradients (+ noise) before the next is touched, so a pass's a and g are still in the
  * memory-side cache when the gradient kernels read them again.  A layer on the instantiated
  * path (path == DP_PATH_PEREX, 16-bit storage) whose whole gradient fits one workgroup tile (up to
- * 128 x 128, 512 x 32 or 32 x 512) is done in ONE kernel that reads a and g once: per sample it
+ * 128 x 128), of up to 512 tokens, is done in ONE kernel that reads a and g once if the whole stack is
+ * such layers or more than 64 MiB of G_i are saved so: per sample it
  * forms G_i = a_i^T g_i in registers, takes ||G_i||, C_i = clip(||G_i||; R_l) and adds C_i G_i.
- * A larger layer on the instantiated path keeps its G_i ([B, d_in, d_out] fp32) in the workspace
+ * Any other layer on the instantiated path keeps its G_i ([B, d_in, d_out] fp32) in the workspace
  * between its norm kernel and a weighted sum, as dp_norms_multi_keep + dp_clipped_grad_kept_multi
  * do, so its a and g are read once as well; layers are given room in stack order up to 2 GiB in
  * total, the rest contract a and g a second time.
