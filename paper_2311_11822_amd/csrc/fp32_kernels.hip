@@ -165,7 +165,7 @@ __device__ __forceinline__ f32x16 mul_item(const TnItem& it, f32x16 acc) {
 // instantiated: || a_i^T g_i ||_F^2.
 // A tile's entries outside the layer (past d, p or T) are selected out before they are added: their
 // zero operands meet the other side's values, and an infinity there would make them NaN.
-// VEC: every width of the launch is a multiple of 4.  (A kernel of its own: beside the single loads of other widths the
+// VEC: every width of the launch is a multiple of 4, every slab small (small_slabs).  (A kernel of its own: beside the single loads of other widths the
 // compiler orders either form's loads worse; eight layers ten to 40 wide, 28 x 56 tokens, 34.8 us a step apart, 36.6 to 45.8
 // in one.)
 template <bool VEC>
@@ -231,7 +231,6 @@ norms_f32_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int first
     // The waves share the tokens of each tile where that employs more of them than a tile to each (5 x 176, 7 tokens, 406
     // samples of 11 layers: 59 us before there were tiles, 77 shared, 29 so).
     const bool split = tiles < kWaves && items > tiles;
-    // T d p <= 2^28: 32-bit byte offsets
     const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)a, 0, T * d * 4, 0x00020000);
     const auto rg = __builtin_amdgcn_make_buffer_rsrc((void*)g, 0, T * p * 4, 0x00020000);
     for (int tile = split ? 0 : wave; tile < tiles; tile += split ? 1 : kWaves) {
@@ -384,6 +383,11 @@ clipped_grad_f32_kernel(const GroupArgs ga, const float* __restrict__ C_all, con
   }
 }
 
+// Byte offsets inside a sample stay below kOutside, those of the last chunk's rows past the end included.
+bool small_slabs(const GroupLayer& ly) {
+  return ((int64_t)ly.T + kChunk) * std::max(ly.d_in, ly.d_out) * 4 < (int64_t)1 << 31;
+}
+
 }  // namespace
 
 int64_t clipped_grad_f32_tiles(int d, int p) {
@@ -391,20 +395,17 @@ int64_t clipped_grad_f32_tiles(int d, int p) {
 }
 
 dp_status launch_norms_f32_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s) {
-  int widths = 0;
-  for (int l = 0; l < ga.n_layers; ++l) widths |= ga.layer[l].d_in | ga.layer[l].d_out;
-  auto kernel = widths & 3 ? norms_f32_kernel<false> : norms_f32_kernel<true>;
+  bool vec = true;
+  for (int l = 0; l < ga.n_layers; ++l) vec = vec && ((ga.layer[l].d_in | ga.layer[l].d_out) & 3) == 0 && small_slabs(ga.layer[l]);
+  auto kernel = vec ? norms_f32_kernel<true> : norms_f32_kernel<false>;
   return launch_in_runs(ga.total_blocks, [&](dim3 grid, int first) {
     hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, ga, sqnorm, nc, first);
   });
 }
 
 dp_status launch_clipped_grad_f32_group(const GroupArgs& ga, const float* C, const NoiseArgs& na, hipStream_t s) {
-  bool small = true;                                     // rows of the last chunk past the end included
-  for (int l = 0; l < ga.n_layers; ++l) {
-    const int64_t rows = (int64_t)ga.layer[l].T + kChunk;
-    small = small && rows * std::max(ga.layer[l].d_in, ga.layer[l].d_out) * 4 < (int64_t)1 << 31;
-  }
+  bool small = true;
+  for (int l = 0; l < ga.n_layers; ++l) small = small && small_slabs(ga.layer[l]);
   auto kernel = small ? clipped_grad_f32_kernel<true> : clipped_grad_f32_kernel<false>;
   return launch_in_runs(ga.total_blocks, [&](dim3 grid, int first) {
     hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, ga, C, na, first);
