@@ -29,10 +29,10 @@ dp_status check_layer_ptrs(const void* a, const void* g) {
   return DP_OK;
 }
 
-// Ghost layers of more than a handful of tokens take the large-tile kernel; the rest take the
-// 128x128-tile kernel with per-chunk edge handling.
+// Ghost layers of more than 32 tokens that the large-tile kernel can address; up to 128 tokens the 128 x 128-tile kernel
+// takes them too (ghost_stays_small), with the same bits.
 bool ghost_uses_big(const dp_layer& ly) {
-  return ly.T >= 96 && ghost_big_supports(ly.T, ly.d_in, ly.d_out);
+  return !ghost_brief_supports(ly.T) && ghost_big_supports(ly.T, ly.d_in, ly.d_out);
 }
 
 // Up to 128 tokens a sample is one workgroup in either kernel.  The large-tile kernel keeps deeper prefetch and has a
@@ -41,10 +41,14 @@ bool ghost_uses_big(const dp_layer& ly) {
 // over before a deep prefetch pays, stay on the small kernel beyond one round (d_in + d_out = 272: 12.5 and 9.7 us a
 // round), and wide ones on the large kernel (2096: 43.5 and 24.4).  512 samples 24 + 16 wide: 10.0 us here, 13.3 on the
 // large kernel, 2048 of 392 + 296: 80 and 94; 768 of 760 + 520: 49.5 and 45.9.
-// Whole 64-wide k-blocks: the large kernel, which has no edge handling there.
-bool ghost_stays_small(const dp_layer& ly, int64_t samples) {
-  if (ly.T > 128 || (ly.d_in % 64 == 0 && ly.d_out % 64 == 0)) return false;
-  const int64_t width = (int64_t)ly.d_in + ly.d_out;
+// From 96 tokens on, whole 64-wide k-blocks: the large kernel, which has no edge handling there.
+// Below 96 tokens either kernel pays for 128, so the same rounds; which of them is decided for the call by its widest layer,
+// one launch instead of two.  Norms of 64 tokens, us, small and large kernel: 7 samples of five layers 512 + 512 18.5, 12.3;
+// 4 of 1024 + 3072 .. 4096 66.5, 31.7; 10 of 24 layers 1472 + 4416 .. 5888 94.1, 47.2; 32 of twelve 768 + 2304 .. 3072 59.4, 47.5;
+// 96 of eight 760 + 520 43.1, 38.4; 320 samples of 392 + 296 17.3, 19.7; 2048 of 128 + 384 .. 512 43.9, 52.6.
+bool ghost_stays_small(const dp_layer& ly, int64_t samples, int64_t widest) {
+  if (ly.T > 128 || (ly.T >= 96 && ly.d_in % 64 == 0 && ly.d_out % 64 == 0)) return false;
+  const int64_t width = ly.T >= 96 ? (int64_t)ly.d_in + ly.d_out : widest;
   if (samples <= 256 || width >= 1800) return false;
   return width < 500 || 3 * ((samples + 255) / 256) >= 5 * ((samples + 511) / 512);
 }
@@ -345,15 +349,18 @@ dp_status norms_impl(const dp_layer* layers, int L, dp_dtype dt, int B, float* s
   int* list[kNormKernels];
   for (int k = 0; k < kNormKernels; ++k) list[k] = idx + (size_t)k * L;
   int count[kNormKernels] = {};
-  int64_t samples = 0;                                   // that either large-tile or 128 x 128 kernel may take
+  int64_t samples = 0, widest = 0;                       // that either large-tile or 128 x 128 kernel may take
   for (int l = 0; l < L; ++l)
-    if (layers[l].path == DP_PATH_GHOST && ghost_uses_big(layers[l]) && layers[l].T <= 128) samples += B;
+    if (layers[l].path == DP_PATH_GHOST && ghost_uses_big(layers[l]) && layers[l].T <= 128) {
+      samples += B;
+      widest = std::max(widest, (int64_t)layers[l].d_in + layers[l].d_out);
+    }
   for (int l = 0; l < L; ++l) {
     const bool narrow = perex_narrow_supports(layers[l].T, layers[l].d_in, layers[l].d_out);
     const int k = layers[l].path == DP_PATH_PEREX ? (narrow ? kPerexNarrow : kPerex)
                   : ghost_brief_supports(layers[l].T) ? kGhostBrief
                   : ghost_uses_sample(layers[l])  ? kGhostSample
-                  : ghost_uses_big(layers[l]) && !ghost_stays_small(layers[l], samples) ? kGhostBig
+                  : ghost_uses_big(layers[l]) && !ghost_stays_small(layers[l], samples, widest) ? kGhostBig
                                                                                         : kGhostSmall;
     list[k][count[k]++] = l;
   }

@@ -589,3 +589,27 @@ def test_accumulate_rounds_once(dims, T):
     dp.dp_clipped_grad_multi(desc, dp.DP_BF16, 1, c, got, 1)
     for x, y, z in zip(got, plain, old):
         assert torch.equal(x, (y.double() * c.double() + z.double()).float())
+
+
+# Ghost norms of 33 to 95 tokens: on large tiles for few samples, on 128 x 128 ones for many; the same bits.
+@pytest.mark.parametrize("dtype", [si.BF16, si.F16])
+@pytest.mark.parametrize("T,d,p", [(33, 136, 120), (64, 64, 128), (65, 8, 200), (95, 72, 64)])
+def test_ghost_norms_of_33_to_95_tokens(dtype, T, d, p):
+    from paper_2311_11822_amd import binding as dp
+    dt, tdt = (dp.DP_BF16, torch.bfloat16) if dtype == si.BF16 else (dp.DP_F16, torch.float16)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    a = torch.randn((300, T, d), generator=gen, device="cuda").to(tdt)
+    g = torch.randn((300, T, p), generator=gen, device="cuda").to(tdt)
+
+    def norms(B):
+        desc = dp.layer_array([(a, g, T, d, p, dp.DP_PATH_GHOST)])
+        ws = torch.empty(dp.dp_norms_multi_workspace_bytes(desc, dt, B), dtype=torch.uint8, device="cuda")
+        out = torch.empty((1, B), device="cuda")
+        dp.dp_norms_multi(desc, dt, B, out, ws)
+        return out[0]
+
+    many, few = norms(300), norms(50)
+    assert torch.equal(many[:50], few)
+    want = torch.stack([(a[i].double().t().contiguous() @ g[i].double()).square().sum() for i in range(50)])
+    # exact products; sums of up to 200 columns and T^2 pairs in fp32
+    assert float(((few.double() - want) / want).abs().max()) < 1e-5
