@@ -29,10 +29,10 @@ dp_status check_layer_ptrs(const void* a, const void* g) {
   return DP_OK;
 }
 
-// Ghost layers of more than 32 tokens that the large-tile kernel can address; up to 128 tokens the 128 x 128-tile kernel
+// Ghost layers of more than 64 tokens (wide ones: 32) that the large-tile kernel can address; up to 128 tokens the 128 x 128-tile kernel
 // takes them too (ghost_stays_small), with the same bits.
 bool ghost_uses_big(const dp_layer& ly) {
-  return !ghost_brief_supports(ly.T) && ghost_big_supports(ly.T, ly.d_in, ly.d_out);
+  return !ghost_brief_supports(ly.T) && !ghost_pair_supports(ly.T, ly.d_in, ly.d_out) && ghost_big_supports(ly.T, ly.d_in, ly.d_out);
 }
 
 // Up to 128 tokens a sample is one workgroup in either kernel.  The large-tile kernel keeps deeper prefetch and has a
@@ -43,9 +43,9 @@ bool ghost_uses_big(const dp_layer& ly) {
 // large kernel, 2048 of 392 + 296: 80 and 94; 768 of 760 + 520: 49.5 and 45.9.
 // From 96 tokens on, whole 64-wide k-blocks: the large kernel, which has no edge handling there.
 // Below 96 tokens either kernel pays for 128, so the same rounds; which of them is decided for the call by its widest layer,
-// one launch instead of two.  Norms of 64 tokens, us, small and large kernel: 7 samples of five layers 512 + 512 18.5, 12.3;
-// 4 of 1024 + 3072 .. 4096 66.5, 31.7; 10 of 24 layers 1472 + 4416 .. 5888 94.1, 47.2; 32 of twelve 768 + 2304 .. 3072 59.4, 47.5;
-// 96 of eight 760 + 520 43.1, 38.4; 320 samples of 392 + 296 17.3, 19.7; 2048 of 128 + 384 .. 512 43.9, 52.6.
+// one launch instead of two.  Norms of 80 tokens, us, small and large kernel: 7 samples of five layers 512 + 512 18.7, 12.3;
+// 4 of 1024 + 3072 .. 4096 67.0, 31.8; 10 of 24 layers 1472 + 4416 .. 5888 94.8, 49.1; 32 of twelve 768 + 2304 .. 3072 61.2, 49.1;
+// of 90 tokens: 96 of eight 760 + 520 46.5, 40.1; 320 samples of 392 + 296 17.8, 20.3; 2048 of 128 + 384 .. 512 45.8, 55.9.
 bool ghost_stays_small(const dp_layer& ly, int64_t samples, int64_t widest) {
   if (ly.T > 128 || (ly.T >= 96 && ly.d_in % 64 == 0 && ly.d_out % 64 == 0)) return false;
   const int64_t width = ly.T >= 96 ? (int64_t)ly.d_in + ly.d_out : widest;
@@ -168,8 +168,8 @@ int64_t share_brief_samples(GroupArgs& ga) {
 // Launches the norm kernels of one path for the listed layers, in chunks of kMaxGroup.
 // part_begin[l] is the layer's first slot in the partial-sum workspace.  last_rows: rows of the whole call if these are
 // its last norm launches (0: not); *formed: the last of them formed the factors.
-enum NormKernel { kGhostBig = 0, kGhostSmall = 1, kPerex = 2, kGhostSample = 3, kGhostBrief = 4, kPerexNarrow = 5 };
-constexpr int kNormKernels = 6;
+enum NormKernel { kGhostBig = 0, kGhostSmall = 1, kPerex = 2, kGhostSample = 3, kGhostBrief = 4, kPerexNarrow = 5, kGhostPair = 6 };
+constexpr int kNormKernels = 7;
 
 dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, int n_which,
                         const int64_t* part_begin, dp_dtype dt, int B, float* partials,
@@ -217,13 +217,14 @@ dp_status run_norm_path(NormKernel kernel, const dp_layer* layers, int* which, i
     }
     if (kernel == kGhostBrief) blocks = share_brief_samples(ga);
     ga.total_blocks = (int)blocks;
-    if (kernel == kGhostBrief || kernel == kGhostSample) {       // final norms: nothing to add up
+    if (kernel == kGhostBrief || kernel == kGhostSample || kernel == kGhostPair) {       // final norms: nothing to add up
       if (last_rows && begin + kMaxGroup >= n_which && last_forms_factors(clip, blocks, layers, last_rows, dt, B)) {
         set_group_factors(nc, *clip, blocks, last_rows);
         *formed = true;
       }
-      dp_status st = kernel == kGhostBrief ? launch_ghost_brief_group(ga, sqnorm_out, nc, s)
-                                           : launch_ghost_sample_group(ga, sqnorm_out, nc, s);
+      dp_status st = kernel == kGhostBrief  ? launch_ghost_brief_group(ga, sqnorm_out, nc, s)
+                     : kernel == kGhostPair ? launch_ghost_pair_group(ga, sqnorm_out, nc, s)
+                                            : launch_ghost_sample_group(ga, sqnorm_out, nc, s);
       if (st != DP_OK) return st;
       continue;
     }
@@ -359,6 +360,7 @@ dp_status norms_impl(const dp_layer* layers, int L, dp_dtype dt, int B, float* s
     const bool narrow = perex_narrow_supports(layers[l].T, layers[l].d_in, layers[l].d_out);
     const int k = layers[l].path == DP_PATH_PEREX ? (narrow ? kPerexNarrow : kPerex)
                   : ghost_brief_supports(layers[l].T) ? kGhostBrief
+                  : ghost_pair_supports(layers[l].T, layers[l].d_in, layers[l].d_out) ? kGhostPair
                   : ghost_uses_sample(layers[l])  ? kGhostSample
                   : ghost_uses_big(layers[l]) && !ghost_stays_small(layers[l], samples, widest) ? kGhostBig
                                                                                         : kGhostSmall;

@@ -201,6 +201,9 @@ bool ghost_brief_supports(int T);
 int64_t ghost_brief_blocks(int B, int T, int parts);
 int ghost_brief_max_parts(int B, int T);
 dp_status launch_ghost_brief_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s);
+// 33 to 64 tokens of not too wide layers, a workgroup to a sample (ghost_brief.hip): final norms too.
+bool ghost_pair_supports(int T, int d, int p);
+dp_status launch_ghost_pair_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s);
 // 256x256-tile kernel with direct global->LDS loads (grad_gemm.hip).
 int clipped_grad_big_tiles(int d, int p);
 int64_t clipped_grad_mid_tiles(int d, int p);

@@ -117,7 +117,113 @@ ghost_brief_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int fir
   finish_norms<kThreads>(ga, nc, sqnorm, reinterpret_cast<unsigned*>(rows));
 }
 
+// 33 to 64 tokens: a workgroup to a sample, its rows read once, the three 32 x 32 tiles on and above the diagonal side by
+// side.  Norms, us, on the large-tile kernel (which pays for 128 rows) and here: 48 tokens, 7 samples of five layers 512 + 512
+// 12.3, 7.6; 32 of twelve 768 + 2304 .. 3072 46.9, 28.2; 128 of sixteen 392 + 296 57.1, 46.5.  Like the form above it reads no more than
+// some 28 GB/s a workgroup from memory (twice the loads in flight: the same), so samples of many values stay on large tiles: one
+// of 64 tokens, 20 layers 1792 + 5376 .. 7168, a step 226 us there and 238 here; of 544 + 1632 .. 2176 57.7 and 51.0.
+// Error against 64 bits: 0.6 to 1.1e-7 of the norm, there up to 2.2e-7.
+constexpr int kPairDepth = kDepth / 2;           // of each half: kDepth loads in flight
+template <bool F16>
+__device__ __forceinline__ void gram_parts3(const uint16_t* x, int T, int width, int wave, int lane, f32x16 (&acc)[3]) {
+#pragma unroll
+  for (int n = 0; n < 3; ++n)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[n][r] = 0.f;
+  const int t = lane & 31, u = kRows + t;
+  const uint16_t* rt = x + (size_t)t * width;
+  const uint16_t* ru = x + (size_t)min(u, T - 1) * width;
+  for (int k0 = wave * 16; k0 < width; k0 += kPairDepth * kWaves * 16) {
+    bf16x8 f[kPairDepth], h[kPairDepth];
+#pragma unroll
+    for (int q = 0; q < kPairDepth; ++q) {
+      const int k = k0 + q * kWaves * 16 + 8 * (lane >> 5);
+      uint4 w = make_uint4(0, 0, 0, 0), v = w;
+      if (k < width) w = *reinterpret_cast<const uint4*>(rt + k);
+      if (k < width && u < T) v = *reinterpret_cast<const uint4*>(ru + k);
+      f[q] = __builtin_bit_cast(bf16x8, w);
+      h[q] = __builtin_bit_cast(bf16x8, v);
+    }
+#pragma unroll
+    for (int q = 0; q < kPairDepth; ++q) {
+      acc[0] = mfma16<F16>(f[q], f[q], acc[0]);
+      acc[1] = mfma16<F16>(f[q], h[q], acc[1]);
+      acc[2] = mfma16<F16>(h[q], h[q], acc[2]);
+    }
+  }
+}
+
+template <bool F16>
+__global__ void __launch_bounds__(kThreads)
+ghost_pair_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int first) {
+  __shared__ float part_a[kWaves][16][64], part_g[kWaves][16][64];       // 64 KiB: two workgroups per compute unit
+  __shared__ float wave_sum[kWaves];
+  const int block = first + blockIdx.x;
+  const int l = layer_of(ga, block);
+  const GroupLayer& ly = ga.layer[l];
+  const int T = ly.T, i = block - ly.tile_begin;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const size_t row0 = (size_t)i * T;
+  f32x16 xa[3], xg[3];
+  gram_parts3<F16>(static_cast<const uint16_t*>(ly.a) + row0 * ly.d_in, T, ly.d_in, wave, lane, xa);
+  gram_parts3<F16>(static_cast<const uint16_t*>(ly.g) + row0 * ly.d_out, T, ly.d_out, wave, lane, xg);
+  float sum = 0.f;
+#pragma unroll
+  for (int n = 0; n < 3; ++n) {
+    if (n > 0) __syncthreads();                        // the last tile's parts are read
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      part_a[wave][r][lane] = xa[n][r];
+      part_g[wave][r][lane] = xg[n][r];
+    }
+    __syncthreads();
+    // This thread: registers wave and wave + 8 of lane `lane` of every wave; row 8 (r >> 2) + 4 (lane >> 5) + (r & 3) of one
+    // half, column lane & 31 of the other.  Rows past the sample are zeros, beside an infinity NaN: they stay out.
+    float s = 0.f;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int r = wave + 8 * h;
+      float sa = 0.f, sg = 0.f;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        sa += part_a[w][r][lane];
+        sg += part_g[w][r][lane];
+      }
+      const int row = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), col = lane & 31;
+      const bool in = n == 0 || kRows + (n == 1 ? col : max(row, col)) < T;
+      s = in ? fmaf(sa, sg, s) : s;
+    }
+    sum += n == 1 ? 2.f * s : s;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+  if (lane == 0) wave_sum[wave] = sum;
+  __syncthreads();
+  if (tid == 0) {
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) s += wave_sum[w];
+    store_norm(ga, nc, l, i, s, sqnorm);
+  }
+  finish_norms<kThreads>(ga, nc, sqnorm, reinterpret_cast<unsigned*>(&part_a[0][0][0]));
+}
+
 }  // namespace
+
+bool ghost_pair_supports(int T, int d, int p) {
+  constexpr int64_t kMostValues = 300000;
+  return T > kRows && T <= 2 * kRows && T * ((int64_t)d + p) <= kMostValues;
+}
+
+dp_status launch_ghost_pair_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s) {
+  return launch_in_runs(ga.total_blocks, [&](dim3 grid, int first) {
+    if (ga.f16)
+      hipLaunchKernelGGL(ghost_pair_kernel<true>, grid, dim3(kThreads), 0, s, ga, sqnorm, nc, first);
+    else
+      hipLaunchKernelGGL(ghost_pair_kernel<false>, grid, dim3(kThreads), 0, s, ga, sqnorm, nc, first);
+  });
+}
 
 bool ghost_brief_supports(int T) { return T <= kRows; }
 

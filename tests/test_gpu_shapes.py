@@ -591,9 +591,10 @@ def test_accumulate_rounds_once(dims, T):
         assert torch.equal(x, (y.double() * c.double() + z.double()).float())
 
 
-# Ghost norms of 33 to 95 tokens: on large tiles for few samples, on 128 x 128 ones for many; the same bits.
+# Ghost norms of 33 to 95 tokens: up to 64 in pairs of 32-row tiles unless the layer is wide, beyond on large tiles for few
+# samples and on 128 x 128 ones for many; the same bits for any number of samples.
 @pytest.mark.parametrize("dtype", [si.BF16, si.F16])
-@pytest.mark.parametrize("T,d,p", [(33, 136, 120), (64, 64, 128), (65, 8, 200), (95, 72, 64)])
+@pytest.mark.parametrize("T,d,p", [(33, 136, 120), (47, 8, 520), (64, 64, 128), (64, 4608, 80), (64, 4608, 72), (65, 8, 200), (95, 72, 64)])
 def test_ghost_norms_of_33_to_95_tokens(dtype, T, d, p):
     from paper_2311_11822_amd import binding as dp
     dt, tdt = (dp.DP_BF16, torch.bfloat16) if dtype == si.BF16 else (dp.DP_F16, torch.float16)
@@ -611,5 +612,5 @@ def test_ghost_norms_of_33_to_95_tokens(dtype, T, d, p):
     many, few = norms(300), norms(50)
     assert torch.equal(many[:50], few)
     want = torch.stack([(a[i].double().t().contiguous() @ g[i].double()).square().sum() for i in range(50)])
-    # exact products; sums of up to 200 columns and T^2 pairs in fp32
+    # exact products; sums of up to 4608 columns and T^2 pairs in fp32
     assert float(((few.double() - want) / want).abs().max()) < 1e-5
