@@ -73,6 +73,8 @@ EXPORTS = tuple(_PROTOS)
 for _name, (_res, _args) in _PROTOS.items():
     _fn = getattr(lib, _name)          # AttributeError here = header/library mismatch
     _fn.restype, _fn.argtypes = _res, _args
+    if hasattr(_pycall, _name):        # host arrays by their element type, everything else None
+        _pycall.set_host_arrays(_name, tuple(getattr(t, "_type_", None) if issubclass(t, C._Pointer) else None for t in _args))
 
 
 class DpError(RuntimeError):
@@ -115,11 +117,11 @@ def _check(status: int, where: str) -> None:
 
 
 def _call(name: str, *args) -> None:
-    """Library call `name`; pointers as tensors, addresses, None or ctypes arrays, the stream last."""
+    """Library call `name`; device pointers as tensors, addresses or None, host arrays as ctypes arrays, the stream last."""
     status = getattr(_pycall, name)(*args)
     if status is None:                     # something that the native conversion leaves to ctypes
         fn = getattr(lib, name)
-        status = fn(*[_ptr(x) if t is _vp and not isinstance(x, C.Array) else x for x, t in zip(args[:-1], fn.argtypes)],
+        status = fn(*[_ptr(x) if t is _vp else x for x, t in zip(args[:-1], fn.argtypes)],
                     _stream(args[-1]))
     if status:
         raise DpError(status, name)

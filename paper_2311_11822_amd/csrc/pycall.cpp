@@ -4,11 +4,14 @@
 // through ctypes and here: two micro-batches of 32 layers with biases, 18 x 45 tokens 690, 602; of 20 layers, 11 x 32 442, 388;
 // a step of ten 64 x 64 layers, one sample of two tokens 19.8, 18.7.
 //
-// Pointers take what the Python side always took: a tensor (its data_ptr()), an address, None, or a ctypes array; the last
-// argument is the stream, None for torch's current one.  Arguments of another kind make the call return None before
-// anything happened, and the caller takes the general path.  The interpreter's lock is released during the call.
+// Device pointers take a tensor (its data_ptr()), an address or None; host arrays a ctypes array of the prototype's own element
+// type or None (which pointer is which, a C type cannot tell: set_host_arrays); the last argument is the stream, None for
+// torch's current one.  Arguments of another kind make the call return None before anything happened, and the caller takes
+// the general path, which refuses what ctypes refuses.  The interpreter's lock is released during the call.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
+
+#include <string.h>
 
 #include <tuple>
 #include <type_traits>
@@ -18,7 +21,7 @@
 
 namespace {
 
-PyObject* data_ptr_name;
+PyObject *data_ptr_name, *type_name;
 PyTypeObject* array_type;                     // ctypes.Array
 PyObject *torch_c, *device_name, *stream_name;     // torch's module of private functions; null until its GPU side is up
 
@@ -37,18 +40,24 @@ bool as_address(PyObject* x, Address& out) {
     out.p = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(x);
     return true;
   }
-  if (array_type && PyObject_TypeCheck(x, array_type)) {
-    if (PyObject_GetBuffer(x, &out.view, PyBUF_SIMPLE) != 0) return false;
-    out.held = true;
-    out.p = out.view.buf;
-    return true;
-  }
   PyObject* r = PyObject_CallMethodNoArgs(x, data_ptr_name);
   if (!r) return false;
   const bool ok = PyLong_Check(r);
   if (ok) out.p = (void*)(uintptr_t)PyLong_AsUnsignedLongLongMask(r);
   Py_DECREF(r);
   return ok;
+}
+
+// A ctypes array whose elements are of type `element`.
+bool as_host_array(PyObject* x, PyObject* element, Address& out) {
+  if (x == Py_None) return true;
+  if (!array_type || !PyObject_TypeCheck(x, array_type)) return false;
+  PyObject* type = PyObject_GetAttr(reinterpret_cast<PyObject*>(Py_TYPE(x)), type_name);
+  Py_XDECREF(type);                            // (the array's type holds it)
+  if (type != element || PyObject_GetBuffer(x, &out.view, PyBUF_SIMPLE) != 0) return false;
+  out.held = true;
+  out.p = out.view.buf;
+  return true;
 }
 
 bool as_stream(PyObject* x, Address& out) {
@@ -67,7 +76,7 @@ bool as_stream(PyObject* x, Address& out) {
 template <class T>
 struct Value {
   T v{};
-  bool set(PyObject* x) {
+  bool set(PyObject* x, PyObject*) {
     if constexpr (std::is_floating_point_v<T>) {
       if (!PyFloat_Check(x) && !PyLong_Check(x)) return false;
       const double d = PyFloat_AsDouble(x);
@@ -84,7 +93,7 @@ struct Value {
 template <class T>
 struct Value<T*> {
   Address a;
-  bool set(PyObject* x) { return as_address(x, a); }
+  bool set(PyObject* x, PyObject* element) { return element ? as_host_array(x, element, a) : as_address(x, a); }
   T* get() const { return static_cast<T*>(a.p); }
 };
 
@@ -93,10 +102,12 @@ struct Call;
 template <class... A, dp_status (*F)(A...)>
 struct Call<F> {
   static constexpr Py_ssize_t N = sizeof...(A);
+  static inline PyObject* element[N];         // of the arguments that are host arrays; null: not one
+  static inline bool known = false;
   template <size_t... I>
   static PyObject* run(PyObject* const* args, std::index_sequence<I...>) {
     std::tuple<Value<A>...> v;
-    const bool ok = ((I + 1 == N ? as_stream(args[I], address(std::get<I>(v))) : std::get<I>(v).set(args[I])) && ...);
+    const bool ok = ((I + 1 == N ? as_stream(args[I], address(std::get<I>(v))) : std::get<I>(v).set(args[I], element[I])) && ...);
     if (!ok) {
       PyErr_Clear();
       Py_RETURN_NONE;
@@ -115,8 +126,18 @@ struct Call<F> {
     return none;
   }
   static PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t n) {
-    if (n != N) Py_RETURN_NONE;
+    if (n != N || !known) Py_RETURN_NONE;
     return run(args, std::make_index_sequence<N>{});
+  }
+  static bool set_elements(PyObject* types) {
+    if (!PyTuple_Check(types) || PyTuple_GET_SIZE(types) != N) return false;
+    for (Py_ssize_t i = 0; i < N; ++i) {
+      PyObject* t = PyTuple_GET_ITEM(types, i);
+      Py_XDECREF(element[i]);
+      element[i] = t == Py_None ? nullptr : t;
+      Py_XINCREF(element[i]);
+    }
+    return known = true;
   }
 };
 
@@ -135,23 +156,40 @@ PyObject* set_torch(PyObject*, PyObject* module) {
   Py_RETURN_NONE;
 }
 
-#define DP_CALL(name) {#name, (PyCFunction)(void (*)(void))Call<name>::call, METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {DP_CALL(dp_ghost_norm),
-                         DP_CALL(dp_perex_norm),
-                         DP_CALL(dp_clip_factors),
-                         DP_CALL(dp_clipped_grad),
-                         DP_CALL(dp_add_noise),
-                         DP_CALL(dp_norms_multi),
-                         DP_CALL(dp_clipped_grad_multi),
-                         DP_CALL(dp_clipped_grad_noise_multi),
-                         DP_CALL(dp_clipped_grad_noise_multi_h16),
-                         DP_CALL(dp_bias_norm),
-                         DP_CALL(dp_clipped_bias_grad),
-                         DP_CALL(dp_norms_multi_keep),
-                         DP_CALL(dp_clipped_grad_kept_multi),
-                         DP_CALL(dp_private_step_multi),
-                         DP_CALL(dp_layerwise_clipped_grad),
+#define DP_CALLS(X) \
+  X(dp_ghost_norm) \
+  X(dp_perex_norm) \
+  X(dp_clip_factors) \
+  X(dp_clipped_grad) \
+  X(dp_add_noise) \
+  X(dp_norms_multi) \
+  X(dp_clipped_grad_multi) \
+  X(dp_clipped_grad_noise_multi) \
+  X(dp_clipped_grad_noise_multi_h16) \
+  X(dp_bias_norm) \
+  X(dp_clipped_bias_grad) \
+  X(dp_norms_multi_keep) \
+  X(dp_clipped_grad_kept_multi) \
+  X(dp_private_step_multi) \
+  X(dp_layerwise_clipped_grad)
+
+// set_host_arrays(name, types): for each argument of call `name` the ctypes type of the host array's elements, or None.
+PyObject* set_host_arrays(PyObject*, PyObject* args) {
+  const char* name;
+  PyObject* types;
+  if (!PyArg_ParseTuple(args, "sO", &name, &types)) return nullptr;
+  bool ok = false;
+#define DP_SET(f) \
+  if (!strcmp(name, #f)) ok = Call<f>::set_elements(types);
+  DP_CALLS(DP_SET)
+#undef DP_SET
+  return PyBool_FromLong(ok);
+}
+
+#define DP_METHOD(f) {#f, (PyCFunction)(void (*)(void))Call<f>::call, METH_FASTCALL, nullptr},
+PyMethodDef methods[] = {DP_CALLS(DP_METHOD)
                          {"set_array_type", set_array_type, METH_O, nullptr},
+                         {"set_host_arrays", set_host_arrays, METH_VARARGS, nullptr},
                          {"set_torch", set_torch, METH_O, nullptr},
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_pycall", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
@@ -160,7 +198,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_pycall", nullptr, -1, methods, nu
 
 PyMODINIT_FUNC PyInit__pycall(void) {
   data_ptr_name = PyUnicode_InternFromString("data_ptr");
+  type_name = PyUnicode_InternFromString("_type_");
   device_name = PyUnicode_InternFromString("_cuda_getDevice");
   stream_name = PyUnicode_InternFromString("_cuda_getCurrentRawStream");
-  return data_ptr_name && device_name && stream_name ? PyModule_Create(&module) : nullptr;
+  return data_ptr_name && type_name && device_name && stream_name ? PyModule_Create(&module) : nullptr;
 }

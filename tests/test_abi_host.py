@@ -262,3 +262,58 @@ def test_native_argument_conversion(dp):
         dp.dp_clip_factors(16, 1, 1, dp.DP_CLIP_STANDARD, "R", 0.01, 16, None, 0)
     with pytest.raises(AttributeError):
         dp.dp_bias_norm(np.zeros(64, dtype=np.float32), dp.DP_F32, 1, 1, 64, 16, 16, stream=0)    # host memory, no data_ptr
+
+
+def native_calls(dp):
+    """Every call with native argument conversion, by arguments that ctypes takes and the library refuses (B = 0)."""
+    import ctypes as C
+    layers, grads, offs = dp.layer_array([(16, 16, 4, 8, 8, 0)]), (C.c_void_p * 1)(16), (C.c_uint64 * 1)(0)
+    return {
+        "dp_ghost_norm": dict(a=16, g=16, dt=1, B=0, T=4, d_in=8, d_out=8, sqnorm_out=16, ws=None),
+        "dp_perex_norm": dict(a=16, g=16, dt=1, B=0, T=4, d_in=8, d_out=8, sqnorm_out=16, ws=None),
+        "dp_clip_factors": dict(sqnorm=16, L=1, B=0, mode=0, R=1.0, stability=0.01, C_out=16, norm_out=None),
+        "dp_clipped_grad": dict(a=16, g=16, dt=1, B=0, T=4, d_in=8, d_out=8, Cf=16, grad=16),
+        "dp_add_noise": dict(grad_slice=16, global_offset=0, count=4, sigma=-1.0, R=1.0, seed=0, step=0),
+        "dp_norms_multi": dict(layers=layers, dt=1, B=0, sqnorm_out=16, ws=None),
+        "dp_clipped_grad_multi": dict(layers=layers, dt=1, B=0, Cf=16, grads=grads),
+        "dp_clipped_grad_noise_multi": dict(layers=layers, dt=1, B=0, Cf=16, grads=grads, grad_offset=offs, accumulate=0,
+                                            shard_offset=0, shard_count=4, sigma=1.0, R=1.0, seed=0, step=0),
+        "dp_clipped_grad_noise_multi_h16": dict(layers=layers, dt=1, B=0, Cf=16, grads16=grads, grad_offset=offs, accumulate=0,
+                                                shard_offset=0, shard_count=4, sigma=1.0, R=1.0, seed=0, step=0),
+        "dp_bias_norm": dict(g=16, dt=1, B=0, T=4, d_out=8, colsum=16, sqnorm_out=16),
+        "dp_clipped_bias_grad": dict(colsum=16, B=0, d_out=8, Cf=16, grad_b=16),
+        "dp_norms_multi_keep": dict(layers=layers, dt=1, B=0, sqnorm_out=16, kept=grads, ws=None),
+        "dp_clipped_grad_kept_multi": dict(layers=layers, dt=1, B=0, Cf=16, kept=grads, grads=grads, grad_offset=offs,
+                                           accumulate=0, shard_offset=0, shard_count=4, sigma=1.0, R=1.0, seed=0, step=0),
+        "dp_private_step_multi": dict(layers=layers, dt=1, B=0, mode=0, R=1.0, stability=0.01, kept=grads, grads=grads,
+                                      grad_offset=offs, accumulate=0, shard_offset=0, shard_count=4, sigma=1.0, seed=0, step=0,
+                                      sqnorm_out=16, C_out=16, norm_out=None, ws=None, counter=None),
+        "dp_layerwise_clipped_grad": dict(layers=layers, dt=1, B=0, R=[1.0], mode=0, stability=0.01, grads=grads,
+                                          grad_offset=offs, accumulate=0, shard_offset=0, shard_count=4, sigma=1.0, seed=0,
+                                          step=0, sqnorm_out=16, C_out=16, ws=None),
+    }
+
+
+HOST_ARRAYS = ("layers", "grads", "grads16", "kept", "grad_offset")
+DEVICE_POINTERS = ("a", "g", "sqnorm_out", "sqnorm", "C_out", "norm_out", "Cf", "grad", "grad_slice", "colsum", "grad_b", "counter")
+
+
+def test_arrays_are_taken_where_and_as_ctypes_takes_them(dp):
+    """A host array is no device pointer, and its elements are of the prototype's type; nothing is read of one that is not."""
+    import ctypes as C
+    calls = native_calls(dp)
+    assert set(calls) == {n for n in dir(dp._pycall) if n.startswith("dp_")}
+    wrong = {"layers": [C.c_uint8, C.c_void_p], "grad_offset": [C.c_uint32, C.c_float, C.c_void_p]}
+    for name, args in calls.items():
+        call = getattr(dp, name)
+        with pytest.raises(dp.DpError) as e:
+            call(**args, stream=0)
+        assert e.value.status == dp.DP_ERR_INVALID_ARG, name
+        for key in args:
+            if key in HOST_ARRAYS:
+                for t in wrong.get(key, [C.c_uint32, C.c_float, C.c_uint64, dp.dp_layer]):
+                    with pytest.raises(C.ArgumentError):
+                        call(**dict(args, **{key: (t * 1)()}), stream=0)
+            if key in DEVICE_POINTERS:
+                with pytest.raises(AttributeError):
+                    call(**dict(args, **{key: (C.c_float * 64)()}), stream=0)
