@@ -17,9 +17,11 @@ if not os.path.exists(LIB_PATH):
 
 lib = C.CDLL(LIB_PATH)
 
-from . import _pycall  # noqa: E402  (the same library's calls with native argument conversion, built with it)
-
-_pycall.set_array_type(C.Array)
+try:                               # the same library's calls with native argument conversion, built beside it
+    from . import _pycall
+    _pycall.set_array_type(C.Array)
+except ImportError:                # not built, or for another interpreter: every call goes through ctypes
+    _pycall = None
 
 DP_OK, DP_ERR_INVALID_ARG, DP_ERR_UNSUPPORTED, DP_ERR_WORKSPACE, DP_ERR_HIP = range(5)
 DP_F32, DP_BF16, DP_F16 = 0, 1, 2
@@ -100,7 +102,8 @@ def _stream(stream) -> Optional[int]:
         # of one small layer makes three calls in 30 us); private to torch, so not taken for granted
         try:
             handle = torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-            _pycall.set_torch(torch._C)        # its calls look there themselves from now on
+            if _pycall:
+                _pycall.set_torch(torch._C)    # its calls look there themselves from now on
             return handle
         except AttributeError:
             pass
@@ -118,7 +121,7 @@ def _check(status: int, where: str) -> None:
 
 def _call(name: str, *args) -> None:
     """Library call `name`; device pointers as tensors, addresses or None, host arrays as ctypes arrays, the stream last."""
-    status = getattr(_pycall, name)(*args)
+    status = getattr(_pycall, name)(*args) if _pycall else None
     if status is None:                     # something that the native conversion leaves to ctypes
         fn = getattr(lib, name)
         status = fn(*[_ptr(x) if t is _vp else x for x, t in zip(args[:-1], fn.argtypes)],

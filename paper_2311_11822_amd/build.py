@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -10,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdp_bk.so")
-PYCALL = os.path.join(HERE, "_pycall.so")          # the library's calls for Python
+PYCALL = os.path.join(HERE, "_pycall" + sysconfig.get_config_var("EXT_SUFFIX"))     # the library's calls for this Python
 SOURCES = ["dp_api.hip", "noise.hip", "clip.hip", "fp32_kernels.hip", "ghost.hip", "tn_gemm.hip", "grad_gemm.hip", "grad_packed.hip", "ghost_big.hip", "ghost_brief.hip", "bias.hip", "layerwise.hip", "kept.hip", "ghost_sample.hip", "perex_dma.hip", "perex_narrow.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -42,11 +43,23 @@ def build(verbose: bool = False) -> str:
         objs.append(obj)
     link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(link, check=True)
-    subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall",
-                    "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"],
+    build_pycall()
+    return LIB
+
+
+def build_pycall() -> None:
+    """The calls with native argument conversion.  Without Python's headers or a host compiler there are none, and the
+    binding goes through ctypes."""
+    cxx, headers = shutil.which(os.environ.get("CXX", "g++")), sysconfig.get_paths()["include"]
+    if os.path.exists(PYCALL):
+        os.remove(PYCALL)                                # never one of another build beside the library
+    if not cxx or not os.path.exists(os.path.join(headers, "Python.h")):
+        print(f"{os.path.basename(PYCALL)} not built: no host C++ compiler or no Python.h; the binding uses ctypes", file=sys.stderr)
+        return
+    subprocess.run([cxx, "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall",
+                    "-I", os.path.join(ROOT, "include"), "-I", headers,
                     os.path.join(CSRC, "pycall.cpp"), "-o", PYCALL, "-L", HERE, "-l:libdp_bk.so", "-Wl,-rpath,$ORIGIN"],
                    check=True)
-    return LIB
 
 
 if __name__ == "__main__":

@@ -302,7 +302,7 @@ def test_arrays_are_taken_where_and_as_ctypes_takes_them(dp):
     """A host array is no device pointer, and its elements are of the prototype's type; nothing is read of one that is not."""
     import ctypes as C
     calls = native_calls(dp)
-    assert set(calls) == {n for n in dir(dp._pycall) if n.startswith("dp_")}
+    assert not dp._pycall or set(calls) == {n for n in dir(dp._pycall) if n.startswith("dp_")}
     wrong = {"layers": [C.c_uint8, C.c_void_p], "grad_offset": [C.c_uint32, C.c_float, C.c_void_p]}
     for name, args in calls.items():
         call = getattr(dp, name)
@@ -317,3 +317,21 @@ def test_arrays_are_taken_where_and_as_ctypes_takes_them(dp):
             if key in DEVICE_POINTERS:
                 with pytest.raises(AttributeError):
                     call(**dict(args, **{key: (C.c_float * 64)()}), stream=0)
+
+
+def test_calls_without_the_native_conversion(dp, monkeypatch):
+    """A library that was built without it, or for another Python, is called through ctypes alone."""
+    import subprocess
+    import sys
+    code = ("import sys; sys.modules['paper_2311_11822_amd._pycall'] = None\n"            # its import fails
+            "from paper_2311_11822_amd import binding as dp\n"
+            "assert dp._pycall is None and dp.dp_version() >= 100\n"
+            "try: dp.dp_bias_norm(None, 1, 4, 8, 64, None, None, stream=0)\n"
+            "except dp.DpError as e: assert e.status == dp.DP_ERR_INVALID_ARG\n"
+            "else: assert False")
+    subprocess.run([sys.executable, "-c", code], cwd=ROOT, check=True)
+    monkeypatch.setattr(dp, "_pycall", None)
+    for name, args in native_calls(dp).items():
+        with pytest.raises(dp.DpError) as e:
+            getattr(dp, name)(**args, stream=0)
+        assert e.value.status == dp.DP_ERR_INVALID_ARG, name
