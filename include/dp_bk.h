@@ -332,6 +332,8 @@ dp_status dp_private_step_multi(const dp_layer* layers, int L, dp_dtype dt, int 
  * 128 x 128), of up to 512 tokens, is done in ONE kernel that reads a and g once if the whole stack is
  * such layers or more than 64 MiB of G_i are saved so: per sample it
  * forms G_i = a_i^T g_i in registers, takes ||G_i||, C_i = clip(||G_i||; R_l) and adds C_i G_i.
+ * Squared norms and factors are the same bits either way, and those of dp_norms_multi; the order in which
+ * samples are added to a gradient is not.
  * Any other layer on the instantiated path keeps its G_i ([B, d_in, d_out] fp32) in the workspace
  * between its norm kernel and a weighted sum, as dp_norms_multi_keep + dp_clipped_grad_kept_multi
  * do, so its a and g are read once as well; layers are given room in stack order up to 2 GiB in

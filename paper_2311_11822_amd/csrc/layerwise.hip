@@ -9,7 +9,8 @@
 // One workgroup owns (layer, chunk of consecutive samples).  Per sample it runs the token
 // contraction of the instantiated-norm kernel (tn_tile.h machinery) into one accumulator set,
 // reduces the sum of squares over the workgroup in a fixed order, and adds C_i times the
-// accumulators to a second set.  The chunk's weighted sum goes to a workspace; a second small
+// accumulators to a second set.  The norm is added up in the order of the kernel that takes the layer elsewhere, the same bits:
+// which of the two forms a layer takes is a matter of its stack, its norm and factor are not.  The chunk's weighted sum goes to a workspace; a second small
 // kernel adds the chunks in order, adds the noise of eq. (1) and writes the gradient.  No
 // atomics: the result is deterministic.
 #include "clip.h"
@@ -20,17 +21,26 @@ namespace dpbk {
 
 namespace {
 
+typedef __attribute__((ext_vector_type(4))) float f32x4v;
+
 struct FusedArgs {
   int mode;
   float stability;
   float R[kMaxGroup];            // threshold of each layer of the launch
 };
 
+// One step of two butterfly sums at once: that of x stays in the lanes without bit OFF, that of y in those with it.
+template <int OFF>
+__device__ __forceinline__ float halves_sum(float x, float y, int lane) {
+  const bool upper = lane & OFF;
+  return (upper ? y : x) + __shfl_xor(upper ? x : y, OFF);
+}
+
 // GroupLayer fields as used here: tile_begin = first workgroup of the layer, tiles_per_sample =
 // number of sample chunks, part_begin = float offset of the layer's [chunks][d_in * d_out]
 // partial sums in the workspace, sq_index = row of sqnorm / C.
 template <class S, bool F16>
-__global__ void __launch_bounds__(S::NT)
+__global__ void __launch_bounds__(S::NT, 2 * S::LDS_BYTES <= 163840 ? 2 : 1)
 layerwise_fused_kernel(const GroupArgs ga, const FusedArgs fa, float* __restrict__ partial,
                        float* __restrict__ sqnorm, float* __restrict__ C_out) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
@@ -49,8 +59,17 @@ layerwise_fused_kernel(const GroupArgs ga, const FusedArgs fa, float* __restrict
   t.m0 = 0;
   t.n0 = 0;
   const int nkb = (ly.T + S::BK - 1) / S::BK;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  constexpr int NW = S::WM * S::WN;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int wm = (wave / S::WN) * S::WTM, wn = (wave % S::WN) * S::WTN;
+  const int row0 = wm + (lane & 31), col0 = wn + 4 * (lane >> 5);       // the lane's first element
+  // How the sums of squares of the 32 x 32 tiles go together: a 128 x 128 tile of perex_dma.hip wave by wave (kTile); the
+  // four waves of perex_narrow.hip with 32 rows (kStrips), 32 columns (kFlat) or 32 x 64 each (kHalves).
+  static_assert(S::TM == 2 && S::TN == 2 && S::WM == 2, "order of sums");
+  enum { kTile, kStrips, kFlat, kHalves };
+  const int order = ly.d_in > 64 && ly.d_out > 64                        ? kTile
+                    : ly.d_out <= 32 || (ly.d_in > 32 && ly.d_out <= 64) ? kStrips
+                    : ly.d_in <= 32                                      ? kFlat
+                                                                         : kHalves;
   float* red = reinterpret_cast<float*>(lds);
 
   f32x16 total[S::TM][S::TN];
@@ -64,25 +83,44 @@ layerwise_fused_kernel(const GroupArgs ga, const FusedArgs fa, float* __restrict
     for (int kb = 0, stage = 0; kb < nkb; ++kb, stage ^= 1) {
       const bool more = kb + 1 < nkb;
       if (more) t.gload(i, kb + 1);
-      t.template compute<F16>(lds + stage * S::STAGE, acc);
+      t.template compute<F16, true>(lds + stage * S::STAGE, acc);
       if (more) t.lds_store(lds + (stage ^ 1) * S::STAGE);
       __syncthreads();
     }
-    // ||G_i||_F^2: rows and columns past the layer's edge were loaded as zeros and add nothing
-    float s = 0.f;
+    // ||G_i||_F^2.  Rows and columns past the layer's edge were loaded as zeros and add nothing, unless an infinity of the other
+    // operand made NaN of them: then they are taken out and it is added up again.
+    float sq;
+    for (bool again = false;; again = true) {
+      float part[4], s = 0.f;
 #pragma unroll
-    for (int im = 0; im < S::TM; ++im)
+      for (int n = 0; n < 4; ++n) {
+        if (n == 0 || (n % S::TN == 0 ? order != kTile : order == kFlat)) s = 0.f;
 #pragma unroll
-      for (int jn = 0; jn < S::TN; ++jn)
+        for (int r = 0; r < 16; ++r) s = fmaf(acc[n / S::TN][n % S::TN][r], acc[n / S::TN][n % S::TN][r], s);
+        part[n] = s;
+      }
+      const float first = part[order == kFlat ? 0 : 1], second = order == kFlat ? part[1] : part[3];
+      float v = halves_sum<32>(first, second, lane);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s = fmaf(acc[im][jn][r], acc[im][jn][r], s);
+      for (int off = 16; off > 0; off >>= 1) v += __shfl_xor(v, off);
+      if ((lane & 31) == 0) red[2 * wave + (lane >> 5)] = v;        // every LDS read of the loop is behind a barrier
+      __syncthreads();
+      if (order == kTile)                        // same order in every thread
+        sq = red[1] + red[3] + red[5] + red[7];
+      else if (order == kStrips)
+        sq = (red[0] + red[1]) + (red[4] + red[5]);
+      else if (order == kFlat)
+        sq = (red[0] + red[1]) + (red[2] + red[3]);
+      else
+        sq = (red[0] + red[2]) + (red[1] + red[3]);
+      if (sq == sq || again) break;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    if (lane == 0) red[wave] = s;                  // every LDS read of the loop is behind a barrier
-    __syncthreads();
-    float sq = 0.f;
+      for (int n = 0; n < 4; ++n)
 #pragma unroll
-    for (int w = 0; w < NW; ++w) sq += red[w];     // same order in every thread
+        for (int r = 0; r < 16; ++r)
+          if (row0 + n / S::TN * 32 >= ly.d_in || col0 + n % S::TN * 32 + 8 * (r >> 2) >= ly.d_out) acc[n / S::TN][n % S::TN][r] = 0.f;
+      __syncthreads();                             // red is read
+    }
     __syncthreads();                               // red is overwritten by the next sample's tiles
     const float c = clip_factor(norm_of(sq), fa.mode, fa.R[l], fa.stability);
     if (threadIdx.x == 0) {
@@ -100,19 +138,18 @@ layerwise_fused_kernel(const GroupArgs ga, const FusedArgs fa, float* __restrict
   }
 
   // the chunk's weighted sum, [d_in, d_out] row-major
-  const int wm = (wave / S::WN) * S::WTM, wn = (wave % S::WN) * S::WTN;
   float* out = partial + ly.part_begin + (size_t)chunk * ly.d_in * ly.d_out;
 #pragma unroll
   for (int im = 0; im < S::TM; ++im)
 #pragma unroll
-    for (int jn = 0; jn < S::TN; ++jn) {
-      const int col = wn + jn * 32 + (lane & 31);
+    for (int jn = 0; jn < S::TN; ++jn)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = wm + im * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        if (row < ly.d_in && col < ly.d_out) out[(size_t)row * ly.d_out + col] = total[im][jn][r];
+      for (int q = 0; q < 4; ++q) {
+        const int row = row0 + im * 32, col = col0 + jn * 32 + 8 * q;
+        if (row < ly.d_in && col < ly.d_out)
+          *reinterpret_cast<f32x4v*>(out + (size_t)row * ly.d_out + col) =
+              f32x4v{total[im][jn][4 * q], total[im][jn][4 * q + 1], total[im][jn][4 * q + 2], total[im][jn][4 * q + 3]};
       }
-    }
 }
 
 // grad[e] (+)= sum over the layer's chunks, in chunk order, (+ noise of eq. (1) at the element's

@@ -89,7 +89,9 @@ struct TnTile {
     }
   }
 
-  template <bool F16>
+  // TRANSPOSED: lane l holds row l & 31 of a 32 x 32 tile and columns 8 q + 4 (l >> 5) + e in register 4 q + e; else rows
+  // and columns the other way round.
+  template <bool F16, bool TRANSPOSED = false>
   __device__ __forceinline__ void compute(const uint16_t* stage, f32x16 (&acc)[S::TM][S::TN]) const {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = (wave / S::WN) * S::WTM, wn = (wave % S::WN) * S::WTN;
@@ -106,7 +108,7 @@ struct TnTile {
       for (int i = 0; i < S::TM; ++i)
 #pragma unroll
         for (int j = 0; j < S::TN; ++j)
-          acc[i][j] = mfma16<F16>(fa[i], fb[j], acc[i][j]);
+          acc[i][j] = TRANSPOSED ? mfma16<F16>(fb[j], fa[i], acc[i][j]) : mfma16<F16>(fa[i], fb[j], acc[i][j]);
     }
   }
 };

@@ -614,3 +614,42 @@ def test_ghost_norms_of_33_to_95_tokens(dtype, T, d, p):
     want = torch.stack([(a[i].double().t().contiguous() @ g[i].double()).square().sum() for i in range(50)])
     # exact products; sums of up to 4608 columns and T^2 pairs in fp32
     assert float(((few.double() - want) / want).abs().max()) < 1e-5
+
+
+# A layer's norms and factors in the layer-wise pass are the same bits in either form of it, so that they do not depend on the
+# stack: one layer that the one-kernel form cannot take sends few samples to the other.  Every way in which the other
+# form's kernels add up (a 128 x 128 tile; 32 rows, 32 columns or 32 x 64 to a wave; several narrow tiles), with and without
+# padding beside an infinity.
+SQUARES = [(128, 128), (128, 96), (72, 128), (104, 72), (64, 64), (128, 16), (16, 24), (128, 64), (40, 56), (24, 128), (32, 40),
+           (8, 72), (40, 72), (64, 128), (48, 104)]
+
+
+@pytest.mark.parametrize("dtype", [si.BF16, si.F16])
+@pytest.mark.parametrize("B,T,dims", [(5, 1, SQUARES), (5, 33, SQUARES), (5, 100, SQUARES), (300, 70, SQUARES[:4]),
+                                      (300, 40, SQUARES[4:9]), (5, 100, [(512, 32), (160, 8), (264, 16), (400, 24)]),
+                                      (5, 70, [(32, 512), (8, 160), (16, 264), (24, 400)])])
+def test_layerwise_norms_do_not_depend_on_the_stack(dtype, B, T, dims):
+    from paper_2311_11822_amd import binding as dp
+    from paper_2311_11822_amd.pipeline import BkPipeline
+    tdt = torch.bfloat16 if dtype == si.BF16 else torch.float16
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    layers = [tuple((torch.randn((B, T, n), generator=gen, device="cuda") * s).to(tdt) for n, s in ((d, 1.0), (p, 0.01)))
+              for d, p in dims + [(128, 136)]]
+    for a, g in layers:
+        a[0, 0, 0] = g[4, T - 1, -1] = float("inf")
+    got = []
+    for stack in (layers[:-1], layers):
+        pipe = BkPipeline(stack, paths=[dp.DP_PATH_PEREX] * len(stack))
+        pipe.set_groups(list(range(pipe.L)), [0.5] * pipe.L)
+        pipe.layerwise_step(dp.DP_CLIP_STANDARD, 0.01, 0.0, 1, 0, 0, pipe.psi)
+        got.append((pipe.sqnorm[:len(dims)].clone(), pipe.C_groups[:len(dims)].clone()))
+        assert all(torch.isfinite(x).all() for x in pipe.grads)
+        assert torch.isposinf(pipe.sqnorm[:, [0, 4]]).all() and (pipe.C_groups[:, [0, 4]] == 0).all()
+        for l, ((a, g), x) in enumerate(zip(stack, pipe.grads)):
+            each = torch.stack([a[i].double().t().contiguous() @ g[i].double() for i in range(B) if i not in (0, 4)])
+            factor = torch.cat([pipe.C_groups[l, 1:4], pipe.C_groups[l, 5:]]).double()
+            ref = (each * factor[:, None, None]).sum(0)
+            assert float((x.double() - ref).norm() / ref.norm()) < 3e-6       # sums of T rows and B samples in fp32
+        pipe.norms()
+        assert torch.equal(pipe.sqnorm[:len(dims)], got[-1][0])
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
