@@ -329,8 +329,8 @@ dp_status dp_private_step_multi(const dp_layer* layers, int L, dp_dtype dt, int 
  * gradients (+ noise) before the next is touched, so a pass's a and g are still in the
  * memory-side cache when the gradient kernels read them again.  A layer on the instantiated
  * path (path == DP_PATH_PEREX, 16-bit storage) whose whole gradient fits one workgroup tile (up to
- * 128 x 128), of up to 512 tokens, is done in ONE kernel that reads a and g once if the whole stack is
- * such layers or more than 64 MiB of G_i are saved so: per sample it
+ * 128 x 128, 512 x 32 or 32 x 512) is done, where that is estimated to be faster for the stack, in ONE
+ * kernel that reads a and g once: per sample it
  * forms G_i = a_i^T g_i in registers, takes ||G_i||, C_i = clip(||G_i||; R_l) and adds C_i G_i.
  * Squared norms and factors are the same bits either way, and those of dp_norms_multi; the order in which
  * samples are added to a gradient is not.

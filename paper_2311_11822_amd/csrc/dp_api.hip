@@ -998,7 +998,7 @@ constexpr int64_t kLastPassTiles = 512;
 
 // Which layers the one-pass kernel takes, and its sample chunks.
 struct FusedPlan {
-  std::vector<char> fused;       // per layer
+  std::vector<int> shape;        // per layer: shape class or -1
   int n_fused = 0;
   int chunks = 1;                // sample chunks per fused layer
   int64_t floats = 0;            // partial sums of all fused layers
@@ -1011,45 +1011,76 @@ struct FusedPlan {
 };
 constexpr int64_t kKeptMaxBytes = (int64_t)2 << 30;
 
+// The one-pass kernel saves writing and reading the per-sample gradients, but a workgroup goes through its samples one after
+// the other with one k-block in flight, and it takes two launches for each shape.  Norms and factors are the same bits in
+// either form, so the choice is by estimated time (us).  Steps in either form of 855 stacks of one shape or of adapter pairs, 8 to
+// 4096 samples of 16 to 2048 tokens: the estimate's choice is 0.2 % above the faster one, 29 % at worst (one form for all: 17
+// and 33 % above, 4 and 7.5 times as long at worst).  Fused and apart, some of them: eight layers 128 x 128, 8 x 256 tokens 14.8,
+// 15.7; 8 x 2048 35.8, 24.9; 64 x 512 32.4, 40.5; 1024 x 1024 801, 1023; two of 256 x 8, 1024 x 128 52, 105, 8192 x 512
+// 1101, 1620; six pairs 192 x 32, 256 x 128 131, 69; 16 of 512 x 16, 4096 x 128 1640, 2360.
+bool one_pass_is_faster(const dp_layer* layers, const std::vector<int>& shape, int B, int chunks) {
+  const int per = (B + chunks - 1) / chunks;
+  double serial[3] = {}, longest[3] = {}, norms = 0, read_mb = 0, kept_mb = 0, room_mb = 0;
+  bool others = false, kept_others = false;
+  for (size_t l = 0; l < shape.size(); ++l) {
+    const dp_layer& ly = layers[l];
+    const double own_mb = (double)B * ly.d_in * ly.d_out * 4e-6;
+    if (ly.path == DP_PATH_PEREX) room_mb += own_mb;
+    if (shape[l] < 0) {
+      others = true;
+      kept_others = kept_others || ly.path == DP_PATH_PEREX;
+      continue;
+    }
+    const double blocks = (ly.T + 63) / 64, chunk = per * (shape[l] == 0 ? 1.3 + 1.04 * blocks : 2.0 + 1.6 * blocks);
+    longest[shape[l]] = std::max(longest[shape[l]], chunk);
+    serial[shape[l]] += chunks * chunk / 256;
+    norms += (double)B * perex_tiles_per_sample(ly.d_in, ly.d_out) * (3.2 + 0.0056 * ly.T) / 768;
+    read_mb += (double)B * ly.T * (ly.d_in + ly.d_out) * 2e-6;
+    kept_mb += own_mb;
+  }
+  // for each shape two launches, the second of which adds the chunks; samples one after the other, or their bytes at 6.5 TB/s
+  double launches = 0, samples = 0;
+  for (int k = 0; k < 3; ++k)
+    if (longest[k] > 0) {
+      launches += 7.4;
+      samples += std::max(serial[k], longest[k]);
+    }
+  const double fused = launches + 0.07 * chunks + std::max(samples, read_mb / 6.5);
+  // launches that no other layer needs; tiles, or bytes at 7 TB/s; the weighted sum, eight samples to a latency, or bytes at 3
+  const double apart = (others ? 0 : 12.7) + std::max(norms, (read_mb + kept_mb) / 7) +
+                       std::max(kept_others ? 0 : 0.094 * B, kept_mb / 3);
+  return room_mb * 1e6 > kKeptMaxBytes || fused < apart;       // no room for all: some layers would be contracted twice
+}
+
 FusedPlan plan_fused(const dp_layer* layers, int L, dp_dtype dt, int B) {
   FusedPlan fp;
-  fp.fused.assign(L, 0);
+  fp.shape.assign(L, -1);
   fp.kept_off.assign(L, -1);
   if (dt == DP_F32) return fp;
-  // The one-pass kernel saves writing and reading the per-sample gradients, but a workgroup goes through its samples one
-  // after the other with one k-block in flight, and it takes two launches.  So: short samples, and the whole stack or 64 MB
-  // of per-sample gradients each way.  Steps, us, fused and apart: eight layers 128 x 128, 8 x 256 tokens 14.0, 15.0; 64 x 512
-  // 31.8, 38.6; 256 x 128 39.9, 82.4; 8 x 512 17.0, 16.4; 8 x 1024 23.9, 18.5; 2 x 4096 60.9, 36.5; four 64 x 64 among four
-  // 64 x 192, 8 x 128 22.4, 14.0, 256 x 128 71.7, 56.5.  (Strips of up to 512 x 32, which it took too, were the slower ones for
-  // every batch and length: six adapter pairs of 192 x 32, 8 x 3600 180.6, 26.4, 256 x 128 77.6, 48.5.)
-  constexpr int kFusedTokens = 512;
-  constexpr int64_t kFusedSaves = (int64_t)64 << 20;
-  int64_t saved = 0;
-  for (int l = 0; l < L; ++l) {
-    const dp_layer& ly = layers[l];
-    fp.fused[l] = ly.path == DP_PATH_PEREX && ly.T <= kFusedTokens && layerwise_fused_fits(ly.d_in, ly.d_out);
-    fp.n_fused += fp.fused[l];
-    if (fp.fused[l]) saved += (int64_t)B * ly.d_in * ly.d_out * 4;
-  }
-  if (fp.n_fused < L && saved <= kFusedSaves) {
-    fp.fused.assign(L, 0);
-    fp.n_fused = 0;
-  }
   for (int l = 0; l < L; ++l)
-    if (layers[l].path == DP_PATH_PEREX && !fp.fused[l]) {
-      const int64_t n = (int64_t)B * layers[l].d_in * layers[l].d_out;
-      if (n <= INT32_MAX - 4096 && (fp.kept_floats + n) * 4 <= kKeptMaxBytes) {
-        fp.kept_off[l] = fp.kept_floats;
-        fp.kept_floats += (n + 3) & ~(int64_t)3;                  // blocks stay 16-byte aligned
-      }
+    if (layers[l].path == DP_PATH_PEREX) {
+      fp.shape[l] = layerwise_fused_shape(layers[l].d_in, layers[l].d_out);
+      fp.n_fused += fp.shape[l] >= 0;
     }
-  if (fp.n_fused == 0) return fp;
-  // enough workgroups to fill the 256 compute units when the batch allows
-  const int want = std::min(B, std::max(1, 256 / fp.n_fused));
-  const int per = (B + want - 1) / want;
-  fp.chunks = (B + per - 1) / per;
-  for (int l = 0; l < L; ++l)
-    if (fp.fused[l]) fp.floats += (int64_t)fp.chunks * layers[l].d_in * layers[l].d_out;
+  if (fp.n_fused > 0) {
+    // enough workgroups to fill the 256 compute units when the batch allows
+    const int want = std::min(B, std::max(1, 256 / fp.n_fused));
+    const int per = (B + want - 1) / want;
+    fp.chunks = (B + per - 1) / per;
+    if (!one_pass_is_faster(layers, fp.shape, B, fp.chunks)) {
+      fp.shape.assign(L, -1);
+      fp.n_fused = 0;
+    }
+  }
+  for (int l = 0; l < L; ++l) {
+    const int64_t n = (int64_t)B * layers[l].d_in * layers[l].d_out;
+    if (fp.shape[l] >= 0) {
+      fp.floats += (int64_t)fp.chunks * layers[l].d_in * layers[l].d_out;
+    } else if (layers[l].path == DP_PATH_PEREX && n <= INT32_MAX - 4096 && (fp.kept_floats + n) * 4 <= kKeptMaxBytes) {
+      fp.kept_off[l] = fp.kept_floats;
+      fp.kept_floats += (n + 3) & ~(int64_t)3;                    // blocks stay 16-byte aligned
+    }
+  }
   return fp;
 }
 
@@ -1119,7 +1150,7 @@ dp_status dp_layerwise_clipped_grad(const dp_layer* layers, int L, dp_dtype dt, 
   na.rk = make_round_keys(seed);
 
   auto pass_tiles = [&](int l) {
-    return fp.fused[l] ? (int64_t)0 : (int64_t)clipped_grad_big_tiles(layers[l].d_in, layers[l].d_out);
+    return fp.shape[l] >= 0 ? (int64_t)0 : (int64_t)clipped_grad_big_tiles(layers[l].d_in, layers[l].d_out);
   };
   int64_t fused_off = 0, tiles_left = 0;                 // tiles of the layers from l1 on
   for (int l = 0; l < L; ++l) tiles_left += pass_tiles(l);
@@ -1130,7 +1161,7 @@ dp_status dp_layerwise_clipped_grad(const dp_layer* layers, int L, dp_dtype dt, 
     int64_t bytes = 0, tiles = 0;
     const int64_t esize = dt == DP_F32 ? 4 : 2;
     while (l1 < L) {
-      const bool small = fp.fused[l1];
+      const bool small = fp.shape[l1] >= 0;
       const int64_t lb = small ? 0 : (int64_t)B * layers[l1].T * ((int64_t)layers[l1].d_in + layers[l1].d_out) * esize;
       if (l1 > l0 && (layers_per_pass > 0 ? l1 - l0 >= layers_per_pass
                                           : bytes + lb > kPassBytes && tiles >= kPassTiles &&
@@ -1141,41 +1172,43 @@ dp_status dp_layerwise_clipped_grad(const dp_layer* layers, int L, dp_dtype dt, 
       ++l1;
     }
     // (1) layers that fit one workgroup tile: norm, clip factor and weighted sum in one kernel
-    for (int l = l0; l < l1;) {
-      GroupArgs ga;
-      ga.B = B;
-      ga.accumulate = accumulate;
-      ga.f16 = dt == DP_F16;
-      ga.n_layers = 0;
-      float Rg[kMaxGroup];
-      int blocks = 0;
-      for (; l < l1 && ga.n_layers < kMaxGroup; ++l) {
-        if (!fp.fused[l]) continue;
-        GroupLayer& gl = ga.layer[ga.n_layers];
-        gl.a = layers[l].a;
-        gl.g = layers[l].g;
-        gl.out = grads[l];
-        gl.T = layers[l].T;
-        gl.d_in = layers[l].d_in;
-        gl.d_out = layers[l].d_out;
-        gl.path = DP_PATH_PEREX;
-        gl.tile_begin = blocks;
-        gl.sq_index = l;
-        gl.part_begin = (int)fused_off;
-        gl.tiles_per_sample = fp.chunks;
-        gl.c_off = 0;
-        Rg[ga.n_layers] = R[l];
-        na.layer_off[ga.n_layers] = noisy ? grad_offset[l] : 0;
-        fused_off += (int64_t)fp.chunks * gl.d_in * gl.d_out;
-        blocks += fp.chunks;
-        ++ga.n_layers;
+    for (int shape = 0; shape < 3; ++shape) {
+      for (int l = l0; l < l1;) {
+        GroupArgs ga;
+        ga.B = B;
+        ga.accumulate = accumulate;
+        ga.f16 = dt == DP_F16;
+        ga.n_layers = 0;
+        float Rg[kMaxGroup];
+        int blocks = 0;
+        for (; l < l1 && ga.n_layers < kMaxGroup; ++l) {
+          if (fp.shape[l] != shape) continue;
+          GroupLayer& gl = ga.layer[ga.n_layers];
+          gl.a = layers[l].a;
+          gl.g = layers[l].g;
+          gl.out = grads[l];
+          gl.T = layers[l].T;
+          gl.d_in = layers[l].d_in;
+          gl.d_out = layers[l].d_out;
+          gl.path = DP_PATH_PEREX;
+          gl.tile_begin = blocks;
+          gl.sq_index = l;
+          gl.part_begin = (int)fused_off;
+          gl.tiles_per_sample = fp.chunks;
+          gl.c_off = 0;
+          Rg[ga.n_layers] = R[l];
+          na.layer_off[ga.n_layers] = noisy ? grad_offset[l] : 0;
+          fused_off += (int64_t)fp.chunks * gl.d_in * gl.d_out;
+          blocks += fp.chunks;
+          ++ga.n_layers;
+        }
+        if (ga.n_layers == 0) break;
+        ga.total_blocks = blocks;
+        dp_status st = launch_layerwise_fused(shape, ga, Rg, (int)mode, stability, fused_partial, sqnorm_out, C_out, s);
+        if (st != DP_OK) return st;
+        st = launch_layerwise_reduce(ga, fused_partial, na, s);
+        if (st != DP_OK) return st;
       }
-      if (ga.n_layers == 0) break;
-      ga.total_blocks = blocks;
-      dp_status st = launch_layerwise_fused(ga, Rg, (int)mode, stability, fused_partial, sqnorm_out, C_out, s);
-      if (st != DP_OK) return st;
-      st = launch_layerwise_reduce(ga, fused_partial, na, s);
-      if (st != DP_OK) return st;
     }
     // (2) the other layers of the pass: norms, clip factors, weighted gradients
     //     (instantiated layers keep G_i in the workspace: their gradient is sum_i C_i G_i)
@@ -1186,7 +1219,7 @@ dp_status dp_layerwise_clipped_grad(const dp_layer* layers, int L, dp_dtype dt, 
     std::vector<uint64_t> sub_off;
     bool any_kept = false;
     for (int l = l0; l < l1; ++l)
-      if (!fp.fused[l]) {
+      if (fp.shape[l] < 0) {
         sub.push_back(layers[l]);
         row.push_back(l);
         sub_R.push_back(R[l]);

@@ -13,6 +13,8 @@
 // which of the two forms a layer takes is a matter of its stack, its norm and factor are not.  The chunk's weighted sum goes to a workspace; a second small
 // kernel adds the chunks in order, adds the noise of eq. (1) and writes the gradient.  No
 // atomics: the result is deterministic.
+#include <type_traits>
+
 #include "clip.h"
 #include "dp_internal.h"
 #include "tn_tile.h"
@@ -63,10 +65,13 @@ layerwise_fused_kernel(const GroupArgs ga, const FusedArgs fa, float* __restrict
   const int wm = (wave / S::WN) * S::WTM, wn = (wave % S::WN) * S::WTN;
   const int row0 = wm + (lane & 31), col0 = wn + 4 * (lane >> 5);       // the lane's first element
   // How the sums of squares of the 32 x 32 tiles go together: a 128 x 128 tile of perex_dma.hip wave by wave (kTile); the
-  // four waves of perex_narrow.hip with 32 rows (kStrips), 32 columns (kFlat) or 32 x 64 each (kHalves).
-  static_assert(S::TM == 2 && S::TN == 2 && S::WM == 2, "order of sums");
-  enum { kTile, kStrips, kFlat, kHalves };
-  const int order = ly.d_in > 64 && ly.d_out > 64                        ? kTile
+  // four waves of perex_narrow.hip with 32 rows (kStrips), 32 columns (kFlat) or 32 x 64 each (kHalves); its tiles of 128 rows
+  // or columns, one to a wave here (kTiles).
+  enum { kTile, kStrips, kFlat, kHalves, kTiles };
+  constexpr bool kSquare = S::TM == 2 && S::TN == 2 && S::WM == 2;
+  static_assert(kSquare || (S::TM * S::TN == 4 && S::WM * S::WN == 4 && (S::WTM == 128 || S::WTN == 128)), "order of sums");
+  const int order = !kSquare                                             ? kTiles
+                    : ly.d_in > 64 && ly.d_out > 64                      ? kTile
                     : ly.d_out <= 32 || (ly.d_in > 32 && ly.d_out <= 64) ? kStrips
                     : ly.d_in <= 32                                      ? kFlat
                                                                          : kHalves;
@@ -94,25 +99,36 @@ layerwise_fused_kernel(const GroupArgs ga, const FusedArgs fa, float* __restrict
       float part[4], s = 0.f;
 #pragma unroll
       for (int n = 0; n < 4; ++n) {
-        if (n == 0 || (n % S::TN == 0 ? order != kTile : order == kFlat)) s = 0.f;
+        if (n == 0 || (n % S::TN == 0 ? order != kTile : order == kFlat || order == kTiles)) s = 0.f;
 #pragma unroll
         for (int r = 0; r < 16; ++r) s = fmaf(acc[n / S::TN][n % S::TN][r], acc[n / S::TN][n % S::TN][r], s);
         part[n] = s;
       }
-      const float first = part[order == kFlat ? 0 : 1], second = order == kFlat ? part[1] : part[3];
-      float v = halves_sum<32>(first, second, lane);
+      if constexpr (kSquare) {
+        const float first = part[order == kFlat ? 0 : 1], second = order == kFlat ? part[1] : part[3];
+        float v = halves_sum<32>(first, second, lane);
 #pragma unroll
-      for (int off = 16; off > 0; off >>= 1) v += __shfl_xor(v, off);
-      if ((lane & 31) == 0) red[2 * wave + (lane >> 5)] = v;        // every LDS read of the loop is behind a barrier
-      __syncthreads();
-      if (order == kTile)                        // same order in every thread
-        sq = red[1] + red[3] + red[5] + red[7];
-      else if (order == kStrips)
-        sq = (red[0] + red[1]) + (red[4] + red[5]);
-      else if (order == kFlat)
-        sq = (red[0] + red[1]) + (red[2] + red[3]);
-      else
+        for (int off = 16; off > 0; off >>= 1) v += __shfl_xor(v, off);
+        if ((lane & 31) == 0) red[2 * wave + (lane >> 5)] = v;        // every LDS read of the loop is behind a barrier
+        __syncthreads();
+        if (order == kTile)                        // same order in every thread
+          sq = red[1] + red[3] + red[5] + red[7];
+        else if (order == kStrips)
+          sq = (red[0] + red[1]) + (red[4] + red[5]);
+        else if (order == kFlat)
+          sq = (red[0] + red[1]) + (red[2] + red[3]);
+        else
+          sq = (red[0] + red[2]) + (red[1] + red[3]);
+      } else {
+        float v = halves_sum<16>(halves_sum<32>(part[0], part[1], lane), halves_sum<32>(part[2], part[3], lane), lane);
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off);
+        v += __shfl_xor(v, 32);
+        v += __shfl_xor(v, 16);
+        if (lane == 0) red[wave] = v;
+        __syncthreads();
         sq = (red[0] + red[2]) + (red[1] + red[3]);
+      }
       if (sq == sq || again) break;
 #pragma unroll
       for (int n = 0; n < 4; ++n)
@@ -182,8 +198,11 @@ layerwise_reduce_kernel(const GroupArgs ga, const float* __restrict__ partial, c
   ly.out[e] = v;
 }
 
-// One workgroup tile holds the whole layer.
+// One workgroup tile holds the whole layer: 128 x 128, or a strip 512 x 32 / 32 x 512 (the shapes of low-rank adapter
+// factors).
 using FusedSquare = TnShape<128, 128, 64, 2, 2>;
+using FusedTall = TnShape<512, 32, 64, 4, 1>;
+using FusedWide = TnShape<32, 512, 64, 1, 4>;
 
 template <class S, bool F16>
 dp_status launch_fused_t(const GroupArgs& ga, const FusedArgs& fa, float* partial, float* sqnorm, float* C_out,
@@ -198,17 +217,27 @@ dp_status launch_fused_t(const GroupArgs& ga, const FusedArgs& fa, float* partia
 
 }  // namespace
 
-bool layerwise_fused_fits(int d, int p) { return d <= FusedSquare::BM && p <= FusedSquare::BN; }
+int layerwise_fused_shape(int d, int p) {
+  if (d <= 128 && p <= 128) return 0;
+  if (d <= 512 && p <= 32) return 1;
+  if (d <= 32 && p <= 512) return 2;
+  return -1;
+}
 
-dp_status launch_layerwise_fused(const GroupArgs& ga, const float* R, int mode, float stability, float* partial,
+dp_status launch_layerwise_fused(int shape, const GroupArgs& ga, const float* R, int mode, float stability, float* partial,
                                  float* sqnorm, float* C_out, hipStream_t s) {
   FusedArgs fa;
   fa.mode = mode;
   fa.stability = stability;
   for (int j = 0; j < ga.n_layers; ++j) fa.R[j] = R[j];
   for (int j = ga.n_layers; j < kMaxGroup; ++j) fa.R[j] = 1.f;
-  return ga.f16 ? launch_fused_t<FusedSquare, true>(ga, fa, partial, sqnorm, C_out, s)
-                : launch_fused_t<FusedSquare, false>(ga, fa, partial, sqnorm, C_out, s);
+  auto launch = [&](auto f16) {
+    constexpr bool F16 = decltype(f16)::value;
+    return shape == 0   ? launch_fused_t<FusedSquare, F16>(ga, fa, partial, sqnorm, C_out, s)
+           : shape == 1 ? launch_fused_t<FusedTall, F16>(ga, fa, partial, sqnorm, C_out, s)
+                        : launch_fused_t<FusedWide, F16>(ga, fa, partial, sqnorm, C_out, s);
+  };
+  return ga.f16 ? launch(std::true_type{}) : launch(std::false_type{});
 }
 
 dp_status launch_layerwise_reduce(const GroupArgs& ga, const float* partial, const NoiseArgs& na, hipStream_t s) {

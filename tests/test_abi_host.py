@@ -56,6 +56,21 @@ def test_workspace_sizes(dp):
     assert both == sum(dp.dp_norm_workspace_bytes(path, 1, 16, T, d, p) for _, _, T, d, p, path in layers)
 
 
+# Layer-wise pass: layers that fit one workgroup tile take the one-kernel form, which keeps no per-sample gradients, where it is
+# the faster one: many samples, however few layers; not few long samples, nor tall and wide strips of many tokens together.
+@pytest.mark.parametrize("B,T,dims,one_kernel", [
+    (8192, 128, [(256, 8)] * 2, True), (4096, 128, [(512, 16)] * 16, True), (1024, 1024, [(128, 128)] * 8, True),
+    (1024, 256, [(512, 16)] * 80, True), (256, 128, [(128, 128)] * 8, True),
+    (8, 2048, [(128, 128)] * 8, False), (1024, 256, [(512, 16), (16, 512)] * 12, False),
+    (256, 128, [(192, 32), (32, 192)] * 6, False), (2048, 600, [(32, 32)] * 16, False)])
+def test_layerwise_form(dp, B, T, dims, one_kernel):
+    layers = [(None, None, T, d, p, dp.DP_PATH_PEREX) for d, p in dims]
+    norms = dp.dp_norms_multi_workspace_bytes(layers, dp.DP_BF16, B)
+    kept = dp.dp_layerwise_workspace_bytes(layers, dp.DP_BF16, B) - norms
+    each = 4 * sum(d * p for d, p in dims)
+    assert kept <= 256 * each if one_kernel else kept >= min(B * each, 2 ** 31 - 4 * max(d * p for d, p in dims) * B)
+
+
 def test_validation_refuses_before_any_launch(dp):
     lib, INV = dp.lib, dp.DP_ERR_INVALID_ARG
     fake = 0x1000                     # never dereferenced: every call below fails validation
