@@ -168,8 +168,11 @@ __device__ __forceinline__ f32x16 mul_item(const TnItem& it, f32x16 acc) {
 // VEC: every width of the launch is a multiple of 4, every slab small (small_slabs).  (A kernel of its own: beside the single loads of other widths the
 // compiler orders either form's loads worse; eight layers ten to 40 wide, 28 x 56 tokens, 34.8 us a step apart, 36.6 to 45.8
 // in one.)
+// Two workgroups to a compute unit, which 128 registers allow (the three tiles side by side took 145 of them, and one workgroup was alone):
+// 4096 samples, one and two to a unit: 16 tokens, two layers 256 + 256 190, 130 us; 48, two of 64 + 128 208, 148; instantiated,
+// 8, two of 64 x 64 47, 30.
 template <bool VEC>
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(kThreads, 4)
 norms_f32_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int first) {
   __shared__ float part_a[kWaves][16][64], part_g[kWaves][16][64];   // 64 KiB
   const unsigned block = first + blockIdx.x;
@@ -196,9 +199,7 @@ norms_f32_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int first
   auto run = [&](int r) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); };
 
   if (ly.path == DP_PATH_GHOST) {
-    auto add_tile = [&](int t0, int u0, const f32x16& xa, const f32x16& xg) {
-      put(part_a, xa);
-      put(part_g, xg);
+    auto add_parts = [&](int t0, int u0) {                 // the tile whose parts are in LDS
       __syncthreads();
       float s = 0.f;
 #pragma unroll
@@ -210,11 +211,18 @@ norms_f32_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int first
       sum += t0 == u0 ? s : 2.f * s;
       __syncthreads();
     };
+    auto add_tile = [&](int t0, int u0, const f32x16& xa, const f32x16& xg) {
+      put(part_a, xa);
+      put(part_g, xg);
+      add_parts(t0, u0);
+    };
     if (VEC && T > kTile && T <= 2 * kTile) {
       f32x16 xa[3], xg[3];
       gram_parts3(a, T, d, wave, lane, xa);
+      put(part_a, xa[0]);                                  // at once: 16 registers that the g side can use
       gram_parts3(g, T, p, wave, lane, xg);
-      add_tile(0, 0, xa[0], xg[0]);
+      put(part_g, xg[0]);
+      add_parts(0, 0);
       add_tile(0, kTile, xa[1], xg[1]);
       add_tile(kTile, kTile, xa[2], xg[2]);
     } else {
