@@ -154,9 +154,11 @@ __device__ __forceinline__ void gram_parts3(const uint16_t* x, int T, int width,
 }
 
 template <bool F16>
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(kThreads, 4)
 ghost_pair_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int first) {
-  __shared__ float part_a[kWaves][16][64], part_g[kWaves][16][64];       // 64 KiB: two workgroups per compute unit
+  // 64 KiB and 128 registers: two workgroups per compute unit (48 tokens, 2048 samples of two layers 392 + 296: 88 us with 142
+  // registers and one, 60 so; 24 + 16 57, 37, and without the sums of waves that had no columns 28)
+  __shared__ float part_a[kWaves][16][64], part_g[kWaves][16][64];
   __shared__ float wave_sum[kWaves];
   const int block = first + blockIdx.x;
   const int l = layer_of(ga, block);
@@ -165,18 +167,23 @@ ghost_pair_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int firs
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const size_t row0 = (size_t)i * T;
+  const int used = min(kWaves, (max(ly.d_in, ly.d_out) + 15) / 16);        // the other waves' sums are zeros: they stay out
   f32x16 xa[3], xg[3];
   gram_parts3<F16>(static_cast<const uint16_t*>(ly.a) + row0 * ly.d_in, T, ly.d_in, wave, lane, xa);
+  if (wave < used)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part_a[wave][r][lane] = xa[0][r];       // at once: 16 registers that the g side can use
   gram_parts3<F16>(static_cast<const uint16_t*>(ly.g) + row0 * ly.d_out, T, ly.d_out, wave, lane, xg);
   float sum = 0.f;
 #pragma unroll
   for (int n = 0; n < 3; ++n) {
     if (n > 0) __syncthreads();                        // the last tile's parts are read
+    if (wave < used)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      part_a[wave][r][lane] = xa[n][r];
-      part_g[wave][r][lane] = xg[n][r];
-    }
+      for (int r = 0; r < 16; ++r) {
+        if (n > 0) part_a[wave][r][lane] = xa[n][r];
+        part_g[wave][r][lane] = xg[n][r];
+      }
     __syncthreads();
     // This thread: registers wave and wave + 8 of lane `lane` of every wave; row 8 (r >> 2) + 4 (lane >> 5) + (r & 3) of one
     // half, column lane & 31 of the other.  Rows past the sample are zeros, beside an infinity NaN: they stay out.
@@ -185,10 +192,17 @@ ghost_pair_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int firs
     for (int h = 0; h < 2; ++h) {
       const int r = wave + 8 * h;
       float sa = 0.f, sg = 0.f;
+      if (used == kWaves) {
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) {
-        sa += part_a[w][r][lane];
-        sg += part_g[w][r][lane];
+        for (int w = 0; w < kWaves; ++w) {
+          sa += part_a[w][r][lane];
+          sg += part_g[w][r][lane];
+        }
+      } else {
+        for (int w = 0; w < used; ++w) {
+          sa += part_a[w][r][lane];
+          sg += part_g[w][r][lane];
+        }
       }
       const int row = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), col = lane & 31;
       const bool in = n == 0 || kRows + (n == 1 ? col : max(row, col)) < T;
@@ -216,13 +230,28 @@ bool ghost_pair_supports(int T, int d, int p) {
   return T > kRows && T <= 2 * kRows && T * ((int64_t)d + p) <= kMostValues;
 }
 
-dp_status launch_ghost_pair_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s) {
+// Large samples, many rounds of them: one workgroup to a compute unit, by LDS that it does not use.  64 tokens, 2048 + 1024: 2048
+// samples 186 us so and 197 with two, 6000 527 and 566, but 600 52 and 46; of 760 + 520, 6000 509 and 502.
+constexpr int kWideValues = 128 * 1024, kWideSamples = 1024, kSoleLds = 32 * 1024;
+
+template <bool F16>
+dp_status launch_pair_t(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s) {
+  int lds = 0;
+  if (ga.total_blocks >= kWideSamples)
+    for (int l = 0; l < ga.n_layers; ++l)
+      if ((int64_t)ga.layer[l].T * ((int64_t)ga.layer[l].d_in + ga.layer[l].d_out) > kWideValues) lds = kSoleLds;
+  if (lds > 0) {
+    static ReadyTable ready;
+    dp_status st = allow_big_lds(ghost_pair_kernel<F16>, lds, ready);
+    if (st != DP_OK) return st;
+  }
   return launch_in_runs(ga.total_blocks, [&](dim3 grid, int first) {
-    if (ga.f16)
-      hipLaunchKernelGGL(ghost_pair_kernel<true>, grid, dim3(kThreads), 0, s, ga, sqnorm, nc, first);
-    else
-      hipLaunchKernelGGL(ghost_pair_kernel<false>, grid, dim3(kThreads), 0, s, ga, sqnorm, nc, first);
+    hipLaunchKernelGGL(ghost_pair_kernel<F16>, grid, dim3(kThreads), lds, s, ga, sqnorm, nc, first);
   });
+}
+
+dp_status launch_ghost_pair_group(const GroupArgs& ga, float* sqnorm, const NormClip& nc, hipStream_t s) {
+  return ga.f16 ? launch_pair_t<true>(ga, sqnorm, nc, s) : launch_pair_t<false>(ga, sqnorm, nc, s);
 }
 
 bool ghost_brief_supports(int T) { return T <= kRows; }

@@ -87,6 +87,14 @@ def test_infinite_instantiated_norms(dp, dtype, where, B, T, d, p):
     check_infinite_norms(dp, dtype, 1, B, T, d, p, where)
 
 
+# 16-bit ghost norms of 33 to 64 tokens: rows past the sample in one half of a tile, the other, both or none.
+@pytest.mark.parametrize("dtype", HALF)
+@pytest.mark.parametrize("where", ["a", "g"])
+@pytest.mark.parametrize("B,T,d,p", [(3, 33, 136, 120), (4, 40, 8, 24), (3, 63, 64, 200), (3, 64, 72, 64)])
+def test_infinite_ghost_norms_of_33_to_64_tokens(dp, dtype, where, B, T, d, p):
+    check_infinite_norms(dp, dtype, 0, B, T, d, p, where, positive=True)
+
+
 def norms_of_copies(dp, dtype, path, L, B, T, d, p):
     """Squared norms of a stack of L layers that all hold the same a and g, and these on the device."""
     tdt = {si.F32: torch.float32, si.BF16: torch.bfloat16, si.F16: torch.float16}[dtype]

@@ -349,6 +349,8 @@ STEP_STACKS = [
     (si.BF16, 5, 21, [(64, 72), (128, 136)], None),
     (si.BF16, 40, 7, [(16, 8)] * 2, None),            # 2 x 10 workgroups of four samples, shared by four each
     (si.F16, 77, 5, [(40, 24)] * 9, None),            # 13 and 26 workgroups a layer
+    (si.BF16, 5, 41, [(64, 72), (128, 136)], [0] * 2),               # 33 to 64 tokens
+    (si.F16, 31, 64, [(72, 136), (128, 64), (8, 8)], [0] * 3),       # 93 workgroups, 3 layers
     (si.BF16, 2, 130, [(64, 128)] * 3, [0] * 3),
     (si.F16, 31, 256, [(72, 136), (128, 64), (8, 8)], [0] * 3),      # 93, 3
     (si.BF16, 32, 200, [(72, 64)] * 3, [0] * 3),
@@ -653,3 +655,24 @@ def test_layerwise_norms_do_not_depend_on_the_stack(dtype, B, T, dims):
         pipe.norms()
         assert torch.equal(pipe.sqnorm[:len(dims)], got[-1][0])
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+# Ghost norms of 33 to 64 tokens: waves without columns of their own, and many large samples, which take a compute unit each.
+@pytest.mark.parametrize("dtype", [si.BF16, si.F16])
+@pytest.mark.parametrize("B,T,d,p", [(70, 40, 24, 16), (70, 64, 104, 8), (70, 33, 8, 112), (1030, 64, 1544, 520)])
+def test_ghost_norms_of_33_to_64_tokens_by_width(dtype, B, T, d, p):
+    from paper_2311_11822_amd import binding as dp
+    dt, tdt = (dp.DP_BF16, torch.bfloat16) if dtype == si.BF16 else (dp.DP_F16, torch.float16)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    a = torch.randn((B, T, d), generator=gen, device="cuda").to(tdt)
+    g = torch.randn((B, T, p), generator=gen, device="cuda").to(tdt)
+    got = []
+    for n in (B, 9):
+        desc = dp.layer_array([(a[:n], g[:n], T, d, p, dp.DP_PATH_GHOST)])
+        ws = torch.empty(dp.dp_norms_multi_workspace_bytes(desc, dt, n), dtype=torch.uint8, device="cuda")
+        got.append(torch.empty((1, n), device="cuda"))
+        dp.dp_norms_multi(desc, dt, n, got[-1], ws)
+    assert torch.equal(got[0][0, :9], got[1][0])
+    want = torch.stack([(a[i].double().t().contiguous() @ g[i].double()).square().sum() for i in range(0, B, 10)])
+    # exact products; sums of up to 1544 columns and T^2 pairs in fp32
+    assert float(((got[0][0, ::10].double() - want) / want).abs().max()) < 1e-5
