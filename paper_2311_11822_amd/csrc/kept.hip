@@ -4,6 +4,8 @@
 //     grad[e] (+)= sum_i C_i G_i[e]  (+ sigma R z_e, eq. (1)),     G_i = a_i^T g_i as kept, [B, d_in * d_out] fp32.
 // A stream over B + 1 arrays of d_in * d_out floats (HBM-bound) in place of a second contraction over
 // the T tokens of a and g.  Samples are added in index order; samples with C_i == 0 do not enter.
+#include <type_traits>
+
 #include "dp_internal.h"
 
 namespace dpbk {
@@ -28,22 +30,27 @@ kept_weighted_sum_kernel(const GroupArgs ga, const float* __restrict__ C_all, co
   const float* src = static_cast<const float*>(ly.a) + e;
   f32x4v v = {0.f, 0.f, 0.f, 0.f};
   // Eight samples in flight, added in order (their factors are the same for all lanes: scalar loads and branches).
-  for (int i0 = 0; i0 < ga.B; i0 += kInFlight) {
+  auto add = [&](int i0, auto whole) {
     float c[kInFlight];
     f32x4v x[kInFlight];
 #pragma unroll
     for (int q = 0; q < kInFlight; ++q) {
-      const int i = min(i0 + q, ga.B - 1);
-      c[q] = C[i];
-      x[q] = *reinterpret_cast<const f32x4v*>(src + (size_t)i * n);
+      c[q] = 0.f;
+      if (decltype(whole)::value || i0 + q < ga.B) {
+        c[q] = C[i0 + q];
+        x[q] = *reinterpret_cast<const f32x4v*>(src + (size_t)(i0 + q) * n);
+      }
     }
 #pragma unroll
     for (int q = 0; q < kInFlight; ++q)
-      if (i0 + q < ga.B && c[q] != 0.f) {
+      if (c[q] != 0.f) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] = fmaf(c[q], x[q][k], v[k]);
       }
-  }
+  };
+  int i0 = 0;
+  for (; i0 + kInFlight <= ga.B; i0 += kInFlight) add(i0, std::true_type{});
+  if (i0 < ga.B) add(i0, std::false_type{});
   f32x4v* dst = reinterpret_cast<f32x4v*>(ly.out + e);
   if (ga.accumulate) {
     const f32x4v old = *dst;

@@ -181,9 +181,9 @@ layerwise_reduce_kernel(const GroupArgs ga, const float* __restrict__ partial, c
   for (int c0 = 0; c0 < ly.tiles_per_sample; c0 += 8) {          // eight chunks in flight, added in order
     float x[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) x[q] = src[(size_t)min(c0 + q, ly.tiles_per_sample - 1) * n];
+    for (int q = 0; q < 8; ++q) x[q] = c0 + q < ly.tiles_per_sample ? src[(size_t)(c0 + q) * n] : 0.f;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) v += c0 + q < ly.tiles_per_sample ? x[q] : 0.f;
+    for (int q = 0; q < 8; ++q) v += x[q];
   }
   if (ga.accumulate) v += ly.out[e];
   if (na.stddev != 0.f) {
