@@ -97,6 +97,14 @@ struct OldRows {
   }
 };
 
+// What the wave's lanes wrote to its region is there for its other lanes, and what they read has been read: LDS serves a
+// wave in order, so this only holds the compiler to it (no instruction).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // acc * held (+ old value) (+ noise of eq. (1)) -> out, in fp32 or the operands' 16-bit type; lds: the wave's WaveRows::BYTES.
 // Noise: same values as the separate pass, which indexes the generator by global element too; requires layer_off and d_out
 // to be multiples of 4, as a lane's four columns are one block of the generator.
@@ -114,6 +122,7 @@ __device__ __forceinline__ void store_rows(const f32x16* acc, float held, unsign
       const f32x4v w = {acc[y][4 * q], acc[y][4 * q + 1], acc[y][4 * q + 2], acc[y][4 * q + 3]};
       *(lds_f4*)(uintptr_t)(lds + (lane & 31) * R::STRIDE + (32 * y + 8 * q + 4 * (lane >> 5)) * 4) = w;
     }
+  wave_lds_fence();
   bool noisy = false, whole = false;
   if constexpr (NOISE) {
     const int rows = min(32, d - row0), cols = min(R::W, p - col0);
@@ -138,6 +147,7 @@ __device__ __forceinline__ void store_rows(const f32x16* acc, float held, unsign
 #pragma unroll
       for (int k = 0; k < 4; ++k) v[n][4 * b + k] = ACCUMULATE ? w[k] : w[k] * held;
     }
+  wave_lds_fence();                                      // the wave's next piece is written over it
 #pragma unroll
   for (int n = 0; n < N; n += U) {
     if constexpr (ACCUMULATE) {
