@@ -34,7 +34,7 @@ import synth_inputs as si  # noqa: E402
 
 PEAK_BF16_FLOPS = 2.5e15       # MI355X dense bf16 MFMA
 PEAK_HBM_BYTES = 8.0e12
-NOISE_ALU_PEAK_BLOCKS = 487e9   # Philox4x32-10 + Box-Muller blocks/s of the bare generator, two waves per SIMD, measured
+BARE_GENERATOR_BLOCKS = 487e9   # Philox4x32-10 + Box-Muller blocks/s, nothing stored, two waves per SIMD (measured, no ALU peak)
 HEADLINE = "cfg4"
 
 
@@ -265,10 +265,8 @@ def measure(name, args, torch, BkPipeline, noise_pass=False):
         res["noise_pass"] = {"kernel": "noise_bulk_kernel", "elements": cnt, "bytes": 8 * cnt,
                              "ms": float(ms.mean()), "ms_min": float(ms.min()),
                              "gbps": gbps, "frac_hbm_peak": gbps * 1e9 / PEAK_HBM_BYTES,
-                             # the generator's instruction stream is ~690 vector-ALU clocks per
-                             # 4-element block and wave: 256 CUs x 4 SIMDs x 64 lanes x 2.4 GHz / 690
                              "gblocks_per_s": cnt / 4 / (ms.mean() * 1e-3) / 1e9,
-                             "frac_alu_peak": cnt / 4 / (ms.mean() * 1e-3) / NOISE_ALU_PEAK_BLOCKS}
+                             "frac_bare_generator": cnt / 4 / (ms.mean() * 1e-3) / BARE_GENERATOR_BLOCKS}
     del pipe, layers
     gc.collect()
     torch.cuda.empty_cache()

@@ -380,7 +380,8 @@ dp_status dp_clipped_bias_grad(const float* colsum, int B, int d_out, const floa
  * that every tile of a layer is computed exactly once for any shape; the arrays may be NULL.
  * dp_clipped_grad_tile_order: tile b of a one-layer launch of the clip-weighted gradient
  *   (section 3, "DP gradient") starts at row tile_row0[b], column tile_col0[b] of the
- *   [d_in, d_out] gradient, for a contraction over more than 512 rows; tiles are 256 x 256.  Tiles that
+ *   [d_in, d_out] gradient, for a contraction over more than 512 rows and, unless d_in and d_out are both
+ *   multiples of 64, up to 2048 (over longer ragged rows a launch may cut other tiles); tiles are 256 x 256.  Tiles that
  *   the launch cuts into sub-tiles (its last ones, or all) come after the others, by the workgroup
  *   of their first sub-tile; -1 if a sub-tile were computed twice.
  * dp_ghost_tile_order: workgroup b of a one-layer ghost-norm launch (appendix A.1) computes, for

@@ -1331,7 +1331,8 @@ int64_t dp_clipped_grad_tile_order(int d_in, int d_out, int32_t* tile_row0, int3
   if (d_in <= 0 || d_out <= 0 || capacity < 0) return -1;
   const int64_t n = clipped_grad_big_tiles(d_in, d_out);
   if (n > INT32_MAX / 2) return -1;
-  // (the split of a long contraction over rows of whole lines: the call knows neither rows nor neighbours)
+  // the split of a long contraction over rows of whole lines, and of up to 2048 ragged rows: the call knows neither the rows
+  // nor neighbours
   const GradTail cut = clipped_grad_tail((int)n, clipped_grad_mid_tiles(d_in, d_out), INT32_MAX, true, false);
   const int n_main = (int)n - cut.tiles;
   const int tiles_m = (d_in + 255) / 256, tiles_n = (d_out + 255) / 256;

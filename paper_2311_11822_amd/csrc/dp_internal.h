@@ -168,6 +168,8 @@ dp_status launch_clipped_grad_f32_group(const GroupArgs& ga, const float* C, con
 // (one per compute unit) or 512 of 128 x 128 (two), and a round of the latter, half the work, takes three
 // fifths of the time (measured on 1024-wide layers, 2048 tokens: 57 us and 34 us).  So large tiles
 // where they come in whole rounds, small ones where few tiles or padding would leave large ones idle.
+// The instantiated norms price rounds so at every width; of the gradients' launches only those over rows of whole 128-byte lines
+// or few rows (clipped_grad_tail: 0.65 to 1.0 of a large round elsewhere).
 constexpr int kBigRound = 256, kMidRound = 512;
 constexpr int kBigRoundCost = 5, kMidRoundCost = 3;
 

@@ -288,8 +288,9 @@ norms_f32_kernel(const GroupArgs ga, float* sqnorm, const NormClip nc, int first
 // Clip-weighted gradient (section 3): grad[j,k] = sum_i C_i sum_t a[i,t,j] g[i,t,k] (+ noise, eq. (1)).
 // One workgroup per 32 x 32 tile; its waves take contiguous runs of the (sample, 16 tokens) items.
 // An item's product is formed unweighted and folded in as total += C_i * item; a sample with
-// C_i == 0 is not read, as in the 16-bit kernels.
-// SMALL: every sample's a and g are less than 2 GiB, so that they load through buffer descriptors.
+// C_i == 0 does not enter.
+// SMALL: every sample's a and g are less than 2 GiB, so that they load through buffer descriptors (samples that do not
+// enter too: the loads do not wait for the weight).
 template <bool SMALL>
 __global__ void __launch_bounds__(kThreads)
 clipped_grad_f32_kernel(const GroupArgs ga, const float* __restrict__ C_all, const NoiseArgs na, int first) {

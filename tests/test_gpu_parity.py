@@ -453,6 +453,43 @@ def test_sample_slabs_at_the_addressing_limit(dp, d):
     assert frob(host(grad), want_G) <= 1e-5
 
 
+# fp32: 2^31 bytes of a sample and the 16 rows past it are the line between loads through buffer descriptors and 64-bit
+# addresses.  T is no multiple of 16; two samples, so that the second slab starts 2 GiB into the array.
+@pytest.mark.parametrize("wide,small", [(32774, True), (32775, False)])
+@pytest.mark.parametrize("side", ["a", "g"])
+def test_fp32_gradient_at_the_addressing_limit(dp, wide, small, side):
+    B, T, narrow = 2, 16365, 3
+    assert ((T + 16) * wide * 4 < 2 ** 31) == small
+    d, p = (wide, narrow) if side == "a" else (narrow, wide)
+    gen_ = torch.Generator(device="cuda").manual_seed(wide)
+    a, g = (torch.randn(B, T, n, device="cuda", generator=gen_) for n in (d, p))
+    C = torch.tensor([0.75, 0.031], device="cuda")
+    grad = torch.full((d, p), 3.0, dtype=torch.float32, device="cuda")
+    dp.dp_clipped_grad(a, g, dp.DP_F32, B, T, d, p, C, grad, 0)
+    want = torch.empty((d, p), dtype=torch.float64, device="cuda")
+    x, y, out = (a, g, want) if side == "a" else (g, a, want.t())
+    for j0 in range(0, wide, 4096):
+        j = slice(j0, j0 + 4096)
+        out[j] = sum(c * (x[i, :, j].double().t() @ y[i].double()) for i, c in enumerate(C.double()))
+    # sums of at most 300 parts in fp32, a rounding of 2^-24 each
+    assert float((grad.double() - want).abs().max()) <= 300 * 2.0 ** -24 * float(want.square().mean().sqrt())
+
+
+# The same line in the norms, which only one long row reaches within their bound on work.
+@pytest.mark.parametrize("d,small", [(31580640, True), (31580644, False)])
+def test_fp32_norm_at_the_addressing_limit(dp, d, small):
+    B, T, p = 2, 1, 4
+    assert ((T + 16) * d * 4 < 2 ** 31) == small
+    a = (torch.arange(B * d, device="cuda") % 1009 == 0).float().view(B, T, d)
+    g = torch.full((B, T, p), 2.0, device="cuda")
+    want = a.sum((1, 2)) * 16                                       # exact: whole numbers below 2^24
+    for path, fn in ((dp.DP_PATH_GHOST, dp.dp_ghost_norm), (dp.DP_PATH_PEREX, dp.dp_perex_norm)):
+        ws = torch.empty(dp.dp_norm_workspace_bytes(path, dp.DP_F32, B, T, d, p), dtype=torch.uint8, device="cuda")
+        out = torch.full((B,), -1.0, dtype=torch.float32, device="cuda")
+        fn(a, g, dp.DP_F32, B, T, d, p, out, ws)
+        assert torch.equal(out, want)
+
+
 def random_stack(seed):
     """A seeded stack of four layers whose (T, d, p) are drawn so that the sweep reaches every
     16-bit kernel: whole and ragged k-blocks, widths from 8 up, both norm paths."""

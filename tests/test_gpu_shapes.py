@@ -676,3 +676,20 @@ def test_ghost_norms_of_33_to_64_tokens_by_width(dtype, B, T, d, p):
     want = torch.stack([(a[i].double().t().contiguous() @ g[i].double()).square().sum() for i in range(0, B, 10)])
     # exact products; sums of up to 1544 columns and T^2 pairs in fp32
     assert float(((got[0][0, ::10].double() - want) / want).abs().max()) < 1e-5
+
+
+# Long contractions over ragged rows: up to 2048, 8192 and more rows a launch cuts the same tiles differently.
+@pytest.mark.parametrize("B,T", [(2, 1000), (2, 1056), (3, 2752)])
+def test_long_contractions_over_ragged_rows(B, T):
+    from paper_2311_11822_amd import binding as dp
+    d, p = 72, 51000
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    a, g = (torch.randn((B, T, n), generator=gen, device="cuda").to(torch.bfloat16) for n in (d, p))
+    C = torch.rand(B, generator=gen, device="cuda") + 0.1
+    got = torch.full((d, p), 7.0, device="cuda")
+    dp.dp_clipped_grad(a, g, dp.DP_BF16, B, T, d, p, C, got, 0)
+    weighted = (a.double() * C.double()[:, None, None]).reshape(B * T, d).t().contiguous()
+    for k in range(0, p, 4096):
+        ref = weighted @ g[:, :, k:k + 4096].double().reshape(B * T, -1)
+        # exact products; sums of up to 8256 of them in fp32, 16 to a matrix instruction
+        assert float((got[:, k:k + 4096].double() - ref).norm() / ref.norm()) < 3e-6
