@@ -65,8 +65,12 @@ __device__ __forceinline__ TileNoise load_tile_noise(const NoiseArgs& na, int la
 // bytes, 3.3 M lines).  So the values go through LDS, a region of the wave's own, and every store instruction writes whole
 // rows of the wave's piece, 16 bytes a lane.  Steps, us, from the registers and through LDS: 2 x 32 tokens, 44 layers of width
 // 1344 stored in 16 bits 290, 255; 2 x 32, 44 of width 1488 in fp32 355, 312; 18 tokens of 3 samples, 48 of width 320 40, 34;
-// 4096 tokens, 144 of width 1280 7.31, 7.36 ms.  (Streaming stores of the registers' 32-byte pieces, which pass L2 by, took
-// four times as long.)
+// 4096 tokens, 144 of width 1280 7.31, 7.36 ms.
+//
+// Whole rows leave by streaming (nontemporal) stores: a launch writes more than the caches hold and reads none of it, so that
+// cached stores only push the operands out of them.  Gradients with noise, us, cached and streaming: 24 layers 1280 x 1280,
+// 16 x 112 tokens 186, 169; 32 x 48 182, 170; 24 GPT layers of width 1024 (fp16), 10 x 100 241, 221; 48 of width 1280, 8 x 512 1845,
+// 1840; accumulating launches alike.  (Of the registers' 32-byte pieces they took four times as long.)
 template <int NY>
 struct WaveRows {
   static constexpr int W = 32 * NY;
@@ -198,10 +202,10 @@ __device__ __forceinline__ void store_rows(const f32x16* acc, float held, unsign
 #pragma unroll
           for (int k = 0; k < 4; ++k)
             w[k] = (uint32_t)to_half_bits<F16>(v[u][2 * k]) | ((uint32_t)to_half_bits<F16>(v[u][2 * k + 1]) << 16);
-          *reinterpret_cast<u32x4v*>(reinterpret_cast<uint16_t*>(out32) + at + u * step) = w;
+          __builtin_nontemporal_store(w, reinterpret_cast<u32x4v*>(reinterpret_cast<uint16_t*>(out32) + at + u * step));
         } else {
           const f32x4v w = {v[u][0], v[u][1], v[u][2], v[u][3]};
-          *reinterpret_cast<f32x4v*>(out32 + at + u * step) = w;
+          __builtin_nontemporal_store(w, reinterpret_cast<f32x4v*>(out32 + at + u * step));
         }
       }
     __builtin_amdgcn_sched_barrier(0);
