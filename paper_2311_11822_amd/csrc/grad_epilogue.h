@@ -10,6 +10,7 @@ namespace dpbk {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4v;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4v;
+typedef __attribute__((address_space(3))) f32x4v lds_f4;
 
 // 16-bit gradient output (mixed-precision training keeps gradients in the storage type of the
 // activations: section 2.3 of the paper): the fp32 value - weighted sum, old value when
@@ -40,7 +41,10 @@ struct TileNoise {
   RoundKeys rk;
 };
 
-__device__ __forceinline__ TileNoise load_tile_noise(const NoiseArgs& na, int layer) {
+__device__ __forceinline__ TileNoise load_tile_noise(const NoiseArgs& args, int layer) {
+  int zero = 0;
+  asm volatile("" : "+s"(zero));                         // where tiles come in a loop: read for each, not held beside the contraction
+  const NoiseArgs& na = (&args)[zero];
   TileNoise t;
   t.stddev = na.stddev;
   t.step_lo = na.step_lo;
@@ -72,24 +76,50 @@ __device__ __forceinline__ TileNoise load_tile_noise(const NoiseArgs& na, int la
 // 16 x 112 tokens 186, 169; 32 x 48 182, 170; 24 GPT layers of width 1024 (fp16), 10 x 100 241, 221; 48 of width 1280, 8 x 512 1845,
 // 1840; accumulating launches alike.  (Of the registers' 32-byte pieces they took four times as long.)
 template <int NY>
-struct WaveRows {
-  static constexpr int W = 32 * NY;
+struct WavePiece {
+  static constexpr int H = 32, W = 32 * NY;            // rows, columns
   static constexpr int STRIDE = 4 * W + 16;            // bytes of a row: 16 of them begin in different banks
-  static constexpr int BYTES = 32 * STRIDE;
+  static constexpr int BYTES = H * STRIDE;
+  const f32x16* acc;                                   // its tiles' sums, first row and column
+  int row0, col0;
+  __device__ __forceinline__ void put(unsigned lds, int lane) const {
+#pragma unroll
+    for (int y = 0; y < NY; ++y)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *(lds_f4*)(uintptr_t)(lds + (lane & 31) * STRIDE + (32 * y + 8 * q + 4 * (lane >> 5)) * 4) =
+            f32x4v{acc[y][4 * q], acc[y][4 * q + 1], acc[y][4 * q + 2], acc[y][4 * q + 3]};
+  }
+  // Columns 4 quad .. 4 quad + 3 of a row
+  static __device__ __forceinline__ unsigned at(unsigned lds, int row, int quad) { return lds + row * STRIDE + quad * 16; }
+};
+
+// 16 rows of four 16 x 16 tiles: lane l has row l & 15 and the columns 4 (l >> 4) + e of a tile in register e.
+// Without room between the rows: 16 bytes are where the row's number exclusive-or'd says, so that 16 rows' are in different banks.
+struct WavePiece16 {
+  static constexpr int H = 16, W = 64;
+  static constexpr int BYTES = H * W * 4;
+  const f32x4v* acc;
+  int row0, col0;
+  __device__ __forceinline__ void put(unsigned lds, int lane) const {
+#pragma unroll
+    for (int y = 0; y < 4; ++y) *(lds_f4*)(uintptr_t)at(lds, lane & 15, 4 * y + (lane >> 4)) = acc[y];
+  }
+  static __device__ __forceinline__ unsigned at(unsigned lds, int row, int quad) { return lds + row * 256 + ((quad ^ row) << 4); }
 };
 
 // How a wave's piece leaves: N store instructions of ROWS rows, LANES lanes to a row, VEC columns a lane.
-template <int NY, bool OUT16>
+template <class Piece, bool OUT16>
 struct RowStores {
-  static constexpr int VEC = OUT16 ? 8 : 4, LANES = WaveRows<NY>::W / VEC, ROWS = 64 / LANES, N = 32 / ROWS;
+  static constexpr int VEC = OUT16 ? 8 : 4, LANES = Piece::W / VEC, ROWS = 64 / LANES, N = Piece::H / ROWS;
 };
 
 // The old values of a piece, asked for before its sums go through LDS.
-template <int NY, bool OUT16>
+template <class Piece, bool OUT16>
 struct OldRows {
-  u32x4v raw[RowStores<NY, OUT16>::N];
+  u32x4v raw[RowStores<Piece, OUT16>::N];
   __device__ __forceinline__ void load(const float* out32, int row0, int col0, int d, int p, int lane) {
-    using S = RowStores<NY, OUT16>;
+    using S = RowStores<Piece, OUT16>;
     const int row = row0 + lane / S::LANES, col = col0 + lane % S::LANES * S::VEC;
     const char* at = reinterpret_cast<const char*>(out32) + ((size_t)row * p + col) * (OUT16 ? 2 : 4);
     const size_t step = (size_t)S::ROWS * p * (OUT16 ? 2 : 4);
@@ -109,45 +139,38 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// acc * held (+ old value) (+ noise of eq. (1)) -> out, in fp32 or the operands' 16-bit type; lds: the wave's WaveRows::BYTES.
+// acc * held (+ old value) (+ noise of eq. (1)) -> out, in fp32 or the operands' 16-bit type; lds: the wave's Piece::BYTES;
+// ready: called before the first store.
 // Noise: same values as the separate pass, which indexes the generator by global element too; requires layer_off and d_out
 // to be multiples of 4, as a lane's four columns are one block of the generator.
-template <int NY, bool F16, bool NOISE, bool OUT16, bool ACCUMULATE>
-__device__ __forceinline__ void store_rows(const f32x16* acc, float held, unsigned lds, float* out32, int row0, int col0,
-                                           int d, int p, const TileNoise& na, int lane) {
-  using R = WaveRows<NY>;
-  OldRows<NY, OUT16> old;
+template <bool F16, bool NOISE, bool OUT16, bool ACCUMULATE, class Piece, class Ready>
+__device__ __forceinline__ void store_rows(const Piece& piece, float held, unsigned lds, float* out32, int d, int p,
+                                           const TileNoise& na, int lane, Ready ready) {
+  const int row0 = piece.row0, col0 = piece.col0;
+  OldRows<Piece, OUT16> old;
   if (ACCUMULATE) old.load(out32, row0, col0, d, p, lane);
-  typedef __attribute__((address_space(3))) f32x4v lds_f4;
-#pragma unroll
-  for (int y = 0; y < NY; ++y)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const f32x4v w = {acc[y][4 * q], acc[y][4 * q + 1], acc[y][4 * q + 2], acc[y][4 * q + 3]};
-      *(lds_f4*)(uintptr_t)(lds + (lane & 31) * R::STRIDE + (32 * y + 8 * q + 4 * (lane >> 5)) * 4) = w;
-    }
+  piece.put(lds, lane);
   wave_lds_fence();
   bool noisy = false, whole = false;
   if constexpr (NOISE) {
-    const int rows = min(32, d - row0), cols = min(R::W, p - col0);
+    const int rows = min(Piece::H, d - row0), cols = min(Piece::W, p - col0);
     const uint64_t e_first = na.layer_off + (uint64_t)row0 * p + col0;
     const uint64_t e_last = na.layer_off + (uint64_t)(row0 + rows - 1) * p + (col0 + cols - 1);
     noisy = rows > 0 && cols > 0 && e_last >= na.lo && e_first < na.hi;              // wave-uniform
     whole = e_first >= na.lo && e_last < na.hi;
   }
-  constexpr int VEC = RowStores<NY, OUT16>::VEC, LANES = RowStores<NY, OUT16>::LANES;
-  constexpr int ROWS = RowStores<NY, OUT16>::ROWS, N = RowStores<NY, OUT16>::N;
+  constexpr int VEC = RowStores<Piece, OUT16>::VEC, LANES = RowStores<Piece, OUT16>::LANES;
+  constexpr int ROWS = RowStores<Piece, OUT16>::ROWS, N = RowStores<Piece, OUT16>::N;
   constexpr int BLOCKS = VEC / 4, U = 4 / BLOCKS;                                     // U at a time: four generator blocks
   static_assert(N % U == 0, "whole groups");
   const int row = row0 + lane / LANES, col = col0 + lane % LANES * VEC;
-  const unsigned from = lds + lane / LANES * R::STRIDE + lane % LANES * VEC * 4;
   const size_t at = (size_t)row * p + col, step = (size_t)ROWS * p;      // the lane's first element; from one to the next
   float v[N][VEC];
 #pragma unroll
   for (int n = 0; n < N; ++n)
 #pragma unroll
     for (int b = 0; b < BLOCKS; ++b) {
-      const f32x4v w = *(const lds_f4*)(uintptr_t)(from + n * ROWS * R::STRIDE + 16 * b);
+      const f32x4v w = *(const lds_f4*)(uintptr_t)Piece::at(lds, lane / LANES + n * ROWS, lane % LANES * BLOCKS + b);
 #pragma unroll
       for (int k = 0; k < 4; ++k) v[n][4 * b + k] = ACCUMULATE ? w[k] : w[k] * held;
     }
@@ -194,6 +217,7 @@ __device__ __forceinline__ void store_rows(const f32x16* acc, float held, unsign
               v[n + u][k] = fmaf(na.stddev, z[u * BLOCKS + k / 4][k % 4], v[n + u][k]);
       }
     }
+    if (n == 0) ready();
 #pragma unroll
     for (int u = n; u < n + U; ++u)
       if (row + u * ROWS < d && col < p) {
@@ -212,20 +236,16 @@ __device__ __forceinline__ void store_rows(const f32x16* acc, float held, unsign
   }
 }
 
-// COUNT pieces of the wave.  piece(i): its tiles' sums, first row and column.
-struct WavePiece {
-  const f32x16* acc;
-  int row0, col0;
-};
-template <int COUNT, int NY, bool F16, bool NOISE, bool OUT16, class Piece>
-__device__ __forceinline__ void store_pieces(Piece piece, bool accumulate, float held, unsigned lds, float* out32, int d, int p,
-                                             const TileNoise& na, int lane) {
+// COUNT pieces of the wave; ready: called before the first store.
+template <int COUNT, bool F16, bool NOISE, bool OUT16, class PieceOf, class Ready>
+__device__ __forceinline__ void store_pieces(PieceOf piece, bool accumulate, float held, unsigned lds, float* out32, int d, int p,
+                                             const TileNoise& na, int lane, Ready ready) {
   auto store_all = [&](auto acc_tag) {
 #pragma unroll
-    for (int i = 0; i < COUNT; ++i) {
-      const WavePiece x = piece(i);
-      store_rows<NY, F16, NOISE, OUT16, decltype(acc_tag)::value>(x.acc, held, lds, out32, x.row0, x.col0, d, p, na, lane);
-    }
+    for (int i = 0; i < COUNT; ++i)
+      store_rows<F16, NOISE, OUT16, decltype(acc_tag)::value>(piece(i), held, lds, out32, d, p, na, lane, [&]() {
+        if (i == 0) ready();
+      });
   };
   if (accumulate)
     store_all(std::true_type{});

@@ -1,7 +1,7 @@
 // Clip-weighted gradient on the matrix cores (section 3 of the paper,
 // "DP gradient"):   grad[j,k] = sum_i C_i sum_t a[i,t,j] g[i,t,k].
 //
-// 256 x 256 output tiles, one workgroup per compute unit (contraction: tn_pipeline.h), and 128 x 128
+// 256 x 256 output tiles, one workgroup per compute unit (contraction: tn_weighted.h, tn_pipeline.h), and 128 x 128
 // or 64 x 64 ones for the end of a launch and for launches that would leave compute units idle.
 #include <type_traits>
 
@@ -10,6 +10,7 @@
 #include "tile_order.h"
 #include "tn_pipeline.h"
 #include "tn_tile.h"
+#include "tn_weighted.h"
 
 namespace dpbk {
 
@@ -39,13 +40,14 @@ __device__ __forceinline__ void gradient_tile(const GroupArgs& ga, int l, int m0
   // epilogue: grad (+)= held * acc (+ noise).  With no active sample the accumulator is zero.
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int wm = (wave / S::WN) * S::WTM, wn = (wave % S::WN) * S::WTN;
-  static_assert(WaveRows<S::TN>::BYTES * S::WM * S::WN <= S::LDS_BYTES, "a region for each wave");
-  const unsigned region = (unsigned)(uintptr_t)lds_raw + wave * WaveRows<S::TN>::BYTES;
+  using Piece = WavePiece<S::TN>;
+  static_assert(Piece::BYTES * S::WM * S::WN <= S::LDS_BYTES, "a region for each wave");
+  const unsigned region = (unsigned)(uintptr_t)lds_raw + wave * Piece::BYTES;
   TileNoise tn = {};
   if (NOISE) tn = load_tile_noise(na, l);
   __syncthreads();                                     // the last fragments are read
-  store_pieces<S::TM, S::TN, F16, NOISE, OUT16>(
-      [&](int x) { return WavePiece{acc[x], m0 + wm + x * 32, n0 + wn}; }, ga.accumulate, held, region, ly.out, d, p, tn, lane);
+  store_pieces<S::TM, F16, NOISE, OUT16>([&](int x) { return Piece{acc[x], m0 + wm + x * 32, n0 + wn}; }, ga.accumulate, held,
+                                         region, ly.out, d, p, tn, lane, []() {});
 }
 
 template <bool F16, bool NOISE, bool OUT16>
@@ -58,6 +60,40 @@ clipped_grad_big_kernel(const GroupArgs ga, const float* __restrict__ C_all, con
   int m0, n0;
   locate_tile(ga, l, logical, m0, n0);
   gradient_tile<BigTile, F16, NOISE, OUT16>(ga, l, m0, n0, C, w, na);
+}
+
+// Epilogue of the kernels of whole k-blocks.
+template <class S, bool F16, bool NOISE, bool OUT16>
+struct StoreTile {
+  const GroupArgs& ga;
+  const NoiseArgs& na;
+  template <class Ready>
+  __device__ __forceinline__ void operator()(const WeightedTile& t, const f32x4 (&acc)[S::WTM / 16][S::WTN / 16], float held,
+                                             unsigned region, int wm, int wn, Ready ready) const {
+    static_assert(WavePiece16::BYTES * S::WM * S::WN <= S::STAGE_BYTES, "a region for each wave");
+    const GroupLayer& ly = ga.layer[t.l];
+    TileNoise tn = {};
+    if (NOISE) tn = load_tile_noise(na, t.l);
+    store_pieces<S::WTM / 16, F16, NOISE, OUT16>(
+        [&](int x) { return WavePiece16{&acc[x][0], t.m0 + wm + x * 16, t.n0 + wn}; }, ga.accumulate, held, region, ly.out,
+        ly.d_in, ly.d_out, tn, threadIdx.x & 63, ready);
+  }
+};
+
+struct BigTiles {
+  int total;
+  __device__ __forceinline__ int tile(int id) const { return grad_logical_tile(id, total); }
+  __device__ __forceinline__ bool operator()(const GroupArgs& ga, WeightedTile& t, int id) const {
+    locate_tile(ga, t.l, tile(id), t.m0, t.n0);
+    return true;
+  }
+};
+
+template <bool F16, bool NOISE, bool OUT16>
+__global__ void __launch_bounds__(BigTile::NT)
+clipped_grad_blocks_kernel(const GroupArgs ga, const float* __restrict__ C_all, const NoiseArgs na) {
+  weighted_tiles<BigTile, F16, true>(ga, C_all, blockIdx.x, gridDim.x, ga.total_blocks, BigTiles{ga.total_blocks},
+                                     StoreTile<BigTile, F16, NOISE, OUT16>{ga, na});
 }
 
 // End of a launch.  All tiles of a launch take the same time and one workgroup fills a compute
@@ -80,6 +116,25 @@ clipped_grad_mid_kernel(const GroupArgs ga, const float* C_all, int first_tile, 
   n0 += sub.col * MidTile::BN;
   if (m0 >= ga.layer[l].d_in || n0 >= ga.layer[l].d_out) return;      // past the layer's edge (whole workgroup)
   gradient_tile<S, F16, NOISE, OUT16>(ga, l, m0, n0, C, w, na);
+}
+
+struct MidTiles {
+  int first_tile;
+  __device__ __forceinline__ SubTile sub(int id) const { return grad_sub_tile<MID_SIDE>(id, gridDim.x); }
+  __device__ __forceinline__ int tile(int id) const { return first_tile + sub(id).tile; }
+  __device__ __forceinline__ bool operator()(const GroupArgs& ga, WeightedTile& t, int id) const {
+    locate_tile(ga, t.l, tile(id), t.m0, t.n0);
+    t.m0 += sub(id).row * MidTile::BM;
+    t.n0 += sub(id).col * MidTile::BN;
+    return t.m0 < ga.layer[t.l].d_in && t.n0 < ga.layer[t.l].d_out;
+  }
+};
+
+template <class S, bool F16, bool NOISE, bool OUT16>
+__global__ void __launch_bounds__(S::NT, 163840 / S::LDS_BYTES)
+clipped_grad_mid_blocks_kernel(const GroupArgs ga, const float* C_all, int first_tile, const NoiseArgs na) {
+  weighted_tiles<S, F16, false>(ga, C_all, blockIdx.x, gridDim.x, gridDim.x, MidTiles{first_tile},
+                                StoreTile<S, F16, NOISE, OUT16>{ga, na});
 }
 
 // ---------------------------------------------------------------------------------
@@ -231,12 +286,12 @@ __device__ __forceinline__ void clipped_grad_tile_deep(const GroupLayer& ly, int
   }
 
   // epilogue; everyone is past the loop's last barrier
-  static_assert(WaveRows<1>::BYTES * 4 <= S::LDS_BYTES, "a region for each wave");
-  const unsigned region = (unsigned)(uintptr_t)lds + wave * WaveRows<1>::BYTES;
+  static_assert(WavePiece<1>::BYTES * 4 <= S::LDS_BYTES, "a region for each wave");
+  const unsigned region = (unsigned)(uintptr_t)lds + wave * WavePiece<1>::BYTES;
   TileNoise tn = {};
   if (NOISE) tn = load_tile_noise(na, layer);
-  store_pieces<1, 1, F16, NOISE, OUT16>([&](int) { return WavePiece{acc[0], m0 + wm, n0 + wn}; }, accumulate, held, region,
-                                        ly.out, d, p, tn, lane);
+  store_pieces<1, F16, NOISE, OUT16>([&](int) { return WavePiece<1>{acc[0], m0 + wm, n0 + wn}; }, accumulate, held, region,
+                                     ly.out, d, p, tn, lane, []() {});
 }
 
 // Sub-tiles are 64 x 64 (16 per tile), k-blocks of 64 rows, four k-blocks in flight: three
@@ -323,34 +378,50 @@ GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows, bool whole_lines,
   return {tail, tail <= kTailMax ? TAIL_SIDE : MID_SIDE, false};
 }
 
+// The kernels of tn_weighted.h, whose samples take whole k-blocks of 32 rows, where the rows that are zeros cost less than 16x16x32
+// matrix instructions gain.  Gradients with noise, us, 16-row steps of 32x32x16 and whole k-blocks: samples that fill an even
+// number of 16-row steps: 8 x 64 tokens, 20 layers of width 896 40.7, 39.9; 16 x 64 69.7, 64.0; 8 x 96, six of width 2048 64.6, 60.4;
+// 16 x 256, twelve 512 x 512 43.1, 41.2; one sample of 64 tokens 21.3, 21.9; one k-block a sample: 64 x 32, 24 of width 1280
+// 207, 217.  An odd number: 32 x 48, 24 of width 1280 170, 185; 20 x 80 160, 169; 24 x 144, 32 of width 1024 245, 254; 10 x 176, 24 of
+// width 1280 161, 163; 32 x 197, 48 of width 768 1072, 1079; 3 x 240, 20 of width 896 47.8, 48.0; 8 x 240, 24 of width 1280 169.3, 167.5.
+bool whole_blocks(int B, int T) {
+  const int steps = (T + 15) / 16;
+  return (int64_t)B * T > 128 && steps >= (steps % 2 == 0 ? 4 : 15);
+}
+
 template <bool F16, bool NOISE, bool OUT16>
 dp_status launch_clipped_grad_big_group_t(const GroupArgs& ga, const float* C, const NoiseArgs& na,
                                           hipStream_t s) {
-  auto big = clipped_grad_big_kernel<F16, NOISE, OUT16>;
-  auto mid = clipped_grad_mid_kernel<MidTile, F16, NOISE, OUT16>;
-  auto brief = clipped_grad_mid_kernel<ShortTile, F16, NOISE, OUT16>;
-  auto tail = clipped_grad_tail_kernel<F16, NOISE, OUT16>;
-  static ReadyTable ready_big, ready_mid, ready_tail;
-  dp_status st = allow_big_lds(big, BigTile::LDS_BYTES, ready_big);
-  if (st == DP_OK) st = allow_big_lds(mid, MidTile::LDS_BYTES, ready_mid);
-  if (st == DP_OK) st = allow_big_lds(tail, (int)TailShape::LDS_BYTES, ready_tail);
-  if (st != DP_OK) return st;
   const int n = ga.total_blocks;
   int64_t n_mid = 0, rows = 0;
-  bool whole_lines = true;
+  bool whole_lines = true, one_length = true, blocks = true;
   for (int j = 0; j < ga.n_layers; ++j) {
     const GroupLayer& ly = ga.layer[j];
     n_mid += clipped_grad_mid_tiles(ly.d_in, ly.d_out);
     whole_lines = whole_lines && ly.d_in % 64 == 0 && ly.d_out % 64 == 0;
+    one_length = one_length && ly.T == ga.layer[0].T;
+    blocks = blocks && whole_blocks(ga.B, ly.T);
     const int64_t r = (int64_t)ga.B * ((ly.T + BigTile::BK - 1) / BigTile::BK) * BigTile::BK;
     rows = r > rows ? r : rows;
   }
+  auto big = blocks ? clipped_grad_blocks_kernel<F16, NOISE, OUT16> : clipped_grad_big_kernel<F16, NOISE, OUT16>;
+  auto mid = blocks ? clipped_grad_mid_blocks_kernel<MidTile, F16, NOISE, OUT16> : clipped_grad_mid_kernel<MidTile, F16, NOISE, OUT16>;
+  auto brief =
+      blocks ? clipped_grad_mid_blocks_kernel<ShortTile, F16, NOISE, OUT16> : clipped_grad_mid_kernel<ShortTile, F16, NOISE, OUT16>;
+  auto tail = clipped_grad_tail_kernel<F16, NOISE, OUT16>;
+  static ReadyTable ready_big[2], ready_mid[2], ready_tail;
+  dp_status st = allow_big_lds(big, BigTile::LDS_BYTES, ready_big[blocks]);
+  if (st == DP_OK) st = allow_big_lds(mid, MidTile::LDS_BYTES, ready_mid[blocks]);
+  if (st == DP_OK) st = allow_big_lds(tail, (int)TailShape::LDS_BYTES, ready_tail);
+  if (st != DP_OK) return st;
   const GradTail cut = clipped_grad_tail(n, n_mid, rows, whole_lines, OUT16);
   const int n_tail = cut.tiles;
   if (n > n_tail) {
     GroupArgs main_args = ga;
     main_args.total_blocks = n - n_tail;
-    hipLaunchKernelGGL(big, dim3(n - n_tail), dim3(BigTile::NT), BigTile::LDS_BYTES, s, main_args, C, na);
+    // Workgroups that go from tile to tile take equal numbers of them: for tiles of one length.
+    const int grid = blocks && one_length && ga.B <= 64 ? std::min(n - n_tail, kBigRound) : n - n_tail;
+    hipLaunchKernelGGL(big, dim3(grid), dim3(BigTile::NT), BigTile::LDS_BYTES, s, main_args, C, na);
     st = hip_status(hipGetLastError());
     if (st != DP_OK) return st;
   }

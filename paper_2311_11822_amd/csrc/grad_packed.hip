@@ -338,11 +338,11 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
   TileNoise tn = {};
   if (NOISE) tn = load_tile_noise(na, layer);
   constexpr int NY = S::TN < 2 ? 1 : 2;
-  static_assert(WaveRows<NY>::BYTES * 4 <= NSTAGE * S::STAGE_BYTES, "a region for each wave");
-  const unsigned region = lds0 + wave * WaveRows<NY>::BYTES;
-  store_pieces<S::TN / NY, NY, F16, NOISE, false>(
-      [&](int y) { return WavePiece{acc + NY * y, m0 + wm, n0 + wn + 32 * NY * y}; }, accumulate, 1.f, region, ly.out, d, p, tn,
-      lane);
+  static_assert(WavePiece<NY>::BYTES * 4 <= NSTAGE * S::STAGE_BYTES, "a region for each wave");
+  const unsigned region = lds0 + wave * WavePiece<NY>::BYTES;
+  store_pieces<S::TN / NY, F16, NOISE, false>(
+      [&](int y) { return WavePiece<NY>{acc + NY * y, m0 + wm, n0 + wn + 32 * NY * y}; }, accumulate, 1.f, region, ly.out, d, p, tn,
+      lane, []() {});
 }
 
 // GroupLayer::path holds the layer's tile shape (packed_shape).

@@ -304,6 +304,48 @@ def test_weighted_stream(side, n, B, T, zero):
         assert torch.linalg.norm(got.double() - want) <= TOL * torch.linalg.norm(want)
 
 
+# Samples in whole 32-row k-blocks, tile after tile in one workgroup (two rounds of 256 tiles and some that are cut): too few
+# blocks to join two tiles and just enough, an odd number of 16-row steps, more than 64 samples, a group without a sample
+# that counts between others, one sample alone, runs of equal weights; the same bits on the tiles of a layer by itself.
+@pytest.mark.parametrize("dtype", [si.BF16, si.F16])
+@pytest.mark.parametrize("B,T", [(2, 65 + 31), (3, 64), (5, 64), (1, 160), (4, 225), (65, 64), (130, 49)])
+def test_whole_k_blocks(dtype, B, T):
+    from paper_2311_11822_amd import binding as dp
+    d, p, n = 2056, 2312, 6
+    dt, tdt = (dp.DP_BF16, torch.bfloat16) if dtype == si.BF16 else (dp.DP_F16, torch.float16)
+    gen = torch.Generator(device="cuda").manual_seed(B * T)
+    layers = [tuple((torch.randn((B, T, w), generator=gen, device="cuda") * s).to(tdt) for w, s in ((d, 1.0), (p, 0.01)))
+              for _ in range(n)]
+    C = torch.rand((n, B), generator=gen, device="cuda") + 0.1
+    C[1, B // 2:B // 2 + 2] = 0.5
+    C[2] = 0.0                                            # nothing of this layer
+    C[3, 1:] = 0.0                                        # one sample
+    C[4, ::2] = 0.0
+    C[5] = 0.25                                           # one weight
+    grads = [torch.full((d, p), float("nan"), device="cuda") for _ in layers]
+    desc = dp.layer_array([(a, g, T, d, p, dp.DP_PATH_GHOST) for a, g in layers])
+    dp.dp_clipped_grad_grouped(desc, dt, B, C, list(range(n)), n, grads)
+    for l, (a, g) in enumerate(layers):
+        alone = torch.empty((d, p), device="cuda")
+        dp.dp_clipped_grad(a, g, dt, B, T, d, p, C[l].contiguous(), alone, 0)
+        assert torch.equal(grads[l], alone)               # whichever tiles the launch takes
+        w = (a.double() * C[l].double()[:, None, None]).reshape(B * T, d)
+        want = w.t().contiguous() @ g.double().reshape(B * T, p)
+        # exact products, sums of up to 6500 terms and B re-expressions in fp32
+        assert float((grads[l].double() - want).norm()) <= 3e-6 * float(want.norm())
+    clean = torch.cat([x.reshape(-1) for x in grads])
+    dp.dp_clipped_grad_grouped(desc, dt, B, C, list(range(n)), n, grads, 1)
+    assert torch.equal(torch.cat([x.reshape(-1) for x in grads]), 2 * clean)
+    flat = torch.empty(n * d * p, device="cuda")
+    pieces, offs = list(flat.view(n, d, p)), [l * d * p for l in range(n)]
+    noise = (1001, n * d * p - 2002, 0.5, 1.0, 3, 4)
+    dp.dp_clipped_grad_noise_multi(desc, dt, B, C[0].contiguous(), pieces, offs, 0, *noise)
+    fused = flat.clone()
+    dp.dp_clipped_grad_multi(desc, dt, B, C[0].contiguous(), pieces)
+    dp.dp_add_noise(flat.data_ptr() + 4 * noise[0], *noise)
+    assert torch.equal(fused, flat)
+
+
 # Column sums and their norm in one launch and in two: fewer and more rows than a thread takes at once, row groups that
 # do not come out even, the widest row of the one-launch form and one beyond, both sides of its line.
 @pytest.mark.parametrize("dtype", HALF)
