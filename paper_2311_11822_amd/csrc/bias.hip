@@ -74,6 +74,69 @@ bias_colsum_kernel(const void* __restrict__ g_all, int T, int p, float* __restri
   }
 }
 
+// The same of few or small strips, 64 columns each, where the kernel above is a chain of memory latencies in few workgroups:
+// thread (rg, ct) adds rows rg, rg + groups, ... of its 8 columns, ROWS rows in flight, and groups of eight row groups are
+// added up side by side.  A whole dp_bias_norm, us, 256-column strips and these: 8 x 128 tokens of 768 columns 5.33, 4.83; of 3072
+// 5.71, 5.56; 16 x 256 x 768 6.33, 5.42; 8 x 512 x 1280 9.3, 6.5; 1 x 512 x 1024 7.4, 4.5; 2 x 4096 x 768 45.8, 17.1; what streams
+// prefers the long rows: 16 x 256 x 3072 9.0, 9.7; 8 x 512 x 5120 12.4, 14.1.
+template <int DT, int THREADS, int ROWS>
+__global__ void __launch_bounds__(THREADS)
+bias_colsum_few_kernel(const uint16_t* __restrict__ g_all, int T, int p, float* __restrict__ colsum) {
+  constexpr int GROUPS = THREADS / 8, PARTS = GROUPS / 8;
+  __shared__ float red[GROUPS][65];
+  __shared__ float sub[PARTS][64];
+  const int ct = threadIdx.x & 7, rg = threadIdx.x >> 3, i = blockIdx.y;
+  const int col = blockIdx.x * 64 + ct * 8;
+  float acc[8] = {};
+  if (col < p) {
+    const uint16_t* g = g_all + (size_t)i * T * p + col;
+    for (unsigned t0 = rg; t0 < (unsigned)T; t0 += ROWS * GROUPS) {
+      uint4 w[ROWS];
+#pragma unroll
+      for (int u = 0; u < ROWS; ++u) {
+        const unsigned t = t0 + u * GROUPS;
+        w[u] = make_uint4(0, 0, 0, 0);
+        if (t < (unsigned)T) w[u] = *reinterpret_cast<const uint4*>(g + (size_t)t * p);
+      }
+#pragma unroll
+      for (int u = 0; u < ROWS; ++u) {
+        const uint32_t x[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const uint32_t pair = x[k / 2];
+          if (DT == DP_BF16)
+            acc[k] += __uint_as_float(k & 1 ? pair & 0xFFFF0000u : pair << 16);      // bf16 -> fp32 is a shift
+          else
+            acc[k] += (float)__builtin_bit_cast(_Float16, (uint16_t)(k & 1 ? pair >> 16 : pair & 0xFFFFu));
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k) red[rg][8 * ct + k] = acc[k];
+  __syncthreads();
+  const int c = threadIdx.x & 63, part = threadIdx.x >> 6;
+  float s = 0.f;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) s += red[8 * part + r][c];
+  sub[part][c] = s;
+  __syncthreads();
+  if (part == 0 && blockIdx.x * 64 + c < (unsigned)p) {
+    float total = 0.f;
+#pragma unroll
+    for (int r = 0; r < PARTS; ++r) total += sub[r][c];
+    colsum[(size_t)i * p + blockIdx.x * 64 + c] = total;
+  }
+}
+
+// Strips of 64 columns: few of them, or not many and of few values in all (both sides beside the kernel; 50 x 20 x 5000, 3950
+// strips, 7.7 and 8.4).
+constexpr int64_t kFewStrips = 256, kMostStrips = 1280, kFewValues = 6 << 20;
+bool few_strips(int B, int64_t T, int p) {
+  const int64_t strips = ((int64_t)p + 63) / 64 * B;
+  return strips <= kFewStrips || (strips <= kMostStrips && T * p <= kFewValues / B);
+}
+
 // Column sums and their norm in one launch, one workgroup to a sample, where that is no slower than two: a launch costs
 // the host 2.4 us, and a workgroup of 1024 threads that has eight loads of each in flight reads 90 GB/s.  Thread (rg, ct)
 // adds rows rg, rg + groups, ... of its 8 columns, eight rows in flight and added in pairs; the row groups are added
@@ -234,6 +297,23 @@ dp_status launch_bias_norm(const void* g, dp_dtype dt, int B, int T, int p, floa
       launch(std::integral_constant<int, 256>{});
     else
       launch(std::integral_constant<int, kOneThreads>{});
+    return hip_status(hipGetLastError());
+  }
+  if (dt != DP_F32 && few_strips(B, T, p)) {
+    auto launch = [&](auto threads_tag, auto rows_tag) {
+      constexpr int THREADS = decltype(threads_tag)::value, ROWS = decltype(rows_tag)::value;
+      auto kernel = dt == DP_BF16 ? bias_colsum_few_kernel<DP_BF16, THREADS, ROWS> : bias_colsum_few_kernel<DP_F16, THREADS, ROWS>;
+      hipLaunchKernelGGL(kernel, dim3((p + 63u) / 64, B), dim3(THREADS), 0, s, static_cast<const uint16_t*>(g), T, p, colsum);
+    };
+    using std::integral_constant;
+    if (T <= 128)                                        // one trip
+      launch(integral_constant<int, 256>{}, integral_constant<int, 4>{});
+    else if (T <= 256)
+      launch(integral_constant<int, 512>{}, integral_constant<int, 4>{});
+    else
+      launch(integral_constant<int, 512>{}, integral_constant<int, 8>{});
+    if (hipGetLastError() != hipSuccess) return DP_ERR_HIP;
+    hipLaunchKernelGGL(bias_sqnorm_kernel, dim3(B), dim3(kSqThreads), 0, s, colsum, p, sqnorm_out);
     return hip_status(hipGetLastError());
   }
   const int cols_per_block = kColThreads * (dt == DP_F32 ? 1 : 8);

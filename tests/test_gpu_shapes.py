@@ -366,6 +366,17 @@ def test_bias_norm_forms(dtype, B, T, p):
     np.testing.assert_allclose(host(sq), o.bias_sqnorm(g64), rtol=TOL)
 
 
+# Column sums in strips of 64 columns: one trip of four rows a thread and one row more, both sides of the lines between the
+# workgroups' sizes and of eight rows' trips, a strip that is not full, the last small enough call and one beyond.
+@pytest.mark.parametrize("dtype", HALF)
+@pytest.mark.parametrize("B,T,p", [
+    (8, 128, 768), (8, 129, 768), (2, 256, 1288), (2, 257, 1288), (3, 513, 520), (1, 4097, 328), (1, 2, 65544),
+    (4, 256, 6144), (4, 257, 6144), (10, 11, 8192), (10, 11, 8200),
+])
+def test_bias_norm_of_few_strips(dtype, B, T, p):
+    test_bias_norm_forms(dtype, B, T, p)
+
+
 # One call for a step against its three stages, and factors written by the kernels that finish the norms against the
 # clip kernels: the same bits.  Stacks whose norms end in every kernel: partial sums of one launch, of several and of two
 # kernels; final norms (fp32, short samples, 129 to 256 tokens in whole and ragged widths) of few workgroups and layers, and of
