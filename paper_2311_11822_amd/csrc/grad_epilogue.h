@@ -94,18 +94,25 @@ struct WavePiece {
   static __device__ __forceinline__ unsigned at(unsigned lds, int row, int quad) { return lds + row * STRIDE + quad * 16; }
 };
 
-// 16 rows of four 16 x 16 tiles: lane l has row l & 15 and the columns 4 (l >> 4) + e of a tile in register e.
-// Without room between the rows: 16 bytes are where the row's number exclusive-or'd says, so that 16 rows' are in different banks.
+// H rows of 2 NY tiles of 16 x 16: lane l has row l & 15 and the columns 4 (l >> 4) + e of a tile in register e; the tiles 16 rows
+// down are PITCH further on.  Without room between the rows: 16 bytes are where the row's number exclusive-or'd says, so
+// that 16 rows' are in different banks.
+template <int NY, int H_, int PITCH>
 struct WavePiece16 {
-  static constexpr int H = 16, W = 64;
+  static constexpr int H = H_, W = 32 * NY;
   static constexpr int BYTES = H * W * 4;
   const f32x4v* acc;
   int row0, col0;
   __device__ __forceinline__ void put(unsigned lds, int lane) const {
 #pragma unroll
-    for (int y = 0; y < 4; ++y) *(lds_f4*)(uintptr_t)at(lds, lane & 15, 4 * y + (lane >> 4)) = acc[y];
+    for (int x = 0; x < H / 16; ++x)
+#pragma unroll
+      for (int y = 0; y < 2 * NY; ++y)
+        *(lds_f4*)(uintptr_t)at(lds, 16 * x + (lane & 15), 4 * y + (lane >> 4)) = acc[PITCH * x + y];
   }
-  static __device__ __forceinline__ unsigned at(unsigned lds, int row, int quad) { return lds + row * 256 + ((quad ^ row) << 4); }
+  static __device__ __forceinline__ unsigned at(unsigned lds, int row, int quad) {
+    return lds + row * (W * 4) + ((quad ^ (NY == 1 ? row >> 1 & 7 : row & 15)) << 4);
+  }
 };
 
 // How a wave's piece leaves: N store instructions of ROWS rows, LANES lanes to a row, VEC columns a lane.

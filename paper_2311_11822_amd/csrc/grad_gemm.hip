@@ -70,12 +70,13 @@ struct StoreTile {
   template <class Ready>
   __device__ __forceinline__ void operator()(const WeightedTile& t, const f32x4 (&acc)[S::WTM / 16][S::WTN / 16], float held,
                                              unsigned region, int wm, int wn, Ready ready) const {
-    static_assert(WavePiece16::BYTES * S::WM * S::WN <= S::STAGE_BYTES, "a region for each wave");
+    using Piece = WavePiece16<2, 16, 4>;
+    static_assert(Piece::BYTES * S::WM * S::WN <= S::STAGE_BYTES, "a region for each wave");
     const GroupLayer& ly = ga.layer[t.l];
     TileNoise tn = {};
     if (NOISE) tn = load_tile_noise(na, t.l);
     store_pieces<S::WTM / 16, F16, NOISE, OUT16>(
-        [&](int x) { return WavePiece16{&acc[x][0], t.m0 + wm + x * 16, t.n0 + wn}; }, ga.accumulate, held, region, ly.out,
+        [&](int x) { return Piece{&acc[x][0], t.m0 + wm + x * 16, t.n0 + wn}; }, ga.accumulate, held, region, ly.out,
         ly.d_in, ly.d_out, tn, threadIdx.x & 63, ready);
   }
 };

@@ -5,9 +5,11 @@
 // their accumulator at every sample boundary and pad every sample to whole 32-row k-blocks: at T = 1
 // that is all they do.  Here the rows of all samples form one contraction of B T rows and the weight
 // is multiplied into the a operand in fp32; that product is then cut into three bfloat16 parts, whose
-// sum is within 2^-25 of it, so each 16-row step takes three matrix instructions and less is lost than
+// sum is within 2^-25 of it, so each 32-row step takes three matrix instructions and less is lost than
 // by rounding C a to fp32.  fp16 operands: g (11 bits) is cut into two bfloat16 parts exactly, six
-// instructions.  Gradients measured against 64 bits: 1.4e-7 (T = 1, B = 512) and 2.1e-7 (T = 31) here,
+// instructions.  They are 16x16x32 ones: the card's power holds the clock (1.25 GHz under 32x32x16), and they take less of it (gradients
+// of eight layers 1024 x 1024, us, 32x32x16 and these: 512 x 1 token 27.3, 26.3; 256 x 16 177.4, 170.4; fp16 64 x 8 49.8, 47.9; 24 of
+// 768 x 16, 512 x 32 260.0, 258.4).  Gradients measured against 64 bits: 1.4e-7 (T = 1, B = 512) and 2.1e-7 (T = 31) here,
 // 6.0e-7 and 3.9e-7 in the large-tile kernel.
 //   Measured, eight layers of 1024 x 1024 .. 4096 outputs, bf16: B = 512, T = 1: 1384 us before, 87 us here; 4096
 // rows: 570 us here for T = 16, 620 for T = 1 (what bounds it: the matrix cores at the clock they hold
@@ -51,7 +53,7 @@ constexpr int BK = 32, NSTAGE = 4, NT = 256;
 template <int BM_, int BN_, int WM_, int WN_>
 struct Shape {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
-  static constexpr int TN = BN / WN / 32;
+  static constexpr int XM = 2, XN = BN / WN / 16;               // 16 x 16 tiles of a wave
   static constexpr int A_BYTES = BK * BM * 2, B_BYTES = BK * BN * 2;
   static constexpr int W_BYTES = 256;                          // weights of the 32 rows (twice)
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES + W_BYTES;
@@ -115,8 +117,8 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave / S::WN) * 32, wn = (wave % S::WN) * (S::BN / S::WN);
 
-  RowOperand<S::BM> oa;
-  RowOperand<S::BN> ob;
+  RowOperand<S::BM, 32> oa;
+  RowOperand<S::BN, 32> ob;
   // weights: lane -> row (lane & 31) of the k-block, sample w_i and token w_t of that row
   const i32x4 rw = make_rsrc(C, (unsigned)B * 4u);
   int w_i, w_t;
@@ -145,11 +147,12 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
     p_stage = p_stage + 1 == NSTAGE ? 0 : p_stage + 1;
   };
 
-  const unsigned a_rd = lds0 + row_frag_base<S::BM>(wm, lane);
-  unsigned b_rd[S::TN];
+  unsigned a_rd[S::XM], b_rd[S::XN];
 #pragma unroll
-  for (int y = 0; y < S::TN; ++y) b_rd[y] = lds0 + S::A_BYTES + row_frag_base<S::BN>(wn + 32 * y, lane);
-  const unsigned w_rd = lds0 + S::A_BYTES + S::B_BYTES + 32u * (lane >> 5);
+  for (int x = 0; x < S::XM; ++x) a_rd[x] = lds0 + row_frag_base<S::BM, 32>(wm + 16 * x, lane);
+#pragma unroll
+  for (int y = 0; y < S::XN; ++y) b_rd[y] = lds0 + S::A_BYTES + row_frag_base<S::BN, 32>(wn + 16 * y, lane);
+  const unsigned w_rd = lds0 + S::A_BYTES + S::B_BYTES + 32u * (lane >> 4);
 
   typedef __attribute__((ext_vector_type(4))) float f4;
   typedef __attribute__((address_space(3))) f4 lds_f4;
@@ -157,11 +160,14 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
   constexpr int G_PARTS = F16 ? 2 : 1;
   // The products of the low parts go to sums of their own, whose roundings are 2^-8 of the others': the
   // result is rounded as often as one matrix instruction per step would.
-  f32x16 acc[S::TN], low[S::TN];
+  f32x4 acc[S::XM][S::XN], low[S::XM][S::XN];
+  auto clear = [&]() {
 #pragma unroll
-  for (int y = 0; y < S::TN; ++y)
+    for (int x = 0; x < S::XM; ++x)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[y][r] = low[y][r] = 0.f;
+      for (int y = 0; y < S::XN; ++y) acc[x][y] = low[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  clear();
 
   float least_w = INFINITY;                              // smallest non-zero weight that this lane met
 
@@ -178,74 +184,74 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
     issue();
     const unsigned so = stage * S::STAGE_BYTES;
     const float own = *(const lds_float*)(uintptr_t)(lds0 + so + S::A_BYTES + S::B_BYTES + 4 * lane);  // row lane & 31
-    f4 w[2][2];                                          // weights of this lane's 8 rows, per 16-row step
-    u32x4 fa[2], fb[2][S::TN];
+    u32x4 fa[S::XM], fb[S::XN];
+    const lds_f4* wp = (const lds_f4*)(uintptr_t)(w_rd + so);
+    f4 w[2] = {wp[0], wp[1]};                            // weights of this lane's 8 rows
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const lds_f4* wp = (const lds_f4*)(uintptr_t)(w_rd + so + ks * 64);
-      w[ks][0] = wp[0];
-      w[ks][1] = wp[1];
-      fa[ks] = __builtin_bit_cast(u32x4, read_row_frag<S::BM>(a_rd + so + ks * 16 * S::BM * 2));
+    for (int x = 0; x < S::XM; ++x) fa[x] = __builtin_bit_cast(u32x4, read_row_frag<S::BM>(a_rd[x] + so));
 #pragma unroll
-      for (int y = 0; y < S::TN; ++y)
-        fb[ks][y] = __builtin_bit_cast(u32x4, read_row_frag<S::BN>(b_rd[y] + so + ks * 16 * S::BN * 2));
-    }
+    for (int y = 0; y < S::XN; ++y) fb[y] = __builtin_bit_cast(u32x4, read_row_frag<S::BN>(b_rd[y] + so));
     DP_PIN();
     least_w = own == 0.f ? least_w : fminf(least_w, fabsf(own));
     if (__any(own == 0.f)) {                             // rows that do not count (or lie past the end)
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int ks = q >> 2, e = 2 * q & 3;
-        const f4 ww = w[ks][(q >> 1) & 1];
+      for (int q = 0; q < 4; ++q) {
+        const int e = 2 * q & 3;
+        const f4 ww = w[q >> 1];
         const uint32_t m = (ww[e] == 0.f ? 0u : 0xFFFFu) | (ww[e + 1] == 0.f ? 0u : 0xFFFF0000u);
-        fa[ks][q & 3] &= m;
 #pragma unroll
-        for (int y = 0; y < S::TN; ++y) fb[ks][y][q & 3] &= m;
+        for (int x = 0; x < S::XM; ++x) fa[x][q] &= m;
+#pragma unroll
+        for (int y = 0; y < S::XN; ++y) fb[y][q] &= m;
       }
     }
-    // The second step's cutting fills the gaps between the first step's matrix instructions.
-    u32x4 xa[2][3], xb[2][S::TN][G_PARTS];
-    auto cut = [&](int ks) {
+    w[0] *= kScale;
+    w[1] *= kScale;
+    // The second half's cutting fills the gaps between the first half's matrix instructions.
+    u32x4 xa[S::XM][3], xb[S::XN][G_PARTS];
+    auto cut = [&](int x) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const f4 ww = w[ks][q >> 1];
+        const f4 ww = w[q >> 1];
         const int e = 2 * q & 3;
         uint32_t part[3];
-        cut_product(ww[e] * kScale, widen_lo<F16>(fa[ks][q]), ww[e + 1] * kScale, widen_hi<F16>(fa[ks][q]), part);
+        cut_product(ww[e], widen_lo<F16>(fa[x][q]), ww[e + 1], widen_hi<F16>(fa[x][q]), part);
 #pragma unroll
-        for (int n = 0; n < 3; ++n) xa[ks][n][q] = part[n];
-#pragma unroll
-        for (int y = 0; y < S::TN; ++y) {
-          if constexpr (F16) {
-            uint32_t gp[2];
-            cut_f16(fb[ks][y][q], gp);
-#pragma unroll
-            for (int m = 0; m < G_PARTS; ++m) xb[ks][y][m][q] = gp[m];
-          } else {
-            xb[ks][y][0][q] = fb[ks][y][q];
-          }
-        }
+        for (int n = 0; n < 3; ++n) xa[x][n][q] = part[n];
       }
     };
-    auto multiply = [&](int ks) {
+    auto multiply = [&](int x) {
 #pragma unroll
       for (int n = 2; n >= 0; --n)
 #pragma unroll
         for (int m = G_PARTS - 1; m >= 0; --m)
 #pragma unroll
-          for (int y = 0; y < S::TN; ++y) {
-            f32x16& sum = n + m ? low[y] : acc[y];
-            sum = mfma16<false>(__builtin_bit_cast(bf16x8, xb[ks][y][m]), __builtin_bit_cast(bf16x8, xa[ks][n]), sum);
+          for (int y = 0; y < S::XN; ++y) {
+            f32x4& sum = n + m ? low[x][y] : acc[x][y];
+            sum = mfma16<false>(__builtin_bit_cast(bf16x8, xb[y][m]), __builtin_bit_cast(bf16x8, xa[x][n]), sum);
           }
     };
     cut(0);
+#pragma unroll
+    for (int y = 0; y < S::XN; ++y)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if constexpr (F16) {
+          uint32_t gp[2];
+          cut_f16(fb[y][q], gp);
+#pragma unroll
+          for (int m = 0; m < G_PARTS; ++m) xb[y][m][q] = gp[m];
+        } else {
+          xb[y][0][q] = fb[y][q];
+        }
+      }
     DP_PIN();
     multiply(0);
     cut(1);
 #pragma unroll
-    for (int n = 0; n < 3 * G_PARTS * S::TN; ++n) {
+    for (int n = 0; n < 3 * G_PARTS * S::XN; ++n) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                       // one MFMA
-      __builtin_amdgcn_sched_group_barrier(0x002, F16 ? 8 : 6, 0);             // some vector-ALU instructions
+      __builtin_amdgcn_sched_group_barrier(0x002, F16 ? 3 : S::XN == 4 ? 5 : 2, 0);   // some vector-ALU instructions, as measured
     }
     DP_PIN();
     multiply(1);
@@ -255,12 +261,14 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
 
   float largest = 0.f;                                   // NaN if a sum is
 #pragma unroll
-  for (int y = 0; y < S::TN; ++y)
+  for (int x = 0; x < S::XM; ++x)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      acc[y][r] = (acc[y][r] + low[y][r]) * (1.f / kScale);
-      largest = __builtin_elementwise_maximum(largest, fabsf(acc[y][r]));
-    }
+    for (int y = 0; y < S::XN; ++y)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        acc[x][y][r] = (acc[x][y][r] + low[x][y][r]) * (1.f / kScale);
+        largest = __builtin_elementwise_maximum(largest, fabsf(acc[x][y][r]));
+      }
   const bool off = least_w < kLeastWeight<F16> || !(largest <= FLT_MAX);
   typedef __attribute__((address_space(3))) int lds_int;
   const bool wave_off = __any(off);
@@ -271,10 +279,7 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
   for (int v = 0; v < 4; ++v) any_off |= *(lds_int*)(uintptr_t)(lds0 + FLAGS + 4 * v);
   if (__builtin_amdgcn_readfirstlane(any_off)) {
     // The tile again, unweighted, sample by sample (low: the sample's sum so far).
-#pragma unroll
-    for (int y = 0; y < S::TN; ++y)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[y][r] = low[y][r] = 0.f;
+    clear();
     rewind();
     for (int q = 0; q < NSTAGE - 1; ++q) issue();
     stage = 0;
@@ -283,14 +288,11 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
       asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NSTAGE - 2) * S::LOADS) : "memory");
       issue();
       const unsigned so = stage * S::STAGE_BYTES;
-      u32x4 fa[2], fb[2][S::TN];
+      u32x4 fa[S::XM], fb[S::XN];
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        fa[ks] = __builtin_bit_cast(u32x4, read_row_frag<S::BM>(a_rd + so + ks * 16 * S::BM * 2));
+      for (int x = 0; x < S::XM; ++x) fa[x] = __builtin_bit_cast(u32x4, read_row_frag<S::BM>(a_rd[x] + so));
 #pragma unroll
-        for (int y = 0; y < S::TN; ++y)
-          fb[ks][y] = __builtin_bit_cast(u32x4, read_row_frag<S::BN>(b_rd[y] + so + ks * 16 * S::BN * 2));
-      }
+      for (int y = 0; y < S::XN; ++y) fb[y] = __builtin_bit_cast(u32x4, read_row_frag<S::BN>(b_rd[y] + so));
       const int here = min(BK, rows - kb * BK);
 #pragma unroll 1
       for (int begin = 0; begin < here;) {
@@ -298,20 +300,18 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
         const int c_bits = *(const lds_int*)(uintptr_t)(lds0 + so + S::A_BYTES + S::B_BYTES + 4 * begin);
         const float c = __int_as_float(__builtin_amdgcn_readfirstlane(c_bits));
         if (c != 0.f) {
+          u32x4 keep;                                    // this lane's rows 8 (lane >> 4) + 0 .. 7
 #pragma unroll
-          for (int ks = 0; ks < 2; ++ks) {
-            u32x4 keep;                                  // this lane's rows 16 ks + 8 (lane >> 5) + 0 .. 7
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const int row = 16 * ks + 8 * (lane >> 5) + 2 * q;
-              keep[q] = (row >= begin && row < end ? 0xFFFFu : 0u) |
-                        (row + 1 >= begin && row + 1 < end ? 0xFFFF0000u : 0u);
-            }
-            const bf16x8 x = __builtin_bit_cast(bf16x8, fa[ks] & keep);
-#pragma unroll
-            for (int y = 0; y < S::TN; ++y)
-              low[y] = mfma16<F16>(__builtin_bit_cast(bf16x8, fb[ks][y] & keep), x, low[y]);
+          for (int q = 0; q < 4; ++q) {
+            const int row = 8 * (lane >> 4) + 2 * q;
+            keep[q] = (row >= begin && row < end ? 0xFFFFu : 0u) |
+                      (row + 1 >= begin && row + 1 < end ? 0xFFFF0000u : 0u);
           }
+#pragma unroll
+          for (int x = 0; x < S::XM; ++x)
+#pragma unroll
+            for (int y = 0; y < S::XN; ++y)
+              low[x][y] = mfma16<F16>(__builtin_bit_cast(bf16x8, fb[y] & keep), __builtin_bit_cast(bf16x8, fa[x] & keep), low[x][y]);
         }
         left -= end - begin;
         begin = end;
@@ -319,12 +319,14 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
           left = T;
           if (c != 0.f) {
 #pragma unroll
-            for (int y = 0; y < S::TN; ++y)
+            for (int x = 0; x < S::XM; ++x)
 #pragma unroll
-              for (int r = 0; r < 16; ++r) {
-                acc[y][r] = fmaf(c, low[y][r], acc[y][r]);
-                low[y][r] = 0.f;
-              }
+              for (int y = 0; y < S::XN; ++y)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                  acc[x][y][r] = fmaf(c, low[x][y][r], acc[x][y][r]);
+                  low[x][y][r] = 0.f;
+                }
           }
         }
       }
@@ -337,12 +339,12 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
   // epilogue; nobody reads a stage any more
   TileNoise tn = {};
   if (NOISE) tn = load_tile_noise(na, layer);
-  constexpr int NY = S::TN < 2 ? 1 : 2;
-  static_assert(WavePiece<NY>::BYTES * 4 <= NSTAGE * S::STAGE_BYTES, "a region for each wave");
-  const unsigned region = lds0 + wave * WavePiece<NY>::BYTES;
-  store_pieces<S::TN / NY, F16, NOISE, false>(
-      [&](int y) { return WavePiece<NY>{acc + NY * y, m0 + wm, n0 + wn + 32 * NY * y}; }, accumulate, 1.f, region, ly.out, d, p, tn,
-      lane, []() {});
+  constexpr int NY = S::XN == 2 ? 1 : 2;
+  using Piece = WavePiece16<NY, 32, S::XN>;
+  static_assert(Piece::BYTES * 4 <= NSTAGE * S::STAGE_BYTES && S::XM == 2, "a region for each wave");
+  store_pieces<S::XN / (2 * NY), F16, NOISE, false>(
+      [&](int y) { return Piece{&acc[0][2 * NY * y], m0 + wm, n0 + wn + 32 * NY * y}; }, accumulate, 1.f,
+      lds0 + wave * Piece::BYTES, ly.out, d, p, tn, lane, []() {});
 }
 
 // GroupLayer::path holds the layer's tile shape (packed_shape).

@@ -40,8 +40,8 @@ __device__ __forceinline__ void narrow_tile(const GroupLayer& ly, int sample, in
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave / S::WN) * 32, wn = (wave % S::WN) * (S::BN / S::WN);
 
-  RowOperand<S::BM> oa;
-  RowOperand<S::BN> ob;
+  RowOperand<S::BM, 16> oa;
+  RowOperand<S::BN, 16> ob;
   oa.init(static_cast<const uint16_t*>(ly.a) + (size_t)sample * T * d, T, d, m0, lds0, wave, lane);
   ob.init(static_cast<const uint16_t*>(ly.g) + (size_t)sample * T * p, T, p, n0, lds0 + S::A_BYTES, wave, lane);
   int p_stage = 0;
@@ -50,10 +50,10 @@ __device__ __forceinline__ void narrow_tile(const GroupLayer& ly, int sample, in
     ob.issue(p_stage * S::STAGE_BYTES, lane);
     p_stage = p_stage + 1 == NSTAGE ? 0 : p_stage + 1;
   };
-  const unsigned a_rd = lds0 + row_frag_base<S::BM>(wm, lane);
+  const unsigned a_rd = lds0 + row_frag_base<S::BM, 16>(wm, lane);
   unsigned b_rd[S::TN];
 #pragma unroll
-  for (int y = 0; y < S::TN; ++y) b_rd[y] = lds0 + S::A_BYTES + row_frag_base<S::BN>(wn + 32 * y, lane);
+  for (int y = 0; y < S::TN; ++y) b_rd[y] = lds0 + S::A_BYTES + row_frag_base<S::BN, 16>(wn + 32 * y, lane);
   f32x16 acc[S::TN];
 #pragma unroll
   for (int y = 0; y < S::TN; ++y)

@@ -31,17 +31,6 @@
 
 namespace dpbk {
 
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
-// One 16x16x32 matrix-core step.
-template <bool F16>
-__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
-  if constexpr (F16)
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
 // c *= f (the bits of a float).  Inside the assembly the accumulator stays one operand: with multiplies of its own the
 // compiler moves accumulators through copies.  A tuple prints as v[first:last]; the inner loop reads `first` off it.
 // The compiler does not see into it, so the waits are counted here: a vector instruction may touch the result of one
