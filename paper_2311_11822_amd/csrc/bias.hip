@@ -129,12 +129,12 @@ bias_colsum_few_kernel(const uint16_t* __restrict__ g_all, int T, int p, float* 
   }
 }
 
-// Strips of 64 columns: few of them, or not many and of few values in all (both sides beside the kernel; 50 x 20 x 5000, 3950
-// strips, 7.7 and 8.4).
+// Strips of 64 columns: few of them, or not many, of few values in all and of whole 128-byte lines (both sides beside the kernel;
+// 50 x 20 x 5000, 3950 strips, 7.7 and 8.4; 55 x 136 x 696, rows of 1392 bytes, 7.1 and 7.9).
 constexpr int64_t kFewStrips = 256, kMostStrips = 1280, kFewValues = 6 << 20;
 bool few_strips(int B, int64_t T, int p) {
   const int64_t strips = ((int64_t)p + 63) / 64 * B;
-  return strips <= kFewStrips || (strips <= kMostStrips && T * p <= kFewValues / B);
+  return strips <= kFewStrips || (p % 64 == 0 && strips <= kMostStrips && T * p <= kFewValues / B);
 }
 
 // Column sums and their norm in one launch, one workgroup to a sample, where that is no slower than two: a launch costs
