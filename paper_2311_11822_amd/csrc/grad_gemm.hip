@@ -9,7 +9,6 @@
 #include "grad_epilogue.h"
 #include "tile_order.h"
 #include "tn_pipeline.h"
-#include "tn_tile.h"
 #include "tn_weighted.h"
 
 namespace dpbk {
@@ -138,186 +137,37 @@ clipped_grad_mid_blocks_kernel(const GroupArgs ga, const float* C_all, int first
                                 StoreTile<S, F16, NOISE, OUT16>{ga, na});
 }
 
-// ---------------------------------------------------------------------------------
-// The last few tiles of a launch are cut finer still, into TAIL x TAIL sub-tiles of one small
-// workgroup each (register-staged tile code of tn_tile.h), which spreads them over the whole
-// chip.
-// ---------------------------------------------------------------------------------
-#ifndef DP_TAIL_SHAPE
-#define DP_TAIL_SHAPE 64, 64, 64, 2, 2
-#endif
-#ifndef DP_TAIL_DEPTH
-#define DP_TAIL_DEPTH 4
-#endif
-
-typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
-
-// One small output tile with D k-blocks in flight between memory and LDS (register slots used
-// in rotation, the loop unrolled D times so that every slot index is a constant).  A small
-// tile's k-block holds too little arithmetic to cover the latency of the next one's loads,
-// and with one wave per SIMD every instruction of the loop counts: the loads are buffer loads
-// whose range check zero-fills what lies outside the sample's slab (rows past T, columns past
-// the layer's edge through the OOB offset, blocks past the last sample through an empty
-// descriptor), so a k-block costs one add and one load per 16 bytes and nothing is
-// conditional: the number of loads in flight is a compile-time constant and a thread waits only
-// for the slot it is about to store.  Two LDS stages, one barrier per k-block.  The k-steps of an output element are added in
-// the same order as in the large kernel.
-template <class S, int D, bool F16, bool NOISE, bool OUT16>
-__device__ __forceinline__ void clipped_grad_tile_deep(const GroupLayer& ly, int B, int accumulate,
-                                                       const NoiseArgs& na, int layer, int m0, int n0,
-                                                       const __attribute__((address_space(4))) float* C,
-                                                       uint16_t* lds) {
-  static_assert(D % 2 == 0, "the LDS stage of slot q is q & 1");
-  const int tid = threadIdx.x;
-  const int T = ly.T, d = ly.d_in, p = ly.d_out;
-  const int nkb = (T + S::BK - 1) / S::BK;
-  const unsigned a_slab = (unsigned)T * d * 2u, b_slab = (unsigned)T * p * 2u;
-  const unsigned a_step = (unsigned)S::BK * d * 2u, b_step = (unsigned)S::BK * p * 2u;
-  const unsigned char* a_base = static_cast<const unsigned char*>(ly.a);
-  const unsigned char* b_base = static_cast<const unsigned char*>(ly.g);
-
-  // Per-thread geometry of the loads of one k-block: byte offset inside the slab (k-block 0)
-  // and element offset inside the LDS stage.
-  unsigned va[S::A_PER_T], vb[S::B_PER_T];
-  int sta[S::A_PER_T], stb[S::B_PER_T];
-#pragma unroll
-  for (int j = 0; j < S::A_PER_T; ++j) {
-    const int c = tid + j * S::NT, row = c / (S::BM / 8), col = (c % (S::BM / 8)) * 8;
-    va[j] = m0 + col < d ? (unsigned)(row * d + m0 + col) * 2u : OOB;
-    sta[j] = row * S::SA + col;
-  }
-#pragma unroll
-  for (int j = 0; j < S::B_PER_T; ++j) {
-    const int c = tid + j * S::NT, row = c / (S::BN / 8), col = (c % (S::BN / 8)) * 8;
-    vb[j] = n0 + col < p ? (unsigned)(row * p + n0 + col) * 2u : OOB;
-    stb[j] = S::BK * S::SA + row * S::SB + col;
-  }
-
-  // All operand fragments of a k-block are requested from LDS before its first MFMA, so one LDS
-  // latency is exposed per k-block instead of one per MFMA (a wave has nothing else to run).
-  static_assert(S::TM == 1 && S::TN == 1, "one 32 x 32 MFMA tile per wave");
-  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = (wave / S::WN) * S::WTM, wn = (wave % S::WN) * S::WTN;
-  auto compute = [&](const uint16_t* stage, f32x16& c) {
-    constexpr int KS = S::BK / 16;
-    bf16x8 fa[KS], fb[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      fa[ks] = read_frag_tr(stage, S::SA, ks * 16, wm, lane);
-      fb[ks] = read_frag_tr(stage + S::BK * S::SA, S::SB, ks * 16, wn, lane);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) c = mfma16<F16>(fb[ks], fa[ks], c);
-  };
-  u32x4 sa[D][S::A_PER_T], sb[D][S::B_PER_T];
-  f32x16 acc[S::TM][S::TN];
-  zero_acc<S>(acc);
-
-  // (sample, k-block) cursors over the samples with a non-zero weight: ld = next block to
-  // request from memory, cp = next block to compute.
-  int ld_i = 0, ld_kb = 0, cp_i, cp_kb = 0, active = 0;
-  for (int i = 0; i < B; ++i) active += C[i] != 0.f;
-  while (ld_i < B && C[ld_i] == 0.f) ++ld_i;
-  cp_i = ld_i;
-  float held = cp_i < B ? C[cp_i] : 0.f;   // weight the accumulator is currently expressed in
-  __amdgpu_buffer_rsrc_t ra, rb;
-  unsigned koff_a = 0, koff_b = 0;         // byte offset of the load cursor's k-block in the slab
-  auto open_sample = [&]() {
-    const bool valid = ld_i < B;
-    const int smp = valid ? ld_i : 0;
-    ra = __builtin_amdgcn_make_buffer_rsrc((void*)(a_base + (size_t)smp * a_slab), 0,
-                                           valid ? (int)a_slab : 0, 0x00020000);
-    rb = __builtin_amdgcn_make_buffer_rsrc((void*)(b_base + (size_t)smp * b_slab), 0,
-                                           valid ? (int)b_slab : 0, 0x00020000);
-    koff_a = 0;
-    koff_b = 0;
-  };
-  open_sample();
-  auto fetch = [&](u32x4 (&xa)[S::A_PER_T], u32x4 (&xb)[S::B_PER_T]) {
-#pragma unroll
-    for (int j = 0; j < S::A_PER_T; ++j)
-      xa[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ra, va[j] + koff_a, 0, 0));
-#pragma unroll
-    for (int j = 0; j < S::B_PER_T; ++j)
-      xb[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rb, vb[j] + koff_b, 0, 0));
-    koff_a += a_step;
-    koff_b += b_step;
-    if (ld_i < B && ++ld_kb == nkb) {
-      ld_kb = 0;
-      ++ld_i;
-      while (ld_i < B && C[ld_i] == 0.f) ++ld_i;
-      open_sample();
-    }
-  };
-#pragma unroll
-  for (int q = 0; q < D; ++q) fetch(sa[q], sb[q]);
-  auto store = [&](uint16_t* stage, const u32x4 (&xa)[S::A_PER_T], const u32x4 (&xb)[S::B_PER_T]) {
-#pragma unroll
-    for (int j = 0; j < S::A_PER_T; ++j) *reinterpret_cast<u32x4*>(stage + sta[j]) = xa[j];
-#pragma unroll
-    for (int j = 0; j < S::B_PER_T; ++j) *reinterpret_cast<u32x4*>(stage + stb[j]) = xb[j];
-  };
-  // Block n is computed from stage n & 1 while block n + 1 is being written to the other stage;
-  // the barrier at the end of an iteration certifies both that write and that nobody still
-  // reads the stage the next iteration overwrites.
-  const int blocks = active * nkb;
-  store(lds, sa[0], sb[0]);
-  fetch(sa[0], sb[0]);
-  __syncthreads();
-  for (int n = 0; n < blocks; n += D) {
-#pragma unroll
-    for (int q = 0; q < D; ++q) {
-      const int nq = (q + 1) % D;
-      store(lds + ((q + 1) & 1) * S::STAGE, sa[nq], sb[nq]);
-      fetch(sa[nq], sb[nq]);
-      compute(lds + (q & 1) * S::STAGE, acc[0][0]);
-      __syncthreads();
-      if (cp_i < B && ++cp_kb == nkb) {
-        cp_kb = 0;
-        ++cp_i;
-        while (cp_i < B && C[cp_i] == 0.f) ++cp_i;
-        if (cp_i < B) {                   // next block starts another sample: re-express acc
-          const float c = C[cp_i];
-          scale_acc<S>(acc, held / c);
-          held = c;
-        }
-      }
-    }
-  }
-
-  // epilogue; everyone is past the loop's last barrier
-  static_assert(WavePiece<1>::BYTES * 4 <= S::LDS_BYTES, "a region for each wave");
-  const unsigned region = (unsigned)(uintptr_t)lds + wave * WavePiece<1>::BYTES;
-  TileNoise tn = {};
-  if (NOISE) tn = load_tile_noise(na, layer);
-  store_pieces<1, F16, NOISE, OUT16>([&](int) { return WavePiece<1>{acc[0], m0 + wm, n0 + wn}; }, accumulate, held, region,
-                                     ly.out, d, p, tn, lane, []() {});
-}
-
-// Sub-tiles are 64 x 64 (16 per tile), k-blocks of 64 rows, four k-blocks in flight: three
-// workgroups fit in a compute unit's LDS.
-using TailShape = TnShape<DP_TAIL_SHAPE>;
-constexpr int TAIL = 64, TAIL_SIDE = kGradTailSide, SUBS = TAIL_SIDE * TAIL_SIDE;
-static_assert(TailShape::BM == TAIL && TailShape::BN == TAIL && TAIL_SIDE * TAIL == BM && BM == BN, "sub-tile shape");
+// The last few tiles of a launch are cut finer still, into 64 x 64 sub-tiles of one small workgroup each, which spreads them
+// over the whole chip.
+constexpr int TAIL = SmallTile::BM, TAIL_SIDE = kGradTailSide, SUBS = TAIL_SIDE * TAIL_SIDE;
+static_assert(TAIL_SIDE * TAIL == BM && BM == BN, "sub-tile shape");
 
 template <bool F16, bool NOISE, bool OUT16>
-__global__ void __launch_bounds__(TailShape::NT)
+__global__ void __launch_bounds__(SmallTile::NT, 2)
 clipped_grad_tail_kernel(const GroupArgs ga, const float* __restrict__ C_all, int first_tile,
                          const NoiseArgs na) {
-  extern __shared__ __attribute__((aligned(16))) uint16_t lds_tail[];
+  extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
+  const unsigned lds0 = (unsigned)(uintptr_t)lds_raw;
   const SubTile sub = grad_sub_tile<TAIL_SIDE>(blockIdx.x, gridDim.x);
   const int l = layer_of(ga, first_tile + sub.tile);
+  const GroupLayer& ly = ga.layer[l];
+  const float* C = C_all + ly.c_off;
+  const float w = first_weights(C, ga.B);
   int m0, n0;
   locate_tile(ga, l, first_tile + sub.tile, m0, n0);
-  const GroupLayer& ly = ga.layer[l];
   m0 += sub.row * TAIL;
   n0 += sub.col * TAIL;
   if (m0 >= ly.d_in || n0 >= ly.d_out) return;       // sub-tile past the layer's edge (whole workgroup)
-  const __attribute__((address_space(4))) float* C =
-      (const __attribute__((address_space(4))) float*)(uintptr_t)(C_all + ly.c_off);
-  clipped_grad_tile_deep<TailShape, DP_TAIL_DEPTH, F16, NOISE, OUT16>(ly, ga.B, ga.accumulate, na, l, m0,
-                                                               n0, C, lds_tail);
+  f32x4 acc[2][2];
+  const float held = tn_weighted_small<F16>(ly, ga.B, C, w, m0, n0, lds0, acc);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  TileNoise tn = {};
+  if (NOISE) tn = load_tile_noise(na, l);
+  __syncthreads();                                   // the last fragments are read
+  using Piece = WavePiece16<1, 32, 2>;
+  store_pieces<1, F16, NOISE, OUT16>([&](int) { return Piece{&acc[0][0], m0 + 32 * (wave >> 1), n0 + 32 * (wave & 1)}; },
+                                     ga.accumulate, held, lds0 + wave * Piece::BYTES, ly.out, ly.d_in, ly.d_out, tn,
+                                     threadIdx.x & 63, []() {});
 }
 
 }  // namespace
@@ -338,9 +188,8 @@ int64_t clipped_grad_mid_tiles(int d, int p) {
 // The tiles of the last round go to sub-tiles where they fit one round of 128 x 128.  K = 4096, alone: 64 tiles 94 us
 // as they are, 51 as sub-tiles; 128 tiles 96 and 74; 160 tiles 98 and 114.  All tiles do where that takes fewer
 // rounds' time, because of the layers' edges (which sub-tiles leave out).
-// Up to kTailMax tiles are cut into 64 x 64: 16 tiles of K = 4096 take 34 us so, 44 us in 128 x 128; 32
-// tiles 43 and 46; 64 tiles 117 and 51 (sub-tiles fetch four times the operand bytes per flop of a
-// large tile, so their kernel runs at the rate the L2 delivers them).
+// Up to kTailMax tiles are cut into 64 x 64: 16 tiles of K = 4096 take 25 us so, 44 us in 128 x 128; 32 tiles 32 and 46; 48
+// tiles 52 and 42; 64 tiles 61 and 42.
 // Short contractions (rows: of all samples, each rounded up to 32, as these lines were measured) are bound by the
 // epilogue, which a large tile has a compute unit to itself for: 128 x 128, two to a unit, unless large ones come in whole
 // rounds.  One sample: two layers 3744 x 2352 33.2 us mixed, 24.7 on 128 x 128 (before: 29); 17 of 33 tokens 76 and 69;
@@ -413,7 +262,7 @@ dp_status launch_clipped_grad_big_group_t(const GroupArgs& ga, const float* C, c
   static ReadyTable ready_big[2], ready_mid[2], ready_tail;
   dp_status st = allow_big_lds(big, BigTile::LDS_BYTES, ready_big[blocks]);
   if (st == DP_OK) st = allow_big_lds(mid, MidTile::LDS_BYTES, ready_mid[blocks]);
-  if (st == DP_OK) st = allow_big_lds(tail, (int)TailShape::LDS_BYTES, ready_tail);
+  if (st == DP_OK) st = allow_big_lds(tail, SmallTile::LDS_BYTES, ready_tail);
   if (st != DP_OK) return st;
   const GradTail cut = clipped_grad_tail(n, n_mid, rows, whole_lines, OUT16);
   const int n_tail = cut.tiles;
@@ -428,7 +277,7 @@ dp_status launch_clipped_grad_big_group_t(const GroupArgs& ga, const float* C, c
   }
   if (n_tail == 0) return DP_OK;
   if (cut.side == TAIL_SIDE)
-    hipLaunchKernelGGL(tail, dim3(n_tail * SUBS), dim3(TailShape::NT), TailShape::LDS_BYTES, s, ga, C, n - n_tail, na);
+    hipLaunchKernelGGL(tail, dim3(n_tail * SUBS), dim3(SmallTile::NT), SmallTile::LDS_BYTES, s, ga, C, n - n_tail, na);
   else if (cut.brief)
     hipLaunchKernelGGL(brief, dim3(n_tail * MID_SUBS), dim3(ShortTile::NT), ShortTile::LDS_BYTES, s, ga, C, n - n_tail, na);
   else

@@ -343,4 +343,201 @@ __device__ __forceinline__ void weighted_tiles(const GroupArgs& ga, const float*
   }
 }
 
+// The same contraction on a 64 x 64 tile, four waves of 32 x 32, for the few tiles at the end of a launch: a wave has four
+// matrix instructions (64 clocks) a k-block, so what counts is what lies between them: two k-blocks to a barrier, four sets of
+// fragments, the next two blocks' read during these two's matrix instructions, the samples' bookkeeping in scalars beside
+// them; a ring of ten 8 KiB stages with eight blocks on their way (sixteen stages: no faster).  A block takes some 370 clocks, 49
+// instructions of each wave.  Gradients, us, through registers with 64-row blocks and a barrier each, with one block to a barrier here,
+// and now: 16 x 256 tokens, one layer 1024 x 1024 29.6, 26.6, 25.1; two 39.1, 33.0, 32.4; 32 x 197, three 768 x 768 68.8, 52.0,
+// 50.1; 32 x 64, two 1024 x 1024 30.3, 23.9, 22.7; 64 x 32, one 49.6, 24.3, 23.0; 4 x 256, two 512 x 512 10.9, 10.4, 10.0.
+struct SmallTile {
+  static constexpr int BM = 64, BK = 32, NSTAGE = 10, NT = 256;
+  static constexpr int ROW_BYTES = 2 * BM, TILE_BYTES = BK * ROW_BYTES, STAGE_BYTES = 2 * TILE_BYTES;
+  static constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES;            // 80 KiB: two workgroups per compute unit
+};
+
+// The four accumulators times f (the bits of a float) where turn is not zero; waits as at scale_tuple: the k-block's barrier,
+// loads and scalars lie between its last matrix instruction and the multiplies.
+__device__ __forceinline__ void scale_if(unsigned turn, unsigned f, f32x4 (&c)[2][2]) {
+  asm volatile(
+      "s_cmp_eq_u32 %[turn], 0\n\ts_cbranch_scc1 .Lkeep%=\n\t"
+      ".irp tuple, %0, %1, %2, %3\n\t"
+      ".set dp_first, 0\n\t"
+      ".set dp_more, 1\n\t"
+      ".irpc ch, \"\\tuple\"\n\t"
+      ".if '\\ch' == ':'\n\t.set dp_more, 0\n\t.endif\n\t"
+      ".if dp_more && '\\ch' >= '0' && '\\ch' <= '9'\n\t"
+      ".set dp_first, 10 * dp_first + ('\\ch' - '0')\n\t.endif\n\t"
+      ".endr\n\t"
+      ".irp i, 0, 1, 2, 3\n\t"
+      "v_mul_f32 v[dp_first+\\i], %[f], v[dp_first+\\i]\n\t"
+      ".endr\n\t"
+      ".endr\n\ts_nop 1\n.Lkeep%=:"
+      : "+v"(c[0][0]), "+v"(c[0][1]), "+v"(c[1][0]), "+v"(c[1][1])
+      : [turn] "s"(turn), [f] "s"(f)
+      : "scc");
+}
+
+// w: the weights of the first 64 samples, one a lane.  Returns the weight that the sums are expressed in (0: no sample counts).
+template <bool F16>
+__device__ __forceinline__ float tn_weighted_small(const GroupLayer& ly, int B, const float* C, float w, int m0, int n0,
+                                                   unsigned lds0, f32x4 (&acc)[2][2]) {
+  using S = SmallTile;
+  const int d = ly.d_in, p = ly.d_out, blocks = (ly.T + S::BK - 1) / S::BK;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  // global -> LDS: a wave's load is rows 8 wave .. 8 wave + 7 of the k-block; chunks as for weighted_tiles, in rows of 128 bytes
+  const int lrow = 8 * wave + (lane >> 3);
+  const int chunk = (lane & 7) ^ ((lrow & 2) << 1 | (lrow >> 3 & 1) << 1);
+  const unsigned a_org = m0 + chunk * 8 < d ? (unsigned)(lrow * d + m0 + chunk * 8) * 2u : OOB;
+  const unsigned b_org = n0 + chunk * 8 < p ? (unsigned)(lrow * p + n0 + chunk * 8) * 2u : OOB;
+  const unsigned a_slab = (unsigned)ly.T * d * 2u, b_slab = (unsigned)ly.T * p * 2u;
+  const unsigned a_step = 2u * S::BK * d, b_step = 2u * S::BK * p;
+  const unsigned lds_ld = lds0 + wave * 1024;
+  uint64_t p_mask = 1;
+  i32x4 ra, rb;
+  unsigned va, vb;
+  int p_left, p_stage;
+  auto prefetch_a = [&]() { load_to_lds(ra, va, 0, lds_ld + p_stage * S::STAGE_BYTES); };
+  auto prefetch_b = [&]() { load_to_lds(rb, vb, 0, lds_ld + p_stage * S::STAGE_BYTES + S::TILE_BYTES); };
+  auto next_slab = [](i32x4& r, uint64_t bytes) {
+    const uint64_t q = ((uint64_t)(uint32_t)r[1] << 32 | (uint32_t)r[0]) + bytes;
+    r[0] = (int)(uint32_t)q;
+    r[1] = (int)(uint32_t)(q >> 32);
+  };
+  auto prefetch_advance = [&]() {
+    p_stage = p_stage + 1 == S::NSTAGE ? 0 : p_stage + 1;
+    va += a_step;
+    vb += b_step;
+    if (--p_left == 0) {
+      p_left = blocks;
+      va = a_org;
+      vb = b_org;
+      p_mask >>= 1;
+      if (p_mask == 0) {                                 // zeros from here on, the same number of loads
+        ra[2] = rb[2] = 0;
+        p_left = INT32_MAX;
+      } else {
+        const int n = __builtin_ctzll(p_mask);           // samples that do not count
+        p_mask >>= n;
+        next_slab(ra, (uint64_t)(n + 1) * a_slab);
+        next_slab(rb, (uint64_t)(n + 1) * b_slab);
+      }
+    }
+  };
+  // LDS -> operands
+  const int s = lane & 15;
+  const int rrow = 8 * (lane >> 4) + (s >> 2);
+  const int sw = (rrow & 2) << 1 | (rrow >> 3 & 1) << 1;
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+  const unsigned a_rd = lds0 + rrow * S::ROW_BYTES + ((((wm + 4 * (s & 3)) >> 3) ^ sw) << 4) + (s & 1) * 8;
+  const unsigned b_rd = lds0 + S::TILE_BYTES + rrow * S::ROW_BYTES + ((((wn + 4 * (s & 3)) >> 3) ^ sw) << 4) + (s & 1) * 8;
+  Frag fa[4][2], fb[4][2];                               // sets of two k-blocks in use and of the next two
+  auto read_frag = [&](Frag& f, unsigned rd, int i, int stage) {
+    unsigned base = stage * S::STAGE_BYTES;
+    asm("" : "+s"(base));
+    const unsigned addr = (rd ^ (unsigned)(i << 5)) + base;
+    f.h[0] = lds_read_tr(addr);
+    f.h[1] = lds_read_tr(addr + 4 * S::ROW_BYTES);
+  };
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y) acc[x][y] = f32x4{0.f, 0.f, 0.f, 0.f};
+  constexpr unsigned kOne = 0x3f800000u;
+  int c_stage;
+  unsigned f, turn;
+  // Two k-blocks: wait for the next two, barrier.
+  auto pair = [&](auto parity, auto next) {
+    constexpr int P = decltype(parity)::value;
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S::NSTAGE - 6) * 2) : "memory");
+    __builtin_amdgcn_s_barrier();
+    DP_PIN();
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      scale_if(turn, f, acc);
+      DP_PIN();
+      const int use = 2 * P + k, fill = 2 * (P ^ 1) + k;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int x = q & 1, y = q >> 1;
+        acc[x][y] = mfma16<F16>(fb[use][y].v, fa[use][x].v, acc[x][y]);
+        DP_PIN();
+        if (q < 2)
+          read_frag(fa[fill][q], a_rd, q, c_stage);
+        else
+          read_frag(fb[fill][q - 2], b_rd, q - 2, c_stage);
+        if (q == 1) prefetch_a();
+        if (q == 2) prefetch_b();
+        if (q == 3) next();
+        DP_PIN();
+      }
+      c_stage = c_stage + 1 == S::NSTAGE ? 0 : c_stage + 1;
+    }
+  };
+  float held = 0.f;
+#pragma unroll 1
+  for (unsigned window = 0; window < (unsigned)B; window += 64) {
+    if (window > 0) w = window_weights(C, window, B);
+    const uint64_t mask = __ballot(w != 0.f && window + lane < (unsigned)B);
+    if (mask == 0) continue;
+    if (held != 0.f) __syncthreads();                    // the last window's fragments are read
+    const int first = __builtin_ctzll(mask);
+    p_mask = mask >> first;
+    p_left = blocks;
+    p_stage = c_stage = 0;
+    va = a_org;
+    vb = b_org;
+    ra = make_rsrc(static_cast<const unsigned char*>(ly.a) + (size_t)(window + first) * a_slab, a_slab);
+    rb = make_rsrc(static_cast<const unsigned char*>(ly.g) + (size_t)(window + first) * b_slab, b_slab);
+#pragma unroll 1
+    for (int q = 0; q < S::NSTAGE - 2; ++q) {
+      prefetch_a();
+      prefetch_b();
+      prefetch_advance();
+    }
+    float ratio = 1.f;
+    if (B > 1) {
+      const uint64_t before = mask & ((1ull << lane) - 1);
+      const float prev = __shfl(w, before ? 63 - __builtin_clzll(before) : lane);
+      ratio = before ? prev / w : held != 0.f ? held / w : 1.f;
+    }
+    held = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), 63 - __builtin_clzll(mask)));
+    f = __builtin_amdgcn_readlane(__float_as_uint(ratio), first);
+    turn = f ^ kOne;
+    uint64_t rest = mask;                                // samples from the one at hand on
+    int left = blocks;
+    auto next = [&]() {
+      prefetch_advance();
+      turn = 0;
+      if (--left == 0) {
+        left = blocks;
+        rest &= rest - 1;
+        f = rest ? __builtin_amdgcn_readlane(__float_as_uint(ratio), __builtin_ctzll(rest)) : kOne;
+        turn = f ^ kOne;
+      }
+    };
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S::NSTAGE - 4) * 2) : "memory");
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        read_frag(fa[k][q], a_rd, q, k);
+        read_frag(fb[k][q], b_rd, q, k);
+      }
+    c_stage = 2;                                         // of the reads
+    constexpr std::integral_constant<int, 0> even{};
+    constexpr std::integral_constant<int, 1> odd{};
+    // An odd number of blocks: one more of zeros, past the stream's end.
+#pragma unroll 1
+    for (int n = __builtin_popcountll(mask) * blocks; n > 0; n -= 4) {
+      pair(even, next);
+      if (n > 2) pair(odd, next);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // zero-fill loads past the end
+  }
+  return held;
+}
+
 }  // namespace dpbk

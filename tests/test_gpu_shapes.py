@@ -346,6 +346,17 @@ def test_whole_k_blocks(dtype, B, T):
     assert torch.equal(fused, flat)
 
 
+# The same on 64 x 64 tiles alone: odd and even numbers of k-blocks, fewer than the ring's eight on their way, more samples than a
+# window, windows and samples that do not count, columns past the last tile's edge.
+@pytest.mark.parametrize("side", [512, 392])
+@pytest.mark.parametrize("B,T,zero", [
+    (1, 40, ()), (1, 96, ()), (3, 64, (1,)), (3, 64, (0,)), (5, 33, (4,)), (2, 300, ()), (7, 288, (0, 3)), (65, 40, (0, 63)), (130, 36, tuple(range(64, 128))),
+    (4, 48, (0, 1, 2, 3)),
+])
+def test_weighted_stream_of_small_tiles(side, B, T, zero):
+    test_weighted_stream(side, 2, B, T, zero)
+
+
 # Column sums and their norm in one launch and in two: fewer and more rows than a thread takes at once, row groups that
 # do not come out even, the widest row of the one-launch form and one beyond, both sides of its line.
 @pytest.mark.parametrize("dtype", HALF)
