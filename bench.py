@@ -241,7 +241,7 @@ def measure(name, args, torch, BkPipeline, noise_pass=False):
                        "tflops_executed": norm_exec / (ms_norm * 1e-3) / 1e12},
         # layers on the instantiated path take their gradient from the kept per-sample gradients
         # (kept_weighted_sum_kernel: B + 1 arrays of d p floats move), the others from the
-        # contraction over a and g (clipped_grad_big_kernel)
+        # contraction over a and g (clipped_grad_blocks_kernel)
         "grad_stage": {"tflops": grad_exec / (ms_grad * 1e-3) / 1e12,
                        "frac_bf16_peak": grad_exec / (ms_grad * 1e-3) / PEAK_BF16_FLOPS,
                        "launches_per_step": grad_launches,
@@ -334,7 +334,7 @@ def main():
         with open(os.path.join(ROOT, "profiles", "l2_miss_traffic.json")) as f:
             per = json.load(f)["per_launch"][w.name]
         traffic = sum(per[k]["fetch_bytes"] + per[k]["write_bytes"]
-                      for k in ("clipped_grad_big_kernel", "clipped_grad_mid_kernel", "clipped_grad_tail_kernel")
+                      for k in ("clipped_grad_blocks_kernel", "clipped_grad_mid_blocks_kernel", "clipped_grad_tail_kernel")
                       if k in per)
     except (OSError, KeyError, ValueError):
         pass
@@ -368,10 +368,10 @@ def main():
         # the noise in the gradient kernels' epilogue unless --separate-noise
         "noise_gbps": noise_pass[f"{w.name}_shard"]["gbps"],
         "noise_pass": noise_pass,
-        # The gradient of one group of up to 48 layers is one launch of clipped_grad_big_kernel
+        # The gradient of one group of up to 48 layers is one launch of clipped_grad_blocks_kernel
         # plus, when the last round of tiles is nearly empty, one of clipped_grad_tail_kernel for
         # those tiles; "launch" below means that pair, timed together by the events around the stage.
-        "roofline": {"kernel": "clipped_grad_big_kernel (+ clipped_grad_tail_kernel)" if w.dtype != si.F32
+        "roofline": {"kernel": "clipped_grad_blocks_kernel (+ clipped_grad_tail_kernel)" if w.dtype != si.F32
                      else "clipped_grad_f32_kernel",
                      "bound": "mfma",
                      "achieved": gs["tflops"], "peak": PEAK_BF16_FLOPS / 1e12, "unit": "TFLOP/s",

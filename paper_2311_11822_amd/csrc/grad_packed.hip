@@ -11,9 +11,9 @@
 // of eight layers 1024 x 1024, us, 32x32x16 and these: 512 x 1 token 27.3, 26.3; 256 x 16 177.4, 170.4; fp16 64 x 8 49.8, 47.9; 24 of
 // 768 x 16, 512 x 32 260.0, 258.4).  Gradients measured against 64 bits: 1.4e-7 (T = 1, B = 512) and 2.1e-7 (T = 31) here,
 // 6.0e-7 and 3.9e-7 in the large-tile kernel.
-//   Measured, eight layers of 1024 x 1024 .. 4096 outputs, bf16: B = 512, T = 1: 1384 us before, 87 us here; 4096
-// rows: 570 us here for T = 16, 620 for T = 1 (what bounds it: the matrix cores at the clock they hold
-// under load, then the cutting), fp16 1080 us; the large-tile kernel 684 us at T = 16, 352 at 32.
+//   Measured, eight layers of 1024 x 1024 .. 4096 outputs, bf16: B = 512, T = 1: 1384 us before, 84 us here; 4096
+// rows, T = 1 and 16: 565 us on 32x32x16 instructions, 530 here (what bounds it: the matrix cores at the clock that the power leaves,
+// then the cutting); the large-tile kernel 684 us at T = 16, 352 at 32.
 // packed_below (dp_api.hip) draws its lines there.
 //
 // Tiles (four waves, 32 gradient rows each where the layer is wide): 128 x 128, or 128 x 32, 128 x 64 and
