@@ -78,7 +78,7 @@ using ShortTile = PipeShape<128, 2, 2, 3>;                         // 48 KiB: th
 // with multiplies, branches or second copies of the k-block of its own it moves the accumulators through scratch memory
 // (126 to 540 registers) or through copies.  A tuple prints as v[first:last]; the inner loops read `first` off it.
 // The compiler does not see into it, so the waits are counted here.  A vector instruction may touch the result of one of
-// these matrix instructions (eight passes) after eleven others.  The multiplies go in the order of the matrix
+// these matrix instructions (eight passes) after twelve others.  The multiplies go in the order of the matrix
 // instructions: between the k-step's first one and the first multiply lie its other matrix instructions, its LDS reads and
 // its loads (7 + 12 + 6 instructions of the 256 x 256 tile, 3 + 8 + 6 of the 128 x 128 one), and before the multiplies of
 // the j-th accumulator 16 j others.  The s_nop is the wait of a matrix instruction for the last multiply.

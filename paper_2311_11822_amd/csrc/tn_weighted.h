@@ -34,7 +34,7 @@ namespace dpbk {
 // c *= f (the bits of a float).  Inside the assembly the accumulator stays one operand: with multiplies of its own the
 // compiler moves accumulators through copies.  A tuple prints as v[first:last]; the inner loop reads `first` off it.
 // The compiler does not see into it, so the waits are counted here: a vector instruction may touch the result of one
-// of these matrix instructions (four passes) after seven others, and a matrix instruction that of a multiply after two.
+// of these matrix instructions (four passes) after eight others, and a matrix instruction that of a multiply after two.
 __device__ __forceinline__ void scale_tuple(f32x4& c, unsigned f) {
   asm volatile(
       ".set dp_first, 0\n\t"
@@ -204,8 +204,11 @@ __device__ __forceinline__ void weighted_tiles(const GroupArgs& ga, const float*
         const int x0 = slot % GX, x = GX * half + x0, y = slot / GX;
         acc[x][y] = mfma16<F16>(fb[y].v, fa[x].v, acc[x][y]);
         DP_PIN();
-        if constexpr (SCALED)
-          if (SLOTS * half + slot + 2 < 2 * SLOTS) scale(SLOTS * half + slot + 2);
+        if constexpr (SCALED) {
+          const int q = SLOTS * half + slot + 2;         // the last one beside the one before it: no multiplies come between later
+          if (q < 2 * SLOTS - 1) scale(q);
+          if (q == 2 * SLOTS - 2) scale(q + 1);
+        }
         if (half == 0) {
           constexpr int EVERY = GX == 4 ? 3 : 1;
           if (slot == 0) read_frag(fb[XN - 1], b_rd, XN - 1, c_stage);
