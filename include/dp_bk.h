@@ -392,6 +392,14 @@ dp_status dp_clipped_bias_grad(const float* colsum, int B, int d_out, const floa
  */
 int64_t dp_clipped_grad_tile_order(int d_in, int d_out, int32_t* tile_row0, int32_t* tile_col0,
                                    int64_t capacity);
+/*
+ * How the gradient (section 3) of up to 48 16-bit layers that take these tiles is launched, so that a test can pin the kernels that
+ * it means to run; a pure host function, which reads only T, d_in and d_out of the layers.  launches[0 .. 5]: 256 x 256 tiles;
+ * their workgroups (fewer: each goes from tile to tile); 1 where samples take whole 32-row k-blocks, else 0; tiles that are cut
+ * after them; into side x side sub-tiles of 256 / side; 1 where those are the three-stage ones of short contractions.
+ * DP_ERR_UNSUPPORTED: a layer takes another kernel, or there are more of them than one launch takes.
+ */
+dp_status dp_clipped_grad_launches(const dp_layer* layers, int n_layers, dp_dtype dt, int B, int out16, int32_t* launches);
 int64_t dp_ghost_tile_order(int T, int B, int32_t* sample, int32_t* token_row0, int32_t* token_col0,
                             int32_t* slot, int64_t capacity);
 

@@ -69,6 +69,7 @@ _PROTOS = {
     "dp_layerwise_clipped_grad": (_i, [C.POINTER(dp_layer), _i, _i, _i, C.POINTER(_f), _i, _f, C.POINTER(_vp),
                                       C.POINTER(_u64), _i, _u64, _u64, _f, _u64, _u64, _vp, _vp, _vp, _sz, _i, _vp]),
     "dp_clipped_grad_tile_order": (C.c_int64, [_i, _i, _vp, _vp, C.c_int64]),
+    "dp_clipped_grad_launches": (_i, [_vp, _i, _i, _i, _i, _vp]),
     "dp_ghost_tile_order": (C.c_int64, [_i, _i, _vp, _vp, _vp, _vp, C.c_int64]),
 }
 EXPORTS = tuple(_PROTOS)
@@ -313,6 +314,14 @@ def dp_clipped_grad_tile_order(d_in: int, d_out: int):
     r, c = np.zeros(n, dtype=np.int32), np.zeros(n, dtype=np.int32)
     lib.dp_clipped_grad_tile_order(d_in, d_out, r.ctypes.data, c.ctypes.data, n)
     return r, c
+
+
+def dp_clipped_grad_launches(layers, dt, B, out16=False):
+    """Dict of how the gradient of these layers is launched on the tile kernels (host function)."""
+    arr = layers if isinstance(layers, C.Array) else layer_array(layers)
+    out = (C.c_int32 * 6)()
+    _check(lib.dp_clipped_grad_launches(arr, len(arr), dt, B, int(out16), out), "dp_clipped_grad_launches")
+    return dict(zip(("tiles", "workgroups", "whole_blocks", "cut", "side", "brief"), out))
 
 
 def dp_ghost_tile_order(T: int, B: int):

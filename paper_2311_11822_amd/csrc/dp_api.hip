@@ -1326,6 +1326,35 @@ extern "C" dp_status dp_norms_multi_static(const dp_layer* layers, int L, dp_dty
 // ---------------------------------------------------------------------------------
 extern "C" {
 
+dp_status dp_clipped_grad_launches(const dp_layer* layers, int n_layers, dp_dtype dt, int B, int out16, int32_t* launches) {
+  if (!layers || !launches || n_layers <= 0 || (dt != DP_BF16 && dt != DP_F16)) return DP_ERR_INVALID_ARG;
+  if (n_layers > kMaxGroup) return DP_ERR_UNSUPPORTED;
+  GroupArgs ga = {};
+  int64_t tiles = 0;
+  for (int l = 0; l < n_layers; ++l) {
+    const dp_layer& ly = layers[l];
+    if (!dims_ok(dt, B, ly.T, ly.d_in, ly.d_out)) return DP_ERR_INVALID_ARG;
+    if (grad_kernel_of(ly, dt, B) != kGradBig) return DP_ERR_UNSUPPORTED;
+    GroupLayer& gl = ga.layer[l];
+    gl.T = ly.T;
+    gl.d_in = ly.d_in;
+    gl.d_out = ly.d_out;
+    tiles += clipped_grad_big_tiles(ly.d_in, ly.d_out);
+    if (tiles > INT32_MAX / 2) return DP_ERR_UNSUPPORTED;
+  }
+  ga.n_layers = n_layers;
+  ga.B = B;
+  ga.total_blocks = (int)tiles;
+  const GradLaunches plan = clipped_grad_launches(ga, out16 != 0);
+  launches[0] = ga.total_blocks - plan.cut.tiles;
+  launches[1] = plan.workgroups;
+  launches[2] = plan.blocks;
+  launches[3] = plan.cut.tiles;
+  launches[4] = plan.cut.side;
+  launches[5] = plan.cut.brief;
+  return DP_OK;
+}
+
 int64_t dp_clipped_grad_tile_order(int d_in, int d_out, int32_t* tile_row0, int32_t* tile_col0,
                                    int64_t capacity) {
   if (d_in <= 0 || d_out <= 0 || capacity < 0) return -1;

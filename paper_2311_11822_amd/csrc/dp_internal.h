@@ -227,6 +227,14 @@ struct GradTail {
   bool brief;
 };
 GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows, bool whole_lines, bool out16);
+// The launches of a group on these tiles.  blocks: in whole k-blocks (tn_weighted.h); workgroups: of the tiles that are not cut,
+// each one or more of them.
+struct GradLaunches {
+  GradTail cut;
+  bool blocks;
+  int workgroups;
+};
+GradLaunches clipped_grad_launches(const GroupArgs& ga, bool out16);
 bool clipped_grad_big_supports(int T, int d, int p);
 // noise == nullptr: gradients only.  out16: the layers' `out` pointers address 16-bit arrays of the
 // operands' storage type (bf16 or fp16) instead of fp32.

@@ -239,9 +239,7 @@ bool whole_blocks(int B, int T) {
   return (int64_t)B * T > 128 && steps >= (steps % 2 == 0 ? 4 : 15);
 }
 
-template <bool F16, bool NOISE, bool OUT16>
-dp_status launch_clipped_grad_big_group_t(const GroupArgs& ga, const float* C, const NoiseArgs& na,
-                                          hipStream_t s) {
+GradLaunches clipped_grad_launches(const GroupArgs& ga, bool out16) {
   const int n = ga.total_blocks;
   int64_t n_mid = 0, rows = 0;
   bool whole_lines = true, one_length = true, blocks = true;
@@ -254,12 +252,23 @@ dp_status launch_clipped_grad_big_group_t(const GroupArgs& ga, const float* C, c
     const int64_t r = (int64_t)ga.B * ((ly.T + BigTile::BK - 1) / BigTile::BK) * BigTile::BK;
     rows = r > rows ? r : rows;
   }
-  const GradTail cut = clipped_grad_tail(n, n_mid, rows, whole_lines, OUT16);
-  const int n_tail = cut.tiles;
+  const GradTail cut = clipped_grad_tail(n, n_mid, rows, whole_lines, out16);
+  const int n_big = n - cut.tiles;
   // Large tiles on part of the chip alone are not held by its power, and 16-row steps take fewer clocks: 144 tiles, 4 x 1024 tokens 88.7
   // us so, 93.1 in whole k-blocks, 16 x 320 111.7, 116.1; 180 tiles, 16 x 256 104.1, 102.1; 245 tiles 118.2 either way.
   constexpr int kPartOfTheChip = 160;
-  if (n_tail == 0 && n <= kPartOfTheChip) blocks = false;
+  if (cut.tiles == 0 && n <= kPartOfTheChip) blocks = false;
+  // Workgroups that go from tile to tile take equal numbers of them: for tiles of one length.
+  return {cut, blocks, blocks && one_length && ga.B <= 64 ? std::min(n_big, kBigRound) : n_big};
+}
+
+template <bool F16, bool NOISE, bool OUT16>
+dp_status launch_clipped_grad_big_group_t(const GroupArgs& ga, const float* C, const NoiseArgs& na,
+                                          hipStream_t s) {
+  const GradLaunches plan = clipped_grad_launches(ga, OUT16);
+  const GradTail cut = plan.cut;
+  const bool blocks = plan.blocks;
+  const int n = ga.total_blocks, n_tail = cut.tiles;
   auto big = blocks ? clipped_grad_blocks_kernel<F16, NOISE, OUT16> : clipped_grad_big_kernel<F16, NOISE, OUT16>;
   auto mid = blocks ? clipped_grad_mid_blocks_kernel<MidTile, F16, NOISE, OUT16> : clipped_grad_mid_kernel<MidTile, F16, NOISE, OUT16>;
   auto brief =
@@ -273,9 +282,7 @@ dp_status launch_clipped_grad_big_group_t(const GroupArgs& ga, const float* C, c
   if (n > n_tail) {
     GroupArgs main_args = ga;
     main_args.total_blocks = n - n_tail;
-    // Workgroups that go from tile to tile take equal numbers of them: for tiles of one length.
-    const int grid = blocks && one_length && ga.B <= 64 ? std::min(n - n_tail, kBigRound) : n - n_tail;
-    hipLaunchKernelGGL(big, dim3(grid), dim3(BigTile::NT), BigTile::LDS_BYTES, s, main_args, C, na);
+    hipLaunchKernelGGL(big, dim3(plan.workgroups), dim3(BigTile::NT), BigTile::LDS_BYTES, s, main_args, C, na);
     st = hip_status(hipGetLastError());
     if (st != DP_OK) return st;
   }

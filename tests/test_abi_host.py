@@ -237,6 +237,26 @@ def test_gradient_tile_order_of_cut_tiles(dp, d, p, n_tail, side):
     assert got == [len(r) - n_tail + t for t in sub_tile_order(n_tail, side)]
 
 
+# The kernels that a gradient of n square layers takes: joined tiles, one workgroup a tile, tiles that are cut.
+@pytest.mark.parametrize("n,side,B,T,want", [
+    (8, 2040, 3, 64, (512, 256, 1, 0)), (11, 2040, 64, 64, (704, 256, 1, 0)), (8, 2040, 65, 64, (512, 512, 1, 0)),
+    (9, 1016, 4, 160, (144, 144, 0, 0)), (12, 1016, 4, 160, (192, 192, 1, 0)), (8, 2040, 16, 48, (512, 512, 0, 0)),
+    (2, 512, 3, 64, (0, 0, 1, 8)), (1, 1536, 5, 64, (0, 0, 1, 36))])
+def test_launches_of_a_gradient(dp, n, side, B, T, want):
+    plan = dp.dp_clipped_grad_launches([(16, 16, T, side, side, 0)] * n, dp.DP_BF16, B)
+    assert (plan["tiles"], plan["workgroups"], plan["whole_blocks"], plan["cut"]) == want
+    assert plan["tiles"] + plan["cut"] == n * (-(-side // 256)) ** 2
+    assert not plan["cut"] or plan["side"] == (4 if plan["cut"] <= 32 else 2)
+
+
+def test_launches_of_a_gradient_refused(dp):
+    query = lambda n, T, side, dt: dp.dp_clipped_grad_launches([(16, 16, T, side, side, 0)] * n, dt, 4)
+    for n, T, side, dt in [(49, 64, 256, dp.DP_BF16), (1, 8, 256, dp.DP_BF16), (1, 64, 256, dp.DP_F32), (1, 64, 250, dp.DP_BF16),
+                           (1, 0, 256, dp.DP_F16)]:
+        with pytest.raises(dp.DpError):
+            query(n, T, side, dt)
+
+
 def grad_tiles_in_number_order(tiles_m, tiles_n):
     """Tile numbers of a layer: super-patches of 16 x 16 row by row, in them patches of 4 x 8, in them columns."""
     for sr in range(0, tiles_m, 16):

@@ -304,9 +304,9 @@ def test_weighted_stream(side, n, B, T, zero):
         assert torch.linalg.norm(got.double() - want) <= TOL * torch.linalg.norm(want)
 
 
-# Samples in whole 32-row k-blocks, tile after tile in one workgroup (two rounds of 256 tiles and some that are cut): too few
-# blocks to join two tiles and just enough, an odd number of 16-row steps, more than 64 samples, a group without a sample
-# that counts between others, one sample alone, runs of equal weights; the same bits on the tiles of a layer by itself.
+# Samples in whole 32-row k-blocks, a workgroup to a tile: 128 x 128 tiles of three stages (the first four cases) and of
+# five, 256 x 256 with more than 64 samples; an odd number of 16-row steps, a group without a sample that counts between
+# others, one sample alone, runs of equal weights; the same bits on the tiles of a layer by itself.
 @pytest.mark.parametrize("dtype", [si.BF16, si.F16])
 @pytest.mark.parametrize("B,T", [(2, 65 + 31), (3, 64), (5, 64), (1, 160), (4, 225), (65, 64), (130, 49)])
 def test_whole_k_blocks(dtype, B, T):
@@ -344,6 +344,100 @@ def test_whole_k_blocks(dtype, B, T):
     dp.dp_clipped_grad_multi(desc, dt, B, C[0].contiguous(), pieces)
     dp.dp_add_noise(flat.data_ptr() + 4 * noise[0], *noise)
     assert torch.equal(fused, flat)
+
+
+# Tile after tile in one workgroup, every one of them two 256 x 256 tiles (eight layers) or some three and some two (eleven): a tile of
+# the first round is followed by one of the fourth layer after it.  Too few k-blocks to join two tiles (fewer than the ring's
+# five) and just enough, on either side; nothing that counts before, behind or between; samples of one weight, samples that
+# begin in the joined tile's first blocks, an odd number of 16-row steps.  Samples that do not count hold NaN.
+@pytest.mark.parametrize("dtype", [si.BF16, si.F16])
+@pytest.mark.parametrize("n,B,T", [(8, 2, 96), (8, 3, 64), (8, 5, 64), (8, 1, 160), (8, 4, 225), (11, 5, 128), (11, 64, 64)])
+def test_joined_tiles(dtype, n, B, T):
+    from paper_2311_11822_amd import binding as dp
+    side = 2040
+    dt, tdt = (dp.DP_BF16, torch.bfloat16) if dtype == si.BF16 else (dp.DP_F16, torch.float16)
+    gen = torch.Generator(device="cuda").manual_seed(B * T + n)
+    layers = [tuple((torch.randn((B, T, side), generator=gen, device="cuda") * s).to(tdt) for s in (1.0, 0.01)) for _ in range(n)]
+    desc = dp.layer_array([(a, g, T, side, side, dp.DP_PATH_GHOST) for a, g in layers])
+
+    def joined(out16):
+        plan = dp.dp_clipped_grad_launches(desc, dt, B, out16)
+        return plan["tiles"] == 64 * n and plan["workgroups"] == 256 and plan["whole_blocks"] == 1 and plan["cut"] == 0
+
+    assert joined(False)
+    blocks = -(-T // 32)
+    some = lambda k: (torch.arange(B, device="cuda") < min(k, B)).float()           # the first k samples
+    C = torch.rand((n, B), generator=gen, device="cuda") + 0.1
+    C[1] = 0.0                                            # nothing, then something
+    C[2] *= some(4 // blocks)                             # up to four blocks, then all
+    C[3] *= some(-(-5 // blocks))                         # five blocks, or the next number there is, then as few
+    C[7] = C[7].flip(0) * some(-(-5 // blocks)).flip(0)
+    C[5] *= some(4 // blocks)
+    C[6] = 0.0                                            # few blocks, then nothing
+    C[4, B // 2:B // 2 + 2] = 0.5
+    if n > 8:
+        C[8] = 0.25                                       # one weight
+        C[9, ::2] = 0.0
+    for (a, _), c in zip(layers, C):
+        a[c == 0] = float("nan")
+    groups = list(range(n))
+    grads = [torch.full((side, side), float("nan"), device="cuda") for _ in layers]
+    dp.dp_clipped_grad_grouped(desc, dt, B, C, groups, n, grads)
+    for l, (a, g) in enumerate(layers):
+        alone = torch.empty((side, side), device="cuda")
+        dp.dp_clipped_grad(a, g, dt, B, T, side, side, C[l].contiguous(), alone, 0)
+        assert torch.equal(grads[l], alone)
+        keep = C[l] != 0
+        w = (a[keep].double() * C[l][keep].double()[:, None, None]).reshape(-1, side)
+        want = w.t().contiguous() @ g[keep].double().reshape(-1, side)
+        # exact products, sums of up to 4096 terms and B re-expressions in fp32
+        assert float((grads[l].double() - want).norm()) <= 3e-6 * float(want.norm())
+    clean = torch.cat([x.reshape(-1) for x in grads])
+    dp.dp_clipped_grad_grouped(desc, dt, B, C, groups, n, grads, 1)                  # old values while the stream runs on
+    assert torch.equal(torch.cat([x.reshape(-1) for x in grads]), 2 * clean)
+    # one group of weights; noise on an uneven shard, stored in 32 and in 16 bits
+    for a, _ in layers:
+        a.nan_to_num_(0.5)
+    one = C[9 if n > 8 else 0].contiguous()
+    flat = torch.empty(n * side * side, device="cuda")
+    pieces, offs = list(flat.view(n, side, side)), [l * side * side for l in range(n)]
+    noise = (1001, n * side * side - 2002, 0.5, 1.0, 3, 4)
+    dp.dp_clipped_grad_noise_multi(desc, dt, B, one, pieces, offs, 0, *noise)
+    fused = flat.clone()
+    dp.dp_clipped_grad_multi(desc, dt, B, one, pieces)
+    dp.dp_add_noise(flat.data_ptr() + 4 * noise[0], *noise)
+    assert torch.equal(fused, flat)
+    if T % 32 == 0:                                       # what the 16-bit call takes
+        assert joined(True)
+        flat16 = torch.empty(n * side * side, dtype=tdt, device="cuda")
+        pieces16 = list(flat16.view(n, side, side))
+        dp.dp_clipped_grad_noise_multi_h16(desc, dt, B, one, pieces16, offs, 0, *noise)
+        assert torch.equal(flat16, fused.to(tdt))
+
+
+# Large tiles on part of the chip alone stay on 16-row steps, more of them take whole k-blocks: the same bits.
+@pytest.mark.parametrize("dtype", [si.BF16, si.F16])
+@pytest.mark.parametrize("B,T", [(4, 160), (3, 250), (65, 64)])
+def test_whole_k_blocks_against_steps(dtype, B, T):
+    from paper_2311_11822_amd import binding as dp
+    side = 1016
+    dt, tdt = (dp.DP_BF16, torch.bfloat16) if dtype == si.BF16 else (dp.DP_F16, torch.float16)
+    gen = torch.Generator(device="cuda").manual_seed(B * T)
+    layers = [tuple((torch.randn((B, T, side), generator=gen, device="cuda") * s).to(tdt) for s in (1.0, 0.01)) for _ in range(12)]
+    C = torch.rand(B, generator=gen, device="cuda") + 0.1
+    C[B // 2] = 0.0
+    grads = {}
+    for n, whole in ((9, 0), (12, 1)):
+        desc = dp.layer_array([(a, g, T, side, side, dp.DP_PATH_GHOST) for a, g in layers[:n]])
+        plan = dp.dp_clipped_grad_launches(desc, dt, B)
+        assert (plan["tiles"], plan["whole_blocks"], plan["cut"]) == (16 * n, whole, 0)
+        grads[n] = torch.full((n, side, side), float("nan"), device="cuda")
+        dp.dp_clipped_grad_multi(desc, dt, B, C, list(grads[n]))
+    assert torch.equal(grads[9], grads[12][:9])
+    for (a, g), got in zip(layers, grads[12]):
+        want = (a.double() * C.double()[:, None, None]).reshape(B * T, side).t().contiguous() @ g.double().reshape(B * T, side)
+        # exact products, sums of up to 4160 terms and B re-expressions in fp32
+        assert float((got.double() - want).norm()) <= 3e-6 * float(want.norm())
 
 
 # The same on 64 x 64 tiles alone: odd and even numbers of k-blocks, fewer than the ring's eight on their way, more samples than a
