@@ -472,11 +472,12 @@ def test_bias_norm_forms(dtype, B, T, p):
 
 
 # Column sums in strips of 64 columns: one trip of four rows a thread and one row more, both sides of the lines between the
-# workgroups' sizes and of eight rows' trips, a strip that is not full, the last small enough call and one beyond.
+# workgroups' sizes and of eight rows' trips, a strip that is not full, the last small enough call and one beyond; rows that are not
+# whole 128-byte lines in 256 strips, in 257 and (the other kernel again) in very many.
 @pytest.mark.parametrize("dtype", HALF)
 @pytest.mark.parametrize("B,T,p", [
     (8, 128, 768), (8, 129, 768), (2, 256, 1288), (2, 257, 1288), (3, 513, 520), (1, 4097, 328), (1, 2, 65544),
-    (4, 256, 6144), (4, 257, 6144), (10, 11, 8192), (10, 11, 8200),
+    (4, 256, 6144), (4, 257, 6144), (10, 11, 8192), (10, 11, 8200), (1, 11, 16376), (1, 11, 16392),
 ])
 def test_bias_norm_of_few_strips(dtype, B, T, p):
     test_bias_norm_forms(dtype, B, T, p)
