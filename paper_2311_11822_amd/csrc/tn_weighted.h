@@ -359,8 +359,12 @@ struct SmallTile {
   static constexpr int LDS_BYTES = NSTAGE * STAGE_BYTES;            // 80 KiB: two workgroups per compute unit
 };
 
-// The four accumulators times f (the bits of a float) where turn is not zero; waits as at scale_tuple: the k-block's barrier,
-// loads and scalars lie between its last matrix instruction and the multiplies.
+// The four accumulators times f (the bits of a float) where turn is not zero; waits as at scale_tuple.  The matrix instructions go
+// c00, c10, c01, c11, the multiplies c00, c01, c10, c11, four each, behind a compare and a branch.  Between a k-block's c01 and its
+// multiplies lie c11, four LDS reads, the scalars, compare and branch, and four multiplies; between c11 and its own two LDS
+// reads, the same scalars and branch and twelve multiplies: more than eight, with the pair's barrier between (its first k-block)
+// or without (its second).  Between the last multiply, of c11, and c11's matrix instruction lie the s_nop and three others; before
+// c00's the multiplies of the other three.
 __device__ __forceinline__ void scale_if(unsigned turn, unsigned f, f32x4 (&c)[2][2]) {
   asm volatile(
       "s_cmp_eq_u32 %[turn], 0\n\ts_cbranch_scc1 .Lkeep%=\n\t"
