@@ -1,6 +1,5 @@
 // Register-staged bf16 tile machinery for products that contract over the token axis of two
-// row-major operands (used by the kernels in tn_gemm.hip and by the tail kernel in
-// grad_gemm.hip).  Tiles are staged in LDS as [k][m], exactly as they lie in memory, and
+// row-major operands (used by the kernels in tn_gemm.hip and layerwise.hip).  Tiles are staged in LDS as [k][m], exactly as they lie in memory, and
 // fetched with the gfx950 transposing LDS read (ds_read_b64_tr_b16): within 16 lanes, lanes
 // 4e..4e+3 supply row k0+e (16 consecutive m), and lane L receives column m0+L for k0..k0+3.
 #pragma once
