@@ -593,6 +593,23 @@ dp_status make_noise(const dp_layer* layers, int L, const uint64_t* grad_offset,
   return DP_OK;
 }
 
+// Whether a layer's rows leave the matrix-core gradient kernels by streaming stores, past the caches, in a launch that writes `bytes`.
+// Streaming to cached, ratios of times (averages of groups of 1640 measurements): up to 32 MB, what the L2s hold together, 0.93 to 1.02,
+// also with a pass behind it that reads the gradient.  Beyond it
+//  * without noise a gradient is there to be read again (by the noise, the next micro-batch, a reduction), and the memory-side cache
+//    holds it up to some 200 MB: alone 0.99 to 1.00, with what reads it 1.01 to 1.07; above 0.94 to 1.02;
+//  * rows that are not whole 128-byte lines: the two pieces of a line meet in L2 only if they stay there.  Without noise 1.01 to
+//    1.13 (2 x 32 tokens, 39 layers 1016 x 1016 1.61); with noise short contractions wait for the stores, 1.02 to 1.27 of 256
+//    rows, others do not, 0.85 to 1.08 of 576 rows and more, on average 0.99;
+//  * whole lines with noise 0.94 to 1.02.
+// An accumulating launch has just read what it writes: 1.00 either way, cached.
+bool rows_stream(const GroupLayer& ly, int B, int64_t bytes, bool noise, bool out16) {
+  constexpr int64_t kInL2 = 32 << 20, kInMemorySideCache = 200 << 20, kShortRows = 512;
+  const bool whole_lines = ly.d_out % (out16 ? 64 : 32) == 0 && reinterpret_cast<uintptr_t>(ly.out) % 128 == 0;
+  if (bytes <= kInL2) return true;
+  return noise ? whole_lines || (int64_t)B * ly.T > kShortRows : whole_lines && bytes > kInMemorySideCache;
+}
+
 // The gradient kernels of layers that check_grads has passed.
 dp_status launch_grads(const dp_layer* layers, int L, dp_dtype dt, int B, const float* C, const int* c_off,
                        float* const* grads, int accumulate, hipStream_t s, const NoiseSpec* noise = nullptr,
@@ -679,6 +696,9 @@ dp_status launch_grads(const dp_layer* layers, int L, dp_dtype dt, int B, const 
       }
       if (fused) set_noise(na, *noise);
       const NoiseArgs* in_kernel = fused ? &na : nullptr;
+      int64_t bytes = 0;
+      for (int j = 0; j < ga.n_layers; ++j) bytes += (int64_t)ga.layer[j].d_in * ga.layer[j].d_out * (out16 ? 2 : 4);
+      for (int j = 0; j < ga.n_layers; ++j) ga.layer[j].stream = !accumulate && rows_stream(ga.layer[j], B, bytes, fused, out16);
       dp_status st = kernel == kGradBig      ? launch_clipped_grad_big_group(ga, C, in_kernel, s, out16)
                      : kernel == kGradPacked ? launch_grad_packed_group(ga, C, in_kernel, s)
                                              : launch_clipped_grad_group(ga, C, s);

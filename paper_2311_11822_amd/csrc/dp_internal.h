@@ -57,6 +57,7 @@ struct GroupLayer {
   int part_begin;   // first partial-sum slot of this layer in the workspace
   int tiles_per_sample;
   int c_off;        // gradient kernels: this layer's weights are C[c_off + i] (its clipping group)
+  int stream;       // matrix-core gradient kernels: rows leave by streaming stores (not of an accumulating launch)
 };
 
 struct GroupArgs {

@@ -71,10 +71,10 @@ __device__ __forceinline__ TileNoise load_tile_noise(const NoiseArgs& args, int 
 // 1344 stored in 16 bits 290, 255; 2 x 32, 44 of width 1488 in fp32 355, 312; 18 tokens of 3 samples, 48 of width 320 40, 34;
 // 4096 tokens, 144 of width 1280 7.31, 7.36 ms.
 //
-// Whole rows leave by streaming (nontemporal) stores: a launch writes more than the caches hold and reads none of it, so that
-// cached stores only push the operands out of them.  Gradients with noise, us, cached and streaming: 24 layers 1280 x 1280,
+// Whole rows leave by streaming (nontemporal) stores where the caller says so (rows_stream in dp_api.hip): cached stores of what the
+// launch does not read only push the operands out of the caches.  Gradients with noise, us, cached and streaming: 24 layers 1280 x 1280,
 // 16 x 112 tokens 186, 169; 32 x 48 182, 170; 24 GPT layers of width 1024 (fp16), 10 x 100 241, 221; 48 of width 1280, 8 x 512 1845,
-// 1840; accumulating launches alike.  (Of the registers' 32-byte pieces they took four times as long.)
+// 1840.  (Of the registers' 32-byte pieces they took four times as long.)
 template <int NY>
 struct WavePiece {
   static constexpr int H = 32, W = 32 * NY;            // rows, columns
@@ -147,11 +147,11 @@ __device__ __forceinline__ void wave_lds_fence() {
 }
 
 // acc * held (+ old value) (+ noise of eq. (1)) -> out, in fp32 or the operands' 16-bit type; lds: the wave's Piece::BYTES;
-// ready: called before the first store.
+// stream: by streaming stores (not of accumulating launches); ready: called before the first store.
 // Noise: same values as the separate pass, which indexes the generator by global element too; requires layer_off and d_out
 // to be multiples of 4, as a lane's four columns are one block of the generator.
 template <bool F16, bool NOISE, bool OUT16, bool ACCUMULATE, class Piece, class Ready>
-__device__ __forceinline__ void store_rows(const Piece& piece, float held, unsigned lds, float* out32, int d, int p,
+__device__ __forceinline__ void store_rows(const Piece& piece, bool stream, float held, unsigned lds, float* out32, int d, int p,
                                            const TileNoise& na, int lane, Ready ready) {
   const int row0 = piece.row0, col0 = piece.col0;
   OldRows<Piece, OUT16> old;
@@ -225,32 +225,45 @@ __device__ __forceinline__ void store_rows(const Piece& piece, float held, unsig
       }
     }
     if (n == 0) ready();
+    u32x4v w[U];
 #pragma unroll
-    for (int u = n; u < n + U; ++u)
-      if (row + u * ROWS < d && col < p) {
-        if constexpr (OUT16) {
-          u32x4v w;
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-          for (int k = 0; k < 4; ++k)
-            w[k] = (uint32_t)to_half_bits<F16>(v[u][2 * k]) | ((uint32_t)to_half_bits<F16>(v[u][2 * k + 1]) << 16);
-          __builtin_nontemporal_store(w, reinterpret_cast<u32x4v*>(reinterpret_cast<uint16_t*>(out32) + at + u * step));
-        } else {
-          const f32x4v w = {v[u][0], v[u][1], v[u][2], v[u][3]};
-          __builtin_nontemporal_store(w, reinterpret_cast<f32x4v*>(out32 + at + u * step));
-        }
+      for (int k = 0; k < 4; ++k) {
+        if constexpr (OUT16)
+          w[u][k] = (uint32_t)to_half_bits<F16>(v[n + u][2 * k]) | ((uint32_t)to_half_bits<F16>(v[n + u][2 * k + 1]) << 16);
+        else
+          w[u][k] = __float_as_uint(v[n + u][k]);
       }
+    auto store = [&](auto streaming) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (row + (n + u) * ROWS < d && col < p) {
+          u32x4v* to = reinterpret_cast<u32x4v*>(reinterpret_cast<char*>(out32) + (at + (n + u) * step) * (OUT16 ? 2 : 4));
+          if constexpr (decltype(streaming)::value)
+            __builtin_nontemporal_store(w[u], to);
+          else
+            *to = w[u];
+        }
+    };
+    if (!ACCUMULATE && stream) {
+      store(std::true_type{});
+      asm volatile("");                                  // or the two become one cached store
+    } else {
+      store(std::false_type{});
+    }
     __builtin_amdgcn_sched_barrier(0);
   }
 }
 
 // COUNT pieces of the wave; ready: called before the first store.
 template <int COUNT, bool F16, bool NOISE, bool OUT16, class PieceOf, class Ready>
-__device__ __forceinline__ void store_pieces(PieceOf piece, bool accumulate, float held, unsigned lds, float* out32, int d, int p,
+__device__ __forceinline__ void store_pieces(PieceOf piece, bool accumulate, bool stream, float held, unsigned lds, float* out32, int d, int p,
                                              const TileNoise& na, int lane, Ready ready) {
   auto store_all = [&](auto acc_tag) {
 #pragma unroll
     for (int i = 0; i < COUNT; ++i)
-      store_rows<F16, NOISE, OUT16, decltype(acc_tag)::value>(piece(i), held, lds, out32, d, p, na, lane, [&]() {
+      store_rows<F16, NOISE, OUT16, decltype(acc_tag)::value>(piece(i), stream, held, lds, out32, d, p, na, lane, [&]() {
         if (i == 0) ready();
       });
   };

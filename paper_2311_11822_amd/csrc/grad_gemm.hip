@@ -45,7 +45,7 @@ __device__ __forceinline__ void gradient_tile(const GroupArgs& ga, int l, int m0
   TileNoise tn = {};
   if (NOISE) tn = load_tile_noise(na, l);
   __syncthreads();                                     // the last fragments are read
-  store_pieces<S::TM, F16, NOISE, OUT16>([&](int x) { return Piece{acc[x], m0 + wm + x * 32, n0 + wn}; }, ga.accumulate, held,
+  store_pieces<S::TM, F16, NOISE, OUT16>([&](int x) { return Piece{acc[x], m0 + wm + x * 32, n0 + wn}; }, ga.accumulate, ly.stream, held,
                                          region, ly.out, d, p, tn, lane, []() {});
 }
 
@@ -75,7 +75,7 @@ struct StoreTile {
     TileNoise tn = {};
     if (NOISE) tn = load_tile_noise(na, t.l);
     store_pieces<S::WTM / 16, F16, NOISE, OUT16>(
-        [&](int x) { return Piece{&acc[x][0], t.m0 + wm + x * 16, t.n0 + wn}; }, ga.accumulate, held, region, ly.out,
+        [&](int x) { return Piece{&acc[x][0], t.m0 + wm + x * 16, t.n0 + wn}; }, ga.accumulate, ly.stream, held, region, ly.out,
         ly.d_in, ly.d_out, tn, threadIdx.x & 63, ready);
   }
 };
@@ -166,7 +166,7 @@ clipped_grad_tail_kernel(const GroupArgs ga, const float* __restrict__ C_all, in
   __syncthreads();                                   // the last fragments are read
   using Piece = WavePiece16<1, 32, 2>;
   store_pieces<1, F16, NOISE, OUT16>([&](int) { return Piece{&acc[0][0], m0 + 32 * (wave >> 1), n0 + 32 * (wave & 1)}; },
-                                     ga.accumulate, held, lds0 + wave * Piece::BYTES, ly.out, ly.d_in, ly.d_out, tn,
+                                     ga.accumulate, ly.stream, held, lds0 + wave * Piece::BYTES, ly.out, ly.d_in, ly.d_out, tn,
                                      threadIdx.x & 63, []() {});
 }
 

@@ -343,7 +343,7 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
   using Piece = WavePiece16<NY, 32, S::XN>;
   static_assert(Piece::BYTES * 4 <= NSTAGE * S::STAGE_BYTES && S::XM == 2, "a region for each wave");
   store_pieces<S::XN / (2 * NY), F16, NOISE, false>(
-      [&](int y) { return Piece{&acc[0][2 * NY * y], m0 + wm, n0 + wn + 32 * NY * y}; }, accumulate, 1.f,
+      [&](int y) { return Piece{&acc[0][2 * NY * y], m0 + wm, n0 + wn + 32 * NY * y}; }, accumulate, ly.stream, 1.f,
       lds0 + wave * Piece::BYTES, ly.out, d, p, tn, lane, []() {});
 }
 

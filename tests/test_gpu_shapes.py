@@ -440,6 +440,31 @@ def test_whole_k_blocks_against_steps(dtype, B, T):
         assert float((got.double() - want).norm()) <= 3e-6 * float(want.norm())
 
 
+# Launches on either side of the lines between streaming and cached stores (rows of whole 128-byte lines and others, 32 and 200 MB, with
+# noise and without, 512 rows): the bits of the layers alone, on all tiles, packed rows among them.
+@pytest.mark.parametrize("n,side,B,T", [(7, 1016, 4, 64), (9, 1016, 4, 64), (9, 1016, 9, 64), (9, 1024, 4, 64), (47, 1024, 2, 64),
+                                        (48, 1032, 2, 64), (48, 1088, 2, 64), (9, 1016, 64, 2), (9, 1024, 64, 2), (32, 512, 4, 33)])
+def test_gradients_of_large_and_small_launches(n, side, B, T):
+    from paper_2311_11822_amd import binding as dp
+    gen = torch.Generator(device="cuda").manual_seed(n * side)
+    layers = [tuple((torch.randn((B, T, side), generator=gen, device="cuda") * s).to(torch.bfloat16) for s in (1.0, 0.01))
+              for _ in range(n)]
+    desc = dp.layer_array([(a, g, T, side, side, dp.DP_PATH_GHOST) for a, g in layers])
+    C = torch.rand(B, generator=gen, device="cuda") + 0.1
+    flat, alone = torch.empty((n, side, side), device="cuda"), torch.empty((n, side, side), device="cuda")
+    pieces, offs = list(flat), [l * side * side for l in range(n)]
+    for l, (a, g) in enumerate(layers):
+        dp.dp_clipped_grad(a, g, dp.DP_BF16, B, T, side, side, C, alone[l], 0)
+    dp.dp_clipped_grad_multi(desc, dp.DP_BF16, B, C, pieces)
+    assert torch.equal(flat, alone)
+    dp.dp_clipped_grad_multi(desc, dp.DP_BF16, B, C, pieces, 1)
+    assert torch.equal(flat, 2 * alone)
+    noise = (1001, n * side * side // 8, 0.5, 1.0, 3, 4)
+    dp.dp_clipped_grad_noise_multi(desc, dp.DP_BF16, B, C, pieces, offs, 0, *noise)
+    dp.dp_add_noise(alone.data_ptr() + 4 * noise[0], *noise)
+    assert torch.equal(flat, alone)
+
+
 # The same on 64 x 64 tiles alone: odd and even numbers of k-blocks, fewer than the ring's eight on their way, more samples than a
 # window, windows and samples that do not count, columns past the last tile's edge.
 @pytest.mark.parametrize("side", [512, 392])
