@@ -254,10 +254,13 @@ GradLaunches clipped_grad_launches(const GroupArgs& ga, bool out16) {
   }
   const GradTail cut = clipped_grad_tail(n, n_mid, rows, whole_lines, out16);
   const int n_big = n - cut.tiles;
-  // Large tiles on part of the chip alone are not held by its power, and 16-row steps take fewer clocks: 144 tiles, 4 x 1024 tokens 88.7
-  // us so, 93.1 in whole k-blocks, 16 x 320 111.7, 116.1; 180 tiles, 16 x 256 104.1, 102.1; 245 tiles 118.2 either way.
-  constexpr int kPartOfTheChip = 160;
-  if (cut.tiles == 0 && n <= kPartOfTheChip) blocks = false;
+  // Large tiles on part of the chip alone (from 129 on: fewer are cut) are not held by its power, and 16-row steps take fewer clocks;
+  // nor is a single round of a short contraction.  Whole k-blocks to steps, ratios of times with noise and without: up to 1024 rows 144 and
+  // 160 tiles 1.01 to 1.07 and 1.00 to 1.04, 176 to 252 tiles 0.99 to 1.08 and 0.97 to 1.02; 2048 rows 1.00 to 1.06 and 1.00 to 1.05, 0.96
+  // to 1.05 and 0.96 to 1.00; 4096 rows 0.99 to 1.02 and 0.98 to 1.02, 0.94 to 1.02 and 0.94 to 0.99.  (128 x 128 tiles on part of the
+  // chip, two to a unit and with their noise beside each other's contraction: 0.92 to 1.02 of samples of an even number of steps.)
+  constexpr int kPartOfTheChip = 160, kShortRound = 1024;
+  if (cut.tiles == 0 && n <= (rows <= kShortRound ? kBigRound : kPartOfTheChip)) blocks = false;
   // Workgroups that go from tile to tile take equal numbers of them: for tiles of one length.
   return {cut, blocks, blocks && one_length && ga.B <= 64 ? std::min(n_big, kBigRound) : n_big};
 }

@@ -417,7 +417,7 @@ def test_joined_tiles(dtype, n, B, T):
 
 # Large tiles on part of the chip alone stay on 16-row steps, more of them take whole k-blocks: the same bits.
 @pytest.mark.parametrize("dtype", [si.BF16, si.F16])
-@pytest.mark.parametrize("B,T", [(4, 160), (3, 250), (65, 64)])
+@pytest.mark.parametrize("B,T", [(7, 160), (5, 250), (65, 64)])
 def test_whole_k_blocks_against_steps(dtype, B, T):
     from paper_2311_11822_amd import binding as dp
     side = 1016
