@@ -185,11 +185,11 @@ int64_t clipped_grad_mid_tiles(int d, int p) {
   return ((int64_t)d + MidTile::BM - 1) / MidTile::BM * (((int64_t)p + MidTile::BN - 1) / MidTile::BN);
 }
 
-// The tiles of the last round go to sub-tiles where they fit one round of 128 x 128.  K = 4096, alone: 64 tiles 94 us
-// as they are, 51 as sub-tiles; 128 tiles 96 and 74; 160 tiles 98 and 114.  All tiles do where that takes fewer
+// The tiles of the last round go to sub-tiles where they fit one round of 128 x 128.  K = 4096, alone: 64 tiles 91 us
+// as they are, 46 as sub-tiles; 128 tiles 98 and 73; 160 tiles 102 and 112.  All tiles do where that takes fewer
 // rounds' time, because of the layers' edges (which sub-tiles leave out).
-// Up to kTailMax tiles are cut into 64 x 64: 16 tiles of K = 4096 take 25 us so, 44 us in 128 x 128; 32 tiles 32 and 46; 48
-// tiles 52 and 42; 64 tiles 61 and 42.
+// Up to kTailMax tiles are cut into 64 x 64: 16 tiles of K = 4096 take 27 us so, 41 us in 128 x 128; 32 tiles 37 and 42; 48
+// tiles 55 and 43; 64 tiles 64 and 46.
 // Short contractions (rows: of all samples, each rounded up to 32, as these lines were measured) are bound by the
 // epilogue, which a large tile has a compute unit to itself for: 128 x 128, two to a unit, unless large ones come in whole
 // rounds.  One sample: two layers 3744 x 2352 33.2 us mixed, 24.7 on 128 x 128 (before: 29); 17 of 33 tokens 76 and 69;
@@ -203,12 +203,19 @@ int64_t clipped_grad_mid_tiles(int d, int p) {
 // twice as often.  Gradients, us, large and 128 x 128 of five stages, 128 x 128 of three: one sample of 32 tokens, 16 layers of
 // width 1472 100, 79, with noise 140, 107, in 16 bits 69, 53; four of 32, 24 layers of width 768 44, 40, with noise 60, 53; eight
 // 56, 51 and 73, 66; eight of 32, 16 layers of width 808 52, 46 and 66, 60; above the line 16 x 32, width 768 84, 83; eight,
-// width 1472 144, 166.
+// width 1472 144, 166.  (The kernels have changed since: of 874 launches of 40 to 528 large tiles and 32 to 512 rows, with
+// noise, without and in 16 bits, what these lines take is within 5 % of the fastest of the three in all but the next rule's and 11.)
+//
+// A single round of large tiles is through before small ones that take a second round of 768.  From 257 rows on, large and three to a
+// unit, us: 16 x 32 tokens, 24 layers 768 x 768 with noise 31.1, 38.4; 8 x 64, 16 of 808 x 808 31.6, 39.8; 8 x 64, one 3744 x 3744 without
+// noise 26.6, 31.1; of 208 to 240 tiles 6 to 21 %.  Up to 256 rows, with noise on an eighth, 20 % slower to 3 % faster; 8 x 64,
+// three 2048 x 2048 (192 tiles, 768 small ones) 29.8, 26.8.
 GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows, bool whole_lines, bool out16) {
-  constexpr int kTailMax = 32, kShortRows = 512, kBriefMost = 1 << 20;         // (of these launch workgroups of 256 threads)
+  constexpr int kTailMax = 32, kShortRows = 512, kOneRoundRows = 256, kBriefMost = 1 << 20;         // (of these launch workgroups of 256 threads)
   constexpr int64_t kBriefRound = 768;
   int tail = n % kBigRound;
   const bool crowded = n_mid > kMidRound && rows <= kShortRows && n <= kBriefMost;
+  if (n <= kBigRound && n_mid > kBriefRound && rows > kOneRoundRows) return {0, TAIL_SIDE, false};
   if (n > kTailMax && tail != 0 && rows * (n < kBigRound ? 1 : n / kBigRound) <= kShortRows) return {n, MID_SIDE, crowded};
   if (crowded) {
     const int64_t blocks = (rows + BigTile::BK - 1) / BigTile::BK;

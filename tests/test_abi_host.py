@@ -241,7 +241,8 @@ def test_gradient_tile_order_of_cut_tiles(dp, d, p, n_tail, side):
 @pytest.mark.parametrize("n,side,B,T,want", [
     (8, 2040, 3, 64, (512, 256, 1, 0)), (11, 2040, 64, 64, (704, 256, 1, 0)), (8, 2040, 65, 64, (512, 512, 1, 0)),
     (9, 1016, 4, 160, (144, 144, 0, 0)), (12, 1016, 4, 160, (192, 192, 0, 0)), (9, 1016, 7, 160, (144, 144, 0, 0)),
-    (12, 1016, 7, 160, (192, 192, 1, 0)), (16, 1016, 4, 256, (256, 256, 0, 0)), (17, 1024, 4, 256, (256, 256, 1, 16)), (8, 2040, 16, 48, (512, 512, 0, 0)),
+    (12, 1016, 7, 160, (192, 192, 1, 0)), (16, 1016, 4, 256, (256, 256, 0, 0)), (17, 1024, 4, 256, (256, 256, 1, 16)),
+    (12, 1024, 8, 64, (0, 0, 1, 192)), (13, 1024, 8, 64, (208, 208, 0, 0)), (13, 1024, 4, 64, (0, 0, 1, 208)), (8, 2040, 16, 48, (512, 512, 0, 0)),
     (2, 512, 3, 64, (0, 0, 1, 8)), (1, 1536, 5, 64, (0, 0, 1, 36))])
 def test_launches_of_a_gradient(dp, n, side, B, T, want):
     plan = dp.dp_clipped_grad_launches([(16, 16, T, side, side, 0)] * n, dp.DP_BF16, B)
