@@ -79,7 +79,8 @@ def summarize(dirs) -> None:
                     extra = ""
                     if "TCC_HIT_sum" in vals[k] and vals[k]["TCC_HIT_sum"] + vals[k]["TCC_MISS_sum"] > 0:
                         extra += f"; L2 hit rate = {vals[k]['TCC_HIT_sum'] / (vals[k]['TCC_HIT_sum'] + vals[k]['TCC_MISS_sum']):.3f}"
-                    if "SQ_WAVE_CYCLES" in vals[k] and "big_kernel" in k and vals[k].get("SQ_WAVES", 0) / n >= 1024:
+                    one_a_unit = any(x in k for x in ("ghost_big_kernel", "clipped_grad_big_kernel", "clipped_grad_blocks_kernel"))
+                    if "SQ_WAVE_CYCLES" in vals[k] and one_a_unit and vals[k].get("SQ_WAVES", 0) / n >= 1024:
                         resident = 2048 if "clipped_grad" in k else 1024
                         extra += f"; shader clock = {4.0 * vals[k]['SQ_WAVE_CYCLES'] / (resident * dur[k]):.2f} GHz"
                     print(f"{k}: launches = {n}, avg duration = {dur[k] / n / 1e3:.1f} us, per launch: {line}{extra}")
