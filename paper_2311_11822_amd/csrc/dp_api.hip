@@ -1393,7 +1393,7 @@ int64_t dp_clipped_grad_tile_order(int d_in, int d_out, int32_t* tile_row0, int3
   if (n > INT32_MAX / 2) return -1;
   // the split of a long contraction over rows of whole lines, and of up to 2048 ragged rows: the call knows neither the rows
   // nor neighbours
-  const GradTail cut = clipped_grad_tail((int)n, clipped_grad_mid_tiles(d_in, d_out), INT32_MAX, true, false);
+  const GradTail cut = clipped_grad_tail((int)n, clipped_grad_mid_tiles(d_in, d_out), INT32_MAX, true, false, false);
   const int n_main = (int)n - cut.tiles;
   const int tiles_m = (d_in + 255) / 256, tiles_n = (d_out + 255) / 256;
   auto put = [&](int64_t b, int t) {

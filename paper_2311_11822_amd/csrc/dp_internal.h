@@ -221,13 +221,14 @@ dp_status launch_ghost_pair_group(const GroupArgs& ga, float* sqnorm, const Norm
 int clipped_grad_big_tiles(int d, int p);
 int64_t clipped_grad_mid_tiles(int d, int p);
 // Of a launch of n large tiles whose layers hold n_mid tiles of 128 x 128 and contract over up to `rows` rows, how many
-// (the last ones) are cut into side x side sub-tiles (whole_lines: every row of every operand is whole 128-byte lines); brief: on the 128 x 128 tiles of short contractions.
+// (the last ones) are cut into side x side sub-tiles (whole_lines: every row of every operand is whole 128-byte lines; long_off_sectors: rows of
+// some operand begin off 64-byte pieces of memory, and no sample is short); brief: on the 128 x 128 tiles of short contractions.
 constexpr int kGradMidSide = 2, kGradTailSide = 4;
 struct GradTail {
   int tiles, side;
   bool brief;
 };
-GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows, bool whole_lines, bool out16);
+GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows, bool whole_lines, bool long_off_sectors, bool out16);
 // The launches of a group on these tiles.  blocks: in whole k-blocks (tn_weighted.h); workgroups: of the tiles that are not cut,
 // each one or more of them.
 struct GradLaunches {

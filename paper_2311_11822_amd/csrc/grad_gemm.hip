@@ -189,7 +189,11 @@ int64_t clipped_grad_mid_tiles(int d, int p) {
 // as they are, 46 as sub-tiles; 128 tiles 98 and 73; 160 tiles 102 and 112.  All tiles do where that takes fewer
 // rounds' time, because of the layers' edges (which sub-tiles leave out).
 // Up to kTailMax tiles are cut into 64 x 64: 16 tiles of K = 4096 take 27 us so, 41 us in 128 x 128; 32 tiles 37 and 42; 48
-// tiles 55 and 43; 64 tiles 64 and 46.
+// tiles 55 and 43; 64 tiles 64 and 46.  More than kTailUnits have two workgroups on some unit, which load half as fast each; where
+// rows begin off 64-byte pieces of memory, 128 x 128 tiles are faster then from 4096 rows on: 39 x 1408 tokens, 17 layers 168 x 168 663
+// and 481, 4 x 1024, two 1000 x 1000 44.1 and 38.7, 5 x 3540, 24 of 232 x 232 234 and 213; not of rows on 64-byte pieces (4 x 1024, 19 of 224 x
+// 224 35.8 and 37.8), of 2048 rows with noise (0.94 to 1.05 of the time) or of short samples (64 x 100, 17 of 168 x 168 63.6 and 80.2; 16 x 300 45.9, 48.4;
+// 32 x 384 111.4, 110.7).
 // Short contractions (rows: of all samples, each rounded up to 32, as these lines were measured) are bound by the
 // epilogue, which a large tile has a compute unit to itself for: 128 x 128, two to a unit, unless large ones come in whole
 // rounds.  One sample: two layers 3744 x 2352 33.2 us mixed, 24.7 on 128 x 128 (before: 29); 17 of 33 tokens 76 and 69;
@@ -210,8 +214,9 @@ int64_t clipped_grad_mid_tiles(int d, int p) {
 // unit, us: 16 x 32 tokens, 24 layers 768 x 768 with noise 31.1, 38.4; 8 x 64, 16 of 808 x 808 31.6, 39.8; 8 x 64, one 3744 x 3744 without
 // noise 26.6, 31.1; of 208 to 240 tiles 6 to 21 %.  Up to 256 rows, with noise on an eighth, 20 % slower to 3 % faster; 8 x 64,
 // three 2048 x 2048 (192 tiles, 768 small ones) 29.8, 26.8.
-GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows, bool whole_lines, bool out16) {
-  constexpr int kTailMax = 32, kShortRows = 512, kOneRoundRows = 256, kBriefMost = 1 << 20;         // (of these launch workgroups of 256 threads)
+GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows, bool whole_lines, bool long_off_sectors, bool out16) {
+  constexpr int kTailMax = 32, kTailUnits = 16, kTailRows = 4096, kShortRows = 512, kOneRoundRows = 256;
+  constexpr int kBriefMost = 1 << 20;                    // of these launch workgroups of 256 threads
   constexpr int64_t kBriefRound = 768;
   int tail = n % kBigRound;
   const bool crowded = n_mid > kMidRound && rows <= kShortRows && n <= kBriefMost;
@@ -232,7 +237,8 @@ GradTail clipped_grad_tail(int n, int64_t n_mid, int64_t rows, bool whole_lines,
   const int64_t mid_cost = whole_lines || rows <= 2048 ? 6 : rows <= 8192 ? 8 : 10;
   const int64_t mixed = (int64_t)(n / kBigRound) * 10 + (tail ? mid_cost : n % kBigRound ? 10 : 0);
   if (mid_cost * ((n_mid + kMidRound - 1) / kMidRound) < mixed) tail = n;
-  return {tail, tail <= kTailMax ? TAIL_SIDE : MID_SIDE, false};
+  const int small = long_off_sectors && rows >= kTailRows ? kTailUnits : kTailMax;
+  return {tail, tail <= small ? TAIL_SIDE : MID_SIDE, false};
 }
 
 // The kernels of tn_weighted.h, whose samples take whole k-blocks of 32 rows, where the rows that are zeros cost less than 16x16x32
@@ -247,19 +253,22 @@ bool whole_blocks(int B, int T) {
 }
 
 GradLaunches clipped_grad_launches(const GroupArgs& ga, bool out16) {
+  constexpr int kLongSample = 384;                       // tokens (clipped_grad_tail)
   const int n = ga.total_blocks;
   int64_t n_mid = 0, rows = 0;
-  bool whole_lines = true, one_length = true, blocks = true;
+  bool whole_lines = true, off_sectors = false, no_short = true, one_length = true, blocks = true;
   for (int j = 0; j < ga.n_layers; ++j) {
     const GroupLayer& ly = ga.layer[j];
     n_mid += clipped_grad_mid_tiles(ly.d_in, ly.d_out);
     whole_lines = whole_lines && ly.d_in % 64 == 0 && ly.d_out % 64 == 0;
+    off_sectors = off_sectors || ly.d_in % 32 != 0 || ly.d_out % 32 != 0;
+    no_short = no_short && ly.T >= kLongSample;
     one_length = one_length && ly.T == ga.layer[0].T;
     blocks = blocks && whole_blocks(ga.B, ly.T);
     const int64_t r = (int64_t)ga.B * ((ly.T + BigTile::BK - 1) / BigTile::BK) * BigTile::BK;
     rows = r > rows ? r : rows;
   }
-  const GradTail cut = clipped_grad_tail(n, n_mid, rows, whole_lines, out16);
+  const GradTail cut = clipped_grad_tail(n, n_mid, rows, whole_lines, off_sectors && no_short, out16);
   const int n_big = n - cut.tiles;
   // Large tiles on part of the chip alone (from 129 on: fewer are cut) are not held by its power, and 16-row steps take fewer clocks;
   // nor is a single round of a short contraction.  Whole k-blocks to steps, ratios of times with noise and without: up to 1024 rows 144 and
