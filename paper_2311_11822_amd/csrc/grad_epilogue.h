@@ -149,12 +149,14 @@ __device__ __forceinline__ void wave_lds_fence() {
 }
 
 // acc * held (+ old value) (+ noise of eq. (1)) -> out, in fp32 or the operands' 16-bit type; lds: the wave's Piece::BYTES;
-// stream: by streaming stores (not of accumulating launches); ready: called before the first store.
+// ready: called before the first store.
 // Noise: same values as the separate pass, which indexes the generator by global element too; requires layer_off and d_out
 // to be multiples of 4, as a lane's four columns are one block of the generator.
-template <bool F16, bool NOISE, bool OUT16, bool ACCUMULATE, class Piece, class Ready>
-__device__ __forceinline__ void store_rows(const Piece& piece, const OldRows<Piece, OUT16>& old, bool stream, float held, unsigned lds,
-                                           float* out32, int d, int p, const TileNoise& na, int lane, Ready ready) {
+enum Rows { kAdd, kStream, kKeep };                      // old values added; by streaming stores; through the caches
+template <bool F16, bool NOISE, bool OUT16, Rows ROWS_GO, class Piece, class Ready>
+__device__ __forceinline__ void store_rows(const Piece& piece, const OldRows<Piece, OUT16>& old, float held, unsigned lds, float* out32,
+                                           int d, int p, const TileNoise& na, int lane, Ready ready) {
+  constexpr bool ACCUMULATE = ROWS_GO == kAdd;
   const int row0 = piece.row0, col0 = piece.col0;
   piece.put(lds, lane);
   wave_lds_fence();
@@ -235,53 +237,50 @@ __device__ __forceinline__ void store_rows(const Piece& piece, const OldRows<Pie
         else
           w[u][k] = __float_as_uint(v[n + u][k]);
       }
-    auto store = [&](auto streaming) {
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (row + (n + u) * ROWS < d && col < p) {
-          u32x4v* to = reinterpret_cast<u32x4v*>(reinterpret_cast<char*>(out32) + (at + (n + u) * step) * (OUT16 ? 2 : 4));
-          if constexpr (decltype(streaming)::value)
-            __builtin_nontemporal_store(w[u], to);
-          else
-            *to = w[u];
-        }
-    };
-    if (!ACCUMULATE && stream) {
-      store(std::true_type{});
-      asm volatile("");                                  // or the two become one cached store
-    } else {
-      store(std::false_type{});
-    }
+    for (int u = 0; u < U; ++u)
+      if (row + (n + u) * ROWS < d && col < p) {
+        u32x4v* to = reinterpret_cast<u32x4v*>(reinterpret_cast<char*>(out32) + (at + (n + u) * step) * (OUT16 ? 2 : 4));
+        if constexpr (ROWS_GO == kStream)
+          __builtin_nontemporal_store(w[u], to);
+        else
+          *to = w[u];
+      }
     __builtin_amdgcn_sched_barrier(0);
   }
 }
 
-// COUNT pieces of the wave; ready: called before the first store.
+// COUNT pieces of the wave; ready: called before the first store.  The three forms lie one behind the other: with a branch at every group of
+// stores a wave fetches both forms' code (seven 1024 x 1024 layers, 4 x 256 tokens 20.6 us with one form, 20.8 so).
 template <int COUNT, bool F16, bool NOISE, bool OUT16, class PieceOf, class Ready>
 __device__ __forceinline__ void store_pieces(PieceOf piece, bool accumulate, bool stream, float held, unsigned lds, float* out32, int d, int p,
                                              const TileNoise& na, int lane, Ready ready) {
   using Piece = decltype(piece(0));
   // With noise in fp32 a 256 x 256 tile has no registers for two pieces', and 128 x 128 ones take 1 % more.
   constexpr int AHEAD = COUNT % 2 == 0 && Piece::H == 16 && (OUT16 || !NOISE) ? 2 : 1;
-  auto store_all = [&](auto acc_tag) {
-    constexpr bool ACCUMULATE = decltype(acc_tag)::value;
+  auto store_all = [&](auto rows) {
+    constexpr Rows GO = decltype(rows)::value;
 #pragma unroll
     for (int i = 0; i < COUNT; i += AHEAD) {
       OldRows<Piece, OUT16> old[AHEAD];
 #pragma unroll
       for (int j = 0; j < AHEAD; ++j)
-        if (ACCUMULATE) old[j].load(out32, piece(i + j).row0, piece(i + j).col0, d, p, lane);
+        if (GO == kAdd) old[j].load(out32, piece(i + j).row0, piece(i + j).col0, d, p, lane);
 #pragma unroll
       for (int j = 0; j < AHEAD; ++j)
-        store_rows<F16, NOISE, OUT16, ACCUMULATE>(piece(i + j), old[j], stream, held, lds, out32, d, p, na, lane, [&]() {
+        store_rows<F16, NOISE, OUT16, GO>(piece(i + j), old[j], held, lds, out32, d, p, na, lane, [&]() {
           if (i + j == 0) ready();
         });
     }
   };
-  if (accumulate)
-    store_all(std::true_type{});
-  else
-    store_all(std::false_type{});
+  if (accumulate) {
+    store_all(std::integral_constant<Rows, kAdd>{});
+  } else if (stream) {
+    store_all(std::integral_constant<Rows, kStream>{});
+    asm volatile("");                                    // or these two become one, through the caches
+  } else {
+    store_all(std::integral_constant<Rows, kKeep>{});
+  }
 }
 
 }  // namespace dpbk

@@ -165,8 +165,9 @@ clipped_grad_tail_kernel(const GroupArgs ga, const float* __restrict__ C_all, in
   if (NOISE) tn = load_tile_noise(na, l);
   __syncthreads();                                   // the last fragments are read
   using Piece = WavePiece16<1, 32, 2>;
+  // streaming: at most 32 tiles of a launch, 1.00 of the time either way
   store_pieces<1, F16, NOISE, OUT16>([&](int) { return Piece{&acc[0][0], m0 + 32 * (wave >> 1), n0 + 32 * (wave & 1)}; },
-                                     ga.accumulate, ly.stream, held, lds0 + wave * Piece::BYTES, ly.out, ly.d_in, ly.d_out, tn,
+                                     ga.accumulate, true, held, lds0 + wave * Piece::BYTES, ly.out, ly.d_in, ly.d_out, tn,
                                      threadIdx.x & 63, []() {});
 }
 

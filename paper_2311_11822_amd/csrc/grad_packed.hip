@@ -110,6 +110,8 @@ template <class S, bool F16, bool NOISE>
 __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int tile, int B, bool accumulate,
                                             const float* C, const NoiseArgs& na, unsigned lds0) {
   const int T = ly.T, d = ly.d_in, p = ly.d_out;
+  int stream = ly.stream;
+  asm volatile("" : "+s"(stream));                       // read with the rest of the layer, not in front of the first store
   const int tiles_n = (p + S::BN - 1) / S::BN;
   const int m0 = (tile / tiles_n) * S::BM, n0 = (tile % tiles_n) * S::BN;
   const int rows = B * T, nkb = (rows + BK - 1) / BK;
@@ -343,7 +345,7 @@ __device__ __forceinline__ void packed_tile(const GroupLayer& ly, int layer, int
   using Piece = WavePiece16<NY, 32, S::XN>;
   static_assert(Piece::BYTES * 4 <= NSTAGE * S::STAGE_BYTES && S::XM == 2, "a region for each wave");
   store_pieces<S::XN / (2 * NY), F16, NOISE, false>(
-      [&](int y) { return Piece{&acc[0][2 * NY * y], m0 + wm, n0 + wn + 32 * NY * y}; }, accumulate, ly.stream, 1.f,
+      [&](int y) { return Piece{&acc[0][2 * NY * y], m0 + wm, n0 + wn + 32 * NY * y}; }, accumulate, stream, 1.f,
       lds0 + wave * Piece::BYTES, ly.out, d, p, tn, lane, []() {});
 }
 

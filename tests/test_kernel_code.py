@@ -107,8 +107,8 @@ def test_waits_of_matrix_instructions(tmp_path):
     assert not faults, f"{len(faults)} pairs: " + "; ".join(map(str, faults[:8]))
 
 
-# The gradient kernels store rows in three forms: old values added (cached), streaming and cached.  The compiler makes one cached
-# form of the last two unless it is kept from it.
+# The gradient kernels store rows in three forms: old values added (cached), streaming and cached (64 x 64 tiles: the first two).  The
+# compiler makes one cached form of the last two unless it is kept from it.
 @pytest.mark.skipif(not os.path.exists(OBJDUMP) or not os.path.exists(LIB), reason="needs the built library and a disassembler")
 def test_gradient_kernels_stream_and_do_not(tmp_path):
     kernels = 0
@@ -117,7 +117,8 @@ def test_gradient_kernels_stream_and_do_not(tmp_path):
             stores = [line for line in lines if "global_store_dwordx4" in line]
             streaming = sum(bool(re.search(r"\bnt\b", line)) for line in stores)
             kernels += 1
-            assert streaming > 0 and len(stores) == 3 * streaming, (name, streaming, len(stores))
+            forms = 2 if "tail" in name else 3
+            assert streaming > 0 and len(stores) == forms * streaming, (name, streaming, len(stores))
     assert kernels == 8 * 7 + 4
 
 
