@@ -594,7 +594,7 @@ dp_status make_noise(const dp_layer* layers, int L, const uint64_t* grad_offset,
 }
 
 // Whether a layer's rows leave the matrix-core gradient kernels by streaming stores, past the caches; in a call that writes `bytes`,
-// round_bytes of them in each of a launch's `rounds` of 256 large tiles.  Streaming to cached, ratios of times (2400 measurements,
+// round_bytes of them in each of a launch's `rounds` of 256 large tiles.  Streaming to cached, ratios of times (3200 measurements,
 // groups of them): up to 32 MB, what the L2s hold together, 0.93 to 1.02, also with a pass behind it that reads the gradient.  Beyond it
 //  * without noise a gradient is there to be read again (by the noise, the next micro-batch, a reduction), and the memory-side cache
 //    holds it up to some 200 MB: alone 0.99 to 1.00, with what reads it 1.01 to 1.07; above 0.94 to 1.02;
@@ -602,15 +602,17 @@ dp_status make_noise(const dp_layer* layers, int L, const uint64_t* grad_offset,
 //    1.13 (2 x 32 tokens, 39 layers 1016 x 1016 1.61); with noise short contractions wait for the stores, the longer the more
 //    the compute units store at once: 128 to 384 rows 0.96 to 1.35; steps of 576 rows and more 0.83 to 1.02 in rounds of up to 44 MB (few
 //    or ragged tiles), in fuller ones 1.02 to 1.15 of 640 and 768 rows, of 1024 to 1536 rows 1.01 to 1.12 of a single round and 0.92 to 1.01 of
-//    more; from 2048 rows on 0.85 to 1.04;
+//    more; from 2048 rows on 0.85 to 1.04; of calls that no cache holds, above 256 MB, 0.82 to 1.07 but for 64 rows, 0.81 to 1.30;
+//  * packed rows, which take longer for what they write: above 256 MB 0.84 to 1.11, on average 0.97; below, rows of no whole lines with
+//    noise 0.93 to 1.06, of 64 rows 1.01 to 1.34;
 //  * whole lines with noise 0.94 to 1.02.
 // An accumulating launch has just read what it writes: 1.00 either way, cached.
-bool rows_stream(const GroupLayer& ly, int B, int64_t bytes, double round_bytes, double rounds, bool noise, bool out16) {
-  constexpr int64_t kInL2 = 32 << 20, kPartOfARound = 44 << 20, kInMemorySideCache = 200 << 20;
+bool rows_stream(const GroupLayer& ly, int B, bool packed, int64_t bytes, double round_bytes, double rounds, bool noise, bool out16) {
+  constexpr int64_t kInL2 = 32 << 20, kPartOfARound = 44 << 20, kInMemorySideCache = 200 << 20, kInNone = 256 << 20;
   const bool whole_lines = ly.d_out % (out16 ? 64 : 32) == 0 && reinterpret_cast<uintptr_t>(ly.out) % 128 == 0;
-  if (bytes <= kInL2) return true;
+  if (bytes <= kInL2 || (packed && bytes > kInNone)) return true;
   if (!noise) return whole_lines && bytes > kInMemorySideCache;
-  const int short_rows = round_bytes <= kPartOfARound ? 512 : rounds < 1.4 ? 1536 : 768;
+  const int short_rows = packed || bytes > kInNone ? 128 : round_bytes <= kPartOfARound ? 512 : rounds < 1.4 ? 1536 : 768;
   return whole_lines || (int64_t)B * ly.T > short_rows;
 }
 
@@ -709,7 +711,7 @@ dp_status launch_grads(const dp_layer* layers, int L, dp_dtype dt, int B, const 
       for (int j = 0; j < ga.n_layers; ++j) launch_bytes += grad_bytes(ga.layer[j].d_in, ga.layer[j].d_out);
       const double rounds = std::max(1.0, (kernel == kGradBig ? (double)blocks : launch_bytes / 262144.0) / 256);
       for (int j = 0; j < ga.n_layers; ++j)
-        ga.layer[j].stream = !accumulate && rows_stream(ga.layer[j], B, bytes, launch_bytes / rounds, rounds, fused, out16);
+        ga.layer[j].stream = !accumulate && rows_stream(ga.layer[j], B, kernel == kGradPacked, bytes, launch_bytes / rounds, rounds, fused, out16);
       dp_status st = kernel == kGradBig      ? launch_clipped_grad_big_group(ga, C, in_kernel, s, out16)
                      : kernel == kGradPacked ? launch_grad_packed_group(ga, C, in_kernel, s)
                                              : launch_clipped_grad_group(ga, C, s);

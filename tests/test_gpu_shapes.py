@@ -440,10 +440,11 @@ def test_whole_k_blocks_against_steps(dtype, B, T):
         assert float((got.double() - want).norm()) <= 3e-6 * float(want.norm())
 
 
-# Launches on either side of the lines between streaming and cached stores (rows of whole 128-byte lines and others, 32 and 200 MB, with
-# noise and without, 512 rows): the bits of the layers alone, on all tiles, packed rows among them.
+# Launches on either side of the lines between streaming and cached stores (rows of whole 128-byte lines and others, 32, 200 and 256 MB, with
+# noise and without, 128 and 512 rows): the bits of the layers alone, on all tiles, packed rows among them.
 @pytest.mark.parametrize("n,side,B,T", [(7, 1016, 4, 64), (9, 1016, 4, 64), (9, 1016, 9, 64), (9, 1024, 4, 64), (47, 1024, 2, 64),
-                                        (48, 1032, 2, 64), (48, 1088, 2, 64), (9, 1016, 64, 2), (9, 1024, 64, 2), (32, 512, 4, 33)])
+                                        (48, 1032, 2, 64), (48, 1088, 2, 64), (9, 1016, 64, 2), (9, 1016, 65, 2), (9, 1024, 64, 2), (48, 1192, 20, 2), (48, 1192, 2, 64), (48, 1192, 5, 32),
+                                        (32, 512, 4, 33)])
 def test_gradients_of_large_and_small_launches(n, side, B, T):
     from paper_2311_11822_amd import binding as dp
     gen = torch.Generator(device="cuda").manual_seed(n * side)
